@@ -415,7 +415,9 @@ class NetMax:
         """Row-major device tensor [M, cols] of x (current), v or g; cols defaults to ld (padding as zeros)."""
         import torch
         cols = self.ld if cols is None else cols
-        out = torch.zeros((self.M, cols), dtype=torch.float32, device=self.device)
+        out = torch.empty((self.M, cols), dtype=torch.float32, device=self.device)
+        if cols > self.D:
+            out[:, self.D:].zero_()                            # netmax_unpack writes the first D columns of every row
         self._join()
         netmax_unpack(self.ctx, self._buffer(name), out, cols)
         self._join()

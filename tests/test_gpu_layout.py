@@ -1,0 +1,35 @@
+"""Layout conversion at its edges: rows that do not start at multiples of 16 bytes, ragged last tiles, tiles of padding only."""
+import pytest
+import torch
+
+import paper_2009_05766_amd as nm
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("M,D,pad_tiles,row_ld,shift", [
+    (2, 1, 0, 1, 0),                       # one column
+    (3, 2048, 0, 2048, 0),                 # exactly one tile
+    (5, 2049, 1, 2052, 0),                 # one column in the last tile, a tile of padding behind it, rows longer than D
+    (4, 3 * 2048 - 4, 0, 3 * 2048, 0),     # aligned rows, a ragged last tile
+    (7, 5003, 2, 5003, 0),                 # rows at odd addresses
+    (3, 4096, 0, 4096, 1),                 # a base pointer that is no multiple of 16 bytes
+])
+def test_pack_and_unpack_move_every_element(M, D, pad_tiles, row_ld, shift):
+    T = nm.NETMAX_TILE
+    tiles = -(-D // T) + pad_tiles
+    ld = tiles * T
+    net = nm.NetMax(M=M, D=D, ld=ld, model=nm.NETMAX_FLAT, lr=0.1, rho=0.01, seed=1, P=(1.0 - torch.eye(M, dtype=torch.float64).numpy()) / (M - 1))
+    gen = torch.Generator(device="cuda").manual_seed(D)
+    rows = torch.randn(M * row_ld + shift, generator=gen, device="cuda")[shift:].view(M, row_ld)
+    tiled = torch.full((M * ld,), 7.0, device="cuda")
+    nm.netmax_pack(net.ctx, rows, row_ld, tiled)
+    want = torch.zeros((M, ld), device="cuda")
+    want[:, :D] = rows[:, :D]
+    assert torch.equal(tiled.view(tiles, M, T).permute(1, 0, 2).reshape(M, ld), want)
+    back = torch.full((M * row_ld + shift,), 7.0, device="cuda")[shift:].view(M, row_ld)
+    nm.netmax_unpack(net.ctx, tiled, back, row_ld)
+    assert torch.equal(back[:, :D], rows[:, :D]) and bool((back[:, D:] == 7.0).all())       # columns from D on are left alone
+    net.set("x", rows)
+    assert torch.equal(net.get("x"), want) and torch.equal(net.get("x", D), want[:, :D])
+    net.close()
