@@ -2,20 +2,13 @@
 // the stochastic gradient of Algorithm 2's first-step update, for all workers at once.  Every GEMM is
 // grouped, one group per worker, because each worker multiplies its own batch with its own weights.
 //
-// This file holds the general tiled kernels (any shape, fp32 matrix instructions).  With bf16 operands the inputs of
-// every product are rounded to bfloat16 first and accumulated in fp32.
-#include "bf16.h"
-#include "kernels.h"
-#include "layout.h"
+// This file holds the sequence of a gradient's launches, the forward pass of layers with few outputs, and the loss and bias
+// gradients of what the more specialised kernels leave.  With bf16 operands the inputs of every product are rounded to
+// bfloat16 first and accumulated in fp32.
 #include "softmax_xent.h"
-
-#include <type_traits>
+#include "tile.h"
 
 namespace netmax {
-
-constexpr int GEMM_THREADS = 256;
-typedef float gemm_acc __attribute__((ext_vector_type(16)));
-constexpr int MAX_BATCH = 1024;
 
 // Where the input of a layer comes from: the gathered data rows (fp32 or bfloat16 storage) for the first
 // layer, else the previous layer's activation (fp32, or its stored bfloat16 copy when the operands are bf16).
@@ -30,30 +23,15 @@ template <int KIND> __device__ __forceinline__ float operand(float x)
     else return x;
 }
 
-// Input of layer l for worker g, batch row r, feature k.  bits<KIND>() is one unconditional load (the caller
-// passes coordinates inside the operand), value<KIND>() turns what was loaded into the multiplicand.
+// Input of a layer: element `index` of it as loaded, and as the multiplicand.
 struct LayerInput {
     const void *feats; const int64_t *row0; const int32_t *idx; const float *act_prev;
     const uint16_t *act_prev_bf16;
     int B; int64_t din; int kind;
-    // rows: the worker's batch as absolute data rows (row0[g] + idx[g][b]), staged in LDS by the kernel
-    template <int KIND> __device__ __forceinline__ uint32_t bits(int g, int r, int64_t k, const int64_t *rows) const
-    {
-        if constexpr (KIND == IN_GATHER_F32) return ((const uint32_t *)feats)[rows[r] * din + k];
-        else if constexpr (KIND == IN_GATHER_BF16) return ((const uint16_t *)feats)[rows[r] * din + k];
-        else if constexpr (KIND == IN_ACT_F32) return ((const uint32_t *)act_prev)[((size_t)g * B + r) * din + k];
-        else return act_prev_bf16[((size_t)g * B + r) * din + k];
-    }
     template <int KIND> __device__ __forceinline__ float value(uint32_t u) const
     {
         if constexpr (KIND == IN_GATHER_BF16 || KIND == IN_ACT_BF16) return as_float(u << 16);
         else return as_float(u);
-    }
-    // the same element as bits(): element index of feature 0 of batch row r, and the load of index + k
-    template <int KIND> __device__ __forceinline__ int64_t row_index(int g, int r, const int64_t *rows) const
-    {
-        if constexpr (KIND == IN_GATHER_F32 || KIND == IN_GATHER_BF16) return rows[r] * din;
-        else return ((int64_t)g * B + r) * din;
     }
     template <int KIND> __device__ __forceinline__ uint32_t load_index(int64_t index) const
     {
@@ -64,40 +42,12 @@ struct LayerInput {
     }
 };
 
-// tiled_offset() with one 32 x 32 -> 64 bit multiply-add: j + (((j >> 11) (M - 1) + i) << 11); needs j < 2^43
-__device__ __forceinline__ size_t tiled_offset_quick(int M, int i, int64_t j)
-{
-    const uint64_t t = (uint64_t)(uint32_t)(j >> TILE_SHIFT) * (uint32_t)(M - 1) + (uint32_t)i;
-    return (size_t)j + (size_t)(t << TILE_SHIFT);
-}
-
-// Z = A W + b, optional ReLU.  rows = batch, cols = dout, K = din.
+// Z = A W + b, optional ReLU.
 struct FwdProblem {
-    static constexpr bool A_K_FAST = true, B_C_FAST = true;
     LayerInput in; const float *X; int64_t woff, din, dout; int M, B, relu; float *out;
     uint16_t *out_bf16, *out_bf16_t;     // optional bfloat16 copies: [B][dout] and transposed [dout][B]
-    __device__ int rows() const { return B; }
-    __device__ int64_t cols() const { return dout; }
-    __device__ int64_t depth() const { return din; }
-    __device__ const LayerInput &input() const { return in; }
-    template <int AK> __device__ uint32_t a_bits(int g, int64_t r, int64_t k, const int64_t *rows) const
-    {
-        return in.bits<AK>(g, (int)r, k, rows);
-    }
     template <int AK> __device__ float a_val(uint32_t u) const { return in.value<AK>(u); }
-    __device__ uint32_t b_bits(int g, int64_t k, int64_t c) const
-    {
-        return ((const uint32_t *)X)[tiled_offset(M, g, woff + k * dout + c)];
-    }
     template <int AK> __device__ float b_val(uint32_t u) const { return operand<AK>(as_float(u)); }
-    // the operands as base + k * step: what does not depend on the contraction index is computed once per thread
-    static constexpr bool A_AFFINE = true;
-    template <int AK> __device__ int64_t a_base(int g, int64_t r, const int64_t *rows) const { return in.row_index<AK>(g, (int)r, rows); }
-    __device__ int64_t a_step() const { return 1; }
-    template <int AK> __device__ uint32_t a_at(int64_t index) const { return in.load_index<AK>(index); }
-    __device__ int64_t b_base(int g, int64_t c) const { return woff + c; }
-    __device__ int64_t b_step() const { return dout; }
-    __device__ uint32_t b_at(int g, int64_t index) const { return ((const uint32_t *)X)[tiled_offset_quick(M, g, index)]; }
     __device__ void store(int g, int64_t r, int64_t c, float acc) const
     {
         float z = acc + X[tiled_offset(M, g, woff + din * dout + c)];
@@ -111,215 +61,8 @@ struct FwdProblem {
     }
 };
 
-// dA = (dZ W^T) * [A > 0].  rows = batch, cols = din, K = dout.
-struct DgradProblem {
-    static constexpr bool A_K_FAST = true, B_C_FAST = false;
-    const float *dz; const float *X; const float *act; const uint16_t *act_bf16; int64_t woff, din, dout;
-    int M, B; float *out; uint16_t *out_bf16, *out_bf16_t;
-    __device__ int rows() const { return B; }
-    __device__ int64_t cols() const { return din; }
-    __device__ int64_t depth() const { return dout; }
-    __device__ LayerInput input() const { return LayerInput{}; }
-    template <int AK> __device__ uint32_t a_bits(int g, int64_t r, int64_t k, const int64_t *) const
-    {
-        return ((const uint32_t *)dz)[((size_t)g * B + r) * dout + k];
-    }
-    template <int AK> __device__ float a_val(uint32_t u) const { return operand<AK>(as_float(u)); }
-    __device__ uint32_t b_bits(int g, int64_t k, int64_t c) const
-    {
-        return ((const uint32_t *)X)[tiled_offset(M, g, woff + c * dout + k)];
-    }
-    template <int AK> __device__ float b_val(uint32_t u) const { return operand<AK>(as_float(u)); }
-    static constexpr bool A_AFFINE = true;
-    template <int AK> __device__ int64_t a_base(int g, int64_t r, const int64_t *) const { return ((int64_t)g * B + r) * dout; }
-    __device__ int64_t a_step() const { return 1; }
-    template <int AK> __device__ uint32_t a_at(int64_t index) const { return ((const uint32_t *)dz)[index]; }
-    __device__ int64_t b_base(int g, int64_t c) const { return woff + c * dout; }
-    __device__ int64_t b_step() const { return 1; }
-    __device__ uint32_t b_at(int g, int64_t index) const { return ((const uint32_t *)X)[tiled_offset_quick(M, g, index)]; }
-    __device__ void store(int g, int64_t r, int64_t c, float acc) const
-    {
-        const size_t q = ((size_t)g * B + r) * din + c;
-        const bool on = act_bf16 ? bf16_positive(act_bf16[q]) : act[q] > 0.0f;
-        const float d = on ? acc : 0.0f;
-        out[q] = d;
-        if (out_bf16) {
-            const uint16_t h = (uint16_t)bf16_bits(d);
-            out_bf16[q] = h;
-            out_bf16_t[((size_t)g * din + c) * B + r] = h;
-        }
-    }
-};
-
-// dW = A^T dZ.  rows = din, cols = dout, K = batch.
-struct WgradProblem {
-    static constexpr bool A_K_FAST = false, B_C_FAST = true;
-    LayerInput in; const float *dz; int64_t woff, din, dout; int M, B; float *G;
-    __device__ int64_t rows() const { return din; }
-    __device__ int64_t cols() const { return dout; }
-    __device__ int64_t depth() const { return B; }
-    __device__ const LayerInput &input() const { return in; }
-    template <int AK> __device__ uint32_t a_bits(int g, int64_t r, int64_t k, const int64_t *rows) const
-    {
-        return in.bits<AK>(g, (int)k, r, rows);
-    }
-    template <int AK> __device__ float a_val(uint32_t u) const { return in.value<AK>(u); }
-    __device__ uint32_t b_bits(int g, int64_t k, int64_t c) const
-    {
-        return ((const uint32_t *)dz)[((size_t)g * B + k) * dout + c];
-    }
-    template <int AK> __device__ float b_val(uint32_t u) const { return operand<AK>(as_float(u)); }
-    static constexpr bool A_AFFINE = false;      // the batch row of contraction index k is looked up (gathered data)
-    template <int AK> __device__ int64_t a_base(int, int64_t, const int64_t *) const { return 0; }
-    __device__ int64_t a_step() const { return 0; }
-    template <int AK> __device__ uint32_t a_at(int64_t) const { return 0u; }
-    __device__ int64_t b_base(int g, int64_t c) const { return (int64_t)g * B * dout + c; }
-    __device__ int64_t b_step() const { return dout; }
-    __device__ uint32_t b_at(int, int64_t index) const { return ((const uint32_t *)dz)[index]; }
-    __device__ void store(int g, int64_t r, int64_t c, float acc) const
-    {
-        G[tiled_offset(M, g, woff + r * dout + c)] = acc;
-    }
-};
-
-// 64 x 64 output tile per workgroup (32 x 32 in the SMALL variant), one 32 x 32 quadrant per wave on v_mfma_f32_32x32x2_f32 (fp32 operands,
-// exact products, fp32 accumulation), K in steps of 32 through LDS.  Lane l of the instruction supplies
-// A[row l % 32][k = l / 32] and B[k = l / 32][col l % 32] and holds D[8 (v / 4) + 4 (l / 32) + v % 4][l % 32]
-// in result register v.  The operands of the
-// next step are fetched into registers while the current step is multiplied.  Every fetch is a run of
-// unconditional loads: coordinates beyond the operand are clamped into it and the value is replaced by zero
-// afterwards, the operand's kind AK is a template parameter and the worker's batch rows are resolved once into
-// LDS, so that no load waits for a branch or for another load.
-template <class Problem, int AK, bool SMALL = false>
-__global__ void __launch_bounds__(GEMM_THREADS) grouped_gemm_kernel(Problem p)
-{
-    // SMALL: a 32 x 32 output tile; the four waves split every step's contraction indices between them (wave w takes
-    // k = 8 w .. 8 w + 7) and their partial tiles are added through LDS at the end, in the order of the waves.  Four
-    // times as many workgroups with a quarter of the matrix instructions per step each: for few, long problems.
-    constexpr int TM = SMALL ? 32 : 64, TN = SMALL ? 32 : 64;
-    constexpr int TK = SMALL ? 64 : 32;      // contraction indices per step
-    __shared__ float As[TK][TM + 4];
-    __shared__ float Bs[TK][TN + 4];
-    __shared__ int64_t s_rows[MAX_BATCH];
-    const int g = blockIdx.z, tid = threadIdx.x;
-    const int64_t row0 = (int64_t)blockIdx.y * TM, col0 = (int64_t)blockIdx.x * TN;
-    const int64_t R = p.rows(), C = p.cols(), K = p.depth();
-    const int lane = tid & 63, wave = tid >> 6, wm = SMALL ? 0 : wave >> 1, wn = SMALL ? 0 : wave & 1;
-    if (AK == IN_GATHER_F32 || AK == IN_GATHER_BF16) {
-        const LayerInput in = p.input();
-        for (int b = tid; b < in.B; b += GEMM_THREADS) s_rows[b] = in.row0[g] + in.idx[(size_t)g * in.B + b];
-        __syncthreads();
-    }
-    constexpr int A_PER = (TM * TK) / GEMM_THREADS, B_PER = (TN * TK) / GEMM_THREADS;
-    uint32_t ra[A_PER], rb[B_PER];
-    unsigned a_ok = 0, b_ok = 0;          // bit q: element q of the fetch lies inside the operand
-    // per element of a fetch: its index at contraction index kk (its own offset inside a step; row / column clamped
-    // into the operand), so that a step only adds k0 * step, the same number for the whole workgroup
-    int64_t a_idx[A_PER], b_idx[B_PER];
-    unsigned a_in = 0, b_in = 0;          // bit q: the row / column of element q exists
-    const int64_t a_step = p.a_step(), b_step = p.b_step();
-#pragma unroll
-    for (int q = 0; q < A_PER; ++q) {
-        const int e = tid + q * GEMM_THREADS;
-        const int r = Problem::A_K_FAST ? e / TK : e % TM, kk = Problem::A_K_FAST ? e % TK : e / TM;
-        const int64_t rr = row0 + r;
-        a_in |= (unsigned)(rr < R) << q;
-        a_idx[q] = Problem::A_AFFINE ? p.template a_base<AK>(g, rr < R ? rr : R - 1, s_rows) + kk * a_step : 0;
-    }
-#pragma unroll
-    for (int q = 0; q < B_PER; ++q) {
-        const int e = tid + q * GEMM_THREADS;
-        const int c = Problem::B_C_FAST ? e % TN : e / TK, kk = Problem::B_C_FAST ? e / TN : e % TK;
-        const int64_t cc = col0 + c;
-        b_in |= (unsigned)(cc < C) << q;
-        b_idx[q] = p.b_base(g, cc < C ? cc : C - 1) + kk * b_step;
-    }
-    // full = std::true_type: every contraction index of the step is below K, nothing to clamp or mask along K
-    auto fetch = [&](int64_t k0, auto full) {
-        constexpr bool FULL = decltype(full)::value;
-        a_ok = FULL ? a_in : 0u;
-        b_ok = FULL ? b_in : 0u;
-        const int64_t a_k0 = k0 * a_step, b_k0 = k0 * b_step;
-#pragma unroll
-        for (int q = 0; q < A_PER; ++q) {
-            const int e = tid + q * GEMM_THREADS;
-            const int r = Problem::A_K_FAST ? e / TK : e % TM, kk = Problem::A_K_FAST ? e % TK : e / TM;
-            const int64_t kq = k0 + kk, kc = (FULL || kq < K) ? kq : K - 1;
-            if (!FULL) a_ok |= (unsigned)(((a_in >> q) & 1u) && kq < K) << q;
-            if constexpr (Problem::A_AFFINE) {
-                ra[q] = p.template a_at<AK>(FULL ? a_idx[q] + a_k0 : a_idx[q] + (kc - kk) * a_step);
-            } else {
-                const int64_t rr = row0 + r;
-                ra[q] = p.template a_bits<AK>(g, rr < R ? rr : R - 1, kc, s_rows);
-            }
-        }
-#pragma unroll
-        for (int q = 0; q < B_PER; ++q) {
-            const int e = tid + q * GEMM_THREADS;
-            const int kk = Problem::B_C_FAST ? e / TN : e % TK;
-            const int64_t kq = k0 + kk, kc = (FULL || kq < K) ? kq : K - 1;
-            if (!FULL) b_ok |= (unsigned)(((b_in >> q) & 1u) && kq < K) << q;
-            rb[q] = p.b_at(g, FULL ? b_idx[q] + b_k0 : b_idx[q] + (kc - kk) * b_step);
-        }
-    };
-    auto fetch_step = [&](int64_t k0) {
-        if (k0 + TK <= K) fetch(k0, std::true_type{});
-        else fetch(k0, std::false_type{});
-    };
-    gemm_acc acc;
-#pragma unroll
-    for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
-    fetch_step(0);
-    for (int64_t k0 = 0; k0 < K; k0 += TK) {
-        __syncthreads();                       // the previous step's reads of LDS are done
-#pragma unroll
-        for (int q = 0; q < A_PER; ++q) {
-            const int e = tid + q * GEMM_THREADS;
-            int kk, r;
-            if (Problem::A_K_FAST) { kk = e % TK; r = e / TK; } else { r = e % TM; kk = e / TM; }
-            const float v = p.template a_val<AK>(ra[q]);
-            As[kk][r] = ((a_ok >> q) & 1u) ? v : 0.0f;
-        }
-#pragma unroll
-        for (int q = 0; q < B_PER; ++q) {
-            const int e = tid + q * GEMM_THREADS;
-            int kk, c;
-            if (Problem::B_C_FAST) { c = e % TN; kk = e / TN; } else { kk = e % TK; c = e / TK; }
-            const float v = p.template b_val<AK>(rb[q]);
-            Bs[kk][c] = ((b_ok >> q) & 1u) ? v : 0.0f;
-        }
-        __syncthreads();
-        if (k0 + TK < K) fetch_step(k0 + TK);
-        constexpr int K_PER_WAVE = SMALL ? TK / 4 : TK;
-#pragma unroll
-        for (int kk = 0; kk < K_PER_WAVE; kk += 2) {
-            const int k = (SMALL ? wave * K_PER_WAVE : 0) + kk + (lane >> 5);
-            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(As[k][32 * wm + (lane & 31)], Bs[k][32 * wn + (lane & 31)], acc, 0, 0, 0);
-        }
-    }
-    if constexpr (SMALL) {
-        __shared__ float part[4][32][33];
-#pragma unroll
-        for (int v = 0; v < 16; ++v) part[wave][8 * (v >> 2) + 4 * (lane >> 5) + (v & 3)][lane & 31] = acc[v];
-        __syncthreads();
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int e = tid + j * GEMM_THREADS, r = e >> 5, c = e & 31;
-            const float sum = ((part[0][r][c] + part[1][r][c]) + part[2][r][c]) + part[3][r][c];
-            if (row0 + r < R && col0 + c < C) p.store(g, row0 + r, col0 + c, sum);
-        }
-    } else {
-    const int64_t cc = col0 + 32 * wn + (lane & 31);
-#pragma unroll
-    for (int v = 0; v < 16; ++v) {
-        const int64_t rr = row0 + 32 * wm + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-        if (rr < R && cc < C) p.store(g, rr, cc, acc[v]);
-    }
-    }
-}
-
 // Forward pass of a layer with few outputs (at most 32: the classifier layer), any input width and kind.  The tiled
-// kernel above would use one 64-column tile per worker for it, most of it padding, on M workgroups.  Here a
+// kernels would use one 64-column tile per worker for it, most of it padding, on few workgroups.  Here a
 // workgroup takes 16 batch rows of one worker; 16 threads share a row and split the contraction index between them
 // (thread q takes k = q, q + 16, ...).  The weights of a chunk of the contraction are a run of consecutive
 // parameters (rows of W are dout long), copied to LDS as they lie; all loads of a chunk are requested before the
@@ -414,40 +157,6 @@ static void launch_fwd_narrow(hipStream_t s, const FwdProblem &p, int kind, int 
     else launch_fwd_narrow_kind<32>(s, p, kind, grid);
 }
 
-template <class Problem> static dim3 gemm_grid(int groups, int64_t rows, int64_t cols, int tile = 64)
-{
-    return dim3((unsigned)((cols + tile - 1) / tile), (unsigned)((rows + tile - 1) / tile), (unsigned)groups);
-}
-
-static void launch_gemm(hipStream_t s, const DgradProblem &p, int kind, int groups, int64_t rows, int64_t cols)
-{
-    const dim3 grid = gemm_grid<DgradProblem>(groups, rows, cols);
-    if (kind == IN_ACT_BF16) hipLaunchKernelGGL((grouped_gemm_kernel<DgradProblem, IN_ACT_BF16>), grid, dim3(GEMM_THREADS), 0, s, p);
-    else hipLaunchKernelGGL((grouped_gemm_kernel<DgradProblem, IN_ACT_F32>), grid, dim3(GEMM_THREADS), 0, s, p);
-}
-
-// depth: the contraction length.  Few tiles and a long contraction (a small batch against a wide layer): the 32 x 32
-// variant, whose four waves share each step, puts four times as many workgroups on the chip.
-template <class Problem>
-static void launch_gemm(hipStream_t s, const Problem &p, int kind, int groups, int64_t rows, int64_t cols, int64_t depth)
-{
-    dim3 grid = gemm_grid<Problem>(groups, rows, cols);
-    const bool small = (int64_t)grid.x * grid.y * grid.z < 256 && depth >= 128;
-    if (small) grid = gemm_grid<Problem>(groups, rows, cols, 32);
-#define NETMAX_GEMM(KIND)                                                                                        \
-    do {                                                                                                         \
-        if (small) hipLaunchKernelGGL((grouped_gemm_kernel<Problem, KIND, true>), grid, dim3(GEMM_THREADS), 0, s, p);  \
-        else hipLaunchKernelGGL((grouped_gemm_kernel<Problem, KIND, false>), grid, dim3(GEMM_THREADS), 0, s, p);       \
-    } while (0)
-    switch (kind) {
-    case IN_GATHER_F32: NETMAX_GEMM(IN_GATHER_F32); break;
-    case IN_GATHER_BF16: NETMAX_GEMM(IN_GATHER_BF16); break;
-    case IN_ACT_F32: NETMAX_GEMM(IN_ACT_F32); break;
-    default: NETMAX_GEMM(IN_ACT_BF16); break;
-    }
-#undef NETMAX_GEMM
-}
-
 // Softmax cross-entropy on the logits (softmax_xent.h): one workgroup per worker.
 __global__ void __launch_bounds__(1024) softmax_xent_kernel(SoftmaxArgs a) { softmax_xent_block(a, blockIdx.x); }
 
@@ -501,6 +210,11 @@ void launch_mlp_grad(hipStream_t s, const MlpPlan &p, const float *X, float *G, 
             launch_fwd_f32(s, p, l, X);
             continue;
         }
+        if (p.dims[l + 1] > 32) {
+            // the transposed bfloat16 activation is read by the matrix-core weight gradients only
+            launch_tile_fwd(s, p, l, X, !last && (fast[l + 1] || (l + 2 == L && small_last)));
+            continue;
+        }
         FwdProblem f;
         f.in = input_of(l); f.X = X; f.M = p.M; f.woff = p.woff[l]; f.din = p.dims[l]; f.dout = p.dims[l + 1];
         f.B = p.B; f.relu = !last;
@@ -508,8 +222,7 @@ void launch_mlp_grad(hipStream_t s, const MlpPlan &p, const float *X, float *G, 
         f.out_bf16 = (bf && !last) ? p.hb[l + 1] : nullptr;
         f.out_bf16_t = (bf && !last) ? p.ht[l + 1] : nullptr;
         // few outputs: the tiled kernel would pad them to a 64-column tile on one workgroup per worker
-        if (f.dout <= 32) launch_fwd_narrow(s, f, f.in.kind, p.M);
-        else launch_gemm(s, f, f.in.kind, p.M, p.B, f.dout, f.din);
+        launch_fwd_narrow(s, f, f.in.kind, p.M);
     }
     bool bias_done[8] = {};
     int cur = 0, l_top = L - 1;
@@ -537,10 +250,7 @@ void launch_mlp_grad(hipStream_t s, const MlpPlan &p, const float *X, float *G, 
         } else if (wgrad_f32_ok(p, l)) {
             launch_wgrad_f32(s, p, l, G, p.dz[cur]);
         } else {
-            WgradProblem wg;
-            wg.in = input_of(l); wg.dz = p.dz[cur]; wg.M = p.M; wg.woff = p.woff[l]; wg.din = din; wg.dout = dout;
-            wg.B = p.B; wg.G = G;
-            launch_gemm(s, wg, wg.in.kind, p.M, din, dout, p.B);
+            launch_tile_wgrad(s, p, l, G, cur);
         }
         if (!bias_done[l]) {
             hipLaunchKernelGGL(bias_grad_kernel, dim3((unsigned)((dout + 63) / 64), (unsigned)p.M), dim3(256), 0, s, p.M, p.B,
@@ -554,13 +264,7 @@ void launch_mlp_grad(hipStream_t s, const MlpPlan &p, const float *X, float *G, 
                 launch_dgrad_small(s, p, X, G, cur, !fast[l - 1]);
                 bias_done[l - 1] = true;
             } else {
-                DgradProblem dg;
-                dg.dz = p.dz[cur]; dg.X = X; dg.act = bf ? nullptr : p.act[l]; dg.act_bf16 = bf ? p.hb[l] : nullptr;
-                dg.M = p.M; dg.woff = p.woff[l]; dg.din = din; dg.dout = dout; dg.B = p.B;
-                dg.out = p.dz[cur ^ 1];
-                dg.out_bf16 = bf ? p.dzb[cur ^ 1] : nullptr;
-                dg.out_bf16_t = bf ? p.dzt[cur ^ 1] : nullptr;
-                launch_gemm(s, dg, bf ? IN_ACT_BF16 : IN_ACT_F32, p.M, p.B, din);     // the kind only says whether operands are rounded
+                bias_done[l - 1] = launch_tile_dgrad(s, p, l, X, G, cur, fast[l - 1]);
             }
             cur ^= 1;
         }

@@ -177,6 +177,13 @@ hipError_t prepare_f32_layers();
 void launch_fwd_f32(hipStream_t s, const MlpPlan &p, int l, const float *X);
 void launch_wgrad_f32(hipStream_t s, const MlpPlan &p, int l, float *G, const float *dz);
 
+// Tiled kernels for layers of any shape, fp32 or bfloat16 operands.  need_t: the transposed bfloat16 activation is wanted (by a
+// matrix-core kernel above); below_fast: so are both bfloat16 copies of the error.  launch_tile_dgrad: true if it has also
+// written the bias gradient of the layer below (its workgroups held the whole batch).
+void launch_tile_fwd(hipStream_t s, const MlpPlan &p, int l, const float *X, bool need_t);
+bool launch_tile_dgrad(hipStream_t s, const MlpPlan &p, int l, const float *X, float *G, int cur, bool below_fast);
+void launch_tile_wgrad(hipStream_t s, const MlpPlan &p, int l, float *G, int cur);
+
 // Last layer with at most 16 classes on fp32 operands above a hidden layer (k_grad_head.hip): one kernel from the
 // last hidden activation to the error of that layer: logits, loss, dW, db, dH and the column sums of dH.
 bool head_ok(const MlpPlan &p);

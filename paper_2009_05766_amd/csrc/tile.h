@@ -1,0 +1,160 @@
+// Building blocks of the tiled kernels for layers of any shape (k_tile_fwd.hip, k_tile_dgrad.hip, k_tile_wgrad.hip): one
+// workgroup computes a BM x BN block of a worker's product, its waves 32 x 32 tiles of it, in steps of BK contraction
+// indices through LDS.  While a step is multiplied the next one is on its way into registers.
+//
+// Both operands lie in LDS as rows along the contraction (As[m][k], Bs[n][k]) in pieces of four neighbouring k, so that a
+// lane reads what an instruction or two want as one 128-bit word.  A piece comes from memory in one of two ways:
+//   along     the operand is contiguous along k there: a piece is one load
+//   across    it is contiguous along m (or n): a thread loads a 4 x 4 block as four rows and turns it by naming registers
+// fp32 operands are multiplied by v_mfma_f32_32x32x2_f32 (exact products, fp32 accumulation; the two lane halves take four
+// consecutive k each, the order inside the sum is the same for both operands), bfloat16 operands (BF) by
+// v_mfma_f32_32x32x16_bf16; values that are fp32 in memory are rounded on their way into LDS.
+#pragma once
+#include "bf16.h"
+#include "kernels.h"
+#include "layout.h"
+#include "vec.h"
+
+namespace netmax {
+
+typedef float tile_f32x16 __attribute__((ext_vector_type(16)));
+typedef uint32_t tile_u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t tile_u32x2 __attribute__((ext_vector_type(2)));
+typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 tile_bf16x8;
+
+// tiled_offset() with one 32 x 32 -> 64 bit multiply-add: j + (((j >> 11) (M - 1) + i) << 11); needs j < 2^43
+__device__ __forceinline__ size_t tiled_offset_quick(int M, int i, int64_t j)
+{
+    const uint64_t t = (uint64_t)(uint32_t)(j >> TILE_SHIFT) * (uint32_t)(M - 1) + (uint32_t)i;
+    return (size_t)j + (size_t)(t << TILE_SHIFT);
+}
+
+// Four neighbouring elements of memory: fp32, or bfloat16 (S16) as two packed words.
+template <bool S16> struct Piece { f32x4 v; };
+template <> struct Piece<true> { tile_u32x2 v; };
+
+// V: one load (the four elements exist and are aligned).  Otherwise element by element, n of them exist (at least one;
+// the others repeat the last).
+template <bool V> __device__ __forceinline__ Piece<false> load_piece(const float *p, int n)
+{
+    Piece<false> r;
+    if constexpr (V) r.v = load4(p);
+    else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) r.v[e] = p[e < n ? e : n - 1];
+    }
+    return r;
+}
+template <bool V> __device__ __forceinline__ Piece<true> load_piece(const uint16_t *p, int n)
+{
+    Piece<true> r;
+    if constexpr (V) r.v = *reinterpret_cast<const tile_u32x2 *>(p);
+    else {
+        uint32_t h[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) h[e] = p[e < n ? e : n - 1];
+        r.v = tile_u32x2{h[0] | (h[1] << 16), h[2] | (h[3] << 16)};
+    }
+    return r;
+}
+
+// Element e of a loaded piece as fp32 / as 16 bits.
+__device__ __forceinline__ float piece_f32(const Piece<false> &p, int e) { return p.v[e]; }
+__device__ __forceinline__ uint32_t piece_bits(const Piece<true> &p, int e) { return (p.v[e >> 1] >> (16 * (e & 1))) & 0xFFFFu; }
+
+template <bool BF, int BK> struct TileLds {
+    typedef float elem;
+    static constexpr int PITCH = BK + 4;             // rows start at multiples of 16 bytes, 32 of them meet all banks evenly
+};
+template <int BK> struct TileLds<true, BK> {
+    typedef uint16_t elem;
+    static constexpr int PITCH = BK + 8;
+};
+
+// Writes the piece k .. k + 3 of an operand row; only the first `left` of the four indices exist, the others become 0.
+__device__ __forceinline__ void put_piece(float *dst, f32x4 v, int left)
+{
+    if (left < 4) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = e < left ? v[e] : 0.0f;
+    }
+    *reinterpret_cast<f32x4 *>(dst) = v;
+}
+__device__ __forceinline__ void put_piece(uint16_t *dst, f32x4 v, int left)
+{
+    if (left < 4) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = e < left ? v[e] : 0.0f;
+    }
+    *reinterpret_cast<tile_u32x2 *>(dst) = tile_u32x2{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
+}
+__device__ __forceinline__ void put_piece(uint16_t *dst, tile_u32x2 v, int left)
+{
+    if (left < 4) {
+        v[0] = left >= 2 ? v[0] : (left == 1 ? v[0] & 0xFFFFu : 0u);
+        v[1] = left == 3 ? v[1] & 0xFFFFu : 0u;
+    }
+    *reinterpret_cast<tile_u32x2 *>(dst) = v;
+}
+
+// A block loaded across: piece of row e = element e of the four loaded rows.
+__device__ __forceinline__ f32x4 turned(const Piece<false> (&r)[4], int e) { return f32x4{r[0].v[e], r[1].v[e], r[2].v[e], r[3].v[e]}; }
+__device__ __forceinline__ tile_u32x2 turned(const Piece<true> (&r)[4], int e)
+{
+    return tile_u32x2{piece_bits(r[0], e) | (piece_bits(r[1], e) << 16), piece_bits(r[2], e) | (piece_bits(r[3], e) << 16)};
+}
+
+// One step: acc[i][j] += As[m0 + 32 i ..][k] Bs[n0 + 32 j ..][k] over the BK indices in LDS.
+template <int BK, int RI, int CJ, int PITCH>
+__device__ __forceinline__ void tile_multiply(const float (*As)[PITCH], const float (*Bs)[PITCH], int m0, int n0, int lane,
+                                              tile_f32x16 (&acc)[RI][CJ])
+{
+#pragma unroll
+    for (int ks = 0; ks < BK; ks += 8) {
+        f32x4 a[RI], b[CJ];
+#pragma unroll
+        for (int i = 0; i < RI; ++i) a[i] = *reinterpret_cast<const f32x4 *>(&As[m0 + 32 * i + (lane & 31)][ks + 4 * (lane >> 5)]);
+#pragma unroll
+        for (int j = 0; j < CJ; ++j) b[j] = *reinterpret_cast<const f32x4 *>(&Bs[n0 + 32 * j + (lane & 31)][ks + 4 * (lane >> 5)]);
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+#pragma unroll
+            for (int i = 0; i < RI; ++i)
+#pragma unroll
+                for (int j = 0; j < CJ; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i][c], b[j][c], acc[i][j], 0, 0, 0);
+    }
+}
+template <int BK, int RI, int CJ, int PITCH>
+__device__ __forceinline__ void tile_multiply(const uint16_t (*As)[PITCH], const uint16_t (*Bs)[PITCH], int m0, int n0, int lane,
+                                              tile_f32x16 (&acc)[RI][CJ])
+{
+#pragma unroll
+    for (int ks = 0; ks < BK; ks += 16) {
+        tile_u32x4 a[RI], b[CJ];
+#pragma unroll
+        for (int i = 0; i < RI; ++i) a[i] = *reinterpret_cast<const tile_u32x4 *>(&As[m0 + 32 * i + (lane & 31)][ks + 8 * (lane >> 5)]);
+#pragma unroll
+        for (int j = 0; j < CJ; ++j) b[j] = *reinterpret_cast<const tile_u32x4 *>(&Bs[n0 + 32 * j + (lane & 31)][ks + 8 * (lane >> 5)]);
+#pragma unroll
+        for (int i = 0; i < RI; ++i)
+#pragma unroll
+            for (int j = 0; j < CJ; ++j)
+                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(tile_bf16x8, a[i]),
+                                                                    __builtin_bit_cast(tile_bf16x8, b[j]), acc[i][j], 0, 0, 0);
+    }
+}
+
+// Row of result register v in a 32 x 32 tile (the column is lane % 32).
+__device__ __forceinline__ int tile_row(int lane, int v) { return 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3); }
+
+template <int RI, int CJ> __device__ __forceinline__ void tile_clear(tile_f32x16 (&acc)[RI][CJ])
+{
+#pragma unroll
+    for (int i = 0; i < RI; ++i)
+#pragma unroll
+        for (int j = 0; j < CJ; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
+}
+
+}  // namespace netmax
