@@ -1,41 +1,43 @@
-// Last layer of a ReLU perceptron with few classes on fp32 operands, from the last hidden activation h to the error
-// handed to the layer below (the stochastic gradient of Algorithm 2's first-step update, its part above the last
-// hidden layer): logits = h W + b, softmax cross-entropy (mean loss, dZ = (softmax - onehot) / B), dW = h^T dZ,
-// db = column sums of dZ, dH = (dZ W^T) masked by h > 0, and the column sums of dH = the bias gradient of the layer
-// below.  The general kernels take five dependent launches of a few microseconds each for this; small perceptrons are
+// Last layer of a perceptron with at most 32 classes, from its input h (the last hidden activation, or the gathered data rows of
+// a softmax regression) to the error handed to the layer below (the stochastic gradient of Algorithm 2's first-step
+// update, its part above the last hidden layer): logits = h W + b, softmax cross-entropy (mean loss, dZ = (softmax - onehot) / B),
+// dW = h^T dZ, db = column sums of dZ, dH = (dZ W^T) masked by h > 0, and the column sums of dH = the bias gradient of the layer
+// below.  Kernels of one purpose each take three to five dependent launches of a few microseconds for this; small models are
 // bound by exactly that latency.  Here it is two:
 //
-//   head_logits_kernel  one workgroup per worker and 16 batch rows; its four waves split the hidden units, add their
+//   head_logits_kernel  one workgroup per worker and 16 batch rows; its waves split the features, add their
 //                       partial logits through LDS in wave order, then sixteen lanes per row do the softmax
-//   head_grads_kernel   one workgroup per worker and 64 hidden units; a wave takes sixteen of them: sixteen rows of
+//   head_grads_kernel   one workgroup per worker and 64 features; a wave takes sixteen of them: sixteen rows of
 //                       dW and sixteen columns of dH from one set of loads of h (the order of the contraction over
 //                       the batch in dW is chosen so that the lanes hold the 16 x B block of h exactly as the result
 //                       block of dH, which needs it for the ReLU mask)
 //
 // so that h is read once by each, by many compute units (one kernel that did everything per worker had a single
-// compute unit pull 200 KB and took 14.6 us at 16 workers, 512 hidden units; these take 4 to 5 us each).
-// The three products run on v_mfma_f32_16x16x4_f32 with the class dimension padded to one 16-wide tile (lane l
-// supplies A[l % 16][l / 16] and B[l / 16][l % 16] and receives D[4 (l / 16) + v][l % 16], v = 0..3); the operands
-// from W are loaded straight into that layout (a wave's load is 4 rows of W = 4 C contiguous floats).
-// No load sits under a branch: where a bound has to be respected the index is clamped and the value discarded.
-#include "kernels.h"
-#include "layout.h"
-#include "vec.h"
+// compute unit pull 200 KB and took 14.6 us at 16 workers, 512 hidden units; these take 4.6 and 4.8 us).  Softmax regression on
+// 784 features, 16 workers, batch 64: 6.2 and 4.2 us in place of three kernels of 15.0, 9.3 and 6.2 us; 1024 hidden units, 32
+// workers, batch 128: 10 and 14 us in place of five kernels of 16, 12, 12, 17 and 16 us.
+// The products run on v_mfma_f32_16x16x4_f32 with the classes padded to one or two 16-wide tiles (lane l
+// supplies A[l % 16][l / 16] and B[l / 16][l % 16] and receives D[4 (l / 16) + v][l % 16], v = 0..3); bfloat16 operands are
+// rounded first, their products are exact there.  The operands from W are loaded straight into that layout (a wave's load is 4
+// rows of W = 4 C contiguous floats).
+// No load sits under a branch: where a bound has to be respected the index is clamped and the value discarded; numbers of
+// features that fill the steps of sixteen have a form without any bound (7.7 -> 6.2 us at 784 features).
+#include "tile.h"
 
 namespace netmax {
 
-constexpr int HD_THREADS = 256, HD_WAVES = HD_THREADS / 64;
-constexpr int HD_CP = 16;                       // padded class dimension
-constexpr int HD_ZP = 20;                       // floats per row of dZ in LDS: the four row groups (16 rows apart) that a
-                                                // wave reads at once fall into different banks
-constexpr int HD_MAX_H = 1024;
-constexpr int HD_KCHUNK = 128;                  // hidden units of one wave's part whose loads are in flight together
+constexpr int HD_THREADS = 256, HD_WAVES = HD_THREADS / 64;          // gradients kernel
+// logits kernel: steps of sixteen features of a wave's part whose loads are in flight together.  Up to 32 steps four waves
+// take them (a wave with fewer than eight steps asks for its first one again instead), more are dealt to eight waves.
+constexpr int HD_STEPS = 8, HL_FEW = 4, HL_MANY = 8;
+constexpr int HD_MAX_B = 256, HD_MAX_C = 32;
 
 struct HeadArgs {
-    const float *h;                 // [M][B][H] activation of the last hidden layer
+    const void *in;                 // [M][B][H] activation of the last hidden layer
+    int gather;                     // (or the data rows)
+    const int64_t *row0; const int32_t *idx;                         // batch rows of every worker [M][B]
     const float *X; float *G;       // parameters and gradient, tile layout
-    const int32_t *labels; const int64_t *row0; const int32_t *idx;
-    float *logits;                  // [M][B][C]
+    const int32_t *labels;
     float *dz;                      // [M][B][C]
     float *row_loss;                // [M][B] loss of every batch row (between the two kernels)
     float *dh;                      // [M][B][H]
@@ -48,103 +50,204 @@ struct HeadArgs {
 
 __device__ __forceinline__ f32x4 mfma_16x16x4(float a, float b, f32x4 acc) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, acc, 0, 0, 0); }
 
-// Grid: (B / 16, workers).
-__global__ void __launch_bounds__(HD_THREADS) head_logits_kernel(HeadArgs p)
+// Operands: fp32 as they are, bfloat16 (BF) rounded; inputs are stored as bfloat16 then.
+template <bool BF> __device__ __forceinline__ float head_operand(float x) { return BF ? round_bf16(x) : x; }
+template <bool BF> __device__ __forceinline__ float head_input(const void *in, int64_t index)
 {
-    __shared__ float part[HD_WAVES][16][HD_CP];
+    if constexpr (BF) return bf16_bits_to_float(((const uint16_t *)in)[index]);
+    else return ((const float *)in)[index];
+}
+template <bool BF> struct HeadElem { typedef float type; };
+template <> struct HeadElem<true> { typedef uint16_t type; };
+// A worker's last layer inside the tile layout: parameter u of it (u = k C + c, bias behind) counted from the start of the tile
+// that holds its first one.  32-bit: head_ok() has checked that the layer's span fits.
+struct HeadParams {
+    size_t base; uint32_t skip, first;
+    __device__ __forceinline__ HeadParams(int M, int g, int64_t woff)
+        : base(((size_t)(woff >> TILE_SHIFT) * M + g) << TILE_SHIFT), skip((uint32_t)(M - 1) << TILE_SHIFT), first((uint32_t)(woff & (TILE - 1))) {}
+    __device__ __forceinline__ uint32_t at(uint32_t u) const { return u + first + ((u + first) >> TILE_SHIFT) * skip; }
+};
+// Element index of feature 0 of batch row b.
+__device__ __forceinline__ int64_t head_row(const HeadArgs &p, int g, int b)
+{
+    return (p.gather ? p.row0[g] + p.idx[(size_t)g * p.B + b] : (int64_t)g * p.B + b) * p.H;
+}
+
+// Grid: (ceil(B / 16), workers).  CT: tiles of sixteen classes.  How the input's rows are read: feature by feature, in pieces of
+// four features, in pieces of a number of features that fills the steps of sixteen (no bounds to respect).
+enum : int { HL_SINGLE = 0, HL_PIECES = 1, HL_WHOLE = 2 };
+template <bool BF, int MODE, int CT, int NW>
+__global__ void __launch_bounds__(64 * NW) head_logits_kernel(HeadArgs p)
+{
+    __shared__ float part[NW][16][16 * CT];
     const int B = p.B, H = p.H, C = p.C;
     const int g = blockIdx.y, rt = blockIdx.x, t = threadIdx.x, lane = t & 63, r = lane & 15, q = lane >> 4;
     const int kp = __builtin_amdgcn_readfirstlane(t >> 6);
-    const int KW = H / HD_WAVES, k_begin = kp * KW, k_end = k_begin + KW;
-    const float *a_ptr = p.h + ((size_t)g * B + 16 * rt + r) * H + 4 * q;
-    const bool real = r < C;
-    const int64_t wbase = p.woff + (real ? r : 0);
-    f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
-    for (int k0 = k_begin; k0 < k_end; k0 += HD_KCHUNK) {
-        f32x4 a[HD_KCHUNK / 16];
-        float b[HD_KCHUNK / 16][4];
+    // each wave takes a run of steps of sixteen features; rows past the batch and features past the end are clamped, the
+    // features' products then masked
+    const int steps = (H + 15) / 16, per = (steps + NW - 1) / NW;
+    const int s_begin = kp * per, s_end = s_begin + per < steps ? s_begin + per : steps;
+    const int64_t a_row = head_row(p, g, 16 * rt + r < B ? 16 * rt + r : B - 1);
+    const HeadParams at(p.M, g, p.woff);
+    const float *Xg = p.X + at.base;
+    uint32_t wcol[CT];
 #pragma unroll
-        for (int i = 0; i < HD_KCHUNK / 16; ++i) {
-            const int kc = k0 + 16 * i < k_end ? k0 + 16 * i : k_begin;       // past the end: the first step again, unused
-            a[i] = *reinterpret_cast<const f32x4 *>(a_ptr + kc);
+    for (int c = 0; c < CT; ++c) wcol[c] = min(16 * c + r, C - 1);
+    f32x4 acc[CT];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) b[i][j] = p.X[tiled_offset(p.M, g, wbase + (int64_t)(kc + 4 * q + j) * C)];
-        }
-        __builtin_amdgcn_sched_barrier(0);
+    for (int c = 0; c < CT; ++c) acc[c] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    float a[HD_STEPS][4], b[HD_STEPS][4][CT];
+    auto request = [&](int s0) {
 #pragma unroll
-        for (int i = 0; i < HD_KCHUNK / 16; ++i)
-            if (k0 + 16 * i < k_end) {
+        for (int i = 0; i < HD_STEPS; ++i) {
+            const int k0 = 16 * (s0 + i < s_end ? s0 + i : s_begin) + 4 * q;        // past the part: its first step again, unused
+            if constexpr (MODE != HL_SINGLE) {
+                const Piece<BF> x = load_piece<true>((const typename HeadElem<BF>::type *)p.in + a_row + (MODE == HL_WHOLE ? k0 : min(k0, H - 4)), 4);
 #pragma unroll
-                for (int j = 0; j < 4; ++j) acc = mfma_16x16x4(a[i][j], real ? b[i][j] : 0.0f, acc);
+                for (int j = 0; j < 4; ++j) a[i][j] = piece_value(x, j);
+            } else {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) a[i][j] = head_input<BF>(p.in, a_row + min(k0 + j, H - 1));
             }
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int c = 0; c < CT; ++c) b[i][j][c] = Xg[at.at((uint32_t)(MODE == HL_WHOLE ? k0 + j : min(k0 + j, H - 1)) * (uint32_t)C + wcol[c])];
+        }
+    };
+    // what the softmax needs is asked for behind the first requests and waited for after the products: sixteen lanes per row
+    const int row = (t >> 4) & 15, l16 = t & 15, b_row = 16 * rt + row;
+    const int32_t drawn = p.idx[(size_t)g * B + min(b_row, B - 1)];
+    if (s_begin < s_end) request(s_begin);
+    __builtin_amdgcn_sched_barrier(0);
+    const int y = p.labels[p.row0[g] + drawn];
+    float bias[CT];
+#pragma unroll
+    for (int c = 0; c < CT; ++c) bias[c] = Xg[at.at((uint32_t)(H * C + min(16 * c + l16, C - 1)))];
+    __builtin_amdgcn_sched_barrier(0);
+    for (int s0 = s_begin; s0 < s_end; s0 += HD_STEPS) {
+#pragma unroll
+        for (int i = 0; i < HD_STEPS; ++i)
+            if (s0 + i < s_end) {
+                const int left = MODE == HL_WHOLE ? 4 : H - 16 * (s0 + i) - 4 * q;      // columns of W past the classes are never looked at
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+#pragma unroll
+                    for (int c = 0; c < CT; ++c)
+                        acc[c] = mfma_16x16x4(j < left ? a[i][j] : 0.0f, j < left ? head_operand<BF>(b[i][j][c]) : 0.0f, acc[c]);
+            }
+        __builtin_amdgcn_sched_barrier(0);
+        if (s0 + HD_STEPS < s_end) request(s0 + HD_STEPS);
+        __builtin_amdgcn_sched_barrier(0);
     }
 #pragma unroll
-    for (int v = 0; v < 4; ++v) part[kp][4 * q + v][r] = acc[v];
+    for (int c = 0; c < CT; ++c)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) part[kp][4 * q + v][16 * c + r] = acc[c][v];
     __syncthreads();
-    // the parts added in order, bias, softmax cross-entropy: sixteen lanes per batch row, one class each
-    const int row = t >> 4, c = t & 15, b_row = 16 * rt + row;
-    const bool cls = c < C;
-    const float bias = p.X[tiled_offset(p.M, g, p.woff + (int64_t)H * C + (cls ? c : 0))];
-    const int y = p.labels[p.row0[g] + p.idx[(size_t)g * B + b_row]];
-    float z = ((part[0][row][c] + part[1][row][c]) + part[2][row][c]) + part[3][row][c];
-    z = cls ? z + bias : -INFINITY;
-    float mx = z;
+    // the parts added in order, bias, softmax cross-entropy: sixteen lanes per batch row, CT classes each
+    if (t >= 256) return;
+    float z[CT], mx = -INFINITY;
+    bool cls[CT];
+#pragma unroll
+    for (int c = 0; c < CT; ++c) {
+        const int k = 16 * c + l16;
+        cls[c] = k < C;
+        float sum = part[0][row][k];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) sum += part[w][row][k];
+        z[c] = cls[c] ? sum + bias[c] : -INFINITY;
+        mx = fmaxf(mx, z[c]);
+    }
 #pragma unroll
     for (int m = 1; m < 16; m <<= 1) mx = fmaxf(mx, __shfl_xor(mx, m, 16));
-    const float ex = cls ? expf(z - mx) : 0.0f;
-    float sum = ex;
+    float ex[CT], sum = 0.0f;
+#pragma unroll
+    for (int c = 0; c < CT; ++c) {
+        ex[c] = cls[c] ? expf(z[c] - mx) : 0.0f;
+        sum += ex[c];
+    }
 #pragma unroll
     for (int m = 1; m < 16; m <<= 1) sum += __shfl_xor(sum, m, 16);
-    if (cls) {
-        const size_t e = ((size_t)g * B + b_row) * C + c;
-        p.logits[e] = z;
-        p.dz[e] = (ex * (1.0f / sum) - (c == y ? 1.0f : 0.0f)) * (1.0f / (float)B);
+    if (b_row >= B) return;
+#pragma unroll
+    for (int c = 0; c < CT; ++c) {
+        const int k = 16 * c + l16;
+        if (cls[c]) p.dz[((size_t)g * B + b_row) * C + k] = (ex[c] * (1.0f / sum) - (k == y ? 1.0f : 0.0f)) * (1.0f / (float)B);
+        if (k == y) p.row_loss[(size_t)g * B + b_row] = logf(sum) - (z[c] - mx);
     }
-    if (c == y) p.row_loss[(size_t)g * B + b_row] = logf(sum) - (z - mx);
 }
 
-// RT: 16-row tiles of the batch (1, 2 or 4).  Grid: (ceil(H / 64), workers).
-template <int RT>
+// RT: 16-row tiles of the batch (1, 2, 4, 8 or 16; rows past the batch count as zeros).  CT: tiles of sixteen classes.  FIRST: the
+// only layer (softmax regression): no error for a layer below.  Grid: (ceil(H / 64), workers).
+template <bool BF, int RT, int CT, bool FIRST>
 __global__ void __launch_bounds__(HD_THREADS) head_grads_kernel(HeadArgs p)
 {
-    constexpr int B = 16 * RT, tp = B + 16;      // tp: pitch of the transposed dZ, rows 16 apart in banks
-    __shared__ float dzs[B][HD_ZP];              // dZ, columns C .. 15 zero
-    __shared__ float dzt[HD_CP][tp];             // its transpose
-    const int H = p.H, C = p.C;
+    constexpr int BP = 16 * RT, CP = 16 * CT, tp = BP + 16;      // tp: pitch of the transposed dZ, rows 16 apart in banks
+    constexpr int ZP = CP + 4;                   // floats per row of dZ: the four row groups that a wave reads at once differ in banks
+    __shared__ float dzs[BP][ZP];                // dZ, columns C .. and rows B .. zero
+    __shared__ float dzt[FIRST ? 1 : CP][tp];    // its transpose
+    const int B = p.B, H = p.H, C = p.C;
     const int g = blockIdx.y, t = threadIdx.x, lane = t & 63, r = lane & 15, q = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const bool first = blockIdx.x == 0;          // the workgroup that also writes what does not split by hidden units
-    const int KT = H >> 4, kt = (int)blockIdx.x * HD_WAVES + wave;
+    const int KT = (H + 15) / 16, kt = (int)blockIdx.x * HD_WAVES + wave;
     const int ktc = kt < KT ? kt : 0;            // waves past the end repeat the first block and store nothing
-    const float *hg = p.h + (size_t)g * B * H;
-    float *dhg = p.dh + (size_t)g * B * H;
-    const int64_t boff = p.woff + (int64_t)H * C;
-    // requests: this wave's 16 columns of h (all batch rows), its 16 rows of W, and dZ
-    float hv[RT][4];                             // h[16 i + 4 q + v][16 kt + r]
+    const int hc = 16 * ktc + r < H ? 16 * ktc + r : H - 1;
+    const HeadParams at(p.M, g, p.woff);
+    const float *Xg = p.X + at.base;
+    float *Gg = p.G + at.base;
+    // requests: this wave's 16 columns of the input (all batch rows; gathered rows by number first), its 16 rows of W, and dZ.
+    // Rows past the batch repeat the last one and count as zeros.
+    float hv[RT][4];                             // in[16 i + 4 q + v][16 kt + r]
+    int32_t rows[RT][4];
+    const int32_t *row_of = p.idx + (size_t)g * B;
+    if (FIRST) {
 #pragma unroll
-    for (int i = 0; i < RT; ++i)
+        for (int i = 0; i < RT; ++i)
 #pragma unroll
-        for (int v = 0; v < 4; ++v) hv[i][v] = hg[(16 * i + 4 * q + v) * H + 16 * ktc + r];
-    float wv[4];                                 // W[16 kt + r][4 s + q]
+            for (int v = 0; v < 4; ++v) rows[i][v] = row_of[min(16 * i + 4 * q + v, B - 1)];
+    } else {
+        const int64_t base = (int64_t)g * B * H;
 #pragma unroll
-    for (int s = 0; s < 4; ++s) {
-        const float w = p.X[tiled_offset(p.M, g, p.woff + (int64_t)(16 * ktc + r) * C + (4 * s + q < C ? 4 * s + q : 0))];
-        wv[s] = 4 * s + q < C ? w : 0.0f;
+        for (int i = 0; i < RT; ++i)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) hv[i][v] = head_input<BF>(p.in, base + (uint32_t)(min(16 * i + 4 * q + v, B - 1) * H + hc));
     }
-    float zv[B * HD_CP / HD_THREADS];
+    float wv[4 * CT];                            // W[16 kt + r][4 s + q]
+    if constexpr (!FIRST) {
 #pragma unroll
-    for (int u = 0; u < B * HD_CP / HD_THREADS; ++u) {
-        const int e = t + u * HD_THREADS, row = e >> 4, c = e & 15;
-        const float d = p.dz[((size_t)g * B + row) * C + (c < C ? c : 0)];
-        zv[u] = c < C ? d : 0.0f;
+        for (int s = 0; s < 4 * CT; ++s) wv[s] = Xg[at.at((uint32_t)(hc * C + (4 * s + q < C ? 4 * s + q : 0)))];
+    }
+    float zv[BP * CP / HD_THREADS];
+    const float *zg = p.dz + (size_t)g * B * C;
+#pragma unroll
+    for (int u = 0; u < BP * CP / HD_THREADS; ++u) {
+        const int e = t + u * HD_THREADS, row = e / CP, c = e % CP;
+        zv[u] = zg[min(row, B - 1) * C + (c < C ? c : 0)];
+    }
+    if (FIRST) {
+        const int64_t base = p.row0[g] * H + hc;
+#pragma unroll
+        for (int i = 0; i < RT; ++i)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) hv[i][v] = head_input<BF>(p.in, base + (int64_t)rows[i][v] * H);
     }
     float lrow = 0.0f;
-    if (first && wave == 0) lrow = lane < B ? p.row_loss[(size_t)g * B + lane] : 0.0f;
+    if (first && wave == 0) {
 #pragma unroll
-    for (int u = 0; u < B * HD_CP / HD_THREADS; ++u) {
-        const int e = t + u * HD_THREADS, row = e >> 4, c = e & 15;
-        dzs[row][c] = zv[u];
-        dzt[c][row] = zv[u];
+        for (int u = 0; u < (BP + 63) / 64; ++u) {
+            const int b = 64 * u + lane;
+            const float l = p.row_loss[(size_t)g * B + (b < B ? b : B - 1)];
+            lrow += b < B ? l : 0.0f;
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < BP * CP / HD_THREADS; ++u) {
+        const int e = t + u * HD_THREADS, row = e / CP, c = e % CP;
+        const float d = c < C && row < B ? zv[u] : 0.0f;
+        dzs[row][c] = d;
+        if constexpr (!FIRST) dzt[c][row] = head_operand<BF>(d);
     }
     __syncthreads();
     if (first) {
@@ -154,82 +257,126 @@ __global__ void __launch_bounds__(HD_THREADS) head_grads_kernel(HeadArgs p)
             if (lane == 0) p.loss[g] = lrow / (float)B;
         }
         for (int64_t e = t; e < p.ld - p.D; e += HD_THREADS) p.G[tiled_offset(p.M, g, p.D + e)] = 0.0f;
-        // db = column sums of dZ: the product below with a row of ones in place of h^T
+        // db = column sums of dZ: the product below with a row of ones in place of h^T (never rounded)
         if (wave == HD_WAVES - 1) {
-            f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
             const float one = r == 0 ? 1.0f : 0.0f;
 #pragma unroll
-            for (int s = 0; s < B / 4; ++s) acc = mfma_16x16x4(one, dzs[4 * s + q][r], acc);
-            if (q == 0 && r < C) p.G[tiled_offset(p.M, g, boff + r)] = acc[0];
+            for (int c = 0; c < CT; ++c) {
+                f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+                for (int s = 0; s < BP / 4; ++s) acc = mfma_16x16x4(one, dzs[4 * s + q][16 * c + r], acc);
+                if (q == 0 && 16 * c + r < C) Gg[at.at((uint32_t)(H * C + 16 * c + r))] = acc[0];
+            }
         }
     }
     if (kt >= KT) return;
+#pragma unroll
+    for (int i = 0; i < RT; ++i)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) hv[i][v] = 16 * i + 4 * q + v < B ? hv[i][v] : 0.0f;
     // ---- dW = h^T dZ, rows 16 kt .. 16 kt + 15: the batch is the contraction, taken in the order in which the lanes hold h
-    {
+#pragma unroll
+    for (int c = 0; c < CT; ++c) {
         f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
         for (int i = 0; i < RT; ++i)
 #pragma unroll
-            for (int v = 0; v < 4; ++v) acc = mfma_16x16x4(hv[i][v], dzs[16 * i + 4 * q + v][r], acc);
-        if (r < C) {
+            for (int v = 0; v < 4; ++v) acc = mfma_16x16x4(hv[i][v], head_operand<BF>(dzs[16 * i + 4 * q + v][16 * c + r]), acc);
+        if (16 * c + r < C) {
 #pragma unroll
-            for (int v = 0; v < 4; ++v) p.G[tiled_offset(p.M, g, p.woff + (int64_t)(16 * kt + 4 * q + v) * C + r)] = acc[v];
+            for (int v = 0; v < 4; ++v)
+                if (16 * kt + 4 * q + v < H) Gg[at.at((uint32_t)((16 * kt + 4 * q + v) * C + 16 * c + r))] = acc[v];
         }
     }
     // ---- dH = (dZ W^T) where h > 0, columns 16 kt .. 16 kt + 15 of all batch rows, and its column sums
-    {
+    if constexpr (!FIRST) {
+#pragma unroll
+        for (int s = 0; s < 4 * CT; ++s) wv[s] = 4 * s + q < C ? head_operand<BF>(wv[s]) : 0.0f;
+        const bool col_ok = 16 * kt + r < H;
+        float *dhg = p.dh + (size_t)g * B * H;
         float colsum = 0.0f;
 #pragma unroll
         for (int i = 0; i < RT; ++i) {
             f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-            for (int s = 0; s < 4; ++s) acc = mfma_16x16x4(dzt[4 * s + q][16 * i + r], wv[s], acc);
+            for (int s = 0; s < 4 * CT; ++s) acc = mfma_16x16x4(dzt[4 * s + q][16 * i + r], wv[s], acc);
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
+                const int b = 16 * i + 4 * q + v;
                 const float d = hv[i][v] > 0.0f ? acc[v] : 0.0f;
-                dhg[(16 * i + 4 * q + v) * H + 16 * kt + r] = d;
+                if (col_ok && b < B) dhg[(uint32_t)(b * H + 16 * kt + r)] = d;
                 colsum += d;
             }
         }
         colsum += __shfl_xor(colsum, 16);
         colsum += __shfl_xor(colsum, 32);
-        if (q == 0) p.G[tiled_offset(p.M, g, p.boff_below + 16 * kt + r)] = colsum;
+        if (q == 0 && col_ok) p.G[tiled_offset_quick(p.M, g, p.boff_below + 16 * kt + r)] = colsum;
     }
 }
 
-// fp32 operands, a hidden layer below, at most 16 classes, a batch of 16, 32 or 64 rows, and a hidden width that the
-// four waves of the logits kernel divide evenly in steps of sixteen.
+// At most 32 classes and 256 batch rows.  With bfloat16 operands the matrix-core kernels go first where they fit, and a
+// matrix-core layer below wants the error as bfloat16 in both orientations, which these kernels do not write.
 bool head_ok(const MlpPlan &p)
 {
     const int L = p.n_layers;
-    if (p.bf16 || L < 2 || p.M > 65535) return false;
-    const int64_t H = p.dims[L - 1], C = p.dims[L];
-    const int B = p.B;
-    if (C < 1 || C > HD_CP) return false;
-    if (B != 16 && B != 32 && B != 64) return false;
-    return H >= 64 && H <= HD_MAX_H && H % (16 * HD_WAVES) == 0;
+    if (p.dims[L] > HD_MAX_C || p.B > HD_MAX_B) return false;
+    // 32-bit element numbers inside the layer's span of the tile layout and inside a worker's activations
+    const int64_t H = p.dims[L - 1], tiles = (H * p.dims[L] + p.dims[L]) / TILE + 2;
+    if (tiles * p.M * TILE >= (int64_t)1 << 32 || H * p.B >= (int64_t)1 << 31) return false;
+    return !p.bf16 || !(mfma_small_last_ok(p) || (L > 1 && mfma_layer_ok(p, L - 2)));
 }
 
-hipError_t prepare_head() { return hipSuccess; }
+template <bool BF, int CT, int NW> static void launch_logits_waves(hipStream_t s, const HeadArgs &a)
+{
+    const dim3 grid((unsigned)((a.B + 15) / 16), (unsigned)a.M), block(64 * NW);
+    // pieces of four features need rows that start at multiples of their size
+    const bool pieces = a.H % 4 == 0 && reinterpret_cast<uintptr_t>(a.in) % (BF ? 8 : 16) == 0;
+    if (pieces && a.H % 16 == 0) hipLaunchKernelGGL((head_logits_kernel<BF, HL_WHOLE, CT, NW>), grid, block, 0, s, a);
+    else if (pieces) hipLaunchKernelGGL((head_logits_kernel<BF, HL_PIECES, CT, NW>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((head_logits_kernel<BF, HL_SINGLE, CT, NW>), grid, block, 0, s, a);
+}
+template <bool BF, int CT> static void launch_logits(hipStream_t s, const HeadArgs &a)
+{
+    if ((a.H + 15) / 16 <= HL_FEW * HD_STEPS) launch_logits_waves<BF, CT, HL_FEW>(s, a);
+    else launch_logits_waves<BF, CT, HL_MANY>(s, a);
+}
+
+template <bool BF, int CT, bool FIRST> static void launch_grads(hipStream_t s, const HeadArgs &a)
+{
+    const dim3 grid((unsigned)(((a.H + 15) / 16 + HD_WAVES - 1) / HD_WAVES), (unsigned)a.M), block(HD_THREADS);
+    if (a.B <= 16) hipLaunchKernelGGL((head_grads_kernel<BF, 1, CT, FIRST>), grid, block, 0, s, a);
+    else if (a.B <= 32) hipLaunchKernelGGL((head_grads_kernel<BF, 2, CT, FIRST>), grid, block, 0, s, a);
+    else if (a.B <= 64) hipLaunchKernelGGL((head_grads_kernel<BF, 4, CT, FIRST>), grid, block, 0, s, a);
+    else if (a.B <= 128) hipLaunchKernelGGL((head_grads_kernel<BF, 8, CT, FIRST>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((head_grads_kernel<BF, 16, CT, FIRST>), grid, block, 0, s, a);
+}
+
+template <bool BF, int CT> static void launch_both(hipStream_t s, const HeadArgs &a, bool only_layer)
+{
+    launch_logits<BF, CT>(s, a);
+    if (only_layer) launch_grads<BF, CT, true>(s, a);
+    else launch_grads<BF, CT, false>(s, a);
+}
 
 void launch_head(hipStream_t s, const MlpPlan &p, const float *X, float *G)
 {
     const int L = p.n_layers;
     HeadArgs a;
-    a.h = p.act[L - 1]; a.X = X; a.G = G; a.labels = p.labels; a.row0 = p.row0; a.idx = p.idx;
-    a.logits = p.act[L]; a.dz = p.dz[0]; a.dh = p.dz[1]; a.loss = p.loss;
+    a.in = L == 1 ? p.feats : (p.bf16 ? (const void *)p.hb[L - 1] : (const void *)p.act[L - 1]);
+    a.row0 = p.row0; a.idx = p.idx; a.gather = L == 1;
+    a.X = X; a.G = G; a.labels = p.labels;
+    a.dz = p.dz[0]; a.dh = p.dz[1]; a.loss = p.loss;
+    a.row_loss = p.act[L];          // [M][B][C], not used for the logits on this path
     a.M = p.M; a.B = p.B; a.H = (int)p.dims[L - 1]; a.C = (int)p.dims[L];
-    a.row_loss = p.dz[0] + (size_t)p.M * p.B * a.C;          // behind dZ: the buffer holds M x B x (widest layer) floats
     a.woff = p.woff[L - 1];
-    a.boff_below = p.woff[L - 2] + p.dims[L - 2] * p.dims[L - 1];
+    a.boff_below = L == 1 ? 0 : p.woff[L - 2] + p.dims[L - 2] * p.dims[L - 1];
     a.D = p.woff[L - 1] + p.dims[L - 1] * p.dims[L] + p.dims[L]; a.ld = p.ld;
-    const dim3 block(HD_THREADS);
-    hipLaunchKernelGGL(head_logits_kernel, dim3((unsigned)(a.B / 16), (unsigned)p.M), block, 0, s, a);
-    const dim3 grid((unsigned)((a.H / 16 + HD_WAVES - 1) / HD_WAVES), (unsigned)p.M);
-    switch (a.B / 16) {
-    case 1: hipLaunchKernelGGL(head_grads_kernel<1>, grid, block, 0, s, a); break;
-    case 2: hipLaunchKernelGGL(head_grads_kernel<2>, grid, block, 0, s, a); break;
-    default: hipLaunchKernelGGL(head_grads_kernel<4>, grid, block, 0, s, a); break;
+    if (p.bf16) {
+        if (a.C <= 16) launch_both<true, 1>(s, a, L == 1);
+        else launch_both<true, 2>(s, a, L == 1);
+    } else {
+        if (a.C <= 16) launch_both<false, 1>(s, a, L == 1);
+        else launch_both<false, 2>(s, a, L == 1);
     }
 }
 

@@ -229,7 +229,8 @@ void launch_mlp_grad(hipStream_t s, const MlpPlan &p, const float *X, float *G, 
     if (head) {
         // logits, loss, the last layer's gradient and the error of the last hidden layer (with its column sums)
         launch_head(s, p, X, G);
-        bias_done[L - 1] = bias_done[L - 2] = true;
+        bias_done[L - 1] = true;
+        if (L > 1) bias_done[L - 2] = true;
         l_top = L - 2;
         cur = 1;
     } else {

@@ -184,10 +184,9 @@ void launch_tile_fwd(hipStream_t s, const MlpPlan &p, int l, const float *X, boo
 bool launch_tile_dgrad(hipStream_t s, const MlpPlan &p, int l, const float *X, float *G, int cur, bool below_fast);
 void launch_tile_wgrad(hipStream_t s, const MlpPlan &p, int l, float *G, int cur);
 
-// Last layer with at most 16 classes on fp32 operands above a hidden layer (k_grad_head.hip): one kernel from the
-// last hidden activation to the error of that layer: logits, loss, dW, db, dH and the column sums of dH.
+// Last layer with at most 32 classes, fp32 or bfloat16 operands (k_grad_head.hip): from its input to the error of the layer
+// below in two kernels: logits, loss, dW, db, dH and the column sums of dH.
 bool head_ok(const MlpPlan &p);
-hipError_t prepare_head();
 void launch_head(hipStream_t s, const MlpPlan &p, const float *X, float *G);
 
 }  // namespace netmax

@@ -58,9 +58,12 @@ template <bool V> __device__ __forceinline__ Piece<true> load_piece(const uint16
     return r;
 }
 
-// Element e of a loaded piece as fp32 / as 16 bits.
+// Element e of a loaded piece as fp32, as 16 bits, as the value of either kind.
 __device__ __forceinline__ float piece_f32(const Piece<false> &p, int e) { return p.v[e]; }
 __device__ __forceinline__ uint32_t piece_bits(const Piece<true> &p, int e) { return (p.v[e >> 1] >> (16 * (e & 1))) & 0xFFFFu; }
+
+__device__ __forceinline__ float piece_value(const Piece<false> &p, int e) { return p.v[e]; }
+__device__ __forceinline__ float piece_value(const Piece<true> &p, int e) { return __uint_as_float(piece_bits(p, e) << 16); }
 
 template <bool BF, int BK> struct TileLds {
     typedef float elem;
