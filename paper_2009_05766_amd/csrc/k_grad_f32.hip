@@ -13,7 +13,9 @@
 //
 // Weight gradient, dW = A^T dZ: a workgroup takes 32 rows of dW (32 input features) of one worker; the strip of A^T
 // stays in registers (batch / 2 values per lane) and each wave multiplies it with 32-column blocks of dZ, read
-// straight into the instruction's layout as 128-byte row pieces; the result leaves as 128-byte row pieces.
+// straight into the instruction's layout as 128-byte row pieces; the result leaves as 128-byte row pieces.  With UPDATE it is
+// turned through LDS and the momentum step and the mix (Eq. (c0), (c1)) are applied to it, x, v and the peer's x asked for ahead of
+// the products: 784 x 512, batch 64, 16 workers 31 us, against 21.6 us and 21.4 us for the separate mix.
 #include "kernels.h"
 #include "layout.h"
 #include "vec.h"
@@ -31,6 +33,7 @@ struct LayerF32Args {
     float *out;                                                    // forward: [M][B][dout]
     int64_t woff, din, dout;
     int M, B, relu, gather;
+    MixArgs mix;                                                   // wgrad_f32_kernel<UPDATE>
 };
 
 __device__ __forceinline__ const float *input_row(const LayerF32Args &p, int g, int b)
@@ -140,9 +143,10 @@ static size_t fwd_f32_lds(int RT)
 // HB = batch / 2: values of the A^T strip per lane.  Grid: grouped_grid(workers, ceil(din / 32) * ceil(dout / (32 * 4 * WG32_TILES)));
 // a wave takes WG32_TILES 32 x 32 blocks of dW, four blocks apart, with the same strip of A^T.
 constexpr int WG32_THREADS = 256, WG32_WAVES = WG32_THREADS / 64, WG32_TILES = 2;
-template <int HB, bool GATHER>
+template <int HB, bool GATHER, bool UPDATE>
 __global__ void __launch_bounds__(WG32_THREADS) wgrad_f32_kernel(LayerF32Args p)
 {
+    __shared__ __attribute__((aligned(16))) float turn[UPDATE ? WG32_WAVES : 1][32][F32_COLS + 4];   // UPDATE: a wave's block, to be read by rows
     const int t = threadIdx.x, lane = t & 63, col = lane & 31, half = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int nct = (int)(p.dout / F32_COLS);
@@ -172,8 +176,31 @@ __global__ void __launch_bounds__(WG32_THREADS) wgrad_f32_kernel(LayerF32Args p)
 #pragma unroll
         for (int j = 0; j < HB; ++j) a[j] = base[(size_t)(2 * j) * p.din];
     }
+    int m = g;
+    float wi = 0.0f;
+    if constexpr (UPDATE) {
+        m = p.mix.peer[g];
+        if ((unsigned)m >= (unsigned)p.M) m = g;                  // an index outside [0, M) is treated as a self draw
+        wi = p.mix.w[(size_t)g * p.M + m];
+    }
+    // UPDATE: eight lanes along the 32 columns of a row, 128-bit pieces, eight rows per pass
+    const int uc = (lane & 7) * 4, ur = lane >> 3;
     __builtin_amdgcn_sched_barrier(0);               // every load is requested before the first product waits for one
     for (int ct = ct0; ct < nct && ct < ct0 + WG32_WAVES * WG32_TILES; ct += WG32_WAVES) {
+        f32x4 ux[4], up[4], uv[4];
+        size_t own[4];
+        if constexpr (UPDATE) {                      // travels while the block is multiplied
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int64_t fr = f0 + 8 * u + ur < p.din ? f0 + 8 * u + ur : p.din - 1;
+                const int64_t j = p.woff + fr * p.dout + ct * F32_COLS + uc;
+                own[u] = tiled_offset(p.M, g, j);
+                ux[u] = load4(p.mix.Xcur + own[u]);
+                uv[u] = load4(p.mix.V + own[u]);
+                up[u] = load4(p.mix.Xcur + tiled_offset(p.M, m, j));
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
         f32x16 acc;
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
@@ -185,10 +212,28 @@ __global__ void __launch_bounds__(WG32_THREADS) wgrad_f32_kernel(LayerF32Args p)
             for (int j = 0; j < HB; ++j) b[j] = zbase[(size_t)(2 * j) * p.dout + next * F32_COLS];
         }
         __builtin_amdgcn_sched_barrier(0);           // the next block's loads go out before this block's stores
+        if constexpr (UPDATE) {
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const int64_t fr = f0 + 8 * (v >> 2) + 4 * half + (v & 3);
-            if (fr < p.din) p.G[tiled_offset(p.M, g, p.woff + fr * p.dout + ct * F32_COLS + col)] = acc[v];
+            for (int v = 0; v < 16; ++v) turn[wave][8 * (v >> 2) + 4 * half + (v & 3)][col] = acc[v];
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const f32x4 gr = *reinterpret_cast<const f32x4 *>(&turn[wave][8 * u + ur][uc]);
+                f32x4 xn, vn;
+                momentum_mix4(ux[u], uv[u], gr, up[u], wi, p.mix.alpha, p.mix.mu, p.mix.wd, xn, vn);
+                if (f0 + 8 * u + ur < p.din) {
+                    store4(p.G + own[u], gr);
+                    store4(p.mix.Xnext + own[u], xn);
+                    store4(p.mix.V + own[u], vn);
+                }
+            }
+            __builtin_amdgcn_wave_barrier();
+        } else {
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int64_t fr = f0 + 8 * (v >> 2) + 4 * half + (v & 3);
+                if (fr < p.din) p.G[tiled_offset(p.M, g, p.woff + fr * p.dout + ct * F32_COLS + col)] = acc[v];
+            }
         }
     }
 }
@@ -233,19 +278,24 @@ void launch_fwd_f32(hipStream_t s, const MlpPlan &p, int l, const float *X)
     else hipLaunchKernelGGL(fwd_f32_kernel<2>, grid, block, fwd_f32_lds(2), s, a);
 }
 
-void launch_wgrad_f32(hipStream_t s, const MlpPlan &p, int l, float *G, const float *dz)
+template <int HB> static void launch_wgrad_half(hipStream_t s, const LayerF32Args &a, dim3 grid, bool update)
 {
-    const LayerF32Args a = layer_f32_args(p, l, nullptr, G, dz);
+    const dim3 block(WG32_THREADS);
+    if (a.gather && update) hipLaunchKernelGGL((wgrad_f32_kernel<HB, true, true>), grid, block, 0, s, a);
+    else if (a.gather) hipLaunchKernelGGL((wgrad_f32_kernel<HB, true, false>), grid, block, 0, s, a);
+    else if (update) hipLaunchKernelGGL((wgrad_f32_kernel<HB, false, true>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((wgrad_f32_kernel<HB, false, false>), grid, block, 0, s, a);
+}
+
+void launch_wgrad_f32(hipStream_t s, const MlpPlan &p, int l, float *G, const float *dz, const MixArgs *tail)
+{
+    LayerF32Args a = layer_f32_args(p, l, nullptr, G, dz);
+    if (tail) a.mix = *tail;
     const int nct = (int)(a.dout / F32_COLS);
     const int per_group = WG32_WAVES * WG32_TILES;
-    const dim3 grid(grouped_grid(p.M, (unsigned)((a.din + 31) / 32) * (unsigned)((nct + per_group - 1) / per_group))), block(WG32_THREADS);
-    if (p.B == 32) {
-        if (a.gather) hipLaunchKernelGGL((wgrad_f32_kernel<16, true>), grid, block, 0, s, a);
-        else hipLaunchKernelGGL((wgrad_f32_kernel<16, false>), grid, block, 0, s, a);
-    } else {
-        if (a.gather) hipLaunchKernelGGL((wgrad_f32_kernel<32, true>), grid, block, 0, s, a);
-        else hipLaunchKernelGGL((wgrad_f32_kernel<32, false>), grid, block, 0, s, a);
-    }
+    const dim3 grid(grouped_grid(p.M, (unsigned)((a.din + 31) / 32) * (unsigned)((nct + per_group - 1) / per_group)));
+    if (p.B == 32) launch_wgrad_half<16>(s, a, grid, tail != nullptr);
+    else launch_wgrad_half<32>(s, a, grid, tail != nullptr);
 }
 
 }  // namespace netmax

@@ -14,7 +14,8 @@
 //
 // so that h is read once by each, by many compute units (one kernel that did everything per worker had a single
 // compute unit pull 200 KB and took 14.6 us at 16 workers, 512 hidden units; these take 4.6 and 4.8 us).  Softmax regression on
-// 784 features, 16 workers, batch 64: 6.2 and 4.2 us in place of three kernels of 15.0, 9.3 and 6.2 us; 1024 hidden units, 32
+// 784 features, 16 workers, batch 64: 6.2 and 4.2 us (5.2 us with the update of all columns, which
+// saves the mix kernel's 3.1 us and its launch) in place of three kernels of 15.0, 9.3 and 6.2 us; 1024 hidden units, 32
 // workers, batch 128: 10 and 14 us in place of five kernels of 16, 12, 12, 17 and 16 us.
 // The products run on v_mfma_f32_16x16x4_f32 with the classes padded to one or two 16-wide tiles (lane l
 // supplies A[l % 16][l / 16] and B[l / 16][l % 16] and receives D[4 (l / 16) + v][l % 16], v = 0..3); bfloat16 operands are
@@ -46,6 +47,7 @@ struct HeadArgs {
     int64_t woff;                   // W [H][C] of the last layer inside a parameter row, its bias behind it
     int64_t boff_below;             // bias of the layer below
     int64_t D, ld;
+    MixArgs mix;                    // UPDATE
 };
 
 __device__ __forceinline__ f32x4 mfma_16x16x4(float a, float b, f32x4 acc) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, acc, 0, 0, 0); }
@@ -179,8 +181,9 @@ __global__ void __launch_bounds__(64 * NW) head_logits_kernel(HeadArgs p)
 }
 
 // RT: 16-row tiles of the batch (1, 2, 4, 8 or 16; rows past the batch count as zeros).  CT: tiles of sixteen classes.  FIRST: the
-// only layer (softmax regression): no error for a layer below.  Grid: (ceil(H / 64), workers).
-template <bool BF, int RT, int CT, bool FIRST>
+// only layer (softmax regression): no error for a layer below.  UPDATE (then it is
+// the only layer): the momentum step and the mix (Eq. (c0), (c1)) are applied to every column of the worker.  Grid: (ceil(H / 64), workers).
+template <bool BF, int RT, int CT, bool FIRST, bool UPDATE>
 __global__ void __launch_bounds__(HD_THREADS) head_grads_kernel(HeadArgs p)
 {
     constexpr int BP = 16 * RT, CP = 16 * CT, tp = BP + 16;      // tp: pitch of the transposed dZ, rows 16 apart in banks
@@ -196,7 +199,6 @@ __global__ void __launch_bounds__(HD_THREADS) head_grads_kernel(HeadArgs p)
     const int hc = 16 * ktc + r < H ? 16 * ktc + r : H - 1;
     const HeadParams at(p.M, g, p.woff);
     const float *Xg = p.X + at.base;
-    float *Gg = p.G + at.base;
     // requests: this wave's 16 columns of the input (all batch rows; gathered rows by number first), its 16 rows of W, and dZ.
     // Rows past the batch repeat the last one and count as zeros.
     float hv[RT][4];                             // in[16 i + 4 q + v][16 kt + r]
@@ -233,6 +235,32 @@ __global__ void __launch_bounds__(HD_THREADS) head_grads_kernel(HeadArgs p)
 #pragma unroll
             for (int v = 0; v < 4; ++v) hv[i][v] = head_input<BF>(p.in, base + (int64_t)rows[i][v] * H);
     }
+    // UPDATE: what it needs of this lane's parameters is asked for behind the operands and used after the products
+    int m = g;
+    float wi = 0.0f;
+    size_t peer_shift = 0;
+    float ux[CT][4], up[CT][4], uv[CT][4];
+    auto update = [&](size_t own, float x, float v, float d, float xp) {
+        float xn, vn;
+        momentum_mix1(x, v, d, xp, wi, p.mix.alpha, p.mix.mu, p.mix.wd, xn, vn);
+        p.mix.Xnext[own] = xn;
+        p.mix.V[own] = vn;
+    };
+    if constexpr (UPDATE) {
+        m = p.mix.peer[g];
+        if ((unsigned)m >= (unsigned)p.M) m = g;              // an index outside [0, M) is treated as a self draw
+        wi = p.mix.w[(size_t)g * p.M + m];
+        peer_shift = ((size_t)m - (size_t)g) << TILE_SHIFT;   // from a worker's element to its peer's
+#pragma unroll
+        for (int c = 0; c < CT; ++c)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const size_t own = at.base + at.at((uint32_t)(min(16 * ktc + 4 * q + v, H - 1) * C + min(16 * c + r, C - 1)));
+                ux[c][v] = p.mix.Xcur[own];
+                up[c][v] = p.mix.Xcur[own + peer_shift];
+                uv[c][v] = p.mix.V[own];
+            }
+    }
     float lrow = 0.0f;
     if (first && wave == 0) {
 #pragma unroll
@@ -256,7 +284,11 @@ __global__ void __launch_bounds__(HD_THREADS) head_grads_kernel(HeadArgs p)
             for (int m = 32; m > 0; m >>= 1) lrow += __shfl_xor(lrow, m);
             if (lane == 0) p.loss[g] = lrow / (float)B;
         }
-        for (int64_t e = t; e < p.ld - p.D; e += HD_THREADS) p.G[tiled_offset(p.M, g, p.D + e)] = 0.0f;
+        for (int64_t e = t; e < p.ld - p.D; e += HD_THREADS) {
+            const size_t own = tiled_offset_quick(p.M, g, p.D + e);
+            p.G[own] = 0.0f;
+            if constexpr (UPDATE) update(own, p.mix.Xcur[own], p.mix.V[own], 0.0f, p.mix.Xcur[own + peer_shift]);
+        }
         // db = column sums of dZ: the product below with a row of ones in place of h^T (never rounded)
         if (wave == HD_WAVES - 1) {
             const float one = r == 0 ? 1.0f : 0.0f;
@@ -265,7 +297,11 @@ __global__ void __launch_bounds__(HD_THREADS) head_grads_kernel(HeadArgs p)
                 f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
                 for (int s = 0; s < BP / 4; ++s) acc = mfma_16x16x4(one, dzs[4 * s + q][16 * c + r], acc);
-                if (q == 0 && 16 * c + r < C) Gg[at.at((uint32_t)(H * C + 16 * c + r))] = acc[0];
+                if (q == 0 && 16 * c + r < C) {
+                    const size_t own = at.base + at.at((uint32_t)(H * C + 16 * c + r));
+                    p.G[own] = acc[0];
+                    if constexpr (UPDATE) update(own, p.mix.Xcur[own], p.mix.V[own], acc[0], p.mix.Xcur[own + peer_shift]);
+                }
             }
         }
     }
@@ -285,7 +321,11 @@ __global__ void __launch_bounds__(HD_THREADS) head_grads_kernel(HeadArgs p)
         if (16 * c + r < C) {
 #pragma unroll
             for (int v = 0; v < 4; ++v)
-                if (16 * kt + 4 * q + v < H) Gg[at.at((uint32_t)((16 * kt + 4 * q + v) * C + 16 * c + r))] = acc[v];
+                if (16 * kt + 4 * q + v < H) {
+                    const size_t own = at.base + at.at((uint32_t)((16 * kt + 4 * q + v) * C + 16 * c + r));
+                    p.G[own] = acc[v];
+                    if constexpr (UPDATE) update(own, ux[c][v], uv[c][v], acc[v], up[c][v]);
+                }
         }
     }
     // ---- dH = (dZ W^T) where h > 0, columns 16 kt .. 16 kt + 15 of all batch rows, and its column sums
@@ -341,27 +381,29 @@ template <bool BF, int CT> static void launch_logits(hipStream_t s, const HeadAr
     else launch_logits_waves<BF, CT, HL_MANY>(s, a);
 }
 
-template <bool BF, int CT, bool FIRST> static void launch_grads(hipStream_t s, const HeadArgs &a)
+template <bool BF, int CT, bool FIRST, bool UPDATE> static void launch_grads(hipStream_t s, const HeadArgs &a)
 {
     const dim3 grid((unsigned)(((a.H + 15) / 16 + HD_WAVES - 1) / HD_WAVES), (unsigned)a.M), block(HD_THREADS);
-    if (a.B <= 16) hipLaunchKernelGGL((head_grads_kernel<BF, 1, CT, FIRST>), grid, block, 0, s, a);
-    else if (a.B <= 32) hipLaunchKernelGGL((head_grads_kernel<BF, 2, CT, FIRST>), grid, block, 0, s, a);
-    else if (a.B <= 64) hipLaunchKernelGGL((head_grads_kernel<BF, 4, CT, FIRST>), grid, block, 0, s, a);
-    else if (a.B <= 128) hipLaunchKernelGGL((head_grads_kernel<BF, 8, CT, FIRST>), grid, block, 0, s, a);
-    else hipLaunchKernelGGL((head_grads_kernel<BF, 16, CT, FIRST>), grid, block, 0, s, a);
+    if (a.B <= 16) hipLaunchKernelGGL((head_grads_kernel<BF, 1, CT, FIRST, UPDATE>), grid, block, 0, s, a);
+    else if (a.B <= 32) hipLaunchKernelGGL((head_grads_kernel<BF, 2, CT, FIRST, UPDATE>), grid, block, 0, s, a);
+    else if (a.B <= 64) hipLaunchKernelGGL((head_grads_kernel<BF, 4, CT, FIRST, UPDATE>), grid, block, 0, s, a);
+    else if (a.B <= 128) hipLaunchKernelGGL((head_grads_kernel<BF, 8, CT, FIRST, UPDATE>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((head_grads_kernel<BF, 16, CT, FIRST, UPDATE>), grid, block, 0, s, a);
 }
 
-template <bool BF, int CT> static void launch_both(hipStream_t s, const HeadArgs &a, bool only_layer)
+template <bool BF, int CT> static void launch_both(hipStream_t s, const HeadArgs &a, bool only_layer, bool update)
 {
     launch_logits<BF, CT>(s, a);
-    if (only_layer) launch_grads<BF, CT, true>(s, a);
-    else launch_grads<BF, CT, false>(s, a);
+    if (!only_layer) launch_grads<BF, CT, false, false>(s, a);
+    else if (update) launch_grads<BF, CT, true, true>(s, a);
+    else launch_grads<BF, CT, true, false>(s, a);
 }
 
-void launch_head(hipStream_t s, const MlpPlan &p, const float *X, float *G)
+void launch_head(hipStream_t s, const MlpPlan &p, const float *X, float *G, const MixArgs *tail)
 {
     const int L = p.n_layers;
     HeadArgs a;
+    a.mix = tail ? *tail : MixArgs{};
     a.in = L == 1 ? p.feats : (p.bf16 ? (const void *)p.hb[L - 1] : (const void *)p.act[L - 1]);
     a.row0 = p.row0; a.idx = p.idx; a.gather = L == 1;
     a.X = X; a.G = G; a.labels = p.labels;
@@ -372,11 +414,11 @@ void launch_head(hipStream_t s, const MlpPlan &p, const float *X, float *G)
     a.boff_below = L == 1 ? 0 : p.woff[L - 2] + p.dims[L - 2] * p.dims[L - 1];
     a.D = p.woff[L - 1] + p.dims[L - 1] * p.dims[L] + p.dims[L]; a.ld = p.ld;
     if (p.bf16) {
-        if (a.C <= 16) launch_both<true, 1>(s, a, L == 1);
-        else launch_both<true, 2>(s, a, L == 1);
+        if (a.C <= 16) launch_both<true, 1>(s, a, L == 1, tail != nullptr);
+        else launch_both<true, 2>(s, a, L == 1, tail != nullptr);
     } else {
-        if (a.C <= 16) launch_both<false, 1>(s, a, L == 1);
-        else launch_both<false, 2>(s, a, L == 1);
+        if (a.C <= 16) launch_both<false, 1>(s, a, L == 1, tail != nullptr);
+        else launch_both<false, 2>(s, a, L == 1, tail != nullptr);
     }
 }
 

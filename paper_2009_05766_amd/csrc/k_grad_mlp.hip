@@ -177,7 +177,25 @@ bias_grad_kernel(int M, int B, int64_t dout, const float *__restrict__ dz, int64
     if (rg == 0 && c < dout) G[tiled_offset(M, g, boff + c)] = ((part[0][lane_c] + part[1][lane_c]) + part[2][lane_c]) + part[3][lane_c];
 }
 
-void launch_mlp_grad(hipStream_t s, const MlpPlan &p, const float *X, float *G, const MixArgs *fuse)
+// A weight gradient on fp32 operands holds dW of most columns on its way to memory; applying the update there saves the read of g
+// and, for middling models, most of a launch.  x' goes to the other buffer and nobody else looks at these columns of v, so a
+// layer's update need not wait for the layers below.  Per iteration, with the separate mix and with the update in the kernels:
+// 3072-1024-10, batch 128, 32 workers 873 and 716 us, 64 workers 1725 and 1420 us; 784-512-10, 16 workers, batch 128 95 and 89 us,
+// batch 64 71 and 63 us.  Where it loses: models of a few hundred thousand parameters in all (256-256-10, 8 workers 26.0 and
+// 28.6 us: the mix costs 3 us and what is left of it still is a launch); rows of W that do not start at multiples of 16 bytes
+// (3001-999-10: 1118 and 1519 us); bfloat16 operands, whose products leave little to hide (784-500-300-10, 16 workers 106 and 113
+// us, 3000-1000-10, 128 workers 2354 and 2644 us; the matrix-core layers likewise).
+constexpr int64_t UPDATE_MIN_FLOATS = 1 << 21;       // M x ld
+int64_t update_end(const MlpPlan &p, int l)
+{
+    const bool head = head_ok(p);
+    if (p.n_layers == 1 && head) return p.ld;                        // the last-layer kernel updates everything
+    if (p.bf16 || (l == p.n_layers - 1 && head) || p.woff[l] % 4 != 0 || p.M * p.ld < UPDATE_MIN_FLOATS) return 0;
+    if (!wgrad_f32_ok(p, l) && !tile_wgrad_update_ok(p, l)) return 0;
+    return p.woff[l] + p.dims[l] * p.dims[l + 1];
+}
+
+void launch_mlp_grad(hipStream_t s, const MlpPlan &p, const float *X, float *G, const MixArgs *fuse, const MixArgs *tail)
 {
     const int L = p.n_layers;
     const bool bf = p.bf16 != 0;
@@ -185,6 +203,7 @@ void launch_mlp_grad(hipStream_t s, const MlpPlan &p, const float *X, float *G, 
     for (int l = 0; l < L; ++l) fast[l] = mfma_layer_ok(p, l);
     const bool small_last = mfma_small_last_ok(p);
     const bool head = head_ok(p);
+    auto tail_of = [&](int l) { return tail && update_end(p, l) > 0 ? tail : nullptr; };
     auto input_of = [&](int l) {
         LayerInput in;
         in.feats = p.feats; in.row0 = p.row0; in.idx = p.idx;
@@ -228,7 +247,7 @@ void launch_mlp_grad(hipStream_t s, const MlpPlan &p, const float *X, float *G, 
     int cur = 0, l_top = L - 1;
     if (head) {
         // logits, loss, the last layer's gradient and the error of the last hidden layer (with its column sums)
-        launch_head(s, p, X, G);
+        launch_head(s, p, X, G, L == 1 ? tail_of(0) : nullptr);
         bias_done[L - 1] = true;
         if (L > 1) bias_done[L - 2] = true;
         l_top = L - 2;
@@ -249,9 +268,9 @@ void launch_mlp_grad(hipStream_t s, const MlpPlan &p, const float *X, float *G, 
         } else if (l == L - 1 && small_last) {
             launch_wgrad_small(s, p, G, cur);
         } else if (wgrad_f32_ok(p, l)) {
-            launch_wgrad_f32(s, p, l, G, p.dz[cur]);
+            launch_wgrad_f32(s, p, l, G, p.dz[cur], tail_of(l));
         } else {
-            launch_tile_wgrad(s, p, l, G, cur);
+            launch_tile_wgrad(s, p, l, G, cur, tail_of(l));
         }
         if (!bias_done[l]) {
             hipLaunchKernelGGL(bias_grad_kernel, dim3((unsigned)((dout + 63) / 64), (unsigned)p.M), dim3(256), 0, s, p.M, p.B,

@@ -1,10 +1,18 @@
 // Weight gradient dW = A^T dZ of a layer of any shape for all workers (the stochastic gradient of Algorithm 2's first-step
 // update): the tiled kernel for what the kernels of k_grad_mfma.hip and k_grad_f32.hip do not take.
 //
-// A workgroup takes 64 input features and BN outputs of one worker; the contraction runs over the batch, both operands lie
-// across it in memory.  The block is turned through LDS and leaves as row pieces of BN floats.
-// 3072 x 1024, batch 128, 32 workers, fp32: 312 us (402 us with 64 x 64 blocks, 4-byte loads and 128-byte row pieces);
-// 784 x 500 and 500 x 300, batch 100, 16 workers, bfloat16: 22 us together (54 us with fp32 instructions).
+// A workgroup takes 64 input features and 128 outputs of one worker; the contraction runs over the batch, both operands lie
+// across it in memory.  The block is turned through LDS and leaves as row pieces of 128 floats.
+// 3072 x 1024, batch 128, 32 workers, fp32: 311 us (402 us with 64 x 64 blocks, 4-byte loads and 128-byte row pieces);
+// 784 x 500 and 500 x 300, batch 100, 16 workers, bfloat16: 21 us together (54 us with fp32 instructions).
+//
+// UPDATE (fp32 operands, aligned rows): the block's columns also get the momentum step and the mix (Eq. (c0), (c1)).  460 to 480
+// us at the first shape, 2.46 GB moved, against 311 us and 314 us for the separate mix.  Bound by how well the fp32 matrix
+// instructions (180 us) and the memory traffic (390 us at the mix kernel's rate) overlap.  What mattered, per iteration of that
+// network: blocks worker by worker (block by block over the workers, as the mix orders its tiles, fetches 2.0 instead of 1.25 GB:
+// every block's operands again); the blocks of a strip side by side and not one after the other in a workgroup (755 against 880
+// us: the pieces of a layout tile should leave together); x and v asked for behind the last operands, the peer's x behind the
+// products (716 us; all ahead of the operands of the second step 817 us, all behind the last operands 722 us).
 #include "tile.h"
 
 namespace netmax {
@@ -13,67 +21,63 @@ struct TileWgrad {
     const void *feats; const int64_t *row0; const int32_t *idx;      // first layer: gathered data rows
     const void *act;                                                  // else the activation below, [M][B][din]
     const float *dz; int M, B, din, dout; int64_t woff; float *G;
+    MixArgs mix;                                                      // UPDATE
 };
 
-constexpr int TW_BM = 64, TW_BK = 32, TW_THREADS = 256;
+constexpr int TW_BM = 64, TW_BN = 128, TW_BK = 64, TW_THREADS = 512;
 
-template <bool BF, bool VA, bool VZ, int BN>
-__global__ void __launch_bounds__(TW_THREADS) tile_wgrad_kernel(TileWgrad p)
+template <bool BF, bool VA, bool VZ, bool UPDATE>
+__global__ void __launch_bounds__(TW_THREADS, 4) tile_wgrad_kernel(TileWgrad p)
 {
-    constexpr int BM = TW_BM, BK = TW_BK, NT = TW_THREADS, CJ = BN / 64, K4 = BK / 4;
-    constexpr int BLOCKS_A = BM / 4 * K4, NB = BN / 4 * K4 / NT;      // 4 x 4 blocks
-    static_assert(BLOCKS_A == NT / 2 && NB * NT == BN / 4 * K4, "half a block of A per thread, whole ones of dZ");
+    static_assert(!UPDATE || VZ, "the update works on 128-bit pieces");
+    constexpr int BM = TW_BM, BN = TW_BN, BK = TW_BK, NT = TW_THREADS;
+    constexpr int A_BLOCKS = BM / 4 * (BK / 4);                       // 4 x 4 blocks of A per step: half a block per thread
+    static_assert(2 * A_BLOCKS == NT && BN / 4 * (BK / 4) == NT, "half a block of A and one of dZ per step and thread");
     typedef TileLds<BF, BK> L;
     typedef typename L::elem elem;
     constexpr int TP = BN + 4;                                        // floats per row of the staged result
     constexpr int OPERANDS = (BM + BN) * L::PITCH * (int)sizeof(elem), RESULT = BM * TP * 4;
     __shared__ __attribute__((aligned(16))) unsigned char smem[OPERANDS > RESULT ? OPERANDS : RESULT];
     elem (*As)[L::PITCH] = reinterpret_cast<elem (*)[L::PITCH]>(smem);
-    elem (*Bs)[L::PITCH] = reinterpret_cast<elem (*)[L::PITCH]>(smem + BM * L::PITCH * sizeof(elem));
+    elem (*Zs)[L::PITCH] = reinterpret_cast<elem (*)[L::PITCH]>(smem + BM * L::PITCH * sizeof(elem));
     float (*T)[TP] = reinterpret_cast<float (*)[TP]>(smem);
-    const int t = threadIdx.x, lane = t & 63, wave = t >> 6, wm = wave >> 1, wn = wave & 1;
-    const unsigned nblk = (unsigned)((p.dout + BN - 1) / BN), mblk = (unsigned)((p.din + BM - 1) / BM);
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6, wm = wave >> 2, wn = wave & 3;
+    const int nblk = (p.dout + BN - 1) / BN, mblk = (p.din + BM - 1) / BM;
     int g;
     unsigned local;
-    if (!decode_group(blockIdx.x, nblk * mblk, p.M, g, local)) return;
-    const int n0 = (int)(local % nblk) * BN, f0 = (int)(local / nblk) * BM;
+    // worker by worker, the blocks of a strip side by side: the operands are read once, into one XCD's L2, and the pieces of a
+    // layout tile leave at about the same time
+    if (!decode_group(blockIdx.x, (unsigned)(nblk * mblk), p.M, g, local)) return;
+    const int f0 = (int)(local / (unsigned)nblk) * BM, n0 = (int)(local % (unsigned)nblk) * BN;
     const int K = p.B;
 
-    // A: half a 4 x 4 block per thread (two batch rows of four features); lanes l and l + 32 of a wave share a block's features
-    const int a_m = (t & 15) * 4, a_k = (t >> 4) * 2;                 // 16 lanes along the 64 features, 16 pairs of batch rows
+    // A: two batch rows of four features per thread
+    const int a_m = t % (BM / 4) * 4, a_k = t / (BM / 4) * 2;
     int a_f = f0 + a_m;
     a_f = a_f < p.din ? a_f : (VA ? p.din - 4 : p.din - 1);
     const int a_have = p.din - a_f;
     const int64_t base_row = p.feats ? p.row0[g] : (int64_t)g * K;
     const int32_t *rows = p.feats ? p.idx + (size_t)g * K : nullptr;
-    int b_n[NB], b_k[NB], b_c[NB];
-#pragma unroll
-    for (int u = 0; u < NB; ++u) {
-        const int c = t + u * NT;
-        b_n[u] = c % (BN / 4) * 4;
-        b_k[u] = c / (BN / 4) * 4;
-        const int want = n0 + b_n[u];
-        b_c[u] = want < p.dout ? want : (VZ ? p.dout - 4 : p.dout - 1);
-    }
-    const float *zg = p.dz + (size_t)g * K * p.dout;
+    const int z_n = t % (BN / 4) * 4, z_k = t / (BN / 4) * 4;
+    int z_c = n0 + z_n;
+    z_c = z_c < p.dout ? z_c : (VZ ? p.dout - 4 : p.dout - 1);
+    const float *zg = p.dz + (size_t)g * K * p.dout + z_c;
     int32_t row_of[2];                                                // batch rows of the coming step, asked for a step ahead
     auto fetch_rows = [&](int k0) {
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
-            const int b = k0 + a_k + i < K ? k0 + a_k + i : K - 1;
-            row_of[i] = rows ? rows[b] : b;
+            const int k = k0 + a_k + i < K ? k0 + a_k + i : K - 1;
+            row_of[i] = rows ? rows[k] : k;
         }
     };
     Piece<BF> ra[2];
-    Piece<false> rb[NB][4];
+    Piece<false> rz[4];
     auto fetch = [&](int k0) {
 #pragma unroll
-        for (int u = 0; u < NB; ++u)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int b = k0 + b_k[u] + i < K ? k0 + b_k[u] + i : K - 1;
-                rb[u][i] = load_piece<VZ>(zg + (size_t)b * p.dout + b_c[u], p.dout - b_c[u]);
-            }
+        for (int i = 0; i < 4; ++i) {
+            const int k = k0 + z_k + i < K ? k0 + z_k + i : K - 1;
+            rz[i] = load_piece<VZ>(zg + (size_t)k * p.dout, p.dout - z_c);
+        }
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
             const int64_t q = (base_row + row_of[i]) * p.din + a_f;
@@ -92,16 +96,33 @@ __global__ void __launch_bounds__(TW_THREADS) tile_wgrad_kernel(TileWgrad p)
                 *reinterpret_cast<uint32_t *>(&As[a_m + e][a_k]) = h;
             } else {
                 typedef float f32x2 __attribute__((ext_vector_type(2)));
-                f32x2 v = {left - a_k >= 1 ? piece_f32(ra[0], e) : 0.0f, left - a_k >= 2 ? piece_f32(ra[1], e) : 0.0f};
+                const f32x2 v = {left - a_k >= 1 ? ra[0].v[e] : 0.0f, left - a_k >= 2 ? ra[1].v[e] : 0.0f};
                 *reinterpret_cast<f32x2 *>(&As[a_m + e][a_k]) = v;
             }
         }
 #pragma unroll
-        for (int u = 0; u < NB; ++u)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) put_piece(&Bs[b_n[u] + e][b_k[u]], turned(rb[u], e), left - b_k[u]);
+        for (int e = 0; e < 4; ++e) put_piece(&Zs[z_n + e][z_k], turned(rz, e), left - z_k);
     };
-    tile_f32x16 acc[1][CJ];
+    int m = g;
+    float wi = 0.0f;
+    if constexpr (UPDATE) {
+        m = p.mix.peer[g];
+        if ((unsigned)m >= (unsigned)p.M) m = g;                      // an index outside [0, M) is treated as a self draw
+        wi = p.mix.w[(size_t)g * p.M + m];
+    }
+    const size_t peer_shift = ((size_t)m - (size_t)g) << TILE_SHIFT;  // from a worker's element to its peer's
+    // the finished block by rows: 128-bit pieces (VZ) or single floats
+    constexpr int W = VZ ? 4 : 1, PER_ROW = BN / W, ROWS = NT / PER_ROW, PASSES = BM / ROWS;
+    const int oc = t % PER_ROW * W, orow = t / PER_ROW;
+    const bool col_ok = n0 + oc < p.dout;
+    const int64_t j0 = p.woff + (int64_t)f0 * p.dout + (col_ok ? n0 + oc : 0);
+    auto own_of = [&](int u) {
+        const int r = tile_opaque(u * ROWS + orow);
+        return tiled_offset_quick(p.M, g, j0 + (int64_t)(f0 + r < p.din ? r : 0) * p.dout);
+    };
+    f32x4 ux[UPDATE ? PASSES : 1], uv[UPDATE ? PASSES : 1], up[UPDATE ? PASSES : 1];
+
+    tile_f32x16 acc[1][1];
     tile_clear(acc);
     fetch_rows(0);
     fetch(0);
@@ -114,62 +135,80 @@ __global__ void __launch_bounds__(TW_THREADS) tile_wgrad_kernel(TileWgrad p)
             fetch(k0 + BK);
             fetch_rows(k0 + 2 * BK);
         }
-        tile_multiply<BK>(As, Bs, 32 * wm, (BN / 2) * wn, lane, acc);
+        if (UPDATE && k0 + BK >= K) {                                 // so do x and v of the block, behind the last operands
+#pragma unroll
+            for (int u = 0; u < PASSES; ++u) {
+                const size_t own = own_of(u);
+                ux[u] = load4(p.mix.Xcur + own);
+                uv[u] = load4_stream(p.mix.V + own);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        tile_multiply<BK>(As, Zs, 32 * wm, 32 * wn, lane, acc, K - k0);
+    }
+    if constexpr (UPDATE) {
+#pragma unroll
+        for (int u = 0; u < PASSES; ++u) up[u] = load4(p.mix.Xcur + own_of(u) + peer_shift);
+        __builtin_amdgcn_sched_barrier(0);
     }
     __syncthreads();                                                  // the operands' space becomes the staged result
 #pragma unroll
-    for (int j = 0; j < CJ; ++j)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) T[32 * wm + tile_row(lane, v)][(BN / 2) * wn + 32 * j + (lane & 31)] = acc[0][j][v];
+    for (int v = 0; v < 16; ++v) T[32 * wm + tile_row(lane, v)][32 * wn + (lane & 31)] = acc[0][0][v];
     __syncthreads();
-    if constexpr (VZ) {
-        constexpr int PER_ROW = BN / 4, ROWS = NT / PER_ROW;
-        const int c = (t % PER_ROW) * 4, r_in = t / PER_ROW;
-        if (n0 + c < p.dout) {
+    if (!col_ok) return;
 #pragma unroll
-            for (int pass = 0; pass < BM / ROWS; ++pass) {
-                const int r = pass * ROWS + r_in;
-                if (f0 + r < p.din)
-                    store4_stream(p.G + tiled_offset_quick(p.M, g, p.woff + (int64_t)(f0 + r) * p.dout + n0 + c),
-                                  *reinterpret_cast<const f32x4 *>(&T[r][c]));
-            }
-        }
-    } else {
-        constexpr int ROWS = NT / BN;
-        const int c = t % BN, r_in = t / BN;
-        if (n0 + c < p.dout) {
-#pragma unroll 8
-            for (int pass = 0; pass < BM / ROWS; ++pass) {
-                const int r = pass * ROWS + r_in;
-                if (f0 + r < p.din)
-                    __builtin_nontemporal_store(T[r][c], p.G + tiled_offset_quick(p.M, g, p.woff + (int64_t)(f0 + r) * p.dout + n0 + c));
+    for (int u = 0; u < PASSES; ++u) {
+        const int r = u * ROWS + orow;
+        if (f0 + r < p.din) {
+            const size_t own = own_of(u);
+            if constexpr (VZ) {
+                const f32x4 gr = *reinterpret_cast<const f32x4 *>(&T[r][oc]);
+                store4_stream(p.G + own, gr);
+                if constexpr (UPDATE) {
+                    f32x4 xn, vn;
+                    momentum_mix4(ux[u], uv[u], gr, up[u], wi, p.mix.alpha, p.mix.mu, p.mix.wd, xn, vn);
+                    store4_stream(p.mix.Xnext + own, xn);
+                    store4_stream(p.mix.V + own, vn);
+                }
+            } else {
+                p.G[own] = T[r][oc];
             }
         }
     }
 }
 
-template <bool BF, bool VA, bool VZ> static void launch_cols(hipStream_t s, const TileWgrad &a)
+template <bool BF, bool VA, bool VZ> static void launch_cols(hipStream_t s, const TileWgrad &a, bool update)
 {
-    const unsigned mblk = (unsigned)((a.din + TW_BM - 1) / TW_BM);
-    const unsigned blocks = (unsigned)((a.dout + 127) / 128) * mblk;
-    hipLaunchKernelGGL((tile_wgrad_kernel<BF, VA, VZ, 128>), dim3(grouped_grid(a.M, blocks)), dim3(TW_THREADS), 0, s, a);
+    const dim3 grid(grouped_grid(a.M, (unsigned)((a.dout + TW_BN - 1) / TW_BN) * (unsigned)((a.din + TW_BM - 1) / TW_BM))), block(TW_THREADS);
+    if constexpr (VZ && !BF)
+        if (update) {
+            hipLaunchKernelGGL((tile_wgrad_kernel<BF, VA, VZ, true>), grid, block, 0, s, a);
+            return;
+        }
+    hipLaunchKernelGGL((tile_wgrad_kernel<BF, VA, VZ, false>), grid, block, 0, s, a);
 }
 
-void launch_tile_wgrad(hipStream_t s, const MlpPlan &p, int l, float *G, int cur)
+// Rows of dZ and of dW start at multiples of 16 bytes.
+static bool rows_in_pieces(const MlpPlan &p, int l) { return p.dims[l + 1] % 4 == 0 && p.woff[l] % 4 == 0; }
+
+bool tile_wgrad_update_ok(const MlpPlan &p, int l) { return !p.bf16 && rows_in_pieces(p, l); }
+
+void launch_tile_wgrad(hipStream_t s, const MlpPlan &p, int l, float *G, int cur, const MixArgs *tail)
 {
-    const bool bf = p.bf16 != 0;
+    const bool bf = p.bf16 != 0, u = tail != nullptr;
     TileWgrad a;
+    a.mix = u ? *tail : MixArgs{};
     a.feats = l == 0 ? p.feats : nullptr; a.row0 = p.row0; a.idx = p.idx;
     a.act = l == 0 ? nullptr : (bf ? (const void *)p.hb[l] : (const void *)p.act[l]);
     a.dz = p.dz[cur]; a.M = p.M; a.B = p.B; a.din = (int)p.dims[l]; a.dout = (int)p.dims[l + 1]; a.woff = p.woff[l]; a.G = G;
     const bool va = a.din % 4 == 0 && reinterpret_cast<uintptr_t>(a.feats ? a.feats : a.act) % (bf ? 8 : 16) == 0;
-    const bool vz = a.dout % 4 == 0 && a.woff % 4 == 0;              // rows of dZ and of dW start at multiples of 16 bytes
+    const bool vz = rows_in_pieces(p, l);
     if (bf) {
-        if (va) { if (vz) launch_cols<true, true, true>(s, a); else launch_cols<true, true, false>(s, a); }
-        else { if (vz) launch_cols<true, false, true>(s, a); else launch_cols<true, false, false>(s, a); }
+        if (va) { if (vz) launch_cols<true, true, true>(s, a, u); else launch_cols<true, true, false>(s, a, u); }
+        else { if (vz) launch_cols<true, false, true>(s, a, u); else launch_cols<true, false, false>(s, a, u); }
     } else {
-        if (va) { if (vz) launch_cols<false, true, true>(s, a); else launch_cols<false, true, false>(s, a); }
-        else { if (vz) launch_cols<false, false, true>(s, a); else launch_cols<false, false, false>(s, a); }
+        if (va) { if (vz) launch_cols<false, true, true>(s, a, u); else launch_cols<false, true, false>(s, a, u); }
+        else { if (vz) launch_cols<false, false, true>(s, a, u); else launch_cols<false, false, false>(s, a, u); }
     }
 }
 

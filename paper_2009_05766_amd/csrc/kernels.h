@@ -153,7 +153,10 @@ struct MixArgs {
 };
 // fuse != nullptr: layers accepted by mfma_layer_ok() do not write their weight gradient to G; they write
 // x' and v' of their weight columns (Eq. (c0)/(c1)) straight from the product.
-void launch_mlp_grad(hipStream_t s, const MlpPlan &p, const float *X, float *G, const MixArgs *fuse = nullptr);
+// tail != nullptr (not together with fuse): the weight gradients of the layers whose update_end() is not 0 write G and apply the
+// update to the columns woff .. update_end() - 1 (multiples of four) while they hold them; the caller updates the others.
+void launch_mlp_grad(hipStream_t s, const MlpPlan &p, const float *X, float *G, const MixArgs *fuse = nullptr, const MixArgs *tail = nullptr);
+int64_t update_end(const MlpPlan &p, int l);
 
 // Matrix-core kernels (k_grad_mfma.hip) for layers that mfma_layer_ok() accepts.
 bool mfma_layer_ok(const MlpPlan &p, int l);
@@ -175,18 +178,20 @@ bool fwd_f32_ok(const MlpPlan &p, int l);
 bool wgrad_f32_ok(const MlpPlan &p, int l);
 hipError_t prepare_f32_layers();
 void launch_fwd_f32(hipStream_t s, const MlpPlan &p, int l, const float *X);
-void launch_wgrad_f32(hipStream_t s, const MlpPlan &p, int l, float *G, const float *dz);
+// tail: see launch_mlp_grad()
+void launch_wgrad_f32(hipStream_t s, const MlpPlan &p, int l, float *G, const float *dz, const MixArgs *tail);
 
 // Tiled kernels for layers of any shape, fp32 or bfloat16 operands.  need_t: the transposed bfloat16 activation is wanted (by a
 // matrix-core kernel above); below_fast: so are both bfloat16 copies of the error.  launch_tile_dgrad: true if it has also
 // written the bias gradient of the layer below (its workgroups held the whole batch).
 void launch_tile_fwd(hipStream_t s, const MlpPlan &p, int l, const float *X, bool need_t);
 bool launch_tile_dgrad(hipStream_t s, const MlpPlan &p, int l, const float *X, float *G, int cur, bool below_fast);
-void launch_tile_wgrad(hipStream_t s, const MlpPlan &p, int l, float *G, int cur);
+bool tile_wgrad_update_ok(const MlpPlan &p, int l);      // its update: fp32 operands, aligned rows
+void launch_tile_wgrad(hipStream_t s, const MlpPlan &p, int l, float *G, int cur, const MixArgs *tail);
 
 // Last layer with at most 32 classes, fp32 or bfloat16 operands (k_grad_head.hip): from its input to the error of the layer
 // below in two kernels: logits, loss, dW, db, dH and the column sums of dH.
 bool head_ok(const MlpPlan &p);
-void launch_head(hipStream_t s, const MlpPlan &p, const float *X, float *G);
+void launch_head(hipStream_t s, const MlpPlan &p, const float *X, float *G, const MixArgs *tail);
 
 }  // namespace netmax

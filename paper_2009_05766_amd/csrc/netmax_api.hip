@@ -54,6 +54,12 @@ struct netmax_ctx {
     int32_t *d_fuse_tiles = nullptr;
     int n_fuse_tiles = 0;
     MixSkip fuse_skip{};
+    // perceptrons with weight gradients that apply the update to their columns inside netmax_run (the gradient is still
+    // written): the tiles the separate mix covers then (none for softmax regression)
+    bool tail = false;
+    int32_t *d_tail_tiles = nullptr;
+    int n_tail_tiles = 0;
+    MixSkip tail_skip{};
     // asynchronous schedule: thresholds of the activity probabilities p_i
     uint32_t *d_act_thr = nullptr;
     std::vector<uint32_t> h_act_thr;          // host image: the host plans the batches of independent steps from the same draws
@@ -219,10 +225,23 @@ static void release(netmax_ctx *ctx)
     for (auto *p : ctx->d_dzb) (void)hipFree(p);
     for (auto *p : ctx->d_dzt) (void)hipFree(p);
     (void)hipFree(ctx->d_partial); (void)hipFree(ctx->d_cd);
-    (void)hipFree(ctx->d_act_thr); (void)hipFree(ctx->d_fuse_tiles);
+    (void)hipFree(ctx->d_act_thr); (void)hipFree(ctx->d_fuse_tiles); (void)hipFree(ctx->d_tail_tiles);
     (void)hipFree(ctx->d_barrier); (void)hipFree(ctx->d_fault);
     (void)hipFree(ctx->d_xc); (void)hipFree(ctx->d_gc); (void)hipFree(ctx->d_lossc); (void)hipFree(ctx->d_row0c); (void)hipFree(ctx->d_nrowsc);
     delete ctx;
+}
+
+// The tiles with at least one column outside the ranges of `skip` (four columns at a time, as the kernel tests them).
+static std::vector<int32_t> tiles_outside(const MixSkip &skip, int64_t ld)
+{
+    std::vector<int32_t> tiles;
+    for (int64_t t = 0; t < ld / TILE; ++t) {
+        const int64_t lo = t * TILE, hi = lo + TILE;
+        bool covered = false;
+        for (int r = 0; r < skip.n; ++r) covered |= (skip.lo[r] <= lo && hi <= skip.hi[r]);
+        if (!covered) tiles.push_back((int32_t)t);
+    }
+    return tiles;
 }
 
 static int check_launch(netmax_ctx *ctx, const char *what)
@@ -232,6 +251,8 @@ static int check_launch(netmax_ctx *ctx, const char *what)
     return NETMAX_OK;
 }
 
+static MlpPlan make_plan(const netmax_ctx *ctx);
+
 // --------------------------------------------------------------------------------------------------
 extern "C" int netmax_init(netmax_ctx **out, const netmax_config *cfg)
 {
@@ -240,6 +261,7 @@ extern "C" int netmax_init(netmax_ctx **out, const netmax_config *cfg)
     if (!cfg || !cfg->P) return fail(nullptr, NETMAX_EINVAL, "cfg or cfg->P is NULL");
     char buf[200];
     if (cfg->M < 2 || cfg->M > 4096) return fail(nullptr, NETMAX_EINVAL, "M must be in 2..4096");
+    static_assert(NETMAX_MAX_LAYERS <= MIX_MAX_SKIP, "one range per layer");
     static_assert(NETMAX_TILE == TILE, "the header and the kernels must agree on the tile size");
     if (cfg->D < 1 || cfg->ld < cfg->D || cfg->ld % TILE != 0)
         return fail(nullptr, NETMAX_EINVAL, "need 1 <= D <= ld and ld a multiple of NETMAX_TILE");
@@ -356,6 +378,22 @@ extern "C" int netmax_init(netmax_ctx **out, const netmax_config *cfg)
             INIT_TRY(hipMalloc(&ctx->d_fault, sizeof(int)));
             INIT_TRY(hipMemset(ctx->d_barrier, 0, sizeof(unsigned)));
             INIT_TRY(hipMemset(ctx->d_fault, 0, sizeof(int)));
+        }
+        const MlpPlan plan = make_plan(ctx);
+        for (int l = 0; l < cfg->n_layers && !ctx->small; ++l)
+            if (update_end(plan, l) > 0) {
+                ctx->tail = true;
+                ctx->tail_skip.lo[ctx->tail_skip.n] = plan.woff[l];
+                ctx->tail_skip.hi[ctx->tail_skip.n] = update_end(plan, l);
+                ++ctx->tail_skip.n;
+            }
+        if (ctx->tail) {
+            const std::vector<int32_t> tiles = tiles_outside(ctx->tail_skip, cfg->ld);
+            ctx->n_tail_tiles = (int)tiles.size();
+            if (!tiles.empty()) {
+                INIT_TRY(hipMalloc(&ctx->d_tail_tiles, tiles.size() * sizeof(int32_t)));
+                INIT_TRY(hipMemcpy(ctx->d_tail_tiles, tiles.data(), tiles.size() * sizeof(int32_t), hipMemcpyHostToDevice));
+            }
         }
     }
 #undef INIT_TRY
@@ -558,54 +596,61 @@ static int enqueue_small(netmax_ctx *ctx, const IterRef &iter, int n_iters, bool
     return NETMAX_OK;
 }
 
-// fused_peers != nullptr: the matrix-core layers apply the update to their weight columns themselves (netmax_run
-// after netmax_set_fusion); enqueue_mix then covers the remaining columns only.
+// run_peers != nullptr (netmax_run): weight-gradient kernels apply the update where the context has it so, enqueue_run_mix then
+// covers the remaining columns only.
 // batch_drawn: the batch rows of this iteration are in d_idx already.
-static int enqueue_local_step(netmax_ctx *ctx, const IterRef &iter, const int32_t *fused_peers = nullptr, bool batch_drawn = false)
+static int enqueue_local_step(netmax_ctx *ctx, const IterRef &iter, const int32_t *run_peers = nullptr, bool batch_drawn = false)
 {
     const netmax_config &c = ctx->cfg;
     if (c.model == NETMAX_FLAT) {
-        if (fused_peers) return NETMAX_OK;           // the fused update generates the gradient itself
+        if (run_peers && ctx->fuse) return NETMAX_OK;           // the fused update generates the gradient itself
         launch_synth_grad(ctx->stream, c.M, c.D, c.ld, c.grad_sigma, c.seed, iter, ctx->g);
         return check_launch(ctx, "synth_grad");
     }
     if (ctx->small) return enqueue_small(ctx, iter, 1, true, nullptr, false);
     if (!batch_drawn) launch_sample_batch(ctx->stream, c.M, c.batch, ctx->d_nrows, c.seed, iter, ctx->d_idx);
     const MlpPlan p = make_plan(ctx);
-    if (fused_peers) {
-        const MixArgs mx = mix_args(ctx, fused_peers);
-        launch_mlp_grad(ctx->stream, p, ctx->x_cur, ctx->g, &mx);
-    } else {
-        launch_mlp_grad(ctx->stream, p, ctx->x_cur, ctx->g);
-    }
+    const MixArgs mx = mix_args(ctx, run_peers);
+    launch_mlp_grad(ctx->stream, p, ctx->x_cur, ctx->g, run_peers && ctx->fuse ? &mx : nullptr,
+                    run_peers && ctx->tail && !ctx->fuse ? &mx : nullptr);
     return check_launch(ctx, "mlp_grad");
 }
 
 static int enqueue_draws_and_local_step(netmax_ctx *ctx, const IterRef &iter, int32_t *peers_dev)
 {
     const netmax_config &c = ctx->cfg;
-    const int32_t *fused_peers = ctx->fuse ? peers_dev : nullptr;
     if (c.model == NETMAX_FLAT || ctx->small) {
         const int rc = enqueue_sample_peers(ctx, iter, peers_dev);
-        return rc != NETMAX_OK ? rc : enqueue_local_step(ctx, iter, fused_peers);
+        return rc != NETMAX_OK ? rc : enqueue_local_step(ctx, iter, peers_dev);
     }
     launch_sample_iteration(ctx->stream, c.M, ctx->d_thr, ctx->d_last, peers_dev, c.batch, ctx->d_nrows, ctx->d_idx, c.seed, iter);
     const int rc = check_launch(ctx, "sample_iteration");
-    return rc != NETMAX_OK ? rc : enqueue_local_step(ctx, iter, fused_peers, true);
+    return rc != NETMAX_OK ? rc : enqueue_local_step(ctx, iter, peers_dev, true);
 }
 
-static int enqueue_mix(netmax_ctx *ctx, const int32_t *peers_dev, bool fused = false, const IterRef &iter = IterRef{0, nullptr})
+// The update of all columns.
+static int enqueue_mix(netmax_ctx *ctx, const int32_t *peers_dev)
 {
     const netmax_config &c = ctx->cfg;
-    if (fused && c.model == NETMAX_FLAT)
+    launch_mix(ctx->stream, c.M, c.ld, ctx->x_cur, ctx->g, ctx->v, ctx->x_next, peers_dev, ctx->d_w, c.lr, c.momentum, c.weight_decay);
+    return check_launch(ctx, "mix");
+}
+
+// The update inside netmax_run: of what the gradient's kernels have left.
+static int enqueue_run_mix(netmax_ctx *ctx, const int32_t *peers_dev, const IterRef &iter)
+{
+    const netmax_config &c = ctx->cfg;
+    if (ctx->fuse && c.model == NETMAX_FLAT)
         launch_mix_synth(ctx->stream, c.M, c.D, c.ld, ctx->x_cur, ctx->g, ctx->v, ctx->x_next, peers_dev, ctx->d_w, c.lr,
                          c.momentum, c.weight_decay, c.grad_sigma, c.seed, iter);
-    else if (fused)
+    else if (ctx->fuse)
         launch_mix_subset(ctx->stream, c.M, ctx->d_fuse_tiles, ctx->n_fuse_tiles, ctx->fuse_skip, ctx->x_cur, ctx->g, ctx->v,
                           ctx->x_next, peers_dev, ctx->d_w, c.lr, c.momentum, c.weight_decay);
+    else if (ctx->tail)
+        launch_mix_subset(ctx->stream, c.M, ctx->d_tail_tiles, ctx->n_tail_tiles, ctx->tail_skip, ctx->x_cur, ctx->g, ctx->v,
+                          ctx->x_next, peers_dev, ctx->d_w, c.lr, c.momentum, c.weight_decay);
     else
-        launch_mix(ctx->stream, c.M, c.ld, ctx->x_cur, ctx->g, ctx->v, ctx->x_next, peers_dev, ctx->d_w, c.lr, c.momentum,
-                   c.weight_decay);
+        return enqueue_mix(ctx, peers_dev);
     return check_launch(ctx, "mix");
 }
 
@@ -666,7 +711,7 @@ static int capture_iteration(netmax_ctx *ctx, int dir, int32_t *peers_dev)
         rc = enqueue_small(ctx, it, 1, false, peers_dev, false);
     } else {
         rc = enqueue_draws_and_local_step(ctx, it, peers_dev);
-        if (rc == NETMAX_OK) rc = enqueue_mix(ctx, peers_dev, ctx->fuse, it);
+        if (rc == NETMAX_OK) rc = enqueue_run_mix(ctx, peers_dev, it);
     }
     if (rc == NETMAX_OK) {
         launch_bump_iteration(ctx->stream, ctx->d_iter);
@@ -711,7 +756,7 @@ extern "C" int netmax_run(netmax_ctx *ctx, uint64_t first_iter, int32_t n_iters,
         for (int32_t k = 0; k < n_iters; ++k) {
             const IterRef it{first_iter + (uint64_t)k, nullptr};
             int rc = enqueue_draws_and_local_step(ctx, it, peers_dev);
-            if (rc == NETMAX_OK) rc = enqueue_mix(ctx, peers_dev, ctx->fuse, it);
+            if (rc == NETMAX_OK) rc = enqueue_run_mix(ctx, peers_dev, it);
             if (rc != NETMAX_OK) return rc;
             flip(ctx);
         }
@@ -759,15 +804,7 @@ extern "C" int netmax_set_fusion(netmax_ctx *ctx, int32_t on)
             ++skip.n;
         }
     if (skip.n == 0) return fail(ctx, NETMAX_ESTATE, "no layer of this model runs on the matrix-core kernels");
-    // tiles with at least one column outside the ranges (four columns at a time, as the kernel tests them)
-    std::vector<int32_t> tiles;
-    const int64_t n_tiles = c.ld / NETMAX_TILE;
-    for (int64_t t = 0; t < n_tiles; ++t) {
-        const int64_t lo = t * NETMAX_TILE, hi = lo + NETMAX_TILE;
-        bool covered = false;
-        for (int r = 0; r < skip.n; ++r) covered |= (skip.lo[r] <= lo && hi <= skip.hi[r]);
-        if (!covered) tiles.push_back((int32_t)t);
-    }
+    const std::vector<int32_t> tiles = tiles_outside(skip, c.ld);
     (void)hipFree(ctx->d_fuse_tiles);
     ctx->d_fuse_tiles = nullptr;
     if (!tiles.empty()) {

@@ -29,6 +29,13 @@ __device__ __forceinline__ size_t tiled_offset_quick(int M, int i, int64_t j)
     return (size_t)j + (size_t)(t << TILE_SHIFT);
 }
 
+// The value, hidden from the optimiser: addresses computed from it inside a loop are computed there, not kept in registers across it.
+__device__ __forceinline__ int tile_opaque(int v)
+{
+    asm volatile("" : "+v"(v));
+    return v;
+}
+
 // Four neighbouring elements of memory: fp32, or bfloat16 (S16) as two packed words.
 template <bool S16> struct Piece { f32x4 v; };
 template <> struct Piece<true> { tile_u32x2 v; };
@@ -107,16 +114,18 @@ __device__ __forceinline__ tile_u32x2 turned(const Piece<true> (&r)[4], int e)
     return tile_u32x2{piece_bits(r[0], e) | (piece_bits(r[1], e) << 16), piece_bits(r[2], e) | (piece_bits(r[3], e) << 16)};
 }
 
-// One step: acc[i][j] += As[m0 + 32 i ..][k] Bs[n0 + 32 j ..][k] over the BK indices in LDS.
-template <int BK, int RI, int CJ, int PITCH>
-__device__ __forceinline__ void tile_multiply(const float (*As)[PITCH], const float (*Bs)[PITCH], int m0, int n0, int lane,
-                                              tile_f32x16 (&acc)[RI][CJ])
+// One step: acc[i][j] += As[m0 + 32 i ..][ka + k] Bs[n0 + 32 j ..][k] over BK indices in LDS, of which `left` exist (the others are
+// zeros; whole groups of 32 of them are left out).
+template <int BK, int RI, int CJ, int PA, int PB>
+__device__ __forceinline__ void tile_multiply(const float (*As)[PA], const float (*Bs)[PB], int m0, int n0, int lane,
+                                              tile_f32x16 (&acc)[RI][CJ], int left = BK, int ka = 0)
 {
 #pragma unroll
     for (int ks = 0; ks < BK; ks += 8) {
+        if (ks % 32 == 0 && ks > 0 && ks >= left) break;
         f32x4 a[RI], b[CJ];
 #pragma unroll
-        for (int i = 0; i < RI; ++i) a[i] = *reinterpret_cast<const f32x4 *>(&As[m0 + 32 * i + (lane & 31)][ks + 4 * (lane >> 5)]);
+        for (int i = 0; i < RI; ++i) a[i] = *reinterpret_cast<const f32x4 *>(&As[m0 + 32 * i + (lane & 31)][ka + ks + 4 * (lane >> 5)]);
 #pragma unroll
         for (int j = 0; j < CJ; ++j) b[j] = *reinterpret_cast<const f32x4 *>(&Bs[n0 + 32 * j + (lane & 31)][ks + 4 * (lane >> 5)]);
 #pragma unroll
@@ -127,15 +136,16 @@ __device__ __forceinline__ void tile_multiply(const float (*As)[PITCH], const fl
                 for (int j = 0; j < CJ; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i][c], b[j][c], acc[i][j], 0, 0, 0);
     }
 }
-template <int BK, int RI, int CJ, int PITCH>
-__device__ __forceinline__ void tile_multiply(const uint16_t (*As)[PITCH], const uint16_t (*Bs)[PITCH], int m0, int n0, int lane,
-                                              tile_f32x16 (&acc)[RI][CJ])
+template <int BK, int RI, int CJ, int PA, int PB>
+__device__ __forceinline__ void tile_multiply(const uint16_t (*As)[PA], const uint16_t (*Bs)[PB], int m0, int n0, int lane,
+                                              tile_f32x16 (&acc)[RI][CJ], int left = BK, int ka = 0)
 {
 #pragma unroll
     for (int ks = 0; ks < BK; ks += 16) {
+        if (ks % 32 == 0 && ks > 0 && ks >= left) break;
         tile_u32x4 a[RI], b[CJ];
 #pragma unroll
-        for (int i = 0; i < RI; ++i) a[i] = *reinterpret_cast<const tile_u32x4 *>(&As[m0 + 32 * i + (lane & 31)][ks + 8 * (lane >> 5)]);
+        for (int i = 0; i < RI; ++i) a[i] = *reinterpret_cast<const tile_u32x4 *>(&As[m0 + 32 * i + (lane & 31)][ka + ks + 8 * (lane >> 5)]);
 #pragma unroll
         for (int j = 0; j < CJ; ++j) b[j] = *reinterpret_cast<const tile_u32x4 *>(&Bs[n0 + 32 * j + (lane & 31)][ks + 8 * (lane >> 5)]);
 #pragma unroll
@@ -145,6 +155,15 @@ __device__ __forceinline__ void tile_multiply(const uint16_t (*As)[PITCH], const
                 acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(tile_bf16x8, a[i]),
                                                                     __builtin_bit_cast(tile_bf16x8, b[j]), acc[i][j], 0, 0, 0);
     }
+}
+
+// momentum_mix4() of a single parameter: the same operations in the same order, so the same bits.
+__device__ __forceinline__ void momentum_mix1(float x, float v, float g, float x_peer, float w, float alpha, float mu, float wd,
+                                              float &x_new, float &v_new)
+{
+    v_new = fmaf(wd, x, fmaf(mu, v, g));
+    const float h = fmaf(-alpha, v_new, x);
+    x_new = fmaf(-w, h - x_peer, h);
 }
 
 // Row of result register v in a 32 x 32 tile (the column is lane % 32).

@@ -1,0 +1,47 @@
+"""netmax_run lets the first layer's weight gradient apply the update to its columns; the separate calls do it with the mix
+kernel.  Parameters, momentum, gradient and losses have to be the same bits, padding included, whichever kernels a shape takes."""
+import numpy as np
+import pytest
+import torch
+
+from harness import inputs_of, make_gpu
+from netmax_inputs import workload
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("name,M,batch,dims", [
+    ("cfg2", 9, 64, (784, 10)), ("cfg2", 3, 200, (900, 17)), ("cfg5", 4, 33, (130, 32)),     # softmax regression
+    ("cfg2", 5, 64, (70, 96, 10)), ("cfg2", 3, 32, (33, 64, 32, 7)),                            # batches of 32 and 64, fp32
+    ("cfg2", 11, 128, (100, 132, 10)), ("cfg2", 3, 40, (130, 36, 40, 10)),                      # tiled, rows aligned
+    ("cfg2", 3, 100, (75, 51, 10)), ("cfg2", 2, 300, (37, 41, 33)),                             # rows not aligned, W's end inside a group of four
+    ("cfg5", 4, 100, (100, 60, 10)), ("cfg5", 3, 90, (61, 131, 10)), ("cfg5", 3, 64, (100, 128, 128, 10)),
+    ("cfg5", 3, 64, (128, 128, 10)),                                                            # matrix-core layers: the separate mix
+    ("cfg2", 3, 300, (40, 20)), ("cfg2", 3, 16, (50, 40)),                                      # one layer outside the last-layer kernels
+])
+@pytest.mark.parametrize("graph", [False, True])
+def test_run_is_the_separate_calls(name, M, batch, dims, graph):
+    w = workload(name, M=M, batch=batch, n_per_worker=batch + 3, dims=dims)
+    inp = inputs_of(w)
+    over = dict(momentum=0.9, weight_decay=1e-4)
+    calls = make_gpu(w, inp, **over)
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        run = make_gpu(w, inp, **over)
+        for net in (calls, run):
+            net.x_b.fill_(3.0)                               # every element of the next parameters has to be written
+        torch.cuda.synchronize()
+        it = 0
+        for n in (1, 2, 3):
+            run.run(it, n, use_graph=graph)
+            side.synchronize()
+            for k in range(n):
+                calls.step(it + k)
+            torch.cuda.synchronize()
+            it += n
+            assert torch.equal(run.peers, calls.peers)
+            for name_ in ("x_a", "x_b", "v", "g"):
+                assert torch.equal(getattr(run, name_), getattr(calls, name_)), (name_, it)
+            assert torch.equal(run.losses(), calls.losses())
+    assert not np.array_equal(run.get("x").cpu().numpy(), inp["X0"])
+    calls.close(), run.close()
