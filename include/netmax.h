@@ -216,9 +216,9 @@ int netmax_set_barrier_patience(netmax_ctx *ctx, int64_t polls);
  * from word 0 of Philox stream 3 at counter (0, 0, k) and m_k from stream 0 at counter (0, i_k, k); the gradient
  * of the active worker uses iteration number k in its counters.  active_dev / peers_dev: device int32 [n_steps],
  * caller-owned, receive i_k and m_k.  x (the current buffer) and v are updated in place, no buffer flip; the active
- * worker's row of g receives its gradient (only that worker's gradient is computed).  Consecutive steps that cannot
- * see each other (no worker active twice, no pull from a row written earlier in the group, no write to a row pulled
- * earlier) run as one batch of launches of up to 32 steps; the host finds these groups by repeating the draws, which
+ * worker's row of g receives its gradient (only that worker's gradient is computed).  Steps that cannot see each other (no row
+ * that one of them writes is read or written by another) run as one batch of launches of up to 32 steps, each step behind the
+ * earlier ones it depends on; the host finds these groups by repeating the draws, which
  * are integer work on the same tables.  The result is that of the strictly sequential schedule.
  * Needs netmax_bind_state, netmax_set_activity and, for perceptron models, netmax_bind_data (else NETMAX_ESTATE).
  * Returns after enqueueing. */

@@ -36,36 +36,33 @@ __global__ void __launch_bounds__(256) async_draw_kernel(int M, const uint32_t *
 
 // The active workers' rows of a batch of global steps that do not touch each other's rows (the host plans the
 // batches): v' = mu v + g + wd x, h = x - alpha v', x' = h - w (h - x_peer), in place.  One workgroup per column
-// tile (8 KB of the row) and step, 256 threads x 2 x 128 bit.  SOURCE 0: the gradient of a flat model is generated
+// tile (8 KB of the row) and slot, 256 threads x 2 x 128 bit.  SOURCE 0: the gradient of a flat model is generated
 // here with the step's number as iteration and stored to the worker's row of G; 1: it is read from the worker's row
-// of G; 2: it is read from slot s of the compact matrix Gc (tile layout over the n_steps slots of the batch) and copied
-// to the worker's row of G.
+// of G; 2: it is read from the slot's row of the compact matrix Gc (tile layout over the slots of the batch) and copied
+// to the worker's row of G, and so is the slot's loss.
 template <int SOURCE>
 __global__ void __launch_bounds__(256) async_row_kernel(int M, int64_t D, float *__restrict__ X, float *__restrict__ V,
-                                                        float *__restrict__ G, const float *__restrict__ Gc, int n_steps,
-                                                        const int32_t *__restrict__ active,
-                                                        const int32_t *__restrict__ peers, const float *__restrict__ w,
-                                                        float alpha, float mu, float wd, float sigma, uint64_t seed, uint64_t k0)
+                                                        float *__restrict__ G, const float *__restrict__ Gc, AsyncSlots slots,
+                                                        const float *__restrict__ w, float alpha, float mu, float wd, float sigma,
+                                                        uint64_t seed, const float *__restrict__ loss_c, float *__restrict__ loss)
 {
     const int64_t tile = blockIdx.x;
-    const int s = blockIdx.y;
-    int i = active[s], m = peers[s];
-    if ((unsigned)i >= (unsigned)M) return;
-    if ((unsigned)m >= (unsigned)M) m = i;
+    const int s = blockIdx.y, i = slots.worker[s], m = slots.peer[s];
     const float wi = w[(size_t)i * M + m];
     const size_t own = ((size_t)tile * M + i) << TILE_SHIFT, other = ((size_t)tile * M + m) << TILE_SHIFT;
+    if (SOURCE == 2 && tile == 0 && threadIdx.x == 0) loss[i] = loss_c[s];
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
         const int q = (u * 256 + (int)threadIdx.x) * 4;
         const f32x4 x = load4(X + own + q), xp = load4(X + other + q), v = load4(V + own + q);
         f32x4 g;
         if (SOURCE == 0) {
-            g = synth_grad4(seed, (uint32_t)i, k0 + (uint64_t)s, tile * TILE + q, D, sigma);
+            g = synth_grad4(seed, (uint32_t)i, slots.first + slots.step[s], tile * TILE + q, D, sigma);
             store4(G + own + q, g);
         } else if (SOURCE == 1) {
             g = load4(G + own + q);
         } else {
-            g = load4(Gc + (((size_t)tile * n_steps + s) << TILE_SHIFT) + q);
+            g = load4(Gc + (((size_t)tile * slots.n + s) << TILE_SHIFT) + q);
             store4(G + own + q, g);
         }
         f32x4 xn, vn;
@@ -75,60 +72,32 @@ __global__ void __launch_bounds__(256) async_row_kernel(int M, int64_t D, float 
     }
 }
 
-// Subset runs of the perceptron gradient: the parameter rows of the listed workers copied into a compact matrix
-// (tile layout over n slots), their shard descriptors, and their losses copied back.
-__global__ void __launch_bounds__(256) gather_rows_kernel(int M, int n, const int32_t *__restrict__ workers,
-                                                          const float *__restrict__ X, float *__restrict__ Xc)
+// Before the perceptron gradient of a batch: the parameter rows of its workers copied into a compact matrix (tile layout over
+// the slots), and, by one more workgroup per slot (blockIdx.x = n_tiles), the first feature row of the worker's shard and the
+// batch draw of the slot's step, as sample_batch_kernel makes it for all workers at one iteration.
+__global__ void __launch_bounds__(256) gather_slots_kernel(int M, int n_tiles, AsyncSlots slots, const float *__restrict__ X,
+                                                           float *__restrict__ Xc, int B, const int64_t *__restrict__ row0,
+                                                           const int32_t *__restrict__ n_rows, uint64_t seed,
+                                                           int64_t *__restrict__ row0_c, int32_t *__restrict__ idx)
 {
-    const int64_t tile = blockIdx.x;
-    const int s = blockIdx.y, i = workers[s];
-    if ((unsigned)i >= (unsigned)M) return;
-    const size_t src = ((size_t)tile * M + i) << TILE_SHIFT, dst = ((size_t)tile * n + s) << TILE_SHIFT;
+    const int s = blockIdx.y, i = slots.worker[s];
+    if ((int)blockIdx.x < n_tiles) {
+        const size_t src = ((size_t)blockIdx.x * M + i) << TILE_SHIFT, dst = ((size_t)blockIdx.x * slots.n + s) << TILE_SHIFT;
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-        const int q = (u * 256 + (int)threadIdx.x) * 4;
-        store4(Xc + dst + q, load4(X + src + q));
+        for (int u = 0; u < 2; ++u) {
+            const int q = (u * 256 + (int)threadIdx.x) * 4;
+            store4(Xc + dst + q, load4(X + src + q));
+        }
+        return;
     }
-}
-
-__global__ void __launch_bounds__(256) gather_shards_kernel(int M, int n, const int32_t *__restrict__ workers,
-                                                            const int64_t *__restrict__ row0, const int32_t *__restrict__ n_rows,
-                                                            int64_t *__restrict__ row0_c, int32_t *__restrict__ n_rows_c)
-{
-    const int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= n) return;
-    int i = workers[s];
-    if ((unsigned)i >= (unsigned)M) i = 0;
-    row0_c[s] = row0[i];
-    n_rows_c[s] = n_rows[i];
-}
-
-__global__ void __launch_bounds__(256) scatter_loss_kernel(int M, int n, const int32_t *__restrict__ workers,
-                                                           const float *__restrict__ loss_c, float *__restrict__ loss)
-{
-    const int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= n) return;
-    const int i = workers[s];
-    if ((unsigned)i < (unsigned)M) loss[i] = loss_c[s];
-}
-
-// Batch draws of listed workers: slot s draws for worker workers[s] at iteration first_iter + s (consecutive global
-// steps), as sample_batch_kernel does for all workers at one iteration.
-__global__ void __launch_bounds__(256) sample_batch_subset_kernel(int n, int B, const int32_t *__restrict__ workers,
-                                                                  const int32_t *__restrict__ n_rows_c, uint64_t seed,
-                                                                  uint64_t first_iter, int32_t *__restrict__ idx)
-{
-    const int quads = (B + 3) >> 2;
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= n * quads) return;
-    const int s = t / quads, q = t - s * quads;
-    const Words4 r = draw_block(seed, STREAM_BATCH, (uint32_t)q, (uint32_t)workers[s], first_iter + (uint64_t)s);
-    const uint32_t rows = (uint32_t)n_rows_c[s];
-    const uint32_t wd[4] = {r.a, r.b, r.c, r.d};
+    if (threadIdx.x == 0) row0_c[s] = row0[i];
+    const uint32_t rows = (uint32_t)n_rows[i];
+    for (int q = threadIdx.x; 4 * q < B; q += 256) {
+        const Words4 r = draw_block(seed, STREAM_BATCH, (uint32_t)q, (uint32_t)i, slots.first + slots.step[s]);
+        const uint32_t wd[4] = {r.a, r.b, r.c, r.d};
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        const int b = 4 * q + e;
-        if (b < B) idx[(size_t)s * B + b] = (int32_t)__umulhi(wd[e], rows);
+        for (int e = 0; e < 4; ++e)
+            if (4 * q + e < B) idx[(size_t)s * B + 4 * q + e] = (int32_t)__umulhi(wd[e], rows);
     }
 }
 
@@ -167,41 +136,25 @@ void launch_async_draw(hipStream_t s, int M, const uint32_t *act_thr, int act_la
 }
 
 void launch_async_rows(hipStream_t s, int source, int M, int64_t D, int64_t ld, float *X, float *V, float *G, const float *Gc,
-                       int n_steps, const int32_t *active, const int32_t *peers, const float *w, float alpha, float mu, float wd,
-                       float sigma, uint64_t seed, uint64_t k0)
+                       const AsyncSlots &slots, const float *w, float alpha, float mu, float wd, float sigma, uint64_t seed,
+                       const float *loss_c, float *loss)
 {
     static_assert(TILE == 2048, "256 threads x 2 x 4 columns cover one tile");
-    const dim3 grid((unsigned)(ld / TILE), (unsigned)n_steps);
+    const dim3 grid((unsigned)(ld / TILE), (unsigned)slots.n);
     if (source == 0)
-        hipLaunchKernelGGL(async_row_kernel<0>, grid, dim3(256), 0, s, M, D, X, V, G, Gc, n_steps, active, peers, w, alpha, mu, wd, sigma, seed, k0);
+        hipLaunchKernelGGL(async_row_kernel<0>, grid, dim3(256), 0, s, M, D, X, V, G, Gc, slots, w, alpha, mu, wd, sigma, seed, loss_c, loss);
     else if (source == 1)
-        hipLaunchKernelGGL(async_row_kernel<1>, grid, dim3(256), 0, s, M, D, X, V, G, Gc, n_steps, active, peers, w, alpha, mu, wd, sigma, seed, k0);
+        hipLaunchKernelGGL(async_row_kernel<1>, grid, dim3(256), 0, s, M, D, X, V, G, Gc, slots, w, alpha, mu, wd, sigma, seed, loss_c, loss);
     else
-        hipLaunchKernelGGL(async_row_kernel<2>, grid, dim3(256), 0, s, M, D, X, V, G, Gc, n_steps, active, peers, w, alpha, mu, wd, sigma, seed, k0);
+        hipLaunchKernelGGL(async_row_kernel<2>, grid, dim3(256), 0, s, M, D, X, V, G, Gc, slots, w, alpha, mu, wd, sigma, seed, loss_c, loss);
 }
 
-void launch_gather_rows(hipStream_t s, int M, int n, int64_t ld, const int32_t *workers, const float *X, float *Xc)
+void launch_gather_slots(hipStream_t s, int M, int64_t ld, const AsyncSlots &slots, const float *X, float *Xc, int B, const int64_t *row0,
+                         const int32_t *n_rows, uint64_t seed, int64_t *row0_c, int32_t *idx)
 {
-    hipLaunchKernelGGL(gather_rows_kernel, dim3((unsigned)(ld / TILE), (unsigned)n), dim3(256), 0, s, M, n, workers, X, Xc);
-}
-
-void launch_gather_shards(hipStream_t s, int M, int n, const int32_t *workers, const int64_t *row0, const int32_t *n_rows,
-                          int64_t *row0_c, int32_t *n_rows_c)
-{
-    hipLaunchKernelGGL(gather_shards_kernel, dim3((n + 255) / 256), dim3(256), 0, s, M, n, workers, row0, n_rows, row0_c, n_rows_c);
-}
-
-void launch_scatter_loss(hipStream_t s, int M, int n, const int32_t *workers, const float *loss_c, float *loss)
-{
-    hipLaunchKernelGGL(scatter_loss_kernel, dim3((n + 255) / 256), dim3(256), 0, s, M, n, workers, loss_c, loss);
-}
-
-void launch_sample_batch_subset(hipStream_t s, int n, int B, const int32_t *workers, const int32_t *n_rows_c, uint64_t seed,
-                                uint64_t first_iter, int32_t *idx)
-{
-    const int total = n * ((B + 3) / 4);
-    hipLaunchKernelGGL(sample_batch_subset_kernel, dim3((total + 255) / 256), dim3(256), 0, s, n, B, workers, n_rows_c, seed,
-                       first_iter, idx);
+    const int n_tiles = (int)(ld / TILE);
+    hipLaunchKernelGGL(gather_slots_kernel, dim3((unsigned)n_tiles + 1, (unsigned)slots.n), dim3(256), 0, s, M, n_tiles, slots, X, Xc, B, row0,
+                       n_rows, seed, row0_c, idx);
 }
 
 }  // namespace netmax

@@ -28,6 +28,8 @@
 #include "philox.h"
 #include "vec.h"
 
+#include <type_traits>
+
 namespace netmax {
 
 constexpr int SI_THREADS = 512, SI_WAVES = SI_THREADS / 64;
@@ -50,9 +52,11 @@ struct SmallIterArgs {
     IterRef iter;                           // number of the first iteration
     int n_iters, grad_only;
     unsigned *barrier; unsigned barrier_base; int *fault;
-    const int32_t *workers;                 // grad_only: workgroup s works for worker workers[s] at iteration iter + s (NULL: s, iter)
     long long patience;                     // polls of the barrier counter before a workgroup gives up
 };
+// grad_only for listed workers: workgroup s works for slot s.  (A struct of its own: the list in the arguments of the other launches
+// would cost them 0.4 us each.)
+struct SmallSlotArgs : SmallIterArgs { AsyncSlots slots; };
 
 // The matrix-instruction form of the two products: classes padded to one 16-wide tile, 16-row tiles of the batch, the
 // the waves split the features of the forward pass evenly in groups of 64 (no bounds test in any loop).
@@ -128,9 +132,10 @@ __device__ __forceinline__ int opaque(int v)
 
 // CAP: classes the unrolled loops cover: dout <= CAP, CAP in {8, 16, 32}.  RT > 0: the two products on matrix
 // instructions, RT = batch / 16 tiles of batch rows (CAP = 16, shapes accepted by small_iter_mm()).
-template <int CAP, int RT = 0>
-__global__ void __launch_bounds__(SI_THREADS) small_softmax_iteration_kernel(SmallIterArgs p)
+template <int CAP, int RT = 0, class Args = SmallIterArgs>
+__global__ void __launch_bounds__(SI_THREADS) small_softmax_iteration_kernel(Args p)
 {
+    constexpr bool SLOTS = !std::is_same<Args, SmallIterArgs>::value;
     constexpr bool MM = RT > 0;
     static_assert(!MM || CAP == 16, "the matrix-instruction form pads the classes to one 16-wide tile");
     extern __shared__ __attribute__((aligned(16))) unsigned char si_smem[];
@@ -139,8 +144,8 @@ __global__ void __launch_bounds__(SI_THREADS) small_softmax_iteration_kernel(Sma
     constexpr int WP = CAP + 4;                               // floats per padded row of W: the eight rows a wave reads
                                                               // together then lie in different LDS banks
     const int t0 = threadIdx.x;
-    const int i = p.workers ? p.workers[blockIdx.x] : (int)blockIdx.x;
-    if ((unsigned)i >= (unsigned)p.M) return;
+    int i = (int)blockIdx.x;
+    if constexpr (SLOTS) i = p.slots.worker[blockIdx.x];
     const int pitch = p.din + (MM ? SI_MM_PAD : SI_SPLIT);
     float *xl = reinterpret_cast<float *>(si_smem);           // [ld]  the worker's parameters (W row-major [din][dout], b)
     float *gl = xl + p.ld;                                    // [ld]  its gradient
@@ -153,7 +158,9 @@ __global__ void __launch_bounds__(SI_THREADS) small_softmax_iteration_kernel(Sma
     int32_t *ib = reinterpret_cast<int32_t *>(part + (MM ? SI_MM_PART : 0));   // [2][B] batch rows (shard-local) of this and the next iteration
     int32_t *yl = ib + 2 * p.B;                               // [2][B] their labels
     int32_t *cnt = yl + 2 * p.B;                              // [2] thresholds of the peer draw that are <= u
-    const uint64_t iter0 = iteration_of(p.iter) + (p.workers ? (uint64_t)blockIdx.x : 0ull);
+    uint64_t iter0;
+    if constexpr (SLOTS) iter0 = p.slots.first + p.slots.step[blockIdx.x];
+    else iter0 = iteration_of(p.iter);
     const int n_vec = (int)(p.ld >> 2);
     const float invB = 1.0f / (float)p.B;
     const uint32_t n_i = (uint32_t)p.n_rows[i];
@@ -568,51 +575,47 @@ bool small_iter_ok(int model_is_mlp, int n_layers, int bf16, int B, int64_t din,
            small_iter_lds(B, (int)din, (int)dout, ld) <= (size_t)SI_LDS_LIMIT;
 }
 
-static const void *small_iter_kernel(int B, int64_t din, int64_t dout)
+template <class Args> static const void *small_iter_kernel(int B, int64_t din, int64_t dout)
 {
     if (small_iter_mm(B, din, dout)) {
-        if (B == 16) return reinterpret_cast<const void *>(small_softmax_iteration_kernel<16, 1>);
-        if (B == 32) return reinterpret_cast<const void *>(small_softmax_iteration_kernel<16, 2>);
-        return reinterpret_cast<const void *>(small_softmax_iteration_kernel<16, 4>);
+        if (B == 16) return reinterpret_cast<const void *>(small_softmax_iteration_kernel<16, 1, Args>);
+        if (B == 32) return reinterpret_cast<const void *>(small_softmax_iteration_kernel<16, 2, Args>);
+        return reinterpret_cast<const void *>(small_softmax_iteration_kernel<16, 4, Args>);
     }
-    if (dout <= 8) return reinterpret_cast<const void *>(small_softmax_iteration_kernel<8>);
-    if (dout <= 16) return reinterpret_cast<const void *>(small_softmax_iteration_kernel<16>);
-    return reinterpret_cast<const void *>(small_softmax_iteration_kernel<SI_MAX_OUT>);
+    if (dout <= 8) return reinterpret_cast<const void *>(small_softmax_iteration_kernel<8, 0, Args>);
+    if (dout <= 16) return reinterpret_cast<const void *>(small_softmax_iteration_kernel<16, 0, Args>);
+    return reinterpret_cast<const void *>(small_softmax_iteration_kernel<SI_MAX_OUT, 0, Args>);
 }
 
-hipError_t prepare_small_iter()
+// For the shape of a context: both forms of its kernel.
+hipError_t prepare_small_iter(int B, int64_t din, int64_t dout)
 {
-    const void *kernels[] = {reinterpret_cast<const void *>(small_softmax_iteration_kernel<8>),
-                             reinterpret_cast<const void *>(small_softmax_iteration_kernel<16>),
-                             reinterpret_cast<const void *>(small_softmax_iteration_kernel<SI_MAX_OUT>),
-                             reinterpret_cast<const void *>(small_softmax_iteration_kernel<16, 1>),
-                             reinterpret_cast<const void *>(small_softmax_iteration_kernel<16, 2>),
-                             reinterpret_cast<const void *>(small_softmax_iteration_kernel<16, 4>)};
-    for (const void *k : kernels) {
-        const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, SI_LDS_LIMIT);
-        if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
+    hipError_t e = hipFuncSetAttribute(small_iter_kernel<SmallIterArgs>(B, din, dout), hipFuncAttributeMaxDynamicSharedMemorySize, SI_LDS_LIMIT);
+    if (e == hipSuccess)
+        e = hipFuncSetAttribute(small_iter_kernel<SmallSlotArgs>(B, din, dout), hipFuncAttributeMaxDynamicSharedMemorySize, SI_LDS_LIMIT);
+    return e;
 }
 
 // cooperative != 0: every workgroup must be resident (the caller has checked M against small_iter_max_resident()).
 hipError_t launch_small_iter(hipStream_t s, const SmallIterLaunch &a, int cooperative)
 {
-    SmallIterArgs p{};
+    SmallSlotArgs p{};
     p.M = a.M; p.B = a.B; p.din = (int)a.din; p.dout = (int)a.dout; p.D = a.D; p.ld = a.ld;
     p.feats = a.feats; p.labels = a.labels; p.row0 = a.row0; p.n_rows = a.n_rows;
     p.thr = a.thr; p.last = a.last; p.w = a.w;
     p.x_first = a.x_first; p.x_second = a.x_second; p.V = a.V; p.G = a.G; p.loss = a.loss; p.peers = a.peers; p.idx = a.idx;
     p.alpha = a.alpha; p.mu = a.mu; p.wd = a.wd; p.seed = a.seed; p.iter = a.iter; p.n_iters = a.n_iters;
     p.grad_only = a.grad_only; p.barrier = a.barrier; p.barrier_base = a.barrier_base; p.fault = a.fault;
-    p.workers = a.grad_only ? a.workers : nullptr;
     p.patience = a.patience;
-    const unsigned groups = p.workers ? (unsigned)a.n_workers : (unsigned)a.M;
     const size_t lds = small_iter_lds(a.B, p.din, p.dout, a.ld);
-    void *args[] = {&p};
-    if (cooperative)
-        return hipLaunchCooperativeKernel(small_iter_kernel(a.B, a.din, a.dout), dim3(groups), dim3(SI_THREADS), args, (unsigned)lds, s);
-    return hipLaunchKernel(small_iter_kernel(a.B, a.din, a.dout), dim3(groups), dim3(SI_THREADS), args, lds, s);
+    void *args[] = {&p};                    // the shorter struct is its beginning
+    if (a.grad_only && a.slots) {
+        p.slots = *a.slots;
+        return hipLaunchKernel(small_iter_kernel<SmallSlotArgs>(a.B, a.din, a.dout), dim3((unsigned)p.slots.n), dim3(SI_THREADS), args, lds, s);
+    }
+    const void *kernel = small_iter_kernel<SmallIterArgs>(a.B, a.din, a.dout);
+    if (cooperative) return hipLaunchCooperativeKernel(kernel, dim3((unsigned)a.M), dim3(SI_THREADS), args, (unsigned)lds, s);
+    return hipLaunchKernel(kernel, dim3((unsigned)a.M), dim3(SI_THREADS), args, lds, s);
 }
 
 // How many workgroups of the kernel fit on the device at once with this much LDS each (0 if unknown).
@@ -622,7 +625,7 @@ int small_iter_max_resident(int B, int64_t din, int64_t dout, int64_t ld)
     hipDeviceProp_t prop;
     if (hipGetDevice(&dev) != hipSuccess || hipGetDeviceProperties(&prop, dev) != hipSuccess) return 0;
     if (!prop.cooperativeLaunch) return 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, small_iter_kernel(B, din, dout), SI_THREADS,
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, small_iter_kernel<SmallIterArgs>(B, din, dout), SI_THREADS,
                                                      small_iter_lds(B, (int)din, (int)dout, ld)) != hipSuccess)
         return 0;
     return per_cu * prop.multiProcessorCount;

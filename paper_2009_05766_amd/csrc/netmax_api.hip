@@ -1,6 +1,7 @@
 // C ABI of the library (see include/netmax.h): context, host-side policy tables, argument checks and
 // kernel launches.  Everything that touches model data runs in the kernels of this directory.
 #include "../../include/netmax.h"
+#include "async_plan.h"
 #include "kernels.h"
 #include "layout.h"
 #include "philox.h"
@@ -68,7 +69,6 @@ struct netmax_ctx {
     int sub_cap = 0;                          // slots allocated
     float *d_xc = nullptr, *d_gc = nullptr, *d_lossc = nullptr;
     int64_t *d_row0c = nullptr;
-    int32_t *d_nrowsc = nullptr;
     uint64_t iterations = 0;
     // small softmax-regression models: whole iterations in one kernel (k_small_iter.hip)
     bool small = false;                       // the model qualifies
@@ -227,7 +227,7 @@ static void release(netmax_ctx *ctx)
     (void)hipFree(ctx->d_partial); (void)hipFree(ctx->d_cd);
     (void)hipFree(ctx->d_act_thr); (void)hipFree(ctx->d_fuse_tiles); (void)hipFree(ctx->d_tail_tiles);
     (void)hipFree(ctx->d_barrier); (void)hipFree(ctx->d_fault);
-    (void)hipFree(ctx->d_xc); (void)hipFree(ctx->d_gc); (void)hipFree(ctx->d_lossc); (void)hipFree(ctx->d_row0c); (void)hipFree(ctx->d_nrowsc);
+    (void)hipFree(ctx->d_xc); (void)hipFree(ctx->d_gc); (void)hipFree(ctx->d_lossc); (void)hipFree(ctx->d_row0c);
     delete ctx;
 }
 
@@ -372,7 +372,7 @@ extern "C" int netmax_init(netmax_ctx **out, const netmax_config *cfg)
         INIT_TRY(prepare_f32_layers());
         ctx->small = small_iter_ok(1, cfg->n_layers, cfg->gemm_in == NETMAX_BF16, cfg->batch, cfg->dims[0], cfg->dims[1], cfg->ld);
         if (ctx->small) {
-            INIT_TRY(prepare_small_iter());
+            INIT_TRY(prepare_small_iter(cfg->batch, cfg->dims[0], cfg->dims[1]));
             ctx->small_resident = small_iter_max_resident(cfg->batch, cfg->dims[0], cfg->dims[1], cfg->ld);
             INIT_TRY(hipMalloc(&ctx->d_barrier, sizeof(unsigned)));
             INIT_TRY(hipMalloc(&ctx->d_fault, sizeof(int)));
@@ -582,7 +582,7 @@ static SmallIterLaunch small_launch(netmax_ctx *ctx, const IterRef &iter, int n_
     a.alpha = c.lr; a.mu = c.momentum; a.wd = c.weight_decay; a.seed = c.seed; a.iter = iter; a.n_iters = n_iters;
     a.grad_only = grad_only ? 1 : 0;
     a.barrier = ctx->d_barrier; a.barrier_base = ctx->barrier_count; a.fault = ctx->d_fault;
-    a.workers = nullptr; a.n_workers = 0;
+    a.slots = nullptr;
     a.patience = ctx->barrier_patience;
     return a;
 }
@@ -894,11 +894,13 @@ static int host_draw(const uint32_t *row, int n, int last, uint32_t u)
     return pos < last ? pos : last;
 }
 
-constexpr int ASYNC_MAX_BATCH = 32;
+// Global steps planned at a time: long enough that few levels are cut short at its end, short enough that the first launch does
+// not wait for the plan (two Philox blocks and two searches per step).
+constexpr int ASYNC_WINDOW = 512;
 
-// The gradients of the n listed workers (device list `workers`, consecutive global steps from k0) into the compact
-// matrix d_gc: their rows and shard descriptors are gathered, the grouped kernels run on n groups.
-static int enqueue_subset_gradient(netmax_ctx *ctx, const int32_t *workers, int n, uint64_t k0)
+// The gradients of the slots' workers into the compact matrix d_gc: their rows are gathered, the grouped kernels run on
+// slots.n groups.
+static int enqueue_subset_gradient(netmax_ctx *ctx, const AsyncSlots &slots)
 {
     const netmax_config &c = ctx->cfg;
     if (!ctx->sub_cap) {
@@ -907,18 +909,15 @@ static int enqueue_subset_gradient(netmax_ctx *ctx, const int32_t *workers, int 
         HIP_TRY(ctx, hipMalloc(&ctx->d_gc, (size_t)cap * c.ld * sizeof(float)));
         HIP_TRY(ctx, hipMalloc(&ctx->d_lossc, (size_t)cap * sizeof(float)));
         HIP_TRY(ctx, hipMalloc(&ctx->d_row0c, (size_t)cap * sizeof(int64_t)));
-        HIP_TRY(ctx, hipMalloc(&ctx->d_nrowsc, (size_t)cap * sizeof(int32_t)));
         ctx->sub_cap = cap;
     }
-    launch_gather_shards(ctx->stream, c.M, n, workers, ctx->d_row0, ctx->d_nrows, ctx->d_row0c, ctx->d_nrowsc);
-    launch_sample_batch_subset(ctx->stream, n, c.batch, workers, ctx->d_nrowsc, c.seed, k0, ctx->d_idx);
-    launch_gather_rows(ctx->stream, c.M, n, c.ld, workers, ctx->x_cur, ctx->d_xc);
+    launch_gather_slots(ctx->stream, c.M, c.ld, slots, ctx->x_cur, ctx->d_xc, c.batch, ctx->d_row0, ctx->d_nrows, c.seed, ctx->d_row0c,
+                        ctx->d_idx);
     MlpPlan p = make_plan(ctx);
-    p.M = n;
+    p.M = slots.n;
     p.row0 = ctx->d_row0c;
     p.loss = ctx->d_lossc;
     launch_mlp_grad(ctx->stream, p, ctx->d_xc, ctx->d_gc);
-    launch_scatter_loss(ctx->stream, c.M, n, workers, ctx->d_lossc, ctx->d_loss);
     return check_launch(ctx, "subset gradient");
 }
 
@@ -936,49 +935,51 @@ extern "C" int netmax_async_run(netmax_ctx *ctx, uint64_t first_step, uint64_t n
     launch_async_draw(ctx->stream, c.M, ctx->d_act_thr, ctx->act_last, ctx->d_thr, ctx->d_last, c.seed, first_step, n_steps,
                       active_dev, peers_dev);
     int rc = check_launch(ctx, "async_draw");
-    // The host repeats the draws (integer work on the same tables) and cuts the run into batches of consecutive
-    // steps that cannot see each other: a step joins the batch unless its active worker was active or pulled
-    // from earlier in the batch, or it pulls from a worker that was active.  A batch is one set of launches.
+    // The host repeats the draws (integer work on the same tables) and sorts a window of steps into batches of steps that do
+    // not see each other.  A batch is one set of launches.
     const int cap = std::min<int>(c.M, ASYNC_MAX_BATCH);
-    std::vector<uint8_t> wrote(c.M, 0), read(c.M, 0);
-    std::vector<int> touched;
-    uint64_t s0 = 0;
-    while (s0 < n_steps && rc == NETMAX_OK) {
-        int n = 0;
-        touched.clear();
-        while (s0 + n < n_steps && n < cap) {
-            const uint64_t k = first_step + s0 + n;
+    AsyncPlanner planner(c.M);
+    std::vector<int> active, peer;
+    for (uint64_t s0 = 0; s0 < n_steps && rc == NETMAX_OK; s0 += ASYNC_WINDOW) {
+        const int n = (int)std::min<uint64_t>(ASYNC_WINDOW, n_steps - s0);
+        active.resize(n);
+        peer.resize(n);
+        for (int q = 0; q < n; ++q) {
+            const uint64_t k = first_step + s0 + (uint64_t)q;
             const int i = host_draw(ctx->h_act_thr.data(), c.M, ctx->act_last, draw_block(c.seed, STREAM_ACTIVE, 0u, 0u, k).a);
-            const int m = host_draw(ctx->h_thr.data() + (size_t)i * c.M, c.M, ctx->h_last[i],
-                                    draw_block(c.seed, STREAM_PEER, 0u, (uint32_t)i, k).a);
-            if (n > 0 && (wrote[i] || read[i] || wrote[m])) break;
-            wrote[i] = 1;
-            read[m] = 1;
-            touched.push_back(i);
-            touched.push_back(m);
-            ++n;
+            active[q] = i;
+            peer[q] = host_draw(ctx->h_thr.data() + (size_t)i * c.M, c.M, ctx->h_last[i],
+                                draw_block(c.seed, STREAM_PEER, 0u, (uint32_t)i, k).a);
         }
-        for (int q : touched) wrote[q] = read[q] = 0;
-        const uint64_t k0 = first_step + s0;
-        int source = 0;
-        if (c.model == NETMAX_MLP) {
-            if (ctx->small) {
-                SmallIterLaunch a = small_launch(ctx, IterRef{k0, nullptr}, 1, true, nullptr);
-                a.workers = active_dev + s0;
-                a.n_workers = n;
-                const hipError_t e = launch_small_iter(ctx->stream, a, 0);
-                if (e != hipSuccess) return fail(ctx, NETMAX_EDEVICE, std::string("small-model gradient kernel: ") + hipGetErrorString(e));
-                source = 1;
-            } else {
-                rc = enqueue_subset_gradient(ctx, active_dev + s0, n, k0);
-                if (rc != NETMAX_OK) break;
-                source = 2;
+        planner.plan(active.data(), peer.data(), n, cap);
+        for (int b = 0; b < planner.batches() && rc == NETMAX_OK; ++b) {
+            AsyncSlots slots;
+            slots.n = planner.start(b + 1) - planner.start(b);
+            slots.first = first_step + s0;
+            for (int q = 0; q < ASYNC_MAX_BATCH; ++q) {
+                const int step = planner.order()[planner.start(b) + (q < slots.n ? q : 0)];
+                slots.worker[q] = active[step];
+                slots.peer[q] = peer[step];
+                slots.step[q] = (uint32_t)step;
             }
+            int source = 0;
+            if (c.model == NETMAX_MLP) {
+                if (ctx->small) {
+                    SmallIterLaunch a = small_launch(ctx, IterRef{0, nullptr}, 1, true, nullptr);
+                    a.slots = &slots;
+                    const hipError_t e = launch_small_iter(ctx->stream, a, 0);
+                    if (e != hipSuccess) return fail(ctx, NETMAX_EDEVICE, std::string("small-model gradient kernel: ") + hipGetErrorString(e));
+                    source = 1;
+                } else {
+                    rc = enqueue_subset_gradient(ctx, slots);
+                    if (rc != NETMAX_OK) break;
+                    source = 2;
+                }
+            }
+            launch_async_rows(ctx->stream, source, c.M, c.D, c.ld, ctx->x_cur, ctx->v, ctx->g, ctx->d_gc, slots, ctx->d_w, c.lr, c.momentum,
+                              c.weight_decay, c.grad_sigma, c.seed, ctx->d_lossc, ctx->d_loss);
+            rc = check_launch(ctx, "async_rows");
         }
-        launch_async_rows(ctx->stream, source, c.M, c.D, c.ld, ctx->x_cur, ctx->v, ctx->g, ctx->d_gc, n, active_dev + s0,
-                          peers_dev + s0, ctx->d_w, c.lr, c.momentum, c.weight_decay, c.grad_sigma, c.seed, k0);
-        rc = check_launch(ctx, "async_rows");
-        s0 += (uint64_t)n;
     }
     if (rc == NETMAX_OK) ctx->iterations = first_step + n_steps;
     return rc;
