@@ -7,8 +7,8 @@ namespace netmax {
 
 // One thread per worker.  Row i of `thr` holds non-decreasing cumulative thresholds; the peer is the
 // number of thresholds <= u (the first m whose threshold exceeds u), clamped to the last positive entry.
-__device__ __forceinline__ void draw_peer(int i, int M, const uint32_t *__restrict__ thr, const int32_t *__restrict__ last,
-                                          uint64_t seed, uint64_t iter, int32_t *__restrict__ peer)
+__device__ __forceinline__ int draw_peer(int i, int M, const uint32_t *__restrict__ thr, const int32_t *__restrict__ last,
+                                         uint64_t seed, uint64_t iter)
 {
     const uint32_t u = draw_block(seed, STREAM_PEER, 0u, (uint32_t)i, iter).a;
     const uint32_t *row = thr + (size_t)i * M;
@@ -18,7 +18,7 @@ __device__ __forceinline__ void draw_peer(int i, int M, const uint32_t *__restri
         if (row[mid] <= u) lo = mid + 1; else hi = mid;
     }
     const int l = last[i];
-    peer[i] = lo < l ? lo : l;
+    return lo < l ? lo : l;
 }
 
 __global__ void __launch_bounds__(256) sample_peers_kernel(int M, const uint32_t *__restrict__ thr,
@@ -27,7 +27,7 @@ __global__ void __launch_bounds__(256) sample_peers_kernel(int M, const uint32_t
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= M) return;
-    draw_peer(i, M, thr, last, seed, iteration_of(iter_ref), peer);
+    peer[i] = draw_peer(i, M, thr, last, seed, iteration_of(iter_ref));
 }
 
 // One thread per Philox block of four draws: idx[i][4q..4q+3] = floor(word * n_i / 2^32).
@@ -54,21 +54,26 @@ __global__ void __launch_bounds__(256) sample_batch_kernel(int M, int B, const i
     draw_batch_quad(t, B, quads, n_rows, seed, iteration_of(iter_ref), idx);
 }
 
-// Both draws of an iteration in one launch (they are independent): the first peer_blocks workgroups draw the peers,
-// the others the batch rows.
-__global__ void __launch_bounds__(256) sample_iteration_kernel(int M, const uint32_t *__restrict__ thr,
-                                                               const int32_t *__restrict__ last, int32_t *__restrict__ peer,
-                                                               int peer_blocks, int B, const int32_t *__restrict__ n_rows,
-                                                               int32_t *__restrict__ idx, uint64_t seed, IterRef iter_ref)
+// The draws of consecutive iterations in one launch (they depend on nothing but the iteration number): the first peer_blocks
+// workgroups of a row of the grid draw the peers, the others the batch rows; row q of the grid works for iteration iter + q and
+// writes to row q of peer [n][M] and idx [n][M][B].  last_peer: the last iteration's peers go there too (may be the same memory).
+__global__ void __launch_bounds__(256) sample_iterations_kernel(int M, const uint32_t *__restrict__ thr,
+                                                                const int32_t *__restrict__ last, int32_t *peer, int32_t *last_peer,
+                                                                int peer_blocks, int B, const int32_t *__restrict__ n_rows,
+                                                                int32_t *__restrict__ idx, uint64_t seed, IterRef iter_ref)
 {
-    const uint64_t iter = iteration_of(iter_ref);
+    const unsigned q = blockIdx.y;
+    const uint64_t iter = iteration_of(iter_ref) + q;
     if ((int)blockIdx.x < peer_blocks) {
         const int i = blockIdx.x * blockDim.x + threadIdx.x;
-        if (i < M) draw_peer(i, M, thr, last, seed, iter, peer);
+        if (i >= M) return;
+        const int m = draw_peer(i, M, thr, last, seed, iter);
+        peer[(size_t)q * M + i] = m;
+        if (q == gridDim.y - 1) last_peer[i] = m;
     } else {
         const int quads = (B + 3) >> 2;
         const int t = ((int)blockIdx.x - peer_blocks) * blockDim.x + threadIdx.x;
-        if (t < M * quads) draw_batch_quad(t, B, quads, n_rows, seed, iter, idx);
+        if (t < M * quads) draw_batch_quad(t, B, quads, n_rows, seed, iter, idx + (size_t)q * M * B);
     }
 }
 
@@ -85,12 +90,12 @@ void launch_sample_batch(hipStream_t s, int M, int B, const int32_t *n_rows, uin
     hipLaunchKernelGGL(sample_batch_kernel, dim3((n + 255) / 256), dim3(256), 0, s, M, B, n_rows, seed, iter, idx);
 }
 
-void launch_sample_iteration(hipStream_t s, int M, const uint32_t *thr, const int32_t *last, int32_t *peer, int B,
-                             const int32_t *n_rows, int32_t *idx, uint64_t seed, const IterRef &iter)
+void launch_sample_iterations(hipStream_t s, int n_iters, int M, const uint32_t *thr, const int32_t *last, int32_t *peer, int32_t *last_peer,
+                              int B, const int32_t *n_rows, int32_t *idx, uint64_t seed, const IterRef &iter)
 {
     const int peer_blocks = (M + 255) / 256, n = M * ((B + 3) / 4);
-    hipLaunchKernelGGL(sample_iteration_kernel, dim3(peer_blocks + (n + 255) / 256), dim3(256), 0, s, M, thr, last, peer,
-                       peer_blocks, B, n_rows, idx, seed, iter);
+    hipLaunchKernelGGL(sample_iterations_kernel, dim3(peer_blocks + (n + 255) / 256, n_iters), dim3(256), 0, s, M, thr, last, peer,
+                       last_peer, peer_blocks, B, n_rows, idx, seed, iter);
 }
 
 // Algorithm 2, UpdateTimeVector, on a simulated network: worker i records the time t[i][m] of its iteration with

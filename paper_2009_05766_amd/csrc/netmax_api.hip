@@ -13,6 +13,7 @@
 #include <mutex>
 #include <new>
 #include <string>
+#include <utility>
 #include <vector>
 
 using namespace netmax;
@@ -24,6 +25,7 @@ struct netmax_ctx {
     bool has_adj = false;
     hipStream_t stream = nullptr;
     int device = 0;
+    void *d_block = nullptr;                  // the one allocation that the pointers set in netmax_init lie in
     // policy tables (device) and their host images
     uint32_t *d_thr = nullptr;
     int32_t *d_last = nullptr;
@@ -39,7 +41,9 @@ struct netmax_ctx {
     bool data_bound = false;
     int64_t *d_row0 = nullptr;
     int32_t *d_nrows = nullptr;
-    int32_t *d_idx = nullptr;
+    int32_t *d_idx = nullptr;                 // batch rows [draw_chunk][M][batch]; a single iteration uses the first block
+    int32_t *d_draw_peers = nullptr;          // netmax_run: peers [draw_chunk][M] of the iterations drawn ahead
+    int draw_chunk = 1;                       // iterations that netmax_run draws in one launch
     float *d_act[NETMAX_MAX_LAYERS + 1] = {};
     float *d_dz[2] = {};
     float *d_loss = nullptr;
@@ -84,6 +88,9 @@ struct netmax_ctx {
     const int32_t *graph_peers = nullptr;
     std::string err;
 };
+
+constexpr int DRAW_AHEAD = 16;
+constexpr int64_t DRAW_AHEAD_INTS = 1 << 20;
 
 static thread_local std::string g_init_error;
 
@@ -214,19 +221,8 @@ static void drop_graphs(netmax_ctx *ctx)
 static void release(netmax_ctx *ctx)
 {
     drop_graphs(ctx);
-    (void)hipFree(ctx->d_iter);
-    (void)hipFree(ctx->d_thr); (void)hipFree(ctx->d_last); (void)hipFree(ctx->d_w);
-    (void)hipFree(ctx->d_row0); (void)hipFree(ctx->d_nrows); (void)hipFree(ctx->d_idx);
-    for (auto *p : ctx->d_act) (void)hipFree(p);
-    (void)hipFree(ctx->d_dz[0]); (void)hipFree(ctx->d_dz[1]);
-    (void)hipFree(ctx->d_loss); (void)hipFree(ctx->d_flag);
-    for (auto *p : ctx->d_hb) (void)hipFree(p);
-    for (auto *p : ctx->d_ht) (void)hipFree(p);
-    for (auto *p : ctx->d_dzb) (void)hipFree(p);
-    for (auto *p : ctx->d_dzt) (void)hipFree(p);
-    (void)hipFree(ctx->d_partial); (void)hipFree(ctx->d_cd);
-    (void)hipFree(ctx->d_act_thr); (void)hipFree(ctx->d_fuse_tiles); (void)hipFree(ctx->d_tail_tiles);
-    (void)hipFree(ctx->d_barrier); (void)hipFree(ctx->d_fault);
+    (void)hipFree(ctx->d_block);
+    (void)hipFree(ctx->d_act_thr); (void)hipFree(ctx->d_fuse_tiles);
     (void)hipFree(ctx->d_xc); (void)hipFree(ctx->d_gc); (void)hipFree(ctx->d_lossc); (void)hipFree(ctx->d_row0c);
     delete ctx;
 }
@@ -338,48 +334,52 @@ extern "C" int netmax_init(netmax_ctx **out, const netmax_config *cfg)
     INIT_TRY(hipGetDevice(&ctx->device));
     INIT_TRY(prepare_mix());
     INIT_TRY(prepare_mix_synth());
-    INIT_TRY(hipMalloc(&ctx->d_thr, mm * sizeof(uint32_t)));
-    INIT_TRY(hipMalloc(&ctx->d_last, M * sizeof(int32_t)));
-    INIT_TRY(hipMalloc(&ctx->d_w, mm * sizeof(float)));
-    INIT_TRY(hipMalloc(&ctx->d_partial, (size_t)consensus_partials(cfg->ld) * sizeof(double)));
-    INIT_TRY(hipMalloc(&ctx->d_cd, sizeof(double)));
-    INIT_TRY(hipMalloc(&ctx->d_iter, sizeof(uint64_t)));
     prepare_kernels();
+    // what the context keeps on the device, carved from one allocation
+    std::vector<std::pair<void **, size_t>> parts;
+    auto want = [&](auto **where, size_t count) { parts.emplace_back(reinterpret_cast<void **>(where), count * sizeof(**where)); };
+    want(&ctx->d_thr, mm);
+    want(&ctx->d_last, M);
+    want(&ctx->d_w, mm);
+    want(&ctx->d_partial, (size_t)consensus_partials(cfg->ld));
+    want(&ctx->d_cd, 1);
+    want(&ctx->d_iter, 1);
+    // a few launches' worth of draws ahead, at most 4 MB of them
+    ctx->draw_chunk = (int)std::max<int64_t>(1, std::min<int64_t>(DRAW_AHEAD, DRAW_AHEAD_INTS / ((int64_t)M * (1 + (cfg->model == NETMAX_MLP ? cfg->batch : 0)))));
+    want(&ctx->d_draw_peers, (size_t)ctx->draw_chunk * M);
+    std::vector<int32_t> tail_tiles;
     if (cfg->model == NETMAX_MLP) {
         const size_t MB = (size_t)M * cfg->batch;
         int64_t widest = 0;
         for (int l = 1; l <= cfg->n_layers; ++l) {
-            INIT_TRY(hipMalloc(&ctx->d_act[l], MB * cfg->dims[l] * sizeof(float)));
+            want(&ctx->d_act[l], MB * cfg->dims[l]);
             if (cfg->dims[l] > widest) widest = cfg->dims[l];
         }
-        INIT_TRY(hipMalloc(&ctx->d_dz[0], MB * widest * sizeof(float)));
-        INIT_TRY(hipMalloc(&ctx->d_dz[1], MB * widest * sizeof(float)));
+        for (int q = 0; q < 2; ++q) want(&ctx->d_dz[q], MB * widest);
         if (cfg->gemm_in == NETMAX_BF16) {
-            for (int l = 0; l < cfg->n_layers; ++l) {
-                if (l > 0) INIT_TRY(hipMalloc(&ctx->d_hb[l], MB * cfg->dims[l] * sizeof(uint16_t)));
-                if (l > 0) INIT_TRY(hipMalloc(&ctx->d_ht[l], MB * cfg->dims[l] * sizeof(uint16_t)));
+            for (int l = 1; l < cfg->n_layers; ++l) {
+                want(&ctx->d_hb[l], MB * cfg->dims[l]);
+                want(&ctx->d_ht[l], MB * cfg->dims[l]);
             }
             for (int q = 0; q < 2; ++q) {
-                INIT_TRY(hipMalloc(&ctx->d_dzb[q], MB * widest * sizeof(uint16_t)));
-                INIT_TRY(hipMalloc(&ctx->d_dzt[q], MB * widest * sizeof(uint16_t)));
+                want(&ctx->d_dzb[q], MB * widest);
+                want(&ctx->d_dzt[q], MB * widest);
             }
         }
-        INIT_TRY(hipMalloc(&ctx->d_idx, MB * sizeof(int32_t)));
-        INIT_TRY(hipMalloc(&ctx->d_row0, M * sizeof(int64_t)));
-        INIT_TRY(hipMalloc(&ctx->d_nrows, M * sizeof(int32_t)));
-        INIT_TRY(hipMalloc(&ctx->d_loss, M * sizeof(float)));
-        INIT_TRY(hipMalloc(&ctx->d_flag, sizeof(int32_t)));
+        want(&ctx->d_idx, MB * ctx->draw_chunk);
+        want(&ctx->d_row0, M);
+        want(&ctx->d_nrows, M);
+        want(&ctx->d_loss, M);
+        want(&ctx->d_flag, 1);
         INIT_TRY(prepare_f32_layers());
         ctx->small = small_iter_ok(1, cfg->n_layers, cfg->gemm_in == NETMAX_BF16, cfg->batch, cfg->dims[0], cfg->dims[1], cfg->ld);
         if (ctx->small) {
             INIT_TRY(prepare_small_iter(cfg->batch, cfg->dims[0], cfg->dims[1]));
             ctx->small_resident = small_iter_max_resident(cfg->batch, cfg->dims[0], cfg->dims[1], cfg->ld);
-            INIT_TRY(hipMalloc(&ctx->d_barrier, sizeof(unsigned)));
-            INIT_TRY(hipMalloc(&ctx->d_fault, sizeof(int)));
-            INIT_TRY(hipMemset(ctx->d_barrier, 0, sizeof(unsigned)));
-            INIT_TRY(hipMemset(ctx->d_fault, 0, sizeof(int)));
+            want(&ctx->d_barrier, 1);
+            want(&ctx->d_fault, 1);
         }
-        const MlpPlan plan = make_plan(ctx);
+        const MlpPlan plan = make_plan(ctx);         // its shapes: nothing is allocated yet
         for (int l = 0; l < cfg->n_layers && !ctx->small; ++l)
             if (update_end(plan, l) > 0) {
                 ctx->tail = true;
@@ -387,15 +387,24 @@ extern "C" int netmax_init(netmax_ctx **out, const netmax_config *cfg)
                 ctx->tail_skip.hi[ctx->tail_skip.n] = update_end(plan, l);
                 ++ctx->tail_skip.n;
             }
-        if (ctx->tail) {
-            const std::vector<int32_t> tiles = tiles_outside(ctx->tail_skip, cfg->ld);
-            ctx->n_tail_tiles = (int)tiles.size();
-            if (!tiles.empty()) {
-                INIT_TRY(hipMalloc(&ctx->d_tail_tiles, tiles.size() * sizeof(int32_t)));
-                INIT_TRY(hipMemcpy(ctx->d_tail_tiles, tiles.data(), tiles.size() * sizeof(int32_t), hipMemcpyHostToDevice));
-            }
-        }
+        if (ctx->tail) tail_tiles = tiles_outside(ctx->tail_skip, cfg->ld);
+        ctx->n_tail_tiles = (int)tail_tiles.size();
+        want(&ctx->d_tail_tiles, tail_tiles.size());
     }
+    size_t total = 0;
+    for (const auto &part : parts) total += (part.second + 255) / 256 * 256;
+    INIT_TRY(hipMalloc(&ctx->d_block, total));
+    char *at = (char *)ctx->d_block;
+    for (const auto &part : parts) {
+        *part.first = at;
+        at += (part.second + 255) / 256 * 256;
+    }
+    if (ctx->small) {
+        INIT_TRY(hipMemset(ctx->d_barrier, 0, sizeof(unsigned)));
+        INIT_TRY(hipMemset(ctx->d_fault, 0, sizeof(int)));
+    }
+    if (!tail_tiles.empty())
+        INIT_TRY(hipMemcpy(ctx->d_tail_tiles, tail_tiles.data(), tail_tiles.size() * sizeof(int32_t), hipMemcpyHostToDevice));
 #undef INIT_TRY
     rc = upload_tables(ctx);
     if (rc != NETMAX_OK) {
@@ -543,10 +552,6 @@ static int enqueue_sample_peers(netmax_ctx *ctx, const IterRef &iter, int32_t *p
     return check_launch(ctx, "sample_peers");
 }
 
-// Peer draw and local step of one iteration inside netmax_run: perceptrons that take the kernel-by-kernel path draw
-// peers and batch rows in one launch.
-static int enqueue_draws_and_local_step(netmax_ctx *ctx, const IterRef &iter, int32_t *peers_dev);
-
 static MlpPlan make_plan(const netmax_ctx *ctx)
 {
     const netmax_config &c = ctx->cfg;
@@ -598,8 +603,8 @@ static int enqueue_small(netmax_ctx *ctx, const IterRef &iter, int n_iters, bool
 
 // run_peers != nullptr (netmax_run): weight-gradient kernels apply the update where the context has it so, enqueue_run_mix then
 // covers the remaining columns only.
-// batch_drawn: the batch rows of this iteration are in d_idx already.
-static int enqueue_local_step(netmax_ctx *ctx, const IterRef &iter, const int32_t *run_peers = nullptr, bool batch_drawn = false)
+// drawn: the batch rows of this iteration if they have been drawn already.
+static int enqueue_local_step(netmax_ctx *ctx, const IterRef &iter, const int32_t *run_peers = nullptr, const int32_t *drawn = nullptr)
 {
     const netmax_config &c = ctx->cfg;
     if (c.model == NETMAX_FLAT) {
@@ -608,24 +613,23 @@ static int enqueue_local_step(netmax_ctx *ctx, const IterRef &iter, const int32_
         return check_launch(ctx, "synth_grad");
     }
     if (ctx->small) return enqueue_small(ctx, iter, 1, true, nullptr, false);
-    if (!batch_drawn) launch_sample_batch(ctx->stream, c.M, c.batch, ctx->d_nrows, c.seed, iter, ctx->d_idx);
-    const MlpPlan p = make_plan(ctx);
+    if (!drawn) launch_sample_batch(ctx->stream, c.M, c.batch, ctx->d_nrows, c.seed, iter, ctx->d_idx);
+    MlpPlan p = make_plan(ctx);
+    if (drawn) p.idx = drawn;
     const MixArgs mx = mix_args(ctx, run_peers);
     launch_mlp_grad(ctx->stream, p, ctx->x_cur, ctx->g, run_peers && ctx->fuse ? &mx : nullptr,
                     run_peers && ctx->tail && !ctx->fuse ? &mx : nullptr);
     return check_launch(ctx, "mlp_grad");
 }
 
-static int enqueue_draws_and_local_step(netmax_ctx *ctx, const IterRef &iter, int32_t *peers_dev)
+// The draws of n iterations from `iter` on: peers to `peers` [n][M] (the last one's to last_peers too), batch rows of perceptrons
+// to d_idx.
+static int enqueue_draws(netmax_ctx *ctx, const IterRef &iter, int n, int32_t *peers, int32_t *last_peers)
 {
     const netmax_config &c = ctx->cfg;
-    if (c.model == NETMAX_FLAT || ctx->small) {
-        const int rc = enqueue_sample_peers(ctx, iter, peers_dev);
-        return rc != NETMAX_OK ? rc : enqueue_local_step(ctx, iter, peers_dev);
-    }
-    launch_sample_iteration(ctx->stream, c.M, ctx->d_thr, ctx->d_last, peers_dev, c.batch, ctx->d_nrows, ctx->d_idx, c.seed, iter);
-    const int rc = check_launch(ctx, "sample_iteration");
-    return rc != NETMAX_OK ? rc : enqueue_local_step(ctx, iter, peers_dev, true);
+    const int B = c.model == NETMAX_MLP && !ctx->small ? c.batch : 0;
+    launch_sample_iterations(ctx->stream, n, c.M, ctx->d_thr, ctx->d_last, peers, last_peers, B, ctx->d_nrows, ctx->d_idx, c.seed, iter);
+    return check_launch(ctx, "sample_iterations");
 }
 
 // The update of all columns.
@@ -652,6 +656,13 @@ static int enqueue_run_mix(netmax_ctx *ctx, const int32_t *peers_dev, const Iter
     else
         return enqueue_mix(ctx, peers_dev);
     return check_launch(ctx, "mix");
+}
+
+// One iteration of netmax_run behind its draws (`drawn`: its batch rows).
+static int enqueue_run_iteration(netmax_ctx *ctx, const IterRef &iter, const int32_t *peers, const int32_t *drawn)
+{
+    const int rc = enqueue_local_step(ctx, iter, peers, drawn);
+    return rc != NETMAX_OK ? rc : enqueue_run_mix(ctx, peers, iter);
 }
 
 static void flip(netmax_ctx *ctx)
@@ -710,8 +721,8 @@ static int capture_iteration(netmax_ctx *ctx, int dir, int32_t *peers_dev)
     if (ctx->small && !ctx->fuse) {
         rc = enqueue_small(ctx, it, 1, false, peers_dev, false);
     } else {
-        rc = enqueue_draws_and_local_step(ctx, it, peers_dev);
-        if (rc == NETMAX_OK) rc = enqueue_run_mix(ctx, peers_dev, it);
+        rc = enqueue_draws(ctx, it, 1, peers_dev, peers_dev);
+        if (rc == NETMAX_OK) rc = enqueue_run_iteration(ctx, it, peers_dev, ctx->d_idx);
     }
     if (rc == NETMAX_OK) {
         launch_bump_iteration(ctx->stream, ctx->d_iter);
@@ -753,10 +764,16 @@ extern "C" int netmax_run(netmax_ctx *ctx, uint64_t first_iter, int32_t n_iters,
         return NETMAX_OK;
     }
     if (!use_graph) {
+        // draws depend on the iteration number only: one launch makes those of several iterations
+        const int32_t ahead = ctx->draw_chunk;
         for (int32_t k = 0; k < n_iters; ++k) {
             const IterRef it{first_iter + (uint64_t)k, nullptr};
-            int rc = enqueue_draws_and_local_step(ctx, it, peers_dev);
-            if (rc == NETMAX_OK) rc = enqueue_run_mix(ctx, peers_dev, it);
+            const int32_t q = k % ahead;
+            int rc = NETMAX_OK;
+            if (q == 0) rc = enqueue_draws(ctx, it, std::min(ahead, n_iters - k), ctx->d_draw_peers, peers_dev);
+            if (rc == NETMAX_OK)
+                rc = enqueue_run_iteration(ctx, it, ctx->d_draw_peers + (size_t)q * ctx->cfg.M,
+                                           ctx->d_idx ? ctx->d_idx + (size_t)q * ctx->cfg.M * ctx->cfg.batch : nullptr);
             if (rc != NETMAX_OK) return rc;
             flip(ctx);
         }

@@ -45,3 +45,20 @@ def test_run_is_the_separate_calls(name, M, batch, dims, graph):
             assert torch.equal(run.losses(), calls.losses())
     assert not np.array_equal(run.get("x").cpu().numpy(), inp["X0"])
     calls.close(), run.close()
+
+
+@pytest.mark.parametrize("name,over", [("cfg2", dict(M=5, batch=24, n_per_worker=40, dims=(30, 20, 10))), ("cfg3", dict(M=7, D=5000)),
+                                       ("cfg5", dict(M=2, batch=1024, n_per_worker=1100, dims=(20, 8)))])
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 35])
+def test_draws_ahead_are_the_draws_of_each_iteration(name, over, n):
+    """netmax_run draws up to sixteen iterations in one launch: iteration counts around that, and far from zero."""
+    w = workload(name, **over)
+    inp = inputs_of(w)
+    run, calls = make_gpu(w, inp), make_gpu(w, inp)
+    first = 2**32 - 3
+    run.run(first, n)
+    for k in range(n):
+        calls.step(first + k)
+    assert torch.equal(run.peers, calls.peers)
+    assert torch.equal(run.get("x"), calls.get("x")) and torch.equal(run.v, calls.v)
+    run.close(), calls.close()
