@@ -166,6 +166,80 @@ __device__ __forceinline__ void momentum_mix1(float x, float v, float g, float x
     x_new = fmaf(-w, h - x_peer, h);
 }
 
+// ---- fp32 operands as three bfloat16 planes -----------------------------------------------------------------------------
+// x = hi + mid + lo, each the rounding of what the ones before leave (8 + 8 + 8 bits: exact for finite x below 2^127).  Of the nine
+// products of two such sums the six above 2^-25 of the whole are taken, smallest first, each group of sixteen contraction
+// indices with one rounding per product: 6 x 32 cycles where v_mfma_f32_32x32x2_f32 takes 8 x 64.  A value that is not finite
+// does not survive the split (inf - inf) and makes every sum it enters a NaN: the caller looks at its sums and does a product
+// with one that is not finite again in fp32.
+__device__ __forceinline__ void split2(float x0, float x1, uint32_t (&plane)[3])
+{
+    plane[0] = pack_bf16x2(x0, x1);
+    const float r0 = x0 - __uint_as_float(plane[0] << 16), r1 = x1 - __uint_as_float(plane[0] & 0xFFFF0000u);
+    plane[1] = pack_bf16x2(r0, r1);
+    plane[2] = pack_bf16x2(r0 - __uint_as_float(plane[1] << 16), r1 - __uint_as_float(plane[1] & 0xFFFF0000u));
+}
+
+// Four neighbouring k of an operand row into the three planes (plane p of the row starts at dst + p * stride).
+__device__ __forceinline__ void put_split(uint16_t *dst, int stride, f32x4 v)
+{
+    uint32_t a[3], b[3];
+    split2(v[0], v[1], a);
+    split2(v[2], v[3], b);
+#pragma unroll
+    for (int p = 0; p < 3; ++p) *reinterpret_cast<tile_u32x2 *>(dst + p * stride) = tile_u32x2{a[p], b[p]};
+}
+// Two neighbouring k.
+__device__ __forceinline__ void put_split(uint16_t *dst, int stride, float x0, float x1)
+{
+    uint32_t a[3];
+    split2(x0, x1, a);
+#pragma unroll
+    for (int p = 0; p < 3; ++p) *reinterpret_cast<uint32_t *>(dst + p * stride) = a[p];
+}
+// The piece with only its first `left` elements kept, the others 0.
+__device__ __forceinline__ f32x4 first_of(f32x4 v, int left)
+{
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = e < left ? v[e] : 0.0f;
+    return v;
+}
+
+// LDS rows of 32 contraction indices.  Pieces of four k, eight lanes along a row: rows of 64 bytes, their four 16-byte units
+// permuted by the row's group of four, so that neither the writes nor the 128-bit reads of sixteen rows meet a bank twice.
+__device__ __forceinline__ int split_at(int row, int k) { return row * 32 + ((((k >> 3) ^ (row >> 2)) & 3) << 3) + (k & 7); }
+// Pairs of k, sixteen lanes along a row, of columns four apart: rows of 80 bytes do the same for those.
+constexpr int SPLIT_PITCH = 40;
+
+// One step of 32 indices; As (split_at) and Bs (SPLIT_PITCH) hold three planes, `sa` and `sb` elements apart.
+template <int RI, int CJ>
+__device__ __forceinline__ void split_multiply(const uint16_t *As, int sa, const uint16_t *Bs, int sb, int m0, int n0, int lane,
+                                               tile_f32x16 (&acc)[RI][CJ])
+{
+#pragma unroll
+    for (int ks = 0; ks < 32; ks += 16) {
+        const int k = ks + 8 * (lane >> 5);
+        tile_bf16x8 a[RI][3], b[CJ][3];
+#pragma unroll
+        for (int p = 0; p < 3; ++p) {
+#pragma unroll
+            for (int i = 0; i < RI; ++i)
+                a[i][p] = *reinterpret_cast<const tile_bf16x8 *>(As + split_at(m0 + 32 * i + (lane & 31), k) + p * sa);
+#pragma unroll
+            for (int j = 0; j < CJ; ++j)
+                b[j][p] = *reinterpret_cast<const tile_bf16x8 *>(Bs + (n0 + 32 * j + (lane & 31)) * SPLIT_PITCH + k + p * sb);
+        }
+        constexpr int PA[6] = {2, 0, 1, 1, 0, 0}, PB[6] = {0, 2, 1, 0, 1, 0};
+#pragma unroll
+        for (int q = 0; q < 6; ++q)
+#pragma unroll
+            for (int i = 0; i < RI; ++i)
+#pragma unroll
+                for (int j = 0; j < CJ; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i][PA[q]], b[j][PB[q]], acc[i][j], 0, 0, 0);
+    }
+}
+
 // Row of result register v in a 32 x 32 tile (the column is lane % 32).
 __device__ __forceinline__ int tile_row(int lane, int v) { return 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3); }
 

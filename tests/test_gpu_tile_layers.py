@@ -42,3 +42,34 @@ def test_gradient_of_odd_layers(ora, dtype, M, batch, dims):
         np.testing.assert_allclose(gpu.losses().cpu().numpy(), o.loss, rtol=1e-4 if dtype == "bf16" else 1e-5)
     ora.set_threads(1)
     gpu.close()
+
+
+def test_wide_fp32_layers_keep_what_is_not_finite():
+    """Large fp32 layers multiply bfloat16 planes of their operands, which an infinity, or a number that rounds to one, does not
+    survive: such blocks are computed again in fp32.  Activations against float64, block edges included."""
+    import oracle
+    w = workload("cfg2", M=64, batch=128, n_per_worker=130, dims=(36, 513, 10))
+    inp = inputs_of(w)
+    X = inp["X0"].copy()
+    inf, big = np.float32(np.inf), np.float32(3.4e38)          # the latter lies above the largest bfloat16
+    X[1, 3 * 513 + 7] = inf
+    X[5, 35 * 513 + 512] = -inf
+    X[9, 20 * 513 + 64] = np.float32(np.nan)
+    X[13, 0] = big
+    gpu = make_gpu(w, dict(inp, X0=X))
+    gpu.local_step(2)
+    h = gpu.hidden(1).cpu().numpy()
+    idx = oracle.sample_batch(w.M, w.batch, inp["shard_off"], w.seed, 2)
+    for i in range(w.M):
+        a = inp["feats"][inp["shard_off"][i] + idx[i]].astype(np.float64)
+        with np.errstate(invalid="ignore", over="ignore"):
+            W = X[i, :36 * 513].reshape(36, 513).astype(np.float64)
+            z = a @ W + X[i, 36 * 513:37 * 513]
+            # 36 products and the bias, each addition off by at most 2^-24 of the sum of the magnitudes
+            bound = 38 * 2.0**-24 * (np.abs(a) @ np.abs(W) + np.abs(X[i, 36 * 513:37 * 513]))
+            want = np.where(z > 0, z, 0.0).astype(np.float32)
+        assert np.array_equal(np.isinf(h[i]), np.isinf(want)) and not np.isnan(h[i]).any()
+        fine = np.isfinite(want) & np.isfinite(bound)
+        assert np.all(np.abs(h[i][fine].astype(np.float64) - np.where(z > 0, z, 0.0)[fine]) <= bound[fine])
+    assert np.isinf(h).any() and h[13].max() > 1e37
+    gpu.close()
