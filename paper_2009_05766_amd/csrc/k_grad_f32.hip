@@ -16,9 +16,7 @@
 // straight into the instruction's layout as 128-byte row pieces; the result leaves as 128-byte row pieces.  With UPDATE it is
 // turned through LDS and the momentum step and the mix (Eq. (c0), (c1)) are applied to it, x, v and the peer's x asked for ahead of
 // the products: 784 x 512, batch 64, 16 workers 31 us, against 21.6 us and 21.4 us for the separate mix.
-#include "kernels.h"
-#include "layout.h"
-#include "vec.h"
+#include "mix_subset.h"
 
 namespace netmax {
 
@@ -34,6 +32,8 @@ struct LayerF32Args {
     int64_t woff, din, dout;
     int M, B, relu, gather;
     MixArgs mix;                                                   // wgrad_f32_kernel<UPDATE>
+    // and the other columns, by the first `other_blocks` workgroups (a multiple of the XCDs)
+    const int32_t *tiles; int n_tiles; unsigned other_blocks; MixSkip skip;
 };
 
 __device__ __forceinline__ const float *input_row(const LayerF32Args &p, int g, int b)
@@ -151,9 +151,18 @@ __global__ void __launch_bounds__(WG32_THREADS) wgrad_f32_kernel(LayerF32Args p)
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int nct = (int)(p.dout / F32_COLS);
     const unsigned groups = (unsigned)((nct + WG32_WAVES * WG32_TILES - 1) / (WG32_WAVES * WG32_TILES));
+    unsigned bid = blockIdx.x;
+    if constexpr (UPDATE && GATHER) {
+        if (bid < p.other_blocks) {
+            const unsigned tile = bid / (unsigned)p.M;
+            if (tile < (unsigned)p.n_tiles) mix_subset_block<WG32_THREADS>(p.M, p.tiles[tile], (int)(bid - tile * (unsigned)p.M), p.skip, p.G, p.mix);
+            return;
+        }
+        bid -= p.other_blocks;
+    }
     int g;
     unsigned local;
-    if (!decode_group(blockIdx.x, (unsigned)((p.din + 31) / 32) * groups, p.M, g, local)) return;   // a worker's blocks share an XCD (its dZ)
+    if (!decode_group(bid, (unsigned)((p.din + 31) / 32) * groups, p.M, g, local)) return;   // a worker's blocks share an XCD (its dZ)
     const int ct0 = (int)(local % groups) * (WG32_WAVES * WG32_TILES) + wave;
     if (ct0 >= nct) return;
     const int64_t f0 = (int64_t)(local / groups) * 32;
@@ -287,13 +296,17 @@ template <int HB> static void launch_wgrad_half(hipStream_t s, const LayerF32Arg
     else hipLaunchKernelGGL((wgrad_f32_kernel<HB, false, false>), grid, block, 0, s, a);
 }
 
-void launch_wgrad_f32(hipStream_t s, const MlpPlan &p, int l, float *G, const float *dz, const MixArgs *tail)
+void launch_wgrad_f32(hipStream_t s, const MlpPlan &p, int l, float *G, const float *dz, const TailArgs *tail, bool others)
 {
     LayerF32Args a = layer_f32_args(p, l, nullptr, G, dz);
-    if (tail) a.mix = *tail;
+    if (tail) a.mix = tail->mix;
+    if (others) {
+        a.tiles = tail->tiles; a.n_tiles = tail->n_tiles; a.skip = tail->skip;
+        a.other_blocks = grouped_blocks((unsigned)a.n_tiles * (unsigned)p.M);
+    }
     const int nct = (int)(a.dout / F32_COLS);
     const int per_group = WG32_WAVES * WG32_TILES;
-    const dim3 grid(grouped_grid(p.M, (unsigned)((a.din + 31) / 32) * (unsigned)((nct + per_group - 1) / per_group)));
+    const dim3 grid(a.other_blocks + grouped_grid(p.M, (unsigned)((a.din + 31) / 32) * (unsigned)((nct + per_group - 1) / per_group)));
     if (p.B == 32) launch_wgrad_half<16>(s, a, grid, tail != nullptr);
     else launch_wgrad_half<32>(s, a, grid, tail != nullptr);
 }

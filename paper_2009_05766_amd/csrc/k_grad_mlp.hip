@@ -181,21 +181,28 @@ bias_grad_kernel(int M, int B, int64_t dout, const float *__restrict__ dz, int64
 // and, for middling models, most of a launch.  x' goes to the other buffer and nobody else looks at these columns of v, so a
 // layer's update need not wait for the layers below.  Per iteration, with the separate mix and with the update in the kernels:
 // 3072-1024-10, batch 128, 32 workers 873 and 716 us, 64 workers 1725 and 1420 us; 784-512-10, 16 workers, batch 128 95 and 89 us,
-// batch 64 71 and 63 us.  Where it loses: models of a few hundred thousand parameters in all (256-256-10, 8 workers 26.0 and
-// 28.6 us: the mix costs 3 us and what is left of it still is a launch); rows of W that do not start at multiples of 16 bytes
-// (3001-999-10: 1118 and 1519 us); bfloat16 operands, whose products leave little to hide (784-500-300-10, 16 workers 106 and 113
-// us, 3000-1000-10, 128 workers 2354 and 2644 us; the matrix-core layers likewise).
+// batch 64 71 and 63 us.  The first layer's kernel, if it is the last of the iteration, also updates the columns that no kernel
+// has, which saves the mix's launch: batch 64 63 and 58 us.
+// Models of a few hundred thousand parameters in all have the first layer update and take the other columns as those that are
+// left, if that does save the launch: 256-256-10, 8 workers, batch 32 27.0 us with the mix and 23.0 us, 784-512-10, 4 workers
+// 45.0 and 39.6 us; every layer for itself lengthens the chain (300-60-60-60-10, 8 workers 64.7 and 66.5 us).
+// Where it loses: rows of W that do not start at multiples of 16 bytes (3001-999-10: 1118 and 1519 us); bfloat16 operands, whose
+// products leave little to hide (784-500-300-10, 16 workers 106 and 113 us, 3000-1000-10, 128 workers 2354 and 2644 us; the
+// matrix-core layers likewise).
 constexpr int64_t UPDATE_MIN_FLOATS = 1 << 21;       // M x ld
+static bool first_layer_last(const MlpPlan &p) { return p.n_layers == 1 || (p.n_layers == 2 && head_ok(p)) || p.B <= TILE_DGRAD_BATCH; }
+
 int64_t update_end(const MlpPlan &p, int l)
 {
     const bool head = head_ok(p);
     if (p.n_layers == 1 && head) return p.ld;                        // the last-layer kernel updates everything
-    if (p.bf16 || (l == p.n_layers - 1 && head) || p.woff[l] % 4 != 0 || p.M * p.ld < UPDATE_MIN_FLOATS) return 0;
+    if (p.bf16 || (l == p.n_layers - 1 && head) || p.woff[l] % 4 != 0) return 0;
+    if (p.M * p.ld < UPDATE_MIN_FLOATS && (l > 0 || !first_layer_last(p))) return 0;
     if (!wgrad_f32_ok(p, l) && !tile_wgrad_update_ok(p, l)) return 0;
     return p.woff[l] + p.dims[l] * p.dims[l + 1];
 }
 
-void launch_mlp_grad(hipStream_t s, const MlpPlan &p, const float *X, float *G, const MixArgs *fuse, const MixArgs *tail)
+bool launch_mlp_grad(hipStream_t s, const MlpPlan &p, const float *X, float *G, const MixArgs *fuse, const TailArgs *tail)
 {
     const int L = p.n_layers;
     const bool bf = p.bf16 != 0;
@@ -243,11 +250,11 @@ void launch_mlp_grad(hipStream_t s, const MlpPlan &p, const float *X, float *G, 
         // few outputs: the tiled kernel would pad them to a 64-column tile on one workgroup per worker
         launch_fwd_narrow(s, f, f.in.kind, p.M);
     }
-    bool bias_done[8] = {};
+    bool bias_done[8] = {}, all_updated = L == 1 && head && tail_of(0);
     int cur = 0, l_top = L - 1;
     if (head) {
         // logits, loss, the last layer's gradient and the error of the last hidden layer (with its column sums)
-        launch_head(s, p, X, G, L == 1 ? tail_of(0) : nullptr);
+        launch_head(s, p, X, G, L == 1 && tail_of(0) ? &tail->mix : nullptr);
         bias_done[L - 1] = true;
         if (L > 1) bias_done[L - 2] = true;
         l_top = L - 2;
@@ -262,15 +269,17 @@ void launch_mlp_grad(hipStream_t s, const MlpPlan &p, const float *X, float *G, 
     // backward
     for (int l = l_top; l >= 0; --l) {
         const int64_t din = p.dims[l], dout = p.dims[l + 1];
+        const bool others = l == 0 && bias_done[0] && tail_of(0) != nullptr;       // the last launch: it can update what is left
+        all_updated |= others;
         if (fast[l]) {
             if (fuse) launch_wgrad_mix_mfma(s, p, l, cur, *fuse);
             else launch_wgrad_mfma(s, p, l, G, cur);
         } else if (l == L - 1 && small_last) {
             launch_wgrad_small(s, p, G, cur);
         } else if (wgrad_f32_ok(p, l)) {
-            launch_wgrad_f32(s, p, l, G, p.dz[cur], tail_of(l));
+            launch_wgrad_f32(s, p, l, G, p.dz[cur], tail_of(l), others);
         } else {
-            launch_tile_wgrad(s, p, l, G, cur, tail_of(l));
+            launch_tile_wgrad(s, p, l, G, cur, tail_of(l), others);
         }
         if (!bias_done[l]) {
             hipLaunchKernelGGL(bias_grad_kernel, dim3((unsigned)((dout + 63) / 64), (unsigned)p.M), dim3(256), 0, s, p.M, p.B,
@@ -289,6 +298,7 @@ void launch_mlp_grad(hipStream_t s, const MlpPlan &p, const float *X, float *G, 
             cur ^= 1;
         }
     }
+    return all_updated;
 }
 
 }  // namespace netmax

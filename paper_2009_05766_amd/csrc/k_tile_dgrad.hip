@@ -136,6 +136,7 @@ static bool launch_shape(hipStream_t s, const TileDgrad &a)
 // Few workgroups are bound by the chain of steps, not by what a step costs: longer steps, narrower blocks.
 template <bool BF, bool V> static bool launch_rows(hipStream_t s, const TileDgrad &a)
 {
+    static_assert(TILE_DGRAD_BATCH == 128, "the rows of the largest block below");
     constexpr int LONG = BF ? 128 : 64;
     const int64_t wide = (int64_t)a.M * ((a.din + 63) / 64) * ((a.B + 127) / 128);
     if (a.B <= 32) return launch_shape<BF, V, 32, 64, 64, 1, 2>(s, a);

@@ -13,6 +13,7 @@
 // every block's operands again); the blocks of a strip side by side and not one after the other in a workgroup (755 against 880
 // us: the pieces of a layout tile should leave together); x and v asked for behind the last operands, the peer's x behind the
 // products (716 us; all ahead of the operands of the second step 817 us, all behind the last operands 722 us).
+#include "mix_subset.h"
 #include "tile.h"
 
 namespace netmax {
@@ -22,6 +23,8 @@ struct TileWgrad {
     const void *act;                                                  // else the activation below, [M][B][din]
     const float *dz; int M, B, din, dout; int64_t woff; float *G;
     MixArgs mix;                                                      // UPDATE
+    // and the other columns, by the first `other_blocks` workgroups (a multiple of the XCDs)
+    const int32_t *tiles; int n_tiles; unsigned other_blocks; MixSkip skip;
 };
 
 constexpr int TW_BM = 64, TW_BN = 128, TW_BK = 64, TW_THREADS = 512;
@@ -43,11 +46,20 @@ __global__ void __launch_bounds__(TW_THREADS, 4) tile_wgrad_kernel(TileWgrad p)
     float (*T)[TP] = reinterpret_cast<float (*)[TP]>(smem);
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6, wm = wave >> 2, wn = wave & 3;
     const int nblk = (p.dout + BN - 1) / BN, mblk = (p.din + BM - 1) / BM;
+    unsigned bid = blockIdx.x;
+    if constexpr (UPDATE) {
+        if (bid < p.other_blocks) {
+            const unsigned tile = bid / (unsigned)p.M;
+            if (tile < (unsigned)p.n_tiles) mix_subset_block<TW_THREADS>(p.M, p.tiles[tile], (int)(bid - tile * (unsigned)p.M), p.skip, p.G, p.mix);
+            return;
+        }
+        bid -= p.other_blocks;
+    }
     int g;
     unsigned local;
     // worker by worker, the blocks of a strip side by side: the operands are read once, into one XCD's L2, and the pieces of a
     // layout tile leave at about the same time
-    if (!decode_group(blockIdx.x, (unsigned)(nblk * mblk), p.M, g, local)) return;
+    if (!decode_group(bid, (unsigned)(nblk * mblk), p.M, g, local)) return;
     const int f0 = (int)(local / (unsigned)nblk) * BM, n0 = (int)(local % (unsigned)nblk) * BN;
     const int K = p.B;
 
@@ -179,7 +191,7 @@ __global__ void __launch_bounds__(TW_THREADS, 4) tile_wgrad_kernel(TileWgrad p)
 
 template <bool BF, bool VA, bool VZ> static void launch_cols(hipStream_t s, const TileWgrad &a, bool update)
 {
-    const dim3 grid(grouped_grid(a.M, (unsigned)((a.dout + TW_BN - 1) / TW_BN) * (unsigned)((a.din + TW_BM - 1) / TW_BM))), block(TW_THREADS);
+    const dim3 grid(a.other_blocks + grouped_grid(a.M, (unsigned)((a.dout + TW_BN - 1) / TW_BN) * (unsigned)((a.din + TW_BM - 1) / TW_BM))), block(TW_THREADS);
     if constexpr (VZ && !BF)
         if (update) {
             hipLaunchKernelGGL((tile_wgrad_kernel<BF, VA, VZ, true>), grid, block, 0, s, a);
@@ -193,11 +205,15 @@ static bool rows_in_pieces(const MlpPlan &p, int l) { return p.dims[l + 1] % 4 =
 
 bool tile_wgrad_update_ok(const MlpPlan &p, int l) { return !p.bf16 && rows_in_pieces(p, l); }
 
-void launch_tile_wgrad(hipStream_t s, const MlpPlan &p, int l, float *G, int cur, const MixArgs *tail)
+void launch_tile_wgrad(hipStream_t s, const MlpPlan &p, int l, float *G, int cur, const TailArgs *tail, bool others)
 {
     const bool bf = p.bf16 != 0, u = tail != nullptr;
-    TileWgrad a;
-    a.mix = u ? *tail : MixArgs{};
+    TileWgrad a{};
+    if (u) a.mix = tail->mix;
+    if (others) {
+        a.tiles = tail->tiles; a.n_tiles = tail->n_tiles; a.skip = tail->skip;
+        a.other_blocks = grouped_blocks((unsigned)a.n_tiles * (unsigned)p.M);
+    }
     a.feats = l == 0 ? p.feats : nullptr; a.row0 = p.row0; a.idx = p.idx;
     a.act = l == 0 ? nullptr : (bf ? (const void *)p.hb[l] : (const void *)p.act[l]);
     a.dz = p.dz[cur]; a.M = p.M; a.B = p.B; a.din = (int)p.dims[l]; a.dout = (int)p.dims[l + 1]; a.woff = p.woff[l]; a.G = G;

@@ -67,13 +67,16 @@ void launch_mix_synth(hipStream_t s, int M, int64_t D, int64_t ld, const float *
                       const int32_t *peer, const float *w, float alpha, float mu, float wd, float sigma, uint64_t seed,
                       const IterRef &iter);
 
+// What the second-step update needs besides the gradient: passed to the gradient code when the weight-gradient
+// kernels of the matrix-core layers apply the update themselves instead of writing the gradient.
+struct MixArgs {
+    const float *Xcur; float *V, *Xnext; const int32_t *peer; const float *w; float alpha, mu, wd;
+};
 // The same update for a list of column tiles only, leaving out up to MIX_MAX_SKIP column ranges (multiples of four
-// columns) that another kernel has already updated.  tiles: device [n_tiles_listed].
+// columns) that another kernel updates.  tiles: device [n_listed].
 constexpr int MIX_MAX_SKIP = 8;
 struct MixSkip { int n; int64_t lo[MIX_MAX_SKIP], hi[MIX_MAX_SKIP]; };
-void launch_mix_subset(hipStream_t s, int M, const int32_t *tiles, int n_listed, const MixSkip &skip, const float *Xcur,
-                       const float *G, float *V, float *Xnext, const int32_t *peer, const float *w, float alpha, float mu,
-                       float wd);
+void launch_mix_subset(hipStream_t s, int M, const int32_t *tiles, int n_listed, const MixSkip &skip, const float *G, const MixArgs &mix);
 
 // Consensus distance: per-block partial sums (double), then a fixed-order final sum into out_dev[0].
 // partial must hold consensus_partials(ld) doubles: one per CONSENSUS_COLS columns.
@@ -127,6 +130,9 @@ inline unsigned grouped_grid(int M, unsigned blocks_per_worker)
     return (unsigned)((M + MF_XCD - 1) / MF_XCD * MF_XCD) * blocks_per_worker;
 }
 
+// A number of workgroups rounded up to whole rounds over the XCDs: what follows them in a grid keeps its place in the deal.
+inline unsigned grouped_blocks(unsigned n) { return (n + MF_XCD - 1) / MF_XCD * MF_XCD; }
+
 // Per-worker MLP / softmax-regression gradient (grouped GEMMs).
 struct MlpPlan {
     int M, n_layers, B;
@@ -147,16 +153,15 @@ struct MlpPlan {
     uint16_t *dzb[2];       // [M][B][max width]
     uint16_t *dzt[2];       // [M][max width][B]
 };
-// What the second-step update needs besides the gradient: passed to the gradient code when the weight-gradient
-// kernels of the matrix-core layers apply the update themselves instead of writing the gradient.
-struct MixArgs {
-    const float *Xcur; float *V, *Xnext; const int32_t *peer; const float *w; float alpha, mu, wd;
-};
+// The second-step update inside netmax_run, for the columns that no weight gradient has updated: the columns of the listed tiles
+// (device [n_tiles]) outside `skip`.
+struct TailArgs { MixArgs mix; const int32_t *tiles; int n_tiles; MixSkip skip; };
 // fuse != nullptr: layers accepted by mfma_layer_ok() do not write their weight gradient to G; they write
 // x' and v' of their weight columns (Eq. (c0)/(c1)) straight from the product.
 // tail != nullptr (not together with fuse): the weight gradients of the layers whose update_end() is not 0 write G and apply the
-// update to the columns woff .. update_end() - 1 (multiples of four) while they hold them; the caller updates the others.
-void launch_mlp_grad(hipStream_t s, const MlpPlan &p, const float *X, float *G, const MixArgs *fuse = nullptr, const MixArgs *tail = nullptr);
+// update to the columns woff .. update_end() - 1 (multiples of four) while they hold them.  The others are updated by the first
+// layer's weight gradient where it can (it is the last launch then), else by the caller: false is returned in that case.
+bool launch_mlp_grad(hipStream_t s, const MlpPlan &p, const float *X, float *G, const MixArgs *fuse = nullptr, const TailArgs *tail = nullptr);
 int64_t update_end(const MlpPlan &p, int l);
 
 // Matrix-core kernels (k_grad_mfma.hip) for layers that mfma_layer_ok() accepts.
@@ -179,16 +184,17 @@ bool fwd_f32_ok(const MlpPlan &p, int l);
 bool wgrad_f32_ok(const MlpPlan &p, int l);
 hipError_t prepare_f32_layers();
 void launch_fwd_f32(hipStream_t s, const MlpPlan &p, int l, const float *X);
-// tail: see launch_mlp_grad()
-void launch_wgrad_f32(hipStream_t s, const MlpPlan &p, int l, float *G, const float *dz, const MixArgs *tail);
+// tail: see launch_mlp_grad(); others: this launch also updates the columns of tail->tiles (first layer only)
+void launch_wgrad_f32(hipStream_t s, const MlpPlan &p, int l, float *G, const float *dz, const TailArgs *tail, bool others);
 
 // Tiled kernels for layers of any shape, fp32 or bfloat16 operands.  need_t: the transposed bfloat16 activation is wanted (by a
 // matrix-core kernel above); below_fast: so are both bfloat16 copies of the error.  launch_tile_dgrad: true if it has also
 // written the bias gradient of the layer below (its workgroups held the whole batch).
 void launch_tile_fwd(hipStream_t s, const MlpPlan &p, int l, const float *X, bool need_t);
+constexpr int TILE_DGRAD_BATCH = 128;                   // up to here they do
 bool launch_tile_dgrad(hipStream_t s, const MlpPlan &p, int l, const float *X, float *G, int cur, bool below_fast);
 bool tile_wgrad_update_ok(const MlpPlan &p, int l);      // its update: fp32 operands, aligned rows
-void launch_tile_wgrad(hipStream_t s, const MlpPlan &p, int l, float *G, int cur, const MixArgs *tail);
+void launch_tile_wgrad(hipStream_t s, const MlpPlan &p, int l, float *G, int cur, const TailArgs *tail, bool others);
 
 // Last layer with at most 32 classes, fp32 or bfloat16 operands (k_grad_head.hip): from its input to the error of the layer
 // below in two kernels: logits, loss, dW, db, dH and the column sums of dH.

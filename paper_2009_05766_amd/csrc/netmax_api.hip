@@ -601,10 +601,11 @@ static int enqueue_small(netmax_ctx *ctx, const IterRef &iter, int n_iters, bool
     return NETMAX_OK;
 }
 
-// run_peers != nullptr (netmax_run): weight-gradient kernels apply the update where the context has it so, enqueue_run_mix then
-// covers the remaining columns only.
+// run_peers != nullptr (netmax_run): weight-gradient kernels apply the update where the context has it so; *updated: to all
+// columns, else enqueue_run_mix covers the remaining ones.
 // drawn: the batch rows of this iteration if they have been drawn already.
-static int enqueue_local_step(netmax_ctx *ctx, const IterRef &iter, const int32_t *run_peers = nullptr, const int32_t *drawn = nullptr)
+static int enqueue_local_step(netmax_ctx *ctx, const IterRef &iter, const int32_t *run_peers = nullptr, const int32_t *drawn = nullptr,
+                              bool *updated = nullptr)
 {
     const netmax_config &c = ctx->cfg;
     if (c.model == NETMAX_FLAT) {
@@ -616,9 +617,10 @@ static int enqueue_local_step(netmax_ctx *ctx, const IterRef &iter, const int32_
     if (!drawn) launch_sample_batch(ctx->stream, c.M, c.batch, ctx->d_nrows, c.seed, iter, ctx->d_idx);
     MlpPlan p = make_plan(ctx);
     if (drawn) p.idx = drawn;
-    const MixArgs mx = mix_args(ctx, run_peers);
-    launch_mlp_grad(ctx->stream, p, ctx->x_cur, ctx->g, run_peers && ctx->fuse ? &mx : nullptr,
-                    run_peers && ctx->tail && !ctx->fuse ? &mx : nullptr);
+    const TailArgs tail{mix_args(ctx, run_peers), ctx->d_tail_tiles, ctx->n_tail_tiles, ctx->tail_skip};
+    const bool done = launch_mlp_grad(ctx->stream, p, ctx->x_cur, ctx->g, run_peers && ctx->fuse ? &tail.mix : nullptr,
+                                      run_peers && ctx->tail && !ctx->fuse ? &tail : nullptr);
+    if (updated) *updated = done;
     return check_launch(ctx, "mlp_grad");
 }
 
@@ -648,11 +650,9 @@ static int enqueue_run_mix(netmax_ctx *ctx, const int32_t *peers_dev, const Iter
         launch_mix_synth(ctx->stream, c.M, c.D, c.ld, ctx->x_cur, ctx->g, ctx->v, ctx->x_next, peers_dev, ctx->d_w, c.lr,
                          c.momentum, c.weight_decay, c.grad_sigma, c.seed, iter);
     else if (ctx->fuse)
-        launch_mix_subset(ctx->stream, c.M, ctx->d_fuse_tiles, ctx->n_fuse_tiles, ctx->fuse_skip, ctx->x_cur, ctx->g, ctx->v,
-                          ctx->x_next, peers_dev, ctx->d_w, c.lr, c.momentum, c.weight_decay);
+        launch_mix_subset(ctx->stream, c.M, ctx->d_fuse_tiles, ctx->n_fuse_tiles, ctx->fuse_skip, ctx->g, mix_args(ctx, peers_dev));
     else if (ctx->tail)
-        launch_mix_subset(ctx->stream, c.M, ctx->d_tail_tiles, ctx->n_tail_tiles, ctx->tail_skip, ctx->x_cur, ctx->g, ctx->v,
-                          ctx->x_next, peers_dev, ctx->d_w, c.lr, c.momentum, c.weight_decay);
+        launch_mix_subset(ctx->stream, c.M, ctx->d_tail_tiles, ctx->n_tail_tiles, ctx->tail_skip, ctx->g, mix_args(ctx, peers_dev));
     else
         return enqueue_mix(ctx, peers_dev);
     return check_launch(ctx, "mix");
@@ -661,8 +661,9 @@ static int enqueue_run_mix(netmax_ctx *ctx, const int32_t *peers_dev, const Iter
 // One iteration of netmax_run behind its draws (`drawn`: its batch rows).
 static int enqueue_run_iteration(netmax_ctx *ctx, const IterRef &iter, const int32_t *peers, const int32_t *drawn)
 {
-    const int rc = enqueue_local_step(ctx, iter, peers, drawn);
-    return rc != NETMAX_OK ? rc : enqueue_run_mix(ctx, peers, iter);
+    bool updated = false;
+    const int rc = enqueue_local_step(ctx, iter, peers, drawn, &updated);
+    return rc != NETMAX_OK || updated ? rc : enqueue_run_mix(ctx, peers, iter);
 }
 
 static void flip(netmax_ctx *ctx)

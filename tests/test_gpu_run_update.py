@@ -18,6 +18,10 @@ pytestmark = pytest.mark.gpu
     ("cfg5", 4, 100, (100, 60, 10)), ("cfg5", 3, 90, (61, 131, 10)), ("cfg5", 3, 64, (100, 128, 128, 10)),
     ("cfg5", 3, 64, (128, 128, 10)),                                                            # matrix-core layers: the separate mix
     ("cfg2", 3, 300, (40, 20)), ("cfg2", 3, 16, (50, 40)),                                      # one layer outside the last-layer kernels
+    # from two million floats on every fp32 weight gradient updates its columns, the first layer's the remaining ones too
+    ("cfg2", 16, 64, (784, 192, 10)), ("cfg2", 37, 32, (33, 1024, 32, 7)),                      # batches of 32 and 64
+    ("cfg2", 21, 100, (784, 132, 40)), ("cfg2", 9, 128, (100, 804, 252, 10)),                   # tiled, rows aligned; 40 classes
+    ("cfg2", 70, 40, (784, 40)), ("cfg2", 41, 50, (804, 68, 9, 33, 12)),                        # one layer; layers that do not update
 ])
 @pytest.mark.parametrize("graph", [False, True])
 def test_run_is_the_separate_calls(name, M, batch, dims, graph):
