@@ -4,7 +4,7 @@
 // streams out (weight gradient), and with few workers by how much of that is in flight.  Both kernels hand the
 // operands to v_mfma_f32_32x32x2_f32 (exact fp32 products, fp32 accumulation) in the layout the loads deliver them in.
 //
-// Forward, Z = A W + b: a workgroup takes 32 columns of one worker's W and all batch rows; its eight waves split
+// Forward, Z = A W + b: a workgroup takes 32 columns of one worker's W and all batch rows (half of 64, if few); its eight waves split
 // the contraction (wave w takes indices 64 s + 8 w .. + 7) and add their partial tiles through LDS in the order of the
 // waves.  W is read exactly once, as 128-bit loads of whole 128-byte row pieces, and turned into the matrix
 // instruction's layout through a wave-private LDS buffer (no workgroup barrier in the loop); A is read straight into
@@ -41,8 +41,9 @@ __device__ __forceinline__ const float *input_row(const LayerF32Args &p, int g, 
     return p.gather ? p.feats + (p.row0[g] + p.idx[(size_t)g * p.B + b]) * p.din : p.act + ((size_t)g * p.B + b) * p.din;
 }
 
-// RT: 32-row tiles of the batch (1 or 2).  Grid: grouped_grid(workers, dout / 32).
-template <int RT>
+// RT: 32-row tiles in a workgroup (1 or 2), ROWS: workgroups that share the batch (batch = 32 RT ROWS).  Grid: grouped_grid(workers,
+// dout / 32 * ROWS).
+template <int RT, int ROWS>
 __global__ void __launch_bounds__(F32_THREADS) fwd_f32_kernel(LayerF32Args p)
 {
     extern __shared__ __attribute__((aligned(16))) float f32_smem[];
@@ -50,9 +51,10 @@ __global__ void __launch_bounds__(F32_THREADS) fwd_f32_kernel(LayerF32Args p)
     const int t = threadIdx.x, lane = t & 63, row = lane & 31, half = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
     int g;
-    unsigned cblk;
-    if (!decode_group(blockIdx.x, (unsigned)(p.dout / F32_COLS), p.M, g, cblk)) return;      // a worker's blocks share an XCD (its A)
-    const int64_t col0 = (int64_t)cblk * F32_COLS;
+    unsigned local;
+    if (!decode_group(blockIdx.x, (unsigned)(p.dout / F32_COLS) * ROWS, p.M, g, local)) return;      // a worker's blocks share an XCD (its A)
+    const int64_t col0 = (int64_t)(local / ROWS) * F32_COLS;
+    const int row0 = (int)(local % ROWS) * (32 * RT);
     float *stage = f32_smem + wave * (2 * F32_KS * F32_COLS);
     const float bias = p.X[tiled_offset(p.M, g, p.woff + p.din * p.dout + col0 + (t & 31))];     // for the end; requested first
     const int kr = lane >> 3, c4 = (lane & 7) * 4;               // this lane's piece of a staged W block
@@ -73,7 +75,7 @@ __global__ void __launch_bounds__(F32_THREADS) fwd_f32_kernel(LayerF32Args p)
     }
     const float *arow[RT];
 #pragma unroll
-    for (int i = 0; i < RT; ++i) arow[i] = input_row(p, g, 32 * i + row) + 4 * half;
+    for (int i = 0; i < RT; ++i) arow[i] = input_row(p, g, row0 + 32 * i + row) + 4 * half;
     auto request_a = [&](int d, int s) {
 #pragma unroll
         for (int i = 0; i < RT; ++i) fa[d][i] = *reinterpret_cast<const f32x4 *>(arow[i] + (int64_t)s * F32_KS);
@@ -130,7 +132,7 @@ __global__ void __launch_bounds__(F32_THREADS) fwd_f32_kernel(LayerF32Args p)
         for (int w = 1; w < F32_WAVES; ++w) z += part[(w * 32 * RT + r) * PP + c];
         z += bias;
         if (p.relu) z = z > 0.0f ? z : 0.0f;
-        p.out[((size_t)g * p.B + r) * p.dout + col0 + c] = z;
+        p.out[((size_t)g * p.B + row0 + r) * p.dout + col0 + c] = z;
     }
 }
 
@@ -274,17 +276,23 @@ bool wgrad_f32_ok(const MlpPlan &p, int l) { return f32_layer_common(p, l); }
 
 hipError_t prepare_f32_layers()
 {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(fwd_f32_kernel<1>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)fwd_f32_lds(1));
-    if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void *>(fwd_f32_kernel<2>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)fwd_f32_lds(2));
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(fwd_f32_kernel<1, 1>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)fwd_f32_lds(1));
+    if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void *>(fwd_f32_kernel<1, 2>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)fwd_f32_lds(1));
+    if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void *>(fwd_f32_kernel<2, 1>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)fwd_f32_lds(2));
     return e;
 }
 
 void launch_fwd_f32(hipStream_t s, const MlpPlan &p, int l, const float *X)
 {
     const LayerF32Args a = layer_f32_args(p, l, X, nullptr, nullptr);
-    const dim3 grid(grouped_grid(p.M, (unsigned)(a.dout / F32_COLS))), block(F32_THREADS);
-    if (p.B == 32) hipLaunchKernelGGL(fwd_f32_kernel<1>, grid, block, fwd_f32_lds(1), s, a);
-    else hipLaunchKernelGGL(fwd_f32_kernel<2>, grid, block, fwd_f32_lds(2), s, a);
+    const unsigned cols = (unsigned)(a.dout / F32_COLS);
+    const dim3 block(F32_THREADS);
+    // A batch of 64: while two workgroups of 32 rows for each group of columns find a compute unit each, they halve the products that
+    // a wave makes one after the other.  Per iteration of 784-512-10, one and two: 2 workers 31.7 and 28.7 us, 8 workers (256
+    // workgroups) 40.5 and 37.1 us; 3072-1024-10, 2 workers 76 and 61 us; beyond, 8 workers (512) 164 and 174 us.
+    if (p.B == 32) hipLaunchKernelGGL((fwd_f32_kernel<1, 1>), dim3(grouped_grid(p.M, cols)), block, fwd_f32_lds(1), s, a);
+    else if (p.M * (int64_t)cols * 2 <= MF_XCD * XCD_CUS) hipLaunchKernelGGL((fwd_f32_kernel<1, 2>), dim3(grouped_grid(p.M, 2 * cols)), block, fwd_f32_lds(1), s, a);
+    else hipLaunchKernelGGL((fwd_f32_kernel<2, 1>), dim3(grouped_grid(p.M, cols)), block, fwd_f32_lds(2), s, a);
 }
 
 template <int HB> static void launch_wgrad_half(hipStream_t s, const LayerF32Args &a, dim3 grid, bool update)

@@ -25,6 +25,8 @@ TOL = {"f32": 1e-5, "bf16": 1e-3}
     ("bf16", 2, 100, (101, 52, 38, 10)),
     # enough blocks for the short-step form (512 blocks of 128 x 64)
     ("f32", 64, 128, (36, 513, 10)), ("bf16", 64, 128, (36, 513, 10)),
+    # a batch of 64 in two workgroups for each group of 32 columns: few, the most (256), and one worker more
+    ("f32", 2, 64, (8, 32, 10)), ("f32", 8, 64, (72, 512, 32, 10)), ("f32", 9, 64, (72, 512, 32, 10)),
     # general layers under and over matrix-core layers (bfloat16 copies in both orientations are wanted)
     ("bf16", 3, 64, (100, 128, 256, 10)), ("bf16", 3, 32, (128, 128, 100, 128, 10)), ("bf16", 2, 96, (60, 128, 40)),
 ])
