@@ -186,6 +186,7 @@ __global__ void __launch_bounds__(SF_THREADS, 2) split_fwd_kernel(TileFwd p)
     const int b_c = n0 + b_n < p.dout ? n0 + b_n : (VW ? p.dout - 4 : p.dout - 1);     // columns past the end repeat the last one(s)
     const int b_have = p.dout - b_c;
     Piece<false> ra[NA], rb[2];
+    bool lost = false;                                                // an operand of this thread that its planes do not hold
     auto fetch = [&](int k0) {
         int k = k0 + a_k;
         k = k < K ? k : (VA ? K - 4 : K - 1);
@@ -206,10 +207,11 @@ __global__ void __launch_bounds__(SF_THREADS, 2) split_fwd_kernel(TileFwd p)
         const int left = decltype(whole)::value ? BK : K - k0;
 #pragma unroll
         for (int u = 0; u < NA; ++u)
-            put_split(buf + split_at((t + u * NT) / K4, a_k), SA, decltype(whole)::value ? ra[u].v : first_of(ra[u].v, left - a_k));
+            put_split(buf + split_at((t + u * NT) / K4, a_k), SA, decltype(whole)::value ? ra[u].v : first_of(ra[u].v, left - a_k), lost);
 #pragma unroll
         for (int e = 0; e < 4; ++e)
-            put_split(buf + 3 * SA + (b_n + e) * SPLIT_PITCH + b_k, SB, left > b_k ? rb[0].v[e] : 0.0f, left > b_k + 1 ? rb[1].v[e] : 0.0f);
+            put_split(buf + 3 * SA + (b_n + e) * SPLIT_PITCH + b_k, SB, left > b_k ? rb[0].v[e] : 0.0f, left > b_k + 1 ? rb[1].v[e] : 0.0f,
+                      lost);
     };
     tile_f32x16 acc[RI][CJ];
     tile_clear(acc);
@@ -228,14 +230,20 @@ __global__ void __launch_bounds__(SF_THREADS, 2) split_fwd_kernel(TileFwd p)
     };
     while (k0 + 2 * BK <= K) step(std::true_type{});                  // the step behind is whole
     while (k0 < K) step(std::false_type{});
+    // again, in fp32: an operand that its planes do not hold, a sum that is not finite, or one so small that the products of the
+    // lower planes come near the smallest number there is
+    constexpr float FEW_BITS = 0x1p-100f;
     float watch = 0.0f;                                               // 0 or NaN
 #pragma unroll
     for (int i = 0; i < RI; ++i)
 #pragma unroll
         for (int j = 0; j < CJ; ++j)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) watch = fmaf(acc[i][j][v], 0.0f, watch);
-    if (__syncthreads_or(!(watch == 0.0f)))                           // a sum that is not finite: again, in fp32
+            for (int v = 0; v < 16; ++v) {
+                watch = fmaf(acc[i][j][v], 0.0f, watch);
+                lost |= fabsf(acc[i][j][v]) < FEW_BITS && acc[i][j][v] != 0.0f;
+            }
+    if (__syncthreads_or(lost || !(watch == 0.0f)))
         tile_fwd_product<false, VA, VW, BM, BN, 64, WM, WN>(p, g, m0, n0, smem, acc);
     tile_fwd_store<false, BM, BN, WM, WN>(p, g, m0, n0, wm, wn, lane, acc);
 }

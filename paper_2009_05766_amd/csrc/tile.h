@@ -167,33 +167,39 @@ __device__ __forceinline__ void momentum_mix1(float x, float v, float g, float x
 }
 
 // ---- fp32 operands as three bfloat16 planes -----------------------------------------------------------------------------
-// x = hi + mid + lo, each the rounding of what the ones before leave (8 + 8 + 8 bits: exact for finite x below 2^127).  Of the nine
-// products of two such sums the six above 2^-25 of the whole are taken, smallest first, each group of sixteen contraction
-// indices with one rounding per product: 6 x 32 cycles where v_mfma_f32_32x32x2_f32 takes 8 x 64.  A value that is not finite
-// does not survive the split (inf - inf) and makes every sum it enters a NaN: the caller looks at its sums and does a product
-// with one that is not finite again in fp32.
-__device__ __forceinline__ void split2(float x0, float x1, uint32_t (&plane)[3])
+// x = hi + mid + lo, each the rounding of what the ones before leave (8 + 8 + 8 bits).  Exact while x rounds to a finite bfloat16
+// and the last part is no subnormal number (true from |x| = 2^-102 on; below, bfloat16 may not have the bits that float has).  Of the
+// nine products of two such sums the six largest are taken (mid lo, lo mid and lo lo are left out: at most 2^-24 of the product
+// in all), smallest first, each group of sixteen contraction indices with one rounding per product: 6 x 32 cycles where
+// v_mfma_f32_32x32x2_f32 takes 8 x 64.  Where the split is not exact the caller does the product again in fp32: `lost` tells it
+// of a last part that is subnormal; a value that is not finite does not survive the split (inf - inf) and makes every sum it
+// enters a NaN.
+constexpr unsigned FP_SUBNORMAL_CLASS = 0x90;                         // of either sign (v_cmp_class_f32)
+__device__ __forceinline__ void split2(float x0, float x1, uint32_t (&plane)[3], bool &lost)
 {
     plane[0] = pack_bf16x2(x0, x1);
     const float r0 = x0 - __uint_as_float(plane[0] << 16), r1 = x1 - __uint_as_float(plane[0] & 0xFFFF0000u);
     plane[1] = pack_bf16x2(r0, r1);
-    plane[2] = pack_bf16x2(r0 - __uint_as_float(plane[1] << 16), r1 - __uint_as_float(plane[1] & 0xFFFF0000u));
+    const float l0 = r0 - __uint_as_float(plane[1] << 16), l1 = r1 - __uint_as_float(plane[1] & 0xFFFF0000u);
+    plane[2] = pack_bf16x2(l0, l1);
+    lost |= __builtin_isfpclass(l0, FP_SUBNORMAL_CLASS);
+    lost |= __builtin_isfpclass(l1, FP_SUBNORMAL_CLASS);
 }
 
 // Four neighbouring k of an operand row into the three planes (plane p of the row starts at dst + p * stride).
-__device__ __forceinline__ void put_split(uint16_t *dst, int stride, f32x4 v)
+__device__ __forceinline__ void put_split(uint16_t *dst, int stride, f32x4 v, bool &lost)
 {
     uint32_t a[3], b[3];
-    split2(v[0], v[1], a);
-    split2(v[2], v[3], b);
+    split2(v[0], v[1], a, lost);
+    split2(v[2], v[3], b, lost);
 #pragma unroll
     for (int p = 0; p < 3; ++p) *reinterpret_cast<tile_u32x2 *>(dst + p * stride) = tile_u32x2{a[p], b[p]};
 }
 // Two neighbouring k.
-__device__ __forceinline__ void put_split(uint16_t *dst, int stride, float x0, float x1)
+__device__ __forceinline__ void put_split(uint16_t *dst, int stride, float x0, float x1, bool &lost)
 {
     uint32_t a[3];
-    split2(x0, x1, a);
+    split2(x0, x1, a, lost);
 #pragma unroll
     for (int p = 0; p < 3; ++p) *reinterpret_cast<uint32_t *>(dst + p * stride) = a[p];
 }

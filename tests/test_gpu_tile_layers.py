@@ -75,3 +75,37 @@ def test_wide_fp32_layers_keep_what_is_not_finite():
         assert np.all(np.abs(h[i][fine].astype(np.float64) - np.where(z > 0, z, 0.0)[fine]) <= bound[fine])
     assert np.isinf(h).any() and h[13].max() > 1e37
     gpu.close()
+
+
+@pytest.mark.parametrize("batch,dims", [
+    # one step of 32 and its remainder, whole steps, steps and a remainder; features a multiple of four and not, outputs likewise
+    (128, (36, 516, 10)), (128, (64, 513, 10)), (128, (96, 516, 10)), (128, (100, 516, 10)), (100, (101, 513, 10)), (65, (163, 516, 10)),
+])
+def test_wide_fp32_layers_against_64_bits(batch, dims):
+    """Large fp32 layers multiply bfloat16 planes of their operands.  Every activation against float64, of ordinary operands (a lost
+    product of planes is 2^-16 of a term, the bound some 2^-22 of the sum) and of operands near and below the smallest normal
+    number, which planes do not hold: such blocks are computed again in fp32."""
+    import oracle
+    w = workload("cfg2", M=64, batch=batch, n_per_worker=130, dims=dims)
+    inp = inputs_of(w)
+    K, N = dims[0], dims[1]
+    X, feats, off = inp["X0"].copy(), inp["feats"].copy(), inp["shard_off"]
+    X[3, :K * N] *= np.float32(1e-37)                            # weights of which planes keep a part
+    feats[off[5]:off[6]] *= np.float32(3e-37)                    # data rows likewise
+    X[8, :K * N] *= np.float32(1e-20)                            # operands that planes hold, products that are subnormal numbers
+    feats[off[8]:off[9]] *= np.float32(1e-20)
+    X[11, 7:K * N:N] *= np.float32(1e-37)                        # one column of them
+    X[14, :K * N] *= np.float32(1e-41)                           # subnormal weights
+    gpu = make_gpu(w, dict(inp, X0=X, feats=feats))
+    gpu.local_step(2)
+    h = gpu.hidden(1).cpu().numpy().astype(np.float64)
+    idx = oracle.sample_batch(w.M, w.batch, off, w.seed, 2)
+    for i in range(w.M):
+        a = feats[off[i] + idx[i]].astype(np.float64)
+        W, b = X[i, :K * N].reshape(K, N).astype(np.float64), X[i, K * N:K * N + N].astype(np.float64)
+        z = np.maximum(a @ W + b, 0.0)
+        # K products and the bias: each addition off by at most 2^-24 of the sum of the magnitudes, or half the smallest number
+        bound = (K + 2) * (2.0**-24 * (np.abs(a) @ np.abs(W) + np.abs(b)) + 2.0**-150)
+        assert np.all(np.abs(h[i] - z) <= bound), (i, float((np.abs(h[i] - z) / bound).max()))
+    assert 0 < h[3].max() < 1e-34 and 0 < h[14].max() < 1e-38
+    gpu.close()
