@@ -26,8 +26,9 @@ __device__ __forceinline__ bool decode_group(unsigned bid, unsigned blocks_per_w
         g = (int)(round * MF_XCD + xcd);
         return g < M;
     }
-    const unsigned run = (dealt * blocks_per_worker + MF_XCD - 1) / MF_XCD, at = xcd * run + (slot - rounds * blocks_per_worker);
-    const unsigned w = at / blocks_per_worker;
+    const unsigned run = (dealt * blocks_per_worker + MF_XCD - 1) / MF_XCD, nth = slot - rounds * blocks_per_worker;
+    if (nth >= run) return false;                            // behind the grid
+    const unsigned at = xcd * run + nth, w = at / blocks_per_worker;
     local = at - w * blocks_per_worker;
     g = (int)(rounds * MF_XCD + w);
     return w < dealt;
@@ -37,6 +38,17 @@ inline unsigned grouped_grid(int M, unsigned blocks_per_worker)
     const unsigned dealt = dealt_workers(blocks_per_worker, M);
     if (dealt == 0) return (unsigned)((M + MF_XCD - 1) / MF_XCD * MF_XCD) * blocks_per_worker;
     return ((unsigned)M / MF_XCD * blocks_per_worker + (dealt * blocks_per_worker + MF_XCD - 1) / MF_XCD) * MF_XCD;
+}
+
+// One direction of a launch holds fewer than 2^32 work-items (beyond, the count wraps and most of the launch is left out, without an
+// error), which many workers with wide layers of few outputs can exceed.  Such a grid is cut into rows of whole rounds over the
+// XCDs; a workgroup's id is then its row's start plus its place in the row, and ids behind the grid decode to nothing.
+constexpr unsigned GRID_ROW = 1u << 21;                     // x 1024 threads at the most
+struct GridRows { unsigned x, y; };
+inline GridRows grid_rows(unsigned workgroups)
+{
+    if (workgroups <= GRID_ROW) return {workgroups, 1};
+    return {GRID_ROW, (workgroups - 1) / GRID_ROW + 1};
 }
 
 // A number of workgroups rounded up to whole rounds over the XCDs: what follows them in a grid keeps its place in the deal.

@@ -30,7 +30,7 @@ __global__ void __launch_bounds__(64 * WM * WN) tile_dgrad_kernel(TileDgrad p)
     const unsigned nblk = (unsigned)((p.din + BN - 1) / BN), mblk = (unsigned)((p.B + BM - 1) / BM);
     int g;
     unsigned local;
-    if (!decode_group(blockIdx.x, nblk * mblk, p.M, g, local)) return;
+    if (!decode_group(tile_block(), nblk * mblk, p.M, g, local)) return;
     const int n0 = (int)(local % nblk) * BN, m0 = (int)(local / nblk) * BM;
     const int K = p.dout;
 
@@ -129,7 +129,7 @@ template <bool BF, bool V, int BM, int BN, int BK, int WM, int WN>
 static bool launch_shape(hipStream_t s, const TileDgrad &a)
 {
     const unsigned mblk = (unsigned)((a.B + BM - 1) / BM), blocks = (unsigned)((a.din + BN - 1) / BN) * mblk;
-    hipLaunchKernelGGL((tile_dgrad_kernel<BF, V, BM, BN, BK, WM, WN>), dim3(grouped_grid(a.M, blocks)), dim3(64 * WM * WN), 0, s, a);
+    hipLaunchKernelGGL((tile_dgrad_kernel<BF, V, BM, BN, BK, WM, WN>), tile_grid(grouped_grid(a.M, blocks)), dim3(64 * WM * WN), 0, s, a);
     return mblk == 1;
 }
 

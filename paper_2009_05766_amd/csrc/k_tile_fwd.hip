@@ -147,7 +147,7 @@ __global__ void __launch_bounds__(64 * WM * WN) tile_fwd_kernel(TileFwd p)
     const unsigned nblk = (unsigned)((p.dout + BN - 1) / BN), mblk = (unsigned)((p.B + BM - 1) / BM);
     int g;
     unsigned local;
-    if (!decode_group(blockIdx.x, nblk * mblk, p.M, g, local)) return;
+    if (!decode_group(tile_block(), nblk * mblk, p.M, g, local)) return;
     const int n0 = (int)(local % nblk) * BN, m0 = (int)(local / nblk) * BM;
     tile_f32x16 acc[RI][CJ];
     tile_fwd_product<BF, VA, VW, BM, BN, BK, WM, WN>(p, g, m0, n0, smem, acc);
@@ -171,7 +171,7 @@ __global__ void __launch_bounds__(SF_THREADS, 2) split_fwd_kernel(TileFwd p)
     const unsigned nblk = (unsigned)((p.dout + BN - 1) / BN), mblk = (unsigned)((p.B + BM - 1) / BM);
     int g;
     unsigned local;
-    if (!decode_group(blockIdx.x, nblk * mblk, p.M, g, local)) return;
+    if (!decode_group(tile_block(), nblk * mblk, p.M, g, local)) return;
     const int n0 = (int)(local % nblk) * BN, m0 = (int)(local / nblk) * BM;
     const int K = p.din;
     const float *in = (const float *)(p.feats ? p.feats : p.act);
@@ -252,7 +252,7 @@ template <bool BF, bool VA, bool VW, int BM, int BN, int BK, int WM, int WN>
 static void launch_shape(hipStream_t s, const TileFwd &a)
 {
     const unsigned blocks = (unsigned)((a.dout + BN - 1) / BN) * (unsigned)((a.B + BM - 1) / BM);
-    hipLaunchKernelGGL((tile_fwd_kernel<BF, VA, VW, BM, BN, BK, WM, WN>), dim3(grouped_grid(a.M, blocks)), dim3(64 * WM * WN), 0, s, a);
+    hipLaunchKernelGGL((tile_fwd_kernel<BF, VA, VW, BM, BN, BK, WM, WN>), tile_grid(grouped_grid(a.M, blocks)), dim3(64 * WM * WN), 0, s, a);
 }
 
 // Few workgroups are bound by the chain of steps, not by what a step costs: longer steps, narrower blocks.  Only full chips of
@@ -267,7 +267,7 @@ template <bool BF, bool VA, bool VW> static void launch_rows(hipStream_t s, cons
     else if constexpr (BF) launch_shape<BF, VA, VW, 128, 64, 64, 2, 2>(s, a);
     else {
         const unsigned blocks = (unsigned)((a.dout + SF_BN - 1) / SF_BN) * (unsigned)((a.B + SF_BM - 1) / SF_BM);
-        hipLaunchKernelGGL((split_fwd_kernel<VA, VW>), dim3(grouped_grid(a.M, blocks)), dim3(SF_THREADS), 0, s, a);
+        hipLaunchKernelGGL((split_fwd_kernel<VA, VW>), tile_grid(grouped_grid(a.M, blocks)), dim3(SF_THREADS), 0, s, a);
     }
 }
 

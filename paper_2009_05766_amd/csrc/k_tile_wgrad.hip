@@ -46,7 +46,7 @@ __global__ void __launch_bounds__(TW_THREADS, 4) tile_wgrad_kernel(TileWgrad p)
     float (*T)[TP] = reinterpret_cast<float (*)[TP]>(smem);
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6, wm = wave >> 2, wn = wave & 3;
     const int nblk = (p.dout + BN - 1) / BN, mblk = (p.din + BM - 1) / BM;
-    unsigned bid = blockIdx.x;
+    unsigned bid = tile_block();
     if constexpr (UPDATE) {
         if (bid < p.other_blocks) {
             const unsigned tile = bid / (unsigned)p.M;
@@ -191,7 +191,7 @@ __global__ void __launch_bounds__(TW_THREADS, 4) tile_wgrad_kernel(TileWgrad p)
 
 template <bool BF, bool VA, bool VZ> static void launch_cols(hipStream_t s, const TileWgrad &a, bool update)
 {
-    const dim3 grid(a.other_blocks + grouped_grid(a.M, (unsigned)((a.dout + TW_BN - 1) / TW_BN) * (unsigned)((a.din + TW_BM - 1) / TW_BM))), block(TW_THREADS);
+    const dim3 grid = tile_grid(a.other_blocks + grouped_grid(a.M, (unsigned)((a.dout + TW_BN - 1) / TW_BN) * (unsigned)((a.din + TW_BM - 1) / TW_BM))), block(TW_THREADS);
     if constexpr (VZ && !BF)
         if (update) {
             hipLaunchKernelGGL((tile_wgrad_kernel<BF, VA, VZ, true>), grid, block, 0, s, a);

@@ -22,6 +22,14 @@ typedef uint32_t tile_u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t tile_u32x2 __attribute__((ext_vector_type(2)));
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 tile_bf16x8;
 
+// Grid of a tiled kernel, and a workgroup's id in it.
+inline dim3 tile_grid(unsigned workgroups)
+{
+    const GridRows r = grid_rows(workgroups);
+    return dim3(r.x, r.y);
+}
+__device__ __forceinline__ unsigned tile_block() { return blockIdx.y * GRID_ROW + blockIdx.x; }
+
 // tiled_offset() with one 32 x 32 -> 64 bit multiply-add: j + (((j >> 11) (M - 1) + i) << 11); needs j < 2^43
 __device__ __forceinline__ size_t tiled_offset_quick(int M, int i, int64_t j)
 {

@@ -109,3 +109,37 @@ def test_wide_fp32_layers_against_64_bits(batch, dims):
         assert np.all(np.abs(h[i] - z) <= bound), (i, float((np.abs(h[i] - z) / bound).max()))
     assert 0 < h[3].max() < 1e-34 and 0 < h[14].max() < 1e-38
     gpu.close()
+
+
+@pytest.mark.parametrize("hidden,call", [(2, "local_step"), (4, "run")])
+def test_more_workgroups_than_one_direction_holds(hidden, call):
+    """A wide first layer of few outputs with many workers: more than 2^32 work-items in the weight gradient's launch.  Every worker
+    owns one data row, so its weight gradient is the product of that row and the bias gradient."""
+    import torch
+    import paper_2009_05766_amd as nm
+    M, K, T = 130, 64 * 65535, nm.NETMAX_TILE
+    dims = (K, hidden, 10)
+    D = K * hidden + hidden + hidden * 10 + 10
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    feats = torch.randn((M, K), generator=gen, device="cuda")
+    labels = torch.arange(M, device="cuda", dtype=torch.int32) % 10
+    net = nm.NetMax(M=M, D=D, ld=-(-D // T) * T, model=nm.NETMAX_MLP, dims=dims, batch=4, lr=0.01, momentum=0.9, rho=0.001, seed=3,
+                    P=(np.ones((M, M)) - np.eye(M)) / (M - 1), feats=feats, labels=labels, shard_off=np.arange(M + 1))
+    net.x_a.normal_(generator=gen).mul_(1e-3)
+    net.x_a.view(-1, M, T)[-1, :, D % T:] = 0.0                      # the padding
+    for buffer in (net.x_b, net.g):
+        buffer.fill_(7.0)
+    net.run(0, 1) if call == "run" else net.local_step(0)
+    torch.cuda.synchronize()
+    g = net.get("g", D)
+    slope = g[:, K * hidden:K * hidden + hidden]
+    assert int((slope != 0).any(dim=1).sum()) > M // 2               # some workers' units may all be off
+    for i in range(M):
+        want = feats[i][:, None] * slope[i][None, :]
+        # four products of four equal rows and their sums, each rounded, on either side
+        assert bool((g[i, :K * hidden].view(K, hidden) - want).abs().le(want.abs() * 2.0**-20 + 1e-30).all()), i
+    if call == "run":                                                # v was 0: it is g now; every parameter has been written
+        assert torch.equal(net.get("v", D), g)
+        x = net.get("x", D)
+        assert not bool((x == 7.0).any()) and bool(x.isfinite().all())
+    net.close()
