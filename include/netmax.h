@@ -138,9 +138,11 @@ int netmax_bind_data(netmax_ctx *ctx, const void *feats, const int32_t *labels, 
 
 /* Layout conversion on the context's stream.  rows_dev: device float, row-major [M][row_ld], row_ld >= D;
  * tiled_dev: device float M x ld in the tile layout.  netmax_pack copies the first D columns of every row
- * and zeroes the padding; netmax_unpack writes the first D columns of every row. */
+ * and zeroes the padding; netmax_unpack writes the first D columns of every row, netmax_unpack_zeroed also zeroes the row_ld - D
+ * columns behind them. */
 int netmax_pack(netmax_ctx *ctx, const float *rows_dev, int64_t row_ld, float *tiled_dev);
 int netmax_unpack(netmax_ctx *ctx, const float *tiled_dev, float *rows_dev, int64_t row_ld);
+int netmax_unpack_zeroed(netmax_ctx *ctx, const float *tiled_dev, float *rows_dev, int64_t row_ld);
 
 /* Peer selection of Algorithm 2 for all workers at iteration `iter`: worker i draws word 0 of block 0 of
  * stream 0 and takes the first m whose cumulative threshold exceeds it.  peers_dev: device int32 [M]. */

@@ -24,7 +24,7 @@ NETMAX_MIX_POLICY, NETMAX_MIX_FIXED = 0, 1
 
 EXPORTS = (
     "netmax_init", "netmax_build_tables", "netmax_generate_policy", "netmax_set_policy", "netmax_set_lr", "netmax_bind_state",
-    "netmax_bind_data", "netmax_pack", "netmax_unpack", "netmax_sample_peers", "netmax_sample_batch", "netmax_local_step", "netmax_mix", "netmax_run", "netmax_update_times", "netmax_update_times_async", "netmax_activity", "netmax_mean_times", "netmax_set_activity", "netmax_async_run", "netmax_set_fusion", "netmax_set_barrier_patience",
+    "netmax_bind_data", "netmax_pack", "netmax_unpack", "netmax_unpack_zeroed", "netmax_sample_peers", "netmax_sample_batch", "netmax_local_step", "netmax_mix", "netmax_run", "netmax_update_times", "netmax_update_times_async", "netmax_activity", "netmax_mean_times", "netmax_set_activity", "netmax_async_run", "netmax_set_fusion", "netmax_set_barrier_patience",
     "netmax_consensus_dist", "netmax_consensus_dist_static", "netmax_params", "netmax_losses", "netmax_read_losses", "netmax_read_hidden", "netmax_iteration", "netmax_get_tables",
     "netmax_last_error", "netmax_destroy",
 )
@@ -75,6 +75,7 @@ def load():
         "netmax_bind_data": (C.c_int, [vp, vp, vp, vp]),
         "netmax_pack": (C.c_int, [vp, vp, i64, vp]),
         "netmax_unpack": (C.c_int, [vp, vp, vp, i64]),
+        "netmax_unpack_zeroed": (C.c_int, [vp, vp, vp, i64]),
         "netmax_sample_peers": (C.c_int, [vp, u64, vp]),
         "netmax_sample_batch": (C.c_int, [vp, u64, vp]),
         "netmax_local_step": (C.c_int, [vp, u64]),
@@ -216,6 +217,11 @@ def netmax_pack(ctx, rows, row_ld: int, tiled):
 def netmax_unpack(ctx, tiled, rows, row_ld: int):
     import torch
     _check(load().netmax_unpack(ctx, _dp(tiled, torch.float32), _dp(rows, torch.float32), row_ld), ctx)
+
+
+def netmax_unpack_zeroed(ctx, tiled, rows, row_ld: int):
+    import torch
+    _check(load().netmax_unpack_zeroed(ctx, _dp(tiled, torch.float32), _dp(rows, torch.float32), row_ld), ctx)
 
 
 def netmax_sample_peers(ctx, it: int, peers):
@@ -416,10 +422,8 @@ class NetMax:
         import torch
         cols = self.ld if cols is None else cols
         out = torch.empty((self.M, cols), dtype=torch.float32, device=self.device)
-        if cols > self.D:
-            out[:, self.D:].zero_()                            # netmax_unpack writes the first D columns of every row
         self._join()
-        netmax_unpack(self.ctx, self._buffer(name), out, cols)
+        netmax_unpack_zeroed(self.ctx, self._buffer(name), out, cols)
         self._join()
         return out
 

@@ -86,9 +86,10 @@ int consensus_partials(int64_t ld);
 void launch_consensus(hipStream_t s, int M, int64_t D, int64_t ld, const float *X, double *partial,
                       double *out_dev);
 
-// Layout conversion between row-major [M][row_ld] and the tile layout (columns >= cols read as / are left 0).
+// Layout conversion between row-major [M][row_ld] and the tile layout.  pack: columns from `cols` on become 0; unpack: so do the
+// columns cols .. wide - 1.
 void launch_pack(hipStream_t s, int M, int64_t cols, int64_t ld, const float *rows, int64_t row_ld, float *tiled);
-void launch_unpack(hipStream_t s, int M, int64_t cols, const float *tiled, float *rows, int64_t row_ld);
+void launch_unpack(hipStream_t s, int M, int64_t cols, const float *tiled, float *rows, int64_t row_ld, int64_t wide);
 
 // out[k] = bfloat16 in[k] as float, k < n.
 void launch_widen_bf16(hipStream_t s, int64_t n, const uint16_t *in, float *out);

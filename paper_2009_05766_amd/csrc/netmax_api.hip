@@ -537,12 +537,22 @@ extern "C" int netmax_pack(netmax_ctx *ctx, const float *rows_dev, int64_t row_l
     return check_launch(ctx, "pack");
 }
 
+// wide: columns of a row that are written (D, or more: zeros behind it)
+static int unpack(netmax_ctx *ctx, const float *tiled_dev, float *rows_dev, int64_t row_ld, int64_t wide)
+{
+    if (!rows_dev || !tiled_dev || row_ld < ctx->cfg.D) return fail(ctx, NETMAX_EINVAL, "NULL pointer or row_ld < D");
+    launch_unpack(ctx->stream, ctx->cfg.M, ctx->cfg.D, tiled_dev, rows_dev, row_ld, wide);
+    return check_launch(ctx, "unpack");
+}
+
 extern "C" int netmax_unpack(netmax_ctx *ctx, const float *tiled_dev, float *rows_dev, int64_t row_ld)
 {
-    if (!ctx) return NETMAX_EINVAL;
-    if (!rows_dev || !tiled_dev || row_ld < ctx->cfg.D) return fail(ctx, NETMAX_EINVAL, "NULL pointer or row_ld < D");
-    launch_unpack(ctx->stream, ctx->cfg.M, ctx->cfg.D, tiled_dev, rows_dev, row_ld);
-    return check_launch(ctx, "unpack");
+    return ctx ? unpack(ctx, tiled_dev, rows_dev, row_ld, ctx->cfg.D) : NETMAX_EINVAL;
+}
+
+extern "C" int netmax_unpack_zeroed(netmax_ctx *ctx, const float *tiled_dev, float *rows_dev, int64_t row_ld)
+{
+    return ctx ? unpack(ctx, tiled_dev, rows_dev, row_ld, row_ld) : NETMAX_EINVAL;
 }
 
 // The three phases of one iteration, enqueued on the context's stream (no argument checks, no pointer flip).

@@ -30,6 +30,14 @@ def test_pack_and_unpack_move_every_element(M, D, pad_tiles, row_ld, shift):
     back = torch.full((M * row_ld + shift,), 7.0, device="cuda")[shift:].view(M, row_ld)
     nm.netmax_unpack(net.ctx, tiled, back, row_ld)
     assert torch.equal(back[:, :D], rows[:, :D]) and bool((back[:, D:] == 7.0).all())       # columns from D on are left alone
+    nm.netmax_unpack_zeroed(net.ctx, tiled, back, row_ld)
+    assert torch.equal(back[:, :D], rows[:, :D]) and bool((back[:, D:] == 0.0).all())
+    # wider than the tiles that exist, and not a multiple of four; nothing behind the last row is written
+    for wide in (D, D + 1, ld + 1, ld + 2 * T + 3):
+        out = torch.full((M * wide + 64,), 7.0, device="cuda")
+        nm.netmax_unpack_zeroed(net.ctx, tiled, out, wide)
+        assert torch.equal(out[:M * wide].view(M, wide)[:, :D], rows[:, :D]) and bool((out[:M * wide].view(M, wide)[:, D:] == 0.0).all())
+        assert bool((out[M * wide:] == 7.0).all())
     net.set("x", rows)
     assert torch.equal(net.get("x"), want) and torch.equal(net.get("x", D), want[:, :D])
     net.close()
