@@ -2,14 +2,19 @@
 // Algorithm 2's first-step update): the tiled kernel for what the kernels of k_grad_mfma.hip and k_grad_f32.hip do not take.
 //
 // A workgroup takes BM batch rows and BN outputs of one worker.  A is contiguous along the contraction (gathered data rows
-// or activations), W across it.  Large layers on fp32 operands are bound by the fp32 matrix rate: 3072 -> 1024, batch 128, 32 workers
+// or activations), W across it.  Pieces of A are one load whatever the length of its rows, W is read in pieces where its rows start
+// at multiples of four and lane by lane elsewhere.  Element by element with the lanes four elements apart, and without the steps
+// shared by four waves (launch_rows), odd shapes took two to three times as long, in us: 5 x 1227 -> 254, batch 128, 69 and now 19;
+// 52 x 3072 -> 51, batch 42, 103 and 38; 47 x 1330 -> 184, batch 128, 134 and 61; bfloat16 5 x 3072 -> 82, batch 20, 81 and 29.
+//
+// Large layers on fp32 operands are bound by the fp32 matrix rate: 3072 -> 1024, batch 128, 32 workers
 // 273 to 292 us, the matrix pipe busy 66 % of the time (64 x 64 blocks: 293 us; the 64 x 64 kernel with 4-byte loads and steps of 32
-// before it: 367 us).  With the operands as three bfloat16 planes (split_fwd_kernel) 223 to 233 us on the same boxes, 3072-1024-10
+// before it: 367 us).  With the operands as three bfloat16 planes (split_fwd_kernel) 223 to 240 us on the same boxes, 3072-1024-10
 // with it 679 instead of 716 us per iteration, 784-1024-10 with 64 workers 399 instead of 449 us; the hidden activations are then
 // 8.6e-7 off their 64-bit values instead of 9.9e-7 (3072 terms; 1.5e-7 and 1.8e-7 with 100).  Bound there by the vector
 // instructions of the split (55 % of a SIMD's cycles) beside the products (39 %); forcing the two into turns inside a wave, and eight
 // waves instead of four, changed nothing.  Small bfloat16 layers are bound by the chain of steps: 784 -> 500 and 500 -> 300, batch
-// 100, 16 workers 33 us together (66 us with the earlier kernel, which multiplied the rounded operands by fp32 instructions).
+// 100, 16 workers 20 and 10 us (39 and 28 us with the earlier kernel, which multiplied the rounded operands by fp32 instructions).
 #include "tile.h"
 
 #include <type_traits>
@@ -23,6 +28,25 @@ struct TileFwd {
     float *out; uint16_t *out_bf16, *out_bf16_t;                      // [M][B][dout], and [M][dout][B]; each may be absent
 };
 
+// ReLU and the store of one element (bias added)
+template <bool BF> __device__ __forceinline__ void tile_fwd_put(const TileFwd &p, int g, int row, int col, float z)
+{
+    if (p.relu) z = z > 0.0f ? z : 0.0f;
+    if (col < p.dout && row < p.B) {
+        const size_t q = ((size_t)g * p.B + row) * p.dout + col;
+        if (p.out) p.out[q] = z;
+        if constexpr (BF) {
+            const uint16_t h = (uint16_t)bf16_bits(z);
+            if (p.out_bf16) p.out_bf16[q] = h;
+            if (p.out_bf16_t) p.out_bf16_t[((size_t)g * p.dout + col) * p.B + row] = h;
+        }
+    }
+}
+__device__ __forceinline__ float tile_fwd_bias(const TileFwd &p, int g, int col)
+{
+    return p.X[tiled_offset_quick(p.M, g, p.woff + (int64_t)p.din * p.dout + (col < p.dout ? col : p.dout - 1))];
+}
+
 // bias, ReLU and the store of a finished block
 template <bool BF, int BM, int BN, int WM, int WN, int RI, int CJ>
 __device__ __forceinline__ void tile_fwd_store(const TileFwd &p, int g, int m0, int n0, int wm, int wn, int lane, const tile_f32x16 (&acc)[RI][CJ])
@@ -30,40 +54,46 @@ __device__ __forceinline__ void tile_fwd_store(const TileFwd &p, int g, int m0, 
 #pragma unroll
     for (int j = 0; j < CJ; ++j) {
         const int col = n0 + wn * (BN / WN) + 32 * j + (lane & 31);
-        const int cc = col < p.dout ? col : p.dout - 1;
-        const float bias = p.X[tiled_offset_quick(p.M, g, p.woff + (int64_t)p.din * p.dout + cc)];
+        const float bias = tile_fwd_bias(p, g, col);
 #pragma unroll
         for (int i = 0; i < RI; ++i)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int row = m0 + wm * (BM / WM) + 32 * i + tile_row(lane, v);
-                float z = acc[i][j][v] + bias;
-                if (p.relu) z = z > 0.0f ? z : 0.0f;
-                if (col < p.dout && row < p.B) {
-                    const size_t q = ((size_t)g * p.B + row) * p.dout + col;
-                    if (p.out) p.out[q] = z;
-                    if constexpr (BF) {
-                        const uint16_t h = (uint16_t)bf16_bits(z);
-                        if (p.out_bf16) p.out_bf16[q] = h;
-                        if (p.out_bf16_t) p.out_bf16_t[((size_t)g * p.dout + col) * p.B + row] = h;
-                    }
-                }
-            }
+            for (int v = 0; v < 16; ++v)
+                tile_fwd_put<BF>(p, g, m0 + wm * (BM / WM) + 32 * i + tile_row(lane, v), col, acc[i][j][v] + bias);
     }
 }
 
-// The product of one block, operands as they are (BF: rounded to bfloat16).  smem: LDS for both.
-template <bool BF, bool VA, bool VW, int BM, int BN, int BK, int WM, int WN, int RI, int CJ>
+// Where the weights of a step lie: those of its first row start `rem` floats into a tile whose part of this worker starts at `base`.
+// Offsets of a step count from there in 32 bits (128 rows of at most 2^24 columns).
+struct StepWeights {
+    const float *base; uint32_t rem, skip;
+    __device__ __forceinline__ StepWeights(const TileFwd &p, int g, int k0)
+    {
+        const int64_t j = p.woff + (int64_t)k0 * p.dout;
+        base = p.X + (((size_t)(j >> TILE_SHIFT) * p.M + g) << TILE_SHIFT);
+        rem = (uint32_t)(j & (TILE - 1));
+        skip = (uint32_t)(p.M - 1) << TILE_SHIFT;
+    }
+    __device__ __forceinline__ float at(uint32_t u) const { return base[(uint64_t)(u >> TILE_SHIFT) * skip + u]; }
+};
+
+// The product of one block, operands as they are (BF: rounded to bfloat16).  smem: LDS for both.  VA: rows of A have four elements or
+// more; VW: rows of W start at multiples of four and four columns at a time are one load, otherwise a thread's loads are single
+// floats, neighbouring lanes neighbouring columns.  WK waves share the contraction indices of every step; the parts are the
+// caller's to add.
+template <bool BF, bool VA, bool VW, int BM, int BN, int BK, int WM, int WN, int WK, int RI, int CJ>
 __device__ __forceinline__ void tile_fwd_product(const TileFwd &p, int g, int m0, int n0, unsigned char *smem, tile_f32x16 (&acc)[RI][CJ])
 {
-    constexpr int NT = 64 * WM * WN, K4 = BK / 4;
+    constexpr int NT = 64 * WM * WN * WK, K4 = BK / 4;
     constexpr int NA = BM * K4 / NT, NB = BN * K4 / 4 / NT;           // pieces of A, 4 x 4 blocks of W per thread and step
     static_assert(NA * NT == BM * K4 && NB * NT == BN * K4 / 4, "every thread has the same share");
+    static_assert(BK <= 128 && NT % BN == 0, "offsets inside a step; a column per thread");
     typedef TileLds<BF, BK> L;
     typedef typename L::elem elem;
     elem (*As)[L::PITCH] = reinterpret_cast<elem (*)[L::PITCH]>(smem);
     elem (*Bs)[L::PITCH] = reinterpret_cast<elem (*)[L::PITCH]>(smem + BM * L::PITCH * sizeof(elem));
-    const int t = threadIdx.x, lane = t & 63, wave = t >> 6, wm = wave / WN, wn = wave % WN;
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6, wm = wave / WK / WN, wn = wave / WK % WN;
+    const int ka = __builtin_amdgcn_readfirstlane(wave % WK * (BK / WK));             // this wave's indices of a step
     const int K = p.din;
 
     int64_t a_row[NA];                                                // element index of a piece at step 0 (row clamped)
@@ -76,50 +106,61 @@ __device__ __forceinline__ void tile_fwd_product(const TileFwd &p, int g, int m0
         const int r = m0 + a_m[u] < p.B ? m0 + a_m[u] : p.B - 1;
         a_row[u] = p.feats ? (p.row0[g] + p.idx[(size_t)g * p.B + r]) * K : ((int64_t)g * p.B + r) * K;
     }
-    int b_n[NB], b_k[NB], b_c[NB], b_have[NB];
+    // VW: a 4 x 4 block at rows b_k, columns b_n.  Otherwise four pieces of four rows of a column: 4 u + i at rows b_k[u] + i * NT / BN * 4
+    constexpr int STRIPE = VW ? 0 : NT / BN * 4;
+    int b_n[NB], b_k[NB], b_c[NB];
 #pragma unroll
     for (int u = 0; u < NB; ++u) {
         const int c = t + u * NT;
-        b_n[u] = c % (BN / 4) * 4;
-        b_k[u] = c / (BN / 4) * 4;
+        b_n[u] = VW ? c % (BN / 4) * 4 : t % BN;
+        b_k[u] = VW ? c / (BN / 4) * 4 : t / BN * 4 + u * 4 * STRIPE;
         const int want = n0 + b_n[u];                                 // columns past the end repeat the last one(s)
         b_c[u] = want < p.dout ? want : (VW ? p.dout - 4 : p.dout - 1);
-        b_have[u] = p.dout - b_c[u];
     }
     Piece<BF> ra[NA];
     Piece<false> rb[NB][4];
-    const float *Xg = p.X;
     auto fetch = [&](int k0) {
 #pragma unroll
         for (int u = 0; u < NA; ++u) {
-            int k = k0 + a_k[u];
-            k = k < K ? k : (VA ? K - 4 : K - 1);
+            const int k = min(k0 + a_k[u], VA ? K - 4 : K - 1);
             if constexpr (BF) ra[u] = load_piece<VA>((const uint16_t *)(p.feats ? p.feats : p.act) + a_row[u] + k, K - k);
             else ra[u] = load_piece<VA>((const float *)(p.feats ? p.feats : p.act) + a_row[u] + k, K - k);
         }
+        if constexpr (VW) {
 #pragma unroll
-        for (int u = 0; u < NB; ++u)
+            for (int u = 0; u < NB; ++u)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int k = k0 + b_k[u] + i < K ? k0 + b_k[u] + i : K - 1;
-                const int64_t j = p.woff + (int64_t)k * p.dout + b_c[u];
-                if constexpr (VW) rb[u][i] = load_piece<true>(Xg + tiled_offset_quick(p.M, g, j), 4);
-                else {
+                for (int i = 0; i < 4; ++i) {
+                    const int k = k0 + b_k[u] + i < K ? k0 + b_k[u] + i : K - 1;
+                    rb[u][i].v = load4(p.X + tiled_offset_quick(p.M, g, p.woff + (int64_t)k * p.dout + b_c[u]));
+                }
+        } else {
+            const StepWeights w(p, g, k0);
+            const uint32_t last = (uint32_t)min(K - 1 - k0, BK) * (uint32_t)p.dout;   // rows past the end repeat the last one
+#pragma unroll
+            for (int u = 0; u < NB; ++u)
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
-                        rb[u][i].v[e] = Xg[tiled_offset_quick(p.M, g, j + (e < b_have[u] ? e : b_have[u] - 1))];
-                }
-            }
+                        rb[u][i].v[e] = w.at(min((uint32_t)(b_k[u] + i * STRIPE + e) * (uint32_t)p.dout, last) + (w.rem + (uint32_t)b_c[u]));
+        }
     };
     auto stash = [&](int k0) {
         // indices that exist from k on: 4 or more everywhere but in the last step
         const int left = K - k0;
 #pragma unroll
-        for (int u = 0; u < NA; ++u) put_piece(&As[a_m[u]][a_k[u]], ra[u].v, left - a_k[u]);
+        for (int u = 0; u < NA; ++u) {
+            if constexpr (VA) put_piece(&As[a_m[u]][a_k[u]], piece_tail(ra[u], left - a_k[u]).v, 4);
+            else put_piece(&As[a_m[u]][a_k[u]], ra[u].v, left - a_k[u]);
+        }
 #pragma unroll
         for (int u = 0; u < NB; ++u)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) put_piece(&Bs[b_n[u] + e][b_k[u]], turned(rb[u], e), left - b_k[u]);
+            for (int e = 0; e < 4; ++e) {
+                if constexpr (VW) put_piece(&Bs[b_n[u] + e][b_k[u]], turned(rb[u], e), left - b_k[u]);
+                else put_piece(&Bs[b_n[u]][b_k[u] + e * STRIPE], rb[u][e].v, left - b_k[u] - e * STRIPE);
+            }
     };
 
     tile_clear(acc);
@@ -129,7 +170,7 @@ __device__ __forceinline__ void tile_fwd_product(const TileFwd &p, int g, int m0
         stash(k0);
         __syncthreads();
         if (k0 + BK < K) fetch(k0 + BK);                              // travels while this step is multiplied
-        tile_multiply<BK>(As, Bs, wm * (BM / WM), wn * (BN / WN), lane, acc);
+        if (WK == 1 || k0 + ka < K) tile_multiply<BK / WK>(As, Bs, wm * (BM / WM), wn * (BN / WN), lane, acc, BK / WK, ka);
     }
 }
 
@@ -138,7 +179,7 @@ template <bool BF, int BM, int BN, int BK> constexpr int tile_fwd_lds()
     return (BM + BN) * TileLds<BF, BK>::PITCH * (int)sizeof(typename TileLds<BF, BK>::elem);
 }
 
-template <bool BF, bool VA, bool VW, int BM, int BN, int BK, int WM, int WN>
+template <bool BF, bool VW, int BM, int BN, int BK, int WM, int WN>
 __global__ void __launch_bounds__(64 * WM * WN) tile_fwd_kernel(TileFwd p)
 {
     constexpr int RI = BM / WM / 32, CJ = BN / WN / 32;
@@ -150,14 +191,46 @@ __global__ void __launch_bounds__(64 * WM * WN) tile_fwd_kernel(TileFwd p)
     if (!decode_group(tile_block(), nblk * mblk, p.M, g, local)) return;
     const int n0 = (int)(local % nblk) * BN, m0 = (int)(local / nblk) * BM;
     tile_f32x16 acc[RI][CJ];
-    tile_fwd_product<BF, VA, VW, BM, BN, BK, WM, WN>(p, g, m0, n0, smem, acc);
+    tile_fwd_product<BF, true, VW, BM, BN, BK, WM, WN, 1>(p, g, m0, n0, smem, acc);
     tile_fwd_store<BF, BM, BN, WM, WN>(p, g, m0, n0, wm, wn, lane, acc);
+}
+
+// 32 x 32 blocks, four waves that share every step's contraction indices; their parts are added through LDS in the order of the
+// waves.
+constexpr int SH_BK = 128, SH_WAVES = 4, SH_PITCH = 33;
+template <bool BF, bool VA, bool VW>
+__global__ void __launch_bounds__(64 * SH_WAVES) shared_fwd_kernel(TileFwd p)
+{
+    constexpr int LDS = tile_fwd_lds<BF, 32, 32, SH_BK>(), PARTS = SH_WAVES * 32 * SH_PITCH * (int)sizeof(float);
+    __shared__ __attribute__((aligned(16))) unsigned char smem[LDS > PARTS ? LDS : PARTS];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const unsigned nblk = (unsigned)((p.dout + 31) / 32), mblk = (unsigned)((p.B + 31) / 32);
+    int g;
+    unsigned local;
+    if (!decode_group(tile_block(), nblk * mblk, p.M, g, local)) return;
+    const int n0 = (int)(local % nblk) * 32, m0 = (int)(local / nblk) * 32, col = lane & 31;
+    const float bias = tile_fwd_bias(p, g, n0 + col);
+    tile_f32x16 acc[1][1];
+    tile_fwd_product<BF, VA, VW, 32, 32, SH_BK, 1, 1, SH_WAVES>(p, g, m0, n0, smem, acc);
+    __syncthreads();                                                  // the operands' space becomes the parts
+    float (*part)[32][SH_PITCH] = reinterpret_cast<float (*)[32][SH_PITCH]>(smem);
+#pragma unroll
+    for (int v = 0; v < 16; ++v) part[wave][tile_row(lane, v)][col] = acc[0][0][v];
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const int row = tile_row(lane, 4 * wave + e);
+        float z = part[0][row][col];
+#pragma unroll
+        for (int w = 1; w < SH_WAVES; ++w) z += part[w][row][col];
+        tile_fwd_put<BF>(p, g, m0 + row, n0 + col, z + bias);
+    }
 }
 
 // fp32 operands on the bfloat16 matrix instructions: 128 x 64 blocks, steps of 32, three planes of each operand in LDS, twice:
 // the next step is split while this one is multiplied.
 constexpr int SF_BM = 128, SF_BN = 64, SF_BK = 32, SF_WM = 2, SF_WN = 2, SF_THREADS = 256;
-template <bool VA, bool VW>
+template <bool VW>
 __global__ void __launch_bounds__(SF_THREADS, 2) split_fwd_kernel(TileFwd p)
 {
     constexpr int BM = SF_BM, BN = SF_BN, BK = SF_BK, WM = SF_WM, WN = SF_WN, NT = SF_THREADS, RI = BM / WM / 32, CJ = BN / WN / 32, K4 = BK / 4;
@@ -182,36 +255,48 @@ __global__ void __launch_bounds__(SF_THREADS, 2) split_fwd_kernel(TileFwd p)
         const int m = m0 + (t + u * NT) / K4, r = m < p.B ? m : p.B - 1;
         a_row[u] = p.feats ? (p.row0[g] + p.idx[(size_t)g * p.B + r]) * K : ((int64_t)g * p.B + r) * K;
     }
-    const int b_n = t / (BK / 2) * 4, b_k = t % (BK / 2) * 2;
+    // VW: two rows of four columns.  Otherwise eight rows of a column: neighbouring lanes, neighbouring columns
+    const int b_n = VW ? t / (BK / 2) * 4 : t % BN, b_k = VW ? t % (BK / 2) * 2 : t / BN * 8;
+    static_assert(NT / BN * 8 == BK, "a column and eight rows per thread");
     const int b_c = n0 + b_n < p.dout ? n0 + b_n : (VW ? p.dout - 4 : p.dout - 1);     // columns past the end repeat the last one(s)
-    const int b_have = p.dout - b_c;
     Piece<false> ra[NA], rb[2];
     bool lost = false;                                                // an operand of this thread that its planes do not hold
     auto fetch = [&](int k0) {
-        int k = k0 + a_k;
-        k = k < K ? k : (VA ? K - 4 : K - 1);
+        const int k = min(k0 + a_k, K - 4);
 #pragma unroll
-        for (int u = 0; u < NA; ++u) ra[u] = load_piece<VA>(in + a_row[u] + k, K - k);
+        for (int u = 0; u < NA; ++u) ra[u] = load_piece<true>(in + a_row[u] + k, 4);
+        if constexpr (VW) {
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const int kb = k0 + b_k + i < K ? k0 + b_k + i : K - 1;
-            const int64_t j = p.woff + (int64_t)kb * p.dout + b_c;
-            if constexpr (VW) rb[i] = load_piece<true>(p.X + tiled_offset_quick(p.M, g, j), 4);
-            else {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) rb[i].v[e] = p.X[tiled_offset_quick(p.M, g, j + (e < b_have ? e : b_have - 1))];
+            for (int i = 0; i < 2; ++i) {
+                const int kb = k0 + b_k + i < K ? k0 + b_k + i : K - 1;
+                rb[i].v = load4(p.X + tiled_offset_quick(p.M, g, p.woff + (int64_t)kb * p.dout + b_c));
             }
+        } else {
+            const int from = k0 < K ? k0 : K - 1;                     // fetches past the end: the last row again
+            const StepWeights w(p, g, from);
+            const uint32_t last = (uint32_t)min(K - 1 - from, BK) * (uint32_t)p.dout;
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) rb[i].v[e] = w.at(min((uint32_t)(b_k + 4 * i + e) * (uint32_t)p.dout, last) + (w.rem + (uint32_t)b_c));
         }
     };
     auto stash = [&](int k0, uint16_t *buf, auto whole) {             // whole: all indices of the step exist
         const int left = decltype(whole)::value ? BK : K - k0;
 #pragma unroll
         for (int u = 0; u < NA; ++u)
-            put_split(buf + split_at((t + u * NT) / K4, a_k), SA, decltype(whole)::value ? ra[u].v : first_of(ra[u].v, left - a_k), lost);
+            put_split(buf + split_at((t + u * NT) / K4, a_k), SA,
+                      decltype(whole)::value ? ra[u].v : piece_tail(ra[u], left - a_k).v, lost);
+        if constexpr (VW) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-            put_split(buf + 3 * SA + (b_n + e) * SPLIT_PITCH + b_k, SB, left > b_k ? rb[0].v[e] : 0.0f, left > b_k + 1 ? rb[1].v[e] : 0.0f,
-                      lost);
+            for (int e = 0; e < 4; ++e)
+                put_split(buf + 3 * SA + (b_n + e) * SPLIT_PITCH + b_k, SB, left > b_k ? rb[0].v[e] : 0.0f, left > b_k + 1 ? rb[1].v[e] : 0.0f,
+                          lost);
+        } else {
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+                put_split(buf + 3 * SA + b_n * SPLIT_PITCH + b_k + 4 * i, SB, first_of(rb[i].v, left - b_k - 4 * i), lost);
+        }
     };
     tile_f32x16 acc[RI][CJ];
     tile_clear(acc);
@@ -244,31 +329,45 @@ __global__ void __launch_bounds__(SF_THREADS, 2) split_fwd_kernel(TileFwd p)
                 lost |= fabsf(acc[i][j][v]) < FEW_BITS && acc[i][j][v] != 0.0f;
             }
     if (__syncthreads_or(lost || !(watch == 0.0f)))
-        tile_fwd_product<false, VA, VW, BM, BN, 64, WM, WN>(p, g, m0, n0, smem, acc);
+        tile_fwd_product<false, true, VW, BM, BN, 64, WM, WN, 1>(p, g, m0, n0, smem, acc);
     tile_fwd_store<false, BM, BN, WM, WN>(p, g, m0, n0, wm, wn, lane, acc);
 }
 
-template <bool BF, bool VA, bool VW, int BM, int BN, int BK, int WM, int WN>
+template <bool BF, bool VW, int BM, int BN, int BK, int WM, int WN>
 static void launch_shape(hipStream_t s, const TileFwd &a)
 {
     const unsigned blocks = (unsigned)((a.dout + BN - 1) / BN) * (unsigned)((a.B + BM - 1) / BM);
-    hipLaunchKernelGGL((tile_fwd_kernel<BF, VA, VW, BM, BN, BK, WM, WN>), tile_grid(grouped_grid(a.M, blocks)), dim3(64 * WM * WN), 0, s, a);
+    hipLaunchKernelGGL((tile_fwd_kernel<BF, VW, BM, BN, BK, WM, WN>), tile_grid(grouped_grid(a.M, blocks)), dim3(64 * WM * WN), 0, s, a);
 }
 
-// Few workgroups are bound by the chain of steps, not by what a step costs: longer steps, narrower blocks.  Only full chips of
-// more than 64 batch rows are bound by the fp32 matrix rate.
+// Few workgroups are bound by the chain of steps: 32 x 32 blocks whose steps four waves share, until there are enough of the larger
+// blocks.  Counted in 32 x 64 blocks; us per iteration, shared and the larger form, either side of each line:
+//   fp32, batch <= 32      96 x 784-515 (864) 287 and 304, 128 x 784-515 (1152) 381 and 385, 128 x 100-900 (1920) 104 and 104
+//   fp32, batch <= 64      64 x 784-300 (640) 131 and 137, 96 x 784-300 (960) 190 and 178
+//   fp32, more             24 x 784-512, batch 128 (768) 107 and 115, 48 x 784-512 (1536) 188 and 168; on the line (1024) 64 x 784-256
+//                          135 and 131, 16 x 3072-1024 400 and 404, 8 x 3072-1024, batch 200 323 and 339
+//   bfloat16               48 x 1227-254, batch 64 (384) 117 and 119, 31 x 3001-999, batch 20 (496) 577 and 590; 64 x 784-300, batch 50
+//                          (640) 107 and 106, 48 x 784-515, batch 50 (864) 151 and 145
+// Larger forms, bfloat16, batch > 64: 128 x 32 blocks while the 128 x 64 ones do not fill the chip: 31 x 784-500, batch 100 (248 of
+// the latter) 97 and 102, 64 x 1000-300 (320) 145 and 143, 31 x 3001-999 (496) 755 and 710.
 template <bool BF, bool VA, bool VW> static void launch_rows(hipStream_t s, const TileFwd &a)
 {
-    constexpr int LONG = BF ? 128 : 64;
-    const int64_t wide = (int64_t)a.M * ((a.dout + 63) / 64) * ((a.B + 127) / 128);
-    if (a.B <= 32) launch_shape<BF, VA, VW, 32, 64, 64, 1, 2>(s, a);
-    else if (a.B <= 64) launch_shape<BF, VA, VW, 64, 64, LONG, 2, 2>(s, a);
-    else if (wide < 512) launch_shape<BF, VA, VW, 128, 32, 128, 4, 1>(s, a);
-    else if constexpr (BF) launch_shape<BF, VA, VW, 128, 64, 64, 2, 2>(s, a);
-    else {
-        const unsigned blocks = (unsigned)((a.dout + SF_BN - 1) / SF_BN) * (unsigned)((a.B + SF_BM - 1) / SF_BM);
-        hipLaunchKernelGGL((split_fwd_kernel<VA, VW>), tile_grid(grouped_grid(a.M, blocks)), dim3(SF_THREADS), 0, s, a);
-    }
+    const int64_t cols = (int64_t)a.M * ((a.dout + 63) / 64), blocks = cols * ((a.B + 31) / 32), wide = cols * ((a.B + 127) / 128);
+    const int64_t enough = BF ? 512 : a.B > 32 && a.B <= 64 ? 641 : 1025;
+    if constexpr (VA)
+        if (blocks >= enough) {
+            if (a.B <= 32) launch_shape<BF, VW, 32, 64, 64, 1, 2>(s, a);
+            else if (a.B <= 64) launch_shape<BF, VW, 64, 64, BF ? 128 : 64, 2, 2>(s, a);
+            else if constexpr (!BF) {
+                const unsigned n = (unsigned)((a.dout + SF_BN - 1) / SF_BN) * (unsigned)((a.B + SF_BM - 1) / SF_BM);
+                hipLaunchKernelGGL((split_fwd_kernel<VW>), tile_grid(grouped_grid(a.M, n)), dim3(SF_THREADS), 0, s, a);
+            }
+            else if (wide <= MF_XCD * XCD_CUS) launch_shape<BF, VW, 128, 32, 128, 4, 1>(s, a);
+            else launch_shape<BF, VW, 128, 64, 64, 2, 2>(s, a);
+            return;
+        }
+    const unsigned n = (unsigned)((a.dout + 31) / 32) * (unsigned)((a.B + 31) / 32);
+    hipLaunchKernelGGL((shared_fwd_kernel<BF, VA, VW>), tile_grid(grouped_grid(a.M, n)), dim3(64 * SH_WAVES), 0, s, a);
 }
 
 void launch_tile_fwd(hipStream_t s, const MlpPlan &p, int l, const float *X, bool need_t)
@@ -281,8 +380,8 @@ void launch_tile_fwd(hipStream_t s, const MlpPlan &p, int l, const float *X, boo
     a.out = (last || !bf) ? p.act[l + 1] : nullptr;
     a.out_bf16 = (bf && !last) ? p.hb[l + 1] : nullptr;
     a.out_bf16_t = (bf && !last && need_t) ? p.ht[l + 1] : nullptr;
-    // pieces of A: four elements, aligned to their size; pieces of W: four columns of a row that starts at a multiple of four
-    const bool va = a.din % 4 == 0 && reinterpret_cast<uintptr_t>(a.feats ? a.feats : a.act) % (bf ? 8 : 16) == 0;
+    // pieces of A: any four neighbours; pieces of W: four columns of a row that starts at a multiple of four
+    const bool va = a.din >= 4;
     const bool vw = a.dout % 4 == 0 && a.woff % 4 == 0;
     if (bf) {
         if (va) { if (vw) launch_rows<true, true, true>(s, a); else launch_rows<true, true, false>(s, a); }

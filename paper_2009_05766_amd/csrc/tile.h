@@ -48,12 +48,14 @@ __device__ __forceinline__ int tile_opaque(int v)
 template <bool S16> struct Piece { f32x4 v; };
 template <> struct Piece<true> { tile_u32x2 v; };
 
-// V: one load (the four elements exist and are aligned).  Otherwise element by element, n of them exist (at least one;
-// the others repeat the last).
+// V: one load of four elements that exist, at any address of an element (gfx950 takes wide loads there).  Otherwise element by
+// element, n of them exist (at least one; the others repeat the last).
+typedef float tile_f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t tile_u32x2_any __attribute__((ext_vector_type(2), aligned(2)));
 template <bool V> __device__ __forceinline__ Piece<false> load_piece(const float *p, int n)
 {
     Piece<false> r;
-    if constexpr (V) r.v = load4(p);
+    if constexpr (V) r.v = *reinterpret_cast<const tile_f32x4_any *>(p);
     else {
 #pragma unroll
         for (int e = 0; e < 4; ++e) r.v[e] = p[e < n ? e : n - 1];
@@ -63,7 +65,7 @@ template <bool V> __device__ __forceinline__ Piece<false> load_piece(const float
 template <bool V> __device__ __forceinline__ Piece<true> load_piece(const uint16_t *p, int n)
 {
     Piece<true> r;
-    if constexpr (V) r.v = *reinterpret_cast<const tile_u32x2 *>(p);
+    if constexpr (V) r.v = *reinterpret_cast<const tile_u32x2_any *>(p);
     else {
         uint32_t h[4];
 #pragma unroll
@@ -73,8 +75,29 @@ template <bool V> __device__ __forceinline__ Piece<true> load_piece(const uint16
     return r;
 }
 
-// Element e of a loaded piece as fp32, as 16 bits, as the value of either kind.
-__device__ __forceinline__ float piece_f32(const Piece<false> &p, int e) { return p.v[e]; }
+// A row whose length is no multiple of four: its last piece is loaded from four elements before the end.  The piece with the last
+// `left` (1 .. 3) of those first and zeros behind them; of more than three nothing changes, of less than one all zeros.
+__device__ __forceinline__ Piece<false> piece_tail(Piece<false> p, int left)
+{
+    if (left < 4) {
+        const f32x4 v = p.v;
+        p.v[0] = left == 3 ? v[1] : left == 2 ? v[2] : left == 1 ? v[3] : 0.0f;
+        p.v[1] = left == 3 ? v[2] : left == 2 ? v[3] : 0.0f;
+        p.v[2] = left == 3 ? v[3] : 0.0f;
+        p.v[3] = 0.0f;
+    }
+    return p;
+}
+__device__ __forceinline__ Piece<true> piece_tail(Piece<true> p, int left)
+{
+    if (left < 4) {
+        const uint64_t v = left > 0 ? (((uint64_t)p.v[1] << 32) | p.v[0]) >> (16 * (4 - left)) : 0ull;
+        p.v = tile_u32x2{(uint32_t)v, (uint32_t)(v >> 32)};
+    }
+    return p;
+}
+
+// Element e of a loaded piece as 16 bits, as the value of either kind.
 __device__ __forceinline__ uint32_t piece_bits(const Piece<true> &p, int e) { return (p.v[e >> 1] >> (16 * (e & 1))) & 0xFFFFu; }
 
 __device__ __forceinline__ float piece_value(const Piece<false> &p, int e) { return p.v[e]; }
@@ -122,7 +145,7 @@ __device__ __forceinline__ tile_u32x2 turned(const Piece<true> (&r)[4], int e)
     return tile_u32x2{piece_bits(r[0], e) | (piece_bits(r[1], e) << 16), piece_bits(r[2], e) | (piece_bits(r[3], e) << 16)};
 }
 
-// One step: acc[i][j] += As[m0 + 32 i ..][ka + k] Bs[n0 + 32 j ..][k] over BK indices in LDS, of which `left` exist (the others are
+// One step: acc[i][j] += As[m0 + 32 i ..][ka + k] Bs[n0 + 32 j ..][ka + k] over BK indices in LDS, of which `left` exist (the others are
 // zeros; whole groups of 32 of them are left out).
 template <int BK, int RI, int CJ, int PA, int PB>
 __device__ __forceinline__ void tile_multiply(const float (*As)[PA], const float (*Bs)[PB], int m0, int n0, int lane,
@@ -135,7 +158,7 @@ __device__ __forceinline__ void tile_multiply(const float (*As)[PA], const float
 #pragma unroll
         for (int i = 0; i < RI; ++i) a[i] = *reinterpret_cast<const f32x4 *>(&As[m0 + 32 * i + (lane & 31)][ka + ks + 4 * (lane >> 5)]);
 #pragma unroll
-        for (int j = 0; j < CJ; ++j) b[j] = *reinterpret_cast<const f32x4 *>(&Bs[n0 + 32 * j + (lane & 31)][ks + 4 * (lane >> 5)]);
+        for (int j = 0; j < CJ; ++j) b[j] = *reinterpret_cast<const f32x4 *>(&Bs[n0 + 32 * j + (lane & 31)][ka + ks + 4 * (lane >> 5)]);
 #pragma unroll
         for (int c = 0; c < 4; ++c)
 #pragma unroll
@@ -155,7 +178,7 @@ __device__ __forceinline__ void tile_multiply(const uint16_t (*As)[PA], const ui
 #pragma unroll
         for (int i = 0; i < RI; ++i) a[i] = *reinterpret_cast<const tile_u32x4 *>(&As[m0 + 32 * i + (lane & 31)][ka + ks + 8 * (lane >> 5)]);
 #pragma unroll
-        for (int j = 0; j < CJ; ++j) b[j] = *reinterpret_cast<const tile_u32x4 *>(&Bs[n0 + 32 * j + (lane & 31)][ks + 8 * (lane >> 5)]);
+        for (int j = 0; j < CJ; ++j) b[j] = *reinterpret_cast<const tile_u32x4 *>(&Bs[n0 + 32 * j + (lane & 31)][ka + ks + 8 * (lane >> 5)]);
 #pragma unroll
         for (int i = 0; i < RI; ++i)
 #pragma unroll

@@ -143,3 +143,49 @@ def test_more_workgroups_than_one_direction_holds(hidden, call):
         x = net.get("x", D)
         assert not bool((x == 7.0).any()) and bool(x.isfinite().all())
     net.close()
+
+
+@pytest.mark.parametrize("dtype,M,batch,dims", [
+    # steps shared by four waves: contractions around its step of 128 and of one to four elements, rows of data and of weights at
+    # every alignment
+    *[(t, 2, b, d) for t in ("f32", "bf16") for b, d in (
+        (33, (127, 35, 33, 10)), (20, (129, 64, 10)), (128, (257, 51, 66, 10)), (31, (1, 40, 10)), (45, (2, 37, 9)), (32, (3, 36, 10)), (7, (4, 33, 10)),
+        (64, (5, 2050, 10)), (100, (1023, 46, 10)))],
+])
+def test_gradient_where_waves_share_the_steps(ora, dtype, M, batch, dims):
+    test_gradient_of_odd_layers(ora, dtype, M, batch, dims)
+
+
+@pytest.mark.parametrize("dtype,M,batch,dims", [
+    # enough blocks for the larger forms: batches up to 32, 64 and more, weights in pieces and not, rows of any length
+    ("f32", 128, 20, (149, 515, 10)), ("f32", 128, 32, (132, 516, 10)), ("bf16", 64, 20, (131, 515, 10)), ("bf16", 64, 32, (66, 516, 10)),
+    ("f32", 40, 50, (130, 515, 10)), ("f32", 40, 64, (67, 516, 10)), ("bf16", 32, 50, (131, 515, 10)), ("bf16", 32, 64, (260, 516, 10)),
+    ("bf16", 20, 100, (150, 515, 10)), ("bf16", 20, 128, (129, 516, 10)), ("bf16", 64, 100, (133, 513, 10)), ("bf16", 64, 128, (196, 516, 10)),
+    # and one block less than the lines between them (in blocks of 32 x 64: 512 and 641, 1025; 256 of 128 x 64)
+    ("f32", 114, 20, (149, 515, 10)), ("f32", 35, 50, (130, 515, 10)), ("f32", 28, 128, (130, 515, 10)), ("bf16", 28, 50, (131, 515, 10)),
+    ("bf16", 28, 128, (129, 515, 10)), ("bf16", 29, 128, (129, 515, 10)),
+])
+def test_activations_of_the_larger_forms(dtype, M, batch, dims):
+    """Every activation of the first layer against float64 with the same operands."""
+    import oracle
+    w = workload("cfg5" if dtype == "bf16" else "cfg2", M=M, batch=batch, n_per_worker=batch + 7, dims=dims)
+    inp = inputs_of(w)
+    K, N, off = dims[0], dims[1], inp["shard_off"]
+    gpu = make_gpu(w, inp)
+    gpu.local_step(2)
+    h = gpu.hidden(1).cpu().numpy().astype(np.float64)
+    idx = oracle.sample_batch(w.M, w.batch, off, w.seed, 2)
+
+    def operand(x):                                                  # to the nearest bfloat16, ties to even
+        u = x.view(np.uint32)
+        return (((u + 0x7FFF + ((u >> 16) & 1)) >> 16) << 16).view(np.float32)
+    for i in range(M):
+        a, W = inp["feats"][off[i] + idx[i]], inp["X0"][i, :K * N]
+        if dtype == "bf16":
+            a, W = (a.astype(np.uint32) << 16).view(np.float32), operand(W)
+        a, W, b = a.astype(np.float64), W.reshape(K, N).astype(np.float64), inp["X0"][i, K * N:K * N + N].astype(np.float64)
+        z = np.maximum(a @ W + b, 0.0)
+        # K products and the bias, each addition off by at most 2^-24 of the sum of the magnitudes; stored as bfloat16 2^-8 more
+        bound = (K + 2) * 2.0**-24 * (np.abs(a) @ np.abs(W) + np.abs(b)) + (2.0**-8 * z if dtype == "bf16" else 0.0)
+        assert np.all(np.abs(h[i] - z) <= bound), i
+    gpu.close()
