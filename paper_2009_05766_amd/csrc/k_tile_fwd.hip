@@ -63,20 +63,6 @@ __device__ __forceinline__ void tile_fwd_store(const TileFwd &p, int g, int m0, 
     }
 }
 
-// Where the weights of a step lie: those of its first row start `rem` floats into a tile whose part of this worker starts at `base`.
-// Offsets of a step count from there in 32 bits (128 rows of at most 2^24 columns).
-struct StepWeights {
-    const float *base; uint32_t rem, skip;
-    __device__ __forceinline__ StepWeights(const TileFwd &p, int g, int k0)
-    {
-        const int64_t j = p.woff + (int64_t)k0 * p.dout;
-        base = p.X + (((size_t)(j >> TILE_SHIFT) * p.M + g) << TILE_SHIFT);
-        rem = (uint32_t)(j & (TILE - 1));
-        skip = (uint32_t)(p.M - 1) << TILE_SHIFT;
-    }
-    __device__ __forceinline__ float at(uint32_t u) const { return base[(uint64_t)(u >> TILE_SHIFT) * skip + u]; }
-};
-
 // The product of one block, operands as they are (BF: rounded to bfloat16).  smem: LDS for both.  VA: rows of A have four elements or
 // more; VW: rows of W start at multiples of four and four columns at a time are one load, otherwise a thread's loads are single
 // floats, neighbouring lanes neighbouring columns.  WK waves share the contraction indices of every step; the parts are the
@@ -135,7 +121,8 @@ __device__ __forceinline__ void tile_fwd_product(const TileFwd &p, int g, int m0
                     rb[u][i].v = load4(p.X + tiled_offset_quick(p.M, g, p.woff + (int64_t)k * p.dout + b_c[u]));
                 }
         } else {
-            const StepWeights w(p, g, k0);
+            const TileSpan w(p.M, g, p.woff + (int64_t)k0 * p.dout);
+            const float *Xs = p.X + w.base;
             const uint32_t last = (uint32_t)min(K - 1 - k0, BK) * (uint32_t)p.dout;   // rows past the end repeat the last one
 #pragma unroll
             for (int u = 0; u < NB; ++u)
@@ -143,7 +130,7 @@ __device__ __forceinline__ void tile_fwd_product(const TileFwd &p, int g, int m0
                 for (int i = 0; i < 4; ++i)
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
-                        rb[u][i].v[e] = w.at(min((uint32_t)(b_k[u] + i * STRIPE + e) * (uint32_t)p.dout, last) + (w.rem + (uint32_t)b_c[u]));
+                        rb[u][i].v[e] = Xs[w.at(min((uint32_t)(b_k[u] + i * STRIPE + e) * (uint32_t)p.dout, last) + (uint32_t)b_c[u])];
         }
     };
     auto stash = [&](int k0) {
@@ -273,12 +260,13 @@ __global__ void __launch_bounds__(SF_THREADS, 2) split_fwd_kernel(TileFwd p)
             }
         } else {
             const int from = k0 < K ? k0 : K - 1;                     // fetches past the end: the last row again
-            const StepWeights w(p, g, from);
+            const TileSpan w(p.M, g, p.woff + (int64_t)from * p.dout);
+            const float *Xs = p.X + w.base;
             const uint32_t last = (uint32_t)min(K - 1 - from, BK) * (uint32_t)p.dout;
 #pragma unroll
             for (int i = 0; i < 2; ++i)
 #pragma unroll
-                for (int e = 0; e < 4; ++e) rb[i].v[e] = w.at(min((uint32_t)(b_k + 4 * i + e) * (uint32_t)p.dout, last) + (w.rem + (uint32_t)b_c));
+                for (int e = 0; e < 4; ++e) rb[i].v[e] = Xs[w.at(min((uint32_t)(b_k + 4 * i + e) * (uint32_t)p.dout, last) + (uint32_t)b_c)];
         }
     };
     auto stash = [&](int k0, uint16_t *buf, auto whole) {             // whole: all indices of the step exist

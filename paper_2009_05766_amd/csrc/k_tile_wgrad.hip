@@ -1,8 +1,10 @@
 // Weight gradient dW = A^T dZ of a layer of any shape for all workers (the stochastic gradient of Algorithm 2's first-step
 // update): the tiled kernel for what the kernels of k_grad_mfma.hip and k_grad_f32.hip do not take.
 //
-// A workgroup takes 64 input features and 128 outputs of one worker; the contraction runs over the batch, both operands lie
-// across it in memory.  The block is turned through LDS and leaves as row pieces of 128 floats.
+// A workgroup takes 64 input features and 64 or 128 outputs of one worker; the contraction runs over the batch, both operands lie
+// across it in memory.  The block is turned through LDS and leaves as pieces of rows.
+// Rows of any length are read in pieces of four elements: 52 workers 3072 x 51, batch 42, fp32 25 us (50 us element by element, the
+// lanes four apart, in blocks of 128 columns; 32 us with the 64 x 64 blocks and 4-byte loads before that).
 // 3072 x 1024, batch 128, 32 workers, fp32: 311 us (402 us with 64 x 64 blocks, 4-byte loads and 128-byte row pieces);
 // 784 x 500 and 500 x 300, batch 100, 16 workers, bfloat16: 21 us together (54 us with fp32 instructions).
 //
@@ -27,15 +29,20 @@ struct TileWgrad {
     const int32_t *tiles; int n_tiles; unsigned other_blocks; MixSkip skip;
 };
 
-constexpr int TW_BM = 64, TW_BN = 128, TW_BK = 64, TW_THREADS = 512;
-
-template <bool BF, bool VA, bool VZ, bool UPDATE>
-__global__ void __launch_bounds__(TW_THREADS, 4) tile_wgrad_kernel(TileWgrad p)
+// Rows of dZ and dW that start at multiples of 16 bytes; rows of at least four elements at any address; anything.  The first two read
+// pieces of four elements, the first one writes them.
+enum : int { TW_ALIGNED = 0, TW_PIECES = 1, TW_SINGLE = 2 };
+constexpr int TW_BM = 64, TW_BK = 64;
+constexpr int tw_threads(int BN) { return 4 * BN; }                   // waves of 32 x 32 blocks
+// (Four waves per SIMD; the narrow block with update would spill its pieces of x and v at that.)
+template <bool BF, int MODE, bool UPDATE, int BN>
+__global__ void __launch_bounds__(tw_threads(BN), UPDATE && BN == 64 ? 3 : 4) tile_wgrad_kernel(TileWgrad p)
 {
+    constexpr bool V = MODE != TW_SINGLE, VZ = MODE == TW_ALIGNED;
     static_assert(!UPDATE || VZ, "the update works on 128-bit pieces");
-    constexpr int BM = TW_BM, BN = TW_BN, BK = TW_BK, NT = TW_THREADS;
-    constexpr int A_BLOCKS = BM / 4 * (BK / 4);                       // 4 x 4 blocks of A per step: half a block per thread
-    static_assert(2 * A_BLOCKS == NT && BN / 4 * (BK / 4) == NT, "half a block of A and one of dZ per step and thread");
+    constexpr int BM = TW_BM, BK = TW_BK, NT = tw_threads(BN), CW = BN / 32;
+    constexpr int AR = BM * BK / 4 / NT;                              // batch rows of four features of A per step and thread
+    static_assert((AR == 2 || AR == 4) && BN / 4 * (BK / 4) == NT, "half a 4 x 4 block of A or a whole one, and one of dZ");
     typedef TileLds<BF, BK> L;
     typedef typename L::elem elem;
     constexpr int TP = BN + 4;                                        // floats per row of the staged result
@@ -44,13 +51,13 @@ __global__ void __launch_bounds__(TW_THREADS, 4) tile_wgrad_kernel(TileWgrad p)
     elem (*As)[L::PITCH] = reinterpret_cast<elem (*)[L::PITCH]>(smem);
     elem (*Zs)[L::PITCH] = reinterpret_cast<elem (*)[L::PITCH]>(smem + BM * L::PITCH * sizeof(elem));
     float (*T)[TP] = reinterpret_cast<float (*)[TP]>(smem);
-    const int t = threadIdx.x, lane = t & 63, wave = t >> 6, wm = wave >> 2, wn = wave & 3;
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6, wm = wave / CW, wn = wave % CW;
     const int nblk = (p.dout + BN - 1) / BN, mblk = (p.din + BM - 1) / BM;
     unsigned bid = tile_block();
     if constexpr (UPDATE) {
         if (bid < p.other_blocks) {
             const unsigned tile = bid / (unsigned)p.M;
-            if (tile < (unsigned)p.n_tiles) mix_subset_block<TW_THREADS>(p.M, p.tiles[tile], (int)(bid - tile * (unsigned)p.M), p.skip, p.G, p.mix);
+            if (tile < (unsigned)p.n_tiles) mix_subset_block<NT>(p.M, p.tiles[tile], (int)(bid - tile * (unsigned)p.M), p.skip, p.G, p.mix);
             return;
         }
         bid -= p.other_blocks;
@@ -63,46 +70,56 @@ __global__ void __launch_bounds__(TW_THREADS, 4) tile_wgrad_kernel(TileWgrad p)
     const int f0 = (int)(local / (unsigned)nblk) * BM, n0 = (int)(local % (unsigned)nblk) * BN;
     const int K = p.B;
 
-    // A: two batch rows of four features per thread
-    const int a_m = t % (BM / 4) * 4, a_k = t / (BM / 4) * 2;
-    int a_f = f0 + a_m;
-    a_f = a_f < p.din ? a_f : (VA ? p.din - 4 : p.din - 1);
-    const int a_have = p.din - a_f;
+    // A: AR batch rows of four features per thread.  Pieces that reach over the end are read from four elements before it and
+    // turned to their place; what is past the end is never stored
+    const int a_m = t % (BM / 4) * 4, a_k = t / (BM / 4) * AR;
+    const int a_left = p.din - f0 - a_m, a_f = V ? min(f0 + a_m, p.din - 4) : min(f0 + a_m, p.din - 1);
     const int64_t base_row = p.feats ? p.row0[g] : (int64_t)g * K;
     const int32_t *rows = p.feats ? p.idx + (size_t)g * K : nullptr;
     const int z_n = t % (BN / 4) * 4, z_k = t / (BN / 4) * 4;
-    int z_c = n0 + z_n;
-    z_c = z_c < p.dout ? z_c : (VZ ? p.dout - 4 : p.dout - 1);
+    const int z_left = p.dout - n0 - z_n, z_c = V ? min(n0 + z_n, p.dout - 4) : min(n0 + z_n, p.dout - 1);
     const float *zg = p.dz + (size_t)g * K * p.dout + z_c;
-    int32_t row_of[2];                                                // batch rows of the coming step, asked for a step ahead
+    int32_t row_of[AR];                                               // batch rows of the coming step, asked for a step ahead
     auto fetch_rows = [&](int k0) {
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
+        for (int i = 0; i < AR; ++i) {
             const int k = k0 + a_k + i < K ? k0 + a_k + i : K - 1;
             row_of[i] = rows ? rows[k] : k;
         }
     };
-    Piece<BF> ra[2];
+    Piece<BF> ra[AR];
     Piece<false> rz[4];
     auto fetch = [&](int k0) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int k = k0 + z_k + i < K ? k0 + z_k + i : K - 1;
-            rz[i] = load_piece<VZ>(zg + (size_t)k * p.dout, p.dout - z_c);
+            rz[i] = load_piece<V>(zg + (size_t)k * p.dout, p.dout - z_c);
         }
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
+        for (int i = 0; i < AR; ++i) {
             const int64_t q = (base_row + row_of[i]) * p.din + a_f;
-            if constexpr (BF) ra[i] = load_piece<VA>((const uint16_t *)(p.feats ? p.feats : p.act) + q, a_have);
-            else ra[i] = load_piece<VA>((const float *)(p.feats ? p.feats : p.act) + q, a_have);
+            if constexpr (BF) ra[i] = load_piece<V>((const uint16_t *)(p.feats ? p.feats : p.act) + q, p.din - a_f);
+            else ra[i] = load_piece<V>((const float *)(p.feats ? p.feats : p.act) + q, p.din - a_f);
         }
     };
     auto stash = [&](int k0) {
         const int left = K - k0;
-        // two neighbouring k of a feature: one 64-bit (32-bit) word of its row
+        if constexpr (V) {
+            if (a_left < 4) {
+#pragma unroll
+                for (int i = 0; i < AR; ++i) ra[i] = piece_tail(ra[i], a_left);
+            }
+            if (MODE == TW_PIECES && z_left < 4) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) rz[i] = piece_tail(rz[i], z_left);
+            }
+        }
+        // neighbouring k of a feature: one word of its row, of two or four elements
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            if constexpr (BF) {
+            if constexpr (AR == 4) {
+                put_piece(&As[a_m + e][a_k], turned(ra, e), left - a_k);
+            } else if constexpr (BF) {
                 uint32_t h = piece_bits(ra[0], e) | (piece_bits(ra[1], e) << 16);
                 h = left - a_k >= 2 ? h : (left - a_k == 1 ? h & 0xFFFFu : 0u);
                 *reinterpret_cast<uint32_t *>(&As[a_m + e][a_k]) = h;
@@ -128,6 +145,8 @@ __global__ void __launch_bounds__(TW_THREADS, 4) tile_wgrad_kernel(TileWgrad p)
     const int oc = t % PER_ROW * W, orow = t / PER_ROW;
     const bool col_ok = n0 + oc < p.dout;
     const int64_t j0 = p.woff + (int64_t)f0 * p.dout + (col_ok ? n0 + oc : 0);
+    const TileSpan rows_of_g(p.M, g, p.woff + (int64_t)f0 * p.dout);
+    float *Gs = p.G + rows_of_g.base;
     auto own_of = [&](int u) {
         const int r = tile_opaque(u * ROWS + orow);
         return tiled_offset_quick(p.M, g, j0 + (int64_t)(f0 + r < p.din ? r : 0) * p.dout);
@@ -172,8 +191,8 @@ __global__ void __launch_bounds__(TW_THREADS, 4) tile_wgrad_kernel(TileWgrad p)
     for (int u = 0; u < PASSES; ++u) {
         const int r = u * ROWS + orow;
         if (f0 + r < p.din) {
-            const size_t own = own_of(u);
             if constexpr (VZ) {
+                const size_t own = own_of(u);
                 const f32x4 gr = *reinterpret_cast<const f32x4 *>(&T[r][oc]);
                 store4_stream(p.G + own, gr);
                 if constexpr (UPDATE) {
@@ -183,27 +202,40 @@ __global__ void __launch_bounds__(TW_THREADS, 4) tile_wgrad_kernel(TileWgrad p)
                     store4_stream(p.mix.V + own, vn);
                 }
             } else {
-                p.G[own] = T[r][oc];
+                Gs[rows_of_g.at((uint32_t)r * (uint32_t)p.dout + (uint32_t)(n0 + oc))] = T[r][oc];
             }
         }
     }
 }
 
-template <bool BF, bool VA, bool VZ> static void launch_cols(hipStream_t s, const TileWgrad &a, bool update)
+template <bool BF, int MODE, int BN> static void launch_block(hipStream_t s, TileWgrad &a, bool update)
 {
-    const dim3 grid = tile_grid(a.other_blocks + grouped_grid(a.M, (unsigned)((a.dout + TW_BN - 1) / TW_BN) * (unsigned)((a.din + TW_BM - 1) / TW_BM))), block(TW_THREADS);
-    if constexpr (VZ && !BF)
+    const dim3 grid = tile_grid(a.other_blocks + grouped_grid(a.M, (unsigned)((a.dout + BN - 1) / BN) * (unsigned)((a.din + TW_BM - 1) / TW_BM)));
+    const dim3 block(tw_threads(BN));
+    if constexpr (MODE == TW_ALIGNED && !BF)
         if (update) {
-            hipLaunchKernelGGL((tile_wgrad_kernel<BF, VA, VZ, true>), grid, block, 0, s, a);
+            hipLaunchKernelGGL((tile_wgrad_kernel<BF, MODE, true, BN>), grid, block, 0, s, a);
             return;
         }
-    hipLaunchKernelGGL((tile_wgrad_kernel<BF, VA, VZ, false>), grid, block, 0, s, a);
+    hipLaunchKernelGGL((tile_wgrad_kernel<BF, MODE, false, BN>), grid, block, 0, s, a);
+}
+
+// Blocks of 64 columns where they leave less of a narrow layer empty (up to 64 columns, 129 to 192), and on fp32 rows that are not
+// aligned, whose results leave as single floats either way.  us per iteration, 52 workers, with 64 and with 128 columns:
+//   784-64, batch 100 49 and 59, 784-192 92 and 101, 784-150 bfloat16, batch 200 104 and 106; but 784-100, batch 42 57 and 51,
+//   784-300 124 and 115, batch 200 216 and 226
+//   rows not aligned, batch 200: 3072-51 190 and 249, 1227-254 262 and 273, 784-515 350 and 379; bfloat16 126 and 141, 173 and 169,
+//   227 and 226
+template <bool BF, int MODE> static void launch_cols(hipStream_t s, TileWgrad &a, bool update)
+{
+    if ((a.dout <= 192 && (a.dout + 63) / 64 % 2) || (!BF && MODE != TW_ALIGNED)) launch_block<BF, MODE, 64>(s, a, update);
+    else launch_block<BF, MODE, 128>(s, a, update);
 }
 
 // Rows of dZ and of dW start at multiples of 16 bytes.
 static bool rows_in_pieces(const MlpPlan &p, int l) { return p.dims[l + 1] % 4 == 0 && p.woff[l] % 4 == 0; }
 
-bool tile_wgrad_update_ok(const MlpPlan &p, int l) { return !p.bf16 && rows_in_pieces(p, l); }
+bool tile_wgrad_update_ok(const MlpPlan &p, int l) { return !p.bf16 && rows_in_pieces(p, l) && p.dims[l] >= 4; }
 
 void launch_tile_wgrad(hipStream_t s, const MlpPlan &p, int l, float *G, int cur, const TailArgs *tail, bool others)
 {
@@ -217,14 +249,15 @@ void launch_tile_wgrad(hipStream_t s, const MlpPlan &p, int l, float *G, int cur
     a.feats = l == 0 ? p.feats : nullptr; a.row0 = p.row0; a.idx = p.idx;
     a.act = l == 0 ? nullptr : (bf ? (const void *)p.hb[l] : (const void *)p.act[l]);
     a.dz = p.dz[cur]; a.M = p.M; a.B = p.B; a.din = (int)p.dims[l]; a.dout = (int)p.dims[l + 1]; a.woff = p.woff[l]; a.G = G;
-    const bool va = a.din % 4 == 0 && reinterpret_cast<uintptr_t>(a.feats ? a.feats : a.act) % (bf ? 8 : 16) == 0;
-    const bool vz = rows_in_pieces(p, l);
+    const bool pieces = a.din >= 4 && a.dout >= 4;
     if (bf) {
-        if (va) { if (vz) launch_cols<true, true, true>(s, a, u); else launch_cols<true, true, false>(s, a, u); }
-        else { if (vz) launch_cols<true, false, true>(s, a, u); else launch_cols<true, false, false>(s, a, u); }
+        if (!pieces) launch_cols<true, TW_SINGLE>(s, a, u);
+        else if (rows_in_pieces(p, l)) launch_cols<true, TW_ALIGNED>(s, a, u);
+        else launch_cols<true, TW_PIECES>(s, a, u);
     } else {
-        if (va) { if (vz) launch_cols<false, true, true>(s, a, u); else launch_cols<false, true, false>(s, a, u); }
-        else { if (vz) launch_cols<false, false, true>(s, a, u); else launch_cols<false, false, false>(s, a, u); }
+        if (!pieces) launch_cols<false, TW_SINGLE>(s, a, u);
+        else if (rows_in_pieces(p, l)) launch_cols<false, TW_ALIGNED>(s, a, u);
+        else launch_cols<false, TW_PIECES>(s, a, u);
     }
 }
 

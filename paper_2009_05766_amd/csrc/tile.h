@@ -37,6 +37,19 @@ __device__ __forceinline__ size_t tiled_offset_quick(int M, int i, int64_t j)
     return (size_t)j + (size_t)(t << TILE_SHIFT);
 }
 
+// A stretch of a worker's parameters that starts at parameter j: offset of parameter j + u as base + at(u), in 32 bits but for the last
+// step (u < 2^32 - TILE, a block of 128 rows of at most 2^24 columns).  j is the same for all lanes.
+struct TileSpan {
+    size_t base; uint32_t rem, skip;
+    __device__ __forceinline__ TileSpan(int M, int g, int64_t j)
+        : base(((size_t)(j >> TILE_SHIFT) * M + g) << TILE_SHIFT), rem((uint32_t)(j & (TILE - 1))), skip((uint32_t)(M - 1) << TILE_SHIFT) {}
+    __device__ __forceinline__ size_t at(uint32_t u) const
+    {
+        const uint32_t q = rem + u;
+        return (uint64_t)(q >> TILE_SHIFT) * skip + q;
+    }
+};
+
 // The value, hidden from the optimiser: addresses computed from it inside a loop are computed there, not kept in registers across it.
 __device__ __forceinline__ int tile_opaque(int v)
 {

@@ -51,6 +51,15 @@ def test_run_is_the_separate_calls(name, M, batch, dims, graph):
     calls.close(), run.close()
 
 
+@pytest.mark.parametrize("name,M,batch,dims", [
+    # blocks of 64 columns with the update (one to three of them), data rows of every alignment and of fewer than four features
+    ("cfg2", 3, 100, (101, 64, 10)), ("cfg2", 22, 128, (786, 192, 10)), ("cfg2", 5, 40, (3, 36, 10)), ("cfg2", 9, 100, (7, 132, 60, 10)),
+    ("cfg2", 40, 90, (787, 148, 60, 10)),
+])
+def test_run_with_narrow_layers(name, M, batch, dims):
+    test_run_is_the_separate_calls(name, M, batch, dims, False)
+
+
 @pytest.mark.parametrize("name,over", [("cfg2", dict(M=5, batch=24, n_per_worker=40, dims=(30, 20, 10))), ("cfg3", dict(M=7, D=5000)),
                                        ("cfg5", dict(M=2, batch=1024, n_per_worker=1100, dims=(20, 8)))])
 @pytest.mark.parametrize("n", [1, 15, 16, 17, 35])

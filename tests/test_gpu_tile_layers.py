@@ -156,6 +156,15 @@ def test_gradient_where_waves_share_the_steps(ora, dtype, M, batch, dims):
     test_gradient_of_odd_layers(ora, dtype, M, batch, dims)
 
 
+@pytest.mark.parametrize("dtype,M,batch,dims", [(t, 2, b, d) for t in ("f32", "bf16") for b, d in (
+    # weight gradients: blocks of 64 and of 128 columns and their remainders, rows aligned or not, one to seven features or outputs,
+    # batches around a step of 64
+    (63, (65, 64, 10)), (65, (66, 65, 10)), (64, (130, 128, 192, 10)), (40, (5, 129, 193, 10)), (129, (6, 188, 7, 10)), (33, (7, 132, 5, 10)),
+    (17, (2, 60, 3, 40)), (70, (90, 2, 61, 33)), (50, (64, 1, 130, 10)))])
+def test_weight_gradients_of_every_width(ora, dtype, M, batch, dims):
+    test_gradient_of_odd_layers(ora, dtype, M, batch, dims)
+
+
 @pytest.mark.parametrize("dtype,M,batch,dims", [
     # enough blocks for the larger forms: batches up to 32, 64 and more, weights in pieces and not, rows of any length
     ("f32", 128, 20, (149, 515, 10)), ("f32", 128, 32, (132, 516, 10)), ("bf16", 64, 20, (131, 515, 10)), ("bf16", 64, 32, (66, 516, 10)),
