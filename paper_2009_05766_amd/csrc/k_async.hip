@@ -40,9 +40,9 @@ __global__ void __launch_bounds__(256) async_draw_kernel(int M, const uint32_t *
 // here with the step's number as iteration and stored to the worker's row of G; 1: it is read from the worker's row
 // of G; 2: it is read from the slot's row of the compact matrix Gc (tile layout over the slots of the batch) and copied
 // to the worker's row of G, and so is the slot's loss.
-template <int SOURCE>
+template <int SOURCE, class Slots>
 __global__ void __launch_bounds__(256) async_row_kernel(int M, int64_t D, float *__restrict__ X, float *__restrict__ V,
-                                                        float *__restrict__ G, const float *__restrict__ Gc, AsyncSlots slots,
+                                                        float *__restrict__ G, const float *__restrict__ Gc, Slots slots,
                                                         const float *__restrict__ w, float alpha, float mu, float wd, float sigma,
                                                         uint64_t seed, const float *__restrict__ loss_c, float *__restrict__ loss)
 {
@@ -75,7 +75,8 @@ __global__ void __launch_bounds__(256) async_row_kernel(int M, int64_t D, float 
 // Before the perceptron gradient of a batch: the parameter rows of its workers copied into a compact matrix (tile layout over
 // the slots), and, by one more workgroup per slot (blockIdx.x = n_tiles), the first feature row of the worker's shard and the
 // batch draw of the slot's step, as sample_batch_kernel makes it for all workers at one iteration.
-__global__ void __launch_bounds__(256) gather_slots_kernel(int M, int n_tiles, AsyncSlots slots, const float *__restrict__ X,
+template <class Slots>
+__global__ void __launch_bounds__(256) gather_slots_kernel(int M, int n_tiles, Slots slots, const float *__restrict__ X,
                                                            float *__restrict__ Xc, int B, const int64_t *__restrict__ row0,
                                                            const int32_t *__restrict__ n_rows, uint64_t seed,
                                                            int64_t *__restrict__ row0_c, int32_t *__restrict__ idx)
@@ -135,26 +136,41 @@ void launch_async_draw(hipStream_t s, int M, const uint32_t *act_thr, int act_la
                        last, seed, first, n_steps, active, peers);
 }
 
-void launch_async_rows(hipStream_t s, int source, int M, int64_t D, int64_t ld, float *X, float *V, float *G, const float *Gc,
-                       const AsyncSlots &slots, const float *w, float alpha, float mu, float wd, float sigma, uint64_t seed,
-                       const float *loss_c, float *loss)
+template <class Slots>
+static void launch_rows(hipStream_t s, int source, int M, int64_t D, int64_t ld, float *X, float *V, float *G, const float *Gc,
+                        const Slots &slots, const float *w, float alpha, float mu, float wd, float sigma, uint64_t seed,
+                        const float *loss_c, float *loss)
 {
     static_assert(TILE == 2048, "256 threads x 2 x 4 columns cover one tile");
     const dim3 grid((unsigned)(ld / TILE), (unsigned)slots.n);
     if (source == 0)
-        hipLaunchKernelGGL(async_row_kernel<0>, grid, dim3(256), 0, s, M, D, X, V, G, Gc, slots, w, alpha, mu, wd, sigma, seed, loss_c, loss);
+        hipLaunchKernelGGL((async_row_kernel<0, Slots>), grid, dim3(256), 0, s, M, D, X, V, G, Gc, slots, w, alpha, mu, wd, sigma, seed, loss_c, loss);
     else if (source == 1)
-        hipLaunchKernelGGL(async_row_kernel<1>, grid, dim3(256), 0, s, M, D, X, V, G, Gc, slots, w, alpha, mu, wd, sigma, seed, loss_c, loss);
+        hipLaunchKernelGGL((async_row_kernel<1, Slots>), grid, dim3(256), 0, s, M, D, X, V, G, Gc, slots, w, alpha, mu, wd, sigma, seed, loss_c, loss);
     else
-        hipLaunchKernelGGL(async_row_kernel<2>, grid, dim3(256), 0, s, M, D, X, V, G, Gc, slots, w, alpha, mu, wd, sigma, seed, loss_c, loss);
+        hipLaunchKernelGGL((async_row_kernel<2, Slots>), grid, dim3(256), 0, s, M, D, X, V, G, Gc, slots, w, alpha, mu, wd, sigma, seed, loss_c, loss);
+}
+
+void launch_async_rows(hipStream_t s, int source, int M, int64_t D, int64_t ld, float *X, float *V, float *G, const float *Gc,
+                       const AsyncSlots &slots, const float *w, float alpha, float mu, float wd, float sigma, uint64_t seed,
+                       const float *loss_c, float *loss)
+{
+    if (slots.n <= ASYNC_FEW)
+        launch_rows(s, source, M, D, ld, X, V, G, Gc, AsyncSlotList<ASYNC_FEW>(slots), w, alpha, mu, wd, sigma, seed, loss_c, loss);
+    else
+        launch_rows(s, source, M, D, ld, X, V, G, Gc, slots, w, alpha, mu, wd, sigma, seed, loss_c, loss);
 }
 
 void launch_gather_slots(hipStream_t s, int M, int64_t ld, const AsyncSlots &slots, const float *X, float *Xc, int B, const int64_t *row0,
                          const int32_t *n_rows, uint64_t seed, int64_t *row0_c, int32_t *idx)
 {
     const int n_tiles = (int)(ld / TILE);
-    hipLaunchKernelGGL(gather_slots_kernel, dim3((unsigned)n_tiles + 1, (unsigned)slots.n), dim3(256), 0, s, M, n_tiles, slots, X, Xc, B, row0,
-                       n_rows, seed, row0_c, idx);
+    const dim3 grid((unsigned)n_tiles + 1, (unsigned)slots.n), block(256);
+    if (slots.n <= ASYNC_FEW)
+        hipLaunchKernelGGL((gather_slots_kernel<AsyncSlotList<ASYNC_FEW>>), grid, block, 0, s, M, n_tiles, AsyncSlotList<ASYNC_FEW>(slots), X, Xc, B,
+                           row0, n_rows, seed, row0_c, idx);
+    else
+        hipLaunchKernelGGL((gather_slots_kernel<AsyncSlots>), grid, block, 0, s, M, n_tiles, slots, X, Xc, B, row0, n_rows, seed, row0_c, idx);
 }
 
 }  // namespace netmax

@@ -30,9 +30,17 @@ void launch_synth_grad(hipStream_t s, int M, int64_t D, int64_t ld, float sigma,
 void launch_async_draw(hipStream_t s, int M, const uint32_t *act_thr, int act_last, const uint32_t *thr, const int32_t *last,
                        uint64_t seed, uint64_t first, uint64_t n_steps, int32_t *active, int32_t *peers);
 // A batch of global steps that do not see each other: slot s is step number first + step[s] of worker[s], which pulls from peer[s].
-// Handed to kernels by value.
-constexpr int ASYNC_MAX_BATCH = 32;
-struct AsyncSlots { int n; uint64_t first; int32_t worker[ASYNC_MAX_BATCH], peer[ASYNC_MAX_BATCH]; uint32_t step[ASYNC_MAX_BATCH]; };
+// Handed to kernels by value; batches of few steps as a shorter list (a launch copies its arguments).
+constexpr int ASYNC_MAX_BATCH = 32, ASYNC_FEW = 4;
+template <int N> struct AsyncSlotList {
+    int n; uint64_t first; int32_t worker[N], peer[N]; uint32_t step[N];
+    AsyncSlotList() = default;
+    template <int K> explicit AsyncSlotList(const AsyncSlotList<K> &o) : n(o.n), first(o.first)      // o.n <= N
+    {
+        for (int s = 0; s < o.n; ++s) { worker[s] = o.worker[s]; peer[s] = o.peer[s]; step[s] = o.step[s]; }
+    }
+};
+typedef AsyncSlotList<ASYNC_MAX_BATCH> AsyncSlots;
 // The update of the active workers' rows.  source 0: flat model, gradient generated; 1: read from the active worker's row of G;
 // 2: read from slot s of the compact matrix Gc and copied to the worker's row of G, as loss_c[s] is to loss.
 void launch_async_rows(hipStream_t s, int source, int M, int64_t D, int64_t ld, float *X, float *V, float *G, const float *Gc,

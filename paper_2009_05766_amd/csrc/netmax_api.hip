@@ -984,8 +984,8 @@ extern "C" int netmax_async_run(netmax_ctx *ctx, uint64_t first_step, uint64_t n
             AsyncSlots slots;
             slots.n = planner.start(b + 1) - planner.start(b);
             slots.first = first_step + s0;
-            for (int q = 0; q < ASYNC_MAX_BATCH; ++q) {
-                const int step = planner.order()[planner.start(b) + (q < slots.n ? q : 0)];
+            for (int q = 0; q < slots.n; ++q) {
+                const int step = planner.order()[planner.start(b) + q];
                 slots.worker[q] = active[step];
                 slots.peer[q] = peer[step];
                 slots.step[q] = (uint32_t)step;
