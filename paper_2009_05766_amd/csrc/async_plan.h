@@ -4,7 +4,7 @@
 // than the highest level of an earlier step that wrote a row it reads or read a row it writes; steps of one level do not see
 // each other, and running the levels one after the other gives every step the rows it would have found in step order.  Against
 // cutting the run where the first step sees an earlier one of its group, a level also takes the steps behind that cut that wait
-// for nobody: 64 steps of 16 workers are 18 batches instead of 23.
+// for nobody: 64 steps of 16 workers are 18 batches instead of 23.  `in_order` cuts the run there all the same.
 #pragma once
 #include <algorithm>
 #include <vector>
@@ -16,8 +16,9 @@ public:
     explicit AsyncPlanner(int M) : wrote_(M, 0), read_(M, 0) {}
 
     // active, peer: n steps.  Afterwards order() lists the steps level by level (in step order inside a level), and batch b is
-    // order()[start(b)] .. order()[start(b + 1) - 1]: steps of one level, at most cap of them.
-    void plan(const int *active, const int *peer, int n, int cap)
+    // order()[start(b)] .. order()[start(b + 1) - 1]: steps of one level, at most cap of them.  in_order: consecutive steps, as many
+    // as do not see each other.
+    void plan(const int *active, const int *peer, int n, int cap, bool in_order = false)
     {
         level_.resize(n);
         order_.resize(n);
@@ -25,7 +26,8 @@ public:
         int top = 0;
         for (int s = 0; s < n; ++s) {
             const int i = active[s], m = peer[s];
-            const int l = 1 + std::max(std::max(wrote_[i], wrote_[m]), read_[i]);
+            const int after = std::max(std::max(wrote_[i], wrote_[m]), read_[i]);     // the step has to come behind this level
+            const int l = in_order ? std::max(std::max(top, 1), after + 1) : after + 1;
             wrote_[i] = l;
             read_[m] = std::max(read_[m], l);
             level_[s] = l;

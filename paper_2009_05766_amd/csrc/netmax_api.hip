@@ -925,6 +925,10 @@ static int host_draw(const uint32_t *row, int n, int last, uint32_t u)
 // Global steps planned at a time: long enough that few levels are cut short at its end, short enough that the first launch does
 // not wait for the plan (two Philox blocks and two searches per step).
 constexpr int ASYNC_WINDOW = 512;
+// Flat models beyond this many parameters in all keep the order of the steps: a step finds the rows that the steps before it wrote or
+// read in the Infinity Cache (256 MB), by levels they have left it.  32 steps, by levels and in order: 30 workers x 4 M 585 and 572
+// us, x 9 M 1365 and 1336, 60 x 3 M 452 and 445; 12 x 6 M (72 M) 786 and 786, 30 x 2 M (60 M) 266 and 274.
+constexpr int64_t ASYNC_IN_ORDER_FLOATS = 100'000'000;
 
 // The gradients of the slots' workers into the compact matrix d_gc: their rows are gathered, the grouped kernels run on
 // slots.n groups.
@@ -966,6 +970,7 @@ extern "C" int netmax_async_run(netmax_ctx *ctx, uint64_t first_step, uint64_t n
     // The host repeats the draws (integer work on the same tables) and sorts a window of steps into batches of steps that do
     // not see each other.  A batch is one set of launches.
     const int cap = std::min<int>(c.M, ASYNC_MAX_BATCH);
+    const bool in_order = c.model == NETMAX_FLAT && (int64_t)c.M * c.ld > ASYNC_IN_ORDER_FLOATS;
     AsyncPlanner planner(c.M);
     std::vector<int> active, peer;
     for (uint64_t s0 = 0; s0 < n_steps && rc == NETMAX_OK; s0 += ASYNC_WINDOW) {
@@ -979,7 +984,7 @@ extern "C" int netmax_async_run(netmax_ctx *ctx, uint64_t first_step, uint64_t n
             peer[q] = host_draw(ctx->h_thr.data() + (size_t)i * c.M, c.M, ctx->h_last[i],
                                 draw_block(c.seed, STREAM_PEER, 0u, (uint32_t)i, k).a);
         }
-        planner.plan(active.data(), peer.data(), n, cap);
+        planner.plan(active.data(), peer.data(), n, cap, in_order);
         for (int b = 0; b < planner.batches() && rc == NETMAX_OK; ++b) {
             AsyncSlots slots;
             slots.n = planner.start(b + 1) - planner.start(b);

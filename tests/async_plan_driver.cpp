@@ -21,7 +21,10 @@ int main()
                 peer[s] = rng() % 8 == 0 ? act[s] : (int)(rng() % M);
                 a[act[s]] = a[act[s]] * 3 + a[peer[s]] * 5 + (uint64_t)s;
             }
-            planner.plan(act.data(), peer.data(), n, cap);
+            const bool in_order = (trial + window) % 2 != 0;
+            planner.plan(act.data(), peer.data(), n, cap, in_order);
+            for (int q = 0; in_order && q < n; ++q)
+                if (planner.order()[q] != q) return std::puts("steps out of order"), 1;
             for (int k = 0; k < planner.batches(); ++k) {
                 const int lo = planner.start(k), hi = planner.start(k + 1);
                 if (hi - lo < 1 || hi - lo > cap) return std::printf("a batch of %d\n", hi - lo), 1;

@@ -506,6 +506,38 @@ def test_async_schedule_perceptron(name, over):
     gpu.close()
 
 
+@pytest.mark.parametrize("over", [dict(M=12, n_per_worker=80, dims=(72, 64, 10), batch=64),       # the fp32 kernels of batches of 32 and 64
+                                  dict(M=24, n_per_worker=40, dims=(40, 96, 32, 10), batch=32),
+                                  dict(M=12, n_per_worker=80, dims=(37, 51, 20, 7), batch=21)])   # and tiled ones
+def test_async_schedule_perceptron_of_other_shapes(over):
+    test_async_schedule_perceptron("cfg2", over)
+
+
+def test_async_schedule_flat_in_order():
+    """Large flat models run consecutive steps side by side, smaller ones whichever do not see each other: one call of many steps
+    against one call per step."""
+    import paper_2009_05766_amd as nm
+    w = workload("cfg3", M=64, D=1_600_000, T=4)
+    assert w.M * w.ld > 100_000_000
+    P = np.full((w.M, w.M), 1.0 / (w.M - 1)) * (1.0 - np.eye(w.M))
+    nets = [nm.NetMax(M=w.M, D=w.D, ld=w.ld, model=nm.NETMAX_FLAT, lr=0.1, momentum=0.9, rho=0.01, grad_sigma=0.03, seed=5, P=P) for _ in range(2)]
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    x = torch.randn((w.M, w.D), generator=gen, device="cuda")
+    n = 40
+    active, peers = torch.zeros((2, n), dtype=torch.int32, device="cuda"), torch.zeros((2, n), dtype=torch.int32, device="cuda")
+    for net in nets:
+        net.set("x", x)
+        nm.netmax_set_activity(net.ctx, np.full(w.M, 1.0 / w.M))
+    nm.netmax_async_run(nets[0].ctx, 0, n, active[0], peers[0])
+    for k in range(n):
+        nm.netmax_async_run(nets[1].ctx, k, 1, active[1, k:], peers[1, k:])
+    assert torch.equal(active[0], active[1]) and torch.equal(peers[0], peers[1])
+    for name in ("x_a", "v", "g"):
+        assert torch.equal(getattr(nets[0], name), getattr(nets[1], name))
+    assert not torch.equal(nets[0].get("x", w.D), x)
+    nets[0].close(), nets[1].close()
+
+
 def test_async_schedule_flat_many_workers_in_batches():
     """With many workers most consecutive global steps touch different rows; the library runs such steps as one
     batch of launches.  Same draws, same rows as the oracle's strictly sequential steps, including the steps at which
