@@ -133,7 +133,10 @@ static bool launch_shape(hipStream_t s, const TileDgrad &a)
     return mblk == 1;
 }
 
-// Few workgroups are bound by the chain of steps, not by what a step costs: longer steps, narrower blocks.
+// Few workgroups are bound by the chain of steps, not by what a step costs: longer steps, narrower blocks, until there are about as
+// many of the wider blocks as half the compute units (bfloat16: as all of them).  us per iteration, 128 x 32 and 128 x 64 blocks,
+// number of the latter: fp32 16 x 784-500-300, batch 100 (128) 134.5 and 135.7, 24 x 784-500-300 (192) 188 and 182, 31 x 300-1000-300,
+// batch 128 (496) 261 and 243; bfloat16 32 x 784-500-300 (256) 147.5 and 149, 40 x (320) 180 and 177, 56 x (448) 236 and 230.
 template <bool BF, bool V> static bool launch_rows(hipStream_t s, const TileDgrad &a)
 {
     static_assert(TILE_DGRAD_BATCH == 128, "the rows of the largest block below");
@@ -141,7 +144,7 @@ template <bool BF, bool V> static bool launch_rows(hipStream_t s, const TileDgra
     const int64_t wide = (int64_t)a.M * ((a.din + 63) / 64) * ((a.B + 127) / 128);
     if (a.B <= 32) return launch_shape<BF, V, 32, 64, 64, 1, 2>(s, a);
     if (a.B <= 64) return launch_shape<BF, V, 64, 64, LONG, 2, 2>(s, a);
-    if (wide < 512) return launch_shape<BF, V, 128, 32, 128, 4, 1>(s, a);
+    if (wide <= (BF ? 256 : 128)) return launch_shape<BF, V, 128, 32, 128, 4, 1>(s, a);
     return launch_shape<BF, V, 128, 64, 64, 2, 2>(s, a);
 }
 

@@ -198,3 +198,56 @@ def test_activations_of_the_larger_forms(dtype, M, batch, dims):
         bound = (K + 2) * 2.0**-24 * (np.abs(a) @ np.abs(W) + np.abs(b)) + (2.0**-8 * z if dtype == "bf16" else 0.0)
         assert np.all(np.abs(h[i] - z) <= bound), i
     gpu.close()
+
+
+@pytest.mark.parametrize("dtype,M,batch,dims", [
+    # error kernel: blocks of 128 x 64 and 128 x 32 on either side of the line between them (128 and 256 of the former), weights in
+    # pieces and not, one and two blocks of rows
+    ("f32", 64, 128, (36, 516, 68, 10)), ("f32", 64, 100, (36, 513, 67, 10)), ("f32", 15, 128, (20, 516, 40, 10)), ("f32", 14, 127, (20, 515, 130, 10)),
+    ("f32", 9, 200, (20, 516, 260, 10)),
+    ("bf16", 64, 128, (36, 516, 68, 10)), ("bf16", 64, 100, (36, 513, 67, 10)), ("bf16", 29, 128, (20, 516, 40, 10)), ("bf16", 28, 127, (20, 515, 130, 10)),
+    ("bf16", 16, 200, (20, 516, 260, 10)),
+])
+def test_errors_of_wide_layers(dtype, M, batch, dims):
+    """The gradient of two hidden layers in float64 from the library's own activations: the same ReLU decisions, so what is left is
+    the rounding of the sums (and of bfloat16 errors that lie between two numbers)."""
+    import oracle
+    w = workload("cfg5" if dtype == "bf16" else "cfg2", M=M, batch=batch, n_per_worker=batch + 7, dims=dims)
+    inp = inputs_of(w)
+    off = inp["shard_off"]
+    gpu = make_gpu(w, inp)
+    gpu.local_step(1)
+    h1, h2, G = (t.cpu().numpy() for t in (gpu.hidden(1), gpu.hidden(2), gpu.get("g")))
+    idx = oracle.sample_batch(w.M, w.batch, off, w.seed, 1)
+
+    def operand(x):
+        if dtype == "f32":
+            return np.asarray(x, np.float64)
+        u = np.ascontiguousarray(x, np.float32).view(np.uint32)
+        return (((u + 0x7FFF + ((u >> 16) & 1)) >> 16) << 16).view(np.float32).astype(np.float64)
+    want = np.zeros_like(G, dtype=np.float64)
+    for i in range(M):
+        rows = off[i] + idx[i]
+        a, o, W, b = inp["feats"][rows], 0, [], []
+        a = (a.astype(np.uint32) << 16).view(np.float32).astype(np.float64) if dtype == "bf16" else a.astype(np.float64)
+        for k in range(3):
+            n = dims[k] * dims[k + 1]
+            W.append(operand(inp["X0"][i, o:o + n]).reshape(dims[k], dims[k + 1]))
+            b.append(inp["X0"][i, o + n:o + n + dims[k + 1]].astype(np.float64))
+            o += n + dims[k + 1]
+        acts = [a, h1[i].astype(np.float64), h2[i].astype(np.float64)]
+        z = acts[2] @ W[2] + b[2]
+        e = np.exp(z - z.max(axis=1, keepdims=True))
+        dz = (e / e.sum(axis=1, keepdims=True) - np.eye(dims[3])[inp["labels"][rows]]) / batch
+        parts = []
+        for k in (2, 1, 0):
+            parts = [(acts[k].T @ operand(dz)).ravel(), dz.sum(axis=0)] + parts
+            if k:
+                dz = (operand(dz) @ W[k].T) * (acts[k] > 0)
+        want[i, :o] = np.concatenate(parts)
+    assert np.all(G[:, w.D:] == 0)
+    assert rel_err_rows(G, want) < TOL[dtype]
+    # and each layer's part by itself: the first one, which the error kernel's results make, is a fraction of the whole
+    first = dims[0] * dims[1] + dims[1]
+    assert rel_err_rows(G[:, :first], want[:, :first]) < 3 * TOL[dtype]
+    gpu.close()
