@@ -183,13 +183,17 @@ bias_grad_kernel(int M, int B, int64_t dout, const float *__restrict__ dz, int64
 // 3072-1024-10, batch 128, 32 workers 873 and 716 us, 64 workers 1725 and 1420 us; 784-512-10, 16 workers, batch 128 95 and 89 us,
 // batch 64 71 and 63 us.  The first layer's kernel, if it is the last of the iteration, also updates the columns that no kernel
 // has, which saves the mix's launch: batch 64 63 and 58 us.
-// Models of a few hundred thousand parameters in all have the first layer update and take the other columns as those that are
+// The line lies where x, v, g and the new x no longer fit the 32 MB of L2 together.  Per iteration, update in the first layer only
+// and in every one: 256-256-256-10, batch 64, 11 workers (1.5 M floats) 47.8 and 47.9 us, 15 workers (2.0 M) 57.3 and 48.8 us;
+// 128-wide 100-128-128-128-10, batch 32, 32 workers (1.5 M) 51.2 and 51.5 us, 43 workers (2.1 M) 58.4 and 53.4 us;
+// 300-60-60-60-10, batch 60, 58 workers (1.6 M) 57.5 and 59.4 us, 116 workers (3.1 M) 71.1 and 70.2 us.
+// Smaller models have the first layer update and take the other columns as those that are
 // left, if that does save the launch: 256-256-10, 8 workers, batch 32 27.0 us with the mix and 23.0 us, 784-512-10, 4 workers
 // 45.0 and 39.6 us; every layer for itself lengthens the chain (300-60-60-60-10, 8 workers 64.7 and 66.5 us).
 // Where it loses: rows of W that do not start at multiples of 16 bytes (3001-999-10: 1118 and 1519 us); bfloat16 operands, whose
 // products leave little to hide (784-500-300-10, 16 workers 106 and 113 us, 3000-1000-10, 128 workers 2354 and 2644 us; the
 // matrix-core layers likewise).
-constexpr int64_t UPDATE_MIN_FLOATS = 1 << 21;       // M x ld
+constexpr int64_t UPDATE_MIN_FLOATS = 7 << 18;       // M x ld
 static bool first_layer_last(const MlpPlan &p) { return p.n_layers == 1 || (p.n_layers == 2 && head_ok(p)) || p.B <= TILE_DGRAD_BATCH; }
 
 int64_t update_end(const MlpPlan &p, int l)
