@@ -161,7 +161,8 @@ static void launch_fwd_narrow(hipStream_t s, const FwdProblem &p, int kind, int 
 __global__ void __launch_bounds__(1024) softmax_xent_kernel(SoftmaxArgs a) { softmax_xent_block(a, blockIdx.x); }
 
 // db = column sums of dZ.  One workgroup = one worker x 64 outputs; the batch rows are dealt to four groups of
-// threads (rows r, r + 4, ...), whose partial sums are added in the order of the groups.
+// threads (rows r, r + 4, ...), whose partial sums are added in the order of the groups.  Eight rows of a group are asked for
+// before the first is added (batch 785, 2 workers 12 us; one by one 49 us).
 __global__ void __launch_bounds__(256)
 bias_grad_kernel(int M, int B, int64_t dout, const float *__restrict__ dz, int64_t boff,
                  float *__restrict__ G)
@@ -170,8 +171,10 @@ bias_grad_kernel(int M, int B, int64_t dout, const float *__restrict__ dz, int64
     const int g = blockIdx.y, lane_c = threadIdx.x & 63, rg = threadIdx.x >> 6;
     const int64_t c = (int64_t)blockIdx.x * 64 + lane_c;
     float s = 0.0f;
-    if (c < dout)
+    if (c < dout) {
+#pragma unroll 8
         for (int b = rg; b < B; b += 4) s += dz[((size_t)g * B + b) * dout + c];
+    }
     part[rg][lane_c] = s;
     __syncthreads();
     if (rg == 0 && c < dout) G[tiled_offset(M, g, boff + c)] = ((part[0][lane_c] + part[1][lane_c]) + part[2][lane_c]) + part[3][lane_c];

@@ -32,15 +32,14 @@ struct TileWgrad {
 // Rows of dZ and dW that start at multiples of 16 bytes; rows of at least four elements at any address; anything.  The first two read
 // pieces of four elements, the first one writes them.
 enum : int { TW_ALIGNED = 0, TW_PIECES = 1, TW_SINGLE = 2 };
-constexpr int TW_BM = 64, TW_BK = 64;
-constexpr int tw_threads(int BN) { return 4 * BN; }                   // waves of 32 x 32 blocks
+constexpr int tw_threads(int BM, int BN, int WK) { return BM * BN * WK / 16; }        // waves of 32 x 32 blocks, WK of them share a step's batch rows
 // (Four waves per SIMD; the narrow block with update would spill its pieces of x and v at that.)
-template <bool BF, int MODE, bool UPDATE, int BN>
-__global__ void __launch_bounds__(tw_threads(BN), UPDATE && BN == 64 ? 3 : 4) tile_wgrad_kernel(TileWgrad p)
+template <bool BF, int MODE, bool UPDATE, int BM, int BN, int WK>
+__global__ void __launch_bounds__(tw_threads(BM, BN, WK), UPDATE && BN == 64 ? 3 : 4) tile_wgrad_kernel(TileWgrad p)
 {
     constexpr bool V = MODE != TW_SINGLE, VZ = MODE == TW_ALIGNED;
     static_assert(!UPDATE || VZ, "the update works on 128-bit pieces");
-    constexpr int BM = TW_BM, BK = TW_BK, NT = tw_threads(BN), CW = BN / 32;
+    constexpr int KW = WK > 1 ? 32 : 64, BK = KW * WK, NT = tw_threads(BM, BN, WK), RW = BM / 32, CW = BN / 32;
     constexpr int AR = BM * BK / 4 / NT;                              // batch rows of four features of A per step and thread
     static_assert((AR == 2 || AR == 4) && BN / 4 * (BK / 4) == NT, "half a 4 x 4 block of A or a whole one, and one of dZ");
     typedef TileLds<BF, BK> L;
@@ -51,13 +50,15 @@ __global__ void __launch_bounds__(tw_threads(BN), UPDATE && BN == 64 ? 3 : 4) ti
     elem (*As)[L::PITCH] = reinterpret_cast<elem (*)[L::PITCH]>(smem);
     elem (*Zs)[L::PITCH] = reinterpret_cast<elem (*)[L::PITCH]>(smem + BM * L::PITCH * sizeof(elem));
     float (*T)[TP] = reinterpret_cast<float (*)[TP]>(smem);
-    const int t = threadIdx.x, lane = t & 63, wave = t >> 6, wm = wave / CW, wn = wave % CW;
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6, wm = wave / CW % RW, wn = wave % CW;
+    const int wk = __builtin_amdgcn_readfirstlane(wave / (RW * CW));
     const int nblk = (p.dout + BN - 1) / BN, mblk = (p.din + BM - 1) / BM;
     unsigned bid = tile_block();
     if constexpr (UPDATE) {
         if (bid < p.other_blocks) {
             const unsigned tile = bid / (unsigned)p.M;
-            if (tile < (unsigned)p.n_tiles) mix_subset_block<NT>(p.M, p.tiles[tile], (int)(bid - tile * (unsigned)p.M), p.skip, p.G, p.mix);
+            constexpr int OT = NT < TILE / 4 ? NT : TILE / 4;
+            if (tile < (unsigned)p.n_tiles && t < OT) mix_subset_block<OT>(p.M, p.tiles[tile], (int)(bid - tile * (unsigned)p.M), p.skip, p.G, p.mix);
             return;
         }
         bid -= p.other_blocks;
@@ -175,7 +176,7 @@ __global__ void __launch_bounds__(tw_threads(BN), UPDATE && BN == 64 ? 3 : 4) ti
             }
             __builtin_amdgcn_sched_barrier(0);
         }
-        tile_multiply<BK>(As, Zs, 32 * wm, 32 * wn, lane, acc, K - k0);
+        if (WK == 1 || k0 + KW * wk < K) tile_multiply<KW>(As, Zs, 32 * wm, 32 * wn, lane, acc, K - k0 - KW * wk, KW * wk);
     }
     if constexpr (UPDATE) {
 #pragma unroll
@@ -183,9 +184,18 @@ __global__ void __launch_bounds__(tw_threads(BN), UPDATE && BN == 64 ? 3 : 4) ti
         __builtin_amdgcn_sched_barrier(0);
     }
     __syncthreads();                                                  // the operands' space becomes the staged result
+    if (wk == 0) {
 #pragma unroll
-    for (int v = 0; v < 16; ++v) T[32 * wm + tile_row(lane, v)][32 * wn + (lane & 31)] = acc[0][0][v];
+        for (int v = 0; v < 16; ++v) T[32 * wm + tile_row(lane, v)][32 * wn + (lane & 31)] = acc[0][0][v];
+    }
     __syncthreads();
+    for (int w = 1; w < WK; ++w) {                                    // the other waves' parts, in their order
+        if (wk == w) {
+#pragma unroll
+            for (int v = 0; v < 16; ++v) T[32 * wm + tile_row(lane, v)][32 * wn + (lane & 31)] += acc[0][0][v];
+        }
+        __syncthreads();
+    }
     if (!col_ok) return;
 #pragma unroll
     for (int u = 0; u < PASSES; ++u) {
@@ -208,18 +218,22 @@ __global__ void __launch_bounds__(tw_threads(BN), UPDATE && BN == 64 ? 3 : 4) ti
     }
 }
 
-template <bool BF, int MODE, int BN> static void launch_block(hipStream_t s, TileWgrad &a, bool update)
+template <bool BF, int MODE, int BM, int BN, int WK> static void launch_block(hipStream_t s, TileWgrad &a, bool update)
 {
-    const dim3 grid = tile_grid(a.other_blocks + grouped_grid(a.M, (unsigned)((a.dout + BN - 1) / BN) * (unsigned)((a.din + TW_BM - 1) / TW_BM)));
-    const dim3 block(tw_threads(BN));
+    const dim3 grid = tile_grid(a.other_blocks + grouped_grid(a.M, (unsigned)((a.dout + BN - 1) / BN) * (unsigned)((a.din + BM - 1) / BM)));
+    const dim3 block(tw_threads(BM, BN, WK));
     if constexpr (MODE == TW_ALIGNED && !BF)
         if (update) {
-            hipLaunchKernelGGL((tile_wgrad_kernel<BF, MODE, true, BN>), grid, block, 0, s, a);
+            hipLaunchKernelGGL((tile_wgrad_kernel<BF, MODE, true, BM, BN, WK>), grid, block, 0, s, a);
             return;
         }
-    hipLaunchKernelGGL((tile_wgrad_kernel<BF, MODE, false, BN>), grid, block, 0, s, a);
+    hipLaunchKernelGGL((tile_wgrad_kernel<BF, MODE, false, BM, BN, WK>), grid, block, 0, s, a);
 }
 
+// From a batch of 128 on and with few blocks, 32 x 32 blocks whose batch rows four waves share: four times as many compute units at
+// work.  us per iteration, shared and 64 x 64 blocks, number of the latter: fp32 2 x 784-100 (26), batch 128 30 and 36, batch 785 82
+// and 131; 9 x 784-100 (234) 35 and 37, 122 and 152; 16 x 784-100 (416) 40 and 37.5; bfloat16 2 x 1227-254 (160), batch 128 39.9 and
+// 40.8; 9 x 784-100 34.5 and 33.8.
 // Blocks of 64 columns where they leave less of a narrow layer empty (up to 64 columns, 129 to 192), and on fp32 rows that are not
 // aligned, whose results leave as single floats either way.  us per iteration, 52 workers, with 64 and with 128 columns:
 //   784-64, batch 100 49 and 59, 784-192 92 and 101, 784-150 bfloat16, batch 200 104 and 106; but 784-100, batch 42 57 and 51,
@@ -228,8 +242,10 @@ template <bool BF, int MODE, int BN> static void launch_block(hipStream_t s, Til
 //   227 and 226
 template <bool BF, int MODE> static void launch_cols(hipStream_t s, TileWgrad &a, bool update)
 {
-    if ((a.dout <= 192 && (a.dout + 63) / 64 % 2) || (!BF && MODE != TW_ALIGNED)) launch_block<BF, MODE, 64>(s, a, update);
-    else launch_block<BF, MODE, 128>(s, a, update);
+    const int64_t blocks = (int64_t)a.M * ((a.dout + 63) / 64) * ((a.din + 63) / 64);
+    if (a.B >= 128 && blocks <= (BF ? 160 : 256)) launch_block<BF, MODE, 32, 32, 4>(s, a, update);
+    else if ((a.dout <= 192 && (a.dout + 63) / 64 % 2) || (!BF && MODE != TW_ALIGNED)) launch_block<BF, MODE, 64, 64, 1>(s, a, update);
+    else launch_block<BF, MODE, 64, 128, 1>(s, a, update);
 }
 
 // Rows of dZ and of dW start at multiples of 16 bytes.

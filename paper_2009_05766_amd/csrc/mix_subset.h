@@ -12,6 +12,7 @@ namespace netmax {
 template <int THREADS>
 __device__ __forceinline__ void mix_subset_block(int M, int64_t tile, int i, const MixSkip &skip, const float *G, const MixArgs &mix)
 {
+    static_assert(TILE % (4 * THREADS) == 0, "every thread has the same share of a tile");
     int m = mix.peer[i];
     if ((unsigned)m >= (unsigned)M) m = i;                   // an index outside [0, M) is treated as a self draw
     const float wi = mix.w[(size_t)i * M + m];

@@ -55,6 +55,9 @@ def test_run_is_the_separate_calls(name, M, batch, dims, graph):
     # blocks of 64 columns with the update (one to three of them), data rows of every alignment and of fewer than four features
     ("cfg2", 3, 100, (101, 64, 10)), ("cfg2", 22, 128, (786, 192, 10)), ("cfg2", 5, 40, (3, 36, 10)), ("cfg2", 9, 100, (7, 132, 60, 10)),
     ("cfg2", 40, 90, (787, 148, 60, 10)),
+    # 32 x 32 blocks whose rows four waves share, with the update; strips in two and three even parts on batches of 32 and 64
+    ("cfg2", 4, 128, (131, 96, 10)), ("cfg2", 3, 256, (45, 68, 10)), ("cfg2", 2, 200, (66, 36)),
+    ("cfg2", 3, 32, (70, 320, 10)), ("cfg2", 2, 64, (33, 544, 10)),
 ])
 def test_run_with_narrow_layers(name, M, batch, dims):
     test_run_is_the_separate_calls(name, M, batch, dims, False)

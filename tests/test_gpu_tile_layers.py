@@ -160,7 +160,9 @@ def test_gradient_where_waves_share_the_steps(ora, dtype, M, batch, dims):
     # weight gradients: blocks of 64 and of 128 columns and their remainders, rows aligned or not, one to seven features or outputs,
     # batches around a step of 64
     (63, (65, 64, 10)), (65, (66, 65, 10)), (64, (130, 128, 192, 10)), (40, (5, 129, 193, 10)), (129, (6, 188, 7, 10)), (33, (7, 132, 5, 10)),
-    (17, (2, 60, 3, 40)), (70, (90, 2, 61, 33)), (50, (64, 1, 130, 10)))])
+    (17, (2, 60, 3, 40)), (70, (90, 2, 61, 33)), (50, (64, 1, 130, 10)),
+    # few blocks and batches from 128 on: four waves share the rows of 32 x 32 blocks
+    (128, (31, 33, 10)), (130, (65, 97, 32, 10)), (255, (3, 40, 35, 10)), (161, (200, 2, 30)), (300, (34, 64, 66, 7)), (513, (5, 36, 10)))])
 def test_weight_gradients_of_every_width(ora, dtype, M, batch, dims):
     test_gradient_of_odd_layers(ora, dtype, M, batch, dims)
 
