@@ -170,8 +170,10 @@ int netmax_mix(netmax_ctx *ctx, uint64_t iter, const int32_t *peers_dev);
  * use_graph != 0 an iteration is recorded once per direction of the parameter ping-pong into a HIP graph and
  * replayed (the iteration number then lives in a device cell that the graph advances), which removes the launch
  * overhead that dominates small models; this needs a context created on a non-default stream (the null stream
- * cannot be captured), else NETMAX_ESTATE.  Perceptrons on float operands apply the update to most columns in the kernels that
- * compute their gradient (which is still written to g).  The graphs are dropped when buffers, data or the learning rate change.
+ * cannot be captured), else NETMAX_ESTATE.  Softmax regression that the last-layer kernels take, on either operand type, and
+ * perceptrons on float operands apply the update in the kernels that compute their gradient (which is still written to g): the
+ * latter in every weight matrix whose rows start at multiples of 16 bytes, models of fewer than 1.8 million parameters in all
+ * in the first one only, where that saves a launch, or in none.  The graphs are dropped when buffers, data or the learning rate change.
  * Results are identical to the individual calls.
  * Small softmax-regression models (one layer, float features, at most 32 classes, parameters and batch within a
  * workgroup's LDS) run whole iterations inside ONE kernel, one workgroup per worker: without use_graph all n_iters

@@ -8,8 +8,9 @@
 // 3072 x 1024, batch 128, 32 workers, fp32: 311 us (402 us with 64 x 64 blocks, 4-byte loads and 128-byte row pieces);
 // 784 x 500 and 500 x 300, batch 100, 16 workers, bfloat16: 21 us together (54 us with fp32 instructions).
 //
-// UPDATE (fp32 operands, aligned rows): the block's columns also get the momentum step and the mix (Eq. (c0), (c1)).  460 to 480
-// us at the first shape, 2.46 GB moved, against 311 us and 314 us for the separate mix.  Bound by how well the fp32 matrix
+// UPDATE (fp32 operands, aligned rows): the block's columns also get the momentum step and the mix (Eq. (c0), (c1)).  480 us
+// at the first shape (median of 30 calls in a row; 509 us of the first six), 2.46 GB moved, 5.1 TB/s, against 311 us and 314 us for
+// the separate mix.  Bound by how well the fp32 matrix
 // instructions (180 us) and the memory traffic (390 us at the mix kernel's rate) overlap.  What mattered, per iteration of that
 // network: blocks worker by worker (block by block over the workers, as the mix orders its tiles, fetches 2.0 instead of 1.25 GB:
 // every block's operands again); the blocks of a strip side by side and not one after the other in a workgroup (755 against 880

@@ -1,5 +1,5 @@
-"""netmax_run lets the first layer's weight gradient apply the update to its columns; the separate calls do it with the mix
-kernel.  Parameters, momentum, gradient and losses have to be the same bits, padding included, whichever kernels a shape takes."""
+"""netmax_run lets weight gradients apply the update to their columns (and the first layer's to those that are left); the separate
+calls do it with the mix kernel.  Parameters, momentum, gradient and losses have to be the same bits, padding included, whichever kernels a shape takes."""
 import numpy as np
 import pytest
 import torch
