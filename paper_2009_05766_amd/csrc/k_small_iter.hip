@@ -173,16 +173,19 @@ __global__ void __launch_bounds__(SI_THREADS) small_softmax_iteration_kernel(Arg
     const int row_units = vec_rows ? p.din >> 2 : p.din, feat_units = p.B * row_units;
     const uint32_t magic_row = magic_of(row_units);
 
-    // The batch draw of one iteration: thread b < B draws its own row (word b % 4 of block b / 4 of stream 1), stores
+    // The batch draw of one iteration: thread b draws row b (word b % 4 of block b / 4 of stream 1), stores
     // it and returns the row's label (still in flight).
-    auto draw_batch = [&](int t, uint64_t iter, int buf) -> int32_t {
-        if (t >= p.B) return 0;
-        const Words4 r = draw_block(p.seed, STREAM_BATCH, (uint32_t)t >> 2, (uint32_t)i, iter);
-        const uint32_t word = (t & 3) == 0 ? r.a : ((t & 3) == 1 ? r.b : ((t & 3) == 2 ? r.c : r.d));
+    auto draw_row = [&](int b, uint64_t iter, int buf) -> int32_t {
+        const Words4 r = draw_block(p.seed, STREAM_BATCH, (uint32_t)b >> 2, (uint32_t)i, iter);
+        const uint32_t word = (b & 3) == 0 ? r.a : ((b & 3) == 1 ? r.b : ((b & 3) == 2 ? r.c : r.d));
         const int32_t v = (int32_t)__umulhi(word, n_i);
-        ib[buf * p.B + t] = v;
-        p.idx[(size_t)i * p.B + t] = v;
+        ib[buf * p.B + b] = v;
+        p.idx[(size_t)i * p.B + b] = v;
         return p.labels[r0 + v];
+    };
+    auto draw_batch = [&](int t, uint64_t iter, int buf) -> int32_t {
+        for (int b = t + SI_THREADS; b < p.B; b += SI_THREADS) yl[buf * p.B + b] = draw_row(b, iter, buf);    // batches beyond the threads
+        return t < p.B ? draw_row(t, iter, buf) : 0;
     };
     // The peer draw: the peer is the number of thresholds of the row that are <= u (they do not decrease), clamped
     // to the last positive entry; the threads count their share, the waves add up in LDS.
