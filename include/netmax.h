@@ -177,8 +177,8 @@ int netmax_mix(netmax_ctx *ctx, uint64_t iter, const int32_t *peers_dev);
  * Results are identical to the individual calls.
  * Small softmax-regression models (one layer, float features, at most 32 classes, parameters and batch within a
  * workgroup's LDS) run whole iterations inside ONE kernel, one workgroup per worker: without use_graph all n_iters
- * iterations are one cooperative launch with a device-wide barrier after every iteration (when all M workgroups fit
- * the device at once, else one launch per iteration); with use_graph the replayed graph holds that kernel.  Same
+ * iterations are one launch with a device-wide barrier in every iteration (when all M workgroups fit
+ * the device at once, else one launch per iteration; such launches of several contexts on a device run one after the other); with use_graph the replayed graph holds that kernel.  Same
  * results bit for bit: netmax_local_step runs the same gradient code for such models and every kernel applies the
  * update with the same instructions.  Should a workgroup ever wait at the barrier in vain, the kernel still ends, the
  * parameters are invalid and the next netmax_consensus_dist returns NETMAX_EDEVICE. */
@@ -197,9 +197,9 @@ int netmax_set_fusion(netmax_ctx *ctx, int32_t on);
 
 /* The device-wide barrier of the multi-iteration launches of netmax_run (small models, above) polls a counter; a
  * workgroup that has polled `polls` times without seeing all others arrive raises the context's fault flag and goes
- * on, so that the kernel always ends (default 2^24 polls, seconds; the barrier itself takes microseconds).  This call
- * sets that number and clears the fault flag; it waits for the stream.  polls = 0 makes every workgroup that is not the
- * last to arrive give up at once: the way to exercise the failure path (netmax_consensus_dist then returns
+ * on, and nobody who sees the flag waits again, so that the kernel always ends (default 2^24 polls, seconds; the barrier itself takes
+ * microseconds).  This call sets that number and clears the fault flag; it waits for the stream.  polls = 0 makes every workgroup give
+ * up at once, without a look at the counter: the way to exercise the failure path (netmax_consensus_dist then returns
  * NETMAX_EDEVICE and the parameters are not valid) without making anything wait. */
 int netmax_set_barrier_patience(netmax_ctx *ctx, int64_t polls);
 

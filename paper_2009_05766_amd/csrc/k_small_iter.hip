@@ -2,27 +2,29 @@
 // workgroup per worker draws its peer and its batch, computes logits, loss and gradient with the worker's parameters
 // and batch rows held in LDS, and applies the momentum step and the mix (Eq. (c0), (c1)) against the peer's copy of the
 // previous iteration.  Models of this size are bound by launch latency (six dependent launches of a few microseconds
-// each otherwise); here an iteration is one launch, or, launched cooperatively, one grid barrier inside a launch that
-// runs many iterations.
+// each otherwise); here an iteration is one launch, or one step between two barriers inside a launch that runs many.
 //
 // Three modes share the code, so their results agree bit for bit:
 //   GRAD      batch draw, loss, gradient -> G (netmax_local_step; the mix kernel then applies the same update function)
 //   STEP      peer draw + GRAD + update  -> Xnext, V, G (one iteration per launch; also what a captured graph replays)
-//   the same with n_iters > 1: cooperative launch, all workgroups resident, a barrier after every iteration.
+//   the same with n_iters > 1: all workgroups resident, a split barrier per iteration; G, loss and peers are written by the last one only.
 //
 // Arithmetic: fp32, fixed order.  Forward: eight lanes share a batch row, lane s takes the features k = s, s + 8, ...
 // in increasing order, the eight partial sums are added in halves.  Weight gradient: one thread per four features
 // and four classes, batch rows in increasing order.  Shapes that tile (at most 16 classes, a batch of 16, 32 or 64
-// rows, features a multiple of 256 / (batch / 16)) take both products on v_mfma_f32_16x16x4_f32 instead (exact fp32 products, fp32
+// rows, features a multiple of 128 or, batch 64, of 64) take both products on v_mfma_f32_16x16x4_f32 instead (exact fp32 products, fp32
 // accumulation; lane l supplies A[l % 16][l / 16] and B[l / 16][l % 16] and receives D[4 (l / 16) + v][l % 16]): the
 // vector units are then left with the softmax and the update.
 //
 // The kernel lives on latency, so little is waited for that could have been asked for earlier: the peer's row and
-// the own momentum are requested before the gradient is computed and used after it; the draws of the NEXT iteration
-// depend on (seed, iteration, worker) only, so its labels are requested before the forward pass and its batch rows
-// after the update, and both arrive while this iteration finishes and waits at the barrier; the new parameters
-// stay in LDS, only the peer's row is read again after the barrier.  (Requests are placed where few registers are
-// live: held across the forward pass they starve its inner loop of registers.)
+// the own momentum are requested before the gradient is computed and used after it; draws depend on (seed, iteration, worker) only,
+// so up to sixteen iterations' are made together, and the NEXT iteration's labels and batch rows are requested behind the forward pass;
+// the new parameters stay in LDS, only the peer's row is read again.  A workgroup arrives at the barrier with its new row and looks for
+// the others' arrival after the softmax of the next iteration, where it needs the peer's: half an iteration during which the last
+// ones catch up.  256-10, batch 32, 8 workers, sixteen iterations in a call: 145 us with the barrier between iterations (release
+// and acquire of the whole cache, about 2 us), a draw per iteration, stores between the loads of the update and a cooperative launch
+// (20 us of it), 78 us now; an iteration takes 4.3 us: rows into LDS 0.2, forward 1.0, softmax 0.8, waiting 0.3, gradient 1.2,
+// update 0.7.
 #include "kernels.h"
 #include "layout.h"
 #include "philox.h"
@@ -35,9 +37,11 @@ namespace netmax {
 constexpr int SI_THREADS = 512, SI_WAVES = SI_THREADS / 64;
 constexpr int SI_SPLIT = 8;                 // lanes that share one batch row in the forward pass
 constexpr int SI_MAX_OUT = 32;              // classes
-constexpr int SI_LDS_LIMIT = 150 * 1024;
-constexpr int SI_BURST = 8;                 // loads a thread has in flight while it fills LDS
-constexpr int SI_UPD = 4;                   // vectors of x_peer and v per thread and pass of the update
+constexpr int SI_LDS_LIMIT = 159 * 1024, SI_OPERANDS_LIMIT = 150 * 1024;
+// What a thread has in flight: pieces of the batch rows while it fills LDS, vectors of x_peer and v per pass of the update.  The
+// matrix-instruction form has a variant of half as many for models that they cover: requests that nobody needs cost their instructions.
+constexpr int SI_BURST = 8, SI_UPD = 4;
+static bool small_iter_few(int B, int64_t din, int64_t ld) { return B * din <= (int64_t)SI_BURST / 2 * SI_THREADS * 4 && ld <= (int64_t)SI_UPD / 2 * SI_THREADS * 4; }
 
 struct SmallIterArgs {
     int M, B, din, dout;
@@ -50,7 +54,7 @@ struct SmallIterArgs {
     float alpha, mu, wd;
     uint64_t seed;
     IterRef iter;                           // number of the first iteration
-    int n_iters, grad_only;
+    int n_iters;
     unsigned *barrier; unsigned barrier_base; int *fault;
     long long patience;                     // polls of the barrier counter before a workgroup gives up
 };
@@ -58,60 +62,90 @@ struct SmallIterArgs {
 // would cost them 0.4 us each.)
 struct SmallSlotArgs : SmallIterArgs { AsyncSlots slots; };
 
-// The matrix-instruction form of the two products: classes padded to one 16-wide tile, 16-row tiles of the batch, the
-// the waves split the features of the forward pass evenly in groups of 64 (no bounds test in any loop).
+// The matrix-instruction form of the two products: classes padded to one 16-wide tile, 16-row tiles of the batch, up to two of them per
+// wave; the waves split the features of the forward pass evenly in groups of 16 (no bounds test in any loop).
+constexpr int si_row_tiles(int RT) { return RT < 2 ? 1 : 2; }                       // a wave's
+constexpr int si_parts(int RT) { return SI_WAVES * si_row_tiles(RT) / RT; }         // of the features
 static bool small_iter_mm(int B, int64_t din, int64_t dout)
 {
-    return dout <= 16 && (B == 16 || B == 32 || B == 64) && din % (64 * SI_WAVES / (B / 16)) == 0;     // every wave's part: whole groups of 64 features
+    return dout <= 16 && (B == 16 || B == 32 || B == 64) && din % (16 * si_parts(B / 16)) == 0;
 }
 static int small_iter_cap(int B, int64_t din, int64_t dout)
 {
     if (small_iter_mm(B, din, dout)) return 16;
     return dout <= 8 ? 8 : (dout <= 16 ? 16 : SI_MAX_OUT);
 }
-constexpr int SI_MM_PAD = 4;                // floats behind a batch row in that form: sixteen rows read together meet all banks
-constexpr int SI_MM_PART = SI_WAVES * 16 * 16;   // floats of partial logits: one 16 x 16 tile per wave
+constexpr int SI_MM_PAD = 20;               // floats behind a batch row in that form: sixteen rows read together meet all banks, and four neighbouring
+                                            // rows of sixteen features nearly so
+constexpr int si_mm_part(int RT) { return si_parts(RT) * RT * 16 * 16; }            // floats of partial logits
+
+// Iterations drawn together: a Philox block takes 0.45 us from its first multiplication to its last, whatever the number of lanes that
+// work on one.  At most 4 KB of row numbers.
+constexpr int SI_AHEAD = 16;
+static __device__ __host__ __forceinline__ int si_ahead(int B) { return B >= 1024 ? 1 : (1024 / B < SI_AHEAD ? 1024 / B : SI_AHEAD); }
 
 static size_t small_iter_lds(int B, int din, int dout, int64_t ld)
 {
     const bool mm = small_iter_mm(B, din, dout);
     const size_t pitch = (size_t)din + (mm ? SI_MM_PAD : SI_SPLIT), cap = (size_t)small_iter_cap(B, din, dout);
-    return (2 * (size_t)ld + ((size_t)din + 1) * (cap + 4) + (size_t)B * pitch + (size_t)B * cap + (size_t)B + (mm ? SI_MM_PART : 0)) * sizeof(float) +
-           (4 * (size_t)B + 2) * sizeof(int32_t);
+    const size_t w = mm ? (size_t)si_mm_part(B / 16) : ((size_t)din + 1) * (cap + 4);
+    return (2 * (size_t)ld + w + (size_t)B * pitch + (size_t)B * cap + (size_t)B) * sizeof(float) +
+           ((size_t)si_ahead(B) * B + 2 * (size_t)B + 2 * SI_AHEAD * SI_WAVES) * sizeof(int32_t);
 }
 
-// All workgroups of the grid have arrived (and their stores are visible to each other) when this returns true.  A
-// workgroup that polls `patience` times without seeing the others raises *fault and goes on, so the kernel always ends.
-__device__ __forceinline__ void grid_barrier(unsigned *counter, unsigned target, int *fault, long long patience)
+// The line up to which a worker's iterations are taken into one workgroup: parameters, gradient, padded weights and the batch.
+static size_t small_iter_operands(int B, int din, int dout, int64_t ld)
 {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");        // this wave's stores, device wide
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        long long polls = 0;
-        while ((int)(__hip_atomic_load(counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - target) < 0) {
-            if (++polls > patience) {
-                *fault = 1;
-                break;
-            }
-            __builtin_amdgcn_s_sleep(4);
-        }
+    const size_t cap = (size_t)small_iter_cap(B, din, dout);
+    return (2 * (size_t)ld + ((size_t)din + 1) * (cap + 4) + (size_t)B * (din + SI_SPLIT + cap + 5) + 2) * sizeof(float);
+}
+
+// The device-wide barrier is split: a workgroup arrives when its new parameters are in memory and looks for the others' arrival
+// only where it needs their rows, half an iteration later.  What the workgroups exchange (the parameter rows, and only they) is
+// stored and loaded at device scope, past the caches of one XCD, so no cache is written back or dropped: a wave's stores have
+// arrived when its vmcnt is zero.
+__device__ __forceinline__ void store4_device(float *p, f32x4 v)
+{
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    unsigned long long *q = reinterpret_cast<unsigned long long *>(p);
+    __hip_atomic_store(q, __builtin_bit_cast(unsigned long long, f32x2{v[0], v[1]}), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(q + 1, __builtin_bit_cast(unsigned long long, f32x2{v[2], v[3]}), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ f32x4 load4_device(const float *p)
+{
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    const unsigned long long *q = reinterpret_cast<const unsigned long long *>(p);
+    const f32x2 a = __builtin_bit_cast(f32x2, __hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    const f32x2 b = __builtin_bit_cast(f32x2, __hip_atomic_load(q + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    return f32x4{a[0], a[1], b[0], b[1]};
+}
+__device__ __forceinline__ void stores_arrived() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+__device__ __forceinline__ unsigned arrivals(unsigned *counter) { return __hip_atomic_load(counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+// Waits until the counter has reached `target`; `seen`: what it was a moment ago.  A workgroup that polls `patience` times in vain raises
+// *fault; it and all that see the flag wait for nothing any more, so the kernel always ends.
+__device__ __forceinline__ void await_arrivals(unsigned *counter, unsigned seen, unsigned target, int *fault, long long patience)
+{
+    long long polls = 0;
+    while (patience == 0 || (int)(seen - target) < 0) {
+        if (++polls > patience) __hip_atomic_store(fault, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (__hip_atomic_load(fault, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) break;
+        __builtin_amdgcn_s_sleep(1);
+        seen = arrivals(counter);
     }
-    __syncthreads();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");        // drop what this compute unit cached of the others' rows
 }
 
 // j / d for 0 <= j < 2^32 / d, with magic = ceil(2^32 / d).
 __device__ __forceinline__ int div_magic(int j, uint32_t magic) { return (int)__umulhi((uint32_t)j, magic); }
 static __device__ __host__ __forceinline__ uint32_t magic_of(int d) { return (uint32_t)((0x100000000ull + (uint32_t)d - 1) / (uint32_t)d); }
 
-// The value that lane (l ^ MASK) holds, MASK in {1, 2, 4}, by data-parallel-primitive moves inside the vector unit
+// The value that lane (l ^ MASK) holds, MASK in {1, 2, 4, 8}, by data-parallel-primitive moves inside the vector unit
 // (no trip through the LDS crossbar as a general lane shuffle takes): quad permutations [1,0,3,2] and [2,3,0,1] for
-// 1 and 2; for 4 the mirror of each group of eight lanes (l -> l ^ 7) followed by the reversal of each quad (^ 3).
+// 1 and 2; for 4 the mirror of each group of eight lanes (l -> l ^ 7) followed by the reversal of each quad (^ 3); for 8 the rotation of
+// each group of sixteen by eight.
 template <int MASK>
 __device__ __forceinline__ float xor_lane(float v)
 {
-    static_assert(MASK == 1 || MASK == 2 || MASK == 4, "lane distances inside a group of eight");
+    static_assert(MASK == 1 || MASK == 2 || MASK == 4 || MASK == 8, "lane distances inside a group of sixteen");
     int x = __float_as_int(v);
     if (MASK == 1) x = __builtin_amdgcn_update_dpp(x, x, 0xB1, 0xF, 0xF, false);
     if (MASK == 2) x = __builtin_amdgcn_update_dpp(x, x, 0x4E, 0xF, 0xF, false);
@@ -119,6 +153,7 @@ __device__ __forceinline__ float xor_lane(float v)
         x = __builtin_amdgcn_update_dpp(x, x, 0x141, 0xF, 0xF, false);
         x = __builtin_amdgcn_update_dpp(x, x, 0x1B, 0xF, 0xF, false);
     }
+    if (MASK == 8) x = __builtin_amdgcn_update_dpp(x, x, 0x128, 0xF, 0xF, false);
     return __int_as_float(x);
 }
 
@@ -132,11 +167,14 @@ __device__ __forceinline__ int opaque(int v)
 
 // CAP: classes the unrolled loops cover: dout <= CAP, CAP in {8, 16, 32}.  RT > 0: the two products on matrix
 // instructions, RT = batch / 16 tiles of batch rows (CAP = 16, shapes accepted by small_iter_mm()).
-template <int CAP, int RT = 0, class Args = SmallIterArgs>
+// STEP: whole iterations, else batch draw, loss and gradient of a single one.
+template <int CAP, int RT, bool STEP, bool FEW, class Args = SmallIterArgs>
 __global__ void __launch_bounds__(SI_THREADS) small_softmax_iteration_kernel(Args p)
 {
     constexpr bool SLOTS = !std::is_same<Args, SmallIterArgs>::value;
+    static_assert(!SLOTS || !STEP, "listed workers: the gradient only");
     constexpr bool MM = RT > 0;
+    constexpr int BURST = FEW ? SI_BURST / 2 : SI_BURST, UPD = FEW ? SI_UPD / 2 : SI_UPD;
     static_assert(!MM || CAP == 16, "the matrix-instruction form pads the classes to one 16-wide tile");
     extern __shared__ __attribute__((aligned(16))) unsigned char si_smem[];
     constexpr int SI_DEPTH = CAP <= 16 ? 4 : 2;               // steps of an inner product whose LDS reads are in flight together
@@ -144,6 +182,8 @@ __global__ void __launch_bounds__(SI_THREADS) small_softmax_iteration_kernel(Arg
     constexpr int WP = CAP + 4;                               // floats per padded row of W: the eight rows a wave reads
                                                               // together then lie in different LDS banks
     const int t0 = threadIdx.x;
+    // the variant for few vectors has the registers for what it would compute anew in every iteration
+    auto hidden = [](int v) { return FEW ? v : opaque(v); };
     int i = (int)blockIdx.x;
     if constexpr (SLOTS) i = p.slots.worker[blockIdx.x];
     const int pitch = p.din + (MM ? SI_MM_PAD : SI_SPLIT);
@@ -151,13 +191,14 @@ __global__ void __launch_bounds__(SI_THREADS) small_softmax_iteration_kernel(Arg
     float *gl = xl + p.ld;                                    // [ld]  its gradient
     float *wp = gl + p.ld;                                    // [din + 1][WP] W and then b with rows padded by zeros to
                                                               //       CAP classes: the inner loops run without a bounds test
-    float *dz = wp + ((size_t)p.din + 1) * WP;                // [B][CAP], zeros beyond dout (16-byte aligned rows)
+    float *dz = MM ? wp : wp + ((size_t)p.din + 1) * WP;      // [B][CAP], zeros beyond dout (16-byte aligned rows); MM reads W where it lies
     float *xs = dz + (size_t)p.B * CAP;                       // [B][pitch] batch rows
     float *lb = xs + (size_t)p.B * pitch;                     // [B] per-row loss
     float *part = lb + p.B;                                   // MM: [parts of the features][B][16] partial logits
-    int32_t *ib = reinterpret_cast<int32_t *>(part + (MM ? SI_MM_PART : 0));   // [2][B] batch rows (shard-local) of this and the next iteration
-    int32_t *yl = ib + 2 * p.B;                               // [2][B] their labels
-    int32_t *cnt = yl + 2 * p.B;                              // [2] thresholds of the peer draw that are <= u
+    const int ahead = si_ahead(p.B);
+    int32_t *ib = reinterpret_cast<int32_t *>(part + (MM ? si_mm_part(RT) : 0));   // [ahead][B] batch rows (shard-local) of the iterations drawn together
+    int32_t *yl = ib + ahead * p.B;                           // [2][B] labels of this and the next iteration
+    int32_t *cnt = yl + 2 * p.B;                              // [2][SI_AHEAD][waves] thresholds of the peer draws that are <= u, two groups of draws
     uint64_t iter0;
     if constexpr (SLOTS) iter0 = p.slots.first + p.slots.step[blockIdx.x];
     else iter0 = iteration_of(p.iter);
@@ -165,61 +206,68 @@ __global__ void __launch_bounds__(SI_THREADS) small_softmax_iteration_kernel(Arg
     const float invB = 1.0f / (float)p.B;
     const uint32_t n_i = (uint32_t)p.n_rows[i];
     const int64_t r0 = p.row0[i];
-    const int last_i = p.grad_only ? 0 : p.last[i];
+    const int last_i = STEP ? p.last[i] : 0;
     const float *shard = p.feats + (size_t)r0 * p.din;
     const uint32_t *thr_row = p.thr + (size_t)i * p.M;
     const uint32_t magic_out = magic_of(p.dout);
-    const bool vec_rows = (p.din & 3) == 0;                   // batch rows as 128-bit pieces, else element by element
+    const bool vec_rows = MM || (p.din & 3) == 0;             // batch rows as 128-bit pieces, else element by element
     const int row_units = vec_rows ? p.din >> 2 : p.din, feat_units = p.B * row_units;
     const uint32_t magic_row = magic_of(row_units);
 
-    // The batch draw of one iteration: thread b draws row b (word b % 4 of block b / 4 of stream 1), stores
-    // it and returns the row's label (still in flight).
-    auto draw_row = [&](int b, uint64_t iter, int buf) -> int32_t {
-        const Words4 r = draw_block(p.seed, STREAM_BATCH, (uint32_t)b >> 2, (uint32_t)i, iter);
-        const uint32_t word = (b & 3) == 0 ? r.a : ((b & 3) == 1 ? r.b : ((b & 3) == 2 ? r.c : r.d));
-        const int32_t v = (int32_t)__umulhi(word, n_i);
-        ib[buf * p.B + b] = v;
-        p.idx[(size_t)i * p.B + b] = v;
-        return p.labels[r0 + v];
-    };
-    auto draw_batch = [&](int t, uint64_t iter, int buf) -> int32_t {
-        for (int b = t + SI_THREADS; b < p.B; b += SI_THREADS) yl[buf * p.B + b] = draw_row(b, iter, buf);    // batches beyond the threads
-        return t < p.B ? draw_row(t, iter, buf) : 0;
-    };
-    // The peer draw: the peer is the number of thresholds of the row that are <= u (they do not decrease), clamped
-    // to the last positive entry; the threads count their share, the waves add up in LDS.
-    auto count_hits = [&](int t, int q, uint32_t threshold, uint32_t u, int buf) {
-        const unsigned long long hit = __ballot(q < p.M && threshold <= u);
-        if ((t & 63) == 0 && hit) atomicAdd(&cnt[buf], (int)__popcll(hit));
-    };
-    auto count_thresholds = [&](int t, uint64_t iter, int buf, uint32_t first) {   // first: thr_row[t], read earlier
-        const uint32_t u = draw_block(p.seed, STREAM_PEER, 0u, (uint32_t)i, iter).a;
-        count_hits(t, t, first, u, buf);
-        for (int q0 = SI_THREADS; q0 < p.M; q0 += SI_THREADS) {
-            const int q = q0 + t;
-            count_hits(t, q, thr_row[q < p.M ? q : 0], u, buf);
+    // The draws of the iterations it0 .. of a group: batch row b is word b % 4 of block b / 4 of stream 1; the peer is the number of
+    // thresholds of the worker's row that are <= u (they do not decrease), clamped to the last positive entry: every wave counts its
+    // share for all iterations of the group.
+    auto draw_group = [&](int t, int it0, int group, uint32_t first) {    // first: thr_row[t], read earlier
+        const int n = p.n_iters - it0 < ahead ? p.n_iters - it0 : ahead, blocks = (p.B + 3) >> 2;
+        for (int e = SI_THREADS - 1 - t; e < n * blocks; e += SI_THREADS) {      // from the last wave down: the first ones count
+            const int k = e / blocks, q = e - k * blocks;
+            const Words4 r = draw_block(p.seed, STREAM_BATCH, (uint32_t)q, (uint32_t)i, iter0 + (uint64_t)(it0 + k));
+            const uint32_t word[4] = {r.a, r.b, r.c, r.d};
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                if (4 * q + c < p.B) ib[k * p.B + 4 * q + c] = (int32_t)__umulhi(word[c], n_i);
+        }
+        if (!STEP || (t & ~63) >= p.M) return;
+        const int lane = t & 63;
+        const uint32_t us = draw_block(p.seed, STREAM_PEER, 0u, (uint32_t)i, iter0 + (uint64_t)(it0 + (lane < n ? lane : 0))).a;
+        int32_t *to = cnt + group * (SI_AHEAD * SI_WAVES) + (t >> 6);
+        for (int k = 0; k < n; ++k) {
+            const uint32_t u = (uint32_t)__builtin_amdgcn_readlane((int)us, k);
+            int hits = (int)__popcll(__ballot(t < p.M && first <= u));
+            for (int q0 = SI_THREADS; q0 < p.M; q0 += SI_THREADS) {
+                const int q = q0 + t;
+                hits += (int)__popcll(__ballot(q < p.M && thr_row[q < p.M ? q : 0] <= u));
+            }
+            if (lane == 0) to[k * SI_WAVES] = hits;
         }
     };
-    // Requests the first SI_BURST pieces per thread of the batch rows listed in ib[buf].
-    auto request_rows = [&](int t, int buf, f32x4 (&r)[SI_BURST]) {
+    // Requests the first BURST pieces per thread of the listed batch rows.
+    auto request_rows = [&](int t, const int32_t *rows, f32x4 (&r)[BURST]) {
+        const float *src[BURST];
 #pragma unroll
-        for (int e = 0; e < SI_BURST; ++e) {
+        for (int e = 0; e < BURST; ++e) {
             const int q = e * SI_THREADS + t, qc = q < feat_units ? q : 0;     // unconditional, see the update's requests
             const int b = div_magic(qc, magic_row), c = qc - b * row_units;
-            const float *src = shard + (size_t)ib[buf * p.B + b] * p.din;
-            if (vec_rows) r[e] = load4(src + 4 * c); else r[e][0] = src[c];
+            src[e] = shard + (size_t)rows[b] * p.din + (vec_rows ? 4 * c : c);
+        }
+        if (vec_rows) {                                       // one branch around all requests: one in each would make them wait for each other
+#pragma unroll
+            for (int e = 0; e < BURST; ++e) r[e] = load4(src[e]);
+        } else {
+#pragma unroll
+            for (int e = 0; e < BURST; ++e) r[e] = f32x4{src[e][0], 0.0f, 0.0f, 0.0f};
         }
     };
     auto store_piece = [&](int q, const f32x4 &v) {
         const int b = div_magic(q, magic_row), c = q - b * row_units;
         float *dst = xs + (size_t)b * pitch;
-        if (vec_rows) { dst[4 * c] = v[0]; dst[4 * c + 1] = v[1]; dst[4 * c + 2] = v[2]; dst[4 * c + 3] = v[3]; }
+        if (vec_rows) *reinterpret_cast<f32x4 *>(dst + 4 * c) = v;
         else dst[c] = v[0];
     };
     // Four neighbouring parameters into LDS: the flat copy and the padded rows.
     auto keep_params = [&](int q, const f32x4 &v) {
         *reinterpret_cast<f32x4 *>(xl + (size_t)q * 4) = v;
+        if constexpr (MM) return;                             // reads W where it lies
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
             const int j = q * 4 + c;
@@ -232,97 +280,129 @@ __global__ void __launch_bounds__(SI_THREADS) small_softmax_iteration_kernel(Arg
 
     // ---- before the first iteration: parameters, draws and batch rows, all requested before any is waited for
     const int t = t0;
-    f32x4 rf[SI_BURST], rpar[SI_BURST];
+    f32x4 rf[BURST], rpar[BURST];
 #pragma unroll
-    for (int e = 0; e < SI_BURST; ++e) {
+    for (int e = 0; e < BURST; ++e) {
         const int q = e * SI_THREADS + t;
         rpar[e] = load4(p.x_first + tiled_offset(p.M, i, (int64_t)(q < n_vec ? q : 0) * 4));
     }
-    if (t < 2) cnt[t] = 0;
-    int32_t label = draw_batch(t, iter0, 0);
+    const uint32_t thr_own = STEP ? thr_row[t0 < p.M ? t0 : 0] : 0u;      // the row does not change during a launch
+    draw_group(t, 0, 0, thr_own);
     __syncthreads();
-    const uint32_t thr_own = p.grad_only ? 0u : thr_row[t0 < p.M ? t0 : 0];      // the row does not change during a launch
-    if (!p.grad_only) count_thresholds(t, iter0, 0, thr_own);
-    request_rows(t, 0, rf);
+    const int t_row = t0 < p.B ? t0 : p.B - 1;
+    int32_t label = p.labels[r0 + ib[t_row]];
+    request_rows(t, ib, rf);
 #pragma unroll
-    for (int e = 0; e < SI_BURST; ++e) {
+    for (int e = 0; e < BURST; ++e) {
         const int q = e * SI_THREADS + t;
         if (q < n_vec) keep_params(q, rpar[e]);
     }
-    for (int q = SI_BURST * SI_THREADS + t; q < n_vec; q += SI_THREADS)
+    for (int q = BURST * SI_THREADS + t; q < n_vec; q += SI_THREADS)
         keep_params(q, load4(p.x_first + tiled_offset(p.M, i, (int64_t)q * 4)));
-    for (int q = t; q < (p.din + 1) * (CAP - p.dout); q += SI_THREADS) {       // the padding of every row
+    for (int q = t; !MM && q < (p.din + 1) * (CAP - p.dout); q += SI_THREADS) {       // the padding of every row
         const int k = q / (CAP - p.dout);
         wp[(size_t)k * WP + p.dout + (q - k * (CAP - p.dout))] = 0.0f;
     }
     if (t < p.B) yl[t] = label;
+    for (int b = SI_THREADS + t; b < p.B; b += SI_THREADS) yl[b] = p.labels[r0 + ib[b]];       // batches beyond the threads
     for (int64_t j = p.D + t; j < p.ld; j += SI_THREADS) gl[j] = 0.0f;     // the padding behind the gradient: written here only
 
-    for (int it = 0; it < p.n_iters; ++it) {
-        const uint64_t iter = iter0 + (uint64_t)it;
+    uint32_t own_at[UPD];                                     // this thread's vectors of the first pass (beyond the end: the first vector, never used)
+#pragma unroll
+    for (int e = 0; e < UPD; ++e) {
+        const int q = e * SI_THREADS + t0;
+        own_at[e] = (uint32_t)tiled_offset(p.M, i, (int64_t)(q < n_vec ? q : 0) * 4);
+    }
+    const int n_iters = STEP ? p.n_iters : 1;
+    int at = 0, group = 0;                                    // the iteration's place in its group of draws, the group's parity
+    for (int it = 0; it < n_iters; ++it) {
         const int cur = it & 1, nxt = cur ^ 1;
-        const bool more = it + 1 < p.n_iters;
-        const int t = opaque(t0);
+        const bool more = STEP && it + 1 < n_iters;
+        const int t = hidden(t0);
         float *Xcur = cur ? p.x_second : p.x_first;
         float *Xnext = cur ? p.x_first : p.x_second;
         // ---- this iteration's batch rows into LDS (the first pieces were requested an iteration ago)
 #pragma unroll
-        for (int e = 0; e < SI_BURST; ++e) {
+        for (int e = 0; e < BURST; ++e) {
             const int q = e * SI_THREADS + t;
             if (q < feat_units) store_piece(q, rf[e]);
         }
-        for (int q = SI_BURST * SI_THREADS + t; q < feat_units; q += SI_THREADS) {
+        for (int q = BURST * SI_THREADS + t; q < feat_units; q += SI_THREADS) {
             const int b = div_magic(q, magic_row), c = q - b * row_units;
-            const float *src = shard + (size_t)ib[cur * p.B + b] * p.din;
+            const float *src = shard + (size_t)ib[at * p.B + b] * p.din;
             f32x4 v;
             if (vec_rows) v = load4(src + 4 * c); else v[0] = src[c];
             store_piece(q, v);
         }
-
+        if (STEP && it > 0) stores_arrived();                 // this wave's new parameters, on their way since the update
         __syncthreads();
+        if (STEP && it > 0 && t == 0) __hip_atomic_fetch_add(p.barrier, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         // ---- the peer
         int m = i;
-        if (!p.grad_only) {
-            const int c = cnt[cur];
-            m = c < last_i ? c : last_i;
-            if (t == 0) p.peers[i] = m;
+        if constexpr (STEP) {
+            const int32_t *counts = cnt + group * (SI_AHEAD * SI_WAVES) + at * SI_WAVES;
+            int c = counts[0];
+            for (int w = 1; w < SI_WAVES && 64 * w < p.M; ++w) c += counts[w];
+            m = __builtin_amdgcn_readfirstlane(c < last_i ? c : last_i);
+            if (t == 0 && !more) p.peers[i] = m;
         }
-        // the next iteration's batch draw (its labels travel while this iteration computes)
-        if (more) {
-            if (t == 0) cnt[nxt] = 0;
-            label = draw_batch(t, iter + 1, nxt);
-        }
+        // the group of draws that the next iteration begins: the rows of this one are in LDS
+        const bool fresh = more && at + 1 == ahead;
+        const int next_at = fresh ? 0 : more ? at + 1 : at;   // the last iteration asks for its own rows again: no load under a branch
+        const int32_t *next_rows = ib + next_at * p.B;
+        if (fresh) draw_group(t, it + 1, group ^ 1, thr_own);
+        unsigned seen;
+        // the count of arrivals and the next iteration's labels and batch rows, on their way while this iteration goes on (in this order:
+        // a wave's loads are waited for in the order of their requests)
+        auto request_ahead = [&]() {
+            seen = arrivals(p.barrier);
+            label = p.labels[r0 + next_rows[t_row]];
+            request_rows(t, next_rows, rf);
+        };
         if constexpr (MM) {
-            // ---- forward on matrix instructions: wave = (16-row tile of the batch, part of the features); four steps
-            // of sixteen features are read from LDS together, then multiplied
-            const int t = opaque(t0);
+            // ---- forward on matrix instructions: wave = (up to two 16-row tiles of the batch, part of the features); two steps of sixteen
+            // features are read from LDS together, then multiplied
+            const int t = hidden(t0);
             const int lane = t & 63, wave = t >> 6, r = lane & 15, q = lane >> 4;
-            constexpr int BT = MM ? RT : 1, KP = SI_WAVES / BT;
-            const int KW = p.din / KP, rt = wave % BT, kp = wave / BT;
-            const float *xrow = xs + (size_t)(16 * rt + r) * pitch + kp * KW + 4 * q;
-            const float *wcol = wp + (size_t)(kp * KW + 4 * q) * WP + r;
-            f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
-            for (int k0 = 0; k0 < KW; k0 += 64) {
-                f32x4 a[4];
-                float b[4][4];
+            constexpr int TILES = si_row_tiles(MM ? RT : 1), KP = si_parts(MM ? RT : 1), DEPTH = 2;
+            const int KW = p.din / KP, kp = wave % KP, row0 = wave / KP * (16 * TILES);
+            const float *xrow = xs + (size_t)(row0 + r) * pitch + kp * KW + 4 * q;
+            // classes past the last one multiply what follows in the row (in LDS, finite or not): their columns are never looked at
+            const float *wcol = xl + (size_t)(kp * KW + 4 * q) * p.dout + r;
+            f32x4 acc[TILES];
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    a[u] = *reinterpret_cast<const f32x4 *>(xrow + k0 + 16 * u);
+            for (int rt = 0; rt < TILES; ++rt) acc[rt] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+            auto steps = [&](int k0, auto n) {                // n steps of sixteen features: all reads, then all products
+                constexpr int N = decltype(n)::value;
+                f32x4 a[N][TILES];
+                float b[N][4];
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) b[u][j] = wcol[(size_t)(k0 + 16 * u + j) * WP];
+                for (int u = 0; u < N; ++u) {
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) b[u][j] = wcol[(k0 + 16 * u + j) * p.dout];
+#pragma unroll
+                    for (int rt = 0; rt < TILES; ++rt) a[u][rt] = *reinterpret_cast<const f32x4 *>(xrow + 16 * rt * pitch + k0 + 16 * u);
                 }
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int u = 0; u < 4; ++u)
+                for (int u = 0; u < N; ++u)
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u][j], b[u][j], acc, 0, 0, 0);
+                    for (int j = 0; j < 4; ++j)
+#pragma unroll
+                        for (int rt = 0; rt < TILES; ++rt) acc[rt] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u][rt][j], b[u][j], acc[rt], 0, 0, 0);
                 __builtin_amdgcn_sched_barrier(0);
-            }
+            };
+            int k0 = 0;
+            for (; k0 + 16 * DEPTH <= KW; k0 += 16 * DEPTH) steps(k0, std::integral_constant<int, DEPTH>{});
+            for (; k0 < KW; k0 += 16) steps(k0, std::integral_constant<int, 1>{});
 #pragma unroll
-            for (int v = 0; v < 4; ++v) part[(size_t)(kp * p.B + 16 * rt + 4 * q + v) * 16 + r] = acc[v];
+            for (int rt = 0; rt < TILES; ++rt)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) part[(size_t)(kp * p.B + row0 + 16 * rt + 4 * q + v) * 16 + r] = acc[rt][v];
             __syncthreads();
+            if constexpr (STEP) request_ahead();
             // ---- the parts added in order, bias, softmax, loss, dZ: sixteen lanes per batch row, one class each
-            const float *bias = wp + (size_t)p.din * WP;
+            const float *bias = xl + (size_t)p.din * p.dout;
             for (int e = t; e < p.B * 16; e += SI_THREADS) {
                 const int b = e >> 4, c = e & 15;
                 float z = part[(size_t)b * 16 + c];
@@ -334,22 +414,22 @@ __global__ void __launch_bounds__(SI_THREADS) small_softmax_iteration_kernel(Arg
                 mx = fmaxf(mx, xor_lane<1>(mx));
                 mx = fmaxf(mx, xor_lane<2>(mx));
                 mx = fmaxf(mx, xor_lane<4>(mx));
-                mx = fmaxf(mx, __shfl_xor(mx, 8, 16));
+                mx = fmaxf(mx, xor_lane<8>(mx));
                 const float ex = real ? expf(z - mx) : 0.0f;
                 float sum = ex;
                 sum += xor_lane<1>(sum);
                 sum += xor_lane<2>(sum);
                 sum += xor_lane<4>(sum);
-                sum += __shfl_xor(sum, 8, 16);
+                sum += xor_lane<8>(sum);
                 const int y = yl[cur * p.B + b];
                 dz[(size_t)b * CAP + c] = real ? (ex * (1.0f / sum) - (c == y ? 1.0f : 0.0f)) * invB : 0.0f;
-                if (c == y) lb[b] = logf(sum) - (z - mx);
+                if (c == y && !more) lb[b] = logf(sum) - (z - mx);
             }
         } else {
         // ---- forward, softmax, loss, dZ: eight lanes per batch row; lane s adds the features s, s + 8, ... in order,
         // the lanes then add their partial sums in halves, so that each ends up owning OWN classes of the row
         {
-            const int t = opaque(t0);
+            const int t = hidden(t0);
             const int sub = t & (SI_SPLIT - 1);
             const int own0 = ((sub >> 2) & 1) * (CAP / 2) + ((sub >> 1) & 1) * (CAP / 4) + (sub & 1) * (CAP / 8);
             const float *bias = wp + (size_t)p.din * WP;
@@ -430,25 +510,29 @@ __global__ void __launch_bounds__(SI_THREADS) small_softmax_iteration_kernel(Arg
             }
         }
         }
+        if constexpr (STEP && !MM) {
+            if (fresh) __syncthreads();       // the group of draws is complete
+            request_ahead();
+        }
+        if (STEP && it > 0 && t == 0) await_arrivals(p.barrier, seen, p.barrier_base + (unsigned)it * (unsigned)p.M, p.fault, p.patience);
         __syncthreads();
         // the peer's row and the own momentum are requested before the gradient is computed and used after it
-        f32x4 rxp[SI_UPD], rv[SI_UPD];
-        if (!p.grad_only) {
-            const int t = opaque(t0);
+        f32x4 rxp[UPD], rv[UPD];
+        const float wi = STEP ? p.w[(size_t)i * p.M + m] : 0.0f;
+        const float *Xpeer = Xcur + ((ptrdiff_t)m - i) * TILE;           // from a worker's element to its peer's
+        if constexpr (STEP) {
 #pragma unroll
-            for (int e = 0; e < SI_UPD; ++e) {
-                // unconditional (beyond the end: the first vector again, never used): a load under a branch is
-                // waited for where the branches join, one round trip per pair instead of one for all
-                const int q = e * SI_THREADS + t, qc = q < n_vec ? q : 0;
-                rxp[e] = load4(Xcur + tiled_offset(p.M, m, (int64_t)qc * 4));
-                rv[e] = load4(p.V + tiled_offset(p.M, i, (int64_t)qc * 4));
+            for (int e = 0; e < UPD; ++e) {
+                // unconditional: a load under a branch is waited for where the branches join, one round trip per pair
+                // instead of one for all
+                rxp[e] = load4_device(Xpeer + own_at[e]);
+                rv[e] = load4(p.V + own_at[e]);
             }
         }
-        if (more) count_thresholds(t, iter + 1, nxt, thr_own);
         // ---- gradient into LDS: dW[k][o] = sum_b x[b][k] dz[b][o], db[o] = sum_b dz[b][o] (batch rows in order), padding 0
         if constexpr (MM) {
             // a wave takes sixteen features at a time; the batch is the contraction (step s, lane group q: row 4 s + q)
-            const int t = opaque(t0);
+            const int t = hidden(t0);
             const int lane = t & 63, wave = t >> 6, r = lane & 15, q = lane >> 4;
             constexpr int STEPS = MM ? 4 * RT : 1;           // batch / 4
             float bz[STEPS];
@@ -475,7 +559,7 @@ __global__ void __launch_bounds__(SI_THREADS) small_softmax_iteration_kernel(Arg
                 for (int s4 = 0; s4 < STEPS; ++s4) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(one, bz[s4], acc, 0, 0, 0);
                 if (q == 0 && r < p.dout) gl[(size_t)p.din * p.dout + r] = acc[0];
             }
-            if (wave == 0) {
+            if (wave == 0 && !more) {
                 // the loss: the rows' terms added by one wave in a fixed tree
                 float l = lane < p.B ? lb[lane] : 0.0f;
 #pragma unroll
@@ -484,7 +568,7 @@ __global__ void __launch_bounds__(SI_THREADS) small_softmax_iteration_kernel(Arg
             }
         } else {
             constexpr int OG = CAP / 4;                       // groups of four classes
-            const int t = opaque(t0);
+            const int t = hidden(t0);
             const int og = t % OG, n_kg = (p.din + 3) >> 2;
             for (int kg = t / OG; kg < n_kg; kg += SI_THREADS / OG) {
                 float acc[4][4];
@@ -526,7 +610,7 @@ __global__ void __launch_bounds__(SI_THREADS) small_softmax_iteration_kernel(Arg
             for (int b = 0; b < p.B; ++b) s += dz[(size_t)b * CAP + t];
             if (t < p.dout) gl[(size_t)p.din * p.dout + t] = s;
         }
-        if (!MM && t == SI_THREADS - 1) {                     // batch rows in order
+        if (!MM && !more && t == SI_THREADS - 1) {                     // batch rows in order
             float s = 0.0f;
 #pragma unroll 8
             for (int b = 0; b < p.B; ++b) s += lb[b];
@@ -535,72 +619,80 @@ __global__ void __launch_bounds__(SI_THREADS) small_softmax_iteration_kernel(Arg
         __syncthreads();
         // ---- gradient to memory; momentum step and mix (Eq. (c0), (c1)) against the peer's previous copy; the new
         // parameters stay in LDS for the next iteration
-        const float wi = p.grad_only ? 0.0f : p.w[(size_t)i * p.M + m];
-        for (int q0 = 0; q0 < n_vec; q0 += SI_THREADS * SI_UPD) {
-            if (q0 > 0 && !p.grad_only) {                     // beyond what was requested ahead
+        for (int q0 = 0; q0 < n_vec; q0 += SI_THREADS * UPD) {
+            if (STEP && q0 > 0) {                     // beyond what was requested ahead
 #pragma unroll
-                for (int e = 0; e < SI_UPD; ++e) {
+                for (int e = 0; e < UPD; ++e) {
                     const int q = q0 + e * SI_THREADS + t, qc = q < n_vec ? q : 0;
-                    rxp[e] = load4(Xcur + tiled_offset(p.M, m, (int64_t)qc * 4));
+                    rxp[e] = load4_device(Xpeer + tiled_offset(p.M, i, (int64_t)qc * 4));
                     rv[e] = load4(p.V + tiled_offset(p.M, i, (int64_t)qc * 4));
                 }
             }
+            // all new values, then all stores: a wave's stores are counted with its loads, and a load waited for behind a
+            // store waits for the store
+            f32x4 g[UPD], xn[UPD], vn[UPD];
 #pragma unroll
-            for (int e = 0; e < SI_UPD; ++e) {
+            for (int e = 0; e < UPD; ++e) {
+                const int q = q0 + e * SI_THREADS + t, j = (q < n_vec ? q : 0) * 4;
+                g[e] = *reinterpret_cast<const f32x4 *>(gl + j);
+                if constexpr (STEP) momentum_mix4(*reinterpret_cast<const f32x4 *>(xl + j), rv[e], g[e], rxp[e], wi, p.alpha, p.mu, p.wd, xn[e], vn[e]);
+            }
+#pragma unroll
+            for (int e = 0; e < UPD; ++e) {
                 const int q = q0 + e * SI_THREADS + t;
                 if (q < n_vec) {
-                    const int64_t j = (int64_t)q * 4;
-                    const size_t own = tiled_offset(p.M, i, j);
-                    const f32x4 g = *reinterpret_cast<const f32x4 *>(gl + j);
-                    store4(p.G + own, g);
-                    if (!p.grad_only) {
-                        const f32x4 x = *reinterpret_cast<const f32x4 *>(xl + j);
-                        f32x4 xn, vn;
-                        momentum_mix4(x, rv[e], g, rxp[e], wi, p.alpha, p.mu, p.wd, xn, vn);
-                        store4(Xnext + own, xn);
-                        store4(p.V + own, vn);
-                        if (more) keep_params(q, xn);
+                    const size_t own = MM && q0 == 0 ? own_at[e] : tiled_offset(p.M, i, (int64_t)q * 4);
+                    if constexpr (STEP) {
+                        store4_device(Xnext + own, xn[e]);
+                        store4(p.V + own, vn[e]);
+                        if (more) keep_params(q, xn[e]);
                     }
+                    if (!more) store4(p.G + own, g[e]);       // the next iteration's gradient replaces it otherwise
                 }
             }
         }
         if (more) {
-            request_rows(t, nxt, rf);                         // the next iteration's batch rows travel across the barrier
             if (t < p.B) yl[nxt * p.B + t] = label;
-            grid_barrier(p.barrier, p.barrier_base + (unsigned)(it + 1) * (unsigned)p.M, p.fault, p.patience);
+            for (int b = SI_THREADS + t; b < p.B; b += SI_THREADS) yl[nxt * p.B + b] = p.labels[r0 + next_rows[b]];
         }
+        at = next_at;
+        group ^= fresh;
     }
 }
 
 bool small_iter_ok(int model_is_mlp, int n_layers, int bf16, int B, int64_t din, int64_t dout, int64_t ld)
 {
     return model_is_mlp && n_layers == 1 && !bf16 && dout <= SI_MAX_OUT && din <= 4096 && ld <= 32768 &&
-           small_iter_lds(B, (int)din, (int)dout, ld) <= (size_t)SI_LDS_LIMIT;
+           small_iter_operands(B, (int)din, (int)dout, ld) <= (size_t)SI_OPERANDS_LIMIT && small_iter_lds(B, (int)din, (int)dout, ld) <= (size_t)SI_LDS_LIMIT;
 }
 
-template <class Args> static const void *small_iter_kernel(int B, int64_t din, int64_t dout)
+template <bool STEP, bool FEW, class Args> static const void *small_iter_mm_kernel(int B)
 {
-    if (small_iter_mm(B, din, dout)) {
-        if (B == 16) return reinterpret_cast<const void *>(small_softmax_iteration_kernel<16, 1, Args>);
-        if (B == 32) return reinterpret_cast<const void *>(small_softmax_iteration_kernel<16, 2, Args>);
-        return reinterpret_cast<const void *>(small_softmax_iteration_kernel<16, 4, Args>);
+    if (B == 16) return reinterpret_cast<const void *>(small_softmax_iteration_kernel<16, 1, STEP, FEW, Args>);
+    if (B == 32) return reinterpret_cast<const void *>(small_softmax_iteration_kernel<16, 2, STEP, FEW, Args>);
+    return reinterpret_cast<const void *>(small_softmax_iteration_kernel<16, 4, STEP, FEW, Args>);
+}
+template <bool STEP, class Args = SmallIterArgs> static const void *small_iter_kernel(int B, int64_t din, int64_t dout, int64_t ld)
+{
+    if (small_iter_mm(B, din, dout)) return small_iter_few(B, din, ld) ? small_iter_mm_kernel<STEP, true, Args>(B) : small_iter_mm_kernel<STEP, false, Args>(B);
+    if (dout <= 8) return reinterpret_cast<const void *>(small_softmax_iteration_kernel<8, 0, STEP, false, Args>);
+    if (dout <= 16) return reinterpret_cast<const void *>(small_softmax_iteration_kernel<16, 0, STEP, false, Args>);
+    return reinterpret_cast<const void *>(small_softmax_iteration_kernel<SI_MAX_OUT, 0, STEP, false, Args>);
+}
+
+// For the shape of a context: the three forms of its kernel.
+hipError_t prepare_small_iter(int B, int64_t din, int64_t dout, int64_t ld)
+{
+    for (const void *kernel : {small_iter_kernel<true>(B, din, dout, ld), small_iter_kernel<false>(B, din, dout, ld), small_iter_kernel<false, SmallSlotArgs>(B, din, dout, ld)}) {
+        const hipError_t e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, SI_LDS_LIMIT);
+        if (e != hipSuccess) return e;
     }
-    if (dout <= 8) return reinterpret_cast<const void *>(small_softmax_iteration_kernel<8, 0, Args>);
-    if (dout <= 16) return reinterpret_cast<const void *>(small_softmax_iteration_kernel<16, 0, Args>);
-    return reinterpret_cast<const void *>(small_softmax_iteration_kernel<SI_MAX_OUT, 0, Args>);
+    return hipSuccess;
 }
 
-// For the shape of a context: both forms of its kernel.
-hipError_t prepare_small_iter(int B, int64_t din, int64_t dout)
-{
-    hipError_t e = hipFuncSetAttribute(small_iter_kernel<SmallIterArgs>(B, din, dout), hipFuncAttributeMaxDynamicSharedMemorySize, SI_LDS_LIMIT);
-    if (e == hipSuccess)
-        e = hipFuncSetAttribute(small_iter_kernel<SmallSlotArgs>(B, din, dout), hipFuncAttributeMaxDynamicSharedMemorySize, SI_LDS_LIMIT);
-    return e;
-}
-
-// cooperative != 0: every workgroup must be resident (the caller has checked M against small_iter_max_resident()).
-hipError_t launch_small_iter(hipStream_t s, const SmallIterLaunch &a, int cooperative)
+// n_iters > 1: every workgroup must be resident (the caller has checked M against small_iter_max_resident(), and no other launch of
+// that kind runs beside it).
+hipError_t launch_small_iter(hipStream_t s, const SmallIterLaunch &a)
 {
     SmallSlotArgs p{};
     p.M = a.M; p.B = a.B; p.din = (int)a.din; p.dout = (int)a.dout; p.D = a.D; p.ld = a.ld;
@@ -608,16 +700,15 @@ hipError_t launch_small_iter(hipStream_t s, const SmallIterLaunch &a, int cooper
     p.thr = a.thr; p.last = a.last; p.w = a.w;
     p.x_first = a.x_first; p.x_second = a.x_second; p.V = a.V; p.G = a.G; p.loss = a.loss; p.peers = a.peers; p.idx = a.idx;
     p.alpha = a.alpha; p.mu = a.mu; p.wd = a.wd; p.seed = a.seed; p.iter = a.iter; p.n_iters = a.n_iters;
-    p.grad_only = a.grad_only; p.barrier = a.barrier; p.barrier_base = a.barrier_base; p.fault = a.fault;
+    p.barrier = a.barrier; p.barrier_base = a.barrier_base; p.fault = a.fault;
     p.patience = a.patience;
     const size_t lds = small_iter_lds(a.B, p.din, p.dout, a.ld);
     void *args[] = {&p};                    // the shorter struct is its beginning
     if (a.grad_only && a.slots) {
         p.slots = *a.slots;
-        return hipLaunchKernel(small_iter_kernel<SmallSlotArgs>(a.B, a.din, a.dout), dim3((unsigned)p.slots.n), dim3(SI_THREADS), args, lds, s);
+        return hipLaunchKernel(small_iter_kernel<false, SmallSlotArgs>(a.B, a.din, a.dout, a.ld), dim3((unsigned)p.slots.n), dim3(SI_THREADS), args, lds, s);
     }
-    const void *kernel = small_iter_kernel<SmallIterArgs>(a.B, a.din, a.dout);
-    if (cooperative) return hipLaunchCooperativeKernel(kernel, dim3((unsigned)a.M), dim3(SI_THREADS), args, (unsigned)lds, s);
+    const void *kernel = a.grad_only ? small_iter_kernel<false>(a.B, a.din, a.dout, a.ld) : small_iter_kernel<true>(a.B, a.din, a.dout, a.ld);
     return hipLaunchKernel(kernel, dim3((unsigned)a.M), dim3(SI_THREADS), args, lds, s);
 }
 
@@ -627,8 +718,7 @@ int small_iter_max_resident(int B, int64_t din, int64_t dout, int64_t ld)
     int per_cu = 0, dev = 0;
     hipDeviceProp_t prop;
     if (hipGetDevice(&dev) != hipSuccess || hipGetDeviceProperties(&prop, dev) != hipSuccess) return 0;
-    if (!prop.cooperativeLaunch) return 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, small_iter_kernel<SmallIterArgs>(B, din, dout), SI_THREADS,
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, small_iter_kernel<true>(B, din, dout, ld), SI_THREADS,
                                                      small_iter_lds(B, (int)din, (int)dout, ld)) != hipSuccess)
         return 0;
     return per_cu * prop.multiProcessorCount;

@@ -104,7 +104,7 @@ void launch_widen_bf16(hipStream_t s, int64_t n, const uint16_t *in, float *out)
 
 // Whole iterations of a small softmax-regression model in one kernel, one workgroup per worker (k_small_iter.hip).
 // grad_only: batch draw, loss and gradient only (G, loss, idx); otherwise also the peer draw (peers) and the update
-// (x_second, V).  n_iters > 1 needs a cooperative launch: x_first / x_second swap roles after every iteration and
+// (x_second, V).  n_iters > 1 needs all workgroups resident: x_first / x_second swap roles after every iteration and
 // the workgroups meet at a barrier (counter `barrier`, which the launch advances by (n_iters - 1) * M from
 // barrier_base); *fault is raised if a workgroup waited in vain.
 struct SmallIterLaunch {
@@ -118,9 +118,9 @@ struct SmallIterLaunch {
     long long patience;                      // polls of the barrier counter before a workgroup gives up and raises *fault
 };
 bool small_iter_ok(int model_is_mlp, int n_layers, int bf16, int B, int64_t din, int64_t dout, int64_t ld);
-hipError_t prepare_small_iter(int B, int64_t din, int64_t dout);
+hipError_t prepare_small_iter(int B, int64_t din, int64_t dout, int64_t ld);
 int small_iter_max_resident(int B, int64_t din, int64_t dout, int64_t ld);
-hipError_t launch_small_iter(hipStream_t s, const SmallIterLaunch &a, int cooperative);
+hipError_t launch_small_iter(hipStream_t s, const SmallIterLaunch &a);
 
 // Per-worker MLP / softmax-regression gradient (grouped GEMMs).
 struct MlpPlan {

@@ -76,7 +76,8 @@ struct netmax_ctx {
     uint64_t iterations = 0;
     // small softmax-regression models: whole iterations in one kernel (k_small_iter.hip)
     bool small = false;                       // the model qualifies
-    int small_resident = 0;                   // workgroups of that kernel the device holds at once (cooperative runs)
+    int small_resident = 0;                   // workgroups of that kernel the device holds at once (runs of several iterations)
+    hipEvent_t waiting_event = nullptr;       // orders launches whose workgroups wait for each other (WaitingLaunch)
     unsigned *d_barrier = nullptr;            // grid-barrier counter, only ever advanced
     unsigned barrier_count = 0;               // its value once everything enqueued so far has run
     int *d_fault = nullptr;                   // raised by a workgroup that waited at the barrier in vain
@@ -218,8 +219,53 @@ static void drop_graphs(netmax_ctx *ctx)
     ctx->graph_peers = nullptr;
 }
 
+// A launch whose workgroups wait for each other needs all of them resident.  The device holds the workgroups of one such launch (the
+// caller has checked); two of them side by side might each hold compute units that the other's missing workgroups need.  So the
+// contexts of a device take turns: a launch on another stream than the last one's waits for what that stream held at this moment.
+// (A cooperative launch gives the same guarantee, but the runtime waits for it on the host: about 20 us a call, 97 instead of 78 us
+// for sixteen iterations of 256-10, 8 workers.)  Usually there is one such stream and nothing is waited for.
+constexpr int MAX_DEVICES = 64;
+static std::mutex g_waiting_mutex;
+static netmax_ctx *g_waiting_last[MAX_DEVICES] = {};      // cleared when that context goes; its stream outlives it
+
+static bool capturing(hipStream_t s)
+{
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    return s && (hipStreamIsCapturing(s, &status) != hipSuccess || status != hipStreamCaptureStatusNone);
+}
+
+// Holds the turn while the launch is enqueued; ok() false: not possible here (a stream is being captured, or an error).
+class WaitingLaunch {
+public:
+    explicit WaitingLaunch(netmax_ctx *ctx) : lock_(g_waiting_mutex)
+    {
+        if (ctx->device < 0 || ctx->device >= MAX_DEVICES || !ctx->waiting_event || capturing(ctx->stream)) return;
+        netmax_ctx *&last = g_waiting_last[ctx->device];
+        if (last && last->stream != ctx->stream) {
+            if (capturing(last->stream) || hipEventRecord(last->waiting_event, last->stream) != hipSuccess ||
+                hipStreamWaitEvent(ctx->stream, last->waiting_event, 0) != hipSuccess) {
+                (void)hipGetLastError();
+                return;
+            }
+        }
+        last = ctx;
+        ok_ = true;
+    }
+    bool ok() const { return ok_; }
+
+private:
+    std::lock_guard<std::mutex> lock_;
+    bool ok_ = false;
+};
+
 static void release(netmax_ctx *ctx)
 {
+    {
+        std::lock_guard<std::mutex> lock(g_waiting_mutex);
+        for (auto &last : g_waiting_last)
+            if (last == ctx) last = nullptr;
+    }
+    if (ctx->waiting_event) (void)hipEventDestroy(ctx->waiting_event);
     drop_graphs(ctx);
     (void)hipFree(ctx->d_block);
     (void)hipFree(ctx->d_act_thr); (void)hipFree(ctx->d_fuse_tiles);
@@ -374,8 +420,9 @@ extern "C" int netmax_init(netmax_ctx **out, const netmax_config *cfg)
         INIT_TRY(prepare_f32_layers());
         ctx->small = small_iter_ok(1, cfg->n_layers, cfg->gemm_in == NETMAX_BF16, cfg->batch, cfg->dims[0], cfg->dims[1], cfg->ld);
         if (ctx->small) {
-            INIT_TRY(prepare_small_iter(cfg->batch, cfg->dims[0], cfg->dims[1]));
+            INIT_TRY(prepare_small_iter(cfg->batch, cfg->dims[0], cfg->dims[1], cfg->ld));
             ctx->small_resident = small_iter_max_resident(cfg->batch, cfg->dims[0], cfg->dims[1], cfg->ld);
+            INIT_TRY(hipEventCreateWithFlags(&ctx->waiting_event, hipEventDisableTiming));
             want(&ctx->d_barrier, 1);
             want(&ctx->d_fault, 1);
         }
@@ -602,10 +649,10 @@ static SmallIterLaunch small_launch(netmax_ctx *ctx, const IterRef &iter, int n_
     return a;
 }
 
-static int enqueue_small(netmax_ctx *ctx, const IterRef &iter, int n_iters, bool grad_only, int32_t *peers_dev, bool cooperative)
+static int enqueue_small(netmax_ctx *ctx, const IterRef &iter, int n_iters, bool grad_only, int32_t *peers_dev)
 {
     const SmallIterLaunch a = small_launch(ctx, iter, n_iters, grad_only, peers_dev);
-    const hipError_t e = launch_small_iter(ctx->stream, a, cooperative ? 1 : 0);
+    const hipError_t e = launch_small_iter(ctx->stream, a);
     if (e != hipSuccess) return fail(ctx, NETMAX_EDEVICE, std::string("small-model iteration kernel: ") + hipGetErrorString(e));
     if (n_iters > 1) ctx->barrier_count += (unsigned)(n_iters - 1) * (unsigned)ctx->cfg.M;
     return NETMAX_OK;
@@ -623,7 +670,7 @@ static int enqueue_local_step(netmax_ctx *ctx, const IterRef &iter, const int32_
         launch_synth_grad(ctx->stream, c.M, c.D, c.ld, c.grad_sigma, c.seed, iter, ctx->g);
         return check_launch(ctx, "synth_grad");
     }
-    if (ctx->small) return enqueue_small(ctx, iter, 1, true, nullptr, false);
+    if (ctx->small) return enqueue_small(ctx, iter, 1, true, nullptr);
     if (!drawn) launch_sample_batch(ctx->stream, c.M, c.batch, ctx->d_nrows, c.seed, iter, ctx->d_idx);
     MlpPlan p = make_plan(ctx);
     if (drawn) p.idx = drawn;
@@ -731,7 +778,7 @@ static int capture_iteration(netmax_ctx *ctx, int dir, int32_t *peers_dev)
     const IterRef it{0, ctx->d_iter};
     int rc;
     if (ctx->small && !ctx->fuse) {
-        rc = enqueue_small(ctx, it, 1, false, peers_dev, false);
+        rc = enqueue_small(ctx, it, 1, false, peers_dev);
     } else {
         rc = enqueue_draws(ctx, it, 1, peers_dev, peers_dev);
         if (rc == NETMAX_OK) rc = enqueue_run_iteration(ctx, it, peers_dev, ctx->d_idx);
@@ -762,13 +809,19 @@ extern "C" int netmax_run(netmax_ctx *ctx, uint64_t first_iter, int32_t n_iters,
     if (ctx->cfg.model == NETMAX_MLP && !ctx->data_bound) return fail(ctx, NETMAX_ESTATE, "no data bound");
     if (!peers_dev || n_iters < 0) return fail(ctx, NETMAX_EINVAL, "peers_dev is NULL or n_iters < 0");
     if (!use_graph && ctx->small && !ctx->fuse) {
-        // whole iterations inside one kernel; as many per launch as a cooperative launch allows (all workgroups
-        // resident), else one launch per iteration
-        const bool coop = ctx->small_resident >= ctx->cfg.M;
+        // whole iterations inside one kernel; all of them in one launch where its workgroups are resident together, else one
+        // launch per iteration
         int32_t k = 0;
         while (k < n_iters) {
-            const int32_t n = coop ? std::min<int32_t>(n_iters - k, 1 << 20) : 1;
-            const int rc = enqueue_small(ctx, IterRef{first_iter + (uint64_t)k, nullptr}, n, false, peers_dev, coop && n > 1);
+            int rc = NETMAX_OK;
+            int32_t n = 1;
+            if (n_iters - k > 1 && ctx->small_resident >= ctx->cfg.M) {
+                const WaitingLaunch turn(ctx);
+                if (turn.ok()) n = std::min<int32_t>(n_iters - k, 1 << 20);
+                rc = enqueue_small(ctx, IterRef{first_iter + (uint64_t)k, nullptr}, n, false, peers_dev);
+            } else {
+                rc = enqueue_small(ctx, IterRef{first_iter + (uint64_t)k, nullptr}, 1, false, peers_dev);
+            }
             if (rc != NETMAX_OK) return rc;
             for (int32_t q = 0; q < n; ++q) flip(ctx);
             k += n;
@@ -1003,7 +1056,7 @@ extern "C" int netmax_async_run(netmax_ctx *ctx, uint64_t first_step, uint64_t n
                 if (ctx->small) {
                     SmallIterLaunch a = small_launch(ctx, IterRef{0, nullptr}, 1, true, nullptr);
                     a.slots = &slots;
-                    const hipError_t e = launch_small_iter(ctx->stream, a, 0);
+                    const hipError_t e = launch_small_iter(ctx->stream, a);
                     if (e != hipSuccess) return fail(ctx, NETMAX_EDEVICE, std::string("small-model gradient kernel: ") + hipGetErrorString(e));
                     source = 1;
                 } else {
