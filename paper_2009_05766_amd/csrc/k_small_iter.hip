@@ -28,7 +28,7 @@
 #include "kernels.h"
 #include "layout.h"
 #include "philox.h"
-#include "vec.h"
+#include "resident.h"
 
 #include <type_traits>
 
@@ -100,78 +100,16 @@ static size_t small_iter_operands(int B, int din, int dout, int64_t ld)
     return (2 * (size_t)ld + ((size_t)din + 1) * (cap + 4) + (size_t)B * (din + SI_SPLIT + cap + 5) + 2) * sizeof(float);
 }
 
-// The device-wide barrier is split: a workgroup arrives when its new parameters are in memory and looks for the others' arrival
-// only where it needs their rows, half an iteration later.  What the workgroups exchange (the parameter rows, and only they) is
-// stored and loaded at device scope, past the caches of one XCD, so no cache is written back or dropped: a wave's stores have
-// arrived when its vmcnt is zero.
-__device__ __forceinline__ void store4_device(float *p, f32x4 v)
-{
-    typedef float f32x2 __attribute__((ext_vector_type(2)));
-    unsigned long long *q = reinterpret_cast<unsigned long long *>(p);
-    __hip_atomic_store(q, __builtin_bit_cast(unsigned long long, f32x2{v[0], v[1]}), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(q + 1, __builtin_bit_cast(unsigned long long, f32x2{v[2], v[3]}), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ f32x4 load4_device(const float *p)
-{
-    typedef float f32x2 __attribute__((ext_vector_type(2)));
-    const unsigned long long *q = reinterpret_cast<const unsigned long long *>(p);
-    const f32x2 a = __builtin_bit_cast(f32x2, __hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-    const f32x2 b = __builtin_bit_cast(f32x2, __hip_atomic_load(q + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-    return f32x4{a[0], a[1], b[0], b[1]};
-}
-__device__ __forceinline__ void stores_arrived() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
-__device__ __forceinline__ unsigned arrivals(unsigned *counter) { return __hip_atomic_load(counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-// Waits until the counter has reached `target`; `seen`: what it was a moment ago.  A workgroup that polls `patience` times in vain raises
-// *fault; it and all that see the flag wait for nothing any more, so the kernel always ends.
-__device__ __forceinline__ void await_arrivals(unsigned *counter, unsigned seen, unsigned target, int *fault, long long patience)
-{
-    long long polls = 0;
-    while (patience == 0 || (int)(seen - target) < 0) {
-        if (++polls > patience) __hip_atomic_store(fault, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (__hip_atomic_load(fault, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) break;
-        __builtin_amdgcn_s_sleep(1);
-        seen = arrivals(counter);
-    }
-}
-
-// j / d for 0 <= j < 2^32 / d, with magic = ceil(2^32 / d).
-__device__ __forceinline__ int div_magic(int j, uint32_t magic) { return (int)__umulhi((uint32_t)j, magic); }
-static __device__ __host__ __forceinline__ uint32_t magic_of(int d) { return (uint32_t)((0x100000000ull + (uint32_t)d - 1) / (uint32_t)d); }
-
-// The value that lane (l ^ MASK) holds, MASK in {1, 2, 4, 8}, by data-parallel-primitive moves inside the vector unit
-// (no trip through the LDS crossbar as a general lane shuffle takes): quad permutations [1,0,3,2] and [2,3,0,1] for
-// 1 and 2; for 4 the mirror of each group of eight lanes (l -> l ^ 7) followed by the reversal of each quad (^ 3); for 8 the rotation of
-// each group of sixteen by eight.
-template <int MASK>
-__device__ __forceinline__ float xor_lane(float v)
-{
-    static_assert(MASK == 1 || MASK == 2 || MASK == 4 || MASK == 8, "lane distances inside a group of sixteen");
-    int x = __float_as_int(v);
-    if (MASK == 1) x = __builtin_amdgcn_update_dpp(x, x, 0xB1, 0xF, 0xF, false);
-    if (MASK == 2) x = __builtin_amdgcn_update_dpp(x, x, 0x4E, 0xF, 0xF, false);
-    if (MASK == 4) {
-        x = __builtin_amdgcn_update_dpp(x, x, 0x141, 0xF, 0xF, false);
-        x = __builtin_amdgcn_update_dpp(x, x, 0x1B, 0xF, 0xF, false);
-    }
-    if (MASK == 8) x = __builtin_amdgcn_update_dpp(x, x, 0x128, 0xF, 0xF, false);
-    return __int_as_float(x);
-}
-
-// The value, hidden from the optimiser: what is computed from it inside a loop is computed there, not once before
-// the loop (address arithmetic of all phases kept in registers across the whole iteration starves the inner loops).
-__device__ __forceinline__ int opaque(int v)
-{
-    asm volatile("" : "+v"(v));
-    return v;
-}
-
 // CAP: classes the unrolled loops cover: dout <= CAP, CAP in {8, 16, 32}.  RT > 0: the two products on matrix
 // instructions, RT = batch / 16 tiles of batch rows (CAP = 16, shapes accepted by small_iter_mm()).
-// STEP: whole iterations, else batch draw, loss and gradient of a single one.
-template <int CAP, int RT, bool STEP, bool FEW, class Args = SmallIterArgs>
+// MODE: batch draw, loss and gradient of one iteration; the whole of one; several.  The last of several asks for its own batch rows
+// again: a load under a branch is waited for where the branches join (82 instead of 78 us for sixteen iterations of 256-10).
+enum : int { SI_GRAD = 0, SI_ONE = 1, SI_RUN = 2 };
+template <int CAP, int RT, int MODE, bool FEW, class Args = SmallIterArgs>
 __global__ void __launch_bounds__(SI_THREADS) small_softmax_iteration_kernel(Args p)
 {
     constexpr bool SLOTS = !std::is_same<Args, SmallIterArgs>::value;
+    constexpr bool STEP = MODE != SI_GRAD, RUN = MODE == SI_RUN;
     static_assert(!SLOTS || !STEP, "listed workers: the gradient only");
     constexpr bool MM = RT > 0;
     constexpr int BURST = FEW ? SI_BURST / 2 : SI_BURST, UPD = FEW ? SI_UPD / 2 : SI_UPD;
@@ -209,10 +147,10 @@ __global__ void __launch_bounds__(SI_THREADS) small_softmax_iteration_kernel(Arg
     const int last_i = STEP ? p.last[i] : 0;
     const float *shard = p.feats + (size_t)r0 * p.din;
     const uint32_t *thr_row = p.thr + (size_t)i * p.M;
-    const uint32_t magic_out = magic_of(p.dout);
+    const DivBy by_out(p.dout);
     const bool vec_rows = MM || (p.din & 3) == 0;             // batch rows as 128-bit pieces, else element by element
     const int row_units = vec_rows ? p.din >> 2 : p.din, feat_units = p.B * row_units;
-    const uint32_t magic_row = magic_of(row_units);
+    const DivBy by_row(row_units);
 
     // The draws of the iterations it0 .. of a group: batch row b is word b % 4 of block b / 4 of stream 1; the peer is the number of
     // thresholds of the worker's row that are <= u (they do not decrease), clamped to the last positive entry: every wave counts its
@@ -247,7 +185,7 @@ __global__ void __launch_bounds__(SI_THREADS) small_softmax_iteration_kernel(Arg
 #pragma unroll
         for (int e = 0; e < BURST; ++e) {
             const int q = e * SI_THREADS + t, qc = q < feat_units ? q : 0;     // unconditional, see the update's requests
-            const int b = div_magic(qc, magic_row), c = qc - b * row_units;
+            const int b = by_row(qc), c = qc - b * row_units;
             src[e] = shard + (size_t)rows[b] * p.din + (vec_rows ? 4 * c : c);
         }
         if (vec_rows) {                                       // one branch around all requests: one in each would make them wait for each other
@@ -259,11 +197,12 @@ __global__ void __launch_bounds__(SI_THREADS) small_softmax_iteration_kernel(Arg
         }
     };
     auto store_piece = [&](int q, const f32x4 &v) {
-        const int b = div_magic(q, magic_row), c = q - b * row_units;
+        const int b = by_row(q), c = q - b * row_units;
         float *dst = xs + (size_t)b * pitch;
         if (vec_rows) *reinterpret_cast<f32x4 *>(dst + 4 * c) = v;
         else dst[c] = v[0];
     };
+    auto load4_peer = [](const float *at) { return RUN ? load4_device(at) : load4(at); };
     // Four neighbouring parameters into LDS: the flat copy and the padded rows.
     auto keep_params = [&](int q, const f32x4 &v) {
         *reinterpret_cast<f32x4 *>(xl + (size_t)q * 4) = v;
@@ -272,7 +211,7 @@ __global__ void __launch_bounds__(SI_THREADS) small_softmax_iteration_kernel(Arg
         for (int c = 0; c < 4; ++c) {
             const int j = q * 4 + c;
             if (j < (int)p.D) {
-                const int k = div_magic(j, magic_out);        // row din holds the bias
+                const int k = by_out(j);        // row din holds the bias
                 wp[(size_t)k * WP + (j - k * p.dout)] = v[c];
             }
         }
@@ -313,11 +252,11 @@ __global__ void __launch_bounds__(SI_THREADS) small_softmax_iteration_kernel(Arg
         const int q = e * SI_THREADS + t0;
         own_at[e] = (uint32_t)tiled_offset(p.M, i, (int64_t)(q < n_vec ? q : 0) * 4);
     }
-    const int n_iters = STEP ? p.n_iters : 1;
+    const int n_iters = RUN ? p.n_iters : 1;
     int at = 0, group = 0;                                    // the iteration's place in its group of draws, the group's parity
     for (int it = 0; it < n_iters; ++it) {
         const int cur = it & 1, nxt = cur ^ 1;
-        const bool more = STEP && it + 1 < n_iters;
+        const bool more = RUN && it + 1 < n_iters;
         const int t = hidden(t0);
         float *Xcur = cur ? p.x_second : p.x_first;
         float *Xnext = cur ? p.x_first : p.x_second;
@@ -328,15 +267,15 @@ __global__ void __launch_bounds__(SI_THREADS) small_softmax_iteration_kernel(Arg
             if (q < feat_units) store_piece(q, rf[e]);
         }
         for (int q = BURST * SI_THREADS + t; q < feat_units; q += SI_THREADS) {
-            const int b = div_magic(q, magic_row), c = q - b * row_units;
+            const int b = by_row(q), c = q - b * row_units;
             const float *src = shard + (size_t)ib[at * p.B + b] * p.din;
             f32x4 v;
             if (vec_rows) v = load4(src + 4 * c); else v[0] = src[c];
             store_piece(q, v);
         }
-        if (STEP && it > 0) stores_arrived();                 // this wave's new parameters, on their way since the update
+        if (RUN && it > 0) stores_arrived();                  // this wave's new parameters, on their way since the update
         __syncthreads();
-        if (STEP && it > 0 && t == 0) __hip_atomic_fetch_add(p.barrier, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (RUN && it > 0 && t == 0) __hip_atomic_fetch_add(p.barrier, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         // ---- the peer
         int m = i;
         if constexpr (STEP) {
@@ -348,10 +287,10 @@ __global__ void __launch_bounds__(SI_THREADS) small_softmax_iteration_kernel(Arg
         }
         // the group of draws that the next iteration begins: the rows of this one are in LDS
         const bool fresh = more && at + 1 == ahead;
-        const int next_at = fresh ? 0 : more ? at + 1 : at;   // the last iteration asks for its own rows again: no load under a branch
+        const int next_at = fresh ? 0 : more ? at + 1 : at;
         const int32_t *next_rows = ib + next_at * p.B;
         if (fresh) draw_group(t, it + 1, group ^ 1, thr_own);
-        unsigned seen;
+        unsigned seen = 0;
         // the count of arrivals and the next iteration's labels and batch rows, on their way while this iteration goes on (in this order:
         // a wave's loads are waited for in the order of their requests)
         auto request_ahead = [&]() {
@@ -400,7 +339,7 @@ __global__ void __launch_bounds__(SI_THREADS) small_softmax_iteration_kernel(Arg
 #pragma unroll
                 for (int v = 0; v < 4; ++v) part[(size_t)(kp * p.B + row0 + 16 * rt + 4 * q + v) * 16 + r] = acc[rt][v];
             __syncthreads();
-            if constexpr (STEP) request_ahead();
+            if constexpr (RUN) request_ahead();
             // ---- the parts added in order, bias, softmax, loss, dZ: sixteen lanes per batch row, one class each
             const float *bias = xl + (size_t)p.din * p.dout;
             for (int e = t; e < p.B * 16; e += SI_THREADS) {
@@ -510,11 +449,11 @@ __global__ void __launch_bounds__(SI_THREADS) small_softmax_iteration_kernel(Arg
             }
         }
         }
-        if constexpr (STEP && !MM) {
+        if constexpr (RUN && !MM) {
             if (fresh) __syncthreads();       // the group of draws is complete
             request_ahead();
         }
-        if (STEP && it > 0 && t == 0) await_arrivals(p.barrier, seen, p.barrier_base + (unsigned)it * (unsigned)p.M, p.fault, p.patience);
+        if (RUN && it > 0 && t == 0) await_arrivals(p.barrier, seen, p.barrier_base + (unsigned)it * (unsigned)p.M, p.fault, p.patience);
         __syncthreads();
         // the peer's row and the own momentum are requested before the gradient is computed and used after it
         f32x4 rxp[UPD], rv[UPD];
@@ -525,7 +464,7 @@ __global__ void __launch_bounds__(SI_THREADS) small_softmax_iteration_kernel(Arg
             for (int e = 0; e < UPD; ++e) {
                 // unconditional: a load under a branch is waited for where the branches join, one round trip per pair
                 // instead of one for all
-                rxp[e] = load4_device(Xpeer + own_at[e]);
+                rxp[e] = load4_peer(Xpeer + own_at[e]);
                 rv[e] = load4(p.V + own_at[e]);
             }
         }
@@ -624,7 +563,7 @@ __global__ void __launch_bounds__(SI_THREADS) small_softmax_iteration_kernel(Arg
 #pragma unroll
                 for (int e = 0; e < UPD; ++e) {
                     const int q = q0 + e * SI_THREADS + t, qc = q < n_vec ? q : 0;
-                    rxp[e] = load4_device(Xpeer + tiled_offset(p.M, i, (int64_t)qc * 4));
+                    rxp[e] = load4_peer(Xpeer + tiled_offset(p.M, i, (int64_t)qc * 4));
                     rv[e] = load4(p.V + tiled_offset(p.M, i, (int64_t)qc * 4));
                 }
             }
@@ -643,7 +582,8 @@ __global__ void __launch_bounds__(SI_THREADS) small_softmax_iteration_kernel(Arg
                 if (q < n_vec) {
                     const size_t own = MM && q0 == 0 ? own_at[e] : tiled_offset(p.M, i, (int64_t)q * 4);
                     if constexpr (STEP) {
-                        store4_device(Xnext + own, xn[e]);
+                        if (more) store4_device(Xnext + own, xn[e]);
+                        else store4(Xnext + own, xn[e]);
                         store4(p.V + own, vn[e]);
                         if (more) keep_params(q, xn[e]);
                     }
@@ -666,24 +606,25 @@ bool small_iter_ok(int model_is_mlp, int n_layers, int bf16, int B, int64_t din,
            small_iter_operands(B, (int)din, (int)dout, ld) <= (size_t)SI_OPERANDS_LIMIT && small_iter_lds(B, (int)din, (int)dout, ld) <= (size_t)SI_LDS_LIMIT;
 }
 
-template <bool STEP, bool FEW, class Args> static const void *small_iter_mm_kernel(int B)
+template <int MODE, bool FEW, class Args> static const void *small_iter_mm_kernel(int B)
 {
-    if (B == 16) return reinterpret_cast<const void *>(small_softmax_iteration_kernel<16, 1, STEP, FEW, Args>);
-    if (B == 32) return reinterpret_cast<const void *>(small_softmax_iteration_kernel<16, 2, STEP, FEW, Args>);
-    return reinterpret_cast<const void *>(small_softmax_iteration_kernel<16, 4, STEP, FEW, Args>);
+    if (B == 16) return reinterpret_cast<const void *>(small_softmax_iteration_kernel<16, 1, MODE, FEW, Args>);
+    if (B == 32) return reinterpret_cast<const void *>(small_softmax_iteration_kernel<16, 2, MODE, FEW, Args>);
+    return reinterpret_cast<const void *>(small_softmax_iteration_kernel<16, 4, MODE, FEW, Args>);
 }
-template <bool STEP, class Args = SmallIterArgs> static const void *small_iter_kernel(int B, int64_t din, int64_t dout, int64_t ld)
+template <int MODE, class Args = SmallIterArgs> static const void *small_iter_kernel(int B, int64_t din, int64_t dout, int64_t ld)
 {
-    if (small_iter_mm(B, din, dout)) return small_iter_few(B, din, ld) ? small_iter_mm_kernel<STEP, true, Args>(B) : small_iter_mm_kernel<STEP, false, Args>(B);
-    if (dout <= 8) return reinterpret_cast<const void *>(small_softmax_iteration_kernel<8, 0, STEP, false, Args>);
-    if (dout <= 16) return reinterpret_cast<const void *>(small_softmax_iteration_kernel<16, 0, STEP, false, Args>);
-    return reinterpret_cast<const void *>(small_softmax_iteration_kernel<SI_MAX_OUT, 0, STEP, false, Args>);
+    if (small_iter_mm(B, din, dout)) return small_iter_few(B, din, ld) ? small_iter_mm_kernel<MODE, true, Args>(B) : small_iter_mm_kernel<MODE, false, Args>(B);
+    if (dout <= 8) return reinterpret_cast<const void *>(small_softmax_iteration_kernel<8, 0, MODE, false, Args>);
+    if (dout <= 16) return reinterpret_cast<const void *>(small_softmax_iteration_kernel<16, 0, MODE, false, Args>);
+    return reinterpret_cast<const void *>(small_softmax_iteration_kernel<SI_MAX_OUT, 0, MODE, false, Args>);
 }
 
-// For the shape of a context: the three forms of its kernel.
+// For the shape of a context: the four forms of its kernel.
 hipError_t prepare_small_iter(int B, int64_t din, int64_t dout, int64_t ld)
 {
-    for (const void *kernel : {small_iter_kernel<true>(B, din, dout, ld), small_iter_kernel<false>(B, din, dout, ld), small_iter_kernel<false, SmallSlotArgs>(B, din, dout, ld)}) {
+    for (const void *kernel : {small_iter_kernel<SI_RUN>(B, din, dout, ld), small_iter_kernel<SI_ONE>(B, din, dout, ld), small_iter_kernel<SI_GRAD>(B, din, dout, ld),
+                               small_iter_kernel<SI_GRAD, SmallSlotArgs>(B, din, dout, ld)}) {
         const hipError_t e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, SI_LDS_LIMIT);
         if (e != hipSuccess) return e;
     }
@@ -706,9 +647,11 @@ hipError_t launch_small_iter(hipStream_t s, const SmallIterLaunch &a)
     void *args[] = {&p};                    // the shorter struct is its beginning
     if (a.grad_only && a.slots) {
         p.slots = *a.slots;
-        return hipLaunchKernel(small_iter_kernel<false, SmallSlotArgs>(a.B, a.din, a.dout, a.ld), dim3((unsigned)p.slots.n), dim3(SI_THREADS), args, lds, s);
+        return hipLaunchKernel(small_iter_kernel<SI_GRAD, SmallSlotArgs>(a.B, a.din, a.dout, a.ld), dim3((unsigned)p.slots.n), dim3(SI_THREADS), args, lds, s);
     }
-    const void *kernel = a.grad_only ? small_iter_kernel<false>(a.B, a.din, a.dout, a.ld) : small_iter_kernel<true>(a.B, a.din, a.dout, a.ld);
+    const void *kernel = a.grad_only ? small_iter_kernel<SI_GRAD>(a.B, a.din, a.dout, a.ld)
+                         : a.n_iters == 1 ? small_iter_kernel<SI_ONE>(a.B, a.din, a.dout, a.ld)
+                                          : small_iter_kernel<SI_RUN>(a.B, a.din, a.dout, a.ld);
     return hipLaunchKernel(kernel, dim3((unsigned)a.M), dim3(SI_THREADS), args, lds, s);
 }
 
@@ -718,7 +661,7 @@ int small_iter_max_resident(int B, int64_t din, int64_t dout, int64_t ld)
     int per_cu = 0, dev = 0;
     hipDeviceProp_t prop;
     if (hipGetDevice(&dev) != hipSuccess || hipGetDeviceProperties(&prop, dev) != hipSuccess) return 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, small_iter_kernel<true>(B, din, dout, ld), SI_THREADS,
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, small_iter_kernel<SI_RUN>(B, din, dout, ld), SI_THREADS,
                                                      small_iter_lds(B, (int)din, (int)dout, ld)) != hipSuccess)
         return 0;
     return per_cu * prop.multiProcessorCount;

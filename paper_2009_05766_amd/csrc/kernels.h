@@ -176,6 +176,20 @@ void launch_fwd_f32(hipStream_t s, const MlpPlan &p, int l, const float *X);
 // tail: see launch_mlp_grad(); others: this launch also updates the columns of tail->tiles (first layer only)
 void launch_wgrad_f32(hipStream_t s, const MlpPlan &p, int l, float *G, const float *dz, const TailArgs *tail, bool others);
 
+// Whole iterations of a softmax regression whose worker takes several workgroups (k_sliced_iter.hip), for netmax_run: mix, G, loss,
+// peers as the separate kernels leave them after the last iteration.  All workgroups have to be resident together: M times
+// sliced_iter_slices() of them.  Tickets: one per iteration, never 0, in turn.  The launch advances rows_base by (n_iters - 1) M.
+struct SlicedIterLaunch {
+    MixArgs mix; float *G; int32_t *peers; const int32_t *n_rows; const uint32_t *thr; const int32_t *last; uint64_t seed; IterRef iter; int n_iters;
+    unsigned long long *parts; float *biases; unsigned *counters; unsigned ticket, rows_base;
+    int *fault; long long patience;
+};
+bool sliced_iter_ok(const MlpPlan &p);
+int sliced_iter_slices(const MlpPlan &p);
+void sliced_iter_scratch(const MlpPlan &p, size_t &parts, size_t &biases, size_t &counters);
+hipError_t prepare_sliced_iter(const MlpPlan &p, int *resident);
+void launch_sliced_iter(hipStream_t s, const MlpPlan &p, const SlicedIterLaunch &a);
+
 // Tiled kernels for layers of any shape, fp32 or bfloat16 operands.  need_t: the transposed bfloat16 activation is wanted (by a
 // matrix-core kernel above); below_fast: so are both bfloat16 copies of the error.  launch_tile_dgrad: true if it has also
 // written the bias gradient of the layer below (its workgroups held the whole batch).

@@ -82,6 +82,13 @@ struct netmax_ctx {
     unsigned barrier_count = 0;               // its value once everything enqueued so far has run
     int *d_fault = nullptr;                   // raised by a workgroup that waited at the barrier in vain
     long long barrier_patience = 1ll << 24;   // polls before it gives up (seconds; the barrier itself takes microseconds)
+    // softmax regression in slices: whole iterations in one kernel (k_sliced_iter.hip)
+    bool sliced = false;
+    unsigned long long *d_parts = nullptr;
+    float *d_biases = nullptr;
+    unsigned *d_counters = nullptr;
+    size_t n_parts = 0, n_counters = 0;
+    unsigned ticket = 1, rows_base = 0;       // of the next iteration; the counters once everything enqueued so far has run
     // graph replay (netmax_run): one captured iteration per direction of the parameter ping-pong
     float *x_first = nullptr;                 // the buffer bound as x_a: decides which graph an iteration uses
     uint64_t *d_iter = nullptr;               // device cell holding the iteration number of the next replay
@@ -422,11 +429,24 @@ extern "C" int netmax_init(netmax_ctx **out, const netmax_config *cfg)
         if (ctx->small) {
             INIT_TRY(prepare_small_iter(cfg->batch, cfg->dims[0], cfg->dims[1], cfg->ld));
             ctx->small_resident = small_iter_max_resident(cfg->batch, cfg->dims[0], cfg->dims[1], cfg->ld);
-            INIT_TRY(hipEventCreateWithFlags(&ctx->waiting_event, hipEventDisableTiming));
             want(&ctx->d_barrier, 1);
             want(&ctx->d_fault, 1);
         }
         const MlpPlan plan = make_plan(ctx);         // its shapes: nothing is allocated yet
+        if (!ctx->small && sliced_iter_ok(plan)) {
+            int resident = 0;
+            INIT_TRY(prepare_sliced_iter(plan, &resident));
+            ctx->sliced = (int64_t)M * sliced_iter_slices(plan) <= resident;
+            if (ctx->sliced) {
+                size_t biases = 0;
+                sliced_iter_scratch(plan, ctx->n_parts, biases, ctx->n_counters);
+                want(&ctx->d_parts, ctx->n_parts);
+                want(&ctx->d_biases, biases);
+                want(&ctx->d_counters, ctx->n_counters);
+                want(&ctx->d_fault, 1);
+            }
+        }
+        if (ctx->small || ctx->sliced) INIT_TRY(hipEventCreateWithFlags(&ctx->waiting_event, hipEventDisableTiming));
         for (int l = 0; l < cfg->n_layers && !ctx->small; ++l)
             if (update_end(plan, l) > 0) {
                 ctx->tail = true;
@@ -446,10 +466,12 @@ extern "C" int netmax_init(netmax_ctx **out, const netmax_config *cfg)
         *part.first = at;
         at += (part.second + 255) / 256 * 256;
     }
-    if (ctx->small) {
-        INIT_TRY(hipMemset(ctx->d_barrier, 0, sizeof(unsigned)));
-        INIT_TRY(hipMemset(ctx->d_fault, 0, sizeof(int)));
+    if (ctx->small) INIT_TRY(hipMemset(ctx->d_barrier, 0, sizeof(unsigned)));
+    if (ctx->sliced) {
+        INIT_TRY(hipMemset(ctx->d_counters, 0, ctx->n_counters * sizeof(unsigned)));
+        INIT_TRY(hipMemset(ctx->d_parts, 0, ctx->n_parts * sizeof(unsigned long long)));
     }
+    if (ctx->d_fault) INIT_TRY(hipMemset(ctx->d_fault, 0, sizeof(int)));
     if (!tail_tiles.empty())
         INIT_TRY(hipMemcpy(ctx->d_tail_tiles, tail_tiles.data(), tail_tiles.size() * sizeof(int32_t), hipMemcpyHostToDevice));
 #undef INIT_TRY
@@ -827,6 +849,31 @@ extern "C" int netmax_run(netmax_ctx *ctx, uint64_t first_iter, int32_t n_iters,
             k += n;
         }
         return NETMAX_OK;
+    }
+    if (!use_graph && ctx->sliced) {
+        int32_t k = 0;
+        while (k < n_iters) {
+            const int32_t n = std::min<int32_t>(n_iters - k, 1 << 20);
+            const WaitingLaunch turn(ctx);
+            if (!turn.ok()) break;                                        // a stream is being captured: the separate kernels
+            MlpPlan p = make_plan(ctx);
+            SlicedIterLaunch a{};
+            a.mix = mix_args(ctx, nullptr); a.G = ctx->g; a.peers = peers_dev; a.n_rows = ctx->d_nrows; a.thr = ctx->d_thr; a.last = ctx->d_last;
+            a.seed = ctx->cfg.seed; a.iter = IterRef{first_iter + (uint64_t)k, nullptr}; a.n_iters = n;
+            a.parts = ctx->d_parts; a.biases = ctx->d_biases; a.counters = ctx->d_counters;
+            a.ticket = ctx->ticket; a.rows_base = ctx->rows_base;
+            a.fault = ctx->d_fault; a.patience = ctx->barrier_patience;
+            launch_sliced_iter(ctx->stream, p, a);
+            const int rc = check_launch(ctx, "sliced iterations");
+            if (rc != NETMAX_OK) return rc;
+            ctx->ticket += (unsigned)n;
+            ctx->rows_base += (unsigned)(n - 1) * (unsigned)ctx->cfg.M;
+            for (int32_t q = 0; q < n; ++q) flip(ctx);
+            k += n;
+        }
+        first_iter += (uint64_t)k;
+        n_iters -= k;
+        if (n_iters == 0) return NETMAX_OK;
     }
     if (!use_graph) {
         // draws depend on the iteration number only: one launch makes those of several iterations (of a single one straight to the

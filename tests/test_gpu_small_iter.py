@@ -1,4 +1,4 @@
-"""Whole iterations of small softmax-regression models in one kernel, at the edges of how its workgroups share the work."""
+"""Whole iterations of softmax-regression models in one kernel, at the edges of how its workgroups share the work."""
 import numpy as np
 import pytest
 import torch
@@ -9,8 +9,8 @@ from netmax_inputs import workload
 pytestmark = pytest.mark.gpu
 
 
-def _run_is_calls_and_oracle(over, runs):
-    w = workload("cfg1", **over)
+def _run_is_calls_and_oracle(over, runs, name="cfg1"):
+    w = workload(name, **over)
     inp = inputs_of(w)
     inp["labels"] = np.minimum(inp["labels"], w.dims[-1] - 1).astype(np.int32)
     calls, run, o = make_gpu(w, inp), make_gpu(w, inp), make_oracle(w, inp)
@@ -38,6 +38,12 @@ def _run_is_calls_and_oracle(over, runs):
 def test_batches_beyond_the_threads(over):
     """A workgroup has 512 threads; every row of a larger batch has to be drawn and to have its label."""
     _run_is_calls_and_oracle(over, (3, 1, 2))
+
+
+@pytest.mark.parametrize("dims", [(4, 3), (1, 2), (6, 1), (1, 1)])
+def test_divisors_of_one(dims):
+    """One piece per data row, one class: positions are divided by 1."""
+    _run_is_calls_and_oracle(dict(M=3, dims=dims, batch=24, n_per_worker=50), (2, 1))
 
 
 @pytest.mark.parametrize("over", [
@@ -79,3 +85,38 @@ def test_runs_on_several_streams():
     torch.cuda.synchronize()
     assert torch.equal(nets[1].get("x"), calls.get("x")) and nets[1].consensus_dist() == calls.consensus_dist()
     nets[1].close(), calls.close()
+
+
+@pytest.mark.parametrize("over", [
+    # slices of seven steps (the waves of the last-layer kernel), four waves' and eight waves'; one row tile, two and four
+    dict(M=16, dims=(784, 10), batch=64), dict(M=3, dims=(784, 10), batch=16), dict(M=2, dims=(512, 16), batch=64), dict(M=5, dims=(900, 3), batch=32),
+    # a last slice of one step, of part of a step, features that are a multiple of four only; batches that fill no row tile
+    dict(M=3, dims=(788, 10), batch=64), dict(M=4, dims=(1028, 7), batch=33), dict(M=3, dims=(500, 10), batch=64), dict(M=3, dims=(900, 2), batch=9),
+    # slices of eight steps, and one step more than that (the separate kernels)
+    dict(M=3, dims=(1024, 16), batch=50), dict(M=2, dims=(512, 5), batch=20), dict(M=2, dims=(1028, 16), batch=20),
+    # as many workgroups as are resident, and one worker more than that (the separate kernels)
+    dict(M=73, dims=(784, 10), batch=40), dict(M=150, dims=(784, 10), batch=24),
+])
+def test_iterations_in_slices(over):
+    _run_is_calls_and_oracle(dict(n_per_worker=over["batch"] + 7, **over), (1, 18, 2), "cfg2")
+
+
+def test_slices_that_give_up_are_reported():
+    """Patience of zero polls: every wait of the sliced kernel gives up at once, the launch ends, the next consensus distance reports it."""
+    import paper_2009_05766_amd as nm
+    w = workload("cfg2", M=4, dims=(784, 10), batch=64, n_per_worker=70)
+    inp = inputs_of(w)
+    net, calls = make_gpu(w, inp), make_gpu(w, inp)
+    nm.netmax_set_barrier_patience(net.ctx, 0)
+    net.run(0, 9)
+    with pytest.raises(nm.NetmaxError) as e:
+        net.consensus_dist()
+    assert e.value.code == nm.NETMAX_EDEVICE
+    nm.netmax_set_barrier_patience(net.ctx, 1 << 24)
+    net.consensus_dist()                                     # the flag is cleared; the parameters stay what they are
+    again = make_gpu(w, inp)
+    again.run(0, 9)
+    for k in range(9):
+        calls.step(k)
+    assert torch.equal(again.get("x"), calls.get("x"))
+    net.close(), calls.close(), again.close()
