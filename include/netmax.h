@@ -181,7 +181,9 @@ int netmax_mix(netmax_ctx *ctx, uint64_t iter, const int32_t *peers_dev);
  * the device at once, else one launch per iteration; such launches of several contexts on a device run one after the other); with use_graph the replayed graph holds that kernel.  Same
  * results bit for bit: netmax_local_step runs the same gradient code for such models and every kernel applies the
  * update with the same instructions.  Larger ones (up to 1024 features in pieces of four, 16 classes, batch 64) are cut into slices of
- * the features, a workgroup each, and run the same way without use_graph where all slices of all workers fit the device at once.  Should a workgroup ever wait at the barrier in vain, the kernel still ends, the
+ * the features, a workgroup each, and so are perceptrons on float operands with one hidden layer (a multiple of 32 units, batch 32 or 64,
+ * up to about 870 features in pieces of eight) into groups of 32 units, where that is faster; they run the same way without use_graph where
+ * all workgroups of all workers fit the device at once.  Should a workgroup ever wait at the barrier in vain, the kernel still ends, the
  * parameters are invalid and the next netmax_consensus_dist returns NETMAX_EDEVICE. */
 int netmax_run(netmax_ctx *ctx, uint64_t first_iter, int32_t n_iters, int32_t *peers_dev, int32_t use_graph);
 

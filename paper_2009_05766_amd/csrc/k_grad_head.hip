@@ -44,6 +44,7 @@ struct HeadArgs {
     float *dh;                      // [M][B][H]
     float *loss;                    // [M]
     int M, B, H, C;
+    int pairs;                      // logits by pairs of steps
     int64_t woff;                   // W [H][C] of the last layer inside a parameter row, its bias behind it
     int64_t boff_below;             // bias of the layer below
     int64_t D, ld;
@@ -77,17 +78,20 @@ __device__ __forceinline__ int64_t head_row(const HeadArgs &p, int g, int b)
 
 // Grid: (ceil(B / 16), workers).  CT: tiles of sixteen classes.  How the input's rows are read: feature by feature, in pieces of
 // four features, in pieces of a number of features that fills the steps of sixteen (no bounds to respect).
+// TWO: a wave's run is summed in pairs of steps, the parts that resident_mlp_kernel's workgroups have, added in their
+// order; eight steps per wave at most then.
 enum : int { HL_SINGLE = 0, HL_PIECES = 1, HL_WHOLE = 2 };
-template <bool BF, int MODE, int CT, int NW>
+template <bool BF, int MODE, int CT, int NW, bool TWO = false>
 __global__ void __launch_bounds__(64 * NW) head_logits_kernel(HeadArgs p)
 {
+    constexpr int PER_WAVE = TWO ? HD_STEPS / 2 : 1;         // sums
     __shared__ float part[NW][16][16 * CT];
     const int B = p.B, H = p.H, C = p.C;
     const int g = blockIdx.y, rt = blockIdx.x, t = threadIdx.x, lane = t & 63, r = lane & 15, q = lane >> 4;
     const int kp = __builtin_amdgcn_readfirstlane(t >> 6);
     // each wave takes a run of steps of sixteen features; rows past the batch and features past the end are clamped, the
     // features' products then masked
-    const int steps = (H + 15) / 16, per = (steps + NW - 1) / NW;
+    const int steps = (H + 15) / 16, per = TWO ? (steps / 2 + NW - 1) / NW * 2 : (steps + NW - 1) / NW;
     const int s_begin = kp * per, s_end = s_begin + per < steps ? s_begin + per : steps;
     const int64_t a_row = head_row(p, g, 16 * rt + r < B ? 16 * rt + r : B - 1);
     const HeadParams at(p.M, g, p.woff);
@@ -95,9 +99,11 @@ __global__ void __launch_bounds__(64 * NW) head_logits_kernel(HeadArgs p)
     uint32_t wcol[CT];
 #pragma unroll
     for (int c = 0; c < CT; ++c) wcol[c] = min(16 * c + r, C - 1);
-    f32x4 acc[CT];
+    f32x4 acc[PER_WAVE][CT];
 #pragma unroll
-    for (int c = 0; c < CT; ++c) acc[c] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    for (int u = 0; u < PER_WAVE; ++u)
+#pragma unroll
+        for (int c = 0; c < CT; ++c) acc[u][c] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
     float a[HD_STEPS][4], b[HD_STEPS][4][CT];
     auto request = [&](int s0) {
 #pragma unroll
@@ -136,7 +142,10 @@ __global__ void __launch_bounds__(64 * NW) head_logits_kernel(HeadArgs p)
                 for (int j = 0; j < 4; ++j)
 #pragma unroll
                     for (int c = 0; c < CT; ++c)
-                        acc[c] = mfma_16x16x4(j < left ? a[i][j] : 0.0f, j < left ? head_operand<BF>(b[i][j][c]) : 0.0f, acc[c]);
+                    {
+                        f32x4 &sum = acc[TWO ? i / 2 : 0][c];
+                        sum = mfma_16x16x4(j < left ? a[i][j] : 0.0f, j < left ? head_operand<BF>(b[i][j][c]) : 0.0f, sum);
+                    }
             }
         __builtin_amdgcn_sched_barrier(0);
         if (s0 + HD_STEPS < s_end) request(s0 + HD_STEPS);
@@ -145,7 +154,12 @@ __global__ void __launch_bounds__(64 * NW) head_logits_kernel(HeadArgs p)
 #pragma unroll
     for (int c = 0; c < CT; ++c)
 #pragma unroll
-        for (int v = 0; v < 4; ++v) part[kp][4 * q + v][16 * c + r] = acc[c][v];
+        for (int v = 0; v < 4; ++v) {
+            float sum = acc[0][c][v];
+#pragma unroll
+            for (int u = 1; u < PER_WAVE; ++u) sum += acc[u][c][v];      // pairs past the wave's run are zeros
+            part[kp][4 * q + v][16 * c + r] = sum;
+        }
     __syncthreads();
     // the parts added in order, bias, softmax cross-entropy: sixteen lanes per batch row, CT classes each
     if (t >= 256) return;
@@ -366,11 +380,28 @@ bool head_ok(const MlpPlan &p)
     return !p.bf16 || !(mfma_small_last_ok(p) || (L > 1 && mfma_layer_ok(p, L - 2)));
 }
 
+int head_pairs_per_wave(const MlpPlan &p)
+{
+    const int pairs = (int)(p.dims[p.n_layers - 1] / 32), waves = 2 * pairs <= HL_FEW * HD_STEPS ? HL_FEW : HL_MANY;
+    return (pairs + waves - 1) / waves;
+}
+// Hidden units in pairs of steps of sixteen, not more than the waves' first ones.
+bool head_parts_of_two(const MlpPlan &p)
+{
+    const int64_t H = p.dims[p.n_layers - 1], C = p.dims[p.n_layers];
+    return p.n_layers > 1 && head_ok(p) && !p.bf16 && C <= 16 && H % 32 == 0 && H <= 16 * HD_STEPS * HL_MANY;
+}
+
 template <bool BF, int CT, int NW> static void launch_logits_waves(hipStream_t s, const HeadArgs &a)
 {
     const dim3 grid((unsigned)((a.B + 15) / 16), (unsigned)a.M), block(64 * NW);
     // pieces of four features need rows that start at multiples of their size
     const bool pieces = a.H % 4 == 0 && reinterpret_cast<uintptr_t>(a.in) % (BF ? 8 : 16) == 0;
+    if constexpr (!BF && CT == 1)
+        if (a.pairs && pieces) {
+            hipLaunchKernelGGL((head_logits_kernel<BF, HL_WHOLE, CT, NW, true>), grid, block, 0, s, a);
+            return;
+        }
     if (pieces && a.H % 16 == 0) hipLaunchKernelGGL((head_logits_kernel<BF, HL_WHOLE, CT, NW>), grid, block, 0, s, a);
     else if (pieces) hipLaunchKernelGGL((head_logits_kernel<BF, HL_PIECES, CT, NW>), grid, block, 0, s, a);
     else hipLaunchKernelGGL((head_logits_kernel<BF, HL_SINGLE, CT, NW>), grid, block, 0, s, a);
@@ -410,6 +441,7 @@ void launch_head(hipStream_t s, const MlpPlan &p, const float *X, float *G, cons
     a.dz = p.dz[0]; a.dh = p.dz[1]; a.loss = p.loss;
     a.row_loss = p.act[L];          // [M][B][C], not used for the logits on this path
     a.M = p.M; a.B = p.B; a.H = (int)p.dims[L - 1]; a.C = (int)p.dims[L];
+    a.pairs = p.head_pairs && head_parts_of_two(p);
     a.woff = p.woff[L - 1];
     a.boff_below = L == 1 ? 0 : p.woff[L - 2] + p.dims[L - 2] * p.dims[L - 1];
     a.D = p.woff[L - 1] + p.dims[L - 1] * p.dims[L] + p.dims[L]; a.ld = p.ld;

@@ -24,15 +24,6 @@ constexpr int SL_P16 = SL_MAX_C + 4;            // floats per row of W and of dZ
 constexpr int SL_STEPS = 8;                     // steps of sixteen features in a slice, at most
 constexpr int SL_PITCH = 16 * SL_STEPS + 20;    // floats per batch row in LDS: 20 more than whole rounds over the banks
 
-// A new parameter, for this launch's workgroups or (the last iteration's) for what follows the launch.
-__device__ __forceinline__ void store_row(float *at, float x, bool more)
-{
-    if (more) __hip_atomic_store(at, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    else *at = x;
-}
-// Element at a 32-bit byte offset: the base stays in scalar registers.
-template <class T> __device__ __forceinline__ T *at_bytes(T *base, uint32_t bytes) { return reinterpret_cast<T *>(reinterpret_cast<uintptr_t>(base) + bytes); }
-
 struct SlicedArgs {
     int M, B, H, C, P, per;                     // P slices of `per` steps of sixteen features
     int64_t D, ld;

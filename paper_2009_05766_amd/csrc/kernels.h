@@ -129,6 +129,7 @@ struct MlpPlan {
     int64_t woff[8];        // offset of layer l's W inside a parameter row; the bias follows the matrix
     int64_t ld;
     int bf16;               // operands rounded to bfloat16 (features are stored as bfloat16)
+    int head_pairs;         // logits summed by pairs of steps, as resident_mlp_kernel does (contexts that can run it)
     const void *feats;      // [n_total][dims[0]]
     const int32_t *labels;  // [n_total]
     const int64_t *row0;    // device [M]: first feature row of each worker's shard
@@ -190,6 +191,15 @@ void sliced_iter_scratch(const MlpPlan &p, size_t &parts, size_t &biases, size_t
 hipError_t prepare_sliced_iter(const MlpPlan &p, int *resident);
 void launch_sliced_iter(hipStream_t s, const MlpPlan &p, const SlicedIterLaunch &a);
 
+// The same for a perceptron with one hidden layer whose first weight matrices fit the chip's LDS together (k_resident_mlp.hip): a grid of
+// resident_mlp_grid() workgroups, all resident together.  Shards of fewer than 2^32 bytes.
+bool resident_mlp_ok(const MlpPlan &p);
+bool resident_mlp_pays(const MlpPlan &p, int n_iters);
+int resident_mlp_grid(const MlpPlan &p);
+void resident_mlp_scratch(const MlpPlan &p, size_t &parts, size_t &biases, size_t &counters);
+hipError_t prepare_resident_mlp(const MlpPlan &p, int *resident);
+void launch_resident_mlp(hipStream_t s, const MlpPlan &p, const SlicedIterLaunch &a);
+
 // Tiled kernels for layers of any shape, fp32 or bfloat16 operands.  need_t: the transposed bfloat16 activation is wanted (by a
 // matrix-core kernel above); below_fast: so are both bfloat16 copies of the error.  launch_tile_dgrad: true if it has also
 // written the bias gradient of the layer below (its workgroups held the whole batch).
@@ -202,6 +212,9 @@ void launch_tile_wgrad(hipStream_t s, const MlpPlan &p, int l, float *G, int cur
 // Last layer with at most 32 classes, fp32 or bfloat16 operands (k_grad_head.hip): from its input to the error of the layer
 // below in two kernels: logits, loss, dW, db, dH and the column sums of dH.
 bool head_ok(const MlpPlan &p);
+// Its logits are sums of parts of 32 hidden units in their order: head_pairs_per_wave() of them at a time, then these.
+bool head_parts_of_two(const MlpPlan &p);
+int head_pairs_per_wave(const MlpPlan &p);
 void launch_head(hipStream_t s, const MlpPlan &p, const float *X, float *G, const MixArgs *tail);
 
 }  // namespace netmax

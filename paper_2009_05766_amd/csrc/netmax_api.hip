@@ -82,8 +82,10 @@ struct netmax_ctx {
     unsigned barrier_count = 0;               // its value once everything enqueued so far has run
     int *d_fault = nullptr;                   // raised by a workgroup that waited at the barrier in vain
     long long barrier_patience = 1ll << 24;   // polls before it gives up (seconds; the barrier itself takes microseconds)
-    // softmax regression in slices: whole iterations in one kernel (k_sliced_iter.hip)
-    bool sliced = false;
+    // whole iterations in one kernel of several workgroups per worker: softmax regression in slices of its features (k_sliced_iter.hip),
+    // perceptrons with one hidden layer in groups of its units (k_resident_mlp.hip)
+    bool sliced = false, resident_mlp = false;
+    int64_t shard_bytes = 0;                  // of the largest shard
     unsigned long long *d_parts = nullptr;
     float *d_biases = nullptr;
     unsigned *d_counters = nullptr;
@@ -446,7 +448,20 @@ extern "C" int netmax_init(netmax_ctx **out, const netmax_config *cfg)
                 want(&ctx->d_fault, 1);
             }
         }
-        if (ctx->small || ctx->sliced) INIT_TRY(hipEventCreateWithFlags(&ctx->waiting_event, hipEventDisableTiming));
+        if (!ctx->sliced && resident_mlp_ok(plan)) {
+            int resident = 0;
+            INIT_TRY(prepare_resident_mlp(plan, &resident));
+            ctx->resident_mlp = resident_mlp_grid(plan) <= resident;
+            if (ctx->resident_mlp) {
+                size_t biases = 0;
+                resident_mlp_scratch(plan, ctx->n_parts, biases, ctx->n_counters);
+                want(&ctx->d_parts, ctx->n_parts);
+                want(&ctx->d_biases, biases);
+                want(&ctx->d_counters, ctx->n_counters);
+                want(&ctx->d_fault, 1);
+            }
+        }
+        if (ctx->small || ctx->sliced || ctx->resident_mlp) INIT_TRY(hipEventCreateWithFlags(&ctx->waiting_event, hipEventDisableTiming));
         for (int l = 0; l < cfg->n_layers && !ctx->small; ++l)
             if (update_end(plan, l) > 0) {
                 ctx->tail = true;
@@ -467,7 +482,7 @@ extern "C" int netmax_init(netmax_ctx **out, const netmax_config *cfg)
         at += (part.second + 255) / 256 * 256;
     }
     if (ctx->small) INIT_TRY(hipMemset(ctx->d_barrier, 0, sizeof(unsigned)));
-    if (ctx->sliced) {
+    if (ctx->d_counters) {
         INIT_TRY(hipMemset(ctx->d_counters, 0, ctx->n_counters * sizeof(unsigned)));
         INIT_TRY(hipMemset(ctx->d_parts, 0, ctx->n_parts * sizeof(unsigned long long)));
     }
@@ -570,12 +585,14 @@ extern "C" int netmax_bind_data(netmax_ctx *ctx, const void *feats, const int32_
     const int M = ctx->cfg.M;
     std::vector<int64_t> row0(M);
     std::vector<int32_t> nrows(M);
+    int64_t most = 0;
     if (shard_off[0] < 0) return fail(ctx, NETMAX_EINVAL, "shard_off[0] < 0");
     for (int i = 0; i < M; ++i) {
         const int64_t n = shard_off[i + 1] - shard_off[i];
         if (n < 1 || n > 0x7FFFFFFFLL) return fail(ctx, NETMAX_EINVAL, "every shard needs 1 .. 2^31-1 rows");
         row0[i] = shard_off[i];
         nrows[i] = (int32_t)n;
+        most = std::max(most, n);
     }
     const int64_t n_total = shard_off[M];
     if (n_total > 0x7FFFFFFFLL * 256) return fail(ctx, NETMAX_EINVAL, "too many rows");
@@ -594,6 +611,7 @@ extern "C" int netmax_bind_data(netmax_ctx *ctx, const void *feats, const int32_
     drop_graphs(ctx);
     ctx->feats = feats;
     ctx->labels = labels;
+    ctx->shard_bytes = most * ctx->cfg.dims[0] * (ctx->cfg.gemm_in == NETMAX_BF16 ? 2 : 4);
     ctx->data_bound = true;
     return NETMAX_OK;
 }
@@ -635,7 +653,7 @@ static MlpPlan make_plan(const netmax_ctx *ctx)
 {
     const netmax_config &c = ctx->cfg;
     MlpPlan p{};
-    p.M = c.M; p.n_layers = c.n_layers; p.B = c.batch; p.ld = c.ld; p.bf16 = (c.gemm_in == NETMAX_BF16);
+    p.M = c.M; p.n_layers = c.n_layers; p.B = c.batch; p.ld = c.ld; p.bf16 = (c.gemm_in == NETMAX_BF16); p.head_pairs = ctx->resident_mlp;
     for (int l = 0; l <= c.n_layers; ++l) {
         p.dims[l] = c.dims[l]; p.woff[l] = ctx->woff[l]; p.act[l] = ctx->d_act[l];
         p.hb[l] = ctx->d_hb[l]; p.ht[l] = ctx->d_ht[l];
@@ -850,7 +868,7 @@ extern "C" int netmax_run(netmax_ctx *ctx, uint64_t first_iter, int32_t n_iters,
         }
         return NETMAX_OK;
     }
-    if (!use_graph && ctx->sliced) {
+    if (!use_graph && (ctx->sliced || (ctx->resident_mlp && ctx->shard_bytes < (int64_t)1 << 32 && resident_mlp_pays(make_plan(ctx), n_iters)))) {
         int32_t k = 0;
         while (k < n_iters) {
             const int32_t n = std::min<int32_t>(n_iters - k, 1 << 20);
@@ -863,8 +881,9 @@ extern "C" int netmax_run(netmax_ctx *ctx, uint64_t first_iter, int32_t n_iters,
             a.parts = ctx->d_parts; a.biases = ctx->d_biases; a.counters = ctx->d_counters;
             a.ticket = ctx->ticket; a.rows_base = ctx->rows_base;
             a.fault = ctx->d_fault; a.patience = ctx->barrier_patience;
-            launch_sliced_iter(ctx->stream, p, a);
-            const int rc = check_launch(ctx, "sliced iterations");
+            if (ctx->sliced) launch_sliced_iter(ctx->stream, p, a);
+            else launch_resident_mlp(ctx->stream, p, a);
+            const int rc = check_launch(ctx, "whole iterations");
             if (rc != NETMAX_OK) return rc;
             ctx->ticket += (unsigned)n;
             ctx->rows_base += (unsigned)(n - 1) * (unsigned)ctx->cfg.M;
@@ -1050,6 +1069,7 @@ static int enqueue_subset_gradient(netmax_ctx *ctx, const AsyncSlots &slots)
                         ctx->d_idx);
     MlpPlan p = make_plan(ctx);
     p.M = slots.n;
+    p.head_pairs = 0;                                        // 0.25 us longer a batch, and no other kernel has to agree with it
     p.row0 = ctx->d_row0c;
     p.loss = ctx->d_lossc;
     launch_mlp_grad(ctx->stream, p, ctx->d_xc, ctx->d_gc);

@@ -47,6 +47,16 @@ __device__ __forceinline__ void await_arrivals(unsigned *counter, unsigned seen,
     asm volatile("" ::: "memory");           // what is read behind the wait is not asked for before it
 }
 
+// A new parameter, for this launch's workgroups or (the last iteration's) for what follows the launch.
+__device__ __forceinline__ void store_row(float *at, float x, bool more)
+{
+    if (more) __hip_atomic_store(at, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    else *at = x;
+}
+// Element at a 32-bit byte offset: the base stays in scalar registers.  (By way of an integer the pointer would lose its address space, and
+// every load be one that may also be of LDS and is waited for as such.)
+template <class T> __device__ __forceinline__ T *at_bytes(T *base, uint32_t bytes) { return (T *)((const char *)base + bytes); }
+
 // j / d for 0 <= j < 2^32 / d: the high half of j times ceil(2^32 / d), which of d = 1 has no 32 bits; j itself there.
 struct DivBy {
     uint32_t magic, one;

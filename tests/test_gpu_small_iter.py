@@ -101,10 +101,11 @@ def test_iterations_in_slices(over):
     _run_is_calls_and_oracle(dict(n_per_worker=over["batch"] + 7, **over), (1, 18, 2), "cfg2")
 
 
-def test_slices_that_give_up_are_reported():
-    """Patience of zero polls: every wait of the sliced kernel gives up at once, the launch ends, the next consensus distance reports it."""
+@pytest.mark.parametrize("dims", [(784, 10), (104, 96, 10)])
+def test_workgroups_that_give_up_are_reported(dims):
+    """Patience of zero polls: every wait of the kernel gives up at once, the launch ends, the next consensus distance reports it."""
     import paper_2009_05766_amd as nm
-    w = workload("cfg2", M=4, dims=(784, 10), batch=64, n_per_worker=70)
+    w = workload("cfg2", M=4, dims=dims, batch=64, n_per_worker=70)
     inp = inputs_of(w)
     net, calls = make_gpu(w, inp), make_gpu(w, inp)
     nm.netmax_set_barrier_patience(net.ctx, 0)
@@ -120,3 +121,38 @@ def test_slices_that_give_up_are_reported():
         calls.step(k)
     assert torch.equal(again.get("x"), calls.get("x"))
     net.close(), calls.close(), again.close()
+
+
+@pytest.mark.parametrize("over", [
+    # units of one workgroup, of several, of all compute units; both batches; strips of features that end inside, one per wave and four
+    dict(M=3, dims=(64, 32, 10), batch=64), dict(M=2, dims=(8, 64, 3), batch=32), dict(M=5, dims=(264, 96, 16), batch=32), dict(M=16, dims=(784, 512, 10), batch=64),
+    dict(M=9, dims=(784, 160, 10), batch=64), dict(M=3, dims=(856, 64, 2), batch=32), dict(M=2, dims=(200, 1024, 7), batch=64), dict(M=128, dims=(40, 64, 5), batch=32),
+    # more units than words asked for together; more workgroups than compute units, columns that do not fit LDS (the separate kernels)
+    dict(M=4, dims=(96, 800, 10), batch=64), dict(M=17, dims=(96, 512, 10), batch=64), dict(M=2, dims=(1000, 64, 10), batch=32),
+])
+def test_iterations_of_resident_perceptrons(over):
+    """One hidden layer: every workgroup keeps 32 units of a worker.  All state, losses and hidden activations are the separate calls' bits;
+    the oracle bounds them until a ReLU decision next to zero differs (the tolerance is the one of the other short perceptron runs)."""
+    w = workload("cfg2", n_per_worker=over["batch"] + 7, **over)
+    inp = inputs_of(w)
+    hyper = dict(momentum=0.9, weight_decay=1e-4)
+    calls, run, o = make_gpu(w, inp, **hyper), make_gpu(w, inp, **hyper), make_oracle(w, inp, **hyper)
+    for net in (calls, run):
+        net.x_b.fill_(3.0)                                   # every element of the next parameters has to be written
+    it = 0
+    for n in (1, 18, 2):
+        run.run(it, n)
+        for k in range(n):
+            calls.step(it + k)
+            if it + k < 3:
+                assert np.array_equal(calls.peers.cpu().numpy(), o.step(it + k))
+        if it == 0:
+            assert rel_err_rows(run.get("x").cpu().numpy(), o.X) < 1e-5
+        it += n
+        assert torch.equal(run.peers, calls.peers)
+        for what in ("x_a", "x_b", "v", "g"):
+            assert torch.equal(getattr(run, what), getattr(calls, what)), (what, it)
+        assert torch.equal(run.losses(), calls.losses())
+        assert torch.equal(run.hidden(1), calls.hidden(1))
+    run.consensus_dist()                                     # reads the barrier's fault flag
+    calls.close(), run.close()
