@@ -237,7 +237,7 @@ __global__ void __launch_bounds__(WG32_THREADS) wgrad_f32_kernel(LayerF32Args p)
                 f32x4 xn, vn;
                 momentum_mix4(ux[u], uv[u], gr, up[u], wi, p.mix.alpha, p.mix.mu, p.mix.wd, xn, vn);
                 if (f0 + 8 * u + ur < p.din) {
-                    store4(p.G + own[u], gr);
+                    if (p.mix.keep_g) store4(p.G + own[u], gr);
                     store4(p.mix.Xnext + own[u], xn);
                     store4(p.mix.V + own[u], vn);
                 }

@@ -205,7 +205,7 @@ __global__ void __launch_bounds__(tw_threads(BM, BN, WK), UPDATE && BN == 64 ? 3
             if constexpr (VZ) {
                 const size_t own = own_of(u);
                 const f32x4 gr = *reinterpret_cast<const f32x4 *>(&T[r][oc]);
-                store4_stream(p.G + own, gr);
+                if (!UPDATE || p.mix.keep_g) store4_stream(p.G + own, gr);
                 if constexpr (UPDATE) {
                     f32x4 xn, vn;
                     momentum_mix4(ux[u], uv[u], gr, up[u], wi, p.mix.alpha, p.mix.mu, p.mix.wd, xn, vn);

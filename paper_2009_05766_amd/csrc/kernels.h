@@ -78,8 +78,10 @@ void launch_mix_synth(hipStream_t s, int M, int64_t D, int64_t ld, const float *
 
 // What the second-step update needs besides the gradient: passed to the gradient code when the weight-gradient
 // kernels of the matrix-core layers apply the update themselves instead of writing the gradient.
+// keep_g: a kernel that applies the update to a gradient it holds also writes it to g (not in an iteration of netmax_run that another
+// follows: that one's replaces it).
 struct MixArgs {
-    const float *Xcur; float *V, *Xnext; const int32_t *peer; const float *w; float alpha, mu, wd;
+    const float *Xcur; float *V, *Xnext; const int32_t *peer; const float *w; float alpha, mu, wd; int keep_g;
 };
 // The same update for a list of column tiles only, leaving out up to MIX_MAX_SKIP column ranges (multiples of four
 // columns) that another kernel updates.  tiles: device [n_listed].

@@ -664,10 +664,10 @@ static MlpPlan make_plan(const netmax_ctx *ctx)
     return p;
 }
 
-static MixArgs mix_args(const netmax_ctx *ctx, const int32_t *peers_dev)
+static MixArgs mix_args(const netmax_ctx *ctx, const int32_t *peers_dev, bool keep_g = true)
 {
     const netmax_config &c = ctx->cfg;
-    return MixArgs{ctx->x_cur, ctx->v, ctx->x_next, peers_dev, ctx->d_w, c.lr, c.momentum, c.weight_decay};
+    return MixArgs{ctx->x_cur, ctx->v, ctx->x_next, peers_dev, ctx->d_w, c.lr, c.momentum, c.weight_decay, keep_g};
 }
 
 // Small softmax-regression models: n_iters whole iterations (or, grad_only, one batch draw + loss + gradient) in one
@@ -702,7 +702,7 @@ static int enqueue_small(netmax_ctx *ctx, const IterRef &iter, int n_iters, bool
 // columns, else enqueue_run_mix covers the remaining ones.
 // drawn: the batch rows of this iteration if they have been drawn already.
 static int enqueue_local_step(netmax_ctx *ctx, const IterRef &iter, const int32_t *run_peers = nullptr, const int32_t *drawn = nullptr,
-                              bool *updated = nullptr)
+                              bool *updated = nullptr, bool keep_g = true)
 {
     const netmax_config &c = ctx->cfg;
     if (c.model == NETMAX_FLAT) {
@@ -714,7 +714,7 @@ static int enqueue_local_step(netmax_ctx *ctx, const IterRef &iter, const int32_
     if (!drawn) launch_sample_batch(ctx->stream, c.M, c.batch, ctx->d_nrows, c.seed, iter, ctx->d_idx);
     MlpPlan p = make_plan(ctx);
     if (drawn) p.idx = drawn;
-    const TailArgs tail{mix_args(ctx, run_peers), ctx->d_tail_tiles, ctx->n_tail_tiles, ctx->tail_skip};
+    const TailArgs tail{mix_args(ctx, run_peers, keep_g), ctx->d_tail_tiles, ctx->n_tail_tiles, ctx->tail_skip};
     const bool done = launch_mlp_grad(ctx->stream, p, ctx->x_cur, ctx->g, run_peers && ctx->fuse ? &tail.mix : nullptr,
                                       run_peers && ctx->tail && !ctx->fuse ? &tail : nullptr);
     if (updated) *updated = done;
@@ -756,11 +756,11 @@ static int enqueue_run_mix(netmax_ctx *ctx, const int32_t *peers_dev, const Iter
     return check_launch(ctx, "mix");
 }
 
-// One iteration of netmax_run behind its draws (`drawn`: its batch rows).
-static int enqueue_run_iteration(netmax_ctx *ctx, const IterRef &iter, const int32_t *peers, const int32_t *drawn)
+// One iteration of netmax_run behind its draws (`drawn`: its batch rows); keep_g: see MixArgs.
+static int enqueue_run_iteration(netmax_ctx *ctx, const IterRef &iter, const int32_t *peers, const int32_t *drawn, bool keep_g)
 {
     bool updated = false;
-    const int rc = enqueue_local_step(ctx, iter, peers, drawn, &updated);
+    const int rc = enqueue_local_step(ctx, iter, peers, drawn, &updated, keep_g);
     return rc != NETMAX_OK || updated ? rc : enqueue_run_mix(ctx, peers, iter);
 }
 
@@ -821,7 +821,7 @@ static int capture_iteration(netmax_ctx *ctx, int dir, int32_t *peers_dev)
         rc = enqueue_small(ctx, it, 1, false, peers_dev);
     } else {
         rc = enqueue_draws(ctx, it, 1, peers_dev, peers_dev);
-        if (rc == NETMAX_OK) rc = enqueue_run_iteration(ctx, it, peers_dev, ctx->d_idx);
+        if (rc == NETMAX_OK) rc = enqueue_run_iteration(ctx, it, peers_dev, ctx->d_idx, true);
     }
     if (rc == NETMAX_OK) {
         launch_bump_iteration(ctx->stream, ctx->d_iter);
@@ -906,7 +906,7 @@ extern "C" int netmax_run(netmax_ctx *ctx, uint64_t first_iter, int32_t n_iters,
             if (q == 0) rc = enqueue_draws(ctx, it, std::min(ahead, n_iters - k), draws, peers_dev);
             if (rc == NETMAX_OK)
                 rc = enqueue_run_iteration(ctx, it, draws + (size_t)q * ctx->cfg.M,
-                                           ctx->d_idx ? ctx->d_idx + (size_t)q * ctx->cfg.M * ctx->cfg.batch : nullptr);
+                                           ctx->d_idx ? ctx->d_idx + (size_t)q * ctx->cfg.M * ctx->cfg.batch : nullptr, k + 1 == n_iters);
             if (rc != NETMAX_OK) return rc;
             flip(ctx);
         }
