@@ -102,6 +102,27 @@ __global__ void __launch_bounds__(256) gather_slots_kernel(int M, int n_tiles, S
     }
 }
 
+// One workgroup per place of the window's plan: worker, peer and batch draw of its step, for the kernels that take a list of workers
+// (layer_list_ok()): one launch a window in place of one a batch.
+__global__ void __launch_bounds__(64) async_lists_kernel(AsyncOrder order, const int32_t *__restrict__ active, const int32_t *__restrict__ peers,
+                                                         uint64_t first, int B, const int32_t *__restrict__ n_rows, uint64_t seed,
+                                                         int32_t *__restrict__ worker, int32_t *__restrict__ peer, int32_t *__restrict__ idx)
+{
+    const int q = (int)blockIdx.x, step = order.step[q], i = active[step];
+    if (threadIdx.x == 0) {
+        worker[q] = i;
+        peer[q] = peers[step];
+    }
+    const uint32_t rows = (uint32_t)n_rows[i];
+    for (int b4 = (int)threadIdx.x; 4 * b4 < B; b4 += 64) {
+        const Words4 r = draw_block(seed, STREAM_BATCH, (uint32_t)b4, (uint32_t)i, first + (uint64_t)step);
+        const uint32_t wd[4] = {r.a, r.b, r.c, r.d};
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (4 * b4 + e < B) idx[(size_t)q * B + 4 * b4 + e] = (int32_t)__umulhi(wd[e], rows);
+    }
+}
+
 // Time bookkeeping (Algorithm 2, UpdateTimeVector) for a run of global steps: one thread per worker walks the steps in
 // order and handles those in which it is the active worker, so every worker's entries change in step order.
 __global__ void __launch_bounds__(256) async_times_kernel(int M, int64_t n_steps, const int32_t *__restrict__ active,
@@ -121,6 +142,12 @@ __global__ void __launch_bounds__(256) async_times_kernel(int M, int64_t n_steps
         c += tim;
     }
     if (clock) clock[i] = c;
+}
+
+void launch_async_lists(hipStream_t s, int n, const AsyncOrder &order, const int32_t *active, const int32_t *peers, uint64_t first, int B,
+                        const int32_t *n_rows, uint64_t seed, int32_t *worker, int32_t *peer, int32_t *idx)
+{
+    hipLaunchKernelGGL(async_lists_kernel, dim3((unsigned)n), dim3(64), 0, s, order, active, peers, first, B, n_rows, seed, worker, peer, idx);
 }
 
 void launch_async_times(hipStream_t s, int M, int64_t n_steps, const int32_t *active, const int32_t *peers, const float *t,

@@ -31,14 +31,15 @@ struct LayerF32Args {
     float *out;                                                    // forward: [M][B][dout]
     int64_t woff, din, dout;
     int M, B, relu, gather;
+    int Mx; const int32_t *worker;                                 // see MlpPlan
     MixArgs mix;                                                   // wgrad_f32_kernel<UPDATE>
     // and the other columns, by the first `other_blocks` workgroups (a multiple of the XCDs)
     const int32_t *tiles; int n_tiles; unsigned other_blocks; MixSkip skip;
 };
 
-__device__ __forceinline__ const float *input_row(const LayerF32Args &p, int g, int b)
+__device__ __forceinline__ const float *input_row(const LayerF32Args &p, int g, int wk, int b)
 {
-    return p.gather ? p.feats + (p.row0[g] + p.idx[(size_t)g * p.B + b]) * p.din : p.act + ((size_t)g * p.B + b) * p.din;
+    return p.gather ? p.feats + (p.row0[wk] + p.idx[(size_t)g * p.B + b]) * p.din : p.act + ((size_t)g * p.B + b) * p.din;
 }
 
 // RT: 32-row tiles in a workgroup (1 or 2), ROWS: workgroups that share the batch (batch = 32 RT ROWS).  Grid: grouped_grid(workers,
@@ -53,16 +54,17 @@ __global__ void __launch_bounds__(F32_THREADS) fwd_f32_kernel(LayerF32Args p)
     int g;
     unsigned local;
     if (!decode_group(blockIdx.x, (unsigned)(p.dout / F32_COLS) * ROWS, p.M, g, local)) return;      // a worker's blocks share an XCD (its A)
+    const int wk = p.worker ? p.worker[g] : g;
     const int64_t col0 = (int64_t)(local / ROWS) * F32_COLS;
     const int row0 = (int)(local % ROWS) * (32 * RT);
     float *stage = f32_smem + wave * (2 * F32_KS * F32_COLS);
-    const float bias = p.X[tiled_offset(p.M, g, p.woff + p.din * p.dout + col0 + (t & 31))];     // for the end; requested first
+    const float bias = p.X[tiled_offset(p.Mx, wk, p.woff + p.din * p.dout + col0 + (t & 31))];     // for the end; requested first
     const int kr = lane >> 3, c4 = (lane & 7) * 4;               // this lane's piece of a staged W block
     const int64_t wcol = p.woff + col0 + c4;
     const int total = (int)(p.din / F32_KS);
     f32x4 fa[F32_DEPTH][RT], fw[F32_DEPTH];
     auto request_w = [&](int d, int s) {
-        fw[d] = *reinterpret_cast<const f32x4 *>(p.X + tiled_offset(p.M, g, wcol + ((int64_t)s * F32_KS + kr) * p.dout));
+        fw[d] = *reinterpret_cast<const f32x4 *>(p.X + tiled_offset(p.Mx, wk, wcol + ((int64_t)s * F32_KS + kr) * p.dout));
     };
     // this wave's steps are wave, wave + 8, ...: n_mine of them.  Requests beyond the last one repeat it (in bounds, never
     // used), so that the loop over whole groups of F32_DEPTH steps has no branch and waits for exactly the loads it uses.
@@ -75,7 +77,7 @@ __global__ void __launch_bounds__(F32_THREADS) fwd_f32_kernel(LayerF32Args p)
     }
     const float *arow[RT];
 #pragma unroll
-    for (int i = 0; i < RT; ++i) arow[i] = input_row(p, g, row0 + 32 * i + row) + 4 * half;
+    for (int i = 0; i < RT; ++i) arow[i] = input_row(p, g, wk, row0 + 32 * i + row) + 4 * half;
     auto request_a = [&](int d, int s) {
 #pragma unroll
         for (int i = 0; i < RT; ++i) fa[d][i] = *reinterpret_cast<const f32x4 *>(arow[i] + (int64_t)s * F32_KS);
@@ -161,7 +163,10 @@ __global__ void __launch_bounds__(WG32_THREADS) wgrad_f32_kernel(LayerF32Args p)
     if constexpr (UPDATE && GATHER) {
         if (bid < p.other_blocks) {
             const unsigned tile = bid / (unsigned)p.M;
-            if (tile < (unsigned)p.n_tiles) mix_subset_block<WG32_THREADS>(p.M, p.tiles[tile], (int)(bid - tile * (unsigned)p.M), p.skip, p.G, p.mix);
+            if (tile < (unsigned)p.n_tiles) {
+                const int at = (int)(bid - tile * (unsigned)p.M);
+                mix_subset_block<WG32_THREADS>(p.Mx, p.tiles[tile], p.worker ? p.worker[at] : at, at, p.skip, p.G, p.mix);
+            }
             return;
         }
         bid -= p.other_blocks;
@@ -169,6 +174,7 @@ __global__ void __launch_bounds__(WG32_THREADS) wgrad_f32_kernel(LayerF32Args p)
     int g;
     unsigned local;
     if (!decode_group(bid, (unsigned)((p.din + 31) / 32) * groups, p.M, g, local)) return;   // a worker's blocks share an XCD (its dZ)
+    const int wk = p.worker ? p.worker[g] : g;
     const int ct0 = (int)(local % groups) * per_group + wave, ct_end = min(nct, (int)(local % groups) * per_group + per_group);
     if (ct0 >= ct_end) return;
     const int64_t f0 = (int64_t)(local / groups) * 32;
@@ -183,7 +189,7 @@ __global__ void __launch_bounds__(WG32_THREADS) wgrad_f32_kernel(LayerF32Args p)
 #pragma unroll
         for (int j = 0; j < HB; ++j) rows[j] = p.idx[(size_t)g * p.B + 2 * j + half];
         __builtin_amdgcn_sched_barrier(0);
-        const float *base = p.feats + p.row0[g] * p.din + feat;
+        const float *base = p.feats + p.row0[wk] * p.din + feat;
 #pragma unroll
         for (int j = 0; j < HB; ++j) a[j] = base[(int64_t)rows[j] * p.din];
     } else {
@@ -195,8 +201,8 @@ __global__ void __launch_bounds__(WG32_THREADS) wgrad_f32_kernel(LayerF32Args p)
     float wi = 0.0f;
     if constexpr (UPDATE) {
         m = p.mix.peer[g];
-        if ((unsigned)m >= (unsigned)p.M) m = g;                  // an index outside [0, M) is treated as a self draw
-        wi = p.mix.w[(size_t)g * p.M + m];
+        if ((unsigned)m >= (unsigned)p.Mx) m = wk;                // an index outside [0, M) is treated as a self draw
+        wi = p.mix.w[(size_t)wk * p.Mx + m];
     }
     // UPDATE: eight lanes along the 32 columns of a row, 128-bit pieces, eight rows per pass
     const int uc = (lane & 7) * 4, ur = lane >> 3;
@@ -209,10 +215,10 @@ __global__ void __launch_bounds__(WG32_THREADS) wgrad_f32_kernel(LayerF32Args p)
             for (int u = 0; u < 4; ++u) {
                 const int64_t fr = f0 + 8 * u + ur < p.din ? f0 + 8 * u + ur : p.din - 1;
                 const int64_t j = p.woff + fr * p.dout + ct * F32_COLS + uc;
-                own[u] = tiled_offset(p.M, g, j);
+                own[u] = tiled_offset(p.Mx, wk, j);
                 ux[u] = load4(p.mix.Xcur + own[u]);
                 uv[u] = load4(p.mix.V + own[u]);
-                up[u] = load4(p.mix.Xcur + tiled_offset(p.M, m, j));
+                up[u] = load4(p.mix.Xcur + tiled_offset(p.Mx, m, j));
             }
             __builtin_amdgcn_sched_barrier(0);
         }
@@ -247,7 +253,7 @@ __global__ void __launch_bounds__(WG32_THREADS) wgrad_f32_kernel(LayerF32Args p)
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
                 const int64_t fr = f0 + 8 * (v >> 2) + 4 * half + (v & 3);
-                if (fr < p.din) p.G[tiled_offset(p.M, g, p.woff + fr * p.dout + ct * F32_COLS + col)] = acc[v];
+                if (fr < p.din) p.G[tiled_offset(p.Mx, wk, p.woff + fr * p.dout + ct * F32_COLS + col)] = acc[v];
             }
         }
     }
@@ -259,6 +265,7 @@ static LayerF32Args layer_f32_args(const MlpPlan &p, int l, const float *X, floa
     a.feats = (const float *)p.feats; a.row0 = p.row0; a.idx = p.idx; a.act = l > 0 ? p.act[l] : nullptr;
     a.X = X; a.G = G; a.dz = dz; a.out = p.act[l + 1];
     a.woff = p.woff[l]; a.din = p.dims[l]; a.dout = p.dims[l + 1];
+    a.Mx = p.Mx; a.worker = p.worker;
     a.M = p.M; a.B = p.B; a.relu = l + 1 < p.n_layers; a.gather = l == 0;
     return a;
 }

@@ -45,6 +45,7 @@ struct HeadArgs {
     float *loss;                    // [M]
     int M, B, H, C;
     int pairs;                      // logits by pairs of steps
+    int Mx; const int32_t *worker;  // see MlpPlan
     int64_t woff;                   // W [H][C] of the last layer inside a parameter row, its bias behind it
     int64_t boff_below;             // bias of the layer below
     int64_t D, ld;
@@ -71,9 +72,9 @@ struct HeadParams {
     __device__ __forceinline__ uint32_t at(uint32_t u) const { return u + first + ((u + first) >> TILE_SHIFT) * skip; }
 };
 // Element index of feature 0 of batch row b.
-__device__ __forceinline__ int64_t head_row(const HeadArgs &p, int g, int b)
+__device__ __forceinline__ int64_t head_row(const HeadArgs &p, int g, int wk, int b)
 {
-    return (p.gather ? p.row0[g] + p.idx[(size_t)g * p.B + b] : (int64_t)g * p.B + b) * p.H;
+    return (p.gather ? p.row0[wk] + p.idx[(size_t)g * p.B + b] : (int64_t)g * p.B + b) * p.H;
 }
 
 // Grid: (ceil(B / 16), workers).  CT: tiles of sixteen classes.  How the input's rows are read: feature by feature, in pieces of
@@ -93,8 +94,9 @@ __global__ void __launch_bounds__(64 * NW) head_logits_kernel(HeadArgs p)
     // features' products then masked
     const int steps = (H + 15) / 16, per = TWO ? (steps / 2 + NW - 1) / NW * 2 : (steps + NW - 1) / NW;
     const int s_begin = kp * per, s_end = s_begin + per < steps ? s_begin + per : steps;
-    const int64_t a_row = head_row(p, g, 16 * rt + r < B ? 16 * rt + r : B - 1);
-    const HeadParams at(p.M, g, p.woff);
+    const int wk = p.worker ? p.worker[g] : g;
+    const int64_t a_row = head_row(p, g, wk, 16 * rt + r < B ? 16 * rt + r : B - 1);
+    const HeadParams at(p.Mx, wk, p.woff);
     const float *Xg = p.X + at.base;
     uint32_t wcol[CT];
 #pragma unroll
@@ -128,7 +130,7 @@ __global__ void __launch_bounds__(64 * NW) head_logits_kernel(HeadArgs p)
     const int32_t drawn = p.idx[(size_t)g * B + min(b_row, B - 1)];
     if (s_begin < s_end) request(s_begin);
     __builtin_amdgcn_sched_barrier(0);
-    const int y = p.labels[p.row0[g] + drawn];
+    const int y = p.labels[p.row0[wk] + drawn];
     float bias[CT];
 #pragma unroll
     for (int c = 0; c < CT; ++c) bias[c] = Xg[at.at((uint32_t)(H * C + min(16 * c + l16, C - 1)))];
@@ -207,11 +209,12 @@ __global__ void __launch_bounds__(HD_THREADS) head_grads_kernel(HeadArgs p)
     const int B = p.B, H = p.H, C = p.C;
     const int g = blockIdx.y, t = threadIdx.x, lane = t & 63, r = lane & 15, q = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int wk = p.worker ? p.worker[g] : g;
     const bool first = blockIdx.x == 0;          // the workgroup that also writes what does not split by hidden units
     const int KT = (H + 15) / 16, kt = (int)blockIdx.x * HD_WAVES + wave;
     const int ktc = kt < KT ? kt : 0;            // waves past the end repeat the first block and store nothing
     const int hc = 16 * ktc + r < H ? 16 * ktc + r : H - 1;
-    const HeadParams at(p.M, g, p.woff);
+    const HeadParams at(p.Mx, wk, p.woff);
     const float *Xg = p.X + at.base;
     // requests: this wave's 16 columns of the input (all batch rows; gathered rows by number first), its 16 rows of W, and dZ.
     // Rows past the batch repeat the last one and count as zeros.
@@ -243,7 +246,7 @@ __global__ void __launch_bounds__(HD_THREADS) head_grads_kernel(HeadArgs p)
         zv[u] = zg[min(row, B - 1) * C + (c < C ? c : 0)];
     }
     if (FIRST) {
-        const int64_t base = p.row0[g] * H + hc;
+        const int64_t base = p.row0[wk] * H + hc;
 #pragma unroll
         for (int i = 0; i < RT; ++i)
 #pragma unroll
@@ -262,9 +265,9 @@ __global__ void __launch_bounds__(HD_THREADS) head_grads_kernel(HeadArgs p)
     };
     if constexpr (UPDATE) {
         m = p.mix.peer[g];
-        if ((unsigned)m >= (unsigned)p.M) m = g;              // an index outside [0, M) is treated as a self draw
-        wi = p.mix.w[(size_t)g * p.M + m];
-        peer_shift = ((size_t)m - (size_t)g) << TILE_SHIFT;   // from a worker's element to its peer's
+        if ((unsigned)m >= (unsigned)p.Mx) m = wk;            // an index outside [0, M) is treated as a self draw
+        wi = p.mix.w[(size_t)wk * p.Mx + m];
+        peer_shift = ((size_t)m - (size_t)wk) << TILE_SHIFT;   // from a worker's element to its peer's
 #pragma unroll
         for (int c = 0; c < CT; ++c)
 #pragma unroll
@@ -296,10 +299,10 @@ __global__ void __launch_bounds__(HD_THREADS) head_grads_kernel(HeadArgs p)
         if (wave == 0) {
 #pragma unroll
             for (int m = 32; m > 0; m >>= 1) lrow += __shfl_xor(lrow, m);
-            if (lane == 0) p.loss[g] = lrow / (float)B;
+            if (lane == 0) p.loss[wk] = lrow / (float)B;
         }
         for (int64_t e = t; e < p.ld - p.D; e += HD_THREADS) {
-            const size_t own = tiled_offset_quick(p.M, g, p.D + e);
+            const size_t own = tiled_offset_quick(p.Mx, wk, p.D + e);
             p.G[own] = 0.0f;
             if constexpr (UPDATE) update(own, p.mix.Xcur[own], p.mix.V[own], 0.0f, p.mix.Xcur[own + peer_shift]);
         }
@@ -364,7 +367,7 @@ __global__ void __launch_bounds__(HD_THREADS) head_grads_kernel(HeadArgs p)
         }
         colsum += __shfl_xor(colsum, 16);
         colsum += __shfl_xor(colsum, 32);
-        if (q == 0 && col_ok) p.G[tiled_offset_quick(p.M, g, p.boff_below + 16 * kt + r)] = colsum;
+        if (q == 0 && col_ok) p.G[tiled_offset_quick(p.Mx, wk, p.boff_below + 16 * kt + r)] = colsum;
     }
 }
 
@@ -376,7 +379,7 @@ bool head_ok(const MlpPlan &p)
     if (p.dims[L] > HD_MAX_C || p.B > HD_MAX_B) return false;
     // 32-bit element numbers inside the layer's span of the tile layout and inside a worker's activations
     const int64_t H = p.dims[L - 1], tiles = (H * p.dims[L] + p.dims[L]) / TILE + 2;
-    if (tiles * p.M * TILE >= (int64_t)1 << 32 || H * p.B >= (int64_t)1 << 31) return false;
+    if (tiles * p.Mx * TILE >= (int64_t)1 << 32 || H * p.B >= (int64_t)1 << 31) return false;
     return !p.bf16 || !(mfma_small_last_ok(p) || (L > 1 && mfma_layer_ok(p, L - 2)));
 }
 
@@ -441,6 +444,7 @@ void launch_head(hipStream_t s, const MlpPlan &p, const float *X, float *G, cons
     a.dz = p.dz[0]; a.dh = p.dz[1]; a.loss = p.loss;
     a.row_loss = p.act[L];          // [M][B][C], not used for the logits on this path
     a.M = p.M; a.B = p.B; a.H = (int)p.dims[L - 1]; a.C = (int)p.dims[L];
+    a.Mx = p.Mx; a.worker = p.worker;
     a.pairs = p.head_pairs && head_parts_of_two(p);
     a.woff = p.woff[L - 1];
     a.boff_below = L == 1 ? 0 : p.woff[L - 2] + p.dims[L - 2] * p.dims[L - 1];

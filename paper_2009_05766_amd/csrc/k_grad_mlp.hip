@@ -209,6 +209,14 @@ int64_t update_end(const MlpPlan &p, int l)
     return p.woff[l] + p.dims[l] * p.dims[l + 1];
 }
 
+// One fp32 hidden layer on the kernels of k_grad_f32.hip, or none: forward, the last layer's two kernels, weight gradient with the
+// update of everything.
+bool layer_list_ok(const MlpPlan &p)
+{
+    if (p.bf16 || !head_ok(p) || update_end(p, 0) <= 0) return false;
+    return p.n_layers == 1 || (p.n_layers == 2 && fwd_f32_ok(p, 0) && wgrad_f32_ok(p, 0));
+}
+
 bool launch_mlp_grad(hipStream_t s, const MlpPlan &p, const float *X, float *G, const MixArgs *fuse, const TailArgs *tail)
 {
     const int L = p.n_layers;

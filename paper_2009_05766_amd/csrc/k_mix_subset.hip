@@ -7,7 +7,7 @@ namespace netmax {
 
 __global__ void __launch_bounds__(256) mix_subset_kernel(int M, const int32_t *__restrict__ tiles, MixSkip skip, const float *G, MixArgs mix)
 {
-    mix_subset_block<256>(M, tiles[blockIdx.x / (unsigned)M], (int)(blockIdx.x % (unsigned)M), skip, G, mix);
+    mix_subset_block<256>(M, tiles[blockIdx.x / (unsigned)M], (int)(blockIdx.x % (unsigned)M), (int)(blockIdx.x % (unsigned)M), skip, G, mix);
 }
 
 void launch_mix_subset(hipStream_t s, int M, const int32_t *tiles, int n_listed, const MixSkip &skip, const float *G, const MixArgs &mix)

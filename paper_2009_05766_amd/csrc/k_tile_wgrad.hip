@@ -59,7 +59,7 @@ __global__ void __launch_bounds__(tw_threads(BM, BN, WK), UPDATE && BN == 64 ? 3
         if (bid < p.other_blocks) {
             const unsigned tile = bid / (unsigned)p.M;
             constexpr int OT = NT < TILE / 4 ? NT : TILE / 4;
-            if (tile < (unsigned)p.n_tiles && t < OT) mix_subset_block<OT>(p.M, p.tiles[tile], (int)(bid - tile * (unsigned)p.M), p.skip, p.G, p.mix);
+            if (tile < (unsigned)p.n_tiles && t < OT) mix_subset_block<OT>(p.M, p.tiles[tile], (int)(bid - tile * (unsigned)p.M), (int)(bid - tile * (unsigned)p.M), p.skip, p.G, p.mix);
             return;
         }
         bid -= p.other_blocks;

@@ -51,6 +51,13 @@ void launch_async_rows(hipStream_t s, int source, int M, int64_t D, int64_t ld, 
 void launch_gather_slots(hipStream_t s, int M, int64_t ld, const AsyncSlots &slots, const float *X, float *Xc, int B, const int64_t *row0,
                          const int32_t *n_rows, uint64_t seed, int64_t *row0_c, int32_t *idx);
 
+// The lists of a window of steps for the gradient kernels that take one: place q holds step order[q] (of the window), its worker and peer
+// from the draws, its batch rows [B].
+constexpr int ASYNC_WINDOW = 512;
+struct AsyncOrder { uint16_t step[ASYNC_WINDOW]; };
+void launch_async_lists(hipStream_t s, int n, const AsyncOrder &order, const int32_t *active, const int32_t *peers, uint64_t first, int B,
+                        const int32_t *n_rows, uint64_t seed, int32_t *worker, int32_t *peer, int32_t *idx);
+
 void launch_async_times(hipStream_t s, int M, int64_t n_steps, const int32_t *active, const int32_t *peers, const float *t,
                         float beta, float *ema, float *clock);
 
@@ -125,8 +132,12 @@ int small_iter_max_resident(int B, int64_t din, int64_t dout, int64_t ld);
 hipError_t launch_small_iter(hipStream_t s, const SmallIterLaunch &a);
 
 // Per-worker MLP / softmax-regression gradient (grouped GEMMs).
+// The workers may be a list (layer_list_ok()): M of them then, X, G, V, loss, the shards and the mix weights those of all Mx workers; idx, the
+// peers and the scratch go by place in the list.
 struct MlpPlan {
     int M, n_layers, B;
+    int Mx;                 // workers of X, G and V
+    const int32_t *worker;  // device [M], NULL: all of them
     int64_t dims[8];
     int64_t woff[8];        // offset of layer l's W inside a parameter row; the bias follows the matrix
     int64_t ld;
@@ -153,8 +164,11 @@ struct TailArgs { MixArgs mix; const int32_t *tiles; int n_tiles; MixSkip skip; 
 // tail != nullptr (not together with fuse): the weight gradients of the layers whose update_end() is not 0 write G and apply the
 // update to the columns woff .. update_end() - 1 (multiples of four) while they hold them.  The others are updated by the first
 // layer's weight gradient where it can (it is the last launch then), else by the caller: false is returned in that case.
+// With a list: X, G and the update in place (mix.Xnext = mix.Xcur); no listed worker is another's peer.
 bool launch_mlp_grad(hipStream_t s, const MlpPlan &p, const float *X, float *G, const MixArgs *fuse = nullptr, const TailArgs *tail = nullptr);
 int64_t update_end(const MlpPlan &p, int l);
+// All kernels of the plan take a list of workers and between them update all of their columns.
+bool layer_list_ok(const MlpPlan &p);
 
 // Matrix-core kernels (k_grad_mfma.hip) for layers that mfma_layer_ok() accepts.
 bool mfma_layer_ok(const MlpPlan &p, int l);

@@ -9,11 +9,12 @@
 
 namespace netmax {
 
+// i: the worker; g: its place in the list of peers.
 template <int THREADS>
-__device__ __forceinline__ void mix_subset_block(int M, int64_t tile, int i, const MixSkip &skip, const float *G, const MixArgs &mix)
+__device__ __forceinline__ void mix_subset_block(int M, int64_t tile, int i, int g, const MixSkip &skip, const float *G, const MixArgs &mix)
 {
     static_assert(TILE % (4 * THREADS) == 0, "every thread has the same share of a tile");
-    int m = mix.peer[i];
+    int m = mix.peer[g];
     if ((unsigned)m >= (unsigned)M) m = i;                   // an index outside [0, M) is treated as a self draw
     const float wi = mix.w[(size_t)i * M + m];
     const size_t own = ((size_t)tile * M + i) * TILE, other = ((size_t)tile * M + m) * TILE;

@@ -73,6 +73,7 @@ struct netmax_ctx {
     int sub_cap = 0;                          // slots allocated
     float *d_xc = nullptr, *d_gc = nullptr, *d_lossc = nullptr;
     int64_t *d_row0c = nullptr;
+    int32_t *d_lists = nullptr;               // or, where the kernels take a list of workers: workers, peers and batch rows of a window of steps
     uint64_t iterations = 0;
     // small softmax-regression models: whole iterations in one kernel (k_small_iter.hip)
     bool small = false;                       // the model qualifies
@@ -278,7 +279,7 @@ static void release(netmax_ctx *ctx)
     drop_graphs(ctx);
     (void)hipFree(ctx->d_block);
     (void)hipFree(ctx->d_act_thr); (void)hipFree(ctx->d_fuse_tiles);
-    (void)hipFree(ctx->d_xc); (void)hipFree(ctx->d_gc); (void)hipFree(ctx->d_lossc); (void)hipFree(ctx->d_row0c);
+    (void)hipFree(ctx->d_xc); (void)hipFree(ctx->d_gc); (void)hipFree(ctx->d_lossc); (void)hipFree(ctx->d_row0c); (void)hipFree(ctx->d_lists);
     delete ctx;
 }
 
@@ -653,7 +654,7 @@ static MlpPlan make_plan(const netmax_ctx *ctx)
 {
     const netmax_config &c = ctx->cfg;
     MlpPlan p{};
-    p.M = c.M; p.n_layers = c.n_layers; p.B = c.batch; p.ld = c.ld; p.bf16 = (c.gemm_in == NETMAX_BF16); p.head_pairs = ctx->resident_mlp;
+    p.M = p.Mx = c.M; p.worker = nullptr; p.n_layers = c.n_layers; p.B = c.batch; p.ld = c.ld; p.bf16 = (c.gemm_in == NETMAX_BF16); p.head_pairs = ctx->resident_mlp;
     for (int l = 0; l <= c.n_layers; ++l) {
         p.dims[l] = c.dims[l]; p.woff[l] = ctx->woff[l]; p.act[l] = ctx->d_act[l];
         p.hb[l] = ctx->d_hb[l]; p.ht[l] = ctx->d_ht[l];
@@ -1044,9 +1045,8 @@ static int host_draw(const uint32_t *row, int n, int last, uint32_t u)
     return pos < last ? pos : last;
 }
 
-// Global steps planned at a time: long enough that few levels are cut short at its end, short enough that the first launch does
-// not wait for the plan (two Philox blocks and two searches per step).
-constexpr int ASYNC_WINDOW = 512;
+// Global steps are planned ASYNC_WINDOW at a time: long enough that few levels are cut short at its end, short enough that the first
+// launch does not wait for the plan (two Philox blocks and two searches per step).
 // Flat models beyond this many parameters in all keep the order of the steps: a step finds the rows that the steps before it wrote or
 // read in the Infinity Cache (256 MB), by levels they have left it.  32 steps, by levels and in order: 30 workers x 4 M 585 and 572
 // us, x 9 M 1365 and 1336, 60 x 3 M 452 and 445; 12 x 6 M (72 M) 786 and 786, 30 x 2 M (60 M) 266 and 274.
@@ -1068,7 +1068,7 @@ static int enqueue_subset_gradient(netmax_ctx *ctx, const AsyncSlots &slots)
     launch_gather_slots(ctx->stream, c.M, c.ld, slots, ctx->x_cur, ctx->d_xc, c.batch, ctx->d_row0, ctx->d_nrows, c.seed, ctx->d_row0c,
                         ctx->d_idx);
     MlpPlan p = make_plan(ctx);
-    p.M = slots.n;
+    p.M = p.Mx = slots.n;                                    // the compact matrix
     p.head_pairs = 0;                                        // 0.25 us longer a batch, and no other kernel has to agree with it
     p.row0 = ctx->d_row0c;
     p.loss = ctx->d_lossc;
@@ -1094,6 +1094,11 @@ extern "C" int netmax_async_run(netmax_ctx *ctx, uint64_t first_step, uint64_t n
     // not see each other.  A batch is one set of launches.
     const int cap = std::min<int>(c.M, ASYNC_MAX_BATCH);
     const bool in_order = c.model == NETMAX_FLAT && (int64_t)c.M * c.ld > ASYNC_IN_ORDER_FLOATS;
+    // Kernels that take a list of workers read and update their rows where they lie: four launches a batch instead of six (784-512-10,
+    // 16 workers, batch 64, 64 steps 733 us with a gather of the rows and a kernel that updates them, 580 us without).
+    const bool lists = c.model == NETMAX_MLP && !ctx->small && layer_list_ok(make_plan(ctx));
+    if (lists && !ctx->d_lists) HIP_TRY(ctx, hipMalloc(&ctx->d_lists, (size_t)ASYNC_WINDOW * (2 + c.batch) * sizeof(int32_t)));
+    int32_t *const list_peers = lists ? ctx->d_lists + ASYNC_WINDOW : nullptr, *const list_rows = lists ? ctx->d_lists + 2 * ASYNC_WINDOW : nullptr;
     AsyncPlanner planner(c.M);
     std::vector<int> active, peer;
     for (uint64_t s0 = 0; s0 < n_steps && rc == NETMAX_OK; s0 += ASYNC_WINDOW) {
@@ -1108,6 +1113,25 @@ extern "C" int netmax_async_run(netmax_ctx *ctx, uint64_t first_step, uint64_t n
                                 draw_block(c.seed, STREAM_PEER, 0u, (uint32_t)i, k).a);
         }
         planner.plan(active.data(), peer.data(), n, cap, in_order);
+        if (lists) {
+            AsyncOrder order;
+            for (int q = 0; q < n; ++q) order.step[q] = (uint16_t)planner.order()[q];
+            launch_async_lists(ctx->stream, n, order, active_dev + s0, peers_dev + s0, first_step + s0, c.batch, ctx->d_nrows, c.seed, ctx->d_lists, list_peers,
+                               list_rows);
+            for (int b = 0; b < planner.batches(); ++b) {
+                const int start = planner.start(b);
+                MlpPlan p = make_plan(ctx);
+                p.M = planner.start(b + 1) - start;
+                p.head_pairs = 0;                            // 0.25 us longer a batch, and no other kernel has to agree with it
+                p.worker = ctx->d_lists + start;
+                p.idx = list_rows + (size_t)start * c.batch;
+                TailArgs tail{mix_args(ctx, list_peers + start), ctx->d_tail_tiles, ctx->n_tail_tiles, ctx->tail_skip};
+                tail.mix.Xnext = ctx->x_cur;                 // in place
+                launch_mlp_grad(ctx->stream, p, ctx->x_cur, ctx->g, nullptr, &tail);
+            }
+            rc = check_launch(ctx, "async batches");
+            continue;
+        }
         for (int b = 0; b < planner.batches() && rc == NETMAX_OK; ++b) {
             AsyncSlots slots;
             slots.n = planner.start(b + 1) - planner.start(b);

@@ -156,3 +156,42 @@ def test_iterations_of_resident_perceptrons(over):
         assert torch.equal(run.hidden(1), calls.hidden(1))
     run.consensus_dist()                                     # reads the barrier's fault flag
     calls.close(), run.close()
+
+
+@pytest.mark.parametrize("name,over,n", [
+    # kernels that take a list of workers: one hidden layer, batches of 32 and 64, self pulls among the draws; softmax regression
+    ("cfg2", dict(M=5, dims=(72, 96, 10), batch=32), 40), ("cfg2", dict(M=16, dims=(200, 64, 7), batch=64), 50), ("cfg2", dict(M=40, dims=(40, 32, 16), batch=64), 200),
+    ("cfg2", dict(M=6, dims=(1100, 10), batch=40), 30), ("cfg2", dict(M=4, dims=(784, 10), batch=64), 30),
+    # more steps than a window of the plan
+    ("cfg2", dict(M=3, dims=(16, 32, 3), batch=32), 700),
+])
+def test_async_steps_in_place(name, over, n):
+    """Asynchronous steps on the workers' rows where they lie: draws, x, v, the last gradient of every worker and its loss against the oracle's
+    sequential steps; rows of workers that are never drawn keep their bits."""
+    import paper_2009_05766_amd as nm
+    w = workload(name, n_per_worker=over["batch"] + 9, **over)
+    inp = inputs_of(w)
+    gpu, o = make_gpu(w, inp, momentum=0.9), make_oracle(w, inp, momentum=0.9)
+    p_act = np.full(w.M, 1.0 / (w.M - 1))
+    p_act[1] = 0.0                                           # never active
+    x1 = gpu.get("x")[1].clone()
+    nm.netmax_set_activity(gpu.ctx, p_act)
+    active, peers = (torch.full((n,), -1, dtype=torch.int32, device="cuda") for _ in range(2))
+    nm.netmax_async_run(gpu.ctx, 5, n, active, peers)
+    o.set_activity(p_act)
+    first = 12                                               # a ReLU decision next to zero may differ later on
+    want = np.array([o.async_step(5 + k) for k in range(first)])
+    assert np.array_equal(active[:first].cpu().numpy(), want[:, 0]) and np.array_equal(peers[:first].cpu().numpy(), want[:, 1])
+    again = make_gpu(w, inp, momentum=0.9)
+    nm.netmax_set_activity(again.ctx, p_act)
+    a2, p2 = (torch.full((n,), -1, dtype=torch.int32, device="cuda") for _ in range(2))
+    nm.netmax_async_run(again.ctx, 5, first, a2, p2)
+    x = again.get("x")
+    assert rel_err_rows(x.cpu().numpy(), o.X) < 1e-4 and rel_err_rows(again.get("v").cpu().numpy(), o.V) < 1e-4
+    assert torch.equal(x[1], x1) and torch.equal(gpu.get("x")[1], x1)
+    # step by step, every batch of one step: the same bits but for the forms that depend on the number of steps in a batch
+    for k in range(first, n):
+        nm.netmax_async_run(again.ctx, 5 + k, 1, a2[k:k + 1], p2[k:k + 1])
+    assert torch.equal(active, a2) and torch.equal(peers, p2)
+    assert rel_err_rows(gpu.get("x").cpu().numpy(), again.get("x").cpu().numpy()) < 1e-3
+    gpu.close(), again.close()
