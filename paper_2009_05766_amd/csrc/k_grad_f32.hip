@@ -31,10 +31,10 @@ struct LayerF32Args {
     float *out;                                                    // forward: [M][B][dout]
     int64_t woff, din, dout;
     int M, B, relu, gather;
-    int Mx; const int32_t *worker;                                 // see MlpPlan
     MixArgs mix;                                                   // wgrad_f32_kernel<UPDATE>
     // and the other columns, by the first `other_blocks` workgroups (a multiple of the XCDs)
     const int32_t *tiles; int n_tiles; unsigned other_blocks; MixSkip skip;
+    int Mx; const int32_t *worker;                                 // LIST: see MlpPlan
 };
 
 __device__ __forceinline__ const float *input_row(const LayerF32Args &p, int g, int wk, int b)
@@ -44,7 +44,8 @@ __device__ __forceinline__ const float *input_row(const LayerF32Args &p, int g, 
 
 // RT: 32-row tiles in a workgroup (1 or 2), ROWS: workgroups that share the batch (batch = 32 RT ROWS).  Grid: grouped_grid(workers,
 // dout / 32 * ROWS).
-template <int RT, int ROWS>
+// LIST: p.worker (a choice at run time costs every launch 0.2 us: nothing is asked for before it is known).
+template <int RT, int ROWS, bool LIST>
 __global__ void __launch_bounds__(F32_THREADS) fwd_f32_kernel(LayerF32Args p)
 {
     extern __shared__ __attribute__((aligned(16))) float f32_smem[];
@@ -54,17 +55,17 @@ __global__ void __launch_bounds__(F32_THREADS) fwd_f32_kernel(LayerF32Args p)
     int g;
     unsigned local;
     if (!decode_group(blockIdx.x, (unsigned)(p.dout / F32_COLS) * ROWS, p.M, g, local)) return;      // a worker's blocks share an XCD (its A)
-    const int wk = p.worker ? p.worker[g] : g;
+    const int wk = LIST ? p.worker[g] : g, Mx = LIST ? p.Mx : p.M;
     const int64_t col0 = (int64_t)(local / ROWS) * F32_COLS;
     const int row0 = (int)(local % ROWS) * (32 * RT);
     float *stage = f32_smem + wave * (2 * F32_KS * F32_COLS);
-    const float bias = p.X[tiled_offset(p.Mx, wk, p.woff + p.din * p.dout + col0 + (t & 31))];     // for the end; requested first
+    const float bias = p.X[tiled_offset(Mx, wk, p.woff + p.din * p.dout + col0 + (t & 31))];     // for the end; requested first
     const int kr = lane >> 3, c4 = (lane & 7) * 4;               // this lane's piece of a staged W block
     const int64_t wcol = p.woff + col0 + c4;
     const int total = (int)(p.din / F32_KS);
     f32x4 fa[F32_DEPTH][RT], fw[F32_DEPTH];
     auto request_w = [&](int d, int s) {
-        fw[d] = *reinterpret_cast<const f32x4 *>(p.X + tiled_offset(p.Mx, wk, wcol + ((int64_t)s * F32_KS + kr) * p.dout));
+        fw[d] = *reinterpret_cast<const f32x4 *>(p.X + tiled_offset(Mx, wk, wcol + ((int64_t)s * F32_KS + kr) * p.dout));
     };
     // this wave's steps are wave, wave + 8, ...: n_mine of them.  Requests beyond the last one repeat it (in bounds, never
     // used), so that the loop over whole groups of F32_DEPTH steps has no branch and waits for exactly the loads it uses.
@@ -150,7 +151,7 @@ static size_t fwd_f32_lds(int RT)
 // HB = batch / 2: values of the A^T strip per lane.  Grid: grouped_grid(workers, ceil(din / 32) * ceil(dout / (32 * 4 * WG32_TILES)));
 // a wave takes WG32_TILES 32 x 32 blocks of dW, four blocks apart, with the same strip of A^T.
 constexpr int WG32_THREADS = 256, WG32_WAVES = WG32_THREADS / 64, WG32_TILES = 2;
-template <int HB, bool GATHER, bool UPDATE>
+template <int HB, bool GATHER, bool UPDATE, bool LIST = false>
 __global__ void __launch_bounds__(WG32_THREADS) wgrad_f32_kernel(LayerF32Args p)
 {
     __shared__ __attribute__((aligned(16))) float turn[UPDATE ? WG32_WAVES : 1][32][F32_COLS + 4];   // UPDATE: a wave's block, to be read by rows
@@ -165,7 +166,7 @@ __global__ void __launch_bounds__(WG32_THREADS) wgrad_f32_kernel(LayerF32Args p)
             const unsigned tile = bid / (unsigned)p.M;
             if (tile < (unsigned)p.n_tiles) {
                 const int at = (int)(bid - tile * (unsigned)p.M);
-                mix_subset_block<WG32_THREADS>(p.Mx, p.tiles[tile], p.worker ? p.worker[at] : at, at, p.skip, p.G, p.mix);
+                mix_subset_block<WG32_THREADS>(LIST ? p.Mx : p.M, p.tiles[tile], LIST ? p.worker[at] : at, at, p.skip, p.G, p.mix);
             }
             return;
         }
@@ -174,7 +175,7 @@ __global__ void __launch_bounds__(WG32_THREADS) wgrad_f32_kernel(LayerF32Args p)
     int g;
     unsigned local;
     if (!decode_group(bid, (unsigned)((p.din + 31) / 32) * groups, p.M, g, local)) return;   // a worker's blocks share an XCD (its dZ)
-    const int wk = p.worker ? p.worker[g] : g;
+    const int wk = LIST ? p.worker[g] : g, Mx = LIST ? p.Mx : p.M;
     const int ct0 = (int)(local % groups) * per_group + wave, ct_end = min(nct, (int)(local % groups) * per_group + per_group);
     if (ct0 >= ct_end) return;
     const int64_t f0 = (int64_t)(local / groups) * 32;
@@ -201,8 +202,8 @@ __global__ void __launch_bounds__(WG32_THREADS) wgrad_f32_kernel(LayerF32Args p)
     float wi = 0.0f;
     if constexpr (UPDATE) {
         m = p.mix.peer[g];
-        if ((unsigned)m >= (unsigned)p.Mx) m = wk;                // an index outside [0, M) is treated as a self draw
-        wi = p.mix.w[(size_t)wk * p.Mx + m];
+        if ((unsigned)m >= (unsigned)Mx) m = wk;                // an index outside [0, M) is treated as a self draw
+        wi = p.mix.w[(size_t)wk * Mx + m];
     }
     // UPDATE: eight lanes along the 32 columns of a row, 128-bit pieces, eight rows per pass
     const int uc = (lane & 7) * 4, ur = lane >> 3;
@@ -215,10 +216,10 @@ __global__ void __launch_bounds__(WG32_THREADS) wgrad_f32_kernel(LayerF32Args p)
             for (int u = 0; u < 4; ++u) {
                 const int64_t fr = f0 + 8 * u + ur < p.din ? f0 + 8 * u + ur : p.din - 1;
                 const int64_t j = p.woff + fr * p.dout + ct * F32_COLS + uc;
-                own[u] = tiled_offset(p.Mx, wk, j);
+                own[u] = tiled_offset(Mx, wk, j);
                 ux[u] = load4(p.mix.Xcur + own[u]);
                 uv[u] = load4(p.mix.V + own[u]);
-                up[u] = load4(p.mix.Xcur + tiled_offset(p.Mx, m, j));
+                up[u] = load4(p.mix.Xcur + tiled_offset(Mx, m, j));
             }
             __builtin_amdgcn_sched_barrier(0);
         }
@@ -253,7 +254,7 @@ __global__ void __launch_bounds__(WG32_THREADS) wgrad_f32_kernel(LayerF32Args p)
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
                 const int64_t fr = f0 + 8 * (v >> 2) + 4 * half + (v & 3);
-                if (fr < p.din) p.G[tiled_offset(p.Mx, wk, p.woff + fr * p.dout + ct * F32_COLS + col)] = acc[v];
+                if (fr < p.din) p.G[tiled_offset(Mx, wk, p.woff + fr * p.dout + ct * F32_COLS + col)] = acc[v];
             }
         }
     }
@@ -287,13 +288,14 @@ bool wgrad_f32_ok(const MlpPlan &p, int l) { return f32_layer_common(p, l); }
 
 hipError_t prepare_f32_layers()
 {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(fwd_f32_kernel<1, 1>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)fwd_f32_lds(1));
-    if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void *>(fwd_f32_kernel<1, 2>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)fwd_f32_lds(1));
-    if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void *>(fwd_f32_kernel<2, 1>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)fwd_f32_lds(2));
-    return e;
+    auto raise = [](auto *kernel, int RT) { return hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)fwd_f32_lds(RT)); };
+    for (hipError_t e : {raise(fwd_f32_kernel<1, 1, false>, 1), raise(fwd_f32_kernel<1, 2, false>, 1), raise(fwd_f32_kernel<2, 1, false>, 2),
+                         raise(fwd_f32_kernel<1, 1, true>, 1), raise(fwd_f32_kernel<1, 2, true>, 1), raise(fwd_f32_kernel<2, 1, true>, 2)})
+        if (e != hipSuccess) return e;
+    return hipSuccess;
 }
 
-void launch_fwd_f32(hipStream_t s, const MlpPlan &p, int l, const float *X)
+template <bool LIST> static void launch_fwd_rows(hipStream_t s, const MlpPlan &p, int l, const float *X)
 {
     const LayerF32Args a = layer_f32_args(p, l, X, nullptr, nullptr);
     const unsigned cols = (unsigned)(a.dout / F32_COLS);
@@ -301,15 +303,21 @@ void launch_fwd_f32(hipStream_t s, const MlpPlan &p, int l, const float *X)
     // A batch of 64: while two workgroups of 32 rows for each group of columns find a compute unit each, they halve the products that
     // a wave makes one after the other.  Per iteration of 784-512-10, one and two: 2 workers 31.7 and 28.7 us, 8 workers (256
     // workgroups) 40.5 and 37.1 us; 3072-1024-10, 2 workers 76 and 61 us; beyond, 8 workers (512) 164 and 174 us.
-    if (p.B == 32) hipLaunchKernelGGL((fwd_f32_kernel<1, 1>), dim3(grouped_grid(p.M, cols)), block, fwd_f32_lds(1), s, a);
-    else if (p.M * (int64_t)cols * 2 <= MF_XCD * XCD_CUS) hipLaunchKernelGGL((fwd_f32_kernel<1, 2>), dim3(grouped_grid(p.M, 2 * cols)), block, fwd_f32_lds(1), s, a);
-    else hipLaunchKernelGGL((fwd_f32_kernel<2, 1>), dim3(grouped_grid(p.M, cols)), block, fwd_f32_lds(2), s, a);
+    if (p.B == 32) hipLaunchKernelGGL((fwd_f32_kernel<1, 1, LIST>), dim3(grouped_grid(p.M, cols)), block, fwd_f32_lds(1), s, a);
+    else if (p.M * (int64_t)cols * 2 <= MF_XCD * XCD_CUS) hipLaunchKernelGGL((fwd_f32_kernel<1, 2, LIST>), dim3(grouped_grid(p.M, 2 * cols)), block, fwd_f32_lds(1), s, a);
+    else hipLaunchKernelGGL((fwd_f32_kernel<2, 1, LIST>), dim3(grouped_grid(p.M, cols)), block, fwd_f32_lds(2), s, a);
+}
+void launch_fwd_f32(hipStream_t s, const MlpPlan &p, int l, const float *X)
+{
+    if (p.worker) launch_fwd_rows<true>(s, p, l, X);
+    else launch_fwd_rows<false>(s, p, l, X);
 }
 
 template <int HB> static void launch_wgrad_half(hipStream_t s, const LayerF32Args &a, dim3 grid, bool update)
 {
     const dim3 block(WG32_THREADS);
-    if (a.gather && update) hipLaunchKernelGGL((wgrad_f32_kernel<HB, true, true>), grid, block, 0, s, a);
+    if (a.worker) hipLaunchKernelGGL((wgrad_f32_kernel<HB, true, true, true>), grid, block, 0, s, a);      // layer_list_ok(): the first layer, with its update
+    else if (a.gather && update) hipLaunchKernelGGL((wgrad_f32_kernel<HB, true, true>), grid, block, 0, s, a);
     else if (a.gather) hipLaunchKernelGGL((wgrad_f32_kernel<HB, true, false>), grid, block, 0, s, a);
     else if (update) hipLaunchKernelGGL((wgrad_f32_kernel<HB, false, true>), grid, block, 0, s, a);
     else hipLaunchKernelGGL((wgrad_f32_kernel<HB, false, false>), grid, block, 0, s, a);

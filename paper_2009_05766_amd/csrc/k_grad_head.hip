@@ -44,12 +44,12 @@ struct HeadArgs {
     float *dh;                      // [M][B][H]
     float *loss;                    // [M]
     int M, B, H, C;
-    int pairs;                      // logits by pairs of steps
-    int Mx; const int32_t *worker;  // see MlpPlan
     int64_t woff;                   // W [H][C] of the last layer inside a parameter row, its bias behind it
     int64_t boff_below;             // bias of the layer below
     int64_t D, ld;
     MixArgs mix;                    // UPDATE
+    int Mx; const int32_t *worker;  // LIST: see MlpPlan
+    int pairs;                      // host: logits by pairs of steps
 };
 
 __device__ __forceinline__ f32x4 mfma_16x16x4(float a, float b, f32x4 acc) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, acc, 0, 0, 0); }
@@ -79,10 +79,10 @@ __device__ __forceinline__ int64_t head_row(const HeadArgs &p, int g, int wk, in
 
 // Grid: (ceil(B / 16), workers).  CT: tiles of sixteen classes.  How the input's rows are read: feature by feature, in pieces of
 // four features, in pieces of a number of features that fills the steps of sixteen (no bounds to respect).
-// TWO: a wave's run is summed in pairs of steps, the parts that resident_mlp_kernel's workgroups have, added in their
+// LIST: p.worker (see k_grad_f32.hip).  TWO: a wave's run is summed in pairs of steps, the parts that resident_mlp_kernel's workgroups have, added in their
 // order; eight steps per wave at most then.
 enum : int { HL_SINGLE = 0, HL_PIECES = 1, HL_WHOLE = 2 };
-template <bool BF, int MODE, int CT, int NW, bool TWO = false>
+template <bool BF, int MODE, int CT, int NW, bool TWO = false, bool LIST = false>
 __global__ void __launch_bounds__(64 * NW) head_logits_kernel(HeadArgs p)
 {
     constexpr int PER_WAVE = TWO ? HD_STEPS / 2 : 1;         // sums
@@ -94,9 +94,9 @@ __global__ void __launch_bounds__(64 * NW) head_logits_kernel(HeadArgs p)
     // features' products then masked
     const int steps = (H + 15) / 16, per = TWO ? (steps / 2 + NW - 1) / NW * 2 : (steps + NW - 1) / NW;
     const int s_begin = kp * per, s_end = s_begin + per < steps ? s_begin + per : steps;
-    const int wk = p.worker ? p.worker[g] : g;
+    const int wk = LIST ? p.worker[g] : g, Mx = LIST ? p.Mx : p.M;
     const int64_t a_row = head_row(p, g, wk, 16 * rt + r < B ? 16 * rt + r : B - 1);
-    const HeadParams at(p.Mx, wk, p.woff);
+    const HeadParams at(Mx, wk, p.woff);
     const float *Xg = p.X + at.base;
     uint32_t wcol[CT];
 #pragma unroll
@@ -199,7 +199,7 @@ __global__ void __launch_bounds__(64 * NW) head_logits_kernel(HeadArgs p)
 // RT: 16-row tiles of the batch (1, 2, 4, 8 or 16; rows past the batch count as zeros).  CT: tiles of sixteen classes.  FIRST: the
 // only layer (softmax regression): no error for a layer below.  UPDATE (then it is
 // the only layer): the momentum step and the mix (Eq. (c0), (c1)) are applied to every column of the worker.  Grid: (ceil(H / 64), workers).
-template <bool BF, int RT, int CT, bool FIRST, bool UPDATE>
+template <bool BF, int RT, int CT, bool FIRST, bool UPDATE, bool LIST>
 __global__ void __launch_bounds__(HD_THREADS) head_grads_kernel(HeadArgs p)
 {
     constexpr int BP = 16 * RT, CP = 16 * CT, tp = BP + 16;      // tp: pitch of the transposed dZ, rows 16 apart in banks
@@ -209,12 +209,12 @@ __global__ void __launch_bounds__(HD_THREADS) head_grads_kernel(HeadArgs p)
     const int B = p.B, H = p.H, C = p.C;
     const int g = blockIdx.y, t = threadIdx.x, lane = t & 63, r = lane & 15, q = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
-    const int wk = p.worker ? p.worker[g] : g;
+    const int wk = LIST ? p.worker[g] : g, Mx = LIST ? p.Mx : p.M;
     const bool first = blockIdx.x == 0;          // the workgroup that also writes what does not split by hidden units
     const int KT = (H + 15) / 16, kt = (int)blockIdx.x * HD_WAVES + wave;
     const int ktc = kt < KT ? kt : 0;            // waves past the end repeat the first block and store nothing
     const int hc = 16 * ktc + r < H ? 16 * ktc + r : H - 1;
-    const HeadParams at(p.Mx, wk, p.woff);
+    const HeadParams at(Mx, wk, p.woff);
     const float *Xg = p.X + at.base;
     // requests: this wave's 16 columns of the input (all batch rows; gathered rows by number first), its 16 rows of W, and dZ.
     // Rows past the batch repeat the last one and count as zeros.
@@ -265,8 +265,8 @@ __global__ void __launch_bounds__(HD_THREADS) head_grads_kernel(HeadArgs p)
     };
     if constexpr (UPDATE) {
         m = p.mix.peer[g];
-        if ((unsigned)m >= (unsigned)p.Mx) m = wk;            // an index outside [0, M) is treated as a self draw
-        wi = p.mix.w[(size_t)wk * p.Mx + m];
+        if ((unsigned)m >= (unsigned)Mx) m = wk;            // an index outside [0, M) is treated as a self draw
+        wi = p.mix.w[(size_t)wk * Mx + m];
         peer_shift = ((size_t)m - (size_t)wk) << TILE_SHIFT;   // from a worker's element to its peer's
 #pragma unroll
         for (int c = 0; c < CT; ++c)
@@ -302,7 +302,7 @@ __global__ void __launch_bounds__(HD_THREADS) head_grads_kernel(HeadArgs p)
             if (lane == 0) p.loss[wk] = lrow / (float)B;
         }
         for (int64_t e = t; e < p.ld - p.D; e += HD_THREADS) {
-            const size_t own = tiled_offset_quick(p.Mx, wk, p.D + e);
+            const size_t own = tiled_offset_quick(Mx, wk, p.D + e);
             p.G[own] = 0.0f;
             if constexpr (UPDATE) update(own, p.mix.Xcur[own], p.mix.V[own], 0.0f, p.mix.Xcur[own + peer_shift]);
         }
@@ -367,7 +367,7 @@ __global__ void __launch_bounds__(HD_THREADS) head_grads_kernel(HeadArgs p)
         }
         colsum += __shfl_xor(colsum, 16);
         colsum += __shfl_xor(colsum, 32);
-        if (q == 0 && col_ok) p.G[tiled_offset_quick(p.Mx, wk, p.boff_below + 16 * kt + r)] = colsum;
+        if (q == 0 && col_ok) p.G[tiled_offset_quick(Mx, wk, p.boff_below + 16 * kt + r)] = colsum;
     }
 }
 
@@ -395,42 +395,49 @@ bool head_parts_of_two(const MlpPlan &p)
     return p.n_layers > 1 && head_ok(p) && !p.bf16 && C <= 16 && H % 32 == 0 && H <= 16 * HD_STEPS * HL_MANY;
 }
 
-template <bool BF, int CT, int NW> static void launch_logits_waves(hipStream_t s, const HeadArgs &a)
+template <bool BF, int CT, int NW, bool LIST> static void launch_logits_waves(hipStream_t s, const HeadArgs &a)
 {
     const dim3 grid((unsigned)((a.B + 15) / 16), (unsigned)a.M), block(64 * NW);
     // pieces of four features need rows that start at multiples of their size
     const bool pieces = a.H % 4 == 0 && reinterpret_cast<uintptr_t>(a.in) % (BF ? 8 : 16) == 0;
-    if constexpr (!BF && CT == 1)
+    if constexpr (!BF && CT == 1 && !LIST)
         if (a.pairs && pieces) {
             hipLaunchKernelGGL((head_logits_kernel<BF, HL_WHOLE, CT, NW, true>), grid, block, 0, s, a);
             return;
         }
-    if (pieces && a.H % 16 == 0) hipLaunchKernelGGL((head_logits_kernel<BF, HL_WHOLE, CT, NW>), grid, block, 0, s, a);
-    else if (pieces) hipLaunchKernelGGL((head_logits_kernel<BF, HL_PIECES, CT, NW>), grid, block, 0, s, a);
-    else hipLaunchKernelGGL((head_logits_kernel<BF, HL_SINGLE, CT, NW>), grid, block, 0, s, a);
+    if (pieces && a.H % 16 == 0) hipLaunchKernelGGL((head_logits_kernel<BF, HL_WHOLE, CT, NW, false, LIST>), grid, block, 0, s, a);
+    else if (pieces) hipLaunchKernelGGL((head_logits_kernel<BF, HL_PIECES, CT, NW, false, LIST>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((head_logits_kernel<BF, HL_SINGLE, CT, NW, false, LIST>), grid, block, 0, s, a);
 }
-template <bool BF, int CT> static void launch_logits(hipStream_t s, const HeadArgs &a)
+template <bool BF, int CT, bool LIST> static void launch_logits(hipStream_t s, const HeadArgs &a)
 {
-    if ((a.H + 15) / 16 <= HL_FEW * HD_STEPS) launch_logits_waves<BF, CT, HL_FEW>(s, a);
-    else launch_logits_waves<BF, CT, HL_MANY>(s, a);
+    if ((a.H + 15) / 16 <= HL_FEW * HD_STEPS) launch_logits_waves<BF, CT, HL_FEW, LIST>(s, a);
+    else launch_logits_waves<BF, CT, HL_MANY, LIST>(s, a);
 }
 
-template <bool BF, int CT, bool FIRST, bool UPDATE> static void launch_grads(hipStream_t s, const HeadArgs &a)
+template <bool BF, int CT, bool FIRST, bool UPDATE, bool LIST> static void launch_grads(hipStream_t s, const HeadArgs &a)
 {
     const dim3 grid((unsigned)(((a.H + 15) / 16 + HD_WAVES - 1) / HD_WAVES), (unsigned)a.M), block(HD_THREADS);
-    if (a.B <= 16) hipLaunchKernelGGL((head_grads_kernel<BF, 1, CT, FIRST, UPDATE>), grid, block, 0, s, a);
-    else if (a.B <= 32) hipLaunchKernelGGL((head_grads_kernel<BF, 2, CT, FIRST, UPDATE>), grid, block, 0, s, a);
-    else if (a.B <= 64) hipLaunchKernelGGL((head_grads_kernel<BF, 4, CT, FIRST, UPDATE>), grid, block, 0, s, a);
-    else if (a.B <= 128) hipLaunchKernelGGL((head_grads_kernel<BF, 8, CT, FIRST, UPDATE>), grid, block, 0, s, a);
-    else hipLaunchKernelGGL((head_grads_kernel<BF, 16, CT, FIRST, UPDATE>), grid, block, 0, s, a);
+    if (a.B <= 16) hipLaunchKernelGGL((head_grads_kernel<BF, 1, CT, FIRST, UPDATE, LIST>), grid, block, 0, s, a);
+    else if (a.B <= 32) hipLaunchKernelGGL((head_grads_kernel<BF, 2, CT, FIRST, UPDATE, LIST>), grid, block, 0, s, a);
+    else if (a.B <= 64) hipLaunchKernelGGL((head_grads_kernel<BF, 4, CT, FIRST, UPDATE, LIST>), grid, block, 0, s, a);
+    else if (a.B <= 128) hipLaunchKernelGGL((head_grads_kernel<BF, 8, CT, FIRST, UPDATE, LIST>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((head_grads_kernel<BF, 16, CT, FIRST, UPDATE, LIST>), grid, block, 0, s, a);
 }
 
 template <bool BF, int CT> static void launch_both(hipStream_t s, const HeadArgs &a, bool only_layer, bool update)
 {
-    launch_logits<BF, CT>(s, a);
-    if (!only_layer) launch_grads<BF, CT, false, false>(s, a);
-    else if (update) launch_grads<BF, CT, true, true>(s, a);
-    else launch_grads<BF, CT, true, false>(s, a);
+    if constexpr (!BF)
+        if (a.worker) {                          // layer_list_ok(): fp32, a single layer with its update
+            launch_logits<BF, CT, true>(s, a);
+            if (!only_layer) launch_grads<BF, CT, false, false, true>(s, a);
+            else launch_grads<BF, CT, true, true, true>(s, a);
+            return;
+        }
+    launch_logits<BF, CT, false>(s, a);
+    if (!only_layer) launch_grads<BF, CT, false, false, false>(s, a);
+    else if (update) launch_grads<BF, CT, true, true, false>(s, a);
+    else launch_grads<BF, CT, true, false, false>(s, a);
 }
 
 void launch_head(hipStream_t s, const MlpPlan &p, const float *X, float *G, const MixArgs *tail)
