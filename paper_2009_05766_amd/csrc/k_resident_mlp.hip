@@ -555,14 +555,14 @@ static ResidentKernel resident_kernel(int B) { return B == 32 ? resident_mlp_ker
 hipError_t prepare_resident_mlp(const MlpPlan &p, int *resident)
 {
     int dev = 0, per_cu = 0;
-    hipDeviceProp_t prop;
+    int cus = 0;
     const void *kernel = reinterpret_cast<const void *>(resident_kernel(p.B));
     *resident = 0;
     hipError_t e = hipGetDevice(&dev);
-    if (e == hipSuccess) e = hipGetDeviceProperties(&prop, dev);
+    if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     if (e == hipSuccess) e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, RM_LDS_LIMIT);
     if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, RM_THREADS, rm_lds(p.B, p.dims[0], rm_padding(p)));
-    if (e == hipSuccess) *resident = per_cu * prop.multiProcessorCount;
+    if (e == hipSuccess) *resident = per_cu * cus;
     return e;
 }
 

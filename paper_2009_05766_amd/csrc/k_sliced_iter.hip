@@ -369,17 +369,17 @@ int sliced_iter_slices(const MlpPlan &p) { return sl_slices(p.dims[0]); }
 hipError_t prepare_sliced_iter(const MlpPlan &p, int *resident)
 {
     int dev = 0;
-    hipDeviceProp_t prop;
+    int cus = 0;
     *resident = 0;
     hipError_t e = hipGetDevice(&dev);
-    if (e == hipSuccess) e = hipGetDeviceProperties(&prop, dev);
+    if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     for (SlicedKernel k : {sliced_kernel<true>(p.B), sliced_kernel<false>(p.B)}) {
         const void *kernel = reinterpret_cast<const void *>(k);
         int per_cu = 0;
         if (e == hipSuccess) e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, SL_LDS_LIMIT);
         if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, SL_THREADS, sl_lds(p.B, sl_padding(p)));
         if (e != hipSuccess) return e;
-        const int held = per_cu * prop.multiProcessorCount;
+        const int held = per_cu * cus;
         *resident = *resident == 0 || held < *resident ? held : *resident;
     }
     return hipSuccess;

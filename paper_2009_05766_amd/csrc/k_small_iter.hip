@@ -659,12 +659,12 @@ hipError_t launch_small_iter(hipStream_t s, const SmallIterLaunch &a)
 int small_iter_max_resident(int B, int64_t din, int64_t dout, int64_t ld)
 {
     int per_cu = 0, dev = 0;
-    hipDeviceProp_t prop;
-    if (hipGetDevice(&dev) != hipSuccess || hipGetDeviceProperties(&prop, dev) != hipSuccess) return 0;
+    int cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, small_iter_kernel<SI_RUN>(B, din, dout, ld), SI_THREADS,
                                                      small_iter_lds(B, (int)din, (int)dout, ld)) != hipSuccess)
         return 0;
-    return per_cu * prop.multiProcessorCount;
+    return per_cu * cus;
 }
 
 }  // namespace netmax
