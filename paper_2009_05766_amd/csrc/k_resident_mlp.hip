@@ -366,26 +366,28 @@ __global__ void __launch_bounds__(RM_THREADS) resident_mlp_kernel(ResidentArgs p
                 dhs[b * RM_HP + 16 * u + r] = hs[b * RM_HP + 16 * u + r] > 0.0f ? dh[v] : 0.0f;
             }
         }
-        // the first strip's operands and the peer's parameters of it
-        float a[HB], xp[2][16];
-        auto request_strip = [&](int strip, float (&x)[16]) {
+        float a[HB], xp[16];
+        auto request_rows = [&](int strip) {
             const int lane = opaque(t0) & 63, col = lane & 31, half = lane >> 5;
             const uint32_t f4 = (uint32_t)min(32 * strip + col, p.din - 1) * 4u;
             const uint32_t *rows = ro + half;
 #pragma unroll
             for (int j = 0; j < HB; ++j) a[j] = *at_bytes(shard, rows[2 * j] + f4);
+        };
+        auto request_peer = [&](int strip) {
+            const int lane = opaque(t0) & 63, col = lane & 31, half = lane >> 5;
             const float *Xp = Xcur + shift;
             if (32 * strip + 32 <= p.din) {
                 const uint32_t from = w1_from(col, half, strip);
 #pragma unroll
-                for (int v = 0; v < 16; ++v) x[v] = __hip_atomic_load(at_bytes(Xp, w1_next(from, v)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                for (int v = 0; v < 16; ++v) xp[v] = __hip_atomic_load(at_bytes(Xp, w1_next(from, v)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             } else {
 #pragma unroll
                 for (int v = 0; v < 16; ++v)
-                    x[v] = __hip_atomic_load(at_bytes(Xp, w1_at(col, min(w1_row(half, strip, v), p.din - 1))), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    xp[v] = __hip_atomic_load(at_bytes(Xp, w1_at(col, min(w1_row(half, strip, v), p.din - 1))), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
         };
-        if (wave >= 2 && strip0 < n_strips) request_strip(strip0, xp[0]);
+        if (wave >= 2 && strip0 < n_strips) request_rows(strip0);
         __syncthreads();                                      // the units' error; W2 has been read
         // ---- waves 0 and 1, sixteen units each: dW2 = h^T dZ2 and the column sums of the error; their update (Eq. (c0), (c1)).  The last wave:
         // the output bias.
@@ -394,7 +396,7 @@ __global__ void __launch_bounds__(RM_THREADS) resident_mlp_kernel(ResidentArgs p
 #pragma unroll
             for (int v = 0; v < 4; ++v) x2p[v] = __hip_atomic_load(at_bytes(Xcur + shift, w2_at[v]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             const float bias_p = __hip_atomic_load(at_bytes(Xcur + shift, bias_at), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (strip0 < n_strips) request_strip(strip0, xp[0]);
+            if (strip0 < n_strips) request_rows(strip0);
             f32x4 dw = {0.0f, 0.0f, 0.0f, 0.0f};
             float colsum = 0.0f;
 #pragma unroll
@@ -472,6 +474,8 @@ __global__ void __launch_bounds__(RM_THREADS) resident_mlp_kernel(ResidentArgs p
             const int strip = strip0 + RM_WAVES * n;
             if (strip >= n_strips) break;
             const int lane = opaque(t0) & 63, col = lane & 31, half = lane >> 5;
+            request_peer(strip);
+            __builtin_amdgcn_sched_barrier(0);
             rm_f32x16 dw;
 #pragma unroll
             for (int v = 0; v < 16; ++v) dw[v] = 0.0f;
@@ -479,7 +483,7 @@ __global__ void __launch_bounds__(RM_THREADS) resident_mlp_kernel(ResidentArgs p
 #pragma unroll
             for (int j = 0; j < HB; ++j) dw = __builtin_amdgcn_mfma_f32_32x32x2f32(a[j], zs[2 * j * RM_HP], dw, 0, 0, 0);
             __builtin_amdgcn_sched_barrier(0);
-            if (n + 1 < RM_STRIPS && strip + RM_WAVES < n_strips) request_strip(strip + RM_WAVES, xp[(n + 1) & 1]);
+            if (n + 1 < RM_STRIPS && strip + RM_WAVES < n_strips) request_rows(strip + RM_WAVES);
             __builtin_amdgcn_sched_barrier(0);
             const uint32_t from = w1_from(col, half, strip);
             float *ws = wl + (32 * strip + 4 * half) * RM_COLS + col;
@@ -489,7 +493,7 @@ __global__ void __launch_bounds__(RM_THREADS) resident_mlp_kernel(ResidentArgs p
                     if (!decltype(whole)::value && w1_row(half, strip, v) >= p.din) continue;
                     float *wv = ws + (8 * (v >> 2) + (v & 3)) * RM_COLS;
                     float xn, vn;
-                    momentum_mix1(*wv, vel[n][v], dw[v], xp[n & 1][v], wi, p.alpha, p.mu, p.wd, xn, vn);
+                    momentum_mix1(*wv, vel[n][v], dw[v], xp[v], wi, p.alpha, p.mu, p.wd, xn, vn);
                     vel[n][v] = vn;
                     *wv = xn;
                     __hip_atomic_store(at_bytes(Xnext, w1_next(from, v)), xn, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
