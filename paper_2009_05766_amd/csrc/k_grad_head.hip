@@ -79,13 +79,14 @@ __device__ __forceinline__ int64_t head_row(const HeadArgs &p, int g, int wk, in
 
 // Grid: (ceil(B / 16), workers).  CT: tiles of sixteen classes.  How the input's rows are read: feature by feature, in pieces of
 // four features, in pieces of a number of features that fills the steps of sixteen (no bounds to respect).
-// LIST: p.worker (see k_grad_f32.hip).  TWO: a wave's run is summed in pairs of steps, the parts that resident_mlp_kernel's workgroups have, added in their
-// order; eight steps per wave at most then.
+// LIST: p.worker (see k_grad_f32.hip).  TWO: a wave's run is summed in pairs of steps, the parts that resident_mlp_kernel's workgroups have, these
+// and then the waves' sums two by two; eight steps per wave at most then.
 enum : int { HL_SINGLE = 0, HL_PIECES = 1, HL_WHOLE = 2 };
 template <bool BF, int MODE, int CT, int NW, bool TWO = false, bool LIST = false>
 __global__ void __launch_bounds__(64 * NW) head_logits_kernel(HeadArgs p)
 {
     constexpr int PER_WAVE = TWO ? HD_STEPS / 2 : 1;         // sums
+    static_assert(!TWO || PER_WAVE == 4, "the sums are added two by two");
     __shared__ float part[NW][16][16 * CT];
     const int B = p.B, H = p.H, C = p.C;
     const int g = blockIdx.y, rt = blockIdx.x, t = threadIdx.x, lane = t & 63, r = lane & 15, q = lane >> 4;
@@ -158,8 +159,7 @@ __global__ void __launch_bounds__(64 * NW) head_logits_kernel(HeadArgs p)
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
             float sum = acc[0][c][v];
-#pragma unroll
-            for (int u = 1; u < PER_WAVE; ++u) sum += acc[u][c][v];      // pairs past the wave's run are zeros
+            if constexpr (TWO) sum = (sum + acc[1][c][v]) + (acc[2][c][v] + acc[3][c][v]);       // pairs past the wave's run are zeros
             part[kp][4 * q + v][16 * c + r] = sum;
         }
     __syncthreads();
@@ -172,8 +172,13 @@ __global__ void __launch_bounds__(64 * NW) head_logits_kernel(HeadArgs p)
         const int k = 16 * c + l16;
         cls[c] = k < C;
         float sum = part[0][row][k];
+        if constexpr (TWO) {
+            sum = (sum + part[1][row][k]) + (part[2][row][k] + part[3][row][k]);
+            if constexpr (NW == 8) sum += (part[4][row][k] + part[5][row][k]) + (part[6][row][k] + part[7][row][k]);
+        } else {
 #pragma unroll
-        for (int w = 1; w < NW; ++w) sum += part[w][row][k];
+            for (int w = 1; w < NW; ++w) sum += part[w][row][k];
+        }
         z[c] = cls[c] ? sum + bias[c] : -INFINITY;
         mx = fmaxf(mx, z[c]);
     }

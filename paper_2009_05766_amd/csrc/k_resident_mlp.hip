@@ -8,11 +8,12 @@
 // below needs no other unit: dZ2 gives dW2's rows, the error of the units and their columns of dW1, which are updated where the product leaves
 // them.  The peer's columns come from the workgroup of the same units, which wrote them half an iteration before.
 //
-// 784-512-10, batch 64, 16 workers (all 256 compute units), four iterations: 146 to 154 us (box to box), the separate kernels 229.  An iteration takes 31 us: forward
-// 7.3 (its matrix instructions 5.3), the waves' tiles added 1.9, exchange and softmax 4.5, error 1.1, the rows of W2 3 (two waves, beside the
-// others' first strips), dW1 and update 13.5 (matrix instructions 5.4, the rest addresses and waiting: without any access to memory the whole
-// call takes 131 us, without the products 133).  What it is made of: loads in global and not in flat address space (169 -> 143 us), the
-// next strip's loads before this one's stores, addresses as 32-bit byte offsets from a strip's first row, one path for all features of a strip.
+// 784-512-10, batch 64, 16 workers (all 256 compute units), four iterations: 135 us, the separate kernels 229.  An iteration takes 27 us:
+// forward 7.3 (its matrix instructions 5.3), the waves' tiles added 1.9, exchange and softmax 4.5, error 1.1, dW1 and its update the rest, beside
+// them the rows of W2 (3, two waves).  The strips of dW1 are bound by addresses and waiting, not by their matrix instructions (5.4).  What it
+// is made of: loads in global and not in flat address space (169 -> 143 us), the next strip's batch rows asked for before this one's stores, the
+// peer's parameters only ahead of the strip's own products (12 registers spilled instead of 74: 148 -> 135 us), addresses as 32-bit byte
+// offsets from a strip's first row, one path for all features of a strip.
 //
 // The sums are those of fwd_f32_kernel, head_logits_kernel, head_grads_kernel and wgrad_f32_kernel, in their order: the results are theirs bit
 // for bit.
@@ -30,7 +31,7 @@ namespace netmax {
 constexpr int RM_THREADS = 512, RM_WAVES = RM_THREADS / 64, RM_COLS = 32, RM_KS = 8, RM_DEPTH = 4, RM_AHEAD = 16;
 constexpr int RM_STRIPS = 4;                    // strips of 32 features per wave: up to 1024 features
 constexpr int RM_MAX_C = 16, RM_P16 = RM_MAX_C + 4, RM_HP = RM_COLS + 4, RM_PP = RM_COLS + 1, RM_MAX_PAD = 2048;
-constexpr int RM_WORDS = 16;                    // partial logits asked for together
+constexpr int RM_WORDS = 16;                    // partial logits asked for together: those of four runs of at most four
 constexpr int RM_LDS_LIMIT = 160 * 1024 - 512;
 
 struct ResidentArgs {
@@ -295,12 +296,11 @@ __global__ void __launch_bounds__(RM_THREADS) resident_mlp_kernel(ResidentArgs p
             constexpr int VPW = T16 * 4 / RM_WAVES;           // of a lane's four rows
             const int tile = wave % T16, v0 = wave / T16 * VPW;
             const unsigned long long *from = p.words + words_of + (size_t)tile * 256 + 64 * v0;
-            float z[VPW], zr[VPW];                            // the sum, that of the current run
+            float z[VPW];
 #pragma unroll
-            for (int e = 0; e < VPW; ++e) z[e] = zr[e] = 0.0f;
-            int in_run = 0;
+            for (int e = 0; e < VPW; ++e) z[e] = 0.0f;
             long long polls = 0;
-            for (int k0 = 0; k0 < p.NB; k0 += RM_WORDS) {
+            for (int k0 = 0; k0 < p.NB; k0 += 4 * p.run) {    // the parts of four waves of head_logits_kernel
                 unsigned long long word[RM_WORDS][VPW];
                 bool here;
                 do {
@@ -315,18 +315,26 @@ __global__ void __launch_bounds__(RM_THREADS) resident_mlp_kernel(ResidentArgs p
 #pragma unroll
                         for (int e = 0; e < VPW; ++e) here &= (unsigned)(word[k][e] >> 32) == ticket;
                 } while ((p.patience == 0 || __any(!here && r < p.C)) && !gives_up(++polls, p.fault, p.patience));
+                auto part = [&](int k, int e) { return k0 + k < p.NB ? __uint_as_float((unsigned)word[k][e]) : 0.0f; };
+                auto add = [&](auto run) {
+                    constexpr int R = decltype(run)::value;
 #pragma unroll
-                for (int k = 0; k < RM_WORDS; ++k)
-                    if (k0 + k < p.NB) {
-                        const bool begins = in_run == 0, ends = in_run + 1 == p.run || k0 + k + 1 == p.NB, first_run = k0 + k < p.run;
-                        in_run = ends ? 0 : in_run + 1;
+                    for (int e = 0; e < VPW; ++e) {
+                        float of[4];
 #pragma unroll
-                        for (int e = 0; e < VPW; ++e) {
-                            const float w = __uint_as_float((unsigned)word[k][e]);
-                            zr[e] = begins ? w : zr[e] + w;
-                            z[e] = ends ? (first_run ? zr[e] : z[e] + zr[e]) : z[e];
+                        for (int w = 0; w < 4; ++w) {
+                            of[w] = part(R * w, e);
+                            if constexpr (R > 1) of[w] += part(R * w + 1, e);
+                            if constexpr (R == 3) of[w] += part(R * w + 2, e);
+                            if constexpr (R == 4) of[w] += part(R * w + 2, e) + part(R * w + 3, e);
                         }
+                        z[e] += (of[0] + of[1]) + (of[2] + of[3]);
                     }
+                };
+                if (p.run == 1) add(std::integral_constant<int, 1>{});
+                else if (p.run == 2) add(std::integral_constant<int, 2>{});
+                else if (p.run == 3) add(std::integral_constant<int, 3>{});
+                else add(std::integral_constant<int, 4>{});
             }
             if (wave == 0) seen = arrivals(p.rows_count + 32 * nb);
             const bool real = r < p.C;
@@ -467,8 +475,8 @@ __global__ void __launch_bounds__(RM_THREADS) resident_mlp_kernel(ResidentArgs p
             if (lane == 0) p.loss[i] = l / (float)B;
         }
         // ---- dW1 = A^T dZ1 strip by strip (32 features x 32 units), the batch rows straight from memory; updated where the product leaves
-        // it.  The next strip's operands and peer's parameters are asked for before this one's results are stored: a load waited for behind a
-        // store waits for the store.
+        // it.  The next strip's batch rows are asked for before this one's results are stored, its peer's parameters ahead of its products: a
+        // load waited for behind a store waits for the store.
 #pragma unroll
         for (int n = 0; n < RM_STRIPS; ++n) {
             const int strip = strip0 + RM_WAVES * n;
@@ -530,17 +538,18 @@ bool resident_mlp_ok(const MlpPlan &p)
            rm_padding(p) <= RM_MAX_PAD && rm_lds(p.B, p.dims[0], rm_padding(p)) <= (size_t)RM_LDS_LIMIT;
 }
 // Whether n iterations are faster here than by the separate kernels, from a model of both in us (features x batch = the work of a
-// workgroup; the separate kernels' time grows with the parameters once their 3 x 16 MB leave the L2).  Measured, separate and here, 512
-// hidden units; for 2, 8 and 16 workers (32, 128, 256 workgroups):
-//   one iteration   128 features, batch 64 28.3 and 24.6, 28.6 and 24.7, 31.3 and 25.7;   256, 64 29.7 and 31.6, 30.1 and 31.2, 34.9 and 33.2
-//                   784, batch 32 30.1 and 32.6, 35.8 and 33.5, 48.3 and 39.0;   784, 64 32.9 and 49.2, 40.2 and 49.9, 56.8 and 54.8
-//   four            128, 64 89 and 58, 93 and 58, 106 and 62;   256, 64 97 and 80, 101 and 79, 121 and 82
-//                   784, 32 100 and 86, 123 and 87, 178 and 95;   784, 64 112 and 136, 142 and 136, 212 and 142
+// workgroup; the separate kernels' time grows with the parameters once their 3 x 16 MB leave the L2), fitted to 330 shapes of 96 to 784
+// features, 256 to 1024 hidden units, 2 to 16 workers; next to the line it errs by up to 4 %.  Measured, separate and here, 512 hidden
+// units; for 2, 8 and 16 workers (32, 128, 256 workgroups):
+//   one iteration   128 features, batch 64 28.9 and 22.0, 29.1 and 22.1, 31.5 and 22.9;   256, 64 29.5 and 28.8, 30.4 and 28.4, 35.7 and 29.7
+//                   784, batch 32 30.3 and 34.9, 35.9 and 35.5, 48.7 and 40.2;   784, 64 33.2 and 44.9, 41.0 and 45.4, 57.0 and 49.4
+//   four            128, 64 90 and 57, 93 and 57, 106 and 59;   256, 64 97 and 77, 101 and 76, 122 and 78
+//                   784, 32 100 and 92, 122 and 93, 178 and 100;   784, 64 112 and 128, 143 and 128, 212 and 131
 bool resident_mlp_pays(const MlpPlan &p, int n_iters)
 {
     const double work = 1e-3 * (double)p.dims[0] * p.B, groups = (double)p.M * (double)(p.dims[1] / RM_COLS);
     const double traffic = 0.15 * fmax(0.0, 1e-3 * groups * (double)p.dims[0] - 50.0);
-    const double here = 15.0 + 0.69 * work + (p.B > 32 ? 3.5 : 0.0) + (n_iters - 1) * (7.0 + 0.44 * work);
+    const double here = 20.5 + 0.56 * work + (n_iters - 1) * (7.5 + 0.38 * work);
     return here < 28.0 + 0.1 * work + traffic + (n_iters - 1) * (16.5 + 0.2 * work + traffic);
 }
 int resident_mlp_grid(const MlpPlan &p) { return (int)grouped_grid(p.M, (unsigned)(p.dims[1] / RM_COLS)); }

@@ -228,7 +228,7 @@ void launch_tile_wgrad(hipStream_t s, const MlpPlan &p, int l, float *G, int cur
 // Last layer with at most 32 classes, fp32 or bfloat16 operands (k_grad_head.hip): from its input to the error of the layer
 // below in two kernels: logits, loss, dW, db, dH and the column sums of dH.
 bool head_ok(const MlpPlan &p);
-// Its logits are sums of parts of 32 hidden units in their order: head_pairs_per_wave() of them at a time, then these.
+// Its logits are then sums of parts of 32 hidden units, added two by two: head_pairs_per_wave() of them at a time, then these.
 bool head_parts_of_two(const MlpPlan &p);
 int head_pairs_per_wave(const MlpPlan &p);
 void launch_head(hipStream_t s, const MlpPlan &p, const float *X, float *G, const MixArgs *tail);

@@ -128,7 +128,7 @@ def test_workgroups_that_give_up_are_reported(dims):
     dict(M=3, dims=(64, 32, 10), batch=64), dict(M=2, dims=(8, 64, 3), batch=32), dict(M=5, dims=(264, 96, 16), batch=32), dict(M=16, dims=(784, 512, 10), batch=64),
     dict(M=9, dims=(784, 160, 10), batch=64), dict(M=3, dims=(856, 64, 2), batch=32), dict(M=2, dims=(200, 1024, 7), batch=64), dict(M=128, dims=(40, 64, 5), batch=32),
     # more units than words asked for together; more workgroups than compute units, columns that do not fit LDS (the separate kernels)
-    dict(M=4, dims=(96, 800, 10), batch=64), dict(M=17, dims=(96, 512, 10), batch=64), dict(M=2, dims=(1000, 64, 10), batch=32),
+    dict(M=4, dims=(96, 800, 10), batch=64), dict(M=3, dims=(96, 544, 10), batch=32), dict(M=3, dims=(64, 352, 4), batch=64), dict(M=17, dims=(96, 512, 10), batch=64), dict(M=2, dims=(1000, 64, 10), batch=32),
 ])
 def test_iterations_of_resident_perceptrons(over):
     """One hidden layer: every workgroup keeps 32 units of a worker.  All state, losses and hidden activations are the separate calls' bits;
