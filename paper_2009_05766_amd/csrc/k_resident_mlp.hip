@@ -113,6 +113,12 @@ __global__ void __launch_bounds__(RM_THREADS) resident_mlp_kernel(ResidentArgs p
             if (lane == 0) to[k * RM_WAVES] = hits;
         }
     };
+    auto drawn_peer = [&](int group, int at) {
+        const int32_t *counts = cnt + group * (RM_AHEAD * RM_WAVES) + at * RM_WAVES;
+        int hits = counts[0];
+        for (int w = 1; w < RM_WAVES && 64 * w < p.M; ++w) hits += counts[w];
+        return __builtin_amdgcn_readfirstlane(hits < last_i ? hits : last_i);
+    };
     // rows 8 (v / 4) + 4 half + v % 4 of a strip, column `col`: where the 32 x 32 product leaves a lane's values
     const uint32_t w1_row4 = (uint32_t)p.H * 4u;
     auto w1_row = [](int half, int strip, int v) { return 32 * strip + 8 * (v >> 2) + 4 * half + (v & 3); };
@@ -163,7 +169,14 @@ __global__ void __launch_bounds__(RM_THREADS) resident_mlp_kernel(ResidentArgs p
         for (int v = 0; v < 4; ++v) w2l[(16 * kt + 4 * q + v) * RM_P16 + r] = x2[v];
     }
     if (bias1) b1l[16 * kt + r] = bias_x;
-    if (bias2) b2l[r] = bias_x;
+    if (bias2) {
+        b2l[r] = bias_x;
+        // The peer's output bias of the first iteration.  All workgroups read the one that the peer's last workgroup replaces in the second, so it
+        // is in LDS (behind a row of W2) before this workgroup sends its first partial logits: the peer's last workgroup writes behind the arrivals
+        // of all last workgroups, and the one of this worker arrives behind the logits of all of its workgroups.  What else a workgroup reads
+        // of a peer comes from the workgroup of the same units, whose arrival it has waited for.
+        w2l[r * RM_P16 + RM_MAX_C] = *at_bytes(p.x_first + ((size_t)drawn_peer(0, 0) << TILE_SHIFT), b2_at);
+    }
     if (t < B) yl[t] = p.labels[r0 + ib[t]];
 
     int at = 0, group = 0;                                    // the iteration's place in its group of draws, the group's parity
@@ -266,10 +279,7 @@ __global__ void __launch_bounds__(RM_THREADS) resident_mlp_kernel(ResidentArgs p
             __builtin_amdgcn_s_setprio(0);
         }
         // the peer, the next group of draws, the next iteration's labels; its rows are brought into this XCD's L2, a share by each workgroup
-        const int32_t *counts = cnt + group * (RM_AHEAD * RM_WAVES) + at * RM_WAVES;
-        int hits = counts[0];
-        for (int w = 1; w < RM_WAVES && 64 * w < p.M; ++w) hits += counts[w];
-        const int m = __builtin_amdgcn_readfirstlane(hits < last_i ? hits : last_i);
+        const int m = drawn_peer(group, at);
         const float wi = p.w[(size_t)i * p.M + m];
         const ptrdiff_t shift = ((ptrdiff_t)m - i) * TILE;    // from a worker's element to its peer's
         if (t == 0 && nb == 0 && !more) p.peers[i] = m;
@@ -440,15 +450,14 @@ __global__ void __launch_bounds__(RM_THREADS) resident_mlp_kernel(ResidentArgs p
             }
         }
         if (wave == RM_WAVES - 1) {
-            const float *peer_bias = it == 0 ? at_bytes(Xcur + shift, b2_at) : p.biases + (((size_t)cur * p.M + m) * p.NB + nb) * 16 + r;
-            const float bias_p = __hip_atomic_load(peer_bias, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const float bias_p = __hip_atomic_load(p.biases + (((size_t)cur * p.M + m) * p.NB + nb) * 16 + r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             f32x4 db = {0.0f, 0.0f, 0.0f, 0.0f};
             const float one = r == 0 ? 1.0f : 0.0f;
 #pragma unroll
             for (int k = 0; k < 4 * T16; ++k) db = __builtin_amdgcn_mfma_f32_16x16x4f32(one, dzs[(4 * k + q) * RM_P16 + r], db, 0, 0, 0);
             if (bias2) {
                 float xn, vn;
-                momentum_mix1(bias_x, bias_v, db[0], bias_p, wi, p.alpha, p.mu, p.wd, xn, vn);
+                momentum_mix1(bias_x, bias_v, db[0], it == 0 ? w2l[r * RM_P16 + RM_MAX_C] : bias_p, wi, p.alpha, p.mu, p.wd, xn, vn);
                 bias_x = xn;
                 bias_v = vn;
                 b2l[r] = xn;

@@ -102,6 +102,12 @@ __global__ void __launch_bounds__(SL_THREADS) sliced_softmax_kernel(SlicedArgs p
             if (lane == 0) to[k * SL_WAVES] = hits;
         }
     };
+    auto drawn_peer = [&](int group, int at) {
+        const int32_t *counts = cnt + group * (SL_AHEAD * SL_WAVES) + at * SL_WAVES;
+        int hits = counts[0];
+        for (int w = 1; w < SL_WAVES && 64 * w < p.M; ++w) hits += counts[w];
+        return __builtin_amdgcn_readfirstlane(hits < last_i ? hits : last_i);
+    };
     // this thread's pieces of the batch rows: row of the batch, first feature (past the end the first piece again, unused)
     const int row_units = Fs >> 2, feat_units = p.B * row_units;
     int piece_row[BURST], piece_at[BURST];
@@ -148,7 +154,14 @@ __global__ void __launch_bounds__(SL_THREADS) sliced_softmax_kernel(SlicedArgs p
 #pragma unroll
     for (int v = 0; v < 4; ++v)
         if (mine[v]) wl[(16 * wave + 4 * q + v) * SL_P16 + r] = x[v];
-    if (bias_lane) xb[r] = bias_x;
+    if (bias_lane) {
+        xb[r] = bias_x;
+        // The peer's bias of the first iteration.  All slices read the one that the peer's last slice replaces in the second, so it is in LDS (behind
+        // a class row of W) before this slice sends its first partial logits: the peer's last slice writes behind the arrivals of all
+        // last slices, and the one of this worker arrives behind the logits of all of its slices.  What else a slice reads of a peer comes from
+        // the same slice, whose arrival it has waited for.
+        wl[r * SL_P16 + SL_MAX_C] = p.x_first[tiled_offset(p.M, drawn_peer(0, 0), (int64_t)p.H * p.C + min(r, p.C - 1))];
+    }
     for (int e = t; e < pad; e += SL_THREADS) {
         const size_t at = tiled_offset(p.M, i, p.D + e);
         px[e] = p.x_first[at];
@@ -209,10 +222,7 @@ __global__ void __launch_bounds__(SL_THREADS) sliced_softmax_kernel(SlicedArgs p
             }
             __builtin_amdgcn_s_setprio(0);
         }
-        const int32_t *counts = cnt + group * (SL_AHEAD * SL_WAVES) + at * SL_WAVES;
-        int hits = counts[0];
-        for (int w = 1; w < SL_WAVES && 64 * w < p.M; ++w) hits += counts[w];
-        const int m = __builtin_amdgcn_readfirstlane(hits < last_i ? hits : last_i);
+        const int m = drawn_peer(group, at);
         const float wi = p.w[(size_t)i * p.M + m];
         const ptrdiff_t shift = ((ptrdiff_t)m - i) * TILE;    // from a worker's element to its peer's
         if (t == 0 && s == 0 && !more) p.peers[i] = m;
@@ -267,8 +277,7 @@ __global__ void __launch_bounds__(SL_THREADS) sliced_softmax_kernel(SlicedArgs p
         float xp[4];
 #pragma unroll
         for (int v = 0; v < 4; ++v) xp[v] = __hip_atomic_load(at_bytes(Xcur + shift, own[v]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const float *peer_bias = it == 0 ? Xcur + tiled_offset(p.M, m, (int64_t)p.H * p.C + min(r, p.C - 1)) : p.biases + (((size_t)cur * p.M + m) * p.P + s) * 16 + r;
-        const float bias_p = __hip_atomic_load(peer_bias, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const float bias_p = __hip_atomic_load(p.biases + (((size_t)cur * p.M + m) * p.P + s) * 16 + r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (RUN) {
             label = p.labels[r0 + ib[next_at * p.B + t_row]];
             request_rows();
@@ -310,7 +319,7 @@ __global__ void __launch_bounds__(SL_THREADS) sliced_softmax_kernel(SlicedArgs p
             for (int k = 0; k < 4 * RT; ++k) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(one, dzs[(4 * k + q) * SL_P16 + r], acc, 0, 0, 0);
             if (bias_lane) {
                 float xn, vn;
-                momentum_mix1(bias_x, bias_v, acc[0], bias_p, wi, p.alpha, p.mu, p.wd, xn, vn);
+                momentum_mix1(bias_x, bias_v, acc[0], it == 0 ? wl[r * SL_P16 + SL_MAX_C] : bias_p, wi, p.alpha, p.mu, p.wd, xn, vn);
                 bias_x = xn;
                 bias_v = vn;
                 xb[r] = xn;
