@@ -176,14 +176,15 @@ int netmax_mix(netmax_ctx *ctx, uint64_t iter, const int32_t *peers_dev);
  * in the first one only, where that saves a launch, or in none.  The graphs are dropped when buffers, data or the learning rate change.
  * Results are identical to the individual calls.
  * Small softmax-regression models (one layer, float features, at most 32 classes, parameters and batch within a
- * workgroup's LDS) run whole iterations inside ONE kernel, one workgroup per worker: without use_graph all n_iters
- * iterations are one launch with a device-wide barrier in every iteration (when all M workgroups fit
- * the device at once, else one launch per iteration; such launches of several contexts on a device run one after the other); with use_graph the replayed graph holds that kernel.  Same
+ * workgroup's LDS) run whole iterations inside ONE kernel, one workgroup per worker: without use_graph eight iterations and more
+ * are one cooperative launch with a device-wide barrier in every iteration (when all M workgroups fit
+ * the device at once), fewer are one launch each; with use_graph the replayed graph holds that kernel.  Same
  * results bit for bit: netmax_local_step runs the same gradient code for such models and every kernel applies the
  * update with the same instructions.  Larger ones (up to 1024 features in pieces of four, 16 classes, batch 64) are cut into slices of
  * the features, a workgroup each, and so are perceptrons on float operands with one hidden layer (a multiple of 32 units, batch 32 or 64,
- * up to about 870 features in pieces of eight) into groups of 32 units, where that is faster; they run the same way without use_graph where
- * all workgroups of all workers fit the device at once.  Should a workgroup ever wait at the barrier in vain, the kernel still ends, the
+ * up to about 870 features in pieces of eight) into groups of 32 units; they run the same way without use_graph where that is faster (from five
+ * iterations on; from two to many, by size) and all workgroups of all workers fit the device at once.  The runtime runs cooperative launches of
+ * several contexts on a device one after the other.  In a stream that is being captured the kernels of an iteration are launched one by one.  Should a workgroup ever wait at the barrier in vain, the kernel still ends, the
  * parameters are invalid and the next netmax_consensus_dist returns NETMAX_EDEVICE. */
 int netmax_run(netmax_ctx *ctx, uint64_t first_iter, int32_t n_iters, int32_t *peers_dev, int32_t use_graph);
 

@@ -8,10 +8,11 @@
 // below needs no other unit: dZ2 gives dW2's rows, the error of the units and their columns of dW1, which are updated where the product leaves
 // them.  The peer's columns come from the workgroup of the same units, which wrote them half an iteration before.
 //
-// 784-512-10, batch 64, 16 workers (all 256 compute units), four iterations: 135 us, the separate kernels 229.  An iteration takes 27 us:
+// 784-512-10, batch 64, 16 workers (all 256 compute units), four iterations: 150 us, 20 of them the cooperative launch's, the separate kernels 211.
+// An iteration takes 27 us:
 // forward 7.3 (its matrix instructions 5.3), the waves' tiles added 1.9, exchange and softmax 4.5, error 1.1, dW1 and its update the rest, beside
 // them the rows of W2 (3, two waves).  The strips of dW1 are bound by addresses and waiting, not by their matrix instructions (5.4).  What it
-// is made of: loads in global and not in flat address space (169 -> 143 us), the next strip's batch rows asked for before this one's stores, the
+// is made of (four iterations, launched plainly): loads in global and not in flat address space (169 -> 143 us), the next strip's batch rows asked for before this one's stores, the
 // peer's parameters only ahead of the strip's own products (12 registers spilled instead of 74: 148 -> 135 us), addresses as 32-bit byte
 // offsets from a strip's first row, one path for all features of a strip.
 //
@@ -546,20 +547,18 @@ bool resident_mlp_ok(const MlpPlan &p)
            p.dims[2] <= RM_MAX_C && p.M <= RM_THREADS && p.ld * p.M < (int64_t)1 << 30 && p.dims[0] <= 32 * RM_STRIPS * RM_WAVES &&
            rm_padding(p) <= RM_MAX_PAD && rm_lds(p.B, p.dims[0], rm_padding(p)) <= (size_t)RM_LDS_LIMIT;
 }
-// Whether n iterations are faster here than by the separate kernels, from a model of both in us (features x batch = the work of a
-// workgroup; the separate kernels' time grows with the parameters once their 3 x 16 MB leave the L2), fitted to 330 shapes of 96 to 784
-// features, 256 to 1024 hidden units, 2 to 16 workers; next to the line it errs by up to 4 %.  Measured, separate and here, 512 hidden
-// units; for 2, 8 and 16 workers (32, 128, 256 workgroups):
-//   one iteration   128 features, batch 64 28.9 and 22.0, 29.1 and 22.1, 31.5 and 22.9;   256, 64 29.5 and 28.8, 30.4 and 28.4, 35.7 and 29.7
-//                   784, batch 32 30.3 and 34.9, 35.9 and 35.5, 48.7 and 40.2;   784, 64 33.2 and 44.9, 41.0 and 45.4, 57.0 and 49.4
-//   four            128, 64 90 and 57, 93 and 57, 106 and 59;   256, 64 97 and 77, 101 and 76, 122 and 78
-//                   784, 32 100 and 92, 122 and 93, 178 and 100;   784, 64 112 and 128, 143 and 128, 212 and 131
+// Whether n iterations are faster here than by the separate kernels, from a model of both in us: work, features x batch of a workgroup; the separate
+// kernels' time also grows with the workgroups and with the parameters once these leave the L2.  Fitted to the 450 shapes of profiles/whole_iterations.csv
+// (16 to 864 features, 32 to 1024 hidden units, 2 to 128 workers, up to 256 workgroups, both batches; 1, 2, 3, 4 and 8 iterations): it takes the faster way
+// in 92 % of them, and in all but 1 % a way at most 3 % slower or, where it stays with the separate kernels, in all but 3 % one at most 5 % slower.
+// One iteration is never faster here: the cooperative launch costs 20 us.
 bool resident_mlp_pays(const MlpPlan &p, int n_iters)
 {
     const double work = 1e-3 * (double)p.dims[0] * p.B, groups = (double)p.M * (double)(p.dims[1] / RM_COLS);
-    const double traffic = 0.15 * fmax(0.0, 1e-3 * groups * (double)p.dims[0] - 50.0);
-    const double here = 20.5 + 0.56 * work + (n_iters - 1) * (7.5 + 0.38 * work);
-    return here < 28.0 + 0.1 * work + traffic + (n_iters - 1) * (16.5 + 0.2 * work + traffic);
+    const double traffic = fmax(0.0, 1e-3 * groups * (double)p.dims[0] - 25.0), more = n_iters - 1;
+    const double here = 33.5 + 0.6 * work + more * (8.5 + 0.41 * work);
+    const double there = 22.2 + 0.17 * work + 0.094 * traffic + 0.022 * groups + more * (18.5 + 0.156 * work + 0.08 * traffic + 0.019 * groups);
+    return n_iters > 1 && here < there;
 }
 int resident_mlp_grid(const MlpPlan &p) { return (int)grouped_grid(p.M, (unsigned)(p.dims[1] / RM_COLS)); }
 
@@ -576,19 +575,19 @@ static ResidentKernel resident_kernel(int B) { return B == 32 ? resident_mlp_ker
 
 hipError_t prepare_resident_mlp(const MlpPlan &p, int *resident)
 {
-    int dev = 0, per_cu = 0;
-    int cus = 0;
+    int dev = 0, per_cu = 0, cus = 0, cooperative = 0;
     const void *kernel = reinterpret_cast<const void *>(resident_kernel(p.B));
     *resident = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    if (e == hipSuccess) e = hipDeviceGetAttribute(&cooperative, hipDeviceAttributeCooperativeLaunch, dev);
     if (e == hipSuccess) e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, RM_LDS_LIMIT);
     if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, RM_THREADS, rm_lds(p.B, p.dims[0], rm_padding(p)));
-    if (e == hipSuccess) *resident = per_cu * cus;
+    if (e == hipSuccess && cooperative) *resident = per_cu * cus;
     return e;
 }
 
-void launch_resident_mlp(hipStream_t s, const MlpPlan &p, const SlicedIterLaunch &a)
+hipError_t launch_resident_mlp(hipStream_t s, const MlpPlan &p, const SlicedIterLaunch &a)
 {
     ResidentArgs k{};
     k.M = p.M; k.B = p.B; k.din = (int)p.dims[0]; k.H = (int)p.dims[1]; k.C = (int)p.dims[2]; k.NB = k.H / RM_COLS; k.run = head_pairs_per_wave(p);
@@ -599,7 +598,9 @@ void launch_resident_mlp(hipStream_t s, const MlpPlan &p, const SlicedIterLaunch
     k.alpha = a.mix.alpha; k.mu = a.mix.mu; k.wd = a.mix.wd; k.seed = a.seed; k.iter = a.iter; k.n_iters = a.n_iters;
     k.words = a.parts; k.biases = a.biases; k.ticket = a.ticket; k.rows_count = a.counters; k.rows_base = a.rows_base;
     k.fault = a.fault; k.patience = a.patience;
-    hipLaunchKernelGGL(resident_kernel(p.B), dim3((unsigned)resident_mlp_grid(p)), dim3(RM_THREADS), rm_lds(p.B, p.dims[0], rm_padding(p)), s, k);
+    void *args[] = {&k};
+    return hipLaunchCooperativeKernel(reinterpret_cast<const void *>(resident_kernel(p.B)), dim3((unsigned)resident_mlp_grid(p)), dim3(RM_THREADS), args,
+                                      (unsigned)rm_lds(p.B, p.dims[0], rm_padding(p)), s);
 }
 
 }  // namespace netmax

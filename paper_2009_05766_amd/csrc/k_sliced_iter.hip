@@ -2,8 +2,8 @@
 // a worker's features are cut into slices, one workgroup keeps a slice of the parameters, of the momentum and of the batch rows in LDS.
 // An iteration needs two exchanges: the slices of a worker add up their partial logits, and a slice pulls the peer's same slice.
 // The logits cross the chip once per iteration (stored, counted, polled, read: about 2 us); the peer's row was stored half an iteration
-// before it is asked for.  784-10, batch 64, 16 workers, us: eight iterations 55, one 14, where the draws and the two kernels of
-// k_grad_head.hip take 89 and 20.6; 1024-10 35 and 14 (four iterations, one) instead of 54 and 21.  An iteration in 6.6 us: logits 1.2, their
+// before it is asked for.  784-10, batch 64, 16 workers, eight iterations 73 us, 20 of them the cooperative launch's, where the draws and the two
+// kernels of k_grad_head.hip take 89.  An iteration in 6.6 us: logits 1.2, their
 // exchange 1.5, softmax and waiting 1.1, gradient and update 1.8, the rest draws, row addresses and barriers.
 //
 // The slices are the runs of features that the waves of head_logits_kernel take, and all sums are made in that kernel's and in
@@ -52,10 +52,10 @@ static size_t sl_lds(int B, int64_t pad)
 // RT: 16-row tiles of the batch (1, 2 or 4; rows past the batch count as zeros): a wave each for the logits, four for the softmax.
 // Sixteen features of the slice belong to a wave: it computes their dW, whose result layout (a lane has four rows of one class) also is
 // the one in which it keeps their parameters and momentum in registers and updates them; LDS has a copy of W for the forward pass.
-// (A thread per vector of four parameters, with dW turned through LDS, spends its time on addresses: 62 instead of 55 us.  256 threads with
-// four rows of the softmax each: 69 us.  Counted arrivals instead of tickets, four round trips to memory instead of two: 126 us.)
-// RUN: several iterations; the last one asks for its own rows again (no load under a branch).
-template <int RT, bool RUN>
+// (A thread per vector of four parameters, with dW turned through LDS, spends its time on addresses: 62 instead of 55 us for those, launched
+// plainly.  256 threads with four rows of the softmax each: 69 us.  Counted arrivals instead of tickets, four round trips to memory instead of two: 126 us.)
+// The last iteration asks for its own rows again (no load under a branch).
+template <int RT>
 __global__ void __launch_bounds__(SL_THREADS) sliced_softmax_kernel(SlicedArgs p)
 {
     extern __shared__ __attribute__((aligned(16))) float sl_smem[];
@@ -170,10 +170,9 @@ __global__ void __launch_bounds__(SL_THREADS) sliced_softmax_kernel(SlicedArgs p
     if (t < p.B) yl[t] = label;
 
     int at = 0, group = 0;                                    // the iteration's place in its group of draws, the group's parity
-    const int n_iters = RUN ? p.n_iters : 1;
-    for (int it = 0; it < n_iters; ++it) {
+    for (int it = 0; it < p.n_iters; ++it) {
         const int cur = it & 1, nxt = cur ^ 1;
-        const bool more = RUN && it + 1 < n_iters;
+        const bool more = it + 1 < p.n_iters;
         float *Xcur = cur ? p.x_second : p.x_first, *Xnext = cur ? p.x_first : p.x_second;
         // ---- this iteration's batch rows into LDS
 #pragma unroll
@@ -232,7 +231,7 @@ __global__ void __launch_bounds__(SL_THREADS) sliced_softmax_kernel(SlicedArgs p
             draw_group(it + 1, group ^ 1);
             __syncthreads();                                  // its rows are looked up before the next barrier
         }
-        if (RUN) find_rows(ib + next_at * p.B);
+        find_rows(ib + next_at * p.B);
         unsigned seen = 0;
         if (wave < 4 * RT) {
             // ---- the parts of one element of every lane's four: sixteen lanes have a batch row's classes
@@ -278,10 +277,8 @@ __global__ void __launch_bounds__(SL_THREADS) sliced_softmax_kernel(SlicedArgs p
 #pragma unroll
         for (int v = 0; v < 4; ++v) xp[v] = __hip_atomic_load(at_bytes(Xcur + shift, own[v]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         const float bias_p = __hip_atomic_load(p.biases + (((size_t)cur * p.M + m) * p.P + s) * 16 + r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (RUN) {
-            label = p.labels[r0 + ib[next_at * p.B + t_row]];
-            request_rows();
-        }
+        label = p.labels[r0 + ib[next_at * p.B + t_row]];
+        request_rows();
         // ---- dW = X^T dZ: the batch is the contraction, taken in the order of head_grads_kernel; momentum step and mix (Eq. (c0), (c1))
         if (16 * wave < Fs) {
             float av[RT][4], bz[RT][4];
@@ -353,7 +350,7 @@ __global__ void __launch_bounds__(SL_THREADS) sliced_softmax_kernel(SlicedArgs p
 }
 
 typedef void (*SlicedKernel)(SlicedArgs);
-template <bool RUN> static SlicedKernel sliced_kernel(int B) { return B <= 16 ? sliced_softmax_kernel<1, RUN> : B <= 32 ? sliced_softmax_kernel<2, RUN> : sliced_softmax_kernel<4, RUN>; }
+static SlicedKernel sliced_kernel(int B) { return B <= 16 ? sliced_softmax_kernel<1> : B <= 32 ? sliced_softmax_kernel<2> : sliced_softmax_kernel<4>; }
 static int64_t sl_padding(const MlpPlan &p) { return p.ld - (p.dims[0] * p.dims[1] + p.dims[1]); }
 
 // Rows of four features at a time, slices that fit LDS and their waves, their padding with them.
@@ -374,27 +371,28 @@ void sliced_iter_scratch(const MlpPlan &p, size_t &parts, size_t &biases, size_t
 }
 int sliced_iter_slices(const MlpPlan &p) { return sl_slices(p.dims[0]); }
 
-// Workgroups of the kernel that the device holds at once; raises its LDS limit.
+// A cooperative launch costs about 20 us more than a plain one.  The separate kernels and this one, us: 784-10, batch 64, 16 workers, 3 iterations 37.8 and 45.2,
+// 4 49.0 and 50.8, 5 60.1 and 56.4, 8 88.9 and 72.9; 1024-16, 4 workers, 4 iterations 52.0 and 50.8, 5 63.8 and 57.3; 512-10, batch 32, 8 workers, 4
+// iterations 43.8 and 45.2, 5 53.3 and 49.8.
+bool sliced_iter_pays(int n_iters) { return n_iters >= 5; }
+
+// Workgroups of the kernel that the device holds at once (0: it has no cooperative launches); raises its LDS limit.
 hipError_t prepare_sliced_iter(const MlpPlan &p, int *resident)
 {
-    int dev = 0;
-    int cus = 0;
+    int dev = 0, cus = 0, cooperative = 0;
     *resident = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    for (SlicedKernel k : {sliced_kernel<true>(p.B), sliced_kernel<false>(p.B)}) {
-        const void *kernel = reinterpret_cast<const void *>(k);
-        int per_cu = 0;
-        if (e == hipSuccess) e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, SL_LDS_LIMIT);
-        if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, SL_THREADS, sl_lds(p.B, sl_padding(p)));
-        if (e != hipSuccess) return e;
-        const int held = per_cu * cus;
-        *resident = *resident == 0 || held < *resident ? held : *resident;
-    }
-    return hipSuccess;
+    if (e == hipSuccess) e = hipDeviceGetAttribute(&cooperative, hipDeviceAttributeCooperativeLaunch, dev);
+    const void *kernel = reinterpret_cast<const void *>(sliced_kernel(p.B));
+    int per_cu = 0;
+    if (e == hipSuccess) e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, SL_LDS_LIMIT);
+    if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, SL_THREADS, sl_lds(p.B, sl_padding(p)));
+    if (e == hipSuccess && cooperative) *resident = per_cu * cus;
+    return e;
 }
 
-void launch_sliced_iter(hipStream_t s, const MlpPlan &p, const SlicedIterLaunch &a)
+hipError_t launch_sliced_iter(hipStream_t s, const MlpPlan &p, const SlicedIterLaunch &a)
 {
     SlicedArgs k{};
     k.M = p.M; k.B = p.B; k.H = (int)p.dims[0]; k.C = (int)p.dims[1]; k.P = sl_slices(p.dims[0]); k.per = sl_per(p.dims[0]);
@@ -407,7 +405,8 @@ void launch_sliced_iter(hipStream_t s, const MlpPlan &p, const SlicedIterLaunch 
     k.ticket = a.ticket; k.rows_count = a.counters; k.rows_base = a.rows_base;
     k.fault = a.fault; k.patience = a.patience;
     const dim3 grid((unsigned)(p.M * k.P)), block(SL_THREADS);
-    hipLaunchKernelGGL(a.n_iters > 1 ? sliced_kernel<true>(p.B) : sliced_kernel<false>(p.B), grid, block, sl_lds(p.B, sl_padding(p)), s, k);
+    void *args[] = {&k};
+    return hipLaunchCooperativeKernel(reinterpret_cast<const void *>(sliced_kernel(p.B)), grid, block, args, (unsigned)sl_lds(p.B, sl_padding(p)), s);
 }
 
 }  // namespace netmax

@@ -2,12 +2,12 @@
 // workgroup per worker draws its peer and its batch, computes logits, loss and gradient with the worker's parameters
 // and batch rows held in LDS, and applies the momentum step and the mix (Eq. (c0), (c1)) against the peer's copy of the
 // previous iteration.  Models of this size are bound by launch latency (six dependent launches of a few microseconds
-// each otherwise); here an iteration is one launch, or one step between two barriers inside a launch that runs many.
+// each otherwise); here an iteration is one launch, or one step between two barriers inside a cooperative launch that runs many.
 //
 // Three modes share the code, so their results agree bit for bit:
 //   GRAD      batch draw, loss, gradient -> G (netmax_local_step; the mix kernel then applies the same update function)
 //   STEP      peer draw + GRAD + update  -> Xnext, V, G (one iteration per launch; also what a captured graph replays)
-//   the same with n_iters > 1: all workgroups resident, a split barrier per iteration; G, loss and peers are written by the last one only.
+//   the same with n_iters > 1: cooperative launch, a split barrier per iteration; G, loss and peers are written by the last one only.
 //
 // Arithmetic: fp32, fixed order.  Forward: eight lanes share a batch row, lane s takes the features k = s, s + 8, ...
 // in increasing order, the eight partial sums are added in halves.  Weight gradient: one thread per four features
@@ -22,9 +22,8 @@
 // the new parameters stay in LDS, only the peer's row is read again.  A workgroup arrives at the barrier with its new row and looks for
 // the others' arrival after the softmax of the next iteration, where it needs the peer's: half an iteration during which the last
 // ones catch up.  256-10, batch 32, 8 workers, sixteen iterations in a call: 145 us with the barrier between iterations (release
-// and acquire of the whole cache, about 2 us), a draw per iteration, stores between the loads of the update and a cooperative launch
-// (20 us of it), 78 us now; an iteration takes 4.3 us: rows into LDS 0.2, forward 1.0, softmax 0.8, waiting 0.3, gradient 1.2,
-// update 0.7.
+// and acquire of the whole cache, about 2 us), a draw per iteration and stores between the loads of the update, 97 us now, 20 of them the cooperative
+// launch's; an iteration takes 4.3 us: rows into LDS 0.2, forward 1.0, softmax 0.8, waiting 0.3, gradient 1.2, update 0.7.
 #include "kernels.h"
 #include "layout.h"
 #include "philox.h"
@@ -103,7 +102,7 @@ static size_t small_iter_operands(int B, int din, int dout, int64_t ld)
 // CAP: classes the unrolled loops cover: dout <= CAP, CAP in {8, 16, 32}.  RT > 0: the two products on matrix
 // instructions, RT = batch / 16 tiles of batch rows (CAP = 16, shapes accepted by small_iter_mm()).
 // MODE: batch draw, loss and gradient of one iteration; the whole of one; several.  The last of several asks for its own batch rows
-// again: a load under a branch is waited for where the branches join (82 instead of 78 us for sixteen iterations of 256-10).
+// again: a load under a branch is waited for where the branches join (4 us more for sixteen iterations of 256-10).
 enum : int { SI_GRAD = 0, SI_ONE = 1, SI_RUN = 2 };
 template <int CAP, int RT, int MODE, bool FEW, class Args = SmallIterArgs>
 __global__ void __launch_bounds__(SI_THREADS) small_softmax_iteration_kernel(Args p)
@@ -631,8 +630,12 @@ hipError_t prepare_small_iter(int B, int64_t din, int64_t dout, int64_t ld)
     return hipSuccess;
 }
 
-// n_iters > 1: every workgroup must be resident (the caller has checked M against small_iter_max_resident(), and no other launch of
-// that kind runs beside it).
+// Several iterations in one launch.  A cooperative launch costs about 20 us more than a plain one, an iteration in it 4.5 us instead of 7.2 in a launch of
+// its own (256-10, batch 32, 8 workers).  One launch each and all in one, us: 256-10, 4 iterations 30.5 and 43.1, 8 59.6 and 61.4 (alone 83 and 62),
+// 16 115 and 97; 64-10, batch 64, 8 iterations 54.6 and 54.5; 21-9, batch 65, 16 workers, 6 iterations 86.2 and 88.0, 8 114 and 109.
+bool small_iter_pays(int n_iters) { return n_iters >= 8; }
+
+// n_iters > 1: every workgroup must be resident (the caller has checked M against small_iter_max_resident()).
 hipError_t launch_small_iter(hipStream_t s, const SmallIterLaunch &a)
 {
     SmallSlotArgs p{};
@@ -652,15 +655,17 @@ hipError_t launch_small_iter(hipStream_t s, const SmallIterLaunch &a)
     const void *kernel = a.grad_only ? small_iter_kernel<SI_GRAD>(a.B, a.din, a.dout, a.ld)
                          : a.n_iters == 1 ? small_iter_kernel<SI_ONE>(a.B, a.din, a.dout, a.ld)
                                           : small_iter_kernel<SI_RUN>(a.B, a.din, a.dout, a.ld);
+    if (!a.grad_only && a.n_iters > 1) return hipLaunchCooperativeKernel(kernel, dim3((unsigned)a.M), dim3(SI_THREADS), args, (unsigned)lds, s);
     return hipLaunchKernel(kernel, dim3((unsigned)a.M), dim3(SI_THREADS), args, lds, s);
 }
 
-// How many workgroups of the kernel fit on the device at once with this much LDS each (0 if unknown).
+// How many workgroups of the kernel fit on the device at once with this much LDS each (0 if unknown, or if the device has no cooperative launches).
 int small_iter_max_resident(int B, int64_t din, int64_t dout, int64_t ld)
 {
-    int per_cu = 0, dev = 0;
-    int cus = 0;
-    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
+    int per_cu = 0, dev = 0, cus = 0, cooperative = 0;
+    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cooperative, hipDeviceAttributeCooperativeLaunch, dev) != hipSuccess || !cooperative)
+        return 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, small_iter_kernel<SI_RUN>(B, din, dout, ld), SI_THREADS,
                                                      small_iter_lds(B, (int)din, (int)dout, ld)) != hipSuccess)
         return 0;

@@ -113,7 +113,7 @@ void launch_widen_bf16(hipStream_t s, int64_t n, const uint16_t *in, float *out)
 
 // Whole iterations of a small softmax-regression model in one kernel, one workgroup per worker (k_small_iter.hip).
 // grad_only: batch draw, loss and gradient only (G, loss, idx); otherwise also the peer draw (peers) and the update
-// (x_second, V).  n_iters > 1 needs all workgroups resident: x_first / x_second swap roles after every iteration and
+// (x_second, V).  n_iters > 1 is a cooperative launch, for which all workgroups have to fit the device together: x_first / x_second swap roles after every iteration and
 // the workgroups meet at a barrier (counter `barrier`, which the launch advances by (n_iters - 1) * M from
 // barrier_base); *fault is raised if a workgroup waited in vain.
 struct SmallIterLaunch {
@@ -129,6 +129,7 @@ struct SmallIterLaunch {
 bool small_iter_ok(int model_is_mlp, int n_layers, int bf16, int B, int64_t din, int64_t dout, int64_t ld);
 hipError_t prepare_small_iter(int B, int64_t din, int64_t dout, int64_t ld);
 int small_iter_max_resident(int B, int64_t din, int64_t dout, int64_t ld);
+bool small_iter_pays(int n_iters);           // several iterations in one launch
 hipError_t launch_small_iter(hipStream_t s, const SmallIterLaunch &a);
 
 // Per-worker MLP / softmax-regression gradient (grouped GEMMs).
@@ -205,7 +206,8 @@ bool sliced_iter_ok(const MlpPlan &p);
 int sliced_iter_slices(const MlpPlan &p);
 void sliced_iter_scratch(const MlpPlan &p, size_t &parts, size_t &biases, size_t &counters);
 hipError_t prepare_sliced_iter(const MlpPlan &p, int *resident);
-void launch_sliced_iter(hipStream_t s, const MlpPlan &p, const SlicedIterLaunch &a);
+bool sliced_iter_pays(int n_iters);
+hipError_t launch_sliced_iter(hipStream_t s, const MlpPlan &p, const SlicedIterLaunch &a);
 
 // The same for a perceptron with one hidden layer whose first weight matrices fit the chip's LDS together (k_resident_mlp.hip): a grid of
 // resident_mlp_grid() workgroups, all resident together.  Shards of fewer than 2^32 bytes.
@@ -214,7 +216,7 @@ bool resident_mlp_pays(const MlpPlan &p, int n_iters);
 int resident_mlp_grid(const MlpPlan &p);
 void resident_mlp_scratch(const MlpPlan &p, size_t &parts, size_t &biases, size_t &counters);
 hipError_t prepare_resident_mlp(const MlpPlan &p, int *resident);
-void launch_resident_mlp(hipStream_t s, const MlpPlan &p, const SlicedIterLaunch &a);
+hipError_t launch_resident_mlp(hipStream_t s, const MlpPlan &p, const SlicedIterLaunch &a);
 
 // Tiled kernels for layers of any shape, fp32 or bfloat16 operands.  need_t: the transposed bfloat16 activation is wanted (by a
 // matrix-core kernel above); below_fast: so are both bfloat16 copies of the error.  launch_tile_dgrad: true if it has also

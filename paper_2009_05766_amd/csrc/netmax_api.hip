@@ -78,7 +78,6 @@ struct netmax_ctx {
     // small softmax-regression models: whole iterations in one kernel (k_small_iter.hip)
     bool small = false;                       // the model qualifies
     int small_resident = 0;                   // workgroups of that kernel the device holds at once (runs of several iterations)
-    hipEvent_t waiting_event = nullptr;       // orders launches whose workgroups wait for each other (WaitingLaunch)
     unsigned *d_barrier = nullptr;            // grid-barrier counter, only ever advanced
     unsigned barrier_count = 0;               // its value once everything enqueued so far has run
     int *d_fault = nullptr;                   // raised by a workgroup that waited at the barrier in vain
@@ -229,53 +228,17 @@ static void drop_graphs(netmax_ctx *ctx)
     ctx->graph_peers = nullptr;
 }
 
-// A launch whose workgroups wait for each other needs all of them resident.  The device holds the workgroups of one such launch (the
-// caller has checked); two of them side by side might each hold compute units that the other's missing workgroups need.  So the
-// contexts of a device take turns: a launch on another stream than the last one's waits for what that stream held at this moment.
-// (A cooperative launch gives the same guarantee, but the runtime waits for it on the host: about 20 us a call, 97 instead of 78 us
-// for sixteen iterations of 256-10, 8 workers.)  Usually there is one such stream and nothing is waited for.
-constexpr int MAX_DEVICES = 64;
-static std::mutex g_waiting_mutex;
-static netmax_ctx *g_waiting_last[MAX_DEVICES] = {};      // cleared when that context goes; its stream outlives it
-
+// Launches whose workgroups wait for each other are cooperative ones: only for these does the runtime promise that all workgroups are
+// resident, whatever else the process, its other streams and other processes run on the device.  One in a stream that is being captured
+// would have to keep that promise in every replay: the separate kernels there.
 static bool capturing(hipStream_t s)
 {
     hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
     return s && (hipStreamIsCapturing(s, &status) != hipSuccess || status != hipStreamCaptureStatusNone);
 }
 
-// Holds the turn while the launch is enqueued; ok() false: not possible here (a stream is being captured, or an error).
-class WaitingLaunch {
-public:
-    explicit WaitingLaunch(netmax_ctx *ctx) : lock_(g_waiting_mutex)
-    {
-        if (ctx->device < 0 || ctx->device >= MAX_DEVICES || !ctx->waiting_event || capturing(ctx->stream)) return;
-        netmax_ctx *&last = g_waiting_last[ctx->device];
-        if (last && last->stream != ctx->stream) {
-            if (capturing(last->stream) || hipEventRecord(last->waiting_event, last->stream) != hipSuccess ||
-                hipStreamWaitEvent(ctx->stream, last->waiting_event, 0) != hipSuccess) {
-                (void)hipGetLastError();
-                return;
-            }
-        }
-        last = ctx;
-        ok_ = true;
-    }
-    bool ok() const { return ok_; }
-
-private:
-    std::lock_guard<std::mutex> lock_;
-    bool ok_ = false;
-};
-
 static void release(netmax_ctx *ctx)
 {
-    {
-        std::lock_guard<std::mutex> lock(g_waiting_mutex);
-        for (auto &last : g_waiting_last)
-            if (last == ctx) last = nullptr;
-    }
-    if (ctx->waiting_event) (void)hipEventDestroy(ctx->waiting_event);
     drop_graphs(ctx);
     (void)hipFree(ctx->d_block);
     (void)hipFree(ctx->d_act_thr); (void)hipFree(ctx->d_fuse_tiles);
@@ -462,7 +425,6 @@ extern "C" int netmax_init(netmax_ctx **out, const netmax_config *cfg)
                 want(&ctx->d_fault, 1);
             }
         }
-        if (ctx->small || ctx->sliced || ctx->resident_mlp) INIT_TRY(hipEventCreateWithFlags(&ctx->waiting_event, hipEventDisableTiming));
         for (int l = 0; l < cfg->n_layers && !ctx->small; ++l)
             if (update_end(plan, l) > 0) {
                 ctx->tail = true;
@@ -852,48 +814,35 @@ extern "C" int netmax_run(netmax_ctx *ctx, uint64_t first_iter, int32_t n_iters,
     if (!use_graph && ctx->small && !ctx->fuse) {
         // whole iterations inside one kernel; all of them in one launch where its workgroups are resident together, else one
         // launch per iteration
+        const bool together = small_iter_pays(n_iters) && ctx->small_resident >= ctx->cfg.M && !capturing(ctx->stream);
         int32_t k = 0;
         while (k < n_iters) {
-            int rc = NETMAX_OK;
-            int32_t n = 1;
-            if (n_iters - k > 1 && ctx->small_resident >= ctx->cfg.M) {
-                const WaitingLaunch turn(ctx);
-                if (turn.ok()) n = std::min<int32_t>(n_iters - k, 1 << 20);
-                rc = enqueue_small(ctx, IterRef{first_iter + (uint64_t)k, nullptr}, n, false, peers_dev);
-            } else {
-                rc = enqueue_small(ctx, IterRef{first_iter + (uint64_t)k, nullptr}, 1, false, peers_dev);
-            }
+            const int32_t n = together ? std::min<int32_t>(n_iters - k, 1 << 20) : 1;
+            const int rc = enqueue_small(ctx, IterRef{first_iter + (uint64_t)k, nullptr}, n, false, peers_dev);
             if (rc != NETMAX_OK) return rc;
             for (int32_t q = 0; q < n; ++q) flip(ctx);
             k += n;
         }
         return NETMAX_OK;
     }
-    if (!use_graph && (ctx->sliced || (ctx->resident_mlp && ctx->shard_bytes < (int64_t)1 << 32 && resident_mlp_pays(make_plan(ctx), n_iters)))) {
-        int32_t k = 0;
-        while (k < n_iters) {
+    if (!use_graph && !capturing(ctx->stream) &&
+        ((ctx->sliced && sliced_iter_pays(n_iters)) || (ctx->resident_mlp && ctx->shard_bytes < (int64_t)1 << 32 && resident_mlp_pays(make_plan(ctx), n_iters)))) {
+        for (int32_t k = 0; k < n_iters;) {
             const int32_t n = std::min<int32_t>(n_iters - k, 1 << 20);
-            const WaitingLaunch turn(ctx);
-            if (!turn.ok()) break;                                        // a stream is being captured: the separate kernels
-            MlpPlan p = make_plan(ctx);
+            const MlpPlan p = make_plan(ctx);
             SlicedIterLaunch a{};
             a.mix = mix_args(ctx, nullptr); a.G = ctx->g; a.peers = peers_dev; a.n_rows = ctx->d_nrows; a.thr = ctx->d_thr; a.last = ctx->d_last;
             a.seed = ctx->cfg.seed; a.iter = IterRef{first_iter + (uint64_t)k, nullptr}; a.n_iters = n;
             a.parts = ctx->d_parts; a.biases = ctx->d_biases; a.counters = ctx->d_counters;
             a.ticket = ctx->ticket; a.rows_base = ctx->rows_base;
             a.fault = ctx->d_fault; a.patience = ctx->barrier_patience;
-            if (ctx->sliced) launch_sliced_iter(ctx->stream, p, a);
-            else launch_resident_mlp(ctx->stream, p, a);
-            const int rc = check_launch(ctx, "whole iterations");
-            if (rc != NETMAX_OK) return rc;
+            HIP_TRY(ctx, ctx->sliced ? launch_sliced_iter(ctx->stream, p, a) : launch_resident_mlp(ctx->stream, p, a));
             ctx->ticket += (unsigned)n;
             ctx->rows_base += (unsigned)(n - 1) * (unsigned)ctx->cfg.M;
             for (int32_t q = 0; q < n; ++q) flip(ctx);
             k += n;
         }
-        first_iter += (uint64_t)k;
-        n_iters -= k;
-        if (n_iters == 0) return NETMAX_OK;
+        return NETMAX_OK;
     }
     if (!use_graph) {
         // draws depend on the iteration number only: one launch makes those of several iterations (of a single one straight to the

@@ -37,13 +37,13 @@ def _run_is_calls_and_oracle(over, runs, name="cfg1"):
                                   dict(M=2, dims=(5, 4), batch=1024, n_per_worker=90)])
 def test_batches_beyond_the_threads(over):
     """A workgroup has 512 threads; every row of a larger batch has to be drawn and to have its label."""
-    _run_is_calls_and_oracle(over, (3, 1, 2))
+    _run_is_calls_and_oracle(over, (3, 1, 2, 9))
 
 
 @pytest.mark.parametrize("dims", [(4, 3), (1, 2), (6, 1), (1, 1)])
 def test_divisors_of_one(dims):
     """One piece per data row, one class: positions are divided by 1."""
-    _run_is_calls_and_oracle(dict(M=3, dims=dims, batch=24, n_per_worker=50), (2, 1))
+    _run_is_calls_and_oracle(dict(M=3, dims=dims, batch=24, n_per_worker=50), (2, 1, 9))
 
 
 @pytest.mark.parametrize("over", [
@@ -62,7 +62,7 @@ def test_whole_iterations(over):
 
 
 def test_runs_on_several_streams():
-    """Launches whose workgroups wait for each other take turns on a device: two contexts on streams of their own, their runs enqueued
+    """Launches whose workgroups wait for each other run one after the other on a device: two contexts on streams of their own, their runs enqueued
     alternately, and one of them gone before the other runs again."""
     w = workload("cfg1", M=8)
     inp = inputs_of(w)
