@@ -540,7 +540,7 @@ __global__ void __launch_bounds__(RM_THREADS) resident_mlp_kernel(ResidentArgs p
 static int64_t rm_padding(const MlpPlan &p) { return p.ld - (p.dims[0] * p.dims[1] + p.dims[1] + p.dims[1] * p.dims[2] + p.dims[2]); }
 
 // One hidden layer that fwd_f32_kernel and wgrad_f32_kernel take, classes and units in the parts that head_logits_kernel then adds, 32-bit byte
-// offsets inside the parameters and (n_rows_max) inside a shard, columns that fit LDS.
+// offsets inside the parameters, columns that fit LDS.  Of the data netmax_bind_data asks the rest.
 bool resident_mlp_ok(const MlpPlan &p)
 {
     return p.n_layers == 2 && !p.bf16 && (p.B == 32 || p.B == 64) && p.dims[0] % RM_KS == 0 && p.dims[1] % RM_COLS == 0 && head_parts_of_two(p) &&

@@ -210,7 +210,7 @@ bool sliced_iter_pays(int n_iters);
 hipError_t launch_sliced_iter(hipStream_t s, const MlpPlan &p, const SlicedIterLaunch &a);
 
 // The same for a perceptron with one hidden layer whose first weight matrices fit the chip's LDS together (k_resident_mlp.hip): a grid of
-// resident_mlp_grid() workgroups, all resident together.  Shards of fewer than 2^32 bytes.
+// resident_mlp_grid() workgroups, all resident together.  Shards of fewer than 2^32 bytes, features where fwd_f32_ok() takes them.
 bool resident_mlp_ok(const MlpPlan &p);
 bool resident_mlp_pays(const MlpPlan &p, int n_iters);
 int resident_mlp_grid(const MlpPlan &p);

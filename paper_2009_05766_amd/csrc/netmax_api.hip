@@ -85,7 +85,7 @@ struct netmax_ctx {
     // whole iterations in one kernel of several workgroups per worker: softmax regression in slices of its features (k_sliced_iter.hip),
     // perceptrons with one hidden layer in groups of its units (k_resident_mlp.hip)
     bool sliced = false, resident_mlp = false;
-    int64_t shard_bytes = 0;                  // of the largest shard
+    bool resident_data = false;               // resident_mlp: the bound data allow it
     unsigned long long *d_parts = nullptr;
     float *d_biases = nullptr;
     unsigned *d_counters = nullptr;
@@ -574,7 +574,9 @@ extern "C" int netmax_bind_data(netmax_ctx *ctx, const void *feats, const int32_
     drop_graphs(ctx);
     ctx->feats = feats;
     ctx->labels = labels;
-    ctx->shard_bytes = most * ctx->cfg.dims[0] * (ctx->cfg.gemm_in == NETMAX_BF16 ? 2 : 4);
+    // 32-bit byte offsets inside a shard; features that start where the separate kernels, too, read them in aligned pieces (elsewhere these take
+    // another forward kernel, whose sums have another order)
+    ctx->resident_data = ctx->resident_mlp && most * ctx->cfg.dims[0] * 4 < (int64_t)1 << 32 && fwd_f32_ok(make_plan(ctx), 0);
     ctx->data_bound = true;
     return NETMAX_OK;
 }
@@ -826,7 +828,7 @@ extern "C" int netmax_run(netmax_ctx *ctx, uint64_t first_iter, int32_t n_iters,
         return NETMAX_OK;
     }
     if (!use_graph && !capturing(ctx->stream) &&
-        ((ctx->sliced && sliced_iter_pays(n_iters)) || (ctx->resident_mlp && ctx->shard_bytes < (int64_t)1 << 32 && resident_mlp_pays(make_plan(ctx), n_iters)))) {
+        ((ctx->sliced && sliced_iter_pays(n_iters)) || (ctx->resident_data && resident_mlp_pays(make_plan(ctx), n_iters)))) {
         for (int32_t k = 0; k < n_iters;) {
             const int32_t n = std::min<int32_t>(n_iters - k, 1 << 20);
             const MlpPlan p = make_plan(ctx);

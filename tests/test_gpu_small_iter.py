@@ -158,6 +158,26 @@ def test_iterations_of_resident_perceptrons(over):
     calls.close(), run.close()
 
 
+@pytest.mark.parametrize("dims,batch", [((784, 10), 64), ((104, 96, 10), 64), ((104, 96, 10), 32)])
+@pytest.mark.parametrize("skip", [0, 1, 2, 3])
+def test_features_that_start_anywhere(dims, batch, skip):
+    """Features inside a larger buffer: netmax_run gives the separate calls' bits, whichever kernels read them."""
+    w = workload("cfg2", M=3, dims=dims, batch=batch, n_per_worker=90)
+    inp = inputs_of(w)
+    flat = torch.zeros(inp["feats"].size + 8, device="cuda")
+    inp["feats"] = flat[skip:skip + inp["feats"].size].copy_(torch.from_numpy(inp["feats"]).flatten()).view(inp["feats"].shape)
+    inp["labels"] = torch.from_numpy(inp["labels"]).cuda()
+    calls, run = make_gpu(w, inp, momentum=0.9), make_gpu(w, inp, momentum=0.9)
+    assert run.feats.data_ptr() % 16 == 4 * skip % 16
+    run.run(0, 9)
+    for k in range(9):
+        calls.step(k)
+    for what in ("x_a", "x_b", "v", "g"):
+        assert torch.equal(getattr(run, what), getattr(calls, what)), what
+    assert torch.equal(run.losses(), calls.losses())
+    calls.close(), run.close()
+
+
 @pytest.mark.parametrize("name,over,n", [
     # kernels that take a list of workers: one hidden layer, batches of 32 and 64, self pulls among the draws; softmax regression
     ("cfg2", dict(M=5, dims=(72, 96, 10), batch=32), 40), ("cfg2", dict(M=16, dims=(200, 64, 7), batch=64), 50), ("cfg2", dict(M=40, dims=(40, 32, 16), batch=64), 200),

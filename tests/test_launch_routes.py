@@ -47,3 +47,15 @@ def test_launches_that_wait_are_cooperative(routes, dims, M, batch, kernel, few,
 @pytest.mark.parametrize("dims,M,batch", [((784, 10), 37, 64), ((784, 512, 10), 17, 64), ((256, 10), 257, 32)])
 def test_more_workgroups_than_fit(routes, dims, M, batch):
     assert all(how == "plain" for how, _ in routes(dims, M, batch, 20)[1])
+
+
+@pytest.mark.parametrize("offset", [0, 4, 8, 12, 16])
+def test_features_that_start_anywhere(routes, offset):
+    """The resident kernel adds the hidden layer's products as fwd_f32_kernel does; where the separate calls take another forward kernel because the
+    features do not start at a multiple of 16 bytes, netmax_run takes that one, too."""
+    calls, run = routes((784, 512, 10), 16, 64, 8, offset=offset)
+    if offset % 16 == 0:
+        assert ("plain", "fwd_f32_kernel") in calls and run == [("cooperative", RESIDENT)]
+    else:
+        forward = calls[2]
+        assert forward[1] not in ("fwd_f32_kernel", RESIDENT) and run.count(forward) == 8 and all(how == "plain" for how, _ in run)
