@@ -49,7 +49,7 @@ struct SmallIterArgs {
     const uint32_t *thr; const int32_t *last; const float *w;
     float *x_first, *x_second;              // x_first holds x^t of the first iteration of the launch
     float *V, *G, *loss;
-    int32_t *peers, *idx;
+    int32_t *peers;
     float alpha, mu, wd;
     uint64_t seed;
     IterRef iter;                           // number of the first iteration
@@ -642,7 +642,7 @@ hipError_t launch_small_iter(hipStream_t s, const SmallIterLaunch &a)
     p.M = a.M; p.B = a.B; p.din = (int)a.din; p.dout = (int)a.dout; p.D = a.D; p.ld = a.ld;
     p.feats = a.feats; p.labels = a.labels; p.row0 = a.row0; p.n_rows = a.n_rows;
     p.thr = a.thr; p.last = a.last; p.w = a.w;
-    p.x_first = a.x_first; p.x_second = a.x_second; p.V = a.V; p.G = a.G; p.loss = a.loss; p.peers = a.peers; p.idx = a.idx;
+    p.x_first = a.x_first; p.x_second = a.x_second; p.V = a.V; p.G = a.G; p.loss = a.loss; p.peers = a.peers;
     p.alpha = a.alpha; p.mu = a.mu; p.wd = a.wd; p.seed = a.seed; p.iter = a.iter; p.n_iters = a.n_iters;
     p.barrier = a.barrier; p.barrier_base = a.barrier_base; p.fault = a.fault;
     p.patience = a.patience;

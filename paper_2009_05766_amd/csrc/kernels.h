@@ -112,7 +112,7 @@ void launch_unpack(hipStream_t s, int M, int64_t cols, const float *tiled, float
 void launch_widen_bf16(hipStream_t s, int64_t n, const uint16_t *in, float *out);
 
 // Whole iterations of a small softmax-regression model in one kernel, one workgroup per worker (k_small_iter.hip).
-// grad_only: batch draw, loss and gradient only (G, loss, idx); otherwise also the peer draw (peers) and the update
+// grad_only: batch draw, loss and gradient only (G, loss); otherwise also the peer draw (peers) and the update
 // (x_second, V).  n_iters > 1 is a cooperative launch, for which all workgroups have to fit the device together: x_first / x_second swap roles after every iteration and
 // the workgroups meet at a barrier (counter `barrier`, which the launch advances by (n_iters - 1) * M from
 // barrier_base); *fault is raised if a workgroup waited in vain.
@@ -120,7 +120,7 @@ struct SmallIterLaunch {
     int M, B; int64_t din, dout, D, ld;
     const float *feats; const int32_t *labels; const int64_t *row0; const int32_t *n_rows;
     const uint32_t *thr; const int32_t *last; const float *w;
-    float *x_first, *x_second, *V, *G, *loss; int32_t *peers, *idx;
+    float *x_first, *x_second, *V, *G, *loss; int32_t *peers;
     float alpha, mu, wd; uint64_t seed; IterRef iter; int n_iters, grad_only;
     unsigned *barrier; unsigned barrier_base; int *fault;
     const AsyncSlots *slots;                 // grad_only: one workgroup per slot instead of per worker (NULL: all workers at `iter`)

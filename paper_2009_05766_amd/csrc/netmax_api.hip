@@ -41,7 +41,7 @@ struct netmax_ctx {
     bool data_bound = false;
     int64_t *d_row0 = nullptr;
     int32_t *d_nrows = nullptr;
-    int32_t *d_idx = nullptr;                 // batch rows [draw_chunk][M][batch]; a single iteration uses the first block
+    int32_t *d_idx = nullptr;                 // batch rows [draw_chunk][M][batch]; a single iteration uses the first block (not for `small`: drawn in the kernel)
     int32_t *d_draw_peers = nullptr;          // netmax_run: peers [draw_chunk][M] of the iterations drawn ahead
     int draw_chunk = 1;                       // iterations that netmax_run draws in one launch
     float *d_act[NETMAX_MAX_LAYERS + 1] = {};
@@ -385,7 +385,6 @@ extern "C" int netmax_init(netmax_ctx **out, const netmax_config *cfg)
                 want(&ctx->d_dzt[q], MB * widest);
             }
         }
-        want(&ctx->d_idx, MB * ctx->draw_chunk);
         want(&ctx->d_row0, M);
         want(&ctx->d_nrows, M);
         want(&ctx->d_loss, M);
@@ -397,6 +396,8 @@ extern "C" int netmax_init(netmax_ctx **out, const netmax_config *cfg)
             ctx->small_resident = small_iter_max_resident(cfg->batch, cfg->dims[0], cfg->dims[1], cfg->ld);
             want(&ctx->d_barrier, 1);
             want(&ctx->d_fault, 1);
+        } else {
+            want(&ctx->d_idx, MB * ctx->draw_chunk);
         }
         const MlpPlan plan = make_plan(ctx);         // its shapes: nothing is allocated yet
         if (!ctx->small && sliced_iter_ok(plan)) {
@@ -645,7 +646,7 @@ static SmallIterLaunch small_launch(netmax_ctx *ctx, const IterRef &iter, int n_
     a.feats = (const float *)ctx->feats; a.labels = ctx->labels; a.row0 = ctx->d_row0; a.n_rows = ctx->d_nrows;
     a.thr = ctx->d_thr; a.last = ctx->d_last; a.w = ctx->d_w;
     a.x_first = ctx->x_cur; a.x_second = ctx->x_next; a.V = ctx->v; a.G = ctx->g; a.loss = ctx->d_loss;
-    a.peers = peers_dev; a.idx = ctx->d_idx;
+    a.peers = peers_dev;
     a.alpha = c.lr; a.mu = c.momentum; a.wd = c.weight_decay; a.seed = c.seed; a.iter = iter; a.n_iters = n_iters;
     a.grad_only = grad_only ? 1 : 0;
     a.barrier = ctx->d_barrier; a.barrier_base = ctx->barrier_count; a.fault = ctx->d_fault;
