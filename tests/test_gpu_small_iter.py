@@ -3,16 +3,36 @@ import numpy as np
 import pytest
 import torch
 
+import paper_2009_05766_amd as nm
 from harness import inputs_of, make_gpu, make_oracle, rel_err_rows
 from netmax_inputs import workload
+from whole_iteration_cases import GROUPS_OF_UNITS, ONE_WORKGROUP, SLICES, SMALL
 
 pytestmark = pytest.mark.gpu
 
 
-def _run_is_calls_and_oracle(over, runs, name="cfg1"):
+def _in_one_launch(w, inp, n):
+    """Whether netmax_run makes n iterations in one launch whose workgroups wait for each other: with a patience of no polls such a launch, and only
+    such a one, reports a fault."""
+    net = make_gpu(w, inp)
+    nm.netmax_set_barrier_patience(net.ctx, 0)
+    net.run(0, n)
+    try:
+        net.consensus_dist()
+        return False
+    except nm.NetmaxError as e:
+        assert e.code == nm.NETMAX_EDEVICE
+        return True
+    finally:
+        net.close()
+
+
+def _run_is_calls_and_oracle(over, runs, name="cfg1", kernel=SMALL):
+    """kernel: which one makes the longest of the runs in one launch, None: none."""
     w = workload(name, **over)
     inp = inputs_of(w)
     inp["labels"] = np.minimum(inp["labels"], w.dims[-1] - 1).astype(np.int32)
+    assert _in_one_launch(w, inp, max(runs)) == (kernel is not None)
     calls, run, o = make_gpu(w, inp), make_gpu(w, inp), make_oracle(w, inp)
     it = 0
     for n in runs:
@@ -46,19 +66,9 @@ def test_divisors_of_one(dims):
     _run_is_calls_and_oracle(dict(M=3, dims=dims, batch=24, n_per_worker=50), (2, 1, 9))
 
 
-@pytest.mark.parametrize("over", [
-    # groups of draws: sixteen iterations, fifteen, five, one
-    dict(M=3, dims=(20, 10), batch=64, n_per_worker=90), dict(M=3, dims=(21, 9), batch=65, n_per_worker=90), dict(M=2, dims=(6, 3), batch=200, n_per_worker=230),
-    dict(M=2, dims=(3, 2), batch=600, n_per_worker=640),
-    # peers counted by more than one wave, by every wave
-    dict(M=65, dims=(24, 5), batch=9, n_per_worker=20), dict(M=256, dims=(12, 4), batch=4, n_per_worker=9),
-    # matrix-instruction form: one, two and four row tiles; parts of one step, of odd and of even numbers of steps; few vectors and many
-    dict(M=3, dims=(128, 10), batch=16, n_per_worker=40), dict(M=5, dims=(384, 16), batch=16, n_per_worker=40), dict(M=3, dims=(128, 7), batch=32, n_per_worker=40),
-    dict(M=8, dims=(256, 10), batch=32, n_per_worker=40), dict(M=3, dims=(640, 3), batch=32, n_per_worker=40), dict(M=4, dims=(64, 16), batch=64, n_per_worker=80),
-    dict(M=3, dims=(192, 2), batch=64, n_per_worker=80), dict(M=3, dims=(256, 10), batch=64, n_per_worker=80),
-])
-def test_whole_iterations(over):
-    _run_is_calls_and_oracle(over, (1, 34, 2))
+@pytest.mark.parametrize("kernel,over", ONE_WORKGROUP)
+def test_whole_iterations(kernel, over):
+    _run_is_calls_and_oracle(over, (1, 34, 2), kernel=kernel)
 
 
 def test_runs_on_several_streams():
@@ -87,24 +97,14 @@ def test_runs_on_several_streams():
     nets[1].close(), calls.close()
 
 
-@pytest.mark.parametrize("over", [
-    # slices of seven steps (the waves of the last-layer kernel), four waves' and eight waves'; one row tile, two and four
-    dict(M=16, dims=(784, 10), batch=64), dict(M=3, dims=(784, 10), batch=16), dict(M=2, dims=(512, 16), batch=64), dict(M=5, dims=(900, 3), batch=32),
-    # a last slice of one step, of part of a step, features that are a multiple of four only; batches that fill no row tile
-    dict(M=3, dims=(788, 10), batch=64), dict(M=4, dims=(1028, 7), batch=33), dict(M=3, dims=(500, 10), batch=64), dict(M=3, dims=(900, 2), batch=9),
-    # slices of eight steps, and one step more than that (the separate kernels)
-    dict(M=3, dims=(1024, 16), batch=50), dict(M=2, dims=(512, 5), batch=20), dict(M=2, dims=(1028, 16), batch=20),
-    # as many workgroups as are resident, and one worker more than that (the separate kernels)
-    dict(M=73, dims=(784, 10), batch=40), dict(M=150, dims=(784, 10), batch=24),
-])
-def test_iterations_in_slices(over):
-    _run_is_calls_and_oracle(dict(n_per_worker=over["batch"] + 7, **over), (1, 18, 2), "cfg2")
+@pytest.mark.parametrize("kernel,over", SLICES)
+def test_iterations_in_slices(kernel, over):
+    _run_is_calls_and_oracle(dict(n_per_worker=over["batch"] + 7, **over), (1, 18, 2), "cfg2", kernel)
 
 
 @pytest.mark.parametrize("dims", [(784, 10), (104, 96, 10)])
 def test_workgroups_that_give_up_are_reported(dims):
     """Patience of zero polls: every wait of the kernel gives up at once, the launch ends, the next consensus distance reports it."""
-    import paper_2009_05766_amd as nm
     w = workload("cfg2", M=4, dims=dims, batch=64, n_per_worker=70)
     inp = inputs_of(w)
     net, calls = make_gpu(w, inp), make_gpu(w, inp)
@@ -123,19 +123,14 @@ def test_workgroups_that_give_up_are_reported(dims):
     net.close(), calls.close(), again.close()
 
 
-@pytest.mark.parametrize("over", [
-    # units of one workgroup, of several, of all compute units; both batches; strips of features that end inside, one per wave and four
-    dict(M=3, dims=(64, 32, 10), batch=64), dict(M=2, dims=(8, 64, 3), batch=32), dict(M=5, dims=(264, 96, 16), batch=32), dict(M=16, dims=(784, 512, 10), batch=64),
-    dict(M=9, dims=(784, 160, 10), batch=64), dict(M=3, dims=(856, 64, 2), batch=32), dict(M=2, dims=(200, 1024, 7), batch=64), dict(M=128, dims=(40, 64, 5), batch=32),
-    # more units than words asked for together; more workgroups than compute units, columns that do not fit LDS (the separate kernels)
-    dict(M=4, dims=(96, 800, 10), batch=64), dict(M=3, dims=(96, 544, 10), batch=32), dict(M=3, dims=(64, 352, 4), batch=64), dict(M=17, dims=(96, 512, 10), batch=64), dict(M=2, dims=(1000, 64, 10), batch=32),
-])
-def test_iterations_of_resident_perceptrons(over):
+@pytest.mark.parametrize("kernel,over", GROUPS_OF_UNITS)
+def test_iterations_of_resident_perceptrons(kernel, over):
     """One hidden layer: every workgroup keeps 32 units of a worker.  All state, losses and hidden activations are the separate calls' bits;
     the oracle bounds them until a ReLU decision next to zero differs (the tolerance is the one of the other short perceptron runs)."""
     w = workload("cfg2", n_per_worker=over["batch"] + 7, **over)
     inp = inputs_of(w)
     hyper = dict(momentum=0.9, weight_decay=1e-4)
+    assert _in_one_launch(w, inp, 18) == (kernel is not None)
     calls, run, o = make_gpu(w, inp, **hyper), make_gpu(w, inp, **hyper), make_oracle(w, inp, **hyper)
     for net in (calls, run):
         net.x_b.fill_(3.0)                                   # every element of the next parameters has to be written
@@ -188,7 +183,6 @@ def test_features_that_start_anywhere(dims, batch, skip):
 def test_async_steps_in_place(name, over, n):
     """Asynchronous steps on the workers' rows where they lie: draws, x, v, the last gradient of every worker and its loss against the oracle's
     sequential steps; rows of workers that are never drawn keep their bits."""
-    import paper_2009_05766_amd as nm
     w = workload(name, n_per_worker=over["batch"] + 9, **over)
     inp = inputs_of(w)
     gpu, o = make_gpu(w, inp, momentum=0.9), make_oracle(w, inp, momentum=0.9)

@@ -6,9 +6,9 @@ import subprocess
 import pytest
 
 from paper_2009_05766_amd.build import LIB, build
+from whole_iteration_cases import GROUPS_OF_UNITS, ONE_WORKGROUP, RESIDENT, SLICED, SLICES, SMALL
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-SMALL, SLICED, RESIDENT = "small_softmax_iteration_kernel", "sliced_softmax_kernel", "resident_mlp_kernel"
 
 pytestmark = pytest.mark.skipif(shutil.which("g++") is None or not os.path.exists("/opt/rocm/include/hip/hip_runtime_api.h"), reason="needs g++ and the HIP headers")
 
@@ -59,3 +59,12 @@ def test_features_that_start_anywhere(routes, offset):
     else:
         forward = calls[2]
         assert forward[1] not in ("fwd_f32_kernel", RESIDENT) and run.count(forward) == 8 and all(how == "plain" for how, _ in run)
+
+
+@pytest.mark.parametrize("kernel,over", ONE_WORKGROUP + SLICES + GROUPS_OF_UNITS)
+def test_cases_reach_their_kernel(routes, kernel, over):
+    run = routes(over["dims"], over["M"], over["batch"], 18)[1]
+    if kernel:
+        assert run == [("cooperative", kernel)]
+    else:
+        assert all(how == "plain" and name not in (SMALL, SLICED, RESIDENT) for how, name in run)
