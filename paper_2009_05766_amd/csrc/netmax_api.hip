@@ -355,8 +355,9 @@ extern "C" int netmax_init(netmax_ctx **out, const netmax_config *cfg)
     INIT_TRY(prepare_mix_synth());
     prepare_kernels();
     // what the context keeps on the device, carved from one allocation
-    std::vector<std::pair<void **, size_t>> parts;
+    std::vector<std::pair<void **, size_t>> parts, cleared;
     auto want = [&](auto **where, size_t count) { parts.emplace_back(reinterpret_cast<void **>(where), count * sizeof(**where)); };
+    auto want_cleared = [&](auto **where, size_t count) { cleared.emplace_back(reinterpret_cast<void **>(where), count * sizeof(**where)); };
     want(&ctx->d_thr, mm);
     want(&ctx->d_last, M);
     want(&ctx->d_w, mm);
@@ -394,8 +395,8 @@ extern "C" int netmax_init(netmax_ctx **out, const netmax_config *cfg)
         if (ctx->small) {
             INIT_TRY(prepare_small_iter(cfg->batch, cfg->dims[0], cfg->dims[1], cfg->ld));
             ctx->small_resident = small_iter_max_resident(cfg->batch, cfg->dims[0], cfg->dims[1], cfg->ld);
-            want(&ctx->d_barrier, 1);
-            want(&ctx->d_fault, 1);
+            want_cleared(&ctx->d_barrier, 1);
+            want_cleared(&ctx->d_fault, 1);
         } else {
             want(&ctx->d_idx, MB * ctx->draw_chunk);
         }
@@ -407,10 +408,10 @@ extern "C" int netmax_init(netmax_ctx **out, const netmax_config *cfg)
             if (ctx->sliced) {
                 size_t biases = 0;
                 sliced_iter_scratch(plan, ctx->n_parts, biases, ctx->n_counters);
-                want(&ctx->d_parts, ctx->n_parts);
+                want_cleared(&ctx->d_parts, ctx->n_parts);
                 want(&ctx->d_biases, biases);
-                want(&ctx->d_counters, ctx->n_counters);
-                want(&ctx->d_fault, 1);
+                want_cleared(&ctx->d_counters, ctx->n_counters);
+                want_cleared(&ctx->d_fault, 1);
             }
         }
         if (!ctx->sliced && resident_mlp_ok(plan)) {
@@ -420,10 +421,10 @@ extern "C" int netmax_init(netmax_ctx **out, const netmax_config *cfg)
             if (ctx->resident_mlp) {
                 size_t biases = 0;
                 resident_mlp_scratch(plan, ctx->n_parts, biases, ctx->n_counters);
-                want(&ctx->d_parts, ctx->n_parts);
+                want_cleared(&ctx->d_parts, ctx->n_parts);
                 want(&ctx->d_biases, biases);
-                want(&ctx->d_counters, ctx->n_counters);
-                want(&ctx->d_fault, 1);
+                want_cleared(&ctx->d_counters, ctx->n_counters);
+                want_cleared(&ctx->d_fault, 1);
             }
         }
         for (int l = 0; l < cfg->n_layers && !ctx->small; ++l)
@@ -438,19 +439,18 @@ extern "C" int netmax_init(netmax_ctx **out, const netmax_config *cfg)
         want(&ctx->d_tail_tiles, tail_tiles.size());
     }
     size_t total = 0;
+    const size_t kept = parts.size();
+    parts.insert(parts.end(), cleared.begin(), cleared.end());
     for (const auto &part : parts) total += (part.second + 255) / 256 * 256;
     INIT_TRY(hipMalloc(&ctx->d_block, total));
-    char *at = (char *)ctx->d_block;
-    for (const auto &part : parts) {
-        *part.first = at;
-        at += (part.second + 255) / 256 * 256;
+    size_t at = 0, clear_from = total;
+    for (size_t k = 0; k < parts.size(); ++k) {
+        if (k == kept) clear_from = at;
+        *parts[k].first = (char *)ctx->d_block + at;
+        at += (parts[k].second + 255) / 256 * 256;
     }
-    if (ctx->small) INIT_TRY(hipMemset(ctx->d_barrier, 0, sizeof(unsigned)));
-    if (ctx->d_counters) {
-        INIT_TRY(hipMemset(ctx->d_counters, 0, ctx->n_counters * sizeof(unsigned)));
-        INIT_TRY(hipMemset(ctx->d_parts, 0, ctx->n_parts * sizeof(unsigned long long)));
-    }
-    if (ctx->d_fault) INIT_TRY(hipMemset(ctx->d_fault, 0, sizeof(int)));
+    // on the context's own stream: nothing else orders it ahead of the kernels there
+    if (clear_from < total) INIT_TRY(hipMemsetAsync((char *)ctx->d_block + clear_from, 0, total - clear_from, ctx->stream));
     if (!tail_tiles.empty())
         INIT_TRY(hipMemcpy(ctx->d_tail_tiles, tail_tiles.data(), tail_tiles.size() * sizeof(int32_t), hipMemcpyHostToDevice));
 #undef INIT_TRY
@@ -1210,7 +1210,7 @@ extern "C" int netmax_set_barrier_patience(netmax_ctx *ctx, int64_t polls)
     HIP_TRY(ctx, hipSetDevice(ctx->device));
     HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
     ctx->barrier_patience = polls;
-    if (ctx->d_fault) HIP_TRY(ctx, hipMemset(ctx->d_fault, 0, sizeof(int)));
+    if (ctx->d_fault) HIP_TRY(ctx, hipMemsetAsync(ctx->d_fault, 0, sizeof(int), ctx->stream));
     return NETMAX_OK;
 }
 

@@ -69,7 +69,8 @@ hipError_t hipMalloc(void **p, size_t n) { *p = calloc(1, n); return *p ? hipSuc
 hipError_t hipFree(void *p) { free(p); return hipSuccess; }
 hipError_t hipMemcpy(void *to, const void *from, size_t n, hipMemcpyKind) { memcpy(to, from, n); return hipSuccess; }
 hipError_t hipMemcpyAsync(void *to, const void *from, size_t n, hipMemcpyKind, hipStream_t) { memcpy(to, from, n); return hipSuccess; }
-hipError_t hipMemset(void *p, int v, size_t n) { memset(p, v, n); return hipSuccess; }
+// on the null stream: not ordered ahead of what a context's own stream does, so not for its memory
+hipError_t hipMemset(void *, int, size_t) { return hipErrorNotSupported; }
 hipError_t hipMemsetAsync(void *p, int v, size_t n, hipStream_t) { memset(p, v, n); return hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
 hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus *status)
