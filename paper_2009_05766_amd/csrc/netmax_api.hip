@@ -7,6 +7,7 @@
 #include "philox.h"
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -237,6 +238,20 @@ static bool capturing(hipStream_t s)
     return s && (hipStreamIsCapturing(s, &status) != hipSuccess || status != hipStreamCaptureStatusNone);
 }
 
+__global__ void no_work_kernel() {}
+
+// A process's first cooperative launch on a device makes the runtime create a queue for such launches (4 ms on the host).  netmax_init makes it, so that
+// the first netmax_run does not.
+static hipError_t first_cooperative_launch(int device, hipStream_t s)
+{
+    static std::atomic<uint64_t> made{0};                     // a bit for each of the first 64 devices; two threads at once: both launch
+    const uint64_t bit = device < 64 ? 1ull << device : 0;
+    if (!bit || (made.load() & bit)) return hipSuccess;
+    const hipError_t e = hipLaunchCooperativeKernel(reinterpret_cast<const void *>(no_work_kernel), dim3(1), dim3(64), nullptr, 0, s);
+    if (e == hipSuccess) made.fetch_or(bit);
+    return e;
+}
+
 static void release(netmax_ctx *ctx)
 {
     drop_graphs(ctx);
@@ -427,6 +442,7 @@ extern "C" int netmax_init(netmax_ctx **out, const netmax_config *cfg)
                 want_cleared(&ctx->d_fault, 1);
             }
         }
+        if (ctx->sliced || ctx->resident_mlp || (ctx->small && ctx->small_resident >= M)) INIT_TRY(first_cooperative_launch(ctx->device, ctx->stream));
         for (int l = 0; l < cfg->n_layers && !ctx->small; ++l)
             if (update_end(plan, l) > 0) {
                 ctx->tail = true;

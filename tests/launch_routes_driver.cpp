@@ -2,8 +2,8 @@
 // the shared library), so that calls of the C ABI run their host code, device memory is host memory and launches are printed.
 //   launch_routes_driver libnetmax.so < cases
 // A case is a line: iterations, workers, batch, bytes by which the features miss an aligned address, 1 for a stream under capture, 1 for a
-// device with cooperative launches, layer widths.  A line of output: "plain:kernel" or "cooperative:kernel" in order: one iteration by separate
-// calls, '|', netmax_run.
+// device with cooperative launches, layer widths.  A line of output: "plain:kernel" or "cooperative:kernel" in order: netmax_init, '|', one
+// iteration by separate calls, '|', netmax_run.
 #include <hip/hip_runtime_api.h>
 
 #include <cstdio>
@@ -121,11 +121,12 @@ int main(int argc, char **argv)
         netmax_ctx *ctx = nullptr;
         g_capturing = false;
         g_cooperative = cooperative;
+        g_out.str("");
         int rc = netmax_init_(&ctx, &c);
         if (rc == NETMAX_OK) rc = netmax_bind_state_(ctx, at(1), at(2), at(3), at(4));
         if (rc == NETMAX_OK) rc = netmax_bind_data_(ctx, reinterpret_cast<char *>(at(5)) + offset, reinterpret_cast<int32_t *>(at(6)), off.data());
         g_capturing = capture;
-        g_out.str("");
+        g_out << " |";
         if (rc == NETMAX_OK) rc = netmax_sample_peers_(ctx, 0, peers.data());
         if (rc == NETMAX_OK) rc = netmax_local_step_(ctx, 0);
         if (rc == NETMAX_OK) rc = netmax_mix_(ctx, 0, peers.data());

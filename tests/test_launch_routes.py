@@ -22,10 +22,13 @@ def routes(tmp_path_factory):
 
     def of(dims, M, batch, iters, offset=0, capture=0, cooperative=1):
         """-> launches of one iteration by separate calls, launches of netmax_run: lists of (how, kernel)."""
-        line = " ".join(str(v) for v in (iters, M, batch, offset, capture, cooperative, *dims))
-        r = subprocess.run([exe, lib], input=line, capture_output=True, text=True, timeout=120)
+        return drive([" ".join(str(v) for v in (iters, M, batch, offset, capture, cooperative, *dims))])[0][1:]
+
+    def drive(lines):
+        r = subprocess.run([exe, lib], input="\n".join(lines), capture_output=True, text=True, timeout=120)
         assert r.returncode == 0, r.stderr
-        return [[tuple(launch.split(":")) for launch in part.split()] for part in r.stdout.split("|")]
+        return [[[tuple(launch.split(":")) for launch in part.split()] for part in line.split("|")] for line in r.stdout.splitlines()]
+    of.drive = drive
     return of
 
 
@@ -42,6 +45,13 @@ def test_launches_that_wait_are_cooperative(routes, dims, M, batch, kernel, few,
     for over in (dict(capture=1), dict(cooperative=0)):
         run = routes(dims, M, batch, many, **over)[1]
         assert len(run) >= many and all(how == "plain" and (name == SMALL) == (kernel == SMALL) for how, name in run)
+
+
+def test_first_cooperative_launch_of_a_process(routes):
+    """It takes milliseconds and belongs to preparation; contexts that make no such launches do without, further ones do not repeat it."""
+    first = [[launch for launch in parts[0] if launch[0] == "cooperative"] for parts in
+             routes.drive(["9 4 50 0 0 1 100 50 10", "9 8 32 0 0 0 256 10", "9 16 64 0 0 1 784 10", "9 8 32 0 0 1 256 10"])]
+    assert first == [[], [], [("cooperative", "no_work_kernel")], []]
 
 
 @pytest.mark.parametrize("dims,M,batch", [((784, 10), 37, 64), ((784, 512, 10), 17, 64), ((256, 10), 257, 32)])
