@@ -181,8 +181,9 @@ int netmax_mix(netmax_ctx *ctx, uint64_t iter, const int32_t *peers_dev);
  * the device at once), fewer are one launch each; with use_graph the replayed graph holds that kernel.  Same
  * results bit for bit: netmax_local_step runs the same gradient code for such models and every kernel applies the
  * update with the same instructions.  Larger ones (up to 1024 features in pieces of four, 16 classes, batch 64) are cut into slices of
- * the features, a workgroup each, and so are perceptrons on float operands with one hidden layer (a multiple of 32 units, batch 32 or 64,
- * up to about 870 features in pieces of eight) into groups of 32 units; they run the same way without use_graph where that is faster (from five
+ * the features, a workgroup each, and so are perceptrons on float operands with one hidden layer (a multiple of 32 units, up to 1024 of them, batch 32
+ * or 64, features in pieces of eight, 16-byte aligned, as many as fit LDS beside the padding: features + (ld - D) / 16 up to 870 with a batch of 64,
+ * 925 with one of 32) into groups of 32 units; they run the same way without use_graph where that is faster (from five
  * iterations on; from two to many, by size) and all workgroups of all workers fit the device at once.  The runtime runs cooperative launches of
  * several contexts on a device one after the other.  In a stream that is being captured the kernels of an iteration are launched one by one.  Should a workgroup ever wait at the barrier in vain, the kernel still ends, the
  * parameters are invalid and the next netmax_consensus_dist returns NETMAX_EDEVICE. */

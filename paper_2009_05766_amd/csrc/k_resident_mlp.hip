@@ -8,8 +8,9 @@
 // below needs no other unit: dZ2 gives dW2's rows, the error of the units and their columns of dW1, which are updated where the product leaves
 // them.  The peer's columns come from the workgroup of the same units, which wrote them half an iteration before.
 //
-// 784-512-10, batch 64, 16 workers (all 256 compute units), four iterations: 150 us, 20 of them the cooperative launch's, the separate kernels 211.
-// An iteration takes 27 us:
+// 784-512-10, batch 64, 16 workers (all 256 compute units), four iterations: 157 us, 17 of them outside the kernel (a cooperative launch), the separate
+// kernels 211.  The matrix units are busy 36 % of the time; the waves wait for memory, LDS or each other 40 % and for their turn to issue 41 % of theirs.  An
+// iteration takes 27 us (this and what follows: time stamps in a copy of the kernel):
 // forward 7.3 (its matrix instructions 5.3), the waves' tiles added 1.9, exchange and softmax 4.5, error 1.1, dW1 and its update the rest, beside
 // them the rows of W2 (3, two waves).  The strips of dW1 are bound by addresses and waiting, not by their matrix instructions (5.4).  What it
 // is made of (four iterations, launched plainly): loads in global and not in flat address space (169 -> 143 us), the next strip's batch rows asked for before this one's stores, the
@@ -540,7 +541,8 @@ __global__ void __launch_bounds__(RM_THREADS) resident_mlp_kernel(ResidentArgs p
 static int64_t rm_padding(const MlpPlan &p) { return p.ld - (p.dims[0] * p.dims[1] + p.dims[1] + p.dims[1] * p.dims[2] + p.dims[2]); }
 
 // One hidden layer that fwd_f32_kernel and wgrad_f32_kernel take, classes and units in the parts that head_logits_kernel then adds, 32-bit byte
-// offsets inside the parameters, columns that fit LDS.  Of the data netmax_bind_data asks the rest.
+// offsets inside the parameters, columns that fit LDS (32 features x 4 bytes and the padding's x and v, which every workgroup has room for: features +
+// padding / 16 up to 870 with a batch of 64, 925 with one of 32).  Of the data netmax_bind_data asks the rest.
 bool resident_mlp_ok(const MlpPlan &p)
 {
     return p.n_layers == 2 && !p.bf16 && (p.B == 32 || p.B == 64) && p.dims[0] % RM_KS == 0 && p.dims[1] % RM_COLS == 0 && head_parts_of_two(p) &&

@@ -2,8 +2,9 @@
 // a worker's features are cut into slices, one workgroup keeps a slice of the parameters, of the momentum and of the batch rows in LDS.
 // An iteration needs two exchanges: the slices of a worker add up their partial logits, and a slice pulls the peer's same slice.
 // The logits cross the chip once per iteration (stored, counted, polled, read: about 2 us); the peer's row was stored half an iteration
-// before it is asked for.  784-10, batch 64, 16 workers, eight iterations 73 us, 20 of them the cooperative launch's, where the draws and the two
-// kernels of k_grad_head.hip take 89.  An iteration in 6.6 us: logits 1.2, their
+// before it is asked for.  784-10, batch 64, 16 workers, eight iterations 75 us, 21 of them outside the kernel (a cooperative launch), where the draws and
+// the two kernels of k_grad_head.hip take 89 to 94.  The matrix units are busy 12 % of the time; the waves wait for memory, LDS or each other 51 % of theirs.
+// An iteration in 6.6 us (time stamps in a copy of the kernel): logits 1.2, their
 // exchange 1.5, softmax and waiting 1.1, gradient and update 1.8, the rest draws, row addresses and barriers.
 //
 // The slices are the runs of features that the waves of head_logits_kernel take, and all sums are made in that kernel's and in

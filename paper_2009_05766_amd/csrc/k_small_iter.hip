@@ -22,8 +22,8 @@
 // the new parameters stay in LDS, only the peer's row is read again.  A workgroup arrives at the barrier with its new row and looks for
 // the others' arrival after the softmax of the next iteration, where it needs the peer's: half an iteration during which the last
 // ones catch up.  256-10, batch 32, 8 workers, sixteen iterations in a call: 145 us with the barrier between iterations (release
-// and acquire of the whole cache, about 2 us), a draw per iteration and stores between the loads of the update, 97 us now, 20 of them the cooperative
-// launch's; an iteration takes 4.3 us: rows into LDS 0.2, forward 1.0, softmax 0.8, waiting 0.3, gradient 1.2, update 0.7.
+// and acquire of the whole cache, about 2 us), a draw per iteration and stores between the loads of the update, 97 us now, 20 of them outside the
+// kernel (a cooperative launch); an iteration takes 4.3 us (time stamps in a copy of the kernel): rows into LDS 0.2, forward 1.0, softmax 0.8, waiting 0.3, gradient 1.2, update 0.7.
 #include "kernels.h"
 #include "layout.h"
 #include "philox.h"

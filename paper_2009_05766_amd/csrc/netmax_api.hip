@@ -1063,7 +1063,7 @@ extern "C" int netmax_async_run(netmax_ctx *ctx, uint64_t first_step, uint64_t n
     const int cap = std::min<int>(c.M, ASYNC_MAX_BATCH);
     const bool in_order = c.model == NETMAX_FLAT && (int64_t)c.M * c.ld > ASYNC_IN_ORDER_FLOATS;
     // Kernels that take a list of workers read and update their rows where they lie: four launches a batch instead of six (784-512-10,
-    // 16 workers, batch 64, 64 steps 733 us with a gather of the rows and a kernel that updates them, 550 us without).
+    // 16 workers, batch 64, 64 steps 730 us with a gather of the rows and a kernel that updates them, 579 us without).
     const bool lists = c.model == NETMAX_MLP && !ctx->small && layer_list_ok(make_plan(ctx));
     if (lists && !ctx->d_lists) HIP_TRY(ctx, hipMalloc(&ctx->d_lists, (size_t)ASYNC_WINDOW * (2 + c.batch) * sizeof(int32_t)));
     int32_t *const list_peers = lists ? ctx->d_lists + ASYNC_WINDOW : nullptr, *const list_rows = lists ? ctx->d_lists + 2 * ASYNC_WINDOW : nullptr;
