@@ -214,6 +214,200 @@ __global__ void __launch_bounds__(64 * SH_WAVES) shared_fwd_kernel(TileFwd p)
     }
 }
 
+// Long contractions in few blocks: 32 columns and RT x 32 batch rows, eight waves that share the contraction.  Wave w takes the steps w, w + 8, ...
+// of 64 bytes of every row of A (sixteen indices, bfloat16 32), asked for two steps ahead.  A crosses LDS by way of the wave's own buffer, so
+// that four lanes read 64 neighbouring bytes of a row; a lane per row, in the layout of the matrix instruction, takes 64 turns of the cache a load
+// instead of 16 (7 x 3072 -> 1024, batch 128, fp32 94 us, 71 with it).  A lane's operands of W are neighbouring rows of its column, each a load
+// of a float (32 lanes 128 bytes of a row).  No barrier until the waves' parts are added, in the order of the waves.  TAIL: indices behind
+// the last whole step.
+// Bound by the chain of loads where there are few blocks, then by the bytes of W: bfloat16 9 x 2432 -> 256, batch 32, 11 us (fwd_mfma_kernel 56),
+// 32 x 3072 -> 256, batch 32, 20 us (69; 100 MB), 16 x 784 -> 500, batch 100, 13.2 us (tile_fwd_kernel 18.9); fp32 12 x 784 -> 768, batch
+// 128, 31 us (shared_fwd_kernel 39).  Three steps ahead take more than 128 registers, one workgroup a compute unit: 81 x 784 -> 426,
+// batch 64, fp32 64 us and 53 with two.
+constexpr int WF_WAVES = 8, WF_THREADS = 64 * WF_WAVES, WF_COLS = 32, WF_PITCH = WF_COLS + 1, WF_DEPTH = 2;
+typedef uint32_t tile_u32x4_any __attribute__((ext_vector_type(4), aligned(2)));
+template <bool BF> struct WaveOperand { typedef f32x4 piece; typedef float elem; typedef tile_f32x4_any any; };      // piece: 16 bytes of a row
+template <> struct WaveOperand<true> { typedef tile_u32x4 piece; typedef uint16_t elem; typedef tile_u32x4_any any; };
+template <int RT>
+__device__ __forceinline__ void wave_multiply(const f32x4 (&a)[RT], const float *w, tile_f32x16 (&acc)[RT])
+{
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int i = 0; i < RT; ++i) acc[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i][e], w[e], acc[i], 0, 0, 0);
+}
+template <int RT>
+__device__ __forceinline__ void wave_multiply(const tile_u32x4 (&a)[RT], const float *w, tile_f32x16 (&acc)[RT])
+{
+    const tile_u32x4 b = {pack_bf16x2(w[0], w[1]), pack_bf16x2(w[2], w[3]), pack_bf16x2(w[4], w[5]), pack_bf16x2(w[6], w[7])};
+#pragma unroll
+    for (int i = 0; i < RT; ++i)
+        acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(tile_bf16x8, a[i]), __builtin_bit_cast(tile_bf16x8, b), acc[i], 0, 0, 0);
+}
+// 16-byte unit of piece `at` (0 .. 3) of a row: sixteen rows' pieces, written or read together, then lie in different banks
+__device__ __forceinline__ int wave_unit(int row, int at) { return 4 * row + ((at ^ (row >> 2)) & 3); }
+
+template <bool BF, int RT, bool TAIL>
+__global__ void __launch_bounds__(WF_THREADS) wave_fwd_kernel(TileFwd p)
+{
+    constexpr int PE = BF ? 8 : 4, KS = 4 * PE, BM = 32 * RT, TP = BM + 8;     // elements of a piece; indices of a step
+    typedef typename WaveOperand<BF>::piece piece;
+    typedef typename WaveOperand<BF>::elem elem;
+    constexpr int PART = WF_WAVES * 32 * WF_PITCH * 4, OPERAND = WF_WAVES * BM * 64;
+    __shared__ __attribute__((aligned(16))) unsigned char smem[PART > OPERAND ? PART : OPERAND];
+    __shared__ __attribute__((aligned(16))) uint16_t turn[BF ? WF_COLS : 1][TP];       // the block's activations, transposed
+    const int t = threadIdx.x, lane = t & 63, row = lane & 31, half = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    piece *own = reinterpret_cast<piece *>(smem) + wave * (BM * 4);
+    const unsigned nblk = (unsigned)((p.dout + WF_COLS - 1) / WF_COLS), mblk = (unsigned)((p.B + BM - 1) / BM);
+    int g;
+    unsigned local;
+    if (!decode_group(tile_block(), nblk * mblk, p.M, g, local)) return;
+    const int n0 = (int)(local % nblk) * WF_COLS, m0 = (int)(local / nblk) * BM, K = p.din;
+    const float bias = tile_fwd_bias(p, g, n0 + (t & 31));            // for the end; requested first
+    const int total = K / KS, n_mine = wave < total ? (total - wave + WF_WAVES - 1) / WF_WAVES : 0, s_last = wave + WF_WAVES * (n_mine - 1);
+    const uint32_t skip = (uint32_t)(p.M - 1) << (TILE_SHIFT + 2), dout4 = (uint32_t)p.dout * 4u;
+    const int col = min(n0 + row, p.dout - 1);                        // columns past the end repeat the last one
+    const uint32_t w_first = (uint32_t)col * 4u + (uint32_t)(PE * half) * dout4;
+    // index of a lane's element e of a step: pieces `half` and `half` + 2
+    auto index = [&](int e) { return e < PE ? PE * half + e : PE * half + PE + e; };
+    float w[WF_DEPTH][2 * PE];
+    piece a[WF_DEPTH][RT][2];
+    auto request_w = [&](int d, int s) {
+        const int64_t j0 = p.woff + (int64_t)s * KS * p.dout;
+        const float *base = p.X + (((size_t)(j0 >> TILE_SHIFT) * p.M + g) << TILE_SHIFT);
+        const uint32_t from = w_first + (uint32_t)(j0 & (TILE - 1)) * 4u;
+#pragma unroll
+        for (int e = 0; e < 2 * PE; ++e) {
+            const uint32_t q = from + (uint32_t)(e < PE ? e : PE + e) * dout4;
+            w[d][e] = *(const float *)((const char *)base + (__umul24(q >> (TILE_SHIFT + 2), skip) + q));
+        }
+    };
+    auto clamped = [&](int s) { return s < s_last ? s : s_last; };    // past the last step: that one again, never used
+    if (n_mine > 0) {                                                 // these do not wait for the batch-row numbers
+#pragma unroll
+        for (int d = 0; d < WF_DEPTH; ++d) request_w(d, clamped(wave + WF_WAVES * d));
+    }
+    // pieces that this lane brings into LDS: lane % 4 of rows lane / 4 and lane / 4 + 16 of every tile
+    const int pa = lane & 3, pr = lane >> 2;
+    const elem *a_row[RT][2];
+#pragma unroll
+    for (int i = 0; i < RT; ++i)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int r = min(m0 + 32 * i + 16 * h + pr, p.B - 1);    // rows past the batch repeat the last one
+            a_row[i][h] = (const elem *)(p.feats ? p.feats : p.act) + (p.feats ? p.row0[g] + p.idx[(size_t)g * p.B + r] : (int64_t)g * p.B + r) * K;
+        }
+    auto request_a = [&](int d, int s) {
+#pragma unroll
+        for (int i = 0; i < RT; ++i)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) a[d][i][h] = *reinterpret_cast<const typename WaveOperand<BF>::any *>(a_row[i][h] + (s * KS + PE * pa));
+    };
+    tile_f32x16 acc[RT];
+#pragma unroll
+    for (int i = 0; i < RT; ++i)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[i][v] = 0.0f;
+    auto multiply = [&](const piece (&from)[RT][2], const float (&ws)[2 * PE]) {
+#pragma unroll
+        for (int i = 0; i < RT; ++i)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) own[32 * 4 * i + wave_unit(16 * h + pr, pa)] = from[i][h];
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            piece x[RT];
+#pragma unroll
+            for (int i = 0; i < RT; ++i) x[i] = own[32 * 4 * i + wave_unit(row, 2 * j + half)];
+            wave_multiply(x, ws + j * PE, acc);
+        }
+        __builtin_amdgcn_wave_barrier();
+    };
+    if (n_mine > 0) {
+#pragma unroll
+        for (int d = 0; d < WF_DEPTH; ++d) request_a(d, clamped(wave + WF_WAVES * d));
+    }
+    if (TAIL && wave == total % WF_WAVES) {                           // the wave whose turn it would be; what does not exist counts as zero
+        const int from = total * KS, left = K - from;
+        float wt[2 * PE];
+        piece at[RT][2];
+#pragma unroll
+        for (int e = 0; e < 2 * PE; ++e) wt[e] = p.X[tiled_offset_quick(p.M, g, p.woff + (int64_t)min(from + index(e), K - 1) * p.dout + col)];
+#pragma unroll
+        for (int i = 0; i < RT; ++i)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                elem x[PE];
+#pragma unroll
+                for (int e = 0; e < PE; ++e) x[e] = a_row[i][h][min(from + PE * pa + e, K - 1)];
+                if constexpr (BF) {
+#pragma unroll
+                    for (int e = 0; e < PE; e += 2)
+                        at[i][h][e / 2] = (PE * pa + e < left ? (uint32_t)x[e] : 0u) | (PE * pa + e + 1 < left ? (uint32_t)x[e + 1] << 16 : 0u);
+                } else {
+#pragma unroll
+                    for (int e = 0; e < PE; ++e) at[i][h][e] = PE * pa + e < left ? x[e] : 0.0f;
+                }
+            }
+#pragma unroll
+        for (int e = 0; e < 2 * PE; ++e) wt[e] = index(e) < left ? wt[e] : 0.0f;
+        multiply(at, wt);
+    }
+    if (n_mine > 0) {
+        int done = 0;
+        for (; done + WF_DEPTH <= n_mine; done += WF_DEPTH) {
+#pragma unroll
+            for (int d = 0; d < WF_DEPTH; ++d) {
+                multiply(a[d], w[d]);
+                const int s = clamped(wave + WF_WAVES * (done + d + WF_DEPTH));
+                request_a(d, s);
+                request_w(d, s);
+            }
+        }
+#pragma unroll
+        for (int d = 0; d < WF_DEPTH - 1; ++d)
+            if (done + d < n_mine) multiply(a[d], w[d]);
+    }
+    __syncthreads();                                                  // the operands' space becomes the parts
+    float (*part)[32][WF_PITCH] = reinterpret_cast<float (*)[32][WF_PITCH]>(smem);
+    const int c = t & 31;
+#pragma unroll
+    for (int i = 0; i < RT; ++i) {
+        if (i > 0) __syncthreads();                                   // the tile before has been read
+#pragma unroll
+        for (int v = 0; v < 16; ++v) part[wave][tile_row(lane, v)][row] = acc[i][v];
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < 16 / WF_WAVES; ++u) {
+            const int r = (t >> 5) + 2 * WF_WAVES * u, b = m0 + 32 * i + r;
+            float z = part[0][r][c];
+#pragma unroll
+            for (int k = 1; k < WF_WAVES; ++k) z += part[k][r][c];
+            z += bias;
+            if (p.relu) z = z > 0.0f ? z : 0.0f;
+            const size_t at = ((size_t)g * p.B + b) * p.dout + n0 + c;
+            const bool real = b < p.B && n0 + c < p.dout;
+            if (real && p.out) p.out[at] = z;
+            if constexpr (BF) {
+                const uint16_t h = (uint16_t)bf16_bits(z);
+                if (real && p.out_bf16) p.out_bf16[at] = h;
+                turn[c][32 * i + r] = h;
+            }
+        }
+    }
+    if constexpr (BF) {
+        if (!p.out_bf16_t) return;
+        __syncthreads();
+        const int rows = min(BM, p.B - m0), cols = min(WF_COLS, p.dout - n0);
+        uint16_t *to = p.out_bf16_t + ((size_t)g * p.dout + n0) * p.B + m0;
+        for (int e = t; e < cols * (BM / 8); e += WF_THREADS) {      // who asks for it has a batch of whole 32 rows
+            const int c8 = e % (BM / 8) * 8, k = e / (BM / 8);
+            if (c8 < rows) *reinterpret_cast<tile_u32x4 *>(to + (size_t)k * p.B + c8) = *reinterpret_cast<const tile_u32x4 *>(&turn[k][c8]);
+        }
+    }
+}
+
 // fp32 operands on the bfloat16 matrix instructions: 128 x 64 blocks, steps of 32, three planes of each operand in LDS, twice:
 // the next step is split while this one is multiplied.
 constexpr int SF_BM = 128, SF_BN = 64, SF_BK = 32, SF_WM = 2, SF_WN = 2, SF_THREADS = 256;
@@ -338,8 +532,54 @@ static void launch_shape(hipStream_t s, const TileFwd &a)
 //                          (640) 107 and 106, 48 x 784-515, batch 50 (864) 151 and 145
 // Larger forms, bfloat16, batch > 64: 128 x 32 blocks while the 128 x 64 ones do not fill the chip: 31 x 784-500, batch 100 (248 of
 // the latter) 97 and 102, 64 x 1000-300 (320) 145 and 143, 31 x 3001-999 (496) 755 and 710.
-template <bool BF, bool VA, bool VW> static void launch_rows(hipStream_t s, const TileFwd &a)
+template <bool BF, int RT> static void launch_wave(hipStream_t s, const TileFwd &a)
 {
+    const unsigned n = (unsigned)((a.dout + WF_COLS - 1) / WF_COLS) * (unsigned)((a.B + 32 * RT - 1) / (32 * RT));
+    const dim3 grid = tile_grid(grouped_grid(a.M, n)), block(WF_THREADS);
+    if (a.din % (BF ? 32 : 16) == 0) hipLaunchKernelGGL((wave_fwd_kernel<BF, RT, false>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((wave_fwd_kernel<BF, RT, true>), grid, block, 0, s, a);
+}
+// Tiles of 32 batch rows in a workgroup: rounds of workgroups over the compute units times what one takes, in proportion to the tiles and a part that does
+// not depend on them (of a tile's time fp32 0.3, bfloat16 1).  us, one, two and four tiles: bfloat16 16 x 784 -> 500, batch 100 17.5, 15.6, 13.2, 48 x 3072
+// -> 256, batch 128 61, 53, 56, 64 x 3072 -> 256 101, 84, 70; fp32 12 x 3072 -> 1024, batch 60 62, 72, 16 x 87, 73, batch 128 12 x 126, 109.
+// fp32 never gains by four: 47 x 1330 -> 184, batch 128, 48, 52, 66.
+template <bool BF> static void launch_wave(hipStream_t s, const TileFwd &a)
+{
+    const int64_t cols = (int64_t)a.M * ((a.dout + WF_COLS - 1) / WF_COLS);
+    auto cost = [&](int rt) { return (cols * ((a.B + 32 * rt - 1) / (32 * rt)) + MF_XCD * XCD_CUS - 1) / (MF_XCD * XCD_CUS) * (10 * rt + (BF ? 10 : 3)); };
+    int rt = 1;
+    for (int k = 2; k <= (BF ? 4 : 2); k *= 2)
+        if (a.B > 16 * k && cost(k) < cost(rt)) rt = k;
+    if (rt == 1) launch_wave<BF, 1>(s, a);
+    else if (rt == 2) launch_wave<BF, 2>(s, a);
+    else if constexpr (BF) launch_wave<BF, 4>(s, a);
+}
+
+// Whether wave_fwd_kernel takes a layer: few blocks of 32 columns (of all workers) and many contraction indices.  us, it and the other kernel, either
+// side of each line:
+//   bfloat16, batch <= 32    60 x 784 -> 516 (1020 blocks) 21.2 and 26.4, 90 x (1530) 30.3 and 31.0; aligned layers 32 x 1024 -> 1024 (1024) 25.6 and 29.7,
+//                            48 x (1536) 36.6 and 33.5
+//   bfloat16, batch <= 64    30 x 784 -> 516 (510) 18.6 and 21.2, 45 x (765) 26 and 22; aligned 16 x 1024 -> 1024 (512) 19.6 and 29.0, 32 x (1024) 36 and 31
+//   bfloat16, more           15 x 784 -> 516, batch 128 (255) 14.9 and 19.4, 23 x (391) 26 and 21.4; aligned 16 x 1024 -> 1024, batch 128 (512) 27 and 30, 24 x
+//                            (768) 40 and 32; 16 x 256 -> 512 (256) 8.0 and 11.2, 32 x (512) 13.4 and 13.4
+//   fp32, batch <= 32        always: 120 x 784 -> 516 49 and 64, 64 x 3072 -> 1024 204 and 223
+//   fp32, batch <= 64        120 x 784 -> 516, batch 60 (2040) 85 and 102; 64 x 3072 -> 1024 (2048) 313 and 306
+//   fp32, more               16 x 3072 -> 1024, batch 128 (512) 148 and 207, 24 x (768) 218 and 212
+// Fewer indices: shared_fwd_kernel, whose workgroups are smaller (23 x 252 -> 516, batch 128, bfloat16 13.4 and 18; fp32 20.2 and 22.5).  Aligned layers have
+// no such form: 8 x 256 -> 1024, batch 32, 4.8 us and 10.0 by fwd_mfma_kernel.
+// 32-bit offsets inside a step's rows of W.
+static bool wave_fwd_pays(int M, int B, int64_t din, int64_t dout, bool bf, bool aligned)
+{
+    const int64_t blocks = M * ((dout + WF_COLS - 1) / WF_COLS), step = (32 * dout + TILE) / TILE + 1;
+    if ((!aligned && din < 640) || M > 2048 || step * M * (TILE * 4) >= (int64_t)1 << 32) return false;
+    if (bf) return blocks <= (B <= 32 ? 1024 : B <= 64 || (aligned && din >= 512) ? 512 : 320);
+    return B <= 32 || blocks <= (B <= 64 ? 2048 : 512);
+}
+bool wave_fwd_pays(const MlpPlan &p, int l) { return wave_fwd_pays(p.M, p.B, p.dims[l], p.dims[l + 1], p.bf16 != 0, mfma_layer_ok(p, l)); }
+
+template <bool BF, bool VA, bool VW> static void launch_rows(hipStream_t s, const TileFwd &a, bool wave)
+{
+    if (wave) return launch_wave<BF>(s, a);
     const int64_t cols = (int64_t)a.M * ((a.dout + 63) / 64), blocks = cols * ((a.B + 31) / 32), wide = cols * ((a.B + 127) / 128);
     const int64_t enough = BF ? 512 : a.B > 32 && a.B <= 64 ? 641 : 1025;
     if constexpr (VA)
@@ -371,12 +611,13 @@ void launch_tile_fwd(hipStream_t s, const MlpPlan &p, int l, const float *X, boo
     // pieces of A: any four neighbours; pieces of W: four columns of a row that starts at a multiple of four
     const bool va = a.din >= 4;
     const bool vw = a.dout % 4 == 0 && a.woff % 4 == 0;
+    const bool wave = wave_fwd_pays(p, l);
     if (bf) {
-        if (va) { if (vw) launch_rows<true, true, true>(s, a); else launch_rows<true, true, false>(s, a); }
-        else { if (vw) launch_rows<true, false, true>(s, a); else launch_rows<true, false, false>(s, a); }
+        if (va) { if (vw) launch_rows<true, true, true>(s, a, wave); else launch_rows<true, true, false>(s, a, wave); }
+        else { if (vw) launch_rows<true, false, true>(s, a, wave); else launch_rows<true, false, false>(s, a, wave); }
     } else {
-        if (va) { if (vw) launch_rows<false, true, true>(s, a); else launch_rows<false, true, false>(s, a); }
-        else { if (vw) launch_rows<false, false, true>(s, a); else launch_rows<false, false, false>(s, a); }
+        if (va) { if (vw) launch_rows<false, true, true>(s, a, wave); else launch_rows<false, true, false>(s, a, wave); }
+        else { if (vw) launch_rows<false, false, true>(s, a, wave); else launch_rows<false, false, false>(s, a, wave); }
     }
 }
 

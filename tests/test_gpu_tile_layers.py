@@ -46,6 +46,21 @@ def test_gradient_of_odd_layers(ora, dtype, M, batch, dims):
     gpu.close()
 
 
+@pytest.mark.parametrize("dtype,M,batch,dims", [
+    # contractions that eight waves share: whole steps of sixteen (bfloat16 32) indices, one more, one fewer, a wave without a step of its own
+    ("f32", 2, 31, (640, 33, 10)), ("f32", 3, 33, (641, 65, 10)), ("f32", 2, 100, (655, 31, 10)), ("f32", 9, 129, (650, 68, 10)), ("f32", 2, 20, (1000, 40)),
+    ("bf16", 2, 31, (640, 33, 10)), ("bf16", 3, 33, (641, 65, 10)), ("bf16", 2, 100, (671, 31, 10)), ("bf16", 9, 129, (650, 68, 10)), ("bf16", 2, 20, (1000, 40)),
+    # aligned layers (both orientations of the activations): fewer steps than waves, one, two and four row tiles, a general layer under them
+    ("bf16", 3, 32, (128, 128, 10)), ("bf16", 2, 64, (256, 384, 128, 10)), ("bf16", 17, 96, (1280, 256, 10)), ("bf16", 2, 128, (700, 128, 128, 10)),
+    # the most blocks that it takes, and one worker more
+    ("f32", 32, 65, (640, 500, 10)), ("f32", 33, 65, (640, 500, 10)), ("f32", 64, 33, (644, 1024, 10)), ("f32", 65, 33, (644, 1024, 10)),
+    ("bf16", 32, 20, (640, 1024, 10)), ("bf16", 33, 20, (640, 1024, 10)), ("bf16", 10, 65, (640, 1020, 10)), ("bf16", 11, 65, (640, 1020, 10)),
+    ("bf16", 16, 64, (512, 1024, 10)), ("bf16", 17, 64, (512, 1024, 10)), ("bf16", 10, 128, (384, 1024, 10)), ("bf16", 11, 128, (384, 1024, 10)),
+])
+def test_gradient_of_long_contractions(ora, dtype, M, batch, dims):
+    test_gradient_of_odd_layers(ora, dtype, M, batch, dims)
+
+
 def test_wide_fp32_layers_keep_what_is_not_finite():
     """Large fp32 layers multiply bfloat16 planes of their operands, which an infinity, or a number that rounds to one, does not
     survive: such blocks are computed again in fp32.  Activations against float64, block edges included."""
