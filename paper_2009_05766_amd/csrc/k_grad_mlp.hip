@@ -239,8 +239,7 @@ bool launch_mlp_grad(hipStream_t s, const MlpPlan &p, const float *X, float *G, 
     for (int l = 0; l < L; ++l) {
         const bool last = (l + 1 == L);
         if (fast[l] && !last) {
-            if (wave_fwd_pays(p, l)) launch_tile_fwd(s, p, l, X, true);
-            else launch_fwd_mfma(s, p, l, X);
+            launch_fwd_mfma(s, p, l, X);
             continue;
         }
         if (last && small_last) {

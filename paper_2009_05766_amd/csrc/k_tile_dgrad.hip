@@ -125,6 +125,148 @@ __global__ void __launch_bounds__(64 * WM * WN) tile_dgrad_kernel(TileDgrad p)
     }
 }
 
+// fp32 operands, few blocks: 32 columns (input features) and RT x 32 batch rows, eight waves that share the contraction.  Wave w takes the steps w, w + 8, ... of
+// sixteen indices; rows of dZ and of W come in as 16-byte pieces, four lanes along a row, two steps ahead, and go through the wave's own LDS
+// into the layout of the matrix instruction; the parts are added in the order of the waves.  V: pieces of W do not cross a layout tile.
+// TAIL: indices behind the last whole step.
+// Bound by one or two chains of loads where the other kernel waits for one at every step: 4 x 1000-1000, batch 20, 9.3 us (tile_dgrad_kernel 27), 13 x
+// 301-1001, batch 60, 18 us (43).
+constexpr int WD_DEPTH = 2, WF_WAVES = 8, WF_THREADS = 64 * WF_WAVES;
+template <int RT, bool V, bool TAIL>
+__global__ void __launch_bounds__(WF_THREADS) wave_dgrad_kernel(TileDgrad p)
+{
+    constexpr int KS = 16, BM = 32 * RT;
+    constexpr int PART = WF_WAVES * 32 * WF_PITCH * 4, OPERAND = WF_WAVES * (BM + 32) * 64;
+    __shared__ __attribute__((aligned(16))) unsigned char smem[PART > OPERAND ? PART : OPERAND];
+    __shared__ float red[2 * WF_WAVES][WF_COLS];
+    const int t = threadIdx.x, lane = t & 63, row = lane & 31, half = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    f32x4 *own = reinterpret_cast<f32x4 *>(smem) + wave * ((BM + 32) * 4);            // rows of dZ, then of W
+    const unsigned nblk = (unsigned)((p.din + WF_COLS - 1) / WF_COLS), mblk = (unsigned)((p.B + BM - 1) / BM);
+    int g;
+    unsigned local;
+    if (!decode_group(tile_block(), nblk * mblk, p.M, g, local)) return;
+    const int n0 = (int)(local % nblk) * WF_COLS, m0 = (int)(local / nblk) * BM, K = p.dout;
+    const int total = K / KS, n_mine = wave < total ? (total - wave + WF_WAVES - 1) / WF_WAVES : 0, s_last = wave + WF_WAVES * (n_mine - 1);
+    // pieces that this lane brings into LDS: `pa` of rows pr and pr + 16 of every tile; rows and features past the end repeat the last one
+    const int pa = lane & 3, pr = lane >> 2;
+    int64_t z_row[RT][2], w_row[2];
+#pragma unroll
+    for (int i = 0; i < RT; ++i)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) z_row[i][h] = ((int64_t)g * p.B + min(m0 + 32 * i + 16 * h + pr, p.B - 1)) * K;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) w_row[h] = p.woff + (int64_t)min(n0 + 16 * h + pr, p.din - 1) * K;
+    auto w4 = [&](int64_t j) { return load4_params<V>(p.X, p.M, g, j); };
+    f32x4 z[WD_DEPTH][RT][2], w[WD_DEPTH][2];
+    auto request = [&](int d, int s) {
+        const int k = s * KS + 4 * pa;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) w[d][h] = w4(w_row[h] + k);
+#pragma unroll
+        for (int i = 0; i < RT; ++i)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) z[d][i][h] = *reinterpret_cast<const tile_f32x4_any *>(p.dz + z_row[i][h] + k);
+    };
+    auto clamped = [&](int s) { return s < s_last ? s : s_last; };    // past the last step: that one again, never used
+    if (n_mine > 0) {
+#pragma unroll
+        for (int d = 0; d < WD_DEPTH; ++d) request(d, clamped(wave + WF_WAVES * d));
+    }
+    // the input: this thread's rows t / 32 and 16 more of every tile, column t % 32
+    const int c = t & 31, col = min(n0 + c, p.din - 1);
+    float on[RT][2];
+#pragma unroll
+    for (int i = 0; i < RT; ++i)
+#pragma unroll
+        for (int u = 0; u < 2; ++u) on[i][u] = p.act[((size_t)g * p.B + min(m0 + 32 * i + (t >> 5) + 16 * u, p.B - 1)) * p.din + col];
+    tile_f32x16 acc[RT];
+#pragma unroll
+    for (int i = 0; i < RT; ++i)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[i][v] = 0.0f;
+    auto multiply = [&](const f32x4 (&zs)[RT][2], const f32x4 (&ws)[2]) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+#pragma unroll
+            for (int i = 0; i < RT; ++i) own[32 * 4 * i + wave_unit(16 * h + pr, pa)] = zs[i][h];
+            own[BM * 4 + wave_unit(16 * h + pr, pa)] = ws[h];
+        }
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int at = wave_unit(row, 2 * j + half);
+            const f32x4 b = own[BM * 4 + at];
+            f32x4 a[RT];
+#pragma unroll
+            for (int i = 0; i < RT; ++i) a[i] = own[32 * 4 * i + at];
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int i = 0; i < RT; ++i) acc[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i][e], b[e], acc[i], 0, 0, 0);
+        }
+        __builtin_amdgcn_wave_barrier();
+    };
+    if (TAIL && wave == total % WF_WAVES) {                           // the wave whose turn it would be; what does not exist counts as zero
+        const int k = total * KS + 4 * pa, left = K - k;
+        f32x4 zt[RT][2], wt[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float x = p.X[tiled_offset_quick(p.M, g, w_row[h] + min(k + e, K - 1))];
+                wt[h][e] = e < left ? x : 0.0f;
+#pragma unroll
+                for (int i = 0; i < RT; ++i) {
+                    const float y = p.dz[z_row[i][h] + min(k + e, K - 1)];
+                    zt[i][h][e] = e < left ? y : 0.0f;
+                }
+            }
+        multiply(zt, wt);
+    }
+    if (n_mine > 0) {
+        int done = 0;
+        for (; done + WD_DEPTH <= n_mine; done += WD_DEPTH) {
+#pragma unroll
+            for (int d = 0; d < WD_DEPTH; ++d) {
+                multiply(z[d], w[d]);
+                request(d, clamped(wave + WF_WAVES * (done + d + WD_DEPTH)));
+            }
+        }
+#pragma unroll
+        for (int d = 0; d < WD_DEPTH - 1; ++d)
+            if (done + d < n_mine) multiply(z[d], w[d]);
+    }
+    __syncthreads();                                                  // the operands' space becomes the parts
+    float (*part)[32][WF_PITCH] = reinterpret_cast<float (*)[32][WF_PITCH]>(smem);
+    float csum = 0.0f;
+#pragma unroll
+    for (int i = 0; i < RT; ++i) {
+        if (i > 0) __syncthreads();                                   // the tile before has been read
+#pragma unroll
+        for (int v = 0; v < 16; ++v) part[wave][tile_row(lane, v)][row] = acc[i][v];
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int r = (t >> 5) + 16 * u, b = m0 + 32 * i + r;
+            float d = part[0][r][c];
+#pragma unroll
+            for (int k = 1; k < WF_WAVES; ++k) d += part[k][r][c];
+            d = on[i][u] > 0.0f && b < p.B ? d : 0.0f;
+            csum += d;
+            if (b < p.B && n0 + c < p.din) p.out[((size_t)g * p.B + b) * p.din + n0 + c] = d;
+        }
+    }
+    red[t >> 5][c] = csum;
+    __syncthreads();
+    if (mblk == 1 && t < WF_COLS && n0 + t < p.din) {
+        float s = red[0][t];
+#pragma unroll
+        for (int k = 1; k < 2 * WF_WAVES; ++k) s += red[k][t];
+        p.G[tiled_offset_quick(p.M, g, p.boff + n0 + t)] = s;
+    }
+}
+
 template <bool BF, bool V, int BM, int BN, int BK, int WM, int WN>
 static bool launch_shape(hipStream_t s, const TileDgrad &a)
 {
@@ -148,6 +290,35 @@ template <bool BF, bool V> static bool launch_rows(hipStream_t s, const TileDgra
     return launch_shape<BF, V, 128, 64, 64, 2, 2>(s, a);
 }
 
+template <int RT> static bool launch_wave(hipStream_t s, const TileDgrad &a)
+{
+    const unsigned mblk = (unsigned)((a.B + 32 * RT - 1) / (32 * RT)), blocks = (unsigned)((a.din + WF_COLS - 1) / WF_COLS) * mblk;
+    const dim3 grid = tile_grid(grouped_grid(a.M, blocks)), block(WF_THREADS);
+    const bool v = a.dout % 4 == 0 && a.woff % 4 == 0, tail = a.dout % 16 != 0;
+    if (v && tail) hipLaunchKernelGGL((wave_dgrad_kernel<RT, true, true>), grid, block, 0, s, a);
+    else if (v) hipLaunchKernelGGL((wave_dgrad_kernel<RT, true, false>), grid, block, 0, s, a);
+    else if (tail) hipLaunchKernelGGL((wave_dgrad_kernel<RT, false, true>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((wave_dgrad_kernel<RT, false, false>), grid, block, 0, s, a);
+    return mblk == 1;
+}
+
+// Whether wave_dgrad_kernel takes a layer: few blocks of 32 columns (of all workers, times the batch's parts of 128 rows).  us, it and the other kernel,
+// either side of each line:
+//   batch <= 32    48 x 1000-300 (1536 blocks) 21.6 and 24.6, 64 x (2048) 27.2 and 27.1
+//   batch <= 64    8 x 1000-300 (256) 8.8 and 11.7, 12 x (384) 12.9 and 12.0; many outputs 16 x 1000-1000 (512) 28.1 and 29.3, 32 x (1024) 56 and 52
+//   more           many outputs 8 x 1000-1000 (256) 29.6 and 31.1, 12 x (384) 53 and 52
+// Rows of W that start anywhere cost the other kernel a load a float:
+//   batch <= 64    102 x 301-1001 (1020) 76 and 81, 51 x 301-102 (510) 11.2 and 10.4
+//   more           128 x 102-602 (512) 43 and 51, 128 x 102-301 30.2 and 29.4, 64 x 102-301 (256) 16 and 23
+static bool wave_dgrad_pays(const TileDgrad &a)
+{
+    const int64_t K = a.dout, blocks = (int64_t)a.M * ((a.din + WF_COLS - 1) / WF_COLS) * ((a.B + 127) / 128);
+    const bool any = K % 4 != 0 || a.woff % 4 != 0, deep = K >= (any ? 256 : 640);
+    if (a.B <= 32) return blocks <= 1536;
+    if (a.B <= 64) return blocks <= (!deep ? 256 : any ? 1024 : 512);
+    return any ? blocks <= (K >= 480 ? 512 : 256) : deep && blocks <= 256;
+}
+
 bool launch_tile_dgrad(hipStream_t s, const MlpPlan &p, int l, const float *X, float *G, int cur, bool below_fast)
 {
     const bool bf = p.bf16 != 0;
@@ -158,6 +329,10 @@ bool launch_tile_dgrad(hipStream_t s, const MlpPlan &p, int l, const float *X, f
     a.out_bf16 = (bf && below_fast) ? p.dzb[cur ^ 1] : nullptr;
     a.out_bf16_t = (bf && below_fast) ? p.dzt[cur ^ 1] : nullptr;
     a.G = G; a.boff = p.woff[l - 1] + p.dims[l - 1] * p.dims[l];
+    if (!bf && wave_dgrad_pays(a)) {
+        if (a.B <= 32) return launch_wave<1>(s, a);
+        return a.B <= 64 ? launch_wave<2>(s, a) : launch_wave<4>(s, a);
+    }
     const bool v = a.dout % 4 == 0 && a.woff % 4 == 0;               // pieces of rows of dZ and W: aligned, none past the end of a row
     if (bf) return v ? launch_rows<true, true>(s, a) : launch_rows<true, false>(s, a);
     return v ? launch_rows<false, true>(s, a) : launch_rows<false, false>(s, a);

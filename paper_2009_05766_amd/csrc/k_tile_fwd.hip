@@ -63,14 +63,13 @@ __device__ __forceinline__ void tile_fwd_store(const TileFwd &p, int g, int m0, 
     }
 }
 
-// The product of one block, operands as they are (BF: rounded to bfloat16).  smem: LDS for both.  VA: rows of A have four elements or
-// more; VW: rows of W start at multiples of four and four columns at a time are one load, otherwise a thread's loads are single
-// floats, neighbouring lanes neighbouring columns.  WK waves share the contraction indices of every step; the parts are the
-// caller's to add.
-template <bool BF, bool VA, bool VW, int BM, int BN, int BK, int WM, int WN, int WK, int RI, int CJ>
+// The product of one block, operands as they are (BF: rounded to bfloat16).  smem: LDS for both.  Rows of A have four elements or
+// more.  VW: rows of W start at multiples of four and four columns at a time are one load, otherwise a thread's loads are single
+// floats, neighbouring lanes neighbouring columns.
+template <bool BF, bool VW, int BM, int BN, int BK, int WM, int WN, int RI, int CJ>
 __device__ __forceinline__ void tile_fwd_product(const TileFwd &p, int g, int m0, int n0, unsigned char *smem, tile_f32x16 (&acc)[RI][CJ])
 {
-    constexpr int NT = 64 * WM * WN * WK, K4 = BK / 4;
+    constexpr int NT = 64 * WM * WN, K4 = BK / 4;
     constexpr int NA = BM * K4 / NT, NB = BN * K4 / 4 / NT;           // pieces of A, 4 x 4 blocks of W per thread and step
     static_assert(NA * NT == BM * K4 && NB * NT == BN * K4 / 4, "every thread has the same share");
     static_assert(BK <= 128 && NT % BN == 0, "offsets inside a step; a column per thread");
@@ -78,8 +77,7 @@ __device__ __forceinline__ void tile_fwd_product(const TileFwd &p, int g, int m0
     typedef typename L::elem elem;
     elem (*As)[L::PITCH] = reinterpret_cast<elem (*)[L::PITCH]>(smem);
     elem (*Bs)[L::PITCH] = reinterpret_cast<elem (*)[L::PITCH]>(smem + BM * L::PITCH * sizeof(elem));
-    const int t = threadIdx.x, lane = t & 63, wave = t >> 6, wm = wave / WK / WN, wn = wave / WK % WN;
-    const int ka = __builtin_amdgcn_readfirstlane(wave % WK * (BK / WK));             // this wave's indices of a step
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6, wm = wave / WN, wn = wave % WN;
     const int K = p.din;
 
     int64_t a_row[NA];                                                // element index of a piece at step 0 (row clamped)
@@ -108,9 +106,9 @@ __device__ __forceinline__ void tile_fwd_product(const TileFwd &p, int g, int m0
     auto fetch = [&](int k0) {
 #pragma unroll
         for (int u = 0; u < NA; ++u) {
-            const int k = min(k0 + a_k[u], VA ? K - 4 : K - 1);
-            if constexpr (BF) ra[u] = load_piece<VA>((const uint16_t *)(p.feats ? p.feats : p.act) + a_row[u] + k, K - k);
-            else ra[u] = load_piece<VA>((const float *)(p.feats ? p.feats : p.act) + a_row[u] + k, K - k);
+            const int k = min(k0 + a_k[u], K - 4);
+            if constexpr (BF) ra[u] = load_piece<true>((const uint16_t *)(p.feats ? p.feats : p.act) + a_row[u] + k, K - k);
+            else ra[u] = load_piece<true>((const float *)(p.feats ? p.feats : p.act) + a_row[u] + k, K - k);
         }
         if constexpr (VW) {
 #pragma unroll
@@ -137,10 +135,7 @@ __device__ __forceinline__ void tile_fwd_product(const TileFwd &p, int g, int m0
         // indices that exist from k on: 4 or more everywhere but in the last step
         const int left = K - k0;
 #pragma unroll
-        for (int u = 0; u < NA; ++u) {
-            if constexpr (VA) put_piece(&As[a_m[u]][a_k[u]], piece_tail(ra[u], left - a_k[u]).v, 4);
-            else put_piece(&As[a_m[u]][a_k[u]], ra[u].v, left - a_k[u]);
-        }
+        for (int u = 0; u < NA; ++u) put_piece(&As[a_m[u]][a_k[u]], piece_tail(ra[u], left - a_k[u]).v, 4);
 #pragma unroll
         for (int u = 0; u < NB; ++u)
 #pragma unroll
@@ -157,7 +152,7 @@ __device__ __forceinline__ void tile_fwd_product(const TileFwd &p, int g, int m0
         stash(k0);
         __syncthreads();
         if (k0 + BK < K) fetch(k0 + BK);                              // travels while this step is multiplied
-        if (WK == 1 || k0 + ka < K) tile_multiply<BK / WK>(As, Bs, wm * (BM / WM), wn * (BN / WN), lane, acc, BK / WK, ka);
+        tile_multiply<BK>(As, Bs, wm * (BM / WM), wn * (BN / WN), lane, acc);
     }
 }
 
@@ -178,82 +173,27 @@ __global__ void __launch_bounds__(64 * WM * WN) tile_fwd_kernel(TileFwd p)
     if (!decode_group(tile_block(), nblk * mblk, p.M, g, local)) return;
     const int n0 = (int)(local % nblk) * BN, m0 = (int)(local / nblk) * BM;
     tile_f32x16 acc[RI][CJ];
-    tile_fwd_product<BF, true, VW, BM, BN, BK, WM, WN, 1>(p, g, m0, n0, smem, acc);
+    tile_fwd_product<BF, VW, BM, BN, BK, WM, WN>(p, g, m0, n0, smem, acc);
     tile_fwd_store<BF, BM, BN, WM, WN>(p, g, m0, n0, wm, wn, lane, acc);
 }
 
-// 32 x 32 blocks, four waves that share every step's contraction indices; their parts are added through LDS in the order of the
-// waves.
-constexpr int SH_BK = 128, SH_WAVES = 4, SH_PITCH = 33;
-template <bool BF, bool VA, bool VW>
-__global__ void __launch_bounds__(64 * SH_WAVES) shared_fwd_kernel(TileFwd p)
-{
-    constexpr int LDS = tile_fwd_lds<BF, 32, 32, SH_BK>(), PARTS = SH_WAVES * 32 * SH_PITCH * (int)sizeof(float);
-    __shared__ __attribute__((aligned(16))) unsigned char smem[LDS > PARTS ? LDS : PARTS];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const unsigned nblk = (unsigned)((p.dout + 31) / 32), mblk = (unsigned)((p.B + 31) / 32);
-    int g;
-    unsigned local;
-    if (!decode_group(tile_block(), nblk * mblk, p.M, g, local)) return;
-    const int n0 = (int)(local % nblk) * 32, m0 = (int)(local / nblk) * 32, col = lane & 31;
-    const float bias = tile_fwd_bias(p, g, n0 + col);
-    tile_f32x16 acc[1][1];
-    tile_fwd_product<BF, VA, VW, 32, 32, SH_BK, 1, 1, SH_WAVES>(p, g, m0, n0, smem, acc);
-    __syncthreads();                                                  // the operands' space becomes the parts
-    float (*part)[32][SH_PITCH] = reinterpret_cast<float (*)[32][SH_PITCH]>(smem);
-#pragma unroll
-    for (int v = 0; v < 16; ++v) part[wave][tile_row(lane, v)][col] = acc[0][0][v];
-    __syncthreads();
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        const int row = tile_row(lane, 4 * wave + e);
-        float z = part[0][row][col];
-#pragma unroll
-        for (int w = 1; w < SH_WAVES; ++w) z += part[w][row][col];
-        tile_fwd_put<BF>(p, g, m0 + row, n0 + col, z + bias);
-    }
-}
-
-// Long contractions in few blocks: 32 columns and RT x 32 batch rows, eight waves that share the contraction.  Wave w takes the steps w, w + 8, ...
-// of 64 bytes of every row of A (sixteen indices, bfloat16 32), asked for two steps ahead.  A crosses LDS by way of the wave's own buffer, so
-// that four lanes read 64 neighbouring bytes of a row; a lane per row, in the layout of the matrix instruction, takes 64 turns of the cache a load
-// instead of 16 (7 x 3072 -> 1024, batch 128, fp32 94 us, 71 with it).  A lane's operands of W are neighbouring rows of its column, each a load
-// of a float (32 lanes 128 bytes of a row).  No barrier until the waves' parts are added, in the order of the waves.  TAIL: indices behind
-// the last whole step.
-// Bound by the chain of loads where there are few blocks, then by the bytes of W: bfloat16 9 x 2432 -> 256, batch 32, 11 us (fwd_mfma_kernel 56),
-// 32 x 3072 -> 256, batch 32, 20 us (69; 100 MB), 16 x 784 -> 500, batch 100, 13.2 us (tile_fwd_kernel 18.9); fp32 12 x 784 -> 768, batch
-// 128, 31 us (shared_fwd_kernel 39).  Three steps ahead take more than 128 registers, one workgroup a compute unit: 81 x 784 -> 426,
-// batch 64, fp32 64 us and 53 with two.
-constexpr int WF_WAVES = 8, WF_THREADS = 64 * WF_WAVES, WF_COLS = 32, WF_PITCH = WF_COLS + 1, WF_DEPTH = 2;
-typedef uint32_t tile_u32x4_any __attribute__((ext_vector_type(4), aligned(2)));
-template <bool BF> struct WaveOperand { typedef f32x4 piece; typedef float elem; typedef tile_f32x4_any any; };      // piece: 16 bytes of a row
-template <> struct WaveOperand<true> { typedef tile_u32x4 piece; typedef uint16_t elem; typedef tile_u32x4_any any; };
-template <int RT>
-__device__ __forceinline__ void wave_multiply(const f32x4 (&a)[RT], const float *w, tile_f32x16 (&acc)[RT])
-{
-#pragma unroll
-    for (int e = 0; e < 4; ++e)
-#pragma unroll
-        for (int i = 0; i < RT; ++i) acc[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i][e], w[e], acc[i], 0, 0, 0);
-}
-template <int RT>
-__device__ __forceinline__ void wave_multiply(const tile_u32x4 (&a)[RT], const float *w, tile_f32x16 (&acc)[RT])
-{
-    const tile_u32x4 b = {pack_bf16x2(w[0], w[1]), pack_bf16x2(w[2], w[3]), pack_bf16x2(w[4], w[5]), pack_bf16x2(w[6], w[7])};
-#pragma unroll
-    for (int i = 0; i < RT; ++i)
-        acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(tile_bf16x8, a[i]), __builtin_bit_cast(tile_bf16x8, b), acc[i], 0, 0, 0);
-}
-// 16-byte unit of piece `at` (0 .. 3) of a row: sixteen rows' pieces, written or read together, then lie in different banks
-__device__ __forceinline__ int wave_unit(int row, int at) { return 4 * row + ((at ^ (row >> 2)) & 3); }
-
-template <bool BF, int RT, bool TAIL>
-__global__ void __launch_bounds__(WF_THREADS) wave_fwd_kernel(TileFwd p)
+// Few blocks: 32 columns and RT x 32 batch rows, four waves that share the contraction, 32 indices of every 128 each.  A wave asks for both operands
+// DEPTH steps of 64 bytes of a row of A (sixteen indices, bfloat16 32) ahead.  A crosses LDS by way of the wave's own buffer, so that four
+// lanes read 64 neighbouring bytes of a row; a lane per row, in the layout of the matrix instruction, takes 64 turns of the cache a load instead of 16 (7 x
+// 3072 -> 1024, batch 128, fp32 94 us, 71 with it).  A lane's operands of W are neighbouring rows of its column, each a load of a float (32
+// lanes 128 bytes of a row).  No barrier until the waves' parts are added, in the order of the waves.  TAIL: indices behind the last
+// whole step.  FAR: rows of W too far apart for 32-bit offsets.
+// Bound by the chain of loads where there are few blocks, then by the fp32 matrix rate or the bytes of W.  Steps through LDS that all waves wait for
+// twice (32 x 32 blocks, the same sums), and now, us: 5 x 3072 -> 858, batch 128, fp32 101 and 73; 28 x 768 -> 192, batch 23, 11.5 and 9.2; bfloat16 27 x
+// 3072 -> 64, batch 32, 29 and 14; 37 x 3072 -> 192, batch 104, 44 and 30.
+constexpr int SH_WAVES = 4, SH_THREADS = 64 * SH_WAVES;
+template <bool BF, int RT, bool TAIL, int DEPTH, bool FAR = false>
+__global__ void __launch_bounds__(SH_THREADS) wave_fwd_kernel(TileFwd p)
 {
     constexpr int PE = BF ? 8 : 4, KS = 4 * PE, BM = 32 * RT, TP = BM + 8;     // elements of a piece; indices of a step
     typedef typename WaveOperand<BF>::piece piece;
     typedef typename WaveOperand<BF>::elem elem;
-    constexpr int PART = WF_WAVES * 32 * WF_PITCH * 4, OPERAND = WF_WAVES * BM * 64;
+    constexpr int PART = SH_WAVES * 32 * WF_PITCH * 4, OPERAND = SH_WAVES * BM * 64;
     __shared__ __attribute__((aligned(16))) unsigned char smem[PART > OPERAND ? PART : OPERAND];
     __shared__ __attribute__((aligned(16))) uint16_t turn[BF ? WF_COLS : 1][TP];       // the block's activations, transposed
     const int t = threadIdx.x, lane = t & 63, row = lane & 31, half = lane >> 5;
@@ -265,15 +205,26 @@ __global__ void __launch_bounds__(WF_THREADS) wave_fwd_kernel(TileFwd p)
     if (!decode_group(tile_block(), nblk * mblk, p.M, g, local)) return;
     const int n0 = (int)(local % nblk) * WF_COLS, m0 = (int)(local / nblk) * BM, K = p.din;
     const float bias = tile_fwd_bias(p, g, n0 + (t & 31));            // for the end; requested first
-    const int total = K / KS, n_mine = wave < total ? (total - wave + WF_WAVES - 1) / WF_WAVES : 0, s_last = wave + WF_WAVES * (n_mine - 1);
+    // this wave's steps, n-th of them: 32 indices of every 128
+    constexpr int OF = 32 / KS;                                       // steps of 32 indices
+    const int total = K / KS, n_mine = total / (4 * OF) * OF + min(max(total % (4 * OF) - OF * wave, 0), OF);
+    auto step = [&](int n) {                                          // past the last one: that one again, never used
+        n = min(n, n_mine - 1);
+        return n / OF * (4 * OF) + OF * wave + n % OF;
+    };
     const uint32_t skip = (uint32_t)(p.M - 1) << (TILE_SHIFT + 2), dout4 = (uint32_t)p.dout * 4u;
     const int col = min(n0 + row, p.dout - 1);                        // columns past the end repeat the last one
     const uint32_t w_first = (uint32_t)col * 4u + (uint32_t)(PE * half) * dout4;
     // index of a lane's element e of a step: pieces `half` and `half` + 2
     auto index = [&](int e) { return e < PE ? PE * half + e : PE * half + PE + e; };
-    float w[WF_DEPTH][2 * PE];
-    piece a[WF_DEPTH][RT][2];
+    float w[DEPTH][2 * PE];
+    piece a[DEPTH][RT][2];
     auto request_w = [&](int d, int s) {
+        if constexpr (FAR) {
+#pragma unroll
+            for (int e = 0; e < 2 * PE; ++e) w[d][e] = p.X[tiled_offset_quick(p.M, g, p.woff + (int64_t)(s * KS + index(e)) * p.dout + col)];
+            return;
+        }
         const int64_t j0 = p.woff + (int64_t)s * KS * p.dout;
         const float *base = p.X + (((size_t)(j0 >> TILE_SHIFT) * p.M + g) << TILE_SHIFT);
         const uint32_t from = w_first + (uint32_t)(j0 & (TILE - 1)) * 4u;
@@ -283,10 +234,9 @@ __global__ void __launch_bounds__(WF_THREADS) wave_fwd_kernel(TileFwd p)
             w[d][e] = *(const float *)((const char *)base + (__umul24(q >> (TILE_SHIFT + 2), skip) + q));
         }
     };
-    auto clamped = [&](int s) { return s < s_last ? s : s_last; };    // past the last step: that one again, never used
     if (n_mine > 0) {                                                 // these do not wait for the batch-row numbers
 #pragma unroll
-        for (int d = 0; d < WF_DEPTH; ++d) request_w(d, clamped(wave + WF_WAVES * d));
+        for (int d = 0; d < DEPTH; ++d) request_w(d, step(d));
     }
     // pieces that this lane brings into LDS: lane % 4 of rows lane / 4 and lane / 4 + 16 of every tile
     const int pa = lane & 3, pr = lane >> 2;
@@ -326,9 +276,24 @@ __global__ void __launch_bounds__(WF_THREADS) wave_fwd_kernel(TileFwd p)
     };
     if (n_mine > 0) {
 #pragma unroll
-        for (int d = 0; d < WF_DEPTH; ++d) request_a(d, clamped(wave + WF_WAVES * d));
+        for (int d = 0; d < DEPTH; ++d) request_a(d, step(d));
     }
-    if (TAIL && wave == total % WF_WAVES) {                           // the wave whose turn it would be; what does not exist counts as zero
+    if (n_mine > 0) {
+        int done = 0;
+        for (; done + DEPTH <= n_mine; done += DEPTH) {
+#pragma unroll
+            for (int d = 0; d < DEPTH; ++d) {
+                multiply(a[d], w[d]);
+                const int s = step(done + d + DEPTH);
+                request_a(d, s);
+                request_w(d, s);
+            }
+        }
+#pragma unroll
+        for (int d = 0; d < DEPTH - 1; ++d)
+            if (done + d < n_mine) multiply(a[d], w[d]);
+    }
+    if (TAIL && wave == total % (4 * OF) / OF) {                      // what does not exist counts as zero
         const int from = total * KS, left = K - from;
         float wt[2 * PE];
         piece at[RT][2];
@@ -354,21 +319,6 @@ __global__ void __launch_bounds__(WF_THREADS) wave_fwd_kernel(TileFwd p)
         for (int e = 0; e < 2 * PE; ++e) wt[e] = index(e) < left ? wt[e] : 0.0f;
         multiply(at, wt);
     }
-    if (n_mine > 0) {
-        int done = 0;
-        for (; done + WF_DEPTH <= n_mine; done += WF_DEPTH) {
-#pragma unroll
-            for (int d = 0; d < WF_DEPTH; ++d) {
-                multiply(a[d], w[d]);
-                const int s = clamped(wave + WF_WAVES * (done + d + WF_DEPTH));
-                request_a(d, s);
-                request_w(d, s);
-            }
-        }
-#pragma unroll
-        for (int d = 0; d < WF_DEPTH - 1; ++d)
-            if (done + d < n_mine) multiply(a[d], w[d]);
-    }
     __syncthreads();                                                  // the operands' space becomes the parts
     float (*part)[32][WF_PITCH] = reinterpret_cast<float (*)[32][WF_PITCH]>(smem);
     const int c = t & 31;
@@ -379,11 +329,11 @@ __global__ void __launch_bounds__(WF_THREADS) wave_fwd_kernel(TileFwd p)
         for (int v = 0; v < 16; ++v) part[wave][tile_row(lane, v)][row] = acc[i][v];
         __syncthreads();
 #pragma unroll
-        for (int u = 0; u < 16 / WF_WAVES; ++u) {
-            const int r = (t >> 5) + 2 * WF_WAVES * u, b = m0 + 32 * i + r;
+        for (int u = 0; u < 16 / SH_WAVES; ++u) {
+            const int r = (t >> 5) + 2 * SH_WAVES * u, b = m0 + 32 * i + r;
             float z = part[0][r][c];
 #pragma unroll
-            for (int k = 1; k < WF_WAVES; ++k) z += part[k][r][c];
+            for (int k = 1; k < SH_WAVES; ++k) z += part[k][r][c];
             z += bias;
             if (p.relu) z = z > 0.0f ? z : 0.0f;
             const size_t at = ((size_t)g * p.B + b) * p.dout + n0 + c;
@@ -401,7 +351,7 @@ __global__ void __launch_bounds__(WF_THREADS) wave_fwd_kernel(TileFwd p)
         __syncthreads();
         const int rows = min(BM, p.B - m0), cols = min(WF_COLS, p.dout - n0);
         uint16_t *to = p.out_bf16_t + ((size_t)g * p.dout + n0) * p.B + m0;
-        for (int e = t; e < cols * (BM / 8); e += WF_THREADS) {      // who asks for it has a batch of whole 32 rows
+        for (int e = t; e < cols * (BM / 8); e += SH_THREADS) {      // who asks for it has a batch of whole 32 rows
             const int c8 = e % (BM / 8) * 8, k = e / (BM / 8);
             if (c8 < rows) *reinterpret_cast<tile_u32x4 *>(to + (size_t)k * p.B + c8) = *reinterpret_cast<const tile_u32x4 *>(&turn[k][c8]);
         }
@@ -511,7 +461,7 @@ __global__ void __launch_bounds__(SF_THREADS, 2) split_fwd_kernel(TileFwd p)
                 lost |= fabsf(acc[i][j][v]) < FEW_BITS && acc[i][j][v] != 0.0f;
             }
     if (__syncthreads_or(lost || !(watch == 0.0f)))
-        tile_fwd_product<false, true, VW, BM, BN, 64, WM, WN, 1>(p, g, m0, n0, smem, acc);
+        tile_fwd_product<false, VW, BM, BN, 64, WM, WN>(p, g, m0, n0, smem, acc);
     tile_fwd_store<false, BM, BN, WM, WN>(p, g, m0, n0, wm, wn, lane, acc);
 }
 
@@ -532,70 +482,61 @@ static void launch_shape(hipStream_t s, const TileFwd &a)
 //                          (640) 107 and 106, 48 x 784-515, batch 50 (864) 151 and 145
 // Larger forms, bfloat16, batch > 64: 128 x 32 blocks while the 128 x 64 ones do not fill the chip: 31 x 784-500, batch 100 (248 of
 // the latter) 97 and 102, 64 x 1000-300 (320) 145 and 143, 31 x 3001-999 (496) 755 and 710.
+// 32-bit offsets do not reach over a step's rows of W.
+static bool far_rows(const TileFwd &a) { return a.M > 2048 || ((32 * (int64_t)a.dout + TILE) / TILE + 1) * a.M * (TILE * 4) >= (int64_t)1 << 32; }
 template <bool BF, int RT> static void launch_wave(hipStream_t s, const TileFwd &a)
 {
     const unsigned n = (unsigned)((a.dout + WF_COLS - 1) / WF_COLS) * (unsigned)((a.B + 32 * RT - 1) / (32 * RT));
-    const dim3 grid = tile_grid(grouped_grid(a.M, n)), block(WF_THREADS);
-    if (a.din % (BF ? 32 : 16) == 0) hipLaunchKernelGGL((wave_fwd_kernel<BF, RT, false>), grid, block, 0, s, a);
-    else hipLaunchKernelGGL((wave_fwd_kernel<BF, RT, true>), grid, block, 0, s, a);
+    const dim3 grid = tile_grid(grouped_grid(a.M, n)), block(SH_THREADS);
+    const bool tail = a.din % (BF ? 32 : 16) != 0;
+    if constexpr (RT == 1)
+        if (far_rows(a)) {
+            hipLaunchKernelGGL((wave_fwd_kernel<BF, 1, true, 2, true>), grid, block, 0, s, a);
+            return;
+        }
+    // fp32, two steps ahead and three: 1330 indices 1.24 and 1.33 times as fast as the kernel before, 3072 1.22 and 1.48, 784 1.33 and 1.31
+    if constexpr (!BF)
+        if (a.din >= 1024) {
+            if (tail) hipLaunchKernelGGL((wave_fwd_kernel<BF, RT, true, 3>), grid, block, 0, s, a);
+            else hipLaunchKernelGGL((wave_fwd_kernel<BF, RT, false, 3>), grid, block, 0, s, a);
+            return;
+        }
+    if (tail) hipLaunchKernelGGL((wave_fwd_kernel<BF, RT, true, 2>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((wave_fwd_kernel<BF, RT, false, 2>), grid, block, 0, s, a);
 }
 // Tiles of 32 batch rows in a workgroup: rounds of workgroups over the compute units times what one takes, in proportion to the tiles and a part that does
-// not depend on them (of a tile's time fp32 0.3, bfloat16 1).  us, one, two and four tiles: bfloat16 16 x 784 -> 500, batch 100 17.5, 15.6, 13.2, 48 x 3072
-// -> 256, batch 128 61, 53, 56, 64 x 3072 -> 256 101, 84, 70; fp32 12 x 3072 -> 1024, batch 60 62, 72, 16 x 87, 73, batch 128 12 x 126, 109.
-// fp32 never gains by four: 47 x 1330 -> 184, batch 128, 48, 52, 66.
+// not depend on them (of a tile's time fp32 0.3, bfloat16 1).  us, one, two and four tiles: bfloat16 48 x 3072 -> 256, batch 128 61, 53, 56, 64 x 101, 84,
+// 70; fp32 12 x 3072 -> 1024, batch 60 62, 72, 16 x 87, 73, batch 128 12 x 126, 109.  fp32 never gains by four: 47 x 1330 -> 184, batch
+// 128, 48, 52, 66.  Short contractions: one (124 indices, batch 128, 300 to 600 blocks 25 % faster than by that rule).
 template <bool BF> static void launch_wave(hipStream_t s, const TileFwd &a)
 {
     const int64_t cols = (int64_t)a.M * ((a.dout + WF_COLS - 1) / WF_COLS);
     auto cost = [&](int rt) { return (cols * ((a.B + 32 * rt - 1) / (32 * rt)) + MF_XCD * XCD_CUS - 1) / (MF_XCD * XCD_CUS) * (10 * rt + (BF ? 10 : 3)); };
     int rt = 1;
-    for (int k = 2; k <= (BF ? 4 : 2); k *= 2)
+    for (int k = 2; k <= (BF ? 4 : 2) && a.din >= 384 && !far_rows(a); k *= 2)
         if (a.B > 16 * k && cost(k) < cost(rt)) rt = k;
     if (rt == 1) launch_wave<BF, 1>(s, a);
     else if (rt == 2) launch_wave<BF, 2>(s, a);
     else if constexpr (BF) launch_wave<BF, 4>(s, a);
 }
 
-// Whether wave_fwd_kernel takes a layer: few blocks of 32 columns (of all workers) and many contraction indices.  us, it and the other kernel, either
-// side of each line:
-//   bfloat16, batch <= 32    60 x 784 -> 516 (1020 blocks) 21.2 and 26.4, 90 x (1530) 30.3 and 31.0; aligned layers 32 x 1024 -> 1024 (1024) 25.6 and 29.7,
-//                            48 x (1536) 36.6 and 33.5
-//   bfloat16, batch <= 64    30 x 784 -> 516 (510) 18.6 and 21.2, 45 x (765) 26 and 22; aligned 16 x 1024 -> 1024 (512) 19.6 and 29.0, 32 x (1024) 36 and 31
-//   bfloat16, more           15 x 784 -> 516, batch 128 (255) 14.9 and 19.4, 23 x (391) 26 and 21.4; aligned 16 x 1024 -> 1024, batch 128 (512) 27 and 30, 24 x
-//                            (768) 40 and 32; 16 x 256 -> 512 (256) 8.0 and 11.2, 32 x (512) 13.4 and 13.4
-//   fp32, batch <= 32        always: 120 x 784 -> 516 49 and 64, 64 x 3072 -> 1024 204 and 223
-//   fp32, batch <= 64        120 x 784 -> 516, batch 60 (2040) 85 and 102; 64 x 3072 -> 1024 (2048) 313 and 306
-//   fp32, more               16 x 3072 -> 1024, batch 128 (512) 148 and 207, 24 x (768) 218 and 212
-// Fewer indices: shared_fwd_kernel, whose workgroups are smaller (23 x 252 -> 516, batch 128, bfloat16 13.4 and 18; fp32 20.2 and 22.5).  Aligned layers have
-// no such form: 8 x 256 -> 1024, batch 32, 4.8 us and 10.0 by fwd_mfma_kernel.
-// 32-bit offsets inside a step's rows of W.
-static bool wave_fwd_pays(int M, int B, int64_t din, int64_t dout, bool bf, bool aligned)
+static bool enough_blocks(int M, int B, int64_t din, int64_t dout, bool bf)
 {
-    const int64_t blocks = M * ((dout + WF_COLS - 1) / WF_COLS), step = (32 * dout + TILE) / TILE + 1;
-    if ((!aligned && din < 640) || M > 2048 || step * M * (TILE * 4) >= (int64_t)1 << 32) return false;
-    if (bf) return blocks <= (B <= 32 ? 1024 : B <= 64 || (aligned && din >= 512) ? 512 : 320);
-    return B <= 32 || blocks <= (B <= 64 ? 2048 : 512);
+    return din >= 4 && M * ((dout + 63) / 64) * ((B + 31) / 32) >= (bf ? 512 : B > 32 && B <= 64 ? 641 : 1025);
 }
-bool wave_fwd_pays(const MlpPlan &p, int l) { return wave_fwd_pays(p.M, p.B, p.dims[l], p.dims[l + 1], p.bf16 != 0, mfma_layer_ok(p, l)); }
 
-template <bool BF, bool VA, bool VW> static void launch_rows(hipStream_t s, const TileFwd &a, bool wave)
+template <bool BF, bool VW> static void launch_rows(hipStream_t s, const TileFwd &a)
 {
-    if (wave) return launch_wave<BF>(s, a);
-    const int64_t cols = (int64_t)a.M * ((a.dout + 63) / 64), blocks = cols * ((a.B + 31) / 32), wide = cols * ((a.B + 127) / 128);
-    const int64_t enough = BF ? 512 : a.B > 32 && a.B <= 64 ? 641 : 1025;
-    if constexpr (VA)
-        if (blocks >= enough) {
-            if (a.B <= 32) launch_shape<BF, VW, 32, 64, 64, 1, 2>(s, a);
-            else if (a.B <= 64) launch_shape<BF, VW, 64, 64, BF ? 128 : 64, 2, 2>(s, a);
-            else if constexpr (!BF) {
-                const unsigned n = (unsigned)((a.dout + SF_BN - 1) / SF_BN) * (unsigned)((a.B + SF_BM - 1) / SF_BM);
-                hipLaunchKernelGGL((split_fwd_kernel<VW>), tile_grid(grouped_grid(a.M, n)), dim3(SF_THREADS), 0, s, a);
-            }
-            else if (wide <= MF_XCD * XCD_CUS) launch_shape<BF, VW, 128, 32, 128, 4, 1>(s, a);
-            else launch_shape<BF, VW, 128, 64, 64, 2, 2>(s, a);
-            return;
-        }
-    const unsigned n = (unsigned)((a.dout + 31) / 32) * (unsigned)((a.B + 31) / 32);
-    hipLaunchKernelGGL((shared_fwd_kernel<BF, VA, VW>), tile_grid(grouped_grid(a.M, n)), dim3(64 * SH_WAVES), 0, s, a);
+    const int64_t wide = (int64_t)a.M * ((a.dout + 63) / 64) * ((a.B + 127) / 128);
+    if (!enough_blocks(a.M, a.B, a.din, a.dout, BF)) return launch_wave<BF>(s, a);
+    if (a.B <= 32) launch_shape<BF, VW, 32, 64, 64, 1, 2>(s, a);
+    else if (a.B <= 64) launch_shape<BF, VW, 64, 64, BF ? 128 : 64, 2, 2>(s, a);
+    else if constexpr (!BF) {
+        const unsigned n = (unsigned)((a.dout + SF_BN - 1) / SF_BN) * (unsigned)((a.B + SF_BM - 1) / SF_BM);
+        hipLaunchKernelGGL((split_fwd_kernel<VW>), tile_grid(grouped_grid(a.M, n)), dim3(SF_THREADS), 0, s, a);
+    }
+    else if (wide <= MF_XCD * XCD_CUS) launch_shape<BF, VW, 128, 32, 128, 4, 1>(s, a);
+    else launch_shape<BF, VW, 128, 64, 64, 2, 2>(s, a);
 }
 
 void launch_tile_fwd(hipStream_t s, const MlpPlan &p, int l, const float *X, bool need_t)
@@ -608,16 +549,11 @@ void launch_tile_fwd(hipStream_t s, const MlpPlan &p, int l, const float *X, boo
     a.out = (last || !bf) ? p.act[l + 1] : nullptr;
     a.out_bf16 = (bf && !last) ? p.hb[l + 1] : nullptr;
     a.out_bf16_t = (bf && !last && need_t) ? p.ht[l + 1] : nullptr;
-    // pieces of A: any four neighbours; pieces of W: four columns of a row that starts at a multiple of four
-    const bool va = a.din >= 4;
-    const bool vw = a.dout % 4 == 0 && a.woff % 4 == 0;
-    const bool wave = wave_fwd_pays(p, l);
+    const bool vw = a.dout % 4 == 0 && a.woff % 4 == 0;               // pieces of W: four columns of a row that starts at a multiple of four
     if (bf) {
-        if (va) { if (vw) launch_rows<true, true, true>(s, a, wave); else launch_rows<true, true, false>(s, a, wave); }
-        else { if (vw) launch_rows<true, false, true>(s, a, wave); else launch_rows<true, false, false>(s, a, wave); }
+        if (vw) launch_rows<true, true>(s, a); else launch_rows<true, false>(s, a);
     } else {
-        if (va) { if (vw) launch_rows<false, true, true>(s, a, wave); else launch_rows<false, true, false>(s, a, wave); }
-        else { if (vw) launch_rows<false, false, true>(s, a, wave); else launch_rows<false, false, false>(s, a, wave); }
+        if (vw) launch_rows<false, true>(s, a); else launch_rows<false, false>(s, a);
     }
 }
 

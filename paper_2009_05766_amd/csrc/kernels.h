@@ -222,7 +222,6 @@ hipError_t launch_resident_mlp(hipStream_t s, const MlpPlan &p, const SlicedIter
 // matrix-core kernel above); below_fast: so are both bfloat16 copies of the error.  launch_tile_dgrad: true if it has also
 // written the bias gradient of the layer below (its workgroups held the whole batch).
 void launch_tile_fwd(hipStream_t s, const MlpPlan &p, int l, const float *X, bool need_t);
-bool wave_fwd_pays(const MlpPlan &p, int l);             // few blocks, long contraction: also faster than launch_fwd_mfma() on its layers
 constexpr int TILE_DGRAD_BATCH = 128;                   // up to here they do
 bool launch_tile_dgrad(hipStream_t s, const MlpPlan &p, int l, const float *X, float *G, int cur, bool below_fast);
 bool tile_wgrad_update_ok(const MlpPlan &p, int l);      // its update: fp32 operands, aligned rows

@@ -303,4 +303,43 @@ template <int RI, int CJ> __device__ __forceinline__ void tile_clear(tile_f32x16
             for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
 }
 
+// ---- operands that cross LDS in steps of 64 bytes of every row (sixteen indices, bfloat16 32), straight from wide loads to the layout of the matrix
+// instruction; blocks of 32 columns
+constexpr int WF_COLS = 32, WF_PITCH = WF_COLS + 1;
+typedef uint32_t tile_u32x4_any __attribute__((ext_vector_type(4), aligned(2)));
+template <bool BF> struct WaveOperand { typedef f32x4 piece; typedef float elem; typedef tile_f32x4_any any; };      // piece: 16 bytes of a row
+template <> struct WaveOperand<true> { typedef tile_u32x4 piece; typedef uint16_t elem; typedef tile_u32x4_any any; };
+template <int RT>
+__device__ __forceinline__ void wave_multiply(const f32x4 (&a)[RT], const float *w, tile_f32x16 (&acc)[RT])
+{
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int i = 0; i < RT; ++i) acc[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i][e], w[e], acc[i], 0, 0, 0);
+}
+template <int RT>
+__device__ __forceinline__ void wave_multiply(const tile_u32x4 (&a)[RT], const float *w, tile_f32x16 (&acc)[RT])
+{
+    const tile_u32x4 b = {pack_bf16x2(w[0], w[1]), pack_bf16x2(w[2], w[3]), pack_bf16x2(w[4], w[5]), pack_bf16x2(w[6], w[7])};
+#pragma unroll
+    for (int i = 0; i < RT; ++i)
+        acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(tile_bf16x8, a[i]), __builtin_bit_cast(tile_bf16x8, b), acc[i], 0, 0, 0);
+}
+// 16-byte unit of piece `at` (0 .. 3) of a row: sixteen rows' pieces, written or read together, then lie in different banks
+__device__ __forceinline__ int wave_unit(int row, int at) { return 4 * row + ((at ^ (row >> 2)) & 3); }
+
+// Parameters j .. j + 3 of a worker.  ALIGNED: they do not cross a layout tile.  Otherwise one load where they lie in a tile together, the last four of the tile
+// for a lane where they do not, and the wave again by floats.
+template <bool ALIGNED> __device__ __forceinline__ f32x4 load4_params(const float *X, int M, int g, int64_t j)
+{
+    if constexpr (ALIGNED) return load4(X + tiled_offset_quick(M, g, j));
+    const int over = max((int)(j & (TILE - 1)) - (TILE - 4), 0);
+    f32x4 r = *reinterpret_cast<const tile_f32x4_any *>(X + tiled_offset_quick(M, g, j - over));
+    if (__any(over > 0)) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) r[e] = X[tiled_offset_quick(M, g, j + e)];
+    }
+    return r;
+}
+
 }  // namespace netmax

@@ -49,15 +49,33 @@ def test_gradient_of_odd_layers(ora, dtype, M, batch, dims):
 @pytest.mark.parametrize("dtype,M,batch,dims", [
     # contractions that eight waves share: whole steps of sixteen (bfloat16 32) indices, one more, one fewer, a wave without a step of its own
     ("f32", 2, 31, (640, 33, 10)), ("f32", 3, 33, (641, 65, 10)), ("f32", 2, 100, (655, 31, 10)), ("f32", 9, 129, (650, 68, 10)), ("f32", 2, 20, (1000, 40)),
+    ("f32", 2, 40, (1030, 33, 10)), ("f32", 3, 3, (3, 34, 10)), ("f32", 2049, 3, (5, 36, 3)), ("bf16", 2049, 3, (5, 36, 3)),
     ("bf16", 2, 31, (640, 33, 10)), ("bf16", 3, 33, (641, 65, 10)), ("bf16", 2, 100, (671, 31, 10)), ("bf16", 9, 129, (650, 68, 10)), ("bf16", 2, 20, (1000, 40)),
     # aligned layers (both orientations of the activations): fewer steps than waves, one, two and four row tiles, a general layer under them
     ("bf16", 3, 32, (128, 128, 10)), ("bf16", 2, 64, (256, 384, 128, 10)), ("bf16", 17, 96, (1280, 256, 10)), ("bf16", 2, 128, (700, 128, 128, 10)),
     # the most blocks that it takes, and one worker more
     ("f32", 32, 65, (640, 500, 10)), ("f32", 33, 65, (640, 500, 10)), ("f32", 64, 33, (644, 1024, 10)), ("f32", 65, 33, (644, 1024, 10)),
-    ("bf16", 32, 20, (640, 1024, 10)), ("bf16", 33, 20, (640, 1024, 10)), ("bf16", 10, 65, (640, 1020, 10)), ("bf16", 11, 65, (640, 1020, 10)),
-    ("bf16", 16, 64, (512, 1024, 10)), ("bf16", 17, 64, (512, 1024, 10)), ("bf16", 10, 128, (384, 1024, 10)), ("bf16", 11, 128, (384, 1024, 10)),
+    ("bf16", 32, 20, (640, 1024, 10)), ("bf16", 33, 20, (640, 1024, 10)), ("bf16", 8, 65, (640, 1020, 10)), ("bf16", 9, 65, (640, 1020, 10)),
+    ("bf16", 16, 64, (512, 1024, 10)), ("bf16", 17, 64, (512, 1024, 10)), ("bf16", 8, 128, (384, 1024, 10)), ("bf16", 9, 128, (384, 1024, 10)),
 ])
 def test_gradient_of_long_contractions(ora, dtype, M, batch, dims):
+    test_gradient_of_odd_layers(ora, dtype, M, batch, dims)
+
+
+@pytest.mark.parametrize("dtype,M,batch,dims", [
+    # errors of layers in few blocks: whole steps of sixteen (bfloat16 32) outputs, one more, fewer than a step; rows of W that start anywhere
+    ("f32", 2, 31, (20, 33, 160, 10)), ("f32", 3, 33, (20, 65, 129, 10)), ("f32", 2, 64, (21, 31, 34, 10)), ("f32", 2, 20, (20, 40, 7, 33, 10)),
+    ("f32", 2, 100, (20, 36, 656, 10)), ("f32", 2, 128, (21, 35, 643, 10)), ("f32", 2, 150, (21, 35, 643, 10)), ("f32", 3, 65, (21, 35, 70, 10)),
+    ("bf16", 2, 31, (20, 33, 160, 10)), ("bf16", 3, 33, (20, 65, 129, 10)), ("bf16", 2, 64, (21, 31, 34, 10)), ("bf16", 2, 20, (20, 40, 7, 33, 10)),
+    # aligned layers over general and aligned ones: fewer steps than waves and more, one, two and four row tiles
+    ("bf16", 2, 32, (60, 128, 128, 10)), ("bf16", 2, 64, (128, 256, 384, 10)), ("bf16", 3, 96, (100, 128, 512, 10)), ("bf16", 2, 128, (128, 128, 128, 40)),
+    ("bf16", 2, 64, (100, 100, 128, 128, 10)),
+    # the most blocks that it takes, and one worker more
+    ("f32", 48, 20, (20, 1000, 30, 10)), ("f32", 49, 20, (20, 1000, 30, 10)), ("f32", 64, 40, (20, 128, 40, 10)), ("f32", 65, 40, (20, 128, 40, 10)),
+    ("bf16", 64, 40, (20, 128, 40, 10)), ("bf16", 65, 40, (20, 128, 40, 10)), ("bf16", 48, 32, (20, 1024, 128, 10)), ("bf16", 49, 32, (20, 1024, 128, 10)),
+    ("bf16", 24, 96, (20, 1024, 128, 10)), ("bf16", 25, 96, (20, 1024, 128, 10)),
+])
+def test_errors_of_few_blocks(ora, dtype, M, batch, dims):
     test_gradient_of_odd_layers(ora, dtype, M, batch, dims)
 
 
