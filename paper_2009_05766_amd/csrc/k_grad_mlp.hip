@@ -239,7 +239,8 @@ bool launch_mlp_grad(hipStream_t s, const MlpPlan &p, const float *X, float *G, 
     for (int l = 0; l < L; ++l) {
         const bool last = (l + 1 == L);
         if (fast[l] && !last) {
-            launch_fwd_mfma(s, p, l, X);
+            if (chain_fwd_pays(p, l)) launch_chain_fwd(s, p, l, X, true);
+            else launch_fwd_mfma(s, p, l, X);
             continue;
         }
         if (last && small_last) {
@@ -253,7 +254,9 @@ bool launch_mlp_grad(hipStream_t s, const MlpPlan &p, const float *X, float *G, 
         }
         if (p.dims[l + 1] > 32) {
             // the transposed bfloat16 activation is read by the matrix-core weight gradients only
-            launch_tile_fwd(s, p, l, X, !last && (fast[l + 1] || (l + 2 == L && small_last)));
+            const bool need_t = !last && (fast[l + 1] || (l + 2 == L && small_last));
+            if (chain_fwd_pays(p, l)) launch_chain_fwd(s, p, l, X, need_t);
+            else launch_tile_fwd(s, p, l, X, need_t);
             continue;
         }
         FwdProblem f;
@@ -301,7 +304,10 @@ bool launch_mlp_grad(hipStream_t s, const MlpPlan &p, const float *X, float *G, 
                                dout, p.dz[cur], p.woff[l] + din * dout, G);
         }
         if (l > 0) {
-            if (fast[l]) {
+            if (chain_dgrad_pays(p, l)) {
+                launch_chain_dgrad(s, p, l, X, G, cur, fast[l - 1]);
+                bias_done[l - 1] = true;
+            } else if (fast[l]) {
                 launch_dgrad_mfma(s, p, l, X, G, cur, !fast[l - 1]);
                 bias_done[l - 1] = true;
             } else if (l == L - 1 && small_last) {

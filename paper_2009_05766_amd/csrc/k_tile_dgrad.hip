@@ -130,7 +130,7 @@ __global__ void __launch_bounds__(64 * WM * WN) tile_dgrad_kernel(TileDgrad p)
 // into the layout of the matrix instruction; the parts are added in the order of the waves.  V: pieces of W do not cross a layout tile.
 // TAIL: indices behind the last whole step.
 // Bound by one or two chains of loads where the other kernel waits for one at every step: 4 x 1000-1000, batch 20, 9.3 us (tile_dgrad_kernel 27), 13 x
-// 301-1001, batch 60, 18 us (43).
+// 301-1001, batch 60, 18 us (43).  (bfloat16 operands: k_chain.hip.)
 constexpr int WD_DEPTH = 2, WF_WAVES = 8, WF_THREADS = 64 * WF_WAVES;
 template <int RT, bool V, bool TAIL>
 __global__ void __launch_bounds__(WF_THREADS) wave_dgrad_kernel(TileDgrad p)

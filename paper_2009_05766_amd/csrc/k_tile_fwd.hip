@@ -524,6 +524,7 @@ static bool enough_blocks(int M, int B, int64_t din, int64_t dout, bool bf)
 {
     return din >= 4 && M * ((dout + 63) / 64) * ((B + 31) / 32) >= (bf ? 512 : B > 32 && B <= 64 ? 641 : 1025);
 }
+bool tile_fwd_one_chain(const MlpPlan &p, int l) { return enough_blocks(p.M, p.B, p.dims[l], p.dims[l + 1], p.bf16 != 0); }
 
 template <bool BF, bool VW> static void launch_rows(hipStream_t s, const TileFwd &a)
 {

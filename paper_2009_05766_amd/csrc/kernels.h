@@ -222,10 +222,18 @@ hipError_t launch_resident_mlp(hipStream_t s, const MlpPlan &p, const SlicedIter
 // matrix-core kernel above); below_fast: so are both bfloat16 copies of the error.  launch_tile_dgrad: true if it has also
 // written the bias gradient of the layer below (its workgroups held the whole batch).
 void launch_tile_fwd(hipStream_t s, const MlpPlan &p, int l, const float *X, bool need_t);
+bool tile_fwd_one_chain(const MlpPlan &p, int l);        // its sums are one chain over the contraction, not four (blocks enough)
 constexpr int TILE_DGRAD_BATCH = 128;                   // up to here they do
 bool launch_tile_dgrad(hipStream_t s, const MlpPlan &p, int l, const float *X, float *G, int cur, bool below_fast);
 bool tile_wgrad_update_ok(const MlpPlan &p, int l);      // its update: fp32 operands, aligned rows
 void launch_tile_wgrad(hipStream_t s, const MlpPlan &p, int l, float *G, int cur, const TailArgs *tail, bool others);
+
+// Layers on bfloat16 operands in few blocks (k_chain.hip), bit for bit as the tiled and the matrix-core kernels; the error's kernel also writes the
+// bias gradient of the layer below.
+bool chain_fwd_pays(const MlpPlan &p, int l);
+void launch_chain_fwd(hipStream_t s, const MlpPlan &p, int l, const float *X, bool need_t);
+bool chain_dgrad_pays(const MlpPlan &p, int l);
+void launch_chain_dgrad(hipStream_t s, const MlpPlan &p, int l, const float *X, float *G, int cur, bool below_fast);
 
 // Last layer with at most 32 classes, fp32 or bfloat16 operands (k_grad_head.hip): from its input to the error of the layer
 // below in two kernels: logits, loss, dW, db, dH and the column sums of dH.

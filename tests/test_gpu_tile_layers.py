@@ -79,6 +79,29 @@ def test_errors_of_few_blocks(ora, dtype, M, batch, dims):
     test_gradient_of_odd_layers(ora, dtype, M, batch, dims)
 
 
+@pytest.mark.parametrize("few,many,batch,dims", [
+    # aligned layers, forward and error: one, two, three and four row tiles, fewer steps than a chunk, a start of the contraction of every kind
+    (3, 70, 32, (128, 1024, 256, 10)), (5, 52, 64, (384, 1024, 128, 10)), (4, 30, 96, (256, 1024, 384, 10)), (9, 30, 128, (1280, 1024, 128, 40)),
+    # a general layer below and above; the last layer's own kernel
+    (3, 70, 32, (60, 1024, 128, 100, 10)), (3, 30, 96, (100, 128, 1024, 10)),
+    # layers of any width in one chain: whole steps and what is behind them, rows and columns that fill no block
+    (16, 18, 100, (784, 500, 10)), (16, 18, 65, (649, 497, 10)), (32, 34, 60, (672, 500, 10)), (32, 34, 33, (641, 511, 10)),
+])
+def test_few_blocks_bit_for_bit(few, many, batch, dims):
+    """bfloat16 layers in few blocks have kernels of their own, which add in the order of those for many: a worker's gradient is the same among few
+    workers and among many."""
+    runs = []
+    for M in (few, many):
+        w = workload("cfg5", M=M, batch=batch, n_per_worker=batch + 7, dims=dims)
+        gpu = make_gpu(w, inputs_of(w))
+        for it in (0, 3):
+            gpu.local_step(it)
+        runs.append([gpu.hidden(l)[:few].cpu().numpy() for l in range(1, len(dims) - 1)] + [gpu.get("g")[:few].cpu().numpy()])
+        gpu.close()
+    for a, b in zip(*runs):
+        assert np.array_equal(a, b)
+
+
 def test_wide_fp32_layers_keep_what_is_not_finite():
     """Large fp32 layers multiply bfloat16 planes of their operands, which an infinity, or a number that rounds to one, does not
     survive: such blocks are computed again in fp32.  Activations against float64, block edges included."""
