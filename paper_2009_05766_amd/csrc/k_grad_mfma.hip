@@ -624,82 +624,151 @@ __global__ void __launch_bounds__(MF_THREADS) __attribute__((amdgpu_waves_per_eu
 }
 
 // ---------------------------------------------------------------------------------------------------
-// Weight gradient with the second-step update applied in place of the store: one workgroup = one worker and one
-// 64-row x 128-column block of W.  The product dW = A^T dZ of the block is computed as above, turned through LDS
-// into rows, and every thread then updates four neighbouring parameters: v' = mu v + dW + wd x, h = x - alpha v',
-// x' = h - w (h - x_peer) (Eq. (c0), (c1)) with 128-bit loads and stores.  The gradient never goes to memory.
+// Weight gradient with the second-step update applied in place of the store, or beside it (KEEP_G): one workgroup = one worker and
+// 128 columns of W, along which it walks in strips of 32 rows.  The product dW = A^T dZ of a strip is computed as above (the same
+// steps in the same order), turned through LDS into rows, and every thread then updates four neighbouring parameters per row:
+// v' = mu v + dW + wd x, h = x - alpha v', x' = h - w (h - x_peer) (Eq. (c0), (c1)) with 128-bit loads and stores.
 // Workgroups are ordered block by block: all M workers of a block run side by side on one XCD (as the mix kernel
-// orders its tiles), so the block a worker pulls from its peer is in that XCD's L2.
+// orders its tiles), so the strip a worker pulls from its peer is in that XCD's L2.
+// Bound by memory: x, v, x', v' and the operands that are read again for every block.  The dZ^T block stays in LDS for the whole walk, A^T's
+// next strip and x, v and the peer's x travel while the present one is multiplied.  3072-1024 and 1024-1024, batch 128, 48
+// workers: 476 and 143 us (5.1 and 5.6 TB/s of the 16 bytes a parameter); with one block of 64 x 128 per workgroup, its operands
+// loaded, multiplied and then x, v and the peer's x asked for, 725 us together.  Without products and operands it would take 460 and 133,
+// whatever the number of workgroups per compute unit (one to three) and the height of a strip (32, 64, 128 rows: the same within 3 %).
 struct WgradMixArgs {
-    const uint16_t *a_t, *dz_t; int M, B; int64_t din, dout, woff;
+    const uint16_t *a_t, *dz_t; int M, B; int64_t din, dout, woff; unsigned walk, apart; float *G;
     MixArgs mix;
     const uint16_t *feats; const int64_t *row0; const int32_t *idx;      // first layer: A^T is gathered from the data rows
 };
-constexpr int WM_ROWS = 64, WM_COLS = 128;
+constexpr int WM_ROWS = 32, WM_COLS = 128;
 constexpr int WM_TILE_PITCH = WM_COLS + 4;           // floats per staged row
 
+template <bool GATHERED, bool KEEP_G>
 __global__ void __launch_bounds__(MF_THREADS) __attribute__((amdgpu_waves_per_eu(3, 3))) wgrad_mix_mfma_kernel(WgradMixArgs p)
 {
-    constexpr int OPERAND_BYTES = (WM_ROWS + WM_COLS) * WG_PITCH * 2, TILE_BYTES = WM_ROWS * WM_TILE_PITCH * 4;
-    __shared__ __attribute__((aligned(16))) unsigned char smem[OPERAND_BYTES > TILE_BYTES ? OPERAND_BYTES : TILE_BYTES];
+    constexpr int STAGE = WM_ROWS * WM_TILE_PITCH * 4;
+    static_assert(STAGE >= WM_ROWS * WG_PITCH * 2, "A's strip lies where the staged block will");
+    __shared__ __attribute__((aligned(16))) uint16_t Zt[WM_COLS][WG_PITCH];
+    __shared__ __attribute__((aligned(16))) unsigned char smem[STAGE];
     uint16_t (*At)[WG_PITCH] = reinterpret_cast<uint16_t (*)[WG_PITCH]>(smem);
-    uint16_t (*Zt)[WG_PITCH] = reinterpret_cast<uint16_t (*)[WG_PITCH]>(smem + WM_ROWS * WG_PITCH * 2);
     float (*T)[WM_TILE_PITCH] = reinterpret_cast<float (*)[WM_TILE_PITCH]>(smem);
-    const int t = threadIdx.x, lane = t & 63, wave = t >> 6, wm = wave >> 1, wn = wave & 1;
-    // workgroup id -> (block, worker): ids are dealt round-robin to the XCDs; a block's workers are consecutive slots
-    const unsigned nbx = (unsigned)(p.dout / WM_COLS), blocks = nbx * (unsigned)(p.din / WM_ROWS);
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    // workgroup id -> (columns and strips, worker): ids are dealt round-robin to the XCDs; a block's workers are consecutive slots
+    const unsigned nbx = (unsigned)(p.dout / WM_COLS), strips = (unsigned)(p.din / WM_ROWS), walks = (strips + p.walk - 1) / p.walk;
     const unsigned xcd = blockIdx.x % MF_XCD, slot = blockIdx.x / MF_XCD;
     const unsigned blk = (slot / (unsigned)p.M) * MF_XCD + xcd;
     const int g = (int)(slot % (unsigned)p.M);
-    if (blk >= blocks) return;
-    const int64_t r0 = (int64_t)(blk / nbx) * WM_ROWS, n0 = (int64_t)(blk % nbx) * WM_COLS;
+    if (blk >= nbx * walks) return;
+    const unsigned first = blk / nbx * p.walk, n = min(p.walk, strips - first);
+    const int64_t r0 = (int64_t)first * WM_ROWS, n0 = (int64_t)(blk % nbx) * WM_COLS;
     const int chunks_per_row = p.B >> 3;
     const uint16_t *z_src = p.dz_t + ((size_t)g * p.dout + n0) * p.B;
-    load_at_block<WM_ROWS>(At, t, g, p.B, p.din, r0, p.a_t, p.feats, p.row0, p.idx);
-#pragma unroll
-    for (int q = 0; q < WM_COLS * 16 / MF_THREADS; ++q) {
-        const int c = t + q * MF_THREADS, row = c / chunks_per_row, col = (c - row * chunks_per_row) * 8;
-        if (c < WM_COLS * chunks_per_row)
-            *reinterpret_cast<u32x4 *>(&Zt[row][col]) = *reinterpret_cast<const u32x4 *>(z_src + (size_t)row * p.B + col);
-    }
-    __syncthreads();
-    f32x16 acc[2];
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[j][v] = 0.0f;
-    for (int b0 = 0; b0 < p.B; b0 += 16) {
-        const int kofs = b0 + 8 * (lane >> 5);
-        const u32x4 a = *reinterpret_cast<const u32x4 *>(&At[32 * wm + (lane & 31)][kofs]);
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-            acc[j] = mfma_bf16(a, *reinterpret_cast<const u32x4 *>(&Zt[64 * wn + 32 * j + (lane & 31)][kofs]), acc[j]);
-    }
-    __syncthreads();                 // the operand tiles are read; their space becomes the staging tile
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) T[32 * wm + d_row(lane, v)][64 * wn + 32 * j + (lane & 31)] = acc[j][v];
-    __syncthreads();
 
+    // A's strip: two pieces of eight elements per thread, of a row of A^T, or of a data row (neighbouring lanes then take neighbouring
+    // batch rows).  Pieces past the end are read from the last one's place and not stored.
+    constexpr int AN = WM_ROWS * 16 / MF_THREADS;
+    const int a_chunks = WM_ROWS * chunks_per_row;
+    const uint16_t *a_src[AN];
+    int a_row[AN], a_col[AN];
+#pragma unroll
+    for (int q = 0; q < AN; ++q) {
+        const int c = min(t + q * MF_THREADS, a_chunks - 1);
+        if constexpr (GATHERED) {
+            a_row[q] = c / p.B * 8;
+            a_col[q] = c % p.B;
+            a_src[q] = p.feats + (size_t)(p.row0[g] + p.idx[(size_t)g * p.B + a_col[q]]) * p.din + r0 + a_row[q];
+        } else {
+            a_row[q] = c / chunks_per_row;
+            a_col[q] = c % chunks_per_row * 8;
+            a_src[q] = p.a_t + ((size_t)g * p.din + r0 + a_row[q]) * p.B + a_col[q];
+        }
+    }
+    const size_t a_step = GATHERED ? WM_ROWS : (size_t)WM_ROWS * p.B;
+    u32x4 ra[AN];
+    auto fetch_a = [&](unsigned k) {
+#pragma unroll
+        for (int q = 0; q < AN; ++q) ra[q] = *reinterpret_cast<const u32x4 *>(a_src[q] + k * a_step);
+    };
+    unsigned at = p.apart ? (unsigned)g / p.apart % n : 0;           // where this worker's walk begins; it goes on from the first strip
+    auto stash_a = [&]() {
+#pragma unroll
+        for (int q = 0; q < AN; ++q) {
+            if (t + q * MF_THREADS >= a_chunks) continue;
+            if constexpr (GATHERED) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    At[a_row[q] + 2 * e][a_col[q]] = (uint16_t)(ra[q][e] & 0xFFFFu);
+                    At[a_row[q] + 2 * e + 1][a_col[q]] = (uint16_t)(ra[q][e] >> 16);
+                }
+            } else {
+                *reinterpret_cast<u32x4 *>(&At[a_row[q]][a_col[q]]) = ra[q];
+            }
+        }
+    };
+    fetch_a(at);
+    {
+        constexpr int ZN = WM_COLS * 16 / MF_THREADS;
+        const int z_chunks = WM_COLS * chunks_per_row;
+        u32x4 rz[ZN];
+#pragma unroll
+        for (int q = 0; q < ZN; ++q) {
+            const int c = min(t + q * MF_THREADS, z_chunks - 1);
+            rz[q] = *reinterpret_cast<const u32x4 *>(z_src + 8 * (size_t)c);
+        }
+#pragma unroll
+        for (int q = 0; q < ZN; ++q) {
+            const int c = t + q * MF_THREADS;
+            if (c < z_chunks) *reinterpret_cast<u32x4 *>(&Zt[c / chunks_per_row][c % chunks_per_row * 8]) = rz[q];
+        }
+    }
     const MixArgs &mx = p.mix;
     int m = mx.peer[g];
-    if ((unsigned)m >= (unsigned)p.M) m = g;
+    if ((unsigned)m >= (unsigned)p.M) m = g;             // an index outside [0, M) is treated as a self draw
     const float wi = mx.w[(size_t)g * p.M + m];
+    const int64_t peer_shift = ((int64_t)m - g) * TILE;
+    constexpr int PASSES = WM_ROWS / 8;
     const int cq = (t & 31) * 4, r_in = t >> 5;          // 32 lanes along the 128 columns, 8 rows per pass
-#pragma unroll 2
-    for (int pass = 0; pass < WM_ROWS / 8; ++pass) {
-        const int row = pass * 8 + r_in;
-        const int64_t j = p.woff + (r0 + row) * p.dout + n0 + cq;
-        const size_t own = tiled_offset_fast(p.M, g, j), other = tiled_offset_fast(p.M, m, j);
-        const f32x4_t x = *reinterpret_cast<const f32x4_t *>(mx.Xcur + own);
-        const f32x4_t xp = *reinterpret_cast<const f32x4_t *>(mx.Xcur + other);
-        const f32x4_t v = __builtin_nontemporal_load(reinterpret_cast<const f32x4_t *>(mx.V + own));
-        const f32x4_t gr = *reinterpret_cast<const f32x4_t *>(&T[row][cq]);
-        f32x4_t xn, vn;
-        momentum_mix4(x, v, gr, xp, wi, mx.alpha, mx.mu, mx.wd, xn, vn);
-        __builtin_nontemporal_store(xn, reinterpret_cast<f32x4_t *>(mx.Xnext + own));
-        __builtin_nontemporal_store(vn, reinterpret_cast<f32x4_t *>(mx.V + own));
+    const int64_t jb = p.woff + (r0 + r_in) * p.dout + n0 + cq;
+
+    for (unsigned s = 0; s < n; ++s) {
+        size_t own[PASSES];
+        f32x4_t x[PASSES], v[PASSES], xp[PASSES];
+        const int64_t j0 = jb + (int64_t)at * WM_ROWS * p.dout;
+        stash_a();
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < PASSES; ++u) {
+            own[u] = tiled_offset_fast(p.M, g, j0 + (int64_t)(8 * u) * p.dout);
+            x[u] = *reinterpret_cast<const f32x4_t *>(mx.Xcur + own[u]);
+            v[u] = __builtin_nontemporal_load(reinterpret_cast<const f32x4_t *>(mx.V + own[u]));
+        }
+#pragma unroll
+        for (int u = 0; u < PASSES; ++u) xp[u] = *reinterpret_cast<const f32x4_t *>(mx.Xcur + own[u] + peer_shift);
+        at = at + 1 < n ? at + 1 : 0;
+        if (s + 1 < n) fetch_a(at);
+        __builtin_amdgcn_sched_barrier(0);
+        f32x16 acc;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[e] = 0.0f;
+        for (int b0 = 0; b0 < p.B; b0 += 16) {
+            const int kofs = b0 + 8 * (lane >> 5);
+            const u32x4 a = *reinterpret_cast<const u32x4 *>(&At[lane & 31][kofs]);
+            acc = mfma_bf16(a, *reinterpret_cast<const u32x4 *>(&Zt[32 * wave + (lane & 31)][kofs]), acc);
+        }
+        __syncthreads();                                  // the strip is read; its space becomes the staged block
+#pragma unroll
+        for (int e = 0; e < 16; ++e) T[d_row(lane, e)][32 * wave + (lane & 31)] = acc[e];
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < PASSES; ++u) {
+            const f32x4_t gr = *reinterpret_cast<const f32x4_t *>(&T[8 * u + r_in][cq]);
+            f32x4_t xn, vn;
+            momentum_mix4(x[u], v[u], gr, xp[u], wi, mx.alpha, mx.mu, mx.wd, xn, vn);
+            if constexpr (KEEP_G) __builtin_nontemporal_store(gr, reinterpret_cast<f32x4_t *>(p.G + own[u]));
+            __builtin_nontemporal_store(xn, reinterpret_cast<f32x4_t *>(mx.Xnext + own[u]));
+            __builtin_nontemporal_store(vn, reinterpret_cast<f32x4_t *>(mx.V + own[u]));
+        }
+        __syncthreads();                                  // the staged block is read; the next strip takes its place
     }
 }
 
@@ -968,15 +1037,34 @@ void launch_dgrad_mfma(hipStream_t s, const MlpPlan &p, int l, const float *X, f
     hipLaunchKernelGGL(dgrad_mfma_kernel, dim3(grouped_grid(p.M, (unsigned)(a.din / MF_BN))), dim3(MF_THREADS), 0, s, a);
 }
 
-void launch_wgrad_mix_mfma(hipStream_t s, const MlpPlan &p, int l, int cur, const MixArgs &mix)
+void launch_wgrad_mix_mfma(hipStream_t s, const MlpPlan &p, int l, float *G, int cur, const MixArgs &mix)
 {
     WgradMixArgs a;
     a.a_t = p.ht[l]; a.dz_t = p.dzt[cur]; a.M = p.M; a.B = p.B; a.din = p.dims[l]; a.dout = p.dims[l + 1];
-    a.woff = p.woff[l]; a.mix = mix;
+    a.woff = p.woff[l]; a.G = G; a.mix = mix;
     a.feats = l == 0 ? (const uint16_t *)p.feats : nullptr; a.row0 = p.row0; a.idx = p.idx;
-    const unsigned blocks = (unsigned)((a.din / WM_ROWS) * (a.dout / WM_COLS));
-    const unsigned grid = (blocks + MF_XCD - 1) / MF_XCD * MF_XCD * (unsigned)p.M;
-    hipLaunchKernelGGL(wgrad_mix_mfma_kernel, dim3(grid), dim3(MF_THREADS), 0, s, a);
+    const unsigned strips = (unsigned)(a.din / WM_ROWS), cols = (unsigned)(a.dout / WM_COLS);
+    // Up to eight strips a walk where dZ^T is large beside the strip's 64 KB of x, v, x' and v' (32 KB at a batch of 128), the XCDs
+    // have the same number of blocks and the compute units two walks each.  us per iteration with eight strips and with one: batch 128,
+    // 128 workers 3072-1024-1024 2527 and 2977, 48 workers 919 and 946, 64 workers 512-512 (512 walks) 138 and 145, but 4 workers
+    // 2944-896-640 (336 and 140 walks) 674 and 617, 100 workers 512-256 (four blocks) 157 and 131, with four strips 127; batch 64, 64
+    // workers 1024-512 370 and 372; batch 32, 61 workers 2304-640 783 and 740.
+    auto blocks_of = [&](unsigned walk) { return (strips + walk - 1) / walk * cols; };
+    a.walk = p.B > 64 ? 8 : 1;
+    while (a.walk > 1 && ((blocks_of(a.walk) % MF_XCD != 0 && blocks_of(a.walk) < 8 * MF_XCD) || (uint64_t)p.M * blocks_of(a.walk) < 2 * 256)) a.walk /= 2;
+    // A tile of the layout is 8 KB of every worker.  At a multiple of 512 KB from tile to tile the workers, strip by strip in step, fall
+    // on few of the memory's channels: eight workers at a time begin their walk a strip further on.  64 workers 3072-1024-1024 1341 and
+    // 1237 us, 128 workers 2527 and 2495; 32 and 48 workers would lose 2 to 10 % (the peer's strip is no longer in the L2).
+    a.apart = p.M % 64 == 0 ? 8 : 0;
+    const unsigned blocks = blocks_of(a.walk);
+    const dim3 grid((blocks + MF_XCD - 1) / MF_XCD * MF_XCD * (unsigned)p.M), block(MF_THREADS);
+    if (l == 0) {
+        if (mix.keep_g) hipLaunchKernelGGL((wgrad_mix_mfma_kernel<true, true>), grid, block, 0, s, a);
+        else hipLaunchKernelGGL((wgrad_mix_mfma_kernel<true, false>), grid, block, 0, s, a);
+    } else {
+        if (mix.keep_g) hipLaunchKernelGGL((wgrad_mix_mfma_kernel<false, true>), grid, block, 0, s, a);
+        else hipLaunchKernelGGL((wgrad_mix_mfma_kernel<false, false>), grid, block, 0, s, a);
+    }
 }
 
 void launch_wgrad_mfma(hipStream_t s, const MlpPlan &p, int l, float *G, int cur)

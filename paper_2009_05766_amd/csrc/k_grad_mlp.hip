@@ -194,8 +194,11 @@ bias_grad_kernel(int M, int B, int64_t dout, const float *__restrict__ dz, int64
 // left, if that does save the launch: 256-256-10, 8 workers, batch 32 27.0 us with the mix and 23.0 us, 784-512-10, 4 workers
 // 45.0 and 39.6 us; every layer for itself lengthens the chain (300-60-60-60-10, 8 workers 64.7 and 66.5 us).
 // Where it loses: rows of W that do not start at multiples of 16 bytes (3001-999-10: 1118 and 1519 us); bfloat16 operands, whose
-// products leave little to hide (784-500-300-10, 16 workers 106 and 113 us, 3000-1000-10, 128 workers 2354 and 2644 us; the
-// matrix-core layers likewise).
+// products leave little to hide (784-500-300-10, 16 workers 106 and 113 us, 3000-1000-10, 128 workers 2354 and 2644 us).  The
+// matrix-core layers have a kernel in the mix's order for it: batch 128, 3072-1024-1024-10, 48 workers 1159 and 1070 us, 128 workers
+// 2826 and 2816 us (two iterations 5821 and 5336 us: the first need not write g); batch 64, 1024-1024-10, 32 workers 2 x 221 and
+// 2 x 181 us, 512-512-256-10, 16 workers 2 x 88 and 2 x 81 us, 1024-512-10, 4 workers (2.1 M floats) 2 x 68 and 2 x 63 us, but
+// 512-128-128-10, 2 workers 4 x 57.5 and 4 x 60 us.
 constexpr int64_t UPDATE_MIN_FLOATS = 7 << 18;       // M x ld
 static bool first_layer_last(const MlpPlan &p) { return p.n_layers == 1 || (p.n_layers == 2 && head_ok(p)) || p.B <= TILE_DGRAD_BATCH; }
 
@@ -203,6 +206,7 @@ int64_t update_end(const MlpPlan &p, int l)
 {
     const bool head = head_ok(p);
     if (p.n_layers == 1 && head) return p.ld;                        // the last-layer kernel updates everything
+    if (mfma_layer_ok(p, l)) return p.M * p.ld < UPDATE_MIN_FLOATS ? 0 : p.woff[l] + p.dims[l] * p.dims[l + 1];
     if (p.bf16 || (l == p.n_layers - 1 && head) || p.woff[l] % 4 != 0) return 0;
     if (p.M * p.ld < UPDATE_MIN_FLOATS && (l > 0 || !first_layer_last(p))) return 0;
     if (!wgrad_f32_ok(p, l) && !tile_wgrad_update_ok(p, l)) return 0;
@@ -287,10 +291,11 @@ bool launch_mlp_grad(hipStream_t s, const MlpPlan &p, const float *X, float *G, 
     // backward
     for (int l = l_top; l >= 0; --l) {
         const int64_t din = p.dims[l], dout = p.dims[l + 1];
-        const bool others = l == 0 && bias_done[0] && tail_of(0) != nullptr;       // the last launch: it can update what is left
+        const bool others = l == 0 && !fast[0] && bias_done[0] && tail_of(0) != nullptr;       // the last launch: it can update what is left
         all_updated |= others;
         if (fast[l]) {
-            if (fuse) launch_wgrad_mix_mfma(s, p, l, cur, *fuse);
+            if (fuse) launch_wgrad_mix_mfma(s, p, l, G, cur, *fuse);
+            else if (const TailArgs *u = tail_of(l)) launch_wgrad_mix_mfma(s, p, l, G, cur, u->mix);
             else launch_wgrad_mfma(s, p, l, G, cur);
         } else if (l == L - 1 && small_last) {
             launch_wgrad_small(s, p, G, cur);

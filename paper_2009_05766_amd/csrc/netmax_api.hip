@@ -696,7 +696,7 @@ static int enqueue_local_step(netmax_ctx *ctx, const IterRef &iter, const int32_
     if (!drawn) launch_sample_batch(ctx->stream, c.M, c.batch, ctx->d_nrows, c.seed, iter, ctx->d_idx);
     MlpPlan p = make_plan(ctx);
     if (drawn) p.idx = drawn;
-    const TailArgs tail{mix_args(ctx, run_peers, keep_g), ctx->d_tail_tiles, ctx->n_tail_tiles, ctx->tail_skip};
+    const TailArgs tail{mix_args(ctx, run_peers, keep_g && !ctx->fuse), ctx->d_tail_tiles, ctx->n_tail_tiles, ctx->tail_skip};
     const bool done = launch_mlp_grad(ctx->stream, p, ctx->x_cur, ctx->g, run_peers && ctx->fuse ? &tail.mix : nullptr,
                                       run_peers && ctx->tail && !ctx->fuse ? &tail : nullptr);
     if (updated) *updated = done;

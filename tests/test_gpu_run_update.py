@@ -4,6 +4,7 @@ import numpy as np
 import pytest
 import torch
 
+import paper_2009_05766_amd as nm
 from harness import inputs_of, make_gpu
 from netmax_inputs import workload
 
@@ -61,6 +62,27 @@ def test_run_is_the_separate_calls(name, M, batch, dims, graph):
 ])
 def test_run_with_narrow_layers(name, M, batch, dims):
     test_run_is_the_separate_calls(name, M, batch, dims, False)
+
+
+@pytest.mark.parametrize("M,batch,dims", [
+    # two million floats, from which on the matrix-core layers update their columns: either side, one strip of 32 rows a walk
+    (6, 32, (512, 512, 128, 10)), (5, 32, (512, 512, 128, 10)), (13, 64, (130, 256, 384, 10)), (7, 128, (384, 640, 128)),
+    # walks of eight strips, whole and with four left over, from the first strip and from a later one
+    (48, 128, (1024, 1024, 10)), (49, 96, (1152, 896, 10)), (64, 96, (1152, 896, 128, 10)), (128, 128, (128, 896, 640, 10)),
+])
+@pytest.mark.parametrize("fused", [False, True])
+def test_run_of_matrix_core_layers(M, batch, dims, fused):
+    if not fused:
+        return test_run_is_the_separate_calls("cfg5", M, batch, dims, False)
+    w = workload("cfg5", M=M, batch=batch, n_per_worker=batch + 3, dims=dims)
+    inp = inputs_of(w)
+    run, calls = (make_gpu(w, inp, momentum=0.9, weight_decay=1e-4) for _ in range(2))
+    nm.netmax_set_fusion(run.ctx, True)
+    run.run(0, 3)
+    for k in range(3):
+        calls.step(k)
+    assert torch.equal(run.get("x"), calls.get("x")) and torch.equal(run.v, calls.v) and torch.equal(run.losses(), calls.losses())
+    run.close(), calls.close()
 
 
 @pytest.mark.parametrize("name,over", [("cfg2", dict(M=5, batch=24, n_per_worker=40, dims=(30, 20, 10))), ("cfg3", dict(M=7, D=5000)),
