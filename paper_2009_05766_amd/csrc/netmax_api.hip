@@ -680,6 +680,16 @@ static int enqueue_small(netmax_ctx *ctx, const IterRef &iter, int n_iters, bool
     return NETMAX_OK;
 }
 
+// Whether the weight gradients of this iteration of netmax_run apply the update.  Those of the matrix-core layers don't where they
+// would write the gradient as well and an XCD doesn't hold all workers of a block at a time (96), so that a good part of the peers' columns
+// come from memory: 3072-1024-1024-10, batch 128, 128 workers 2847 us with the separate mix and 2810 to 2900 us; 112 workers
+// still 2550 and 2430 us.
+static bool update_in_gradients(const netmax_ctx *ctx, bool keep_g)
+{
+    const netmax_config &c = ctx->cfg;
+    return ctx->tail && !ctx->fuse && !(keep_g && c.gemm_in == NETMAX_BF16 && c.n_layers > 1 && c.M >= 128);
+}
+
 // run_peers != nullptr (netmax_run): weight-gradient kernels apply the update where the context has it so; *updated: to all
 // columns, else enqueue_run_mix covers the remaining ones.
 // drawn: the batch rows of this iteration if they have been drawn already.
@@ -698,7 +708,7 @@ static int enqueue_local_step(netmax_ctx *ctx, const IterRef &iter, const int32_
     if (drawn) p.idx = drawn;
     const TailArgs tail{mix_args(ctx, run_peers, keep_g && !ctx->fuse), ctx->d_tail_tiles, ctx->n_tail_tiles, ctx->tail_skip};
     const bool done = launch_mlp_grad(ctx->stream, p, ctx->x_cur, ctx->g, run_peers && ctx->fuse ? &tail.mix : nullptr,
-                                      run_peers && ctx->tail && !ctx->fuse ? &tail : nullptr);
+                                      run_peers && update_in_gradients(ctx, keep_g) ? &tail : nullptr);
     if (updated) *updated = done;
     return check_launch(ctx, "mlp_grad");
 }
@@ -723,7 +733,7 @@ static int enqueue_mix(netmax_ctx *ctx, const int32_t *peers_dev)
 }
 
 // The update inside netmax_run: of what the gradient's kernels have left.
-static int enqueue_run_mix(netmax_ctx *ctx, const int32_t *peers_dev, const IterRef &iter)
+static int enqueue_run_mix(netmax_ctx *ctx, const int32_t *peers_dev, const IterRef &iter, bool keep_g)
 {
     const netmax_config &c = ctx->cfg;
     if (ctx->fuse && c.model == NETMAX_FLAT)
@@ -731,7 +741,7 @@ static int enqueue_run_mix(netmax_ctx *ctx, const int32_t *peers_dev, const Iter
                          c.momentum, c.weight_decay, c.grad_sigma, c.seed, iter);
     else if (ctx->fuse)
         launch_mix_subset(ctx->stream, c.M, ctx->d_fuse_tiles, ctx->n_fuse_tiles, ctx->fuse_skip, ctx->g, mix_args(ctx, peers_dev));
-    else if (ctx->tail)
+    else if (update_in_gradients(ctx, keep_g))
         launch_mix_subset(ctx->stream, c.M, ctx->d_tail_tiles, ctx->n_tail_tiles, ctx->tail_skip, ctx->g, mix_args(ctx, peers_dev));
     else
         return enqueue_mix(ctx, peers_dev);
@@ -743,7 +753,7 @@ static int enqueue_run_iteration(netmax_ctx *ctx, const IterRef &iter, const int
 {
     bool updated = false;
     const int rc = enqueue_local_step(ctx, iter, peers, drawn, &updated, keep_g);
-    return rc != NETMAX_OK || updated ? rc : enqueue_run_mix(ctx, peers, iter);
+    return rc != NETMAX_OK || updated ? rc : enqueue_run_mix(ctx, peers, iter, keep_g);
 }
 
 static void flip(netmax_ctx *ctx)
