@@ -778,18 +778,40 @@ __global__ void __launch_bounds__(MF_THREADS) __attribute__((amdgpu_waves_per_eu
 // reading / writing the [B][din] activations and errors.
 
 // logits = A W + b.  One workgroup per worker; W^T goes to LDS as bf16 [32][din], each wave takes 32
-// batch rows and reads its A operands straight from the bf16 activations.
+// batch rows.  One compute unit pulls a worker's 256 KB of activations (1024 features, batch 128): bound by how much of them is on
+// the way.  A wave asks for four pieces of 64 features ahead, the first ones before W is turned, as lines of 128 bytes by eight lanes
+// (a lane per row asks for 64 lines an instruction), and turns them to the matrix instruction's layout in LDS of its own.  The logits
+// stay in LDS for the softmax, whose chain of loads from memory was the other half.  us, before, with the pieces, and with both:
+// 1024-10, batch 128, 48 workers 26.5, 22.9, 18.7; 2048-10, 4 workers 33.6, 25.7, 23.0; 128-30, batch 96, 8 workers 22.1, 21.7, 12.2; 640-10,
+// batch 32, 61 workers 16.7, 16.2, 14.2.
 struct FwdSmallArgs {
     const uint16_t *a_prev; const float *X; int64_t woff; int M, B; int64_t din, dout; float *out;
     SoftmaxArgs sm;                  // what follows the logits in the same workgroup
 };
 constexpr int SMALL_MAX_DIN = 2048;
+// W^T and the waves' pieces; then the logits
+static_assert(2 * (32 * (128 + 8) + MF_THREADS / 64 * 32 * (64 + 8)) >= 4 * 128 * SOFTMAX_PITCH, "the logits of the largest batch fit the space of the smallest layer");
+constexpr int FS_KS = 64, FS_PITCH = FS_KS + 8, FS_DEPTH = 4;           // features of a piece, elements of its rows in LDS, pieces ahead
+static size_t fwd_small_lds(int64_t din) { return sizeof(uint16_t) * (32 * (size_t)(din + 8) + MF_THREADS / 64 * 32 * FS_PITCH); }
 
 __global__ void __launch_bounds__(MF_THREADS) fwd_small_mfma_kernel(FwdSmallArgs p)
 {
     extern __shared__ __attribute__((aligned(16))) uint16_t Wt[];      // [32][din + 8]
     const int g = blockIdx.x, t = threadIdx.x, lane = t & 63, wave = t >> 6;
     const int din = (int)p.din, dout = (int)p.dout, pitch = din + 8;
+    static_assert(MF_THREADS / 64 * 32 >= 128, "a wave for every 32 rows of the largest batch");
+    const int m0 = 32 * wave, pieces = din / FS_KS;                    // din is a multiple of 128: at least two pieces
+    const bool mine = m0 < p.B;
+    const int label = softmax_label(p.sm, g);
+    const uint16_t *a_src = p.a_prev + ((size_t)g * p.B + (mine ? m0 : 0) + (lane >> 3)) * p.din + 8 * (lane & 7);
+    u32x4 ra[FS_DEPTH][4];
+    auto request = [&](int d, int k) {                                 // past the end: the last piece again, never used
+        const uint16_t *src = a_src + (k < pieces ? k : pieces - 1) * FS_KS;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) ra[d][u] = *reinterpret_cast<const u32x4 *>(src + (size_t)(8 * u) * p.din);
+    };
+#pragma unroll
+    for (int d = 0; d < FS_DEPTH; ++d) request(d, d);
     // rows dout .. 31 of Wt are the zero padding of the class dimension
     for (int e = t + dout * pitch / 2; e < 32 * pitch / 2; e += MF_THREADS) reinterpret_cast<uint32_t *>(Wt)[e] = 0u;
     // W[k][n] -> Wt[n][k]: the din x dout block is contiguous in the parameter row and starts at a multiple of four
@@ -819,32 +841,49 @@ __global__ void __launch_bounds__(MF_THREADS) fwd_small_mfma_kernel(FwdSmallArgs
         }
     }
     __syncthreads();
-    for (int m0 = 32 * wave; m0 < p.B; m0 += 32 * (MF_THREADS / 64)) {
-        const uint16_t *a_ptr = p.a_prev + ((size_t)g * p.B + m0 + (lane & 31)) * p.din + 8 * (lane >> 5);
-        const uint16_t *b_ptr = Wt + (lane & 31) * pitch + 8 * (lane >> 5);
-        f32x16 acc;
+    f32x16 acc;
 #pragma unroll
-        for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
-        // din is a multiple of 128: eight steps of loads are issued before their matrix instructions
-        for (int k0 = 0; k0 < din; k0 += 128) {
-            u32x4 a[8];
+    for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
+    const int col = lane & 31;
+    const float bcol = p.X[tiled_offset(p.M, g, p.woff + (int64_t)din * dout + (col < dout ? col : dout - 1))];
+    if (mine) {
+        uint16_t *own = Wt + 32 * pitch + wave * 32 * FS_PITCH, *to = own + (lane >> 3) * FS_PITCH + 8 * (lane & 7);
+        const uint16_t *a_ptr = own + (lane & 31) * FS_PITCH + 8 * (lane >> 5), *b_ptr = Wt + (lane & 31) * pitch + 8 * (lane >> 5);
+        auto consume = [&](int d, int k) {
 #pragma unroll
-            for (int s = 0; s < 8; ++s) a[s] = *reinterpret_cast<const u32x4 *>(a_ptr + k0 + 16 * s);
-            __builtin_amdgcn_sched_barrier(0);             // or the loads are interleaved with the instructions that wait for them
+            for (int u = 0; u < 4; ++u) *reinterpret_cast<u32x4 *>(to + 8 * u * FS_PITCH) = ra[d][u];
+            __builtin_amdgcn_wave_barrier();
 #pragma unroll
-            for (int s = 0; s < 8; ++s) acc = mfma_bf16(a[s], *reinterpret_cast<const u32x4 *>(b_ptr + k0 + 16 * s), acc);
-            __builtin_amdgcn_sched_barrier(0);
+            for (int s = 0; s < FS_KS / 16; ++s)
+                acc = mfma_bf16(*reinterpret_cast<const u32x4 *>(a_ptr + 16 * s), *reinterpret_cast<const u32x4 *>(b_ptr + k * FS_KS + 16 * s), acc);
+            __builtin_amdgcn_wave_barrier();
+        };
+        int k = 0;
+        for (; k + FS_DEPTH <= pieces; k += FS_DEPTH) {
+#pragma unroll
+            for (int d = 0; d < FS_DEPTH; ++d) {
+                consume(d, k + d);
+                request(d, k + d + FS_DEPTH);
+            }
         }
-        const int col = lane & 31;
-        if (col < dout) {
-            const float bcol = p.X[tiled_offset(p.M, g, p.woff + (int64_t)din * dout + col)];
 #pragma unroll
-            for (int v = 0; v < 16; ++v) p.out[((size_t)g * p.B + m0 + d_row(lane, v)) * p.dout + col] = acc[v] + bcol;
-        }
+        for (int d = 0; d < FS_DEPTH - 1; ++d)
+            if (k + d < pieces) consume(d, k + d);
     }
     // the workgroup holds all logits of its worker: loss, dZ and the last layer's bias gradient follow at once
+    __syncthreads();                                                   // W has been read; the logits take its place
+    float *rows = reinterpret_cast<float *>(Wt);
+    if (mine) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const int row = m0 + d_row(lane, v);
+            const float z = acc[v] + bcol;
+            rows[row * SOFTMAX_PITCH + col] = z;
+            if (col < dout) p.out[((size_t)g * p.B + row) * p.dout + col] = z;
+        }
+    }
     __syncthreads();
-    softmax_xent_block(p.sm, g);
+    softmax_xent_block<32>(p.sm, g, label, rows);
 }
 
 // dW = A^T dZ with dout <= 32: one workgroup = one worker x 128 rows of W, one 32-row tile per wave;
@@ -977,7 +1016,7 @@ void prepare_kernels()
 
     // fwd_small_mfma_kernel keeps W^T in more than the default 64 KB of dynamic LDS
     (void)hipFuncSetAttribute(reinterpret_cast<const void *>(fwd_small_mfma_kernel),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, 32 * (SMALL_MAX_DIN + 8) * 2);
+                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)fwd_small_lds(SMALL_MAX_DIN));
 }
 
 // Outputs of the backward-data kernel of layer l: the error of layer l - 1 and that layer's bias gradient.
@@ -996,8 +1035,7 @@ void launch_fwd_small(hipStream_t s, const MlpPlan &p, const float *X, float *G)
     a.a_prev = p.hb[l]; a.X = X; a.woff = p.woff[l]; a.M = p.M; a.B = p.B; a.din = p.dims[l]; a.dout = p.dims[l + 1];
     a.out = p.act[l + 1];
     a.sm = softmax_args(p, G);
-    const size_t lds = (size_t)32 * (a.din + 8) * sizeof(uint16_t);
-    hipLaunchKernelGGL(fwd_small_mfma_kernel, dim3(p.M), dim3(MF_THREADS), lds, s, a);
+    hipLaunchKernelGGL(fwd_small_mfma_kernel, dim3(p.M), dim3(MF_THREADS), fwd_small_lds(a.din), s, a);
 }
 
 void launch_wgrad_small(hipStream_t s, const MlpPlan &p, float *G, int cur)

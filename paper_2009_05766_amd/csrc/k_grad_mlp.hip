@@ -158,7 +158,7 @@ static void launch_fwd_narrow(hipStream_t s, const FwdProblem &p, int kind, int 
 }
 
 // Softmax cross-entropy on the logits (softmax_xent.h): one workgroup per worker.
-__global__ void __launch_bounds__(1024) softmax_xent_kernel(SoftmaxArgs a) { softmax_xent_block(a, blockIdx.x); }
+__global__ void __launch_bounds__(1024) softmax_xent_kernel(SoftmaxArgs a) { softmax_xent_block(a, blockIdx.x, softmax_label(a, blockIdx.x)); }
 
 // db = column sums of dZ.  One workgroup = one worker x 64 outputs; the batch rows are dealt to four groups of
 // threads (rows r, r + 4, ...), whose partial sums are added in the order of the groups.  Eight rows of a group are asked for

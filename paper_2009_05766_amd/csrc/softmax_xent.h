@@ -27,24 +27,67 @@ inline SoftmaxArgs softmax_args(const MlpPlan &p, float *G)
     return a;
 }
 
+// The label of a thread's batch row.
+__device__ __forceinline__ int softmax_label(const SoftmaxArgs &a, int g)
+{
+    const int b = (int)threadIdx.x < a.B ? (int)threadIdx.x : a.B - 1;
+    return a.labels[a.row0[g] + a.idx[(size_t)g * a.B + b]];
+}
+
 // One thread per batch row; the workgroup then adds up the columns of dz (batch rows in a fixed order).
-__device__ __forceinline__ void softmax_xent_block(const SoftmaxArgs &a, int g)
+// CLASSES > 0: at most so many classes, and the logits lie in LDS at `rows` (SOFTMAX_PITCH apart), where dz then takes their place: bound
+// by the chain of loads otherwise, one for every class three times over and one for every row of a column's part.  With 8 workers
+// 256-128-30, batch 96, the last layer's forward pass took 22 us by way of memory.
+constexpr int SOFTMAX_PITCH = 33;
+template <int CLASSES = 0>
+__device__ __forceinline__ void softmax_xent_block(const SoftmaxArgs &a, int g, int y, float *rows = nullptr)
 {
     const int B = a.B, M = a.M;
     const int64_t C = a.C, boff = a.boff, D = a.D, ld = a.ld;
-    const float *logits = a.logits; const int32_t *labels = a.labels; const int64_t *row0 = a.row0; const int32_t *idx = a.idx;
+    const float *logits = a.logits;
     float *dz = a.dz; uint16_t *dz_bf16 = a.dz_bf16, *dz_bf16_t = a.dz_bf16_t; float *loss = a.loss, *G = a.G;
     __shared__ float red[1024];
     const int b = threadIdx.x;
     float l = 0.0f;
-    if (b < B) {
+    if (CLASSES > 0 && b < B) {
+        float *row = rows + b * SOFTMAX_PITCH;
+        float z[CLASSES > 0 ? CLASSES : 1];
+#pragma unroll
+        for (int o = 0; o < CLASSES; ++o) z[o] = row[o];              // the columns past the last class hold something, too
+        float mx = z[0];
+#pragma unroll
+        for (int o = 1; o < CLASSES; ++o)
+            if (o < C) mx = fmaxf(mx, z[o]);
+        const float zy = row[y];
+        float sum = 0.0f;
+#pragma unroll
+        for (int o = 0; o < CLASSES; ++o)
+            if (o < C) {
+                z[o] = expf(z[o] - mx);
+                sum += z[o];
+            }
+        l = logf(sum) - (zy - mx);
+        const float inv = 1.0f / sum, invB = 1.0f / (float)B;
+        float *d = dz + ((size_t)g * B + b) * C;
+#pragma unroll
+        for (int o = 0; o < CLASSES; ++o)
+            if (o < C) {
+                const float v = (z[o] * inv - (o == y ? 1.0f : 0.0f)) * invB;
+                row[o] = v;
+                d[o] = v;
+                if (dz_bf16) {
+                    const uint16_t h = (uint16_t)bf16_bits(v);
+                    dz_bf16[((size_t)g * B + b) * C + o] = h;
+                    dz_bf16_t[((size_t)g * C + o) * B + b] = h;
+                }
+            }
+    } else if (CLASSES == 0 && b < B) {
         const float *z = logits + ((size_t)g * B + b) * C;
         float *d = dz + ((size_t)g * B + b) * C;
         float mx = z[0];
         for (int64_t o = 1; o < C; ++o) mx = fmaxf(mx, z[o]);
         float sum = 0.0f;
         for (int64_t o = 0; o < C; ++o) sum += expf(z[o] - mx);
-        const int y = labels[row0[g] + idx[(size_t)g * B + b]];
         l = logf(sum) - (z[y] - mx);
         const float inv = 1.0f / sum, invB = 1.0f / (float)B;
         for (int64_t o = 0; o < C; ++o) {
@@ -74,7 +117,7 @@ __device__ __forceinline__ void softmax_xent_block(const SoftmaxArgs &a, int g)
         if (b < c * P) {
             const int o = b % c, part = b / c;
             float s = 0.0f;
-            for (int r = part; r < B; r += P) s += dz[((size_t)g * B + r) * C + o];
+            for (int r = part; r < B; r += P) s += CLASSES > 0 ? rows[r * SOFTMAX_PITCH + o] : dz[((size_t)g * B + r) * C + o];
             red[b] = s;
         }
         __syncthreads();

@@ -46,6 +46,15 @@ def test_gradient_of_odd_layers(ora, dtype, M, batch, dims):
     gpu.close()
 
 
+@pytest.mark.parametrize("M,batch,dims", [
+    # the last layer on matrix cores: two pieces of 64 features, one group of four and two left over, the most (32); one to four waves, classes
+    # on either side of the padding
+    (3, 32, (128, 128, 2)), (2, 64, (64, 384, 17)), (3, 96, (40, 128, 32)), (2, 128, (128, 384, 31)), (2, 128, (36, 2048, 10)), (5, 32, (36, 2048, 32)),
+])
+def test_last_layer_of_few_classes(ora, M, batch, dims):
+    test_gradient_of_odd_layers(ora, "bf16", M, batch, dims)
+
+
 @pytest.mark.parametrize("dtype,M,batch,dims", [
     # contractions that eight waves share: whole steps of sixteen (bfloat16 32) indices, one more, one fewer, a wave without a step of its own
     ("f32", 2, 31, (640, 33, 10)), ("f32", 3, 33, (641, 65, 10)), ("f32", 2, 100, (655, 31, 10)), ("f32", 9, 129, (650, 68, 10)), ("f32", 2, 20, (1000, 40)),
