@@ -684,12 +684,21 @@ __global__ void __launch_bounds__(MF_THREADS) __attribute__((amdgpu_waves_per_eu
         }
     }
     const size_t a_step = GATHERED ? WM_ROWS : (size_t)WM_ROWS * p.B;
-    u32x4 ra[AN];
+    // A strip of data rows is half of their 128-byte lines: two strips are asked for together (walks of more than one strip have an
+    // even number of them), the second one stays in registers.  us per iteration of 3072-1024-1024-10, batch 128, each strip for itself
+    // and two together: 48 workers 907 and 886, 64 workers 1246 and 1210, 128 workers 2449 and 2395.
+    u32x4 ra[AN], rs[GATHERED ? AN : 1];
+    const bool pairs = GATHERED && p.walk > 1;
     auto fetch_a = [&](unsigned k) {
 #pragma unroll
         for (int q = 0; q < AN; ++q) ra[q] = *reinterpret_cast<const u32x4 *>(a_src[q] + k * a_step);
+        if constexpr (GATHERED)
+            if (pairs) {
+#pragma unroll
+                for (int q = 0; q < AN; ++q) rs[q] = *reinterpret_cast<const u32x4 *>(a_src[q] + (k + 1) * a_step);
+            }
     };
-    unsigned at = p.apart ? (unsigned)g / p.apart % n : 0;           // where this worker's walk begins; it goes on from the first strip
+    unsigned at = p.apart ? (unsigned)g / p.apart % n & ~1u : 0;     // where this worker's walk begins; it goes on from the first strip
     auto stash_a = [&]() {
 #pragma unroll
         for (int q = 0; q < AN; ++q) {
@@ -745,7 +754,13 @@ __global__ void __launch_bounds__(MF_THREADS) __attribute__((amdgpu_waves_per_eu
 #pragma unroll
         for (int u = 0; u < PASSES; ++u) xp[u] = *reinterpret_cast<const f32x4_t *>(mx.Xcur + own[u] + peer_shift);
         at = at + 1 < n ? at + 1 : 0;
-        if (s + 1 < n) fetch_a(at);
+        if (s + 1 < n) {
+            if (!pairs || at % 2 == 0) fetch_a(at);
+            else if constexpr (GATHERED) {
+#pragma unroll
+                for (int q = 0; q < AN; ++q) ra[q] = rs[q];
+            }
+        }
         __builtin_amdgcn_sched_barrier(0);
         f32x16 acc;
 #pragma unroll
