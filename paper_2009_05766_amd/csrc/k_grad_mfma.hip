@@ -632,7 +632,7 @@ __global__ void __launch_bounds__(MF_THREADS) __attribute__((amdgpu_waves_per_eu
 // orders its tiles), so the strip a worker pulls from its peer is in that XCD's L2.
 // Bound by memory: x, v, x', v' and the operands that are read again for every block.  The dZ^T block stays in LDS for the whole walk, A^T's
 // next strip and x, v and the peer's x travel while the present one is multiplied.  3072-1024 and 1024-1024, batch 128, 48
-// workers: 476 and 143 us (5.1 and 5.6 TB/s of the 16 bytes a parameter); with one block of 64 x 128 per workgroup, its operands
+// workers: 464 and 144 us (5.2 and 5.6 TB/s of the 16 bytes a parameter; 4.0 GB with operands and peers across the fabric); with one block of 64 x 128 per workgroup, its operands
 // loaded, multiplied and then x, v and the peer's x asked for, 725 us together.  Without products and operands it would take 460 and 133,
 // whatever the number of workgroups per compute unit (one to three) and the height of a strip (32, 64, 128 rows: the same within 3 %).
 struct WgradMixArgs {

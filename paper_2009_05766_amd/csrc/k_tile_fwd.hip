@@ -473,7 +473,8 @@ static void launch_shape(hipStream_t s, const TileFwd &a)
 }
 
 // Few workgroups are bound by the chain of steps: 32 x 32 blocks whose steps four waves share, until there are enough of the larger
-// blocks.  Counted in 32 x 64 blocks; us per iteration, shared and the larger form, either side of each line:
+// blocks.  Counted in 32 x 64 blocks; us per iteration, shared and the larger form, either side of each line (of the form with
+// barriers that wave_fwd_kernel has replaced, which is slower throughout; the lines also separate two orders of sums and stay):
 //   fp32, batch <= 32      96 x 784-515 (864) 287 and 304, 128 x 784-515 (1152) 381 and 385, 128 x 100-900 (1920) 104 and 104
 //   fp32, batch <= 64      64 x 784-300 (640) 131 and 137, 96 x 784-300 (960) 190 and 178
 //   fp32, more             24 x 784-512, batch 128 (768) 107 and 115, 48 x 784-512 (1536) 188 and 168; on the line (1024) 64 x 784-256
