@@ -302,17 +302,18 @@ template <int RT> static bool launch_wave(hipStream_t s, const TileDgrad &a)
     return mblk == 1;
 }
 
-// Whether wave_dgrad_kernel takes a layer: few blocks of 32 columns (of all workers, times the batch's parts of 128 rows).  us, it and the other kernel,
-// either side of each line:
+// Whether wave_dgrad_kernel takes a layer: few blocks of 32 columns (of all workers, times the batch's parts of 128 rows).  The two kernels add in
+// different orders: batches of asynchronous steps go by one number of workers whatever their own, so that a step's errors don't depend on the
+// steps beside it.  us, it and the other kernel, either side of each line:
 //   batch <= 32    48 x 1000-300 (1536 blocks) 21.6 and 24.6, 64 x (2048) 27.2 and 27.1
 //   batch <= 64    8 x 1000-300 (256) 8.8 and 11.7, 12 x (384) 12.9 and 12.0; many outputs 16 x 1000-1000 (512) 28.1 and 29.3, 32 x (1024) 56 and 52
 //   more           many outputs 8 x 1000-1000 (256) 29.6 and 31.1, 12 x (384) 53 and 52
 // Rows of W that start anywhere cost the other kernel a load a float:
 //   batch <= 64    102 x 301-1001 (1020) 76 and 81, 51 x 301-102 (510) 11.2 and 10.4
 //   more           128 x 102-602 (512) 43 and 51, 128 x 102-301 30.2 and 29.4, 64 x 102-301 (256) 16 and 23
-static bool wave_dgrad_pays(const TileDgrad &a)
+static bool wave_dgrad_pays(const TileDgrad &a, int M)
 {
-    const int64_t K = a.dout, blocks = (int64_t)a.M * ((a.din + WF_COLS - 1) / WF_COLS) * ((a.B + 127) / 128);
+    const int64_t K = a.dout, blocks = (int64_t)M * ((a.din + WF_COLS - 1) / WF_COLS) * ((a.B + 127) / 128);
     const bool any = K % 4 != 0 || a.woff % 4 != 0, deep = K >= (any ? 256 : 640);
     if (a.B <= 32) return blocks <= 1536;
     if (a.B <= 64) return blocks <= (!deep ? 256 : any ? 1024 : 512);
@@ -329,7 +330,7 @@ bool launch_tile_dgrad(hipStream_t s, const MlpPlan &p, int l, const float *X, f
     a.out_bf16 = (bf && below_fast) ? p.dzb[cur ^ 1] : nullptr;
     a.out_bf16_t = (bf && below_fast) ? p.dzt[cur ^ 1] : nullptr;
     a.G = G; a.boff = p.woff[l - 1] + p.dims[l - 1] * p.dims[l];
-    if (!bf && wave_dgrad_pays(a)) {
+    if (!bf && wave_dgrad_pays(a, p.M_rule)) {
         if (a.B <= 32) return launch_wave<1>(s, a);
         return a.B <= 64 ? launch_wave<2>(s, a) : launch_wave<4>(s, a);
     }

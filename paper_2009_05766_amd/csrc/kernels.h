@@ -138,6 +138,7 @@ hipError_t launch_small_iter(hipStream_t s, const SmallIterLaunch &a);
 struct MlpPlan {
     int M, n_layers, B;
     int Mx;                 // workers of X, G and V
+    int M_rule;             // workers by which the error's kernel is chosen: M, but the same for all batches of asynchronous steps
     const int32_t *worker;  // device [M], NULL: all of them
     int64_t dims[8];
     int64_t woff[8];        // offset of layer l's W inside a parameter row; the bias follows the matrix

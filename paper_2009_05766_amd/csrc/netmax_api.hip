@@ -635,7 +635,7 @@ static MlpPlan make_plan(const netmax_ctx *ctx)
 {
     const netmax_config &c = ctx->cfg;
     MlpPlan p{};
-    p.M = p.Mx = c.M; p.worker = nullptr; p.n_layers = c.n_layers; p.B = c.batch; p.ld = c.ld; p.bf16 = (c.gemm_in == NETMAX_BF16); p.head_pairs = ctx->resident_mlp;
+    p.M = p.Mx = p.M_rule = c.M; p.worker = nullptr; p.n_layers = c.n_layers; p.B = c.batch; p.ld = c.ld; p.bf16 = (c.gemm_in == NETMAX_BF16); p.head_pairs = ctx->resident_mlp;
     for (int l = 0; l <= c.n_layers; ++l) {
         p.dims[l] = c.dims[l]; p.woff[l] = ctx->woff[l]; p.act[l] = ctx->d_act[l];
         p.hb[l] = ctx->d_hb[l]; p.ht[l] = ctx->d_ht[l];
@@ -1047,6 +1047,7 @@ static int enqueue_subset_gradient(netmax_ctx *ctx, const AsyncSlots &slots)
                         ctx->d_idx);
     MlpPlan p = make_plan(ctx);
     p.M = p.Mx = slots.n;                                    // the compact matrix
+    p.M_rule = std::max(1, std::min(c.M / 4, 16));           // about as many as a batch has (16 workers: 64 steps in 18 batches)
     p.head_pairs = 0;                                        // 0.25 us longer a batch, and no other kernel has to agree with it
     p.row0 = ctx->d_row0c;
     p.loss = ctx->d_lossc;

@@ -513,6 +513,26 @@ def test_async_schedule_perceptron_of_other_shapes(over):
     test_async_schedule_perceptron("cfg2", over)
 
 
+@pytest.mark.parametrize("batch,dims", [(40, (20, 1536, 40, 10)), (24, (20, 8200, 40, 10))])
+def test_async_run_in_one_call_and_step_by_step(batch, dims):
+    """A step's bits do not depend on how a run is cut into calls, that is, on the steps that share its launches: the errors of float layers wide enough
+    that one and several workers lie on either side of the line between their two kernels."""
+    import paper_2009_05766_amd as nm
+    w = workload("cfg2", M=24, batch=batch, n_per_worker=batch + 9, dims=dims)
+    inp = inputs_of(w)
+    whole, steps = (make_gpu(w, inp, momentum=0.9) for _ in range(2))
+    n = 48
+    active, peers = (torch.zeros((2, n), dtype=torch.int32, device="cuda") for _ in range(2))
+    for net in (whole, steps):
+        nm.netmax_set_activity(net.ctx, np.full(w.M, 1.0 / w.M))
+    nm.netmax_async_run(whole.ctx, 0, n, active[0], peers[0])
+    for k in range(n):
+        nm.netmax_async_run(steps.ctx, k, 1, active[1, k:], peers[1, k:])
+    assert torch.equal(active[0], active[1]) and torch.equal(peers[0], peers[1])
+    assert torch.equal(whole.get("x"), steps.get("x")) and torch.equal(whole.v, steps.v)
+    whole.close(), steps.close()
+
+
 def test_async_schedule_flat_in_order():
     """Large flat models run consecutive steps side by side, smaller ones whichever do not see each other: one call of many steps
     against one call per step."""
