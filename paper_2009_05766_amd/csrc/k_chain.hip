@@ -388,7 +388,8 @@ bool chain_fwd_pays(const MlpPlan &p, int l)
     const int64_t blocks = p.M * ((dout + WF_COLS - 1) / WF_COLS) * ((p.B + 127) / 128);
     // 32-bit offsets inside a step's rows of W
     if (!p.bf16 || p.M > 2048 || step * p.M * (TILE * 4) >= (int64_t)1 << 32) return false;
-    if (mfma_layer_ok(p, l)) return blocks <= (p.B > 64 ? 512 : din >= 1024 ? 1024 : p.B > 32 ? 512 : 768);
+    // an aligned last layer has no activations to keep and is a layer of any width for the other kernels, too
+    if (mfma_layer_ok(p, l) && l + 1 < p.n_layers) return blocks <= (p.B > 64 ? 512 : din >= 1024 ? 1024 : p.B > 32 ? 512 : 768);
     return tile_fwd_one_chain(p, l) && din >= 640 && p.B > 32 && blocks <= (p.B > 64 ? 256 : 512);
 }
 

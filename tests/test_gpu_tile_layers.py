@@ -111,6 +111,29 @@ def test_few_blocks_bit_for_bit(few, many, batch, dims):
         assert np.array_equal(a, b)
 
 
+@pytest.mark.parametrize("M,batch,dims", [(7, 96, (640, 128)), (3, 64, (256, 128, 128)), (40, 32, (256, 512))])
+def test_last_layer_of_aligned_width_adds_as_any_other(M, batch, dims):
+    """A last layer on bfloat16 operands adds in the same order whether its classes are a multiple of 128 or four more that never win: the same losses bit
+    for bit."""
+    C, more = dims[-1], 4
+    w = workload("cfg5", M=M, batch=batch, n_per_worker=batch + 7, dims=dims)
+    inp = inputs_of(w)
+    wide = workload("cfg5", M=M, batch=batch, n_per_worker=batch + 7, dims=(*dims[:-1], C + more))
+    at = w.D - (dims[-2] + 1) * C                                    # the last layer's first parameter
+    W = inp["X0"][:, at:at + dims[-2] * C].reshape(M, dims[-2], C)
+    b = inp["X0"][:, at + dims[-2] * C:w.D]
+    X = np.zeros((M, inputs_of(wide)["X0"].shape[1]), np.float32)
+    X[:, :at] = inp["X0"][:, :at]
+    X[:, at:wide.D] = np.concatenate([np.pad(W, ((0, 0), (0, 0), (0, more))).reshape(M, -1), np.pad(b, ((0, 0), (0, more)), constant_values=-1e30)], axis=1)
+    losses = []
+    for v, i in ((w, inp), (wide, dict(inp, X0=X))):
+        gpu = make_gpu(v, i)
+        gpu.local_step(1)
+        losses.append(gpu.losses().cpu().numpy())
+        gpu.close()
+    assert np.isfinite(losses[0]).all() and np.array_equal(losses[0], losses[1])
+
+
 def test_wide_fp32_layers_keep_what_is_not_finite():
     """Large fp32 layers multiply bfloat16 planes of their operands, which an infinity, or a number that rounds to one, does not
     survive: such blocks are computed again in fp32.  Activations against float64, block edges included."""
