@@ -1090,26 +1090,44 @@ void launch_dgrad_mfma(hipStream_t s, const MlpPlan &p, int l, const float *X, f
     hipLaunchKernelGGL(dgrad_mfma_kernel, dim3(grouped_grid(p.M, (unsigned)(a.din / MF_BN))), dim3(MF_THREADS), 0, s, a);
 }
 
+// Strips a walk of wgrad_mix_mfma_kernel, and the bytes that a parameter then costs: 16 of x, v, x' and v', dZ^T of the 128 columns once a walk, the strip's rows of
+// A^T, all that by how much longer the XCD with the most blocks is at work than they are on average.  Of the walks of one, two, four and eight strips the one that costs
+// least, if the compute units have two walks each.  At batches of up to 64, where dZ^T is small beside the strip's 64 KB of x, v, x' and v', one strip: with one and
+// with eight, batch 64, 64 workers 1024-512 372 and 370 us an iteration, batch 32, 61 workers 2304-640 740 and 783.
+// us per iteration with one, two, four and eight strips (fused), bytes by this count: batch 128, 63 workers 1152-896-10 364, 323, 320, 336 (26.4, 22.3, 20.3,
+// 24.1), 640-384-10 134, 123, 120, 131 (27.7, 23.5, 21.3, 40.5), 1024-512-10 203, 190, 185, 182 (26, 22, 20, 19), 128 workers 1664-384-10 462, 408, 400, 420 (26.7,
+// 22.6, 20.5, 23.4); one and eight, 128 workers 3072-1024-1024-10 2977 and 2527; too few walks: 4 workers 2944-896-640-25 617 and 674.  Walks whose blocks
+// are whole rounds over the XCDs, or eight rounds and more, were the only ones before: that left one strip to 127 workers 1152-384-10 (341 us, 302 now; a block of 64 x
+// 128 per workgroup 333) and 48 workers 640-640-10 (150 and 138).  The others have to save 8 %: batch 96, 100 workers 1152-896-10 (126 and 63 blocks) 467 us with
+// two strips and 475 with four (7 % by the count).  At multiples of 64 workers (see `apart`) a walk of four has two places to begin: not those there, batch 96, 64
+// workers 1152-896-10 312 us with two strips and 321 with four; but 128 workers 1280-512-10, batch 128 (40 blocks) 412 and 402.
+struct WgradWalk { unsigned strips; double bytes; };
+static WgradWalk wgrad_walk(int M, int B, int64_t din, int64_t dout)
+{
+    const unsigned strips = (unsigned)(din / WM_ROWS), cols = (unsigned)(dout / WM_COLS);
+    WgradWalk best{};
+    for (unsigned walk = 1; walk <= (B > 64 ? 8u : 1u); walk *= 2) {
+        const unsigned blocks = (strips + walk - 1) / walk * cols, rounds = (blocks + MF_XCD - 1) / MF_XCD;
+        const double b = (16.0 + B / 64.0 + B / (16.0 * walk)) * (rounds * MF_XCD * (double)walk / ((double)strips * cols));
+        const bool even = blocks % MF_XCD == 0 || blocks >= 8 * MF_XCD;
+        if (walk > 1 && ((uint64_t)M * blocks < 2 * MF_XCD * XCD_CUS || (walk > 2 && M % 64 == 0 && !even))) continue;
+        if (walk == 1 || b < (even ? 1.0 : 0.92) * best.bytes) best = WgradWalk{walk, b};
+    }
+    return best;
+}
+
 void launch_wgrad_mix_mfma(hipStream_t s, const MlpPlan &p, int l, float *G, int cur, const MixArgs &mix)
 {
     WgradMixArgs a;
     a.a_t = p.ht[l]; a.dz_t = p.dzt[cur]; a.M = p.M; a.B = p.B; a.din = p.dims[l]; a.dout = p.dims[l + 1];
     a.woff = p.woff[l]; a.G = G; a.mix = mix;
     a.feats = l == 0 ? (const uint16_t *)p.feats : nullptr; a.row0 = p.row0; a.idx = p.idx;
-    const unsigned strips = (unsigned)(a.din / WM_ROWS), cols = (unsigned)(a.dout / WM_COLS);
-    // Up to eight strips a walk where dZ^T is large beside the strip's 64 KB of x, v, x' and v' (32 KB at a batch of 128), the XCDs
-    // have the same number of blocks and the compute units two walks each.  us per iteration with eight strips and with one: batch 128,
-    // 128 workers 3072-1024-1024 2527 and 2977, 48 workers 919 and 946, 64 workers 512-512 (512 walks) 138 and 145, but 4 workers
-    // 2944-896-640 (336 and 140 walks) 674 and 617, 100 workers 512-256 (four blocks) 157 and 131, with four strips 127; batch 64, 64
-    // workers 1024-512 370 and 372; batch 32, 61 workers 2304-640 783 and 740.
-    auto blocks_of = [&](unsigned walk) { return (strips + walk - 1) / walk * cols; };
-    a.walk = p.B > 64 ? 8 : 1;
-    while (a.walk > 1 && ((blocks_of(a.walk) % MF_XCD != 0 && blocks_of(a.walk) < 8 * MF_XCD) || (uint64_t)p.M * blocks_of(a.walk) < 2 * 256)) a.walk /= 2;
+    a.walk = wgrad_walk(p.M, p.B, a.din, a.dout).strips;
     // A tile of the layout is 8 KB of every worker.  At a multiple of 512 KB from tile to tile the workers, strip by strip in step, fall
     // on few of the memory's channels: eight workers at a time begin their walk a strip further on.  64 workers 3072-1024-1024 1341 and
     // 1237 us, 128 workers 2527 and 2495; 32 and 48 workers would lose 2 to 10 % (the peer's strip is no longer in the L2).
     a.apart = p.M % 64 == 0 ? 8 : 0;
-    const unsigned blocks = blocks_of(a.walk);
+    const unsigned blocks = ((unsigned)(a.din / WM_ROWS) + a.walk - 1) / a.walk * (unsigned)(a.dout / WM_COLS);
     const dim3 grid((blocks + MF_XCD - 1) / MF_XCD * MF_XCD * (unsigned)p.M), block(MF_THREADS);
     if (l == 0) {
         if (mix.keep_g) hipLaunchKernelGGL((wgrad_mix_mfma_kernel<true, true>), grid, block, 0, s, a);

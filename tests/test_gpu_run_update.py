@@ -69,6 +69,8 @@ def test_run_with_narrow_layers(name, M, batch, dims):
     (6, 32, (512, 512, 128, 10)), (5, 32, (512, 512, 128, 10)), (13, 64, (130, 256, 384, 10)), (7, 128, (384, 640, 128)),
     # walks of eight strips, whole and with four left over, from the first strip and from a later one
     (48, 128, (1024, 1024, 10)), (49, 96, (1152, 896, 10)), (64, 96, (1152, 896, 128, 10)), (128, 128, (128, 896, 640, 10)),
+    # eight strips a walk and blocks that are no whole rounds over the XCDs
+    (40, 128, (1152, 384, 10)),
 ])
 @pytest.mark.parametrize("fused", [False, True])
 def test_run_of_matrix_core_layers(M, batch, dims, fused):

@@ -20,15 +20,19 @@ def routes(tmp_path_factory):
                     "-rdynamic", "-ldl", "-o", exe], check=True)
     lib = LIB if os.path.exists(LIB) else build()
 
-    def of(dims, M, batch, iters, offset=0, capture=0, cooperative=1):
-        """-> launches of one iteration by separate calls, launches of netmax_run: lists of (how, kernel)."""
-        return drive([" ".join(str(v) for v in (iters, M, batch, offset, capture, cooperative, *dims))])[0][1:]
+    def forms(dims, M, batch, iters, offset=0, capture=0, cooperative=1, bf16=0, fused=0):
+        """-> launches of one iteration by separate calls, launches of netmax_run: lists of (how, kernel, template arguments, workgroups)."""
+        return drive([" ".join(str(int(v)) for v in (iters, M, batch, offset, capture, cooperative, bf16, fused, *dims))])[0][1:]
+
+    def of(*a, **over):
+        """The same as lists of (how, kernel)."""
+        return [[launch[:2] for launch in part] for part in forms(*a, **over)]
 
     def drive(lines):
         r = subprocess.run([exe, lib], input="\n".join(lines), capture_output=True, text=True, timeout=120)
         assert r.returncode == 0, r.stderr
         return [[[tuple(launch.split(":")) for launch in part.split()] for part in line.split("|")] for line in r.stdout.splitlines()]
-    of.drive = drive
+    of.drive, of.forms = drive, forms
     return of
 
 
@@ -50,8 +54,8 @@ def test_launches_that_wait_are_cooperative(routes, dims, M, batch, kernel, few,
 def test_first_cooperative_launch_of_a_process(routes):
     """It takes milliseconds and belongs to preparation; contexts that make no such launches do without, further ones do not repeat it."""
     first = [[launch for launch in parts[0] if launch[0] == "cooperative"] for parts in
-             routes.drive(["9 4 50 0 0 1 100 50 10", "9 8 32 0 0 0 256 10", "9 16 64 0 0 1 784 10", "9 8 32 0 0 1 256 10"])]
-    assert first == [[], [], [("cooperative", "no_work_kernel")], []]
+             routes.drive(["9 4 50 0 0 1 0 0 100 50 10", "9 8 32 0 0 0 0 0 256 10", "9 16 64 0 0 1 0 0 784 10", "9 8 32 0 0 1 0 0 256 10"])]
+    assert first == [[], [], [("cooperative", "no_work_kernel", "", "1")], []]
 
 
 @pytest.mark.parametrize("dims,M,batch", [((784, 10), 37, 64), ((784, 512, 10), 17, 64), ((256, 10), 257, 32)])
@@ -78,3 +82,16 @@ def test_cases_reach_their_kernel(routes, kernel, over):
         assert run == [("cooperative", kernel)]
     else:
         assert all(how == "plain" and name not in (SMALL, SLICED, RESIDENT) for how, name in run)
+
+
+@pytest.mark.parametrize("M,batch,widths,strips", [
+    # the rule's terms, one by one: a block's share of an XCD's rounds, two walks a compute unit, small batches, multiples of 64 workers
+    (127, 128, (1152, 384), 2), (63, 128, (1664, 384), 4), (63, 128, (896, 128), 2), (63, 128, (384, 384), 1), (63, 128, (1024, 512), 8), (48, 128, (640, 640), 2),
+    (8, 128, (1024, 1024), 4), (4, 128, (1024, 512), 1), (127, 64, (1152, 384), 1), (64, 128, (640, 384), 2), (64, 96, (1152, 896), 2), (128, 128, (1280, 512), 4),
+    (128, 128, (3072, 1024), 8), (64, 128, (2944, 640), 4),
+])
+def test_walks_of_the_fused_weight_gradient(routes, M, batch, widths, strips):
+    """The strips that a workgroup walks, from its launch's size."""
+    launched = [int(groups) for _, kernel, _, groups in routes.forms((*widths, 10), M, batch, 1, bf16=1, fused=1)[1] if kernel == "wgrad_mix_mfma_kernel"]
+    size = {walk: -(-(-(-widths[0] // 32 // walk)) * (widths[1] // 128) // 8) * 8 * M for walk in (1, 2, 4, 8)}
+    assert launched == [size[strips]] and list(size.values()).count(size[strips]) == 1
