@@ -1101,19 +1101,44 @@ void launch_dgrad_mfma(hipStream_t s, const MlpPlan &p, int l, const float *X, f
 // 128 per workgroup 333) and 48 workers 640-640-10 (150 and 138).  The others have to save 8 %: batch 96, 100 workers 1152-896-10 (126 and 63 blocks) 467 us with
 // two strips and 475 with four (7 % by the count).  At multiples of 64 workers (see `apart`) a walk of four has two places to begin: not those there, batch 96, 64
 // workers 1152-896-10 312 us with two strips and 321 with four; but 128 workers 1280-512-10, batch 128 (40 blocks) 412 and 402.
-struct WgradWalk { unsigned strips; double bytes; };
+struct WgradWalk { unsigned strips; double operands, uneven; };
 static WgradWalk wgrad_walk(int M, int B, int64_t din, int64_t dout)
 {
     const unsigned strips = (unsigned)(din / WM_ROWS), cols = (unsigned)(dout / WM_COLS);
     WgradWalk best{};
+    double least = 0.0;
     for (unsigned walk = 1; walk <= (B > 64 ? 8u : 1u); walk *= 2) {
         const unsigned blocks = (strips + walk - 1) / walk * cols, rounds = (blocks + MF_XCD - 1) / MF_XCD;
-        const double b = (16.0 + B / 64.0 + B / (16.0 * walk)) * (rounds * MF_XCD * (double)walk / ((double)strips * cols));
+        const double operands = B / 64.0 + B / (16.0 * walk), uneven = rounds * MF_XCD * (double)walk / ((double)strips * cols), bytes = (16.0 + operands) * uneven;
         const bool even = blocks % MF_XCD == 0 || blocks >= 8 * MF_XCD;
         if (walk > 1 && ((uint64_t)M * blocks < 2 * MF_XCD * XCD_CUS || (walk > 2 && M % 64 == 0 && !even))) continue;
-        if (walk == 1 || b < (even ? 1.0 : 0.92) * best.bytes) best = WgradWalk{walk, b};
+        if (walk == 1 || bytes < (even ? 1.0 : 0.92) * least) {
+            best = WgradWalk{walk, operands, uneven};
+            least = bytes;
+        }
     }
     return best;
+}
+
+// The update inside the weight gradients of netmax_run, by the bytes a parameter that it saves: 24 with the separate mix (g written and read), against x, v, x' and v',
+// the operands as long as all workers' do not stay in an XCD's 4 MB of L2, and three quarters of the uneven share (XCDs that are done leave the others their part
+// of the memory); g beside x' and v' as 2.5.  Every parameter that is none of these layers' costs 2.25 more, in the mix of what is left, than in the mix of everything
+// (1.25 from 96 workers on).
+// us, four iterations, separate and in the gradients, saved bytes a parameter of the model: batch 128, 127 workers 384-128-128-10 433 and 462 (-7.8), 384-384-10 570
+// and 605 (-4.1), 640-640-10 1355 and 1238 (0), 1152-384-10 1398 and 1217 (1.4); 64 workers 3000-1000-128-128-10 4820 and 5068 (-2.3), 2000-512-512-10 2215 and
+// 2254 (-0.8), 200-1024-1024-10 2482 and 2326 (3.8); 8 workers 640-640-10 256 and 237 (7.3); batch 64, 64 workers 640-128-10 244 and 236 (-0.2).
+double wgrad_mix_saves(const MlpPlan &p)
+{
+    const double rest = p.M >= 96 ? 1.25 : 2.25;
+    double saved = -rest * (double)p.ld;
+    for (int l = 0; l < p.n_layers; ++l) {
+        if (!mfma_layer_ok(p, l)) continue;
+        const int64_t din = p.dims[l], dout = p.dims[l + 1];
+        const WgradWalk w = wgrad_walk(p.M, p.B, din, dout);
+        const bool in_l2 = p.M * (din + dout) * p.B * 2 <= (int64_t)7 << 19;
+        saved += (double)(din * dout) * (24.0 + rest - (16.0 + (in_l2 ? 0.0 : w.operands)) * (1.0 + 0.75 * (w.uneven - 1.0)));
+    }
+    return saved / (double)p.ld;
 }
 
 void launch_wgrad_mix_mfma(hipStream_t s, const MlpPlan &p, int l, float *G, int cur, const MixArgs &mix)

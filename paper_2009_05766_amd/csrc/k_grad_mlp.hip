@@ -200,13 +200,14 @@ bias_grad_kernel(int M, int B, int64_t dout, const float *__restrict__ dz, int64
 // 2 x 181 us, 512-512-256-10, 16 workers 2 x 88 and 2 x 81 us, 1024-512-10, 4 workers (2.1 M floats) 2 x 68 and 2 x 63 us, but
 // 512-128-128-10, 2 workers 4 x 57.5 and 4 x 60 us.
 constexpr int64_t UPDATE_MIN_FLOATS = 7 << 18;       // M x ld
+constexpr double UPDATE_MIN_SAVED = -0.75;            // bytes a parameter, of wgrad_mix_saves(): from there on none of 70 networks lost more than 2 %
 static bool first_layer_last(const MlpPlan &p) { return p.n_layers == 1 || (p.n_layers == 2 && head_ok(p)) || p.B <= TILE_DGRAD_BATCH; }
 
 int64_t update_end(const MlpPlan &p, int l)
 {
     const bool head = head_ok(p);
     if (p.n_layers == 1 && head) return p.ld;                        // the last-layer kernel updates everything
-    if (mfma_layer_ok(p, l)) return p.M * p.ld < UPDATE_MIN_FLOATS ? 0 : p.woff[l] + p.dims[l] * p.dims[l + 1];
+    if (mfma_layer_ok(p, l)) return p.M * p.ld < UPDATE_MIN_FLOATS || wgrad_mix_saves(p) < UPDATE_MIN_SAVED ? 0 : p.woff[l] + p.dims[l] * p.dims[l + 1];
     if (p.bf16 || (l == p.n_layers - 1 && head) || p.woff[l] % 4 != 0) return 0;
     if (p.M * p.ld < UPDATE_MIN_FLOATS && (l > 0 || !first_layer_last(p))) return 0;
     if (!wgrad_f32_ok(p, l) && !tile_wgrad_update_ok(p, l)) return 0;

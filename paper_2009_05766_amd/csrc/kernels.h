@@ -178,6 +178,7 @@ void launch_fwd_mfma(hipStream_t s, const MlpPlan &p, int l, const float *X);
 // also writes the bias gradient of layer l - 1 into G; want_f32: keep the fp32 copy of the error as well
 void launch_dgrad_mfma(hipStream_t s, const MlpPlan &p, int l, const float *X, float *G, int cur, bool want_f32);
 void launch_wgrad_mfma(hipStream_t s, const MlpPlan &p, int l, float *G, int cur);
+double wgrad_mix_saves(const MlpPlan &p);                // bytes a parameter, by count, that the update in all of them saves an iteration that does not keep g
 void launch_wgrad_mix_mfma(hipStream_t s, const MlpPlan &p, int l, float *G, int cur, const MixArgs &mix);
 // Last layer with at most 32 outputs.
 bool mfma_small_last_ok(const MlpPlan &p);

@@ -95,3 +95,16 @@ def test_walks_of_the_fused_weight_gradient(routes, M, batch, widths, strips):
     launched = [int(groups) for _, kernel, _, groups in routes.forms((*widths, 10), M, batch, 1, bf16=1, fused=1)[1] if kernel == "wgrad_mix_mfma_kernel"]
     size = {walk: -(-(-(-widths[0] // 32 // walk)) * (widths[1] // 128) // 8) * 8 * M for walk in (1, 2, 4, 8)}
     assert launched == [size[strips]] and list(size.values()).count(size[strips]) == 1
+
+
+@pytest.mark.parametrize("M,batch,dims,inside", [
+    # few parameters in matrix-core layers; blocks that leave XCDs without work; walks of few strips; and where it pays
+    (64, 128, (3000, 1000, 128, 128, 10), False), (64, 128, (2000, 512, 512, 10), False), (127, 128, (384, 128, 128, 10), False), (48, 128, (384, 384, 10), False), (48, 128, (640, 640, 10), True),
+    (64, 128, (784, 384, 384, 10), False), (64, 128, (1000, 512, 512, 10), True), (64, 128, (200, 1024, 1024, 10), True), (48, 128, (3072, 1024, 1024, 10), True),
+    (32, 64, (1024, 1024, 10), True), (64, 64, (640, 384, 10), True), (100, 32, (1152, 384, 10), True), (5, 32, (512, 512, 128, 10), False),
+])
+def test_update_in_matrix_core_weight_gradients(routes, M, batch, dims, inside):
+    """Iterations of netmax_run that another follows: the weight gradients of matrix-core layers update their columns where that saves bytes."""
+    run = [kernel for _, kernel in routes(dims, M, batch, 3, bf16=1)[1]]
+    first = run[:run.index("mix_subset_kernel" if inside else "mix_kernel") + 1]
+    assert ("wgrad_mix_mfma_kernel" in first) == inside and ("wgrad_mfma_kernel" in first) != inside
