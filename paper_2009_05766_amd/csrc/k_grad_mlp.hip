@@ -200,18 +200,28 @@ bias_grad_kernel(int M, int B, int64_t dout, const float *__restrict__ dz, int64
 // 2 x 181 us, 512-512-256-10, 16 workers 2 x 88 and 2 x 81 us, 1024-512-10, 4 workers (2.1 M floats) 2 x 68 and 2 x 63 us, but
 // 512-128-128-10, 2 workers 4 x 57.5 and 4 x 60 us.
 constexpr int64_t UPDATE_MIN_FLOATS = 7 << 18;       // M x ld
-constexpr double UPDATE_MIN_SAVED = -0.75;            // bytes a parameter, of wgrad_mix_saves(): from there on none of 70 networks lost more than 2 %
+constexpr double UPDATE_MIN_SAVED = -0.75, UPDATE_MIN_SAVED_G = -0.35;       // bytes a parameter, of wgrad_mix_saves(): from there on none of 70 networks lost more than 2 %
 static bool first_layer_last(const MlpPlan &p) { return p.n_layers == 1 || (p.n_layers == 2 && head_ok(p)) || p.B <= TILE_DGRAD_BATCH; }
 
 int64_t update_end(const MlpPlan &p, int l)
 {
     const bool head = head_ok(p);
     if (p.n_layers == 1 && head) return p.ld;                        // the last-layer kernel updates everything
-    if (mfma_layer_ok(p, l)) return p.M * p.ld < UPDATE_MIN_FLOATS || wgrad_mix_saves(p) < UPDATE_MIN_SAVED ? 0 : p.woff[l] + p.dims[l] * p.dims[l + 1];
+    if (mfma_layer_ok(p, l)) return p.M * p.ld < UPDATE_MIN_FLOATS || wgrad_mix_saves(p, false) < UPDATE_MIN_SAVED ? 0 : p.woff[l] + p.dims[l] * p.dims[l + 1];
     if (p.bf16 || (l == p.n_layers - 1 && head) || p.woff[l] % 4 != 0) return 0;
     if (p.M * p.ld < UPDATE_MIN_FLOATS && (l > 0 || !first_layer_last(p))) return 0;
     if (!wgrad_f32_ok(p, l) && !tile_wgrad_update_ok(p, l)) return 0;
     return p.woff[l] + p.dims[l] * p.dims[l + 1];
+}
+
+// Iterations that keep g.  From 192 workers on, two rounds of the 96 that an XCD holds of a block at a time, much of the peers' columns comes from memory and neither
+// form is ahead: us with the separate mix and in the weight gradients, batch 128, 300 workers 3072-1024-1024-10 6650 and 7090, 200 workers 896-768-10 796 and
+// 850, 1024-1024-10 1184 and 1109, batch 64, 256 workers 1421 and 1466; 160 workers 3072-1024-1024-10 3572 and 3440, 1024-1024-10 919 and 886.
+bool update_beside_g(const MlpPlan &p)
+{
+    bool any = false;
+    for (int l = 0; l < p.n_layers; ++l) any |= mfma_layer_ok(p, l) && update_end(p, l) > 0;
+    return !any || (p.M < 192 && wgrad_mix_saves(p, true) >= UPDATE_MIN_SAVED_G);
 }
 
 // One fp32 hidden layer on the kernels of k_grad_f32.hip, or none: forward, the last layer's two kernels, weight gradient with the

@@ -169,6 +169,7 @@ struct TailArgs { MixArgs mix; const int32_t *tiles; int n_tiles; MixSkip skip; 
 // With a list: X, G and the update in place (mix.Xnext = mix.Xcur); no listed worker is another's peer.
 bool launch_mlp_grad(hipStream_t s, const MlpPlan &p, const float *X, float *G, const MixArgs *fuse = nullptr, const TailArgs *tail = nullptr);
 int64_t update_end(const MlpPlan &p, int l);
+bool update_beside_g(const MlpPlan &p);                  // in iterations that keep g, too
 // All kernels of the plan take a list of workers and between them update all of their columns.
 bool layer_list_ok(const MlpPlan &p);
 
@@ -178,7 +179,7 @@ void launch_fwd_mfma(hipStream_t s, const MlpPlan &p, int l, const float *X);
 // also writes the bias gradient of layer l - 1 into G; want_f32: keep the fp32 copy of the error as well
 void launch_dgrad_mfma(hipStream_t s, const MlpPlan &p, int l, const float *X, float *G, int cur, bool want_f32);
 void launch_wgrad_mfma(hipStream_t s, const MlpPlan &p, int l, float *G, int cur);
-double wgrad_mix_saves(const MlpPlan &p);                // bytes a parameter, by count, that the update in all of them saves an iteration that does not keep g
+double wgrad_mix_saves(const MlpPlan &p, bool keep_g);   // bytes a parameter, by count, that the update in all of them saves an iteration
 void launch_wgrad_mix_mfma(hipStream_t s, const MlpPlan &p, int l, float *G, int cur, const MixArgs &mix);
 // Last layer with at most 32 outputs.
 bool mfma_small_last_ok(const MlpPlan &p);

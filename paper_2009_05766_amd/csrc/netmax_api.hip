@@ -62,7 +62,7 @@ struct netmax_ctx {
     MixSkip fuse_skip{};
     // perceptrons with weight gradients that apply the update to their columns inside netmax_run (the gradient is still
     // written): the tiles the separate mix covers then (none for softmax regression)
-    bool tail = false;
+    bool tail = false, tail_keeps = false;    // tail_keeps: in iterations that leave g, too
     int32_t *d_tail_tiles = nullptr;
     int n_tail_tiles = 0;
     MixSkip tail_skip{};
@@ -450,6 +450,7 @@ extern "C" int netmax_init(netmax_ctx **out, const netmax_config *cfg)
                 ctx->tail_skip.hi[ctx->tail_skip.n] = update_end(plan, l);
                 ++ctx->tail_skip.n;
             }
+        ctx->tail_keeps = ctx->tail && update_beside_g(plan);
         if (ctx->tail) tail_tiles = tiles_outside(ctx->tail_skip, cfg->ld);
         ctx->n_tail_tiles = (int)tail_tiles.size();
         want(&ctx->d_tail_tiles, tail_tiles.size());
@@ -680,15 +681,8 @@ static int enqueue_small(netmax_ctx *ctx, const IterRef &iter, int n_iters, bool
     return NETMAX_OK;
 }
 
-// Whether the weight gradients of this iteration of netmax_run apply the update.  Those of the matrix-core layers don't where they
-// would write the gradient as well and an XCD doesn't hold all workers of a block at a time (96), so that a good part of the peers' columns
-// come from memory: 3072-1024-1024-10, batch 128, 128 workers 2847 us with the separate mix and 2810 to 2900 us; 112 workers
-// still 2550 and 2430 us.
-static bool update_in_gradients(const netmax_ctx *ctx, bool keep_g)
-{
-    const netmax_config &c = ctx->cfg;
-    return ctx->tail && !ctx->fuse && !(keep_g && c.gemm_in == NETMAX_BF16 && c.n_layers > 1 && c.M >= 128);
-}
+// Whether the weight gradients of this iteration of netmax_run apply the update.
+static bool update_in_gradients(const netmax_ctx *ctx, bool keep_g) { return ctx->tail && !ctx->fuse && (ctx->tail_keeps || !keep_g); }
 
 // run_peers != nullptr (netmax_run): weight-gradient kernels apply the update where the context has it so; *updated: to all
 // columns, else enqueue_run_mix covers the remaining ones.
