@@ -6,6 +6,7 @@ import torch
 
 import paper_2009_05766_amd as nm
 from harness import inputs_of, make_gpu
+from kernel_cases import RUNS
 from netmax_inputs import workload
 
 pytestmark = pytest.mark.gpu
@@ -64,16 +65,9 @@ def test_run_with_narrow_layers(name, M, batch, dims):
     test_run_is_the_separate_calls(name, M, batch, dims, False)
 
 
-@pytest.mark.parametrize("M,batch,dims", [
-    # two million floats, from which on the matrix-core layers update their columns: either side, one strip of 32 rows a walk
-    (6, 32, (512, 512, 128, 10)), (5, 32, (512, 512, 128, 10)), (13, 64, (130, 256, 384, 10)), (7, 128, (384, 640, 128)),
-    # walks of eight strips, whole and with four left over, from the first strip and from a later one
-    (48, 128, (1024, 1024, 10)), (49, 96, (1152, 896, 10)), (64, 96, (1152, 896, 128, 10)), (128, 128, (128, 896, 640, 10)),
-    # eight strips a walk and blocks that are no whole rounds over the XCDs
-    (40, 128, (1152, 384, 10)),
-])
+@pytest.mark.parametrize("M,batch,dims,followed,last", RUNS)
 @pytest.mark.parametrize("fused", [False, True])
-def test_run_of_matrix_core_layers(M, batch, dims, fused):
+def test_run_of_matrix_core_layers(M, batch, dims, followed, last, fused):
     if not fused:
         return test_run_is_the_separate_calls("cfg5", M, batch, dims, False)
     w = workload("cfg5", M=M, batch=batch, n_per_worker=batch + 3, dims=dims)
@@ -85,6 +79,12 @@ def test_run_of_matrix_core_layers(M, batch, dims, fused):
         calls.step(k)
     assert torch.equal(run.get("x"), calls.get("x")) and torch.equal(run.v, calls.v) and torch.equal(run.losses(), calls.losses())
     run.close(), calls.close()
+
+
+@pytest.mark.parametrize("M,batch,dims", [c[:3] for c in RUNS if c[4]])
+def test_graph_of_matrix_core_layers(M, batch, dims):
+    """Every replay leaves g: the update in weight gradients that also write it."""
+    test_run_is_the_separate_calls("cfg5", M, batch, dims, True)
 
 
 @pytest.mark.parametrize("name,over", [("cfg2", dict(M=5, batch=24, n_per_worker=40, dims=(30, 20, 10))), ("cfg3", dict(M=7, D=5000)),

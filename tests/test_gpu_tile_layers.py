@@ -3,6 +3,7 @@ import numpy as np
 import pytest
 
 from harness import inputs_of, make_gpu, make_oracle, rel_err_rows
+from kernel_cases import ERRORS, FORWARD, SAME_BITS
 from netmax_inputs import workload
 
 pytestmark = pytest.mark.gpu
@@ -55,57 +56,32 @@ def test_last_layer_of_few_classes(ora, M, batch, dims):
     test_gradient_of_odd_layers(ora, "bf16", M, batch, dims)
 
 
-@pytest.mark.parametrize("dtype,M,batch,dims", [
-    # contractions that eight waves share: whole steps of sixteen (bfloat16 32) indices, one more, one fewer, a wave without a step of its own
-    ("f32", 2, 31, (640, 33, 10)), ("f32", 3, 33, (641, 65, 10)), ("f32", 2, 100, (655, 31, 10)), ("f32", 9, 129, (650, 68, 10)), ("f32", 2, 20, (1000, 40)),
-    ("f32", 2, 40, (1030, 33, 10)), ("f32", 3, 3, (3, 34, 10)), ("f32", 2049, 3, (5, 36, 3)), ("bf16", 2049, 3, (5, 36, 3)),
-    ("bf16", 2, 31, (640, 33, 10)), ("bf16", 3, 33, (641, 65, 10)), ("bf16", 2, 100, (671, 31, 10)), ("bf16", 9, 129, (650, 68, 10)), ("bf16", 2, 20, (1000, 40)),
-    # aligned layers (both orientations of the activations): fewer steps than waves, one, two and four row tiles, a general layer under them
-    ("bf16", 3, 32, (128, 128, 10)), ("bf16", 2, 64, (256, 384, 128, 10)), ("bf16", 17, 96, (1280, 256, 10)), ("bf16", 2, 128, (700, 128, 128, 10)),
-    # the most blocks that it takes, and one worker more
-    ("f32", 32, 65, (640, 500, 10)), ("f32", 33, 65, (640, 500, 10)), ("f32", 64, 33, (644, 1024, 10)), ("f32", 65, 33, (644, 1024, 10)),
-    ("bf16", 32, 20, (640, 1024, 10)), ("bf16", 33, 20, (640, 1024, 10)), ("bf16", 8, 65, (640, 1020, 10)), ("bf16", 9, 65, (640, 1020, 10)),
-    ("bf16", 16, 64, (512, 1024, 10)), ("bf16", 17, 64, (512, 1024, 10)), ("bf16", 8, 128, (384, 1024, 10)), ("bf16", 9, 128, (384, 1024, 10)),
-])
-def test_gradient_of_long_contractions(ora, dtype, M, batch, dims):
+@pytest.mark.parametrize("dtype,M,batch,dims,kernel", FORWARD)
+def test_gradient_of_long_contractions(ora, dtype, M, batch, dims, kernel):
+    """The forward kernels for few blocks in every form, and either side of the lines to the others."""
     test_gradient_of_odd_layers(ora, dtype, M, batch, dims)
 
 
-@pytest.mark.parametrize("dtype,M,batch,dims", [
-    # errors of layers in few blocks: whole steps of sixteen (bfloat16 32) outputs, one more, fewer than a step; rows of W that start anywhere
-    ("f32", 2, 31, (20, 33, 160, 10)), ("f32", 3, 33, (20, 65, 129, 10)), ("f32", 2, 64, (21, 31, 34, 10)), ("f32", 2, 20, (20, 40, 7, 33, 10)),
-    ("f32", 2, 100, (20, 36, 656, 10)), ("f32", 2, 128, (21, 35, 643, 10)), ("f32", 2, 150, (21, 35, 643, 10)), ("f32", 3, 65, (21, 35, 70, 10)),
-    ("bf16", 2, 31, (20, 33, 160, 10)), ("bf16", 3, 33, (20, 65, 129, 10)), ("bf16", 2, 64, (21, 31, 34, 10)), ("bf16", 2, 20, (20, 40, 7, 33, 10)),
-    # aligned layers over general and aligned ones: fewer steps than waves and more, one, two and four row tiles
-    ("bf16", 2, 32, (60, 128, 128, 10)), ("bf16", 2, 64, (128, 256, 384, 10)), ("bf16", 3, 96, (100, 128, 512, 10)), ("bf16", 2, 128, (128, 128, 128, 40)),
-    ("bf16", 2, 64, (100, 100, 128, 128, 10)),
-    # the most blocks that it takes, and one worker more
-    ("f32", 48, 20, (20, 1000, 30, 10)), ("f32", 49, 20, (20, 1000, 30, 10)), ("f32", 64, 40, (20, 128, 40, 10)), ("f32", 65, 40, (20, 128, 40, 10)),
-    ("bf16", 64, 40, (20, 128, 40, 10)), ("bf16", 65, 40, (20, 128, 40, 10)), ("bf16", 48, 32, (20, 1024, 128, 10)), ("bf16", 49, 32, (20, 1024, 128, 10)),
-    ("bf16", 24, 96, (20, 1024, 128, 10)), ("bf16", 25, 96, (20, 1024, 128, 10)),
-])
-def test_errors_of_few_blocks(ora, dtype, M, batch, dims):
+@pytest.mark.parametrize("dtype,M,batch,dims,kernel", ERRORS)
+def test_errors_of_few_blocks(ora, dtype, M, batch, dims, kernel):
+    """Their error kernels."""
     test_gradient_of_odd_layers(ora, dtype, M, batch, dims)
 
 
-@pytest.mark.parametrize("few,many,batch,dims", [
-    # aligned layers, forward and error: one, two, three and four row tiles, fewer steps than a chunk, a start of the contraction of every kind
-    (3, 70, 32, (128, 1024, 256, 10)), (5, 52, 64, (384, 1024, 128, 10)), (4, 30, 96, (256, 1024, 384, 10)), (9, 30, 128, (1280, 1024, 128, 40)),
-    # a general layer below and above; the last layer's own kernel
-    (3, 70, 32, (60, 1024, 128, 100, 10)), (3, 30, 96, (100, 128, 1024, 10)),
-    # layers of any width in one chain: whole steps and what is behind them, rows and columns that fill no block
-    (16, 18, 100, (784, 500, 10)), (16, 18, 65, (649, 497, 10)), (32, 34, 60, (672, 500, 10)), (32, 34, 33, (641, 511, 10)),
-])
-def test_few_blocks_bit_for_bit(few, many, batch, dims):
+@pytest.mark.parametrize("few,many,batch,dims,among_few,among_many,sums", SAME_BITS)
+def test_few_blocks_bit_for_bit(few, many, batch, dims, among_few, among_many, sums):
     """bfloat16 layers in few blocks have kernels of their own, which add in the order of those for many: a worker's gradient is the same among few
-    workers and among many."""
+    workers and among many.  sums: the first layer's bias gradient, too."""
     runs = []
     for M in (few, many):
         w = workload("cfg5", M=M, batch=batch, n_per_worker=batch + 7, dims=dims)
         gpu = make_gpu(w, inputs_of(w))
         for it in (0, 3):
             gpu.local_step(it)
-        runs.append([gpu.hidden(l)[:few].cpu().numpy() for l in range(1, len(dims) - 1)] + [gpu.get("g")[:few].cpu().numpy()])
+        g = gpu.get("g")[:few].cpu().numpy()
+        if not sums:
+            g[:, dims[0] * dims[1]:(dims[0] + 1) * dims[1]] = 0
+        runs.append([gpu.hidden(l)[:few].cpu().numpy() for l in range(1, len(dims) - 1)] + [g])
         gpu.close()
     for a, b in zip(*runs):
         assert np.array_equal(a, b)
@@ -263,6 +239,8 @@ def test_weight_gradients_of_every_width(ora, dtype, M, batch, dims):
     # and one block less than the lines between them (in blocks of 32 x 64: 512 and 641, 1025; 256 of 128 x 64)
     ("f32", 114, 20, (149, 515, 10)), ("f32", 35, 50, (130, 515, 10)), ("f32", 28, 128, (130, 515, 10)), ("bf16", 28, 50, (131, 515, 10)),
     ("bf16", 28, 128, (129, 515, 10)), ("bf16", 29, 128, (129, 515, 10)),
+    # more workers than 32-bit offsets reach over
+    ("f32", 2049, 3, (3, 36, 3)), ("bf16", 2049, 3, (3, 36, 3)),
 ])
 def test_activations_of_the_larger_forms(dtype, M, batch, dims):
     """Every activation of the first layer against float64 with the same operands."""

@@ -6,6 +6,7 @@ import subprocess
 import pytest
 
 from paper_2009_05766_amd.build import LIB, build
+from kernel_cases import ERRORS, FORWARD, RUNS, SAME_BITS
 from whole_iteration_cases import GROUPS_OF_UNITS, ONE_WORKGROUP, RESIDENT, SLICED, SLICES, SMALL
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -118,3 +119,31 @@ def test_update_in_matrix_core_weight_gradients(routes, M, batch, dims, inside):
 def test_update_in_the_last_iteration(routes, M, batch, dims, inside):
     run = [kernel for _, kernel in routes(dims, M, batch, 1, bf16=1)[1]]
     assert ("wgrad_mix_mfma_kernel" in run) == inside and ("mix_kernel" in run) != inside
+
+
+def _local_step(routes, operands, M, batch, dims):
+    """Kernels of a gradient, with their template arguments."""
+    return ["%s<%s>" % launch[1:3] for launch in routes.forms(dims, M, batch, 1, bf16=operands == "bf16")[0]]
+
+
+def test_layer_cases_reach_their_kernel(routes):
+    for operands, M, batch, dims, kernel in FORWARD:
+        assert next(k for k in _local_step(routes, operands, M, batch, dims) if "fwd" in k) == kernel, (operands, M, batch, dims)
+    for operands, M, batch, dims, kernel in ERRORS:                  # from the last layer down: the second layer's comes last
+        assert [k for k in _local_step(routes, operands, M, batch, dims) if "dgrad" in k][-1] == kernel, (operands, M, batch, dims)
+    reached = {c[-1] for c in FORWARD + ERRORS}
+    assert len([k for k in reached if "wave_fwd" in k]) == 16 and len([k for k in reached if "chain_fwd" in k]) == 5
+    assert len([k for k in reached if "wave_dgrad" in k]) == 12 and len([k for k in reached if "chain_dgrad" in k]) == 13
+
+
+def test_few_and_many_workers_differ_in_these_kernels(routes):
+    for few, many, batch, dims, among_few, among_many, _ in SAME_BITS:
+        pairs = list(zip(*(_local_step(routes, "bf16", M, batch, dims) for M in (few, many))))
+        assert [" ".join(k) for k in zip(*(p for p in pairs if p[0] != p[1]))] == [among_few, among_many], (few, many, batch, dims)
+
+
+@pytest.mark.parametrize("M,batch,dims,followed,last", RUNS)
+def test_runs_reach_the_update_in_weight_gradients(routes, M, batch, dims, followed, last):
+    run = [kernel for _, kernel in routes(dims, M, batch, 2, bf16=1)[1]]
+    half = (len(run) + 1) // 2 if followed == last else run.index("mix_subset_kernel" if followed else "mix_kernel") + 1
+    assert ("wgrad_mix_mfma_kernel" in run[:half]) == followed and ("wgrad_mix_mfma_kernel" in run[half:]) == last
