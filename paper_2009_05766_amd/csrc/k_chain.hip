@@ -407,7 +407,7 @@ void launch_chain_fwd(hipStream_t s, const MlpPlan &p, int l, const float *X, bo
         hipLaunchKernelGGL(kernel, tile_grid(grouped_grid(a.M, n)), dim3(CH_THREADS), 0, s, a);
     };
     const bool tail = a.din % CH_STEP != 0;
-    if (a.B <= 32) { if (tail) go(chain_fwd_kernel<1, true>, 1); else go(chain_fwd_kernel<1, false>, 1); }
+    if (a.B <= 32) go(chain_fwd_kernel<1, false>, 1);                 // chain_fwd_pays(): aligned layers only
     else if (a.B <= 64) { if (tail) go(chain_fwd_kernel<2, true>, 2); else go(chain_fwd_kernel<2, false>, 2); }
     else { if (tail) go(chain_fwd_kernel<4, true>, 4); else go(chain_fwd_kernel<4, false>, 4); }
 }
@@ -451,9 +451,11 @@ void launch_chain_dgrad(hipStream_t s, const MlpPlan &p, int l, const float *X, 
     }
     auto rows = [&](auto rt) {
         constexpr int RT = decltype(rt)::value;
-        if (v && tail) go(chain_dgrad_kernel<false, RT, true, true>);
-        else if (v) go(chain_dgrad_kernel<false, RT, true, false>);
-        else if (tail) go(chain_dgrad_kernel<false, RT, false, true>);
+        if constexpr (RT < 4) {                                       // chain_dgrad_pays(): larger batches on other rows only
+            if (v && tail) return go(chain_dgrad_kernel<false, RT, true, true>);
+            if (v) return go(chain_dgrad_kernel<false, RT, true, false>);
+        }
+        if (tail) go(chain_dgrad_kernel<false, RT, false, true>);
         else go(chain_dgrad_kernel<false, RT, false, false>);
     };
     if (a.B <= 32) rows(std::integral_constant<int, 1>{});
