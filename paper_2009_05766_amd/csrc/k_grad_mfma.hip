@@ -1127,8 +1127,8 @@ static WgradWalk wgrad_walk(int M, int B, int64_t din, int64_t dout)
 // us, four iterations, separate and in the gradients, saved bytes a parameter of the model: batch 128, 127 workers 384-128-128-10 433 and 462 (-7.8), 384-384-10 570
 // and 605 (-4.1), 640-640-10 1355 and 1238 (0), 1152-384-10 1398 and 1217 (1.4); 64 workers 3000-1000-128-128-10 4820 and 5068 (-2.3), 2000-512-512-10 2215 and
 // 2254 (-0.8), 200-1024-1024-10 2482 and 2326 (3.8); 8 workers 640-640-10 256 and 237 (7.3); batch 64, 64 workers 640-128-10 244 and 236 (-0.2).
-// One iteration, which keeps g: batch 128, 127 workers 384-384-10 151 and 168 (-6.7), 48 workers 784-384-384-10 213 and 222 (-3.6), 128 workers 3072-1024-1024-10 2824 and
-// 2804 (2.5), 1024-1024-10 746 and 715 (2.5); batch 96, 122 workers 640-640-10 307 and 328 (-2.5); batch 64, 64 workers 512-384-128-10 135 and 139 (-0.9), 96
+// One iteration, which keeps g: batch 128, 127 workers 384-384-10 151 and 168 (-6.7), 48 workers 784-384-384-10 213 and 222 (-3.6), 127 workers 1024-1024-10
+// 787 and 712 (2.5); batch 96, 122 workers 640-640-10 307 and 328 (-2.5); batch 64, 64 workers 512-384-128-10 135 and 139 (-0.9), 96
 // workers 3072-512-512-10 935 and 839 (0.5); batch 32, 128 workers 1024-1024-10 692 and 633 (2.9).
 double wgrad_mix_saves(const MlpPlan &p, bool keep_g)
 {

@@ -214,14 +214,17 @@ int64_t update_end(const MlpPlan &p, int l)
     return p.woff[l] + p.dims[l] * p.dims[l + 1];
 }
 
-// Iterations that keep g.  From 192 workers on, two rounds of the 96 that an XCD holds of a block at a time, much of the peers' columns comes from memory and neither
-// form is ahead: us with the separate mix and in the weight gradients, batch 128, 300 workers 3072-1024-1024-10 6650 and 7090, 200 workers 896-768-10 796 and
-// 850, 1024-1024-10 1184 and 1109, batch 64, 256 workers 1421 and 1466; 160 workers 3072-1024-1024-10 3572 and 3440, 1024-1024-10 919 and 886.
+// Iterations that keep g.  An XCD holds 96 workers of a block at a time; beyond, a good part of the peers' columns comes from memory, the more the further the workers drift
+// apart along their walks, and the time depends on where the buffers lie: 128 workers 3072-1024-1024-10, batch 128, 2804 to 2946 us with the update in the weight
+// gradients and 2824 to 2862 with the separate mix, 112 workers 2371 to 2594 and 2487.  So from 128 workers on only walks of one strip (batches of up to 64) that save
+// a byte a parameter: batch 32, 128 workers 3072-1024-1024-10 2425 to 2560 and 2676, 1024-1024-10 633 to 650 and 692, 160 workers 776 to 834 and 866.  From two
+// rounds of 96 on none: 300 workers 3072-1024-1024-10, batch 128 7090 and 6650, 256 workers 1024-1024-10, batch 64 1466 and 1421, batch 32 1359 and 1360.
 bool update_beside_g(const MlpPlan &p)
 {
     bool any = false;
     for (int l = 0; l < p.n_layers; ++l) any |= mfma_layer_ok(p, l) && update_end(p, l) > 0;
-    return !any || (p.M < 192 && wgrad_mix_saves(p, true) >= UPDATE_MIN_SAVED_G);
+    if (!any) return true;
+    return p.M < 128 ? wgrad_mix_saves(p, true) >= UPDATE_MIN_SAVED_G : p.M < 192 && p.B <= 64 && wgrad_mix_saves(p, true) >= 1.0;
 }
 
 // One fp32 hidden layer on the kernels of k_grad_f32.hip, or none: forward, the last layer's two kernels, weight gradient with the
