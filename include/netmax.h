@@ -171,9 +171,11 @@ int netmax_mix(netmax_ctx *ctx, uint64_t iter, const int32_t *peers_dev);
  * replayed (the iteration number then lives in a device cell that the graph advances), which removes the launch
  * overhead that dominates small models; this needs a context created on a non-default stream (the null stream
  * cannot be captured), else NETMAX_ESTATE.  Softmax regression that the last-layer kernels take, on either operand type, and
- * perceptrons on float operands apply the update in the kernels that compute their gradient (which is still written to g): the
+ * perceptrons on float operands apply the update in the kernels that compute their gradient (which the last iteration still writes to g): the
  * latter in every weight matrix whose rows start at multiples of 16 bytes, models of fewer than 1.8 million parameters in all
- * in the first one only, where that saves a launch, or in none.  The graphs are dropped when buffers, data or the learning rate change.
+ * in the first one only, where that saves a launch, or in none.  So do perceptrons on bfloat16 operands, from 1.8 million parameters in all on, in the
+ * weight matrices that netmax_set_fusion is about, where that moves fewer bytes; an iteration that has to leave g, the last one of a call and every replayed one,
+ * less often than the others.  The graphs are dropped when buffers, data or the learning rate change.
  * Results are identical to the individual calls.
  * Small softmax-regression models (one layer, float features, at most 32 classes, parameters and batch within a
  * workgroup's LDS) run whole iterations inside ONE kernel, one workgroup per worker: without use_graph eight iterations and more
@@ -228,7 +230,9 @@ int netmax_set_barrier_patience(netmax_ctx *ctx, int64_t polls);
  * worker's row of g receives its gradient (only that worker's gradient is computed).  Steps that cannot see each other (no row
  * that one of them writes is read or written by another) run as one batch of launches of up to 32 steps, each step behind the
  * earlier ones it depends on; the host finds these groups by repeating the draws, which
- * are integer work on the same tables.  The result is that of the strictly sequential schedule.
+ * are integer work on the same tables.  The result is that of the strictly sequential schedule up to the order of sums: forward
+ * passes of wide layers and column sums of large batches go by the number of steps that run as one, so that last bits may depend on how the
+ * steps are cut into calls (the errors of hidden layers do not).
  * Needs netmax_bind_state, netmax_set_activity and, for perceptron models, netmax_bind_data (else NETMAX_ESTATE).
  * Returns after enqueueing. */
 int netmax_activity(int32_t M, const double *t_host, const double *P_host, const uint8_t *adj, double *p_act_out);

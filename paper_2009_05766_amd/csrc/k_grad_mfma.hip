@@ -686,7 +686,8 @@ __global__ void __launch_bounds__(MF_THREADS) __attribute__((amdgpu_waves_per_eu
     const size_t a_step = GATHERED ? WM_ROWS : (size_t)WM_ROWS * p.B;
     // A strip of data rows is half of their 128-byte lines: two strips are asked for together (walks of more than one strip have an
     // even number of them), the second one stays in registers.  us per iteration of 3072-1024-1024-10, batch 128, each strip for itself
-    // and two together: 48 workers 907 and 886, 64 workers 1246 and 1210, 128 workers 2449 and 2395.
+    // and two together: calls of eight iterations, 48 workers 907 and 891, of four, 128 workers 2435 and 2392; calls of one, 48 workers 900 and 892, 64 workers 1226 and
+    // 1231, 128 workers 2469 and 2410.
     u32x4 ra[AN], rs[GATHERED ? AN : 1];
     const bool pairs = GATHERED && p.walk > 1;
     auto fetch_a = [&](unsigned k) {

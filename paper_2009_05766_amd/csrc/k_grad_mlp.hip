@@ -195,7 +195,7 @@ bias_grad_kernel(int M, int B, int64_t dout, const float *__restrict__ dz, int64
 // 45.0 and 39.6 us; every layer for itself lengthens the chain (300-60-60-60-10, 8 workers 64.7 and 66.5 us).
 // Where it loses: rows of W that do not start at multiples of 16 bytes (3001-999-10: 1118 and 1519 us); bfloat16 operands, whose
 // products leave little to hide (784-500-300-10, 16 workers 106 and 113 us, 3000-1000-10, 128 workers 2354 and 2644 us).  The
-// matrix-core layers have a kernel in the mix's order for it: batch 128, 3072-1024-1024-10, 48 workers 1159 and 1070 us, 128 workers,
+// matrix-core layers have a kernel in the mix's order for it, which they take where it saves bytes (wgrad_mix_saves()): batch 128, 3072-1024-1024-10, 48 workers 1159 and 1070 us, 128 workers,
 // two iterations 5668 and 5259 us (the first need not write g); batch 64, 1024-1024-10, 32 workers 2 x 221 and
 // 2 x 181 us, 512-512-256-10, 16 workers 2 x 88 and 2 x 81 us, 1024-512-10, 4 workers (2.1 M floats) 2 x 68 and 2 x 63 us, but
 // 512-128-128-10, 2 workers 4 x 57.5 and 4 x 60 us.

@@ -163,7 +163,7 @@ struct MlpPlan {
 struct TailArgs { MixArgs mix; const int32_t *tiles; int n_tiles; MixSkip skip; };
 // fuse != nullptr: layers accepted by mfma_layer_ok() do not write their weight gradient to G; they write
 // x' and v' of their weight columns (Eq. (c0)/(c1)) straight from the product.
-// tail != nullptr (not together with fuse): the weight gradients of the layers whose update_end() is not 0 write G and apply the
+// tail != nullptr (not together with fuse): the weight gradients of the layers whose update_end() is not 0 write G (mix.keep_g) and apply the
 // update to the columns woff .. update_end() - 1 (multiples of four) while they hold them.  The others are updated by the first
 // layer's weight gradient where it can (it is the last launch then), else by the caller: false is returned in that case.
 // With a list: X, G and the update in place (mix.Xnext = mix.Xcur); no listed worker is another's peer.

@@ -61,7 +61,7 @@ struct netmax_ctx {
     int n_fuse_tiles = 0;
     MixSkip fuse_skip{};
     // perceptrons with weight gradients that apply the update to their columns inside netmax_run (the gradient is still
-    // written): the tiles the separate mix covers then (none for softmax regression)
+    // written in the last iteration of a call): the tiles the separate mix covers then (none for softmax regression)
     bool tail = false, tail_keeps = false;    // tail_keeps: in iterations that leave g, too
     int32_t *d_tail_tiles = nullptr;
     int n_tail_tiles = 0;

@@ -108,7 +108,7 @@ SAME_BITS = [
 # netmax_run of bfloat16 networks with matrix-core layers: (workers, batch, dims, whether their weight gradients update their columns in an iteration that
 # another follows, and in one that leaves g)
 RUNS = [
-    # two million floats, from which on they may: either side; one strip of 32 rows a walk
+    # 1.8 million floats, from which on they may: either side; one strip of 32 rows a walk
     (6, 32, (512, 512, 128, 10), True, True), (5, 32, (512, 512, 128, 10), False, False), (14, 64, (130, 256, 384, 10), True, True), (9, 64, (1024, 512), True, True),
     # walks of one strip, of two, four and eight, whole and with four left over, from the first strip and from a later one, of the first layer and of another
     (20, 128, (512, 512, 384, 10), True, False), (48, 128, (1024, 1024, 10), True, True), (64, 128, (1024, 1024, 10), True, True), (7, 128, (2944, 1024, 10), True, True),
