@@ -8,6 +8,7 @@
 //   A operand: 8 values A[row = l % 32][k = 8 (l / 32) + 0..7]
 //   B operand: 8 values B[k = 8 (l / 32) + 0..7][col = l % 32]
 //   D:        16 values D[row = 4 (l / 32) + v % 4 + 8 (v / 4)][col = l % 32], v = 0..15
+#include <algorithm>
 #include "bf16.h"
 #include "kernels.h"
 #include "layout.h"
@@ -799,21 +800,25 @@ __global__ void __launch_bounds__(MF_THREADS) __attribute__((amdgpu_waves_per_eu
 // (a lane per row asks for 64 lines an instruction), and turns them to the matrix instruction's layout in LDS of its own.  The logits
 // stay in LDS for the softmax, whose chain of loads from memory was the other half.  us, before, with the pieces, and with both:
 // 1024-10, batch 128, 48 workers 26.5, 22.9, 18.7; 2048-10, 4 workers 33.6, 25.7, 23.0; 128-30, batch 96, 8 workers 22.1, 21.7, 12.2; 640-10,
-// batch 32, 61 workers 16.7, 16.2, 14.2.
+// batch 32, 61 workers 16.7, 16.2, 14.2.  From 256 workers on, what counts as well is how many workgroups a compute unit holds: W^T has rows of the real classes only,
+// pieces of the real batch.  us, before, with 32 rows and 128, now: 1024-2, batch 128, 520 workers 49, 55, 39; 128-4, batch 32, 700 workers 11.6, 19.2, 10.9; 2048-10, batch
+// 128, 4 workers 32, 23, 19.9, 48 workers 33.6, 24, 20.9.
 struct FwdSmallArgs {
     const uint16_t *a_prev; const float *X; int64_t woff; int M, B; int64_t din, dout; float *out;
     SoftmaxArgs sm;                  // what follows the logits in the same workgroup
 };
 constexpr int SMALL_MAX_DIN = 2048;
-// W^T and the waves' pieces; then the logits
-static_assert(2 * (32 * (128 + 8) + MF_THREADS / 64 * 32 * (64 + 8)) >= 4 * 128 * SOFTMAX_PITCH, "the logits of the largest batch fit the space of the smallest layer");
-constexpr int FS_KS = 64, FS_PITCH = FS_KS + 8, FS_DEPTH = 4;           // features of a piece, elements of its rows in LDS, pieces ahead
-static size_t fwd_small_lds(int64_t din) { return sizeof(uint16_t) * (32 * (size_t)(din + 8) + MF_THREADS / 64 * 32 * FS_PITCH); }
+constexpr int FS_KS = 64, FS_PITCH = FS_KS + 8;                         // features of a piece, elements of its rows in LDS
+// LDS: W^T and the pieces of the batch's waves; then the logits
+constexpr size_t fwd_small_lds(int64_t din, int64_t dout, int B) { return sizeof(uint16_t) * (size_t)(dout * (din + 8) + (int64_t)B * FS_PITCH); }
+static_assert(sizeof(uint16_t) * FS_PITCH >= sizeof(float) * SOFTMAX_PITCH, "the logits fit the space of the pieces");
 
-__global__ void __launch_bounds__(MF_THREADS) fwd_small_mfma_kernel(FwdSmallArgs p)
+// FS_DEPTH pieces ahead; WAVES workgroups fit the registers of a compute unit.
+template <int FS_DEPTH, int WAVES>
+__global__ void __launch_bounds__(MF_THREADS, WAVES) fwd_small_mfma_kernel(FwdSmallArgs p)
 {
-    extern __shared__ __attribute__((aligned(16))) uint16_t Wt[];      // [32][din + 8]
-    const int g = blockIdx.x, t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    extern __shared__ __attribute__((aligned(16))) uint16_t Wt[];      // [dout][din + 8]
+    const int g = blockIdx.x, t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int din = (int)p.din, dout = (int)p.dout, pitch = din + 8;
     static_assert(MF_THREADS / 64 * 32 >= 128, "a wave for every 32 rows of the largest batch");
     const int m0 = 32 * wave, pieces = din / FS_KS;                    // din is a multiple of 128: at least two pieces
@@ -826,10 +831,10 @@ __global__ void __launch_bounds__(MF_THREADS) fwd_small_mfma_kernel(FwdSmallArgs
 #pragma unroll
         for (int u = 0; u < 4; ++u) ra[d][u] = *reinterpret_cast<const u32x4 *>(src + (size_t)(8 * u) * p.din);
     };
+    if (mine) {
 #pragma unroll
-    for (int d = 0; d < FS_DEPTH; ++d) request(d, d);
-    // rows dout .. 31 of Wt are the zero padding of the class dimension
-    for (int e = t + dout * pitch / 2; e < 32 * pitch / 2; e += MF_THREADS) reinterpret_cast<uint32_t *>(Wt)[e] = 0u;
+        for (int d = 0; d < FS_DEPTH; ++d) request(d, d);
+    }
     // W[k][n] -> Wt[n][k]: the din x dout block is contiguous in the parameter row and starts at a multiple of four
     // columns, so it is read as float4 (a float4 never straddles a layout tile)
     {
@@ -863,8 +868,8 @@ __global__ void __launch_bounds__(MF_THREADS) fwd_small_mfma_kernel(FwdSmallArgs
     const int col = lane & 31;
     const float bcol = p.X[tiled_offset(p.M, g, p.woff + (int64_t)din * dout + (col < dout ? col : dout - 1))];
     if (mine) {
-        uint16_t *own = Wt + 32 * pitch + wave * 32 * FS_PITCH, *to = own + (lane >> 3) * FS_PITCH + 8 * (lane & 7);
-        const uint16_t *a_ptr = own + (lane & 31) * FS_PITCH + 8 * (lane >> 5), *b_ptr = Wt + (lane & 31) * pitch + 8 * (lane >> 5);
+        uint16_t *own = Wt + dout * pitch + wave * 32 * FS_PITCH, *to = own + (lane >> 3) * FS_PITCH + 8 * (lane & 7);
+        const uint16_t *a_ptr = own + (lane & 31) * FS_PITCH + 8 * (lane >> 5), *b_ptr = Wt + (col < dout ? col : dout - 1) * pitch + 8 * (lane >> 5);      // columns past the last class repeat it
         auto consume = [&](int d, int k) {
 #pragma unroll
             for (int u = 0; u < 4; ++u) *reinterpret_cast<u32x4 *>(to + 8 * u * FS_PITCH) = ra[d][u];
@@ -899,7 +904,7 @@ __global__ void __launch_bounds__(MF_THREADS) fwd_small_mfma_kernel(FwdSmallArgs
         }
     }
     __syncthreads();
-    softmax_xent_block<32>(p.sm, g, label, rows);
+    softmax_xent_block<32, MF_THREADS>(p.sm, g, label, rows);
 }
 
 // dW = A^T dZ with dout <= 32: one workgroup = one worker x 128 rows of W, one 32-row tile per wave;
@@ -1031,8 +1036,9 @@ void prepare_kernels()
 {
 
     // fwd_small_mfma_kernel keeps W^T in more than the default 64 KB of dynamic LDS
-    (void)hipFuncSetAttribute(reinterpret_cast<const void *>(fwd_small_mfma_kernel),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)fwd_small_lds(SMALL_MAX_DIN));
+    const int lds = (int)fwd_small_lds(SMALL_MAX_DIN, 32, 128);
+    (void)hipFuncSetAttribute(reinterpret_cast<const void *>(fwd_small_mfma_kernel<4, 3>), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    (void)hipFuncSetAttribute(reinterpret_cast<const void *>(fwd_small_mfma_kernel<2, 4>), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
 }
 
 // Outputs of the backward-data kernel of layer l: the error of layer l - 1 and that layer's bias gradient.
@@ -1051,7 +1057,17 @@ void launch_fwd_small(hipStream_t s, const MlpPlan &p, const float *X, float *G)
     a.a_prev = p.hb[l]; a.X = X; a.woff = p.woff[l]; a.M = p.M; a.B = p.B; a.din = p.dims[l]; a.dout = p.dims[l + 1];
     a.out = p.act[l + 1];
     a.sm = softmax_args(p, G);
-    hipLaunchKernelGGL(fwd_small_mfma_kernel, dim3(p.M), dim3(MF_THREADS), fwd_small_lds(a.din), s, a);
+    const dim3 grid(p.M), block(MF_THREADS);
+    const size_t lds = fwd_small_lds(a.din, a.dout, a.B), fit = (160 << 10) / (lds + MF_THREADS * sizeof(float));
+    // Four pieces ahead, where two and the fourth workgroup on a compute unit don't save a round of them.  us, four and two, batch 32: 700 workers 128-10 11.2 and 11.3, 1024-2
+    // 18.8 and 19.8, 820 workers (a round of two) 18.4 and 12.3, 28.1 and 21.1, 1366 workers (two rounds) 21.3 and 20.8, 35.4 and 38.6, 2500
+    // workers (three of four) 36.8 and 30.9, 62.7 and 60.1.
+    auto rounds = [&](size_t most) {
+        const size_t at_once = MF_XCD * XCD_CUS * std::min(fit, most);
+        return (p.M + at_once - 1) / at_once;
+    };
+    if (rounds(4) < rounds(3)) hipLaunchKernelGGL((fwd_small_mfma_kernel<2, 4>), grid, block, lds, s, a);
+    else hipLaunchKernelGGL((fwd_small_mfma_kernel<4, 3>), grid, block, lds, s, a);
 }
 
 void launch_wgrad_small(hipStream_t s, const MlpPlan &p, float *G, int cur)

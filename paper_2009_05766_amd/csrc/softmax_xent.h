@@ -39,14 +39,14 @@ __device__ __forceinline__ int softmax_label(const SoftmaxArgs &a, int g)
 // by the chain of loads otherwise, one for every class three times over and one for every row of a column's part.  With 8 workers
 // 256-128-30, batch 96, the last layer's forward pass took 22 us by way of memory.
 constexpr int SOFTMAX_PITCH = 33;
-template <int CLASSES = 0>
+template <int CLASSES = 0, int MOST_THREADS = 1024>
 __device__ __forceinline__ void softmax_xent_block(const SoftmaxArgs &a, int g, int y, float *rows = nullptr)
 {
     const int B = a.B, M = a.M;
     const int64_t C = a.C, boff = a.boff, D = a.D, ld = a.ld;
     const float *logits = a.logits;
     float *dz = a.dz; uint16_t *dz_bf16 = a.dz_bf16, *dz_bf16_t = a.dz_bf16_t; float *loss = a.loss, *G = a.G;
-    __shared__ float red[1024];
+    __shared__ float red[MOST_THREADS];
     const int b = threadIdx.x;
     float l = 0.0f;
     if (CLASSES > 0 && b < B) {
@@ -102,7 +102,7 @@ __device__ __forceinline__ void softmax_xent_block(const SoftmaxArgs &a, int g, 
     }
     red[b] = l;
     __syncthreads();                 // also: every row of dz is written
-    for (int stride = 512; stride > 0; stride >>= 1) {
+    for (int stride = MOST_THREADS / 2; stride > 0; stride >>= 1) {
         if (b < stride && b + stride < (int)blockDim.x) red[b] += red[b + stride];
         __syncthreads();
     }

@@ -105,6 +105,17 @@ SAME_BITS = [
      "tile_fwd_kernel<true,false,128,64,64,2,2> tile_dgrad_kernel<true,false,128,64,64,2,2>", False),
 ]
 
+# Last layer of the matrix-core path: (workers, batch, dims, its forward kernel).  fwd_small_mfma_kernel<pieces ahead, workgroups that fit a compute unit's registers>
+FEW_CLASSES = [
+    # two pieces of 64 features, one group of four and two left over, the most (32); one to four waves, classes on either side of the columns of a
+    # matrix instruction
+    (3, 32, (128, 128, 2), "fwd_small_mfma_kernel<4,3>"), (2, 64, (64, 384, 17), "fwd_small_mfma_kernel<4,3>"), (3, 96, (40, 128, 32), "fwd_small_mfma_kernel<4,3>"),
+    (2, 128, (128, 384, 31), "fwd_small_mfma_kernel<4,3>"), (2, 128, (36, 2048, 10), "fwd_small_mfma_kernel<4,3>"), (5, 32, (36, 2048, 32), "fwd_small_mfma_kernel<4,3>"),
+    # the most workers in a round of three workgroups a compute unit and one more; in rounds of three and four alike; what LDS leaves no room for
+    (768, 32, (36, 128, 3), "fwd_small_mfma_kernel<4,3>"), (769, 32, (36, 128, 3), "fwd_small_mfma_kernel<2,4>"), (800, 96, (36, 384, 2), "fwd_small_mfma_kernel<2,4>"),
+    (1025, 32, (36, 128, 3), "fwd_small_mfma_kernel<4,3>"), (769, 64, (36, 512, 32), "fwd_small_mfma_kernel<4,3>"),
+]
+
 # netmax_run of bfloat16 networks with matrix-core layers: (workers, batch, dims, whether their weight gradients update their columns in an iteration that
 # another follows, and in one that leaves g)
 RUNS = [

@@ -3,7 +3,7 @@ import numpy as np
 import pytest
 
 from harness import inputs_of, make_gpu, make_oracle, rel_err_rows
-from kernel_cases import ERRORS, FORWARD, SAME_BITS
+from kernel_cases import ERRORS, FEW_CLASSES, FORWARD, SAME_BITS
 from netmax_inputs import workload
 
 pytestmark = pytest.mark.gpu
@@ -47,12 +47,8 @@ def test_gradient_of_odd_layers(ora, dtype, M, batch, dims):
     gpu.close()
 
 
-@pytest.mark.parametrize("M,batch,dims", [
-    # the last layer on matrix cores: two pieces of 64 features, one group of four and two left over, the most (32); one to four waves, classes
-    # on either side of the padding
-    (3, 32, (128, 128, 2)), (2, 64, (64, 384, 17)), (3, 96, (40, 128, 32)), (2, 128, (128, 384, 31)), (2, 128, (36, 2048, 10)), (5, 32, (36, 2048, 32)),
-])
-def test_last_layer_of_few_classes(ora, M, batch, dims):
+@pytest.mark.parametrize("M,batch,dims,kernel", FEW_CLASSES)
+def test_last_layer_of_few_classes(ora, M, batch, dims, kernel):
     test_gradient_of_odd_layers(ora, "bf16", M, batch, dims)
 
 

@@ -6,7 +6,7 @@ import subprocess
 import pytest
 
 from paper_2009_05766_amd.build import LIB, build
-from kernel_cases import ERRORS, FORWARD, RUNS, SAME_BITS
+from kernel_cases import ERRORS, FEW_CLASSES, FORWARD, RUNS, SAME_BITS
 from whole_iteration_cases import GROUPS_OF_UNITS, ONE_WORKGROUP, RESIDENT, SLICED, SLICES, SMALL
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -131,6 +131,8 @@ def test_layer_cases_reach_their_kernel(routes):
         assert next(k for k in _local_step(routes, operands, M, batch, dims) if "fwd" in k) == kernel, (operands, M, batch, dims)
     for operands, M, batch, dims, kernel in ERRORS:                  # from the last layer down: the second layer's comes last
         assert [k for k in _local_step(routes, operands, M, batch, dims) if "dgrad" in k][-1] == kernel, (operands, M, batch, dims)
+    for M, batch, dims, kernel in FEW_CLASSES:
+        assert [k for k in _local_step(routes, "bf16", M, batch, dims) if "fwd_small" in k] == [kernel], (M, batch, dims)
     reached = {c[-1] for c in FORWARD + ERRORS}
     assert len([k for k in reached if "wave_fwd" in k]) == 16 and len([k for k in reached if "chain_fwd" in k]) == 5
     assert len([k for k in reached if "wave_dgrad" in k]) == 12 and len([k for k in reached if "chain_dgrad" in k]) == 13
