@@ -1138,25 +1138,27 @@ static WgradWalk wgrad_walk(int M, int B, int64_t din, int64_t dout)
 }
 
 // The update inside the weight gradients of netmax_run, by the bytes a parameter that it saves: 24 with the separate mix (g written and read), against x, v, x' and v',
-// the operands as long as all workers' do not stay in an XCD's 4 MB of L2, and three quarters of the uneven share (XCDs that are done leave the others their part
-// of the memory); g beside x' and v' as 2.5.  Every parameter that is none of these layers' costs 2.25 more, in the mix of what is left, than in the mix of everything
+// the operands as long as all workers' do not stay in an XCD's 4 MB of L2, and most of the uneven share (XCDs that are done leave the others their part
+// of the memory).  Operands count half, as repeated reads of them mostly end in the last cache, but in full beside g, which counts as 2.  Both and the uneven
+// share count for less where x, v, x' and v' of all workers stay in the last cache themselves (18 M floats, 288 MB) and an XCD holds more workers than there
+// are (96).  Every parameter that is none of these layers' costs 2.25 more, in the mix of what is left, than in the mix of everything
 // (1.25 from 96 workers on).
-// us, four iterations, separate and in the gradients, saved bytes a parameter of the model: batch 128, 127 workers 384-128-128-10 433 and 462 (-7.8), 384-384-10 570
-// and 605 (-4.1), 640-640-10 1355 and 1238 (0), 1152-384-10 1398 and 1217 (1.4); 64 workers 3000-1000-128-128-10 4820 and 5068 (-2.3), 2000-512-512-10 2215 and
-// 2254 (-0.8), 200-1024-1024-10 2482 and 2326 (3.8); 8 workers 640-640-10 256 and 237 (7.3); batch 64, 64 workers 640-128-10 244 and 236 (-0.2).
-// One iteration, which keeps g: batch 128, 127 workers 384-384-10 151 and 168 (-6.7), 48 workers 784-384-384-10 213 and 222 (-3.6), 127 workers 1024-1024-10
-// 787 and 712 (2.5); batch 96, 122 workers 640-640-10 307 and 328 (-2.5); batch 64, 64 workers 512-384-128-10 135 and 139 (-0.9), 96
-// workers 3072-512-512-10 935 and 839 (0.5); batch 32, 128 workers 1024-1024-10 692 and 633 (2.9).
+// us, four iterations, separate and in the gradients, saved bytes a parameter of the model: batch 128, 64 workers 3000-1000-128-128-10 4820 and 5068 (-2.3), 200-1024-1024-10
+// 2482 and 2326 (5.0); 18 workers 128-1408-17 344 and 301 (4.5), 10 workers 128-2048-4 347 and 276 (5.6), 27 workers 128-1280-6 340 and 305 (5.5).
+// One iteration, which keeps g: batch 128, 127 workers 384-384-10 151 and 168 (-6.4), 48 workers 784-384-384-10 205 and 211 (-3.7), 127 workers 1024-1024-10
+// 787 and 712 (3.0), 10 workers 128-2048-4 90 and 68 (1.8), 27 workers 128-1280-6 89 and 79 (1.8); batch 96, 122 workers 640-640-10 307 and 328 (-2.4); batch 64, 96
+// workers 3072-512-512-10 935 and 839 (1.0); batch 32, 128 workers 1024-1024-10 692 and 633 (3.4).
 double wgrad_mix_saves(const MlpPlan &p, bool keep_g)
 {
-    const double rest = p.M >= 96 ? 1.25 : 2.25;
+    const double rest = p.M >= 96 ? 1.25 : 2.25, memory = std::min(1.0, std::max({0.4, (double)p.M * (double)p.ld / 18e6, p.M / 96.0}));
     double saved = -rest * (double)p.ld;
     for (int l = 0; l < p.n_layers; ++l) {
         if (!mfma_layer_ok(p, l)) continue;
         const int64_t din = p.dims[l], dout = p.dims[l + 1];
         const WgradWalk w = wgrad_walk(p.M, p.B, din, dout);
         const bool in_l2 = p.M * (din + dout) * p.B * 2 <= (int64_t)7 << 19;
-        saved += (double)(din * dout) * (24.0 + rest - (16.0 + (keep_g ? 2.5 : 0.0) + (in_l2 ? 0.0 : w.operands)) * (1.0 + 0.75 * (w.uneven - 1.0)));
+        const double moved = 16.0 + (keep_g ? 2.0 : 0.0) + (in_l2 ? 0.0 : memory * (keep_g ? 1.0 : 0.5) * w.operands);
+        saved += (double)(din * dout) * (24.0 + rest - moved * (1.0 + 0.85 * memory * (w.uneven - 1.0)));
     }
     return saved / (double)p.ld;
 }

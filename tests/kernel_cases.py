@@ -122,7 +122,7 @@ RUNS = [
     # 1.8 million floats, from which on they may: either side; one strip of 32 rows a walk
     (6, 32, (512, 512, 128, 10), True, True), (5, 32, (512, 512, 128, 10), False, False), (14, 64, (130, 256, 384, 10), True, True), (9, 64, (1024, 512), True, True),
     # walks of one strip, of two, four and eight, whole and with four left over, from the first strip and from a later one, of the first layer and of another
-    (20, 128, (512, 512, 384, 10), True, False), (48, 128, (1024, 1024, 10), True, True), (64, 128, (1024, 1024, 10), True, True), (7, 128, (2944, 1024, 10), True, True),
+    (20, 128, (512, 512, 384, 10), True, True), (48, 128, (640, 640, 10), True, False), (48, 128, (1024, 1024, 10), True, True), (64, 128, (1024, 1024, 10), True, True), (7, 128, (2944, 1024, 10), True, True),
     (7, 128, (128, 2944, 1024, 10), True, True), (64, 96, (1664, 1024, 128, 10), True, True), (128, 128, (128, 896, 640, 10), True, False),
     # blocks that are no whole rounds over the XCDs
     (40, 128, (1152, 384, 10), True, False),

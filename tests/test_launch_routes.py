@@ -100,7 +100,9 @@ def test_walks_of_the_fused_weight_gradient(routes, M, batch, widths, strips):
 
 @pytest.mark.parametrize("M,batch,dims,inside", [
     # few parameters in matrix-core layers; blocks that leave XCDs without work; walks of few strips; and where it pays
-    (64, 128, (3000, 1000, 128, 128, 10), False), (64, 128, (2000, 512, 512, 10), False), (127, 128, (384, 128, 128, 10), False), (48, 128, (384, 384, 10), False), (48, 128, (640, 640, 10), True),
+    (64, 128, (3000, 1000, 128, 128, 10), False), (64, 128, (2200, 384, 384, 10), False), (127, 128, (384, 128, 128, 10), False), (48, 128, (640, 640, 10), True),
+    # small states, whose operands and peers come from the last cache
+    (48, 128, (384, 384, 10), True), (18, 128, (128, 1536, 3), True), (41, 128, (128, 512, 23), True),
     (64, 128, (784, 384, 384, 10), False), (64, 128, (1000, 512, 512, 10), True), (64, 128, (200, 1024, 1024, 10), True), (48, 128, (3072, 1024, 1024, 10), True),
     (32, 64, (1024, 1024, 10), True), (64, 64, (640, 384, 10), True), (100, 32, (1152, 384, 10), True), (5, 32, (512, 512, 128, 10), False),
 ])
@@ -114,7 +116,7 @@ def test_update_in_matrix_core_weight_gradients(routes, M, batch, dims, inside):
 @pytest.mark.parametrize("M,batch,dims,inside", [
     # an iteration that leaves g: many workers, many more of them, blocks and operands that eat up what is saved
     (127, 128, (1024, 1024, 10), True), (128, 128, (3072, 1024, 1024, 10), False), (128, 64, (1024, 1024, 10), False), (191, 32, (512, 512, 256, 10), True), (192, 32, (512, 512, 256, 10), False),
-    (256, 64, (1024, 1024, 10), False), (127, 128, (384, 384, 10), False), (122, 96, (640, 640, 10), False), (64, 64, (512, 384, 128, 10), False), (96, 64, (3072, 512, 512, 10), True),
+    (256, 64, (1024, 1024, 10), False), (127, 128, (384, 384, 10), False), (122, 96, (640, 640, 10), False), (64, 64, (512, 384, 128, 10), True), (14, 128, (256, 256, 896, 16), True), (48, 128, (784, 384, 384, 10), False), (96, 64, (3072, 512, 512, 10), True),
 ])
 def test_update_in_the_last_iteration(routes, M, batch, dims, inside):
     run = [kernel for _, kernel in routes(dims, M, batch, 1, bf16=1)[1]]
