@@ -217,7 +217,7 @@ int64_t update_end(const MlpPlan &p, int l)
 // Iterations that keep g.  An XCD holds 96 workers of a block at a time; beyond, a good part of the peers' columns comes from memory, the more the further the workers drift
 // apart along their walks, and the time depends on where the buffers lie: 128 workers 3072-1024-1024-10, batch 128, 2804 to 2946 us with the update in the weight
 // gradients and 2824 to 2862 with the separate mix, 112 workers 2371 to 2594 and 2487.  So from 128 workers on only walks of one strip (batches of up to 64) that save
-// a byte a parameter: batch 32, 128 workers 3072-1024-1024-10 2425 to 2560 and 2676, 1024-1024-10 633 to 650 and 692, 160 workers 776 to 834 and 866.  From two
+// a byte and a half a parameter: batch 32, 128 workers 3072-1024-1024-10 2425 to 2560 and 2676, 1024-1024-10 633 to 650 and 692, 160 workers 776 to 834 and 866.  From two
 // rounds of 96 on none: 300 workers 3072-1024-1024-10, batch 128 7090 and 6650, 256 workers 1024-1024-10, batch 64 1466 and 1421, batch 32 1359 and 1360.
 bool update_beside_g(const MlpPlan &p)
 {
